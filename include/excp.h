@@ -307,7 +307,7 @@ int         excp_stage_ms(excp_ctx *ctx, int i, double *ms, int *launches);
  *   EXCP_PARAM_WIDE_ELEMS      (default 2^28): a group holding a tensor of at least this many elements
  *                              computes the per-bucket totals and initial centres of Sec. 3.3 with
  *                              sixteen waves and one workgroup per bucket.
- *   EXCP_PARAM_CAND_LIST_ELEMS (default 2^26): a tensor's median candidates (Sec. 3.2) are filed in
+ *   EXCP_PARAM_CAND_LIST_ELEMS (default 2^20): a tensor's median candidates (Sec. 3.2) are filed in
  *                              n / value lists (at least 1, at most 16), each with a counter of its own. */
 #define EXCP_PARAM_WIDE_ELEMS       1
 #define EXCP_PARAM_CAND_LIST_ELEMS  2

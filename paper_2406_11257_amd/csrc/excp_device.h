@@ -11,6 +11,7 @@
 #define EXCP_CHUNK       8192u     // survivors per chunk of the survivor passes
 #define EXCP_SUPER_CHUNKS 16u      // chunks per unit of the bucket counts (and of the scatter's workgroup ranges)
 #define EXCP_THREADS     256
+#define EXCP_STATS_PER_CU 8u       // workgroups per compute unit of the statistics pass
 #define EXCP_ABSM_BINS   40        // u64 accumulators, 8 binary exponents apart, for the exact sum of |m|
 #define EXCP_MAX_K       255
 #define EXCP_KM_CELLS    4096u     // cells of the value -> bucket map (2048 per sign)
@@ -32,11 +33,16 @@ struct TDesc {
     u64 elem_off;      // start of this tensor's survivor slots in the group workspace
     u64 cand_off;      // start and capacity of this tensor's median-candidate list
     u64 cand_cap;
-    u32 cand_lists;    // the candidate list of a very large tensor is cut into this many lists (1 .. 16), each with a
-    u32 pad0;          // counter of its own, so that thousands of waves do not queue at one address
+    u32 cand_lists;    // a tensor's candidate list is cut into this many lists (1 .. 16), each with a counter of its
+    u32 pad0;          // own, so that thousands of workgroups do not queue at one address
     u32 tile_begin;    // first tile of this tensor in the group's tile list
     u32 tile_count;
 };
+
+// What one workgroup of the statistics pass found out about a tensor: units of the exact sum of |m| (low and
+// high 32-bit halves added up), keys below the median's bracket, non-finite values, keys equal to a one-value
+// bracket, elements equal to the counted bracket values.
+struct StatPart { u64 L, H; u32 clt, nf, cc, pad, atom[4]; };
 
 // Device-written per-tensor state of a compress group.
 struct TState {
@@ -59,6 +65,7 @@ struct TState {
     // repeated are counted, not listed among the candidates
     u32 natoms, atom_key[4], atom_cnt[4];
     u32 pad2[2];
+    StatPart part;              // of a tensor whose tiles all belong to one workgroup of the statistics pass
 };
 
 // One survivor stream (3 per tensor: residual, m, v) during codebook construction.
@@ -141,6 +148,7 @@ struct Workspace {
     u32 *med_hist;            // [tensor][2048]
     u32 *cand;                // median candidates (keys inside the sample bracket), per tensor
     u32 *cand_ctr;            // [tensor][16][32] per list: [0] slots asked for, [1] end of the slots granted (128 B apart)
+    StatPart *stat_part;      // [workgroup of the statistics pass][2] records of the tensors its tile range starts and ends in
     // mask pass
     u64 *tile_status;         // per 2048-element sub-tile: survivors << 32 | moment survivors
     u64 *mask_prefix;         // exclusive scan of tile_status within each tensor

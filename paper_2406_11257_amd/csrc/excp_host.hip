@@ -61,7 +61,7 @@ struct excp_ctx {
     std::vector<u32> tb_offsets;
     // size thresholds of the kernel forms (excp_set_param)
     u64 wide_elems = 1ull << 28;        // a group with a tensor this large takes the sixteen-wave per-bucket kernels
-    u64 cand_list_elems = 1ull << 26;   // one median-candidate list per this many elements of a tensor (1 .. 16 lists)
+    u64 cand_list_elems = 1ull << 20;   // one median-candidate list per this many elements of a tensor (1 .. 16 lists)
     // profiling
     bool profiling = false;
     std::vector<Span> spans;
@@ -396,6 +396,7 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
         ok = hipGetDeviceProperties(&prop, hip_device) == hipSuccess && prop.multiProcessorCount > 0;
         w.cus = ok ? prop.multiProcessorCount : 0;
     }
+    ok = ok && dev_alloc(c, &w.stat_part, 2ull * excp_grid(w, EXCP_STATS_PER_CU));
     if (ok) {
         launch_zero_u32(w.med_hist, (u64)kMaxGroupTensors * 2048, c->stream);
         launch_zero_u32((u32 *)w.km_acc, 2 * acc_words, c->stream);
@@ -549,7 +550,6 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         {
             StageTimer t(c, ST_SELECT_FALLBACK);     // does nothing unless a sample bracket missed its median
             for (int pass = 0; pass < 3; ++pass) { launch_stats(w, p, 5 + pass, s); launch_stats(w, p, 8 + pass, s); }
-            launch_stats(w, p, 11, s);
         }
         { StageTimer t(c, ST_MASK_COMPACT); launch_mask_compact(w, p, 0, s); }
         { StageTimer t(c, ST_MASK_SCAN); launch_mask_compact(w, p, 1, s); }

@@ -135,62 +135,6 @@ __device__ __forceinline__ void window_range(u32 B, u32 &lo, u32 &span) {
     span = ((B + 25u) << 23) - lo;
 }
 
-// Signed bins -> the exact sum rounded once (to nearest, ties to even) to fp64.
-// Everything stays in registers (fixed indices after unrolling): this runs once per centre and
-// iteration on the critical path between two small kernels.
-__device__ double signed_bins_to_double(const u64 *bins) {
-    // base-256 digits of the sum (bin g has weight 2^(8g)), what is left over in a signed top word
-    u64 W[6] = {0, 0, 0, 0, 0, 0};
-    long long carry = 0;
-#pragma unroll
-    for (int g = 0; g < EXCP_ABSM_BINS; ++g) {
-        const u64 b = bins[g];
-        const long long t = (long long)(b & 255ull) + carry;       // |carry| < 2^57: no overflow
-        carry = (t >> 8) + ((long long)b >> 8);
-        W[g >> 3] |= (u64)(t & 255) << (8 * (g & 7));
-    }
-    W[5] = (u64)carry;
-    const bool neg = carry < 0;
-    if (neg) {                                  // magnitude = two's complement negation of the 384 bits
-        u64 c = 1;
-#pragma unroll
-        for (int i = 0; i < 6; ++i) { const u64 v = ~W[i] + c; c = (c && v == 0) ? 1ull : 0ull; W[i] = v; }
-    }
-    // the top non-zero word, the word below it, and whether anything lies below those
-    u64 hi = 0, lo = 0, rest = 0; int wi = -1;
-#pragma unroll
-    for (int i = 5; i >= 0; --i) {
-        if (wi < 0) { if (W[i]) { wi = i; hi = W[i]; } }
-        else if (wi == i + 1) lo = W[i];
-        else rest |= W[i];
-    }
-    if (wi < 0) return 0.0;
-    const int top = 63 - __clzll((long long)hi), msb = 64 * wi + top;
-    double mag;
-    if (msb <= 52) {
-        mag = ldexp((double)hi, -149);          // wi == 0: the value itself, exactly
-    } else {
-        // the 53 bits from msb down, out of hi:lo; sh = number of bits of hi:lo below them
-        const int sh = top + 12;                // 64 + top - 52, in [12, 75]
-        u64 mant, guard, sticky;
-        if (sh < 64) {
-            mant = (hi << (64 - sh)) | (lo >> sh);
-            guard = (lo >> (sh - 1)) & 1ull;
-            sticky = lo & ((1ull << (sh - 1)) - 1ull);
-        } else if (sh == 64) {
-            mant = hi; guard = lo >> 63; sticky = lo & 0x7fffffffffffffffull;
-        } else {
-            mant = hi >> (sh - 64);
-            guard = (hi >> (sh - 65)) & 1ull;
-            sticky = (hi & ((1ull << (sh - 65)) - 1ull)) | lo;
-        }
-        sticky |= rest;
-        if (guard && (sticky || (mant & 1ull))) mant += 1;
-        mag = ldexp((double)mant, msb - 52 - 149);
-    }
-    return neg ? -mag : mag;
-}
-
 // ---------------------------------------------------------------- P0: value -> bucket map from a sample
 // One workgroup per stream.  The sample fixes the magnitude range of each sign (hence offset and
 // shift of the cells); the cells' sample counts, scanned, give every cell its bucket so that the

@@ -20,7 +20,7 @@ namespace {
 
 constexpr u32 MED_SAMPLE = 8192;      // sample size (and the size up to which a tensor is simply sorted)
 constexpr u32 MED_HALF_WIDTH = 192;   // bracket = sample ranks 4096 -+ 192 (about 4.2 sigma of the sample rank)
-constexpr u32 CAND_PER_WAVE = 1024;
+constexpr u32 CAND_STAGE = 2048;       // candidates a wave stages in LDS (it flushes when fewer than 1024 places are left)
 constexpr u32 MED_THREADS = 1024;     // workgroup of the sampling kernel: one per tensor, so its own latency is the kernel's
 
 enum { MED_PENDING = 0, MED_KNOWN = 1, MED_FALLBACK = 2 };
@@ -106,135 +106,155 @@ __global__ __launch_bounds__(MED_THREADS) void k_median_sample(Workspace w, Grou
 // Four consecutive floats at an address that is only known to be 4-byte aligned.
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
+// What one workgroup of the streaming pass found out about a tensor whose tiles it shares with other
+// workgroups (StatPart in excp_device.h).  A workgroup takes a contiguous range of tiles, so it shares at
+// most two tensors: the one its range starts in (record 0) and the one it ends in (record 1).  A tensor that
+// lies inside one workgroup's range goes straight into its TState.  The records replace atomics on the
+// tensor's state: thousands of waves queued at those few addresses (about 20 ns a turn, whatever the size of
+// the tensor), which is what a 16.8 M-element tensor spent 300 of 361 us on.
+__device__ __forceinline__ u32 stats_owner(u32 tile, u32 G, u32 ntiles) {      // workgroup whose range holds the tile
+    return (u32)((((u64)tile + 1ull) * G + ntiles - 1ull) / ntiles) - 1u;
+}
+__device__ __forceinline__ u32 stats_lo(u32 b, u32 G, u32 ntiles) { return (u32)(((u64)b * ntiles) / G); }
+
 // The streaming pass: exact sum of |m|, non-finite check, count of keys below the bracket and
 // collection of the keys inside it.  Persistent workgroups over contiguous tile ranges; a lane
 // takes four consecutive elements of each of four 256-element rows of its wave's quarter tile.
+// Bound by memory: 12 bytes per element and nothing written but the candidates.
 // W16: the weights are 16-bit (fp16 or bf16 by the flags), four to an 8-byte load where the arrays
 // allow it; they are widened on arrival and everything after that is the fp32 code.
 template <bool W16>
 __global__ __launch_bounds__(EXCP_THREADS) void k_stats_stream(Workspace w, GroupParams g) {
     __shared__ u64 bins[EXCP_ABSM_BINS];
-    __shared__ u32 l_cand[4][2 * CAND_PER_WAVE + 1];   // per wave: staged candidates, plus a spare slot
-    __shared__ u32 s_nf, s_lt;
+    __shared__ u32 l_cand[4][CAND_STAGE + 1];   // per wave: staged candidates, plus a spare slot
+    __shared__ u64 s_L, s_H;
+    __shared__ u32 s_nf, s_lt, s_cc, s_atom[4], s_wc[4], s_place;
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const u32 G = gridDim.x, b = blockIdx.x;
-    const u32 lo_tile = (u32)(((u64)b * g.ntiles) / G), hi_tile = (u32)(((u64)(b + 1) * g.ntiles) / G);
+    const u32 lo_tile = stats_lo(b, G, g.ntiles), hi_tile = stats_lo(b + 1u, G, g.ntiles);
     if (lo_tile >= hi_tile) return;
     if (tid < EXCP_ABSM_BINS) bins[tid] = 0;
-    if (tid == 0) { s_nf = 0; s_lt = 0; }
+    if (tid == 0) { s_nf = 0; s_lt = 0; s_cc = 0; s_L = 0; s_H = 0; }
+    if (tid < 4) s_atom[tid] = 0;
     __syncthreads();
 
-    u32 t = find_owner(w.tile_begin, g.ntensors, lo_tile);
-    u32 t_end = w.tile_begin[t + 1];
-    u32 nf = 0, clt = 0;           // clt is the same in every lane of a wave
-    u64 accL = 0, accH = 0;        // this lane's in-window units: sum of low / high 32-bit halves
-    u32 B = w.st[t].absm_base;     // window = bit positions [B, B + 24)
-
-    u32 acnt[4] = {0u, 0u, 0u, 0u};   // W16: elements equal to the tensor's counted bracket values (same in every lane)
-    u32 wcount = 0;                // candidates this wave has staged in LDS (same in every lane)
-    auto flush_cand = [&](u32 tt) {
-        if (W16 && lane == 0) {
+    // the tensor in hand (all of it the same in every lane), read again only when the tensor changes
+    u32 t = 0, t_begin = 0, t_end = 0, B = 0, klo = 0, kspan = 0, natoms = 0, ak[4] = {0u, 0u, 0u, 0u};
+    bool pending = false;
+    u64 n = 0;
+    const float *pW = nullptr, *pP = nullptr, *pM = nullptr;
+    auto open_tensor = [&](u32 tile) {
+        t = (u32)__builtin_amdgcn_readfirstlane((int)find_owner(w.tile_begin, g.ntensors, tile));
+        t_begin = w.tile_begin[t]; t_end = w.tile_begin[t + 1];
+        const TDesc &D = w.desc[t];
+        const TState &S = w.st[t];
+        n = D.n; pW = D.W; pP = D.Wp; pM = D.m;
+        B = S.absm_base;               // window of the exact sum = bit positions [B, B + 24)
+        pending = S.med_state == MED_PENDING;
+        klo = S.br_lo; kspan = S.br_hi - klo;
+        if (W16) {
+            natoms = S.natoms;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) if (acnt[q]) atomicAdd(&w.st[tt].atom_cnt[q], acnt[q]);
-        }
-        if (W16) { acnt[0] = acnt[1] = acnt[2] = acnt[3] = 0u; }
-        // the staged candidates go to the tensor's list: one reservation for many tiles
-        if (wcount) {
-            const TDesc &D = w.desc[tt];
-            const u32 L = D.cand_lists;
-            const bool one_value = w.st[tt].br_lo == w.st[tt].br_hi;
-            if (L == 1u) {
-                u32 at = 0;
-                if (lane == 0) at = atomicAdd(&w.st[tt].cand_count, wcount);
-                at = __shfl(at, 0, WAVE);
-                if (one_value) {
-                    // a bracket of one value (heavily tied data, e.g. 16-bit weights that did not move):
-                    // every candidate is that value, so their number is all that is needed
-                } else if ((u64)at + wcount <= D.cand_cap) {
-                    EXCP_GLOBAL u32 *dst = gptr(w.cand) + D.cand_off + at;
-                    for (u32 i = lane; i < wcount; i += 64) dst[i] = l_cand[wave][i];
-                } else if (lane == 0) {
-                    atomicOr(&w.st[tt].cand_overflow, 1u);
-                }
-            } else {
-                // a very large tensor: L lists with a counter each; a wave starts at "its" list and moves
-                // on to the next when one is full, so the lists fail only when all of them are full
-                u32 *ctr = w.cand_ctr + (u64)tt * 512u;
-                const u32 cap = (u32)(D.cand_cap / L);
-                u32 j = (blockIdx.x * 4u + wave) % L;
-                bool placed = false;
-                for (u32 attempt = 0; attempt < L && !placed; ++attempt, j = (j + 1u == L ? 0u : j + 1u)) {
-                    u32 at = 0;
-                    if (lane == 0) at = atomicAdd(&ctr[j * 32u], wcount);
-                    at = __shfl(at, 0, WAVE);
-                    if (one_value) { placed = true; break; }            // counted only
-                    if ((u64)at + wcount <= cap) {
-                        EXCP_GLOBAL u32 *dst = gptr(w.cand) + D.cand_off + (u64)j * cap + at;
-                        for (u32 i = lane; i < wcount; i += 64) dst[i] = l_cand[wave][i];
-                        if (lane == 0) atomicMax(&ctr[j * 32u + 1u], at + wcount);
-                        placed = true;
-                    }
-                }
-                if (!placed && lane == 0) atomicOr(&w.st[tt].cand_overflow, 1u);
-            }
-            wcount = 0;
+            for (int q = 0; q < 4; ++q) ak[q] = S.atom_key[q];
         }
     };
-    auto flush = [&](u32 tt) {
-        flush_cand(tt);
-        // the lanes' window sums, as three 32-bit pieces at positions B, B + 32, B + 64
+    open_tensor(lo_tile);
+    u32 nf = 0, clt = 0, cc = 0;   // clt, cc: the same in every lane of a wave
+    u64 accL = 0, accH = 0;        // this lane's in-window units: sum of low / high 32-bit halves
+    u32 acnt[4] = {0u, 0u, 0u, 0u};   // W16: elements equal to the tensor's counted bracket values (same in every lane)
+    u32 wcount = 0;                // candidates this wave has staged in LDS (same in every lane)
+    // Room for `cnt` candidates: one lane asks.  A tensor's list is cut into L lists with a counter each, so that
+    // the workgroups do not queue at one address; one that finds its list full moves on to the next, so the lists
+    // fail only when all of them are full.  Returns the place in the group's candidate array, 0xffffffff if none.
+    auto reserve = [&](u32 cnt) -> u32 {
+        const TDesc &D = w.desc[t];
+        const u32 L = D.cand_lists, cap = (u32)(D.cand_cap / L);
+        u32 *ctr = w.cand_ctr + (u64)t * 512u;
+        u32 j = (L == 1u) ? 0u : (b * 4u + wave) % L;
+        for (u32 attempt = 0; attempt < L; ++attempt, j = (j + 1u == L ? 0u : j + 1u)) {
+            const u32 at = atomicAdd(&ctr[j * 32u], cnt);
+            if ((u64)at + cnt <= cap) {
+                atomicMax(&ctr[j * 32u + 1u], at + cnt);
+                return j * cap + at;
+            }
+        }
+        atomicOr(&w.st[t].cand_overflow, 1u);
+        return 0xffffffffu;
+    };
+    auto flush_wave = [&]() {      // a wave's staging area is full: its candidates go to a list
+        u32 at = 0;
+        if (lane == 0) at = reserve(wcount);
+        at = __shfl(at, 0, WAVE);
+        if (at != 0xffffffffu) {
+            EXCP_GLOBAL u32 *dst = gptr(w.cand) + w.desc[t].cand_off + at;
+            for (u32 i = lane; i < wcount; i += 64) dst[i] = l_cand[wave][i];
+        }
+        wcount = 0;
+    };
+    // the workgroup is done with the tensor in hand (called by all its threads)
+    auto flush = [&]() {
+        // the lanes' window sums: at positions B (L) and B + 32 (H)
         const u64 sumL = wave_sum_u64(accL), sumH = wave_sum_u64(accH);
+        const u32 nfw = wave_sum_u32(nf);
         accL = 0; accH = 0;
         if (lane == 0) {
-            const u64 lo64 = sumL + (sumH << 32);
-            const u64 hi64 = (sumH >> 32) + (lo64 < sumL ? 1ull : 0ull);
-            const u64 piece[3] = {lo64 & 0xffffffffull, lo64 >> 32, hi64};
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const u32 p = B + 32u * q;
-                if (piece[q]) atomicAdd(&bins[p >> 3], piece[q] << (p & 7u));
-            }
+            atomicAdd(&s_L, sumL); atomicAdd(&s_H, sumH);
             if (clt) atomicAdd(&s_lt, clt);
+            if (cc) atomicAdd(&s_cc, cc);
+            if (nfw) atomicAdd(&s_nf, nfw);
+            if (W16) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) if (acnt[q]) atomicAdd(&s_atom[q], acnt[q]);
+            }
+            s_wc[wave] = wcount;
         }
-        if (nf) atomicAdd(&s_nf, nf);
-        nf = 0; clt = 0;
+        nf = 0; clt = 0; cc = 0;
+        acnt[0] = acnt[1] = acnt[2] = acnt[3] = 0u;
         __syncthreads();
-        if (tid < EXCP_ABSM_BINS) {
-            u64 c = bins[tid];
-            if (c) { atomicAdd(&w.st[tt].absm[tid], c); bins[tid] = 0; }
+        const u32 c0 = s_wc[0], c1 = s_wc[1], c2 = s_wc[2], total = c0 + c1 + c2 + s_wc[3];
+        if (tid < EXCP_ABSM_BINS) {                       // (values outside the window: rare)
+            const u64 c = bins[tid];
+            if (c) { atomicAdd(&w.st[t].absm[tid], c); bins[tid] = 0; }
         }
         if (tid == 0) {
-            if (s_nf) { atomicAdd(&w.st[tt].nonfinite, (u64)s_nf); s_nf = 0; }
-            if (s_lt) { atomicAdd(&w.st[tt].c_lt, s_lt); s_lt = 0; }
+            s_place = total ? reserve(total) : 0xffffffffu;   // one reservation for the whole workgroup
+            StatPart P;
+            P.L = s_L; P.H = s_H; P.clt = s_lt; P.nf = s_nf; P.cc = s_cc; P.pad = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { P.atom[q] = s_atom[q]; s_atom[q] = 0; }
+            s_L = 0; s_H = 0; s_lt = 0; s_nf = 0; s_cc = 0;
+            if (t_begin >= lo_tile && t_end <= hi_tile) w.st[t].part = P;      // nobody else holds tiles of it
+            else w.stat_part[2u * b + (t_begin <= lo_tile ? 0u : 1u)] = P;
         }
+        __syncthreads();
+        const u32 at = s_place;
+        if (at != 0xffffffffu) {
+            const u32 mine = at + (wave > 0u ? c0 : 0u) + (wave > 1u ? c1 : 0u) + (wave > 2u ? c2 : 0u);
+            EXCP_GLOBAL u32 *dst = gptr(w.cand) + w.desc[t].cand_off + mine;
+            for (u32 i = lane; i < wcount; i += 64) dst[i] = l_cand[wave][i];
+        }
+        wcount = 0;
         __syncthreads();
     };
 
     for (u32 tile = lo_tile; tile < hi_tile; ++tile) {
         if (tile >= t_end) {
-            flush(t);
-            t = find_owner(w.tile_begin, g.ntensors, tile);
-            t_end = w.tile_begin[t + 1];
-            B = w.st[t].absm_base;
+            flush();
+            open_tensor(tile);
         }
-        const TDesc &D = w.desc[t];
-        TState &S = w.st[t];
-        const u64 n = D.n;
-        const u64 base = (u64)(tile - D.tile_begin) * EXCP_TILE;
+        const u64 base = (u64)(tile - t_begin) * EXCP_TILE;
         const u32 rem = (n - base < (u64)EXCP_TILE) ? (u32)(n - base) : EXCP_TILE;
-        const bool pending = S.med_state == MED_PENDING;
-        const u32 klo = S.br_lo, kspan = S.br_hi - klo;
 
         u32 key[16], mb[16];
         u32 worst = 0;             // largest magnitude pattern seen: >= 0x7f800000 means Inf or NaN
         const bool of_weights = (g.flags & 1u) != 0;       // the median is that of |W_t|, not of the residual
         {
-            const EXCP_GLOBAL float *gW = gptr(D.W) + base, *gP = gptr(D.Wp) + base, *gM = gptr(D.m) + base;
+            const EXCP_GLOBAL float *gW = gptr(pW) + base, *gP = gptr(pP) + base, *gM = gptr(pM) + base;
             const u32 wt = W16 ? excp_wtype(g.flags) : 0u;
             const bool bf = wt == 2u;
-            const EXCP_GLOBAL unsigned short *hW = gptr((const unsigned short *)D.W) + base;
-            const EXCP_GLOBAL unsigned short *hP = gptr((const unsigned short *)D.Wp) + base;
-            const bool vec16 = W16 && (((uintptr_t)D.W | (uintptr_t)D.Wp) & 7u) == 0u;   // 8-byte loads need 8-byte alignment
+            const EXCP_GLOBAL unsigned short *hW = gptr((const unsigned short *)pW) + base;
+            const EXCP_GLOBAL unsigned short *hP = gptr((const unsigned short *)pP) + base;
+            const bool vec16 = W16 && (((uintptr_t)pW | (uintptr_t)pP) & 7u) == 0u;   // 8-byte loads need 8-byte alignment
             if (rem == EXCP_TILE && (!W16 || vec16)) {
                 f4u a[4], p[4], mm[4];
 #pragma unroll
@@ -289,27 +309,32 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_stats_stream(Workspace w, Grou
             }
             if (nf == 0 && worst >= 0x7f800000u) nf = 1;
         }
-        const u32 natoms = W16 ? S.natoms : 0u;
-        const u32 ak0 = S.atom_key[0], ak1 = S.atom_key[1], ak2 = S.atom_key[2], ak3 = S.atom_key[3];
-        if (pending) {
+        if (pending && kspan == 0u) {
+            // a bracket of one value (heavily tied data, e.g. 16-bit weights that did not move): its number is
+            // all that is needed
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                clt += __popcll(ballot64(key[j] < klo));
+                cc += __popcll(ballot64(key[j] == klo));
+            }
+        } else if (pending) {
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
                 clt += __popcll(ballot64(key[j] < klo));
                 bool cand = key[j] - klo <= kspan;            // klo <= key <= khi (a padded key wraps far above)
                 if (W16 && natoms) {
-                    const bool e0 = key[j] == ak0, e1 = natoms > 1u && key[j] == ak1;
-                    const bool e2 = natoms > 2u && key[j] == ak2, e3 = natoms > 3u && key[j] == ak3;
+                    const bool e0 = key[j] == ak[0], e1 = natoms > 1u && key[j] == ak[1];
+                    const bool e2 = natoms > 2u && key[j] == ak[2], e3 = natoms > 3u && key[j] == ak[3];
                     acnt[0] += __popcll(ballot64(e0)); acnt[1] += __popcll(ballot64(e1));
                     acnt[2] += __popcll(ballot64(e2)); acnt[3] += __popcll(ballot64(e3));
                     cand = cand && !(e0 || e1 || e2 || e3);
                 }
                 const u64 bal = ballot64(cand);
                 // branch-free: the others write to a spare slot past the end
-                const u32 below = __builtin_amdgcn_mbcnt_hi((u32)(bal >> 32), __builtin_amdgcn_mbcnt_lo((u32)bal, 0u));
-                l_cand[wave][cand ? wcount + below : 2 * CAND_PER_WAVE] = key[j];
+                l_cand[wave][cand ? wcount + lanes_below(bal) : CAND_STAGE] = key[j];
                 wcount += __popcll(bal);
             }
-            if (wcount > CAND_PER_WAVE) flush_cand(t);        // room for another 1024 is kept
+            if (wcount > CAND_STAGE - 1024u) flush_wave();    // room for another 1024 is kept
         }
         {
             // exact sum of |m|: in-window values are whole multiples of 2^(B-149) below 2^48 units,
@@ -334,43 +359,100 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_stats_stream(Workspace w, Grou
             accH += hi32;
         }
     }
-    flush(t);
+    flush();
 }
 
-// After the streaming pass: does the bracket hold the median?  If so the select goes on inside
-// the candidates (base key, number of undecided low bits, rank); if not the tensor falls back.
-__global__ void k_cand_begin(Workspace w, GroupParams g) {
-    const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= g.ntensors) return;
+// After the streaming pass, one workgroup per tensor: the workgroups' records are added up; the exact sum of
+// |m| becomes the second threshold; and the bracket is checked: does it hold the median?  If so the select goes
+// on inside the candidates (base key, number of undecided low bits, rank); if not the tensor falls back.
+// `G` = workgroups of the streaming pass.
+__global__ __launch_bounds__(EXCP_THREADS) void k_stats_finish(Workspace w, GroupParams g, u32 G) {
+    __shared__ u64 bins[EXCP_ABSM_BINS];
+    __shared__ u64 s_u64[3];
+    __shared__ u32 s_u32[6];
+    const u32 t = blockIdx.x, tid = threadIdx.x, lane = tid & 63u;
     TState &S = w.st[t];
-    if (S.med_state != MED_PENDING) return;
-    const u64 n = w.desc[t].n;
-    const u64 r = (n - 1) >> 1;
-    const u32 L = w.desc[t].cand_lists;
-    u64 cnt = S.cand_count;
-    if (L > 1u) {                          // several lists: slots asked for (counting only) or granted (listed)
-        const u32 *ctr = w.cand_ctr + (u64)t * 512u;
-        cnt = 0;
-        for (u32 j = 0; j < L; ++j) cnt += ctr[j * 32u + (S.br_hi == S.br_lo ? 0u : 1u)];
-        S.cand_count = (u32)cnt;
-    }
-    const u64 below = S.c_lt;
-    if (S.br_hi == S.br_lo) {              // one-value bracket: only counted, never listed
-        if (r >= below && r < below + cnt) { S.med_bits = S.br_lo; S.med_state = MED_KNOWN; }
-        else S.med_state = MED_FALLBACK;
+    const TDesc &D = w.desc[t];
+    const u64 n = D.n;
+    if (n == 0) {
+        if (tid == 0) { S.med_bits = 0; S.mean32 = 0.f; S.t_w = 0.f; S.r_o = 0.f; S.abs_sum = 0.0; }
         return;
     }
-    u64 counted = 0;                       // bracket values that were counted instead of listed
-    for (u32 q = 0; q < S.natoms; ++q) counted += S.atom_cnt[q];
-    if (S.cand_overflow || cnt > w.desc[t].cand_cap || r < below || r >= below + cnt + counted) {
-        S.med_state = MED_FALLBACK;
-        return;
+    if (tid < 3) s_u64[tid] = 0;
+    if (tid < 6) s_u32[tid] = 0;
+    if (tid < EXCP_ABSM_BINS) bins[tid] = S.absm[tid];
+    __syncthreads();
+    u64 L = 0, H = 0, nf = 0;
+    u32 clt = 0, cc = 0, atom[4] = {0u, 0u, 0u, 0u};
+    auto take = [&](const StatPart &P) {
+        L += P.L; H += P.H; nf += P.nf; clt += P.clt; cc += P.cc;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) atom[q] += P.atom[q];
+    };
+    const u32 tb = D.tile_begin, te = tb + D.tile_count;
+    const u32 b0 = stats_owner(tb, G, g.ntiles), b1 = stats_owner(te - 1u, G, g.ntiles);
+    if (b0 == b1) {
+        if (tid == 0) take(S.part);
+    } else {
+        for (u32 b = b0 + tid; b <= b1; b += EXCP_THREADS) {
+            const u32 lo = stats_lo(b, G, g.ntiles);
+            if (lo < stats_lo(b + 1u, G, g.ntiles)) take(w.stat_part[2u * b + (tb <= lo ? 0u : 1u)]);
+        }
     }
-    const u32 span = S.br_hi - S.br_lo;
-    S.sel_base = S.br_lo;
-    S.sel_width = span ? 32u - (u32)__clz((int)span) : 0u;
-    S.sel_rank = (u32)(r - below);
-    if (span == 0) { S.med_bits = S.br_lo; S.med_state = MED_KNOWN; }
+    L = wave_sum_u64(L); H = wave_sum_u64(H); nf = wave_sum_u64(nf);
+    clt = wave_sum_u32(clt); cc = wave_sum_u32(cc);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) atom[q] = wave_sum_u32(atom[q]);
+    if (lane == 0) {
+        atomicAdd(&s_u64[0], L); atomicAdd(&s_u64[1], H); atomicAdd(&s_u64[2], nf);
+        atomicAdd(&s_u32[0], clt); atomicAdd(&s_u32[1], cc);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) atomicAdd(&s_u32[2 + q], atom[q]);
+    }
+    __syncthreads();
+    if (tid != 0) return;
+    L = s_u64[0]; H = s_u64[1];
+    S.nonfinite += s_u64[2];
+    {
+        const u32 B = S.absm_base;
+        const u64 lo64 = L + (H << 32), hi64 = (H >> 32) + (lo64 < L ? 1ull : 0ull);
+        const u64 piece[3] = {lo64 & 0xffffffffull, lo64 >> 32, hi64};
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const u32 p = B + 32u * (u32)q;
+            if (piece[q]) bins[p >> 3] += piece[q] << (p & 7u);
+        }
+        const double sum = signed_bins_to_double(bins);
+        const float mean32 = (float)(sum / (double)n);
+        S.abs_sum = sum;
+        S.mean32 = mean32;
+        S.r_o = __fmul_rn(g.beta, mean32);
+    }
+    if (S.med_state == MED_PENDING) {
+        const u64 r = (n - 1) >> 1;
+        const u64 below = s_u32[0];
+        S.c_lt = (u32)below;
+        if (S.br_hi == S.br_lo) {              // one-value bracket: only counted, never listed
+            const u64 cnt = s_u32[1];
+            S.cand_count = (u32)cnt;
+            if (r >= below && r < below + cnt) { S.med_bits = S.br_lo; S.med_state = MED_KNOWN; }
+            else S.med_state = MED_FALLBACK;
+        } else {
+            u64 cnt = 0, counted = 0;          // listed candidates; bracket values that were counted instead of listed
+            for (u32 j = 0; j < D.cand_lists; ++j) cnt += w.cand_ctr[(u64)t * 512u + j * 32u + 1u];
+            S.cand_count = (u32)cnt;
+#pragma unroll
+            for (u32 q = 0; q < 4; ++q) { S.atom_cnt[q] = s_u32[2 + q]; if (q < S.natoms) counted += s_u32[2 + q]; }
+            if (S.cand_overflow || r < below || r >= below + cnt + counted) {
+                S.med_state = MED_FALLBACK;
+            } else {
+                S.sel_base = S.br_lo;
+                S.sel_width = 32u - (u32)__clz((int)(S.br_hi - S.br_lo));
+                S.sel_rank = (u32)(r - below);
+            }
+        }
+    }
+    S.t_w = __fmul_rn(g.alpha, u2f(S.med_bits));          // (final where the median is known by now)
 }
 
 // One radix pass over the candidates: histogram of the top (up to 11) undecided bits.  A workgroup
@@ -401,8 +483,8 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_cand_hist(Workspace w, GroupPa
                 const u32 rel = key - base;               // keys below base wrap around and drop out
                 if ((u64)rel < limit) atomicAdd(&hist[rel >> shift], 1u);
             };
-            for (u32 j = 0; j < L; ++j) {                 // (one list, except for very large tensors)
-                const u32 cnt = L == 1u ? S.cand_count : w.cand_ctr[(u64)t * 512u + j * 32u + 1u];
+            for (u32 j = 0; j < L; ++j) {
+                const u32 cnt = w.cand_ctr[(u64)t * 512u + j * 32u + 1u];
                 const u32 i0 = (u32)(((u64)cnt * (a0 - tb)) / tc), i1 = (u32)(((u64)cnt * (a1 - tb)) / tc);
                 const EXCP_GLOBAL u32 *c = gptr(w.cand) + w.desc[t].cand_off + (u64)j * cap;
                 for (u32 q0 = i0; q0 < i1; q0 += 4u * EXCP_THREADS) {
@@ -463,7 +545,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_cand_resolve(Workspace w, Grou
         S.sel_base = nb;
         S.sel_width = shift;
         S.sel_rank = r;
-        if (shift == 0) { S.med_bits = nb; S.med_state = MED_KNOWN; }
+        if (shift == 0) { S.med_bits = nb; S.med_state = MED_KNOWN; S.t_w = __fmul_rn(g.alpha, u2f(nb)); }
     }
 }
 
@@ -557,64 +639,8 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_full_resolve(Workspace w, Grou
         const u32 np = (PASS == 2) ? ((prefix << 9) | bin) : ((prefix << 11) | bin);
         S.sel_base = np;
         S.sel_rank = r;
-        if (PASS == 2) { S.med_bits = np; S.med_state = MED_KNOWN; }
+        if (PASS == 2) { S.med_bits = np; S.med_state = MED_KNOWN; S.t_w = __fmul_rn(g.alpha, u2f(np)); }
     }
-}
-
-// Exact sum: bins[g] * 2^(8g-149) summed as one big integer, rounded once (to nearest, ties to
-// even) to fp64.
-__device__ double absm_bins_to_double(const u64 *bins) {
-    u32 limb[14];
-    for (int i = 0; i < 14; ++i) limb[i] = 0;
-    for (int gidx = 0; gidx < EXCP_ABSM_BINS; ++gidx) {
-        u64 c = bins[gidx];
-        if (!c) continue;
-        u32 bit = 8u * gidx, li = bit >> 5, sh = bit & 31u;
-        // c << sh spans up to three limbs
-        u64 lo = c << sh;
-        u32 top = sh ? (u32)(c >> (64 - sh)) : 0u;
-        u32 parts[3] = {(u32)lo, (u32)(lo >> 32), top};
-        u64 carry = 0;
-        for (int q = 0; q < 3 || carry; ++q) {
-            if (li + q >= 14) break;
-            u64 s = (u64)limb[li + q] + (q < 3 ? parts[q] : 0u) + carry;
-            limb[li + q] = (u32)s;
-            carry = s >> 32;
-        }
-    }
-    int top = -1;
-    for (int i = 13; i >= 0; --i) if (limb[i]) { top = i; break; }
-    if (top < 0) return 0.0;
-    int msb = 32 * top + (31 - __clz((int)limb[top]));       // position of the leading one
-    auto bit_at = [&](int p) -> u32 { return p < 0 ? 0u : (limb[p >> 5] >> (p & 31)) & 1u; };
-    if (msb <= 52) {
-        u64 x = (u64)limb[0] | ((u64)limb[1] << 32);
-        return ldexp((double)x, -149);
-    }
-    u64 mant = 0;
-    for (int p = msb; p >= msb - 52; --p) mant = (mant << 1) | bit_at(p);
-    u32 guard = bit_at(msb - 53);
-    u32 sticky = 0;
-    for (int p = msb - 54; p >= 0 && !sticky; --p) sticky |= bit_at(p);
-    if (guard && (sticky || (mant & 1ull))) mant += 1;       // 2^53 is still exact in fp64
-    return ldexp((double)mant, msb - 52 - 149);
-}
-
-// The two thresholds of every tensor: t_w = alpha * median, r_o = beta * fp32(exact sum / n).
-__global__ void k_thresholds(Workspace w, GroupParams g) {
-    const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= g.ntensors) return;
-    TState &S = w.st[t];
-    const u64 n = w.desc[t].n;
-    if (n == 0) { S.med_bits = 0; S.mean32 = 0.f; S.t_w = 0.f; S.r_o = 0.f; S.abs_sum = 0.0; return; }
-    const float med = u2f(S.med_bits);
-    S.t_w = __fmul_rn(g.alpha, med);
-    const double sum = absm_bins_to_double(S.absm);
-    const double mean64 = sum / (double)n;
-    const float mean32 = (float)mean64;
-    S.abs_sum = sum;
-    S.mean32 = mean32;
-    S.r_o = __fmul_rn(g.beta, mean32);
 }
 
 __global__ void k_zero_u32(u32 *p, u64 count) {
@@ -646,12 +672,12 @@ void launch_zero_u32(u32 *p, u64 count, hipStream_t s) {
     hipLaunchKernelGGL(k_zero_u32, dim3((u32)blocks), dim3(256), 0, s, p, count);
 }
 
-// phase 0: sample, 1: streaming pass, 2: bracket check, 3: candidate histogram, 4: candidate resolve,
-// 5..7: fallback histograms, 8..10: fallback resolves, 11: thresholds
+// phase 0: sample, 1: streaming pass, 2: its records added up, bracket check, thresholds, 3: candidate
+// histogram, 4: candidate resolve, 5..7: fallback histograms, 8..10: fallback resolves
 void launch_stats(const Workspace &w, const GroupParams &g, int phase, hipStream_t s) {
     if (!g.ntensors) return;
-    const dim3 block(EXCP_THREADS), per_tensor(g.ntensors), small((g.ntensors + 255) / 256);
-    const dim3 stream_grid(excp_grid(w, 8));
+    const dim3 block(EXCP_THREADS), per_tensor(g.ntensors);
+    const dim3 stream_grid(excp_grid(w, EXCP_STATS_PER_CU));
     switch (phase) {
         case 0: hipLaunchKernelGGL(k_median_sample, per_tensor, dim3(MED_THREADS), 0, s, w, g); break;
         case 1:
@@ -659,7 +685,7 @@ void launch_stats(const Workspace &w, const GroupParams &g, int phase, hipStream
             if (g.flags & 0x30u) hipLaunchKernelGGL(k_stats_stream<true>, stream_grid, block, 0, s, w, g);
             else hipLaunchKernelGGL(k_stats_stream<false>, stream_grid, block, 0, s, w, g);
             break;
-        case 2: hipLaunchKernelGGL(k_cand_begin, small, dim3(256), 0, s, w, g); break;
+        case 2: hipLaunchKernelGGL(k_stats_finish, per_tensor, block, 0, s, w, g, stream_grid.x); break;
         case 3: if (g.ntiles) hipLaunchKernelGGL(k_cand_hist, dim3((g.ntiles + CAND_TILES - 1) / CAND_TILES), block, 0, s, w, g); break;
         case 4: hipLaunchKernelGGL(k_cand_resolve, per_tensor, block, 0, s, w, g); break;
         case 5: if (g.ntiles) hipLaunchKernelGGL(k_full_hist<0>, stream_grid, block, 0, s, w, g); break;
@@ -668,7 +694,6 @@ void launch_stats(const Workspace &w, const GroupParams &g, int phase, hipStream
         case 8: hipLaunchKernelGGL(k_full_resolve<0>, per_tensor, block, 0, s, w, g); break;
         case 9: hipLaunchKernelGGL(k_full_resolve<1>, per_tensor, block, 0, s, w, g); break;
         case 10: hipLaunchKernelGGL(k_full_resolve<2>, per_tensor, block, 0, s, w, g); break;
-        case 11: hipLaunchKernelGGL(k_thresholds, small, dim3(256), 0, s, w, g); break;
         default: break;
     }
 }
