@@ -11,6 +11,7 @@
 #define EXCP_CHUNK       8192u     // survivors per chunk of the survivor passes
 #define EXCP_SUPER_CHUNKS 16u      // chunks per unit of the bucket counts (and of the scatter's workgroup ranges)
 #define EXCP_THREADS     256
+#define EXCP_SAMPLE_PARTS 16u      // workgroups that draw a tensor's sample of residuals
 #define EXCP_STATS_PER_CU 8u       // workgroups per compute unit of the statistics pass
 #define EXCP_ABSM_BINS   40        // u64 accumulators, 8 binary exponents apart, for the exact sum of |m|
 #define EXCP_MAX_K       255
@@ -145,6 +146,9 @@ struct Workspace {
     // survivors
     float *xw, *xm, *xv;
     // median select
+    u32 *sample;              // [tensor][8192] residual magnitudes of the sample
+    u32 *sample_mmax;         // [tensor][EXCP_SAMPLE_PARTS] largest finite |m| pattern met by each part of the sample
+    u32 *sel_ticket;          // [tensor] workgroups that have finished the pass of the select in hand (0 between passes)
     u32 *med_hist;            // [tensor][2048]
     u32 *cand;                // median candidates (keys inside the sample bracket), per tensor
     u32 *cand_ctr;            // [tensor][16][32] per list: [0] slots asked for, [1] end of the slots granted (128 B apart)

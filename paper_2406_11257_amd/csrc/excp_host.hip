@@ -19,12 +19,12 @@ constexpr u32 kMaxGroupTensors = 1024;   // tensors processed together (== EXCP_
 constexpr u32 kMaxBatchTensors = 4096;   // tensors per compress / decompress call
 
 enum Stage {
-    ST_SAMPLE = 0, ST_STATS, ST_SELECT, ST_SELECT_FALLBACK, ST_MASK_COMPACT, ST_MASK_SCAN, ST_MASK_GATHER, ST_LAYOUT, ST_KM_SAMPLE, ST_KM_COUNT, ST_KM_SCAN,
+    ST_SAMPLE = 0, ST_STATS, ST_SELECT, ST_MASK_COMPACT, ST_MASK_SCAN, ST_MASK_GATHER, ST_LAYOUT, ST_KM_SAMPLE, ST_KM_COUNT, ST_KM_SCAN,
     ST_KM_SCATTER, ST_KM_BUCKET_STATS, ST_KM_INIT, ST_KM_CLASSIFY, ST_KM_ITER, ST_KM_UPDATE, ST_ASSIGN_PACK, ST_FINALIZE,
     ST_DECODE_PREP, ST_DECODE_MAIN, ST_EXPORT_DENSE, ST_DECODE_DENSE, ST_MISC, ST_COUNT
 };
 const char *kStageNames[ST_COUNT] = {
-    "median_sample", "stats_stream", "select_candidates", "select_fallback", "mask_slots", "mask_scan", "mask_gather", "layout", "km_sample", "km_count", "km_scan",
+    "median_sample", "stats_stream", "select_candidates", "mask_slots", "mask_scan", "mask_gather", "layout", "km_sample", "km_count", "km_scan",
     "km_scatter", "km_bucket_stats", "km_init", "km_classify", "km_iter", "km_update", "assign_pack", "finalize",
     "decode_prep", "decode_main", "export_dense", "decode_dense", "misc"};
 
@@ -350,6 +350,9 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.xm, G);
     ok = ok && dev_alloc(c, &w.xv, G);
     ok = ok && dev_alloc(c, &w.med_hist, (u64)kMaxGroupTensors * 2048);
+    ok = ok && dev_alloc(c, &w.sample, (u64)kMaxGroupTensors * 8192);
+    ok = ok && dev_alloc(c, &w.sample_mmax, (u64)kMaxGroupTensors * EXCP_SAMPLE_PARTS);
+    ok = ok && dev_alloc(c, &w.sel_ticket, kMaxGroupTensors);
     ok = ok && dev_alloc(c, &w.cand, G / 12 + 4096ull * kMaxGroupTensors + 16);
     ok = ok && dev_alloc(c, &w.tile_status, 2 * max_tiles);      // one word per 2048-element sub-tile
     ok = ok && dev_alloc(c, &w.mask_prefix, 2 * max_tiles);
@@ -399,6 +402,7 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.stat_part, 2ull * excp_grid(w, EXCP_STATS_PER_CU));
     if (ok) {
         launch_zero_u32(w.med_hist, (u64)kMaxGroupTensors * 2048, c->stream);
+        launch_zero_u32(w.sel_ticket, kMaxGroupTensors, c->stream);
         launch_zero_u32((u32 *)w.km_acc, 2 * acc_words, c->stream);
         launch_zero_u32(w.km_item_count, 4, c->stream);
         launch_zero_u32((u32 *)w.err_flag, 4, c->stream);
@@ -542,15 +546,7 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
         { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, s); }
         { StageTimer t(c, ST_STATS); launch_stats(w, p, 1, s); }
-        {
-            StageTimer t(c, ST_SELECT);
-            launch_stats(w, p, 2, s);
-            for (int pass = 0; pass < 3; ++pass) { launch_stats(w, p, 3, s); launch_stats(w, p, 4, s); }
-        }
-        {
-            StageTimer t(c, ST_SELECT_FALLBACK);     // does nothing unless a sample bracket missed its median
-            for (int pass = 0; pass < 3; ++pass) { launch_stats(w, p, 5 + pass, s); launch_stats(w, p, 8 + pass, s); }
-        }
+        { StageTimer t(c, ST_SELECT); launch_stats(w, p, 2, s); }
         { StageTimer t(c, ST_MASK_COMPACT); launch_mask_compact(w, p, 0, s); }
         { StageTimer t(c, ST_MASK_SCAN); launch_mask_compact(w, p, 1, s); }
         { StageTimer t(c, ST_LAYOUT); launch_layout(w, p, s); }

@@ -139,60 +139,82 @@ __device__ __forceinline__ void window_range(u32 B, u32 &lo, u32 &span) {
 // One workgroup per stream.  The sample fixes the magnitude range of each sign (hence offset and
 // shift of the cells); the cells' sample counts, scanned, give every cell its bucket so that the
 // buckets hold about equal shares of the sample.
-__global__ __launch_bounds__(EXCP_THREADS) void k_km_sample(Workspace w, GroupParams g) {
+// 1024 threads, eight samples each: the kernel is one chain of dependent look-ups per sample, so what counts is how
+// many of them are in flight (256 threads with four rounds of eight: 97 us for a 16.8 M-element tensor).
+constexpr u32 SM_THREADS = 1024, SM_COARSE = 1024;
+
+__global__ __launch_bounds__(SM_THREADS) void k_km_sample(Workspace w, GroupParams g) {
     __shared__ float smp[SAMPLE];
     __shared__ u32 cnt[EXCP_KM_CELLS];
+    __shared__ u32 s_coarse[SM_COARSE];
     __shared__ u32 s_map[4];
     __shared__ u32 s_ext[4];                       // min / max magnitude of the negative, of the positive samples
-    __shared__ u32 s_part[EXCP_THREADS];
+    __shared__ u32 s_wave[SM_THREADS / 64];
+    constexpr u32 PER_S = SAMPLE / SM_THREADS;
     const u32 sidx = blockIdx.x, tid = threadIdx.x;
     const u64 len = w.seg[sidx].len;
     if (len == 0) return;
     // The stream is read where the mask pass left it, in the sub-tile slots (the dense copy is made
     // afterwards, by the pass that also counts the buckets this map defines): survivor p of the stream
-    // sits in the sub-tile whose scanned count is the last one <= p.  Eight searches go side by side.
+    // sits in the sub-tile whose scanned count is the last one <= p.  Every (nsub / 1024)-th scanned count
+    // is fetched first, side by side; a search then takes ten steps in LDS and only the rest in memory.
     const u32 ts = sidx / 3u, which = sidx % 3u;
-    const u32 sub_first = 2u * w.tile_begin[ts], sub_end = 2u * w.tile_begin[ts + 1u];
-    const u64 *pre = w.mask_prefix;
+    const u32 sub_first = 2u * w.tile_begin[ts], nsub = 2u * w.tile_begin[ts + 1u] - sub_first;
+    const u64 *pre = w.mask_prefix + sub_first;
     const float *__restrict__ slots = (which == 0 ? w.pw : (which == 1 ? w.pm : w.pv)) + w.desc[ts].elem_off;
+    auto at_of = [&](u64 packed) { return which == 0 ? (u32)(packed >> 32) : (u32)packed; };
+    auto coarse_sub = [&](u32 k) { return (u32)(((u64)k * nsub) / SM_COARSE); };
     const u32 ns = len < SAMPLE ? (u32)len : SAMPLE;
     if (tid < 4) s_ext[tid] = (tid & 1u) ? 0u : 0xffffffffu;
-    for (u32 c = tid; c < EXCP_KM_CELLS; c += EXCP_THREADS) cnt[c] = 0;
+    s_coarse[tid] = at_of(pre[coarse_sub(tid)]);
+    for (u32 c = tid; c < EXCP_KM_CELLS; c += SM_THREADS) cnt[c] = 0;
     __syncthreads();
     u32 mn[2] = {0xffffffffu, 0xffffffffu}, mx[2] = {0u, 0u};
-    for (u32 i0 = tid; i0 < ns; i0 += 8u * EXCP_THREADS) {
-        u32 pos[8], lo[8], hi[8];
+    {
+        u32 pos[PER_S], lo[PER_S], hi[PER_S];
 #pragma unroll
-        for (u32 k = 0; k < 8; ++k) {
-            const u32 i = min(i0 + k * EXCP_THREADS, ns - 1u);
+        for (u32 k = 0; k < PER_S; ++k) {
+            const u32 i = min(tid + k * SM_THREADS, ns - 1u);
             pos[k] = (u32)(((u64)i * len) / ns);
-            lo[k] = sub_first; hi[k] = sub_end;         // invariant: prefix(lo) <= pos < prefix(hi)
+            lo[k] = 0;
+        }
+#pragma unroll
+        for (u32 step = SM_COARSE / 2; step >= 1u; step >>= 1) {
+#pragma unroll
+            for (u32 k = 0; k < PER_S; ++k) if (s_coarse[lo[k] + step] <= pos[k]) lo[k] += step;
+        }
+#pragma unroll
+        for (u32 k = 0; k < PER_S; ++k) {               // invariant: prefix(lo) <= pos < prefix(hi)
+            hi[k] = lo[k] + 1u < SM_COARSE ? max(coarse_sub(lo[k] + 1u), coarse_sub(lo[k]) + 1u) : nsub;
+            lo[k] = coarse_sub(lo[k]);
         }
         bool more = true;
         while (more) {
             more = false;
-            u32 mid[8];
-            u64 pv[8];
+            u32 mid[PER_S];
+            u64 pv[PER_S];
 #pragma unroll
-            for (u32 k = 0; k < 8; ++k) { mid[k] = (lo[k] + hi[k]) >> 1; pv[k] = pre[mid[k]]; }
+            for (u32 k = 0; k < PER_S; ++k) { mid[k] = (lo[k] + hi[k]) >> 1; pv[k] = hi[k] - lo[k] > 1u ? pre[mid[k]] : 0ull; }
 #pragma unroll
-            for (u32 k = 0; k < 8; ++k) {
+            for (u32 k = 0; k < PER_S; ++k) {
                 if (hi[k] - lo[k] > 1u) {
-                    const u32 at = which == 0 ? (u32)(pv[k] >> 32) : (u32)pv[k];
-                    if (at <= pos[k]) lo[k] = mid[k]; else hi[k] = mid[k];
+                    if (at_of(pv[k]) <= pos[k]) lo[k] = mid[k]; else hi[k] = mid[k];
                     more = more || hi[k] - lo[k] > 1u;
                 }
             }
         }
+        u32 at[PER_S];
 #pragma unroll
-        for (u32 k = 0; k < 8; ++k) {
-            const u32 i = i0 + k * EXCP_THREADS;
+        for (u32 k = 0; k < PER_S; ++k) at[k] = at_of(pre[lo[k]]);
+        float v[PER_S];
+#pragma unroll
+        for (u32 k = 0; k < PER_S; ++k) v[k] = slots[(u64)lo[k] * 2048u + (pos[k] - at[k])];
+#pragma unroll
+        for (u32 k = 0; k < PER_S; ++k) {
+            const u32 i = tid + k * SM_THREADS;
             if (i < ns) {
-                const u64 pl = pre[lo[k]];
-                const u32 at = which == 0 ? (u32)(pl >> 32) : (u32)pl;
-                const float v = slots[(u64)(lo[k] - sub_first) * 2048u + (pos[k] - at)];
-                smp[i] = v;
-                const u32 bits = f2u(v), a = bits & 0x7fffffffu, sg = bits >> 31;
+                smp[i] = v[k];
+                const u32 bits = f2u(v[k]), a = bits & 0x7fffffffu, sg = bits >> 31;
                 if (sg) { mn[0] = min(mn[0], a); mx[0] = max(mx[0], a); } else { mn[1] = min(mn[1], a); mx[1] = max(mx[1], a); }
             }
         }
@@ -220,16 +242,16 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_km_sample(Workspace w, GroupPa
         s_map[2 * tid] = amin; s_map[2 * tid + 1] = sh;
     }
     __syncthreads();
-    for (u32 i = tid; i < ns; i += EXCP_THREADS) atomicAdd(&cnt[cell_of(smp[i], s_map)], 1u);
+    for (u32 i = tid; i < ns; i += SM_THREADS) atomicAdd(&cnt[cell_of(smp[i], s_map)], 1u);
     __syncthreads();
-    // Exclusive scan over the cells (16 consecutive cells per thread), then bucket = share of the sample
+    // Exclusive scan over the cells (four consecutive cells per thread), then bucket = share of the sample
     // below.  A cell that alone holds more than 1/64 of the sample is a tied value (a continuous
     // distribution never fills one of 4096 cells like that): it gets a bucket of its own, so that a bucket
     // is either one repeated value -- which neither the initial order statistics nor the Lloyd
     // iterations ever have to read again -- or an even share of the rest.  With H such cells the others
     // are spread over S = 255 - 2 H buckets; a heavy cell sits one above the light cells before it and
     // one below those after it.
-    constexpr u32 PER = EXCP_KM_CELLS / EXCP_THREADS;     // 16
+    constexpr u32 PER = EXCP_KM_CELLS / SM_THREADS;       // 4
     const u32 heavy_min = max(ns / 64u, 32u);
     u32 local[PER], sum = 0;                               // sum: heavy cells << 16 | samples in light cells
 #pragma unroll
@@ -237,18 +259,18 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_km_sample(Workspace w, GroupPa
         local[q] = cnt[tid * PER + q];
         sum += local[q] >= heavy_min ? (1u << 16) : local[q];
     }
-    s_part[tid] = sum;
-    __syncthreads();
-    for (u32 off = 1; off < EXCP_THREADS; off <<= 1) {
-        const u32 v = (tid >= off) ? s_part[tid - off] : 0u;
-        __syncthreads();
-        s_part[tid] += v;
-        __syncthreads();
+    u32 incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const u32 v = __shfl_up(incl, off, WAVE);
+        if (lane_id() >= (u32)off) incl += v;
     }
-    const u32 total = s_part[EXCP_THREADS - 1];
+    if (lane_id() == 63u) s_wave[tid >> 6] = incl;
+    __syncthreads();
+    u32 run = incl - sum, total = 0;
+    for (u32 q = 0; q < SM_THREADS / 64u; ++q) { if (q < (tid >> 6)) run += s_wave[q]; total += s_wave[q]; }
     const u32 H = total >> 16, ns_light = total & 0xffffu;
     const u32 S = NBKT - 1u - 2u * H;                      // H <= 64, so S >= 127
-    u32 run = s_part[tid] - sum;
     u32 *out = w.km_split + (u64)sidx * EXCP_KM_MAP_WORDS;
     if (tid < 4) out[tid] = s_map[tid];
 #pragma unroll
@@ -1322,7 +1344,7 @@ void launch_km_partition(const Workspace &w, const GroupParams &g, int phase, hi
     if (!g.ntensors) return;
     const u32 nseg = 3 * g.ntensors;
     switch (phase) {
-        case 0: hipLaunchKernelGGL(k_km_sample, dim3(nseg), dim3(EXCP_THREADS), 0, s, w, g); break;
+        case 0: hipLaunchKernelGGL(k_km_sample, dim3(nseg), dim3(SM_THREADS), 0, s, w, g); break;
         case 1: hipLaunchKernelGGL(k_km_clear_counts, dim3(excp_grid(w, 8)), dim3(EXCP_THREADS), 0, s, w, g); break;
         case 2:
             hipLaunchKernelGGL(k_km_scan_parts, dim3(nseg * SCAN_PARTS), dim3(1024), 0, s, w, g);

@@ -1,11 +1,12 @@
 // Full-tensor statistics for the pruning thresholds of Sec. 3.2:
 //   * the lower median of |W_t - W_prev| per tensor (Eq. "r_w"), exactly, in ONE pass over the
-//     tensor: a sorted sample of 8192 residuals brackets the median between two keys lo <= hi; the
-//     streaming pass counts the keys below lo and collects the few per cent of keys inside the
-//     bracket; a radix-histogram select (LDS histograms, 11 bits per pass) over those candidates
-//     then finds the order statistic.  The bracket can miss (probability about 2e-5 per tensor, or
-//     adversarial data); the counts reveal that, and the tensor then takes the always-correct
-//     fallback: a three-pass radix-histogram select over the whole tensor (11 + 11 + 9 key bits);
+//     tensor: two order statistics of a sample of 8192 residuals bracket the median between two
+//     keys lo <= hi; the streaming pass counts the keys below lo and collects the few per cent of
+//     keys inside the bracket; a radix-histogram select (LDS histograms, 11 bits per pass) over those
+//     candidates then finds the order statistic.  The bracket can miss (probability about 2e-5 per
+//     tensor, or adversarial data); the counts reveal that, and the tensor then takes the
+//     always-correct fallback in the same three passes: a radix-histogram select over the whole
+//     tensor (11 + 11 + 9 key bits);
 //   * the exact sum of |m| per tensor (Eq. "r_o") by integer accumulation: every |m_i| is
 //     mant * 2^(pos-149).  The sample fixes a window of 24 bit positions per tensor that holds
 //     practically every value; inside it a value is a multiple of one unit below 2^48 units, so a
@@ -16,86 +17,167 @@
 //   * non-finite detection on W_prev, W_t, m and the residual.
 #include "excp_util.h"
 
+#include <algorithm>
+
 namespace {
 
 constexpr u32 MED_SAMPLE = 8192;      // sample size (and the size up to which a tensor is simply sorted)
 constexpr u32 MED_HALF_WIDTH = 192;   // bracket = sample ranks 4096 -+ 192 (about 4.2 sigma of the sample rank)
 constexpr u32 CAND_STAGE = 2048;       // candidates a wave stages in LDS (it flushes when fewer than 1024 places are left)
-constexpr u32 MED_THREADS = 1024;     // workgroup of the sampling kernel: one per tensor, so its own latency is the kernel's
+constexpr u32 MED_THREADS = 1024;     // workgroup of the bracket kernel: one per tensor, so its own latency is the kernel's
 
 enum { MED_PENDING = 0, MED_KNOWN = 1, MED_FALLBACK = 2 };
 
-__device__ __forceinline__ void sort_keys_lds(u32 *key, u32 count_pow2) {
-    const u32 tid = threadIdx.x;
-    for (u32 k = 2; k <= count_pow2; k <<= 1) {
-        for (u32 j = k >> 1; j > 0; j >>= 1) {
-            for (u32 t = tid; t < count_pow2 / 2; t += MED_THREADS) {
-                u32 i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
-                u32 p = i | j;
-                u32 a = key[i], b = key[p];
-                bool asc = (i & k) == 0;
-                if ((a > b) == asc) { key[i] = b; key[p] = a; }
-            }
-            __syncthreads();
-        }
-    }
-}
-
-// One workgroup per tensor: sample (or all) residual magnitudes, sorted.
-__global__ __launch_bounds__(MED_THREADS) void k_median_sample(Workspace w, GroupParams g) {
-    __shared__ u32 key[MED_SAMPLE];
+// The sample (all residual magnitudes of a tensor that is no larger): sixteen workgroups per tensor, because
+// what it costs is the latency of 8192 loads from as many pages, and one compute unit overlaps few of those
+// (16.8 M elements: 40 us of loads from one workgroup).
+__global__ __launch_bounds__(EXCP_THREADS) void k_median_sample(Workspace w, GroupParams g) {
+    constexpr u32 PART = MED_SAMPLE / EXCP_SAMPLE_PARTS, PER = PART / EXCP_THREADS;
     __shared__ u32 s_mmax;
-    const u32 t = blockIdx.x, tid = threadIdx.x;
+    const u32 t = blockIdx.x / EXCP_SAMPLE_PARTS, part = blockIdx.x % EXCP_SAMPLE_PARTS, tid = threadIdx.x;
     const TDesc &D = w.desc[t];
-    TState &S = w.st[t];
     const u64 n = D.n;
-    if (n == 0) { if (tid == 0) { S.med_bits = 0; S.med_state = MED_KNOWN; } return; }
+    const u32 ns = n < MED_SAMPLE ? (u32)n : MED_SAMPLE;
+    if (part * PART >= ns) return;
     if (tid == 0) s_mmax = 0;
     __syncthreads();
-    const u32 ns = n < MED_SAMPLE ? (u32)n : MED_SAMPLE;
+    const u32 wt = excp_wtype(g.flags);
     u32 mmax = 0;                                   // largest finite |m| pattern of the sample
 #pragma unroll
-    for (u32 i = tid; i < MED_SAMPLE; i += MED_THREADS) {       // eight samples per thread, their loads side by side
-        u32 k = 0xffffffffu;
+    for (u32 q = 0; q < PER; ++q) {
+        const u32 i = part * PART + q * EXCP_THREADS + tid;
         if (i < ns) {
             const u64 idx = n <= MED_SAMPLE ? (u64)i : ((u64)i * n) / MED_SAMPLE;
-            const u32 wt = excp_wtype(g.flags);
             const float wv = load_weight(D.W, idx, wt);
-            k = f2u((g.flags & 1u) ? wv : wv - load_weight(D.Wp, idx, wt)) & 0x7fffffffu;   // flag: median of |W_t|
-            const u32 mb = f2u(D.m[idx]) & 0x7fffffffu;
-            if (mb < 0x7f800000u) mmax = max(mmax, mb);
+            w.sample[(u64)t * MED_SAMPLE + i] = f2u((g.flags & 1u) ? wv : wv - load_weight(D.Wp, idx, wt)) & 0x7fffffffu;   // flag: median of |W_t|
+            if (q == 0) {                           // (half of them place the window of the exact sum well enough)
+                const u32 mb = f2u(D.m[idx]) & 0x7fffffffu;
+                if (mb < 0x7f800000u) mmax = max(mmax, mb);
+            }
         }
-        key[i] = k;
     }
     mmax = wave_max_u32(mmax);
     if ((tid & 63u) == 0) atomicMax(&s_mmax, mmax);
     __syncthreads();
-    sort_keys_lds(key, MED_SAMPLE);
+    if (tid == 0) w.sample_mmax[t * EXCP_SAMPLE_PARTS + part] = s_mmax;
+}
+
+// One workgroup per tensor: the two order statistics of the sample that bracket the median (the median itself of
+// a small tensor), by a radix select over both ranks at once: 11 + 10 + 10 key bits, LDS histograms scanned by
+// the whole workgroup.  (A full sort of the sample, 91 barrier rounds, took 58 us; this takes about 8.)
+__global__ __launch_bounds__(MED_THREADS) void k_median_bracket(Workspace w, GroupParams g) {
+    __shared__ u32 hist[2][2048];
+    __shared__ u32 s_wave[MED_THREADS / 64];
+    __shared__ u32 s_bin[2], s_rank[2], s_natoms, s_atom[64], s_acnt[64];
+    constexpr u32 PER = MED_SAMPLE / MED_THREADS;
+    const u32 t = blockIdx.x, tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const TDesc &D = w.desc[t];
+    TState &S = w.st[t];
+    const u64 n = D.n;
+    if (n == 0) { if (tid == 0) { S.med_bits = 0; S.med_state = MED_KNOWN; } return; }
+    const u32 ns = n < MED_SAMPLE ? (u32)n : MED_SAMPLE;
+    u32 key[PER];
+#pragma unroll
+    for (u32 j = 0; j < PER; ++j) {
+        const u32 i = j * MED_THREADS + tid;
+        key[j] = i < ns ? w.sample[(u64)t * MED_SAMPLE + i] : 0xffffffffu;      // (never a key: those have 31 bits)
+    }
+    const bool whole = n <= MED_SAMPLE;
+    u32 pref[2] = {0u, 0u}, rank[2];
+    rank[0] = whole ? (ns - 1u) >> 1 : MED_SAMPLE / 2 - MED_HALF_WIDTH;
+    rank[1] = whole ? rank[0] : MED_SAMPLE / 2 + MED_HALF_WIDTH;
+#pragma unroll
+    for (u32 pass = 0; pass < 3; ++pass) {
+        const u32 shift = pass == 0 ? 20u : (pass == 1 ? 10u : 0u), width = pass == 0 ? 11u : 10u;
+#pragma unroll
+        for (u32 i = tid; i < 2u * 2048u; i += MED_THREADS) (&hist[0][0])[i] = 0;
+        __syncthreads();
+        const bool apart = pref[0] != pref[1];           // else both ranks are looked for in the first histogram
+#pragma unroll
+        for (u32 j = 0; j < PER; ++j) {
+            const u32 k = key[j], bin = (k >> shift) & ((1u << width) - 1u);
+            if (k != 0xffffffffu) {
+                const u32 up = pass == 0 ? 0u : k >> (shift + width);
+                if (up == pref[0]) atomicAdd(&hist[0][bin], 1u);
+                else if (apart && up == pref[1]) atomicAdd(&hist[1][bin], 1u);
+            }
+        }
+        __syncthreads();
+        // both histograms scanned together, 16 bits each (at most 8192 keys)
+        const u32 *h1 = apart ? hist[1] : hist[0];
+        const u32 c0 = hist[0][2u * tid] | (h1[2u * tid] << 16), c1 = hist[0][2u * tid + 1u] | (h1[2u * tid + 1u] << 16);
+        u32 incl = c0 + c1;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const u32 v = __shfl_up(incl, off, WAVE);
+            if (lane >= (u32)off) incl += v;
+        }
+        if (lane == 63u) s_wave[wave] = incl;
+        __syncthreads();
+        u32 before = incl - c0 - c1;
+        for (u32 q = 0; q < wave; ++q) before += s_wave[q];
+#pragma unroll
+        for (u32 h = 0; h < 2; ++h) {
+            const u32 lo = (before >> (16u * h)) & 0xffffu, n0 = (c0 >> (16u * h)) & 0xffffu, n1 = (c1 >> (16u * h)) & 0xffffu;
+            if (rank[h] >= lo && rank[h] < lo + n0 + n1) {            // exactly one thread
+                const bool second = rank[h] >= lo + n0;
+                s_bin[h] = 2u * tid + (second ? 1u : 0u);
+                s_rank[h] = rank[h] - lo - (second ? n0 : 0u);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (u32 h = 0; h < 2; ++h) { pref[h] = (pref[h] << width) | s_bin[h]; rank[h] = s_rank[h]; }
+    }
+    const u32 klo = pref[0], khi = pref[1];
+    // 16-bit weights: residuals are few distinct values.  Up to four values of the bracket that fill at least 32
+    // places of the sample (0.4 % of the tensor) are counted during the streaming pass instead of being listed one
+    // by one.  They are found by hashing the bracket's keys: a cell keeps one of its keys and counts that one
+    // (a heavy value that loses its cell to another is listed like the rest: slower, no less exact).
+    const bool atoms = (g.flags & 0x30u) && !whole && klo != khi;
+    if (atoms) {                                         // the same in the whole workgroup
+        u32 *rep = hist[0], *cnt = hist[1];
+        auto cell = [](u32 k) { return (k * 2654435761u) >> 21; };
+        for (u32 i = tid; i < 2048u; i += MED_THREADS) cnt[i] = 0;
+        if (tid == 0) s_natoms = 0;
+#pragma unroll
+        for (u32 j = 0; j < PER; ++j) if (key[j] - klo <= khi - klo) rep[cell(key[j])] = key[j];
+        __syncthreads();
+#pragma unroll
+        for (u32 j = 0; j < PER; ++j) if (key[j] - klo <= khi - klo && rep[cell(key[j])] == key[j]) atomicAdd(&cnt[cell(key[j])], 1u);
+        __syncthreads();
+        for (u32 i = tid; i < 2048u; i += MED_THREADS) {
+            if (cnt[i] >= 32u) {
+                const u32 at = atomicAdd(&s_natoms, 1u);
+                if (at < 64u) { s_atom[at] = rep[i]; s_acnt[at] = cnt[i]; }
+            }
+        }
+        __syncthreads();
+    }
     if (tid == 0) {
         // window of the exact sum: its top sits 4 binary orders above the largest sampled |m|
-        const u32 e = s_mmax >> 23;
+        u32 mmax = 0;
+        for (u32 q = 0; q < (ns + MED_SAMPLE / EXCP_SAMPLE_PARTS - 1u) / (MED_SAMPLE / EXCP_SAMPLE_PARTS); ++q)
+            mmax = max(mmax, w.sample_mmax[t * EXCP_SAMPLE_PARTS + q]);
+        const u32 e = mmax >> 23;
         const u32 pos = (e ? e : 1u) - 1u;
         S.absm_base = pos + 4u > 23u ? min(pos + 4u - 23u, 230u) : 0u;
-        if (n <= MED_SAMPLE) {
-            S.med_bits = key[(n - 1) >> 1];
+        if (whole) {
+            S.med_bits = klo;
             S.med_state = MED_KNOWN;
         } else {
-            const u32 a = MED_SAMPLE / 2 - MED_HALF_WIDTH, b = MED_SAMPLE / 2 + MED_HALF_WIDTH;
-            S.br_lo = key[a];
-            S.br_hi = key[b];
+            S.br_lo = klo;
+            S.br_hi = khi;
             S.med_state = MED_PENDING;
-            // 16-bit weights: residuals are few distinct values.  Up to four values of the bracket
-            // that fill at least 32 places of the sorted sample (0.4 % of the tensor) are counted
-            // during the streaming pass instead of being listed one by one.
             u32 na = 0;
-            if ((g.flags & 0x30u) && key[a] != key[b]) {
-                for (u32 i = a; i <= b && na < 4u;) {
-                    const u32 kv = key[i];
-                    u32 j0 = i, j1 = i;
-                    while (j0 > 0u && key[j0 - 1u] == kv) --j0;
-                    while (j1 + 1u < MED_SAMPLE && key[j1 + 1u] == kv) ++j1;
-                    if (j1 - j0 + 1u >= 32u) S.atom_key[na++] = kv;
-                    i = j1 + 1u;
+            if (atoms) {                                 // the four most frequent
+                const u32 have = min(s_natoms, 64u);
+                for (; na < 4u; ++na) {
+                    u32 best = 0;
+                    for (u32 i = 1; i < have; ++i) if (s_acnt[i] > s_acnt[best]) best = i;
+                    if (best >= have || s_acnt[best] == 0u) break;
+                    S.atom_key[na] = s_atom[best];
+                    s_acnt[best] = 0;
                 }
             }
             S.natoms = na;
@@ -369,7 +451,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_stats_stream(Workspace w, Grou
 __global__ __launch_bounds__(EXCP_THREADS) void k_stats_finish(Workspace w, GroupParams g, u32 G) {
     __shared__ u64 bins[EXCP_ABSM_BINS];
     __shared__ u64 s_u64[3];
-    __shared__ u32 s_u32[6];
+    __shared__ u32 s_u32[7];
     const u32 t = blockIdx.x, tid = threadIdx.x, lane = tid & 63u;
     TState &S = w.st[t];
     const TDesc &D = w.desc[t];
@@ -379,9 +461,10 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_stats_finish(Workspace w, Grou
         return;
     }
     if (tid < 3) s_u64[tid] = 0;
-    if (tid < 6) s_u32[tid] = 0;
+    if (tid < 7) s_u32[tid] = 0;
     if (tid < EXCP_ABSM_BINS) bins[tid] = S.absm[tid];
     __syncthreads();
+    if (tid < D.cand_lists) atomicAdd(&s_u32[6], w.cand_ctr[(u64)t * 512u + tid * 32u + 1u]);      // listed candidates
     u64 L = 0, H = 0, nf = 0;
     u32 clt = 0, cc = 0, atom[4] = {0u, 0u, 0u, 0u};
     auto take = [&](const StatPart &P) {
@@ -394,10 +477,9 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_stats_finish(Workspace w, Grou
     if (b0 == b1) {
         if (tid == 0) take(S.part);
     } else {
-        for (u32 b = b0 + tid; b <= b1; b += EXCP_THREADS) {
-            const u32 lo = stats_lo(b, G, g.ntiles);
-            if (lo < stats_lo(b + 1u, G, g.ntiles)) take(w.stat_part[2u * b + (tb <= lo ? 0u : 1u)]);
-        }
+        const u32 slot0 = tb <= stats_lo(b0, G, g.ntiles) ? 0u : 1u;       // (the others start inside the tensor)
+        for (u32 b = b0 + tid; b <= b1; b += EXCP_THREADS)
+            if (g.ntiles >= G || stats_lo(b, G, g.ntiles) < stats_lo(b + 1u, G, g.ntiles)) take(w.stat_part[2u * b + (b == b0 ? slot0 : 0u)]);
     }
     L = wave_sum_u64(L); H = wave_sum_u64(H); nf = wave_sum_u64(nf);
     clt = wave_sum_u32(clt); cc = wave_sum_u32(cc);
@@ -438,8 +520,8 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_stats_finish(Workspace w, Grou
             if (r >= below && r < below + cnt) { S.med_bits = S.br_lo; S.med_state = MED_KNOWN; }
             else S.med_state = MED_FALLBACK;
         } else {
-            u64 cnt = 0, counted = 0;          // listed candidates; bracket values that were counted instead of listed
-            for (u32 j = 0; j < D.cand_lists; ++j) cnt += w.cand_ctr[(u64)t * 512u + j * 32u + 1u];
+            const u64 cnt = s_u32[6];
+            u64 counted = 0;                   // bracket values that were counted instead of listed
             S.cand_count = (u32)cnt;
 #pragma unroll
             for (u32 q = 0; q < 4; ++q) { S.atom_cnt[q] = s_u32[2 + q]; if (q < S.natoms) counted += s_u32[2 + q]; }
@@ -455,191 +537,147 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_stats_finish(Workspace w, Grou
     S.t_w = __fmul_rn(g.alpha, u2f(S.med_bits));          // (final where the median is known by now)
 }
 
-// One radix pass over the candidates: histogram of the top (up to 11) undecided bits.  A workgroup
-// takes the candidates that belong to 256 consecutive tiles of the group's tile list -- for each
-// tensor it meets, the matching share of that tensor's candidate list -- so that its LDS histogram
-// is flushed once per tensor it meets and not once per tensor of the group.
-constexpr u32 CAND_TILES = 256;
+// The exact median: three radix passes, each one launch for all tensors.  A tensor whose bracket held takes its
+// candidates through the top (up to 11) undecided bits of the bracket's span per pass; one whose bracket
+// missed takes all its keys through 11 + 11 + 9 key bits.  A workgroup does the share that belongs to
+// SEL_TILES consecutive tiles of the group's tile list, tensor by tensor, and the last of a tensor's workgroups
+// to finish resolves the pass: its counts are complete then, so no second launch is needed (this and one path for
+// both kinds of tensor replace twelve launches by three).
+// SEL_TILES: about 512 workgroups, with 32 tiles at least (fewer would leave a workgroup a few hundred candidates) and
+// 256 at most (a workgroup's histogram goes to memory with up to 2048 atomics).
+static u32 sel_tiles(u32 ntiles) { return std::min(std::max(ntiles / 512u, 32u), 256u); }
 
-__global__ __launch_bounds__(EXCP_THREADS) void k_cand_hist(Workspace w, GroupParams g) {
+__global__ __launch_bounds__(EXCP_THREADS) void k_median_select(Workspace w, GroupParams g, u32 pass, u32 SEL_TILES) {
+    __shared__ u32 s_tiles[EXCP_MAX_GROUP_TENSORS + 1];
     __shared__ u32 hist[2048];
-    const u32 tid = threadIdx.x;
-    const u32 lo = blockIdx.x * CAND_TILES, hi = min(lo + CAND_TILES, g.ntiles);
-    if (lo >= hi) return;
+    __shared__ u32 s_wave[EXCP_THREADS / 64], s_ticket, s_state[EXCP_THREADS];
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const u32 lo = blockIdx.x * SEL_TILES, hi = min(lo + SEL_TILES, g.ntiles);
     for (u32 i = tid; i < 2048; i += EXCP_THREADS) hist[i] = 0;
+    load_tile_table(s_tiles, w.tile_begin, g.ntensors);
+    u32 t = find_owner(s_tiles, g.ntensors, lo);
+    const u32 t0 = t;                                     // the states of the first 256 tensors, read side by side
+    if (t0 + tid < g.ntensors) s_state[tid] = w.st[t0 + tid].med_state;
     __syncthreads();
-    u32 t = find_owner(w.tile_begin, g.ntensors, lo);
     for (u32 a0 = lo; a0 < hi; ++t) {
-        const u32 tb = w.tile_begin[t], te = w.tile_begin[t + 1];
+        const u32 tb = s_tiles[t], te = s_tiles[t + 1];
         const u32 a1 = min(te, hi);                       // this workgroup's tiles of tensor t: [a0, a1)
-        const TState &S = w.st[t];
-        if (a1 > a0 && S.med_state == MED_PENDING && S.sel_width != 0) {
-            const u32 base = S.sel_base, width = S.sel_width;
-            const u32 shift = width > 11u ? width - 11u : 0u;
-            const u64 limit = 1ull << width;
+        const u32 b0 = a0;
+        a0 = a1;
+        if (a1 <= b0) continue;
+        TState &S = w.st[t];
+        const u32 state = t - t0 < EXCP_THREADS ? s_state[t - t0] : S.med_state;
+        if (state == MED_KNOWN) continue;                 // the same for the whole workgroup
+        const TDesc &D = w.desc[t];
+        const u32 base = S.sel_base, rank = S.sel_rank;
+        const u32 cwidth = S.sel_width, cshift = cwidth > 11u ? cwidth - 11u : 0u;     // candidates
+        const u32 fshift = pass == 0u ? 20u : (pass == 1u ? 9u : 0u);                  // all keys
+        if (state == MED_PENDING) {
+            const u64 limit = 1ull << cwidth;
             const u32 tc = te - tb;
-            const u32 L = w.desc[t].cand_lists, cap = (u32)(w.desc[t].cand_cap / L);
-            auto tally = [&](u32 key) {
-                const u32 rel = key - base;               // keys below base wrap around and drop out
-                if ((u64)rel < limit) atomicAdd(&hist[rel >> shift], 1u);
-            };
-            for (u32 j = 0; j < L; ++j) {
-                const u32 cnt = w.cand_ctr[(u64)t * 512u + j * 32u + 1u];
-                const u32 i0 = (u32)(((u64)cnt * (a0 - tb)) / tc), i1 = (u32)(((u64)cnt * (a1 - tb)) / tc);
-                const EXCP_GLOBAL u32 *c = gptr(w.cand) + w.desc[t].cand_off + (u64)j * cap;
-                for (u32 q0 = i0; q0 < i1; q0 += 4u * EXCP_THREADS) {
-                    if (q0 + 4u * EXCP_THREADS <= i1) {
-                        u32 k[4];
+            const u32 L = D.cand_lists, cap = (u32)(D.cand_cap / L);
+            const u32 *ctr = w.cand_ctr + (u64)t * 512u;
+            // the workgroup's share of every list; a wave takes every fourth list
+            for (u32 j = L >= 4u ? wave : 0u; j < L; j += L >= 4u ? 4u : 1u) {
+                const u32 cnt = ctr[j * 32u + 1u];
+                const u32 i0 = (u32)(((u64)cnt * (b0 - tb)) / tc), i1 = (u32)(((u64)cnt * (a1 - tb)) / tc);
+                const EXCP_GLOBAL u32 *c = gptr(w.cand) + D.cand_off + (u64)j * cap;
+                const u32 first = L >= 4u ? lane : tid, step = L >= 4u ? 64u : EXCP_THREADS;
+                for (u32 i = i0 + first; i < i1; i += 8u * step) {
+                    u32 k[8];
 #pragma unroll
-                        for (u32 jj = 0; jj < 4; ++jj) k[jj] = c[q0 + jj * EXCP_THREADS + tid];
+                    for (u32 q = 0; q < 8; ++q) k[q] = i + q * step < i1 ? c[i + q * step] : base - 1u;
 #pragma unroll
-                        for (u32 jj = 0; jj < 4; ++jj) tally(k[jj]);
-                    } else {
-                        for (u32 i = q0 + tid; i < i1; i += EXCP_THREADS) tally(c[i]);
+                    for (u32 q = 0; q < 8; ++q) {
+                        const u32 rel = k[q] - base;      // keys below base wrap around and drop out
+                        if ((u64)rel < limit) atomicAdd(&hist[rel >> cshift], 1u);
                     }
                 }
             }
-            __syncthreads();
-            for (u32 i = tid; i < 2048; i += EXCP_THREADS) {
-                const u32 v = hist[i];
-                if (v) { atomicAdd(&w.med_hist[(u64)t * 2048u + i], v); hist[i] = 0; }
-            }
-            __syncthreads();
-        }
-        a0 = a1;
-    }
-}
-
-__global__ __launch_bounds__(EXCP_THREADS) void k_cand_resolve(Workspace w, GroupParams g) {
-    __shared__ u32 s_sum[EXCP_THREADS];
-    const u32 t = blockIdx.x, tid = threadIdx.x;
-    TState &S = w.st[t];
-    if (S.med_state != MED_PENDING || S.sel_width == 0) return;
-    u32 *H = w.med_hist + (u64)t * 2048u;
-    const u32 width = S.sel_width, shift = width > 11u ? width - 11u : 0u, rank = S.sel_rank, base = S.sel_base;
-    if (tid == 0) {
-        // the counted bracket values join the listed candidates, each with its multiplicity
-        for (u32 q = 0; q < S.natoms; ++q) {
-            const u32 rel = S.atom_key[q] - base;
-            if ((u64)rel < (1ull << width)) H[rel >> shift] += S.atom_cnt[q];
-        }
-    }
-    __syncthreads();
-    u32 c[8], local = 0;
+        } else {
+            const u64 n = D.n;
+            const u32 wt = excp_wtype(g.flags);
+            const bool of_weights = (g.flags & 1u) != 0u;
+            for (u32 tile = b0; tile < a1; ++tile) {
+                const u64 first = (u64)(tile - tb) * EXCP_TILE;
+                const u32 rem = (n - first < (u64)EXCP_TILE) ? (u32)(n - first) : EXCP_TILE;
+                // (this path is taken for heavily tied data above all: see hist_add_tied)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) { c[i] = H[tid * 8 + i]; local += c[i]; H[tid * 8 + i] = 0; }
-    s_sum[tid] = local;
-    __syncthreads();
-    for (int off = 1; off < EXCP_THREADS; off <<= 1) {
-        u32 v = (tid >= (u32)off) ? s_sum[tid - off] : 0u;
-        __syncthreads();
-        s_sum[tid] += v;
-        __syncthreads();
-    }
-    const u32 before = s_sum[tid] - local;
-    if (rank >= before && rank < before + local) {           // exactly one thread
-        u32 r = rank - before;
-        int i = 0;
-        while (r >= c[i]) { r -= c[i]; ++i; }
-        const u32 nb = base + ((u32)(tid * 8 + i) << shift);
-        S.sel_base = nb;
-        S.sel_width = shift;
-        S.sel_rank = r;
-        if (shift == 0) { S.med_bits = nb; S.med_state = MED_KNOWN; S.t_w = __fmul_rn(g.alpha, u2f(nb)); }
-    }
-}
-
-// ---------------------------------------------------------------- fallback: select over the whole tensor
-template <int PASS>
-__global__ __launch_bounds__(EXCP_THREADS) void k_full_hist(Workspace w, GroupParams g) {
-    constexpr int NB = (PASS == 2) ? 512 : 2048;
-    __shared__ u32 hist[NB];
-    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const u32 G = gridDim.x, b = blockIdx.x;
-    const u32 lo = (u32)(((u64)b * g.ntiles) / G), hi = (u32)(((u64)(b + 1) * g.ntiles) / G);
-    if (lo >= hi) return;
-    for (u32 i = tid; i < NB; i += EXCP_THREADS) hist[i] = 0;
-    __syncthreads();
-    u32 t = find_owner(w.tile_begin, g.ntensors, lo);
-    u32 t_end = w.tile_begin[t + 1];
-    bool active = w.st[t].med_state == MED_FALLBACK;
-    auto flush = [&](u32 tt) {
-        __syncthreads();
-        if (active)
-            for (u32 i = tid; i < NB; i += EXCP_THREADS) {
-                u32 c = hist[i];
-                if (c) { atomicAdd(&w.med_hist[(u64)tt * 2048u + i], c); hist[i] = 0; }
-            }
-        __syncthreads();
-    };
-    for (u32 tile = lo; tile < hi; ++tile) {
-        if (tile >= t_end) {
-            flush(t);
-            t = find_owner(w.tile_begin, g.ntensors, tile);
-            t_end = w.tile_begin[t + 1];
-            active = w.st[t].med_state == MED_FALLBACK;
-        }
-        if (!active) { tile = t_end - 1; continue; }          // skip the rest of this tensor
-        const TDesc &D = w.desc[t];
-        const u64 n = D.n;
-        const u64 base = (u64)(tile - D.tile_begin) * EXCP_TILE;
-        const u32 prefix = PASS > 0 ? w.st[t].sel_base : 0u;
-        // (this path is taken for heavily tied data above all: see hist_add_tied)
-        const u32 rem = (n - base < (u64)EXCP_TILE) ? (u32)(n - base) : EXCP_TILE;
-        const u32 wt = excp_wtype(g.flags);
-        const bool of_weights = (g.flags & 1u) != 0u;
+                for (int q = 0; q < 4; ++q) {
+                    const u32 off = wave * 1024u + (u32)q * 256u + lane * 4u;
+                    float a[4], pv[4] = {0.f, 0.f, 0.f, 0.f};
+                    load_weights4(D.W, first, off, rem, wt, a);
+                    if (!of_weights) load_weights4(D.Wp, first, off, rem, wt, pv);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const u32 off = wave * 1024u + (u32)q * 256u + lane * 4u;
-            float a[4], pv[4] = {0.f, 0.f, 0.f, 0.f};
-            load_weights4(D.W, base, off, rem, wt, a);
-            if (!of_weights) load_weights4(D.Wp, base, off, rem, wt, pv);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bool act = off + (u32)j < rem;
-                const u32 k = f2u(a[j] - pv[j]) & 0x7fffffffu;
-                if (PASS == 0) hist_add_tied(hist, k >> 20, act);
-                if (PASS == 1) hist_add_tied(hist, (k >> 9) & 2047u, act && (k >> 20) == prefix);
-                if (PASS == 2) hist_add_tied(hist, k & 511u, act && (k >> 9) == prefix);
+                    for (int j = 0; j < 4; ++j) {
+                        const u32 k = f2u(a[j] - pv[j]) & 0x7fffffffu;
+                        const bool act = off + (u32)j < rem && (pass == 0u || (k >> (pass == 1u ? 20u : 9u)) == base);
+                        hist_add_tied(hist, (k >> fshift) & (pass == 2u ? 511u : 2047u), act);
+                    }
+                }
             }
         }
-    }
-    flush(t);
-}
-
-template <int PASS>
-__global__ __launch_bounds__(EXCP_THREADS) void k_full_resolve(Workspace w, GroupParams g) {
-    constexpr int NB = (PASS == 2) ? 512 : 2048;
-    constexpr int PER = NB / EXCP_THREADS;
-    __shared__ u32 s_sum[EXCP_THREADS];
-    const u32 t = blockIdx.x, tid = threadIdx.x;
-    const u64 n = w.desc[t].n;
-    TState &S = w.st[t];
-    if (S.med_state != MED_FALLBACK) return;
-    u32 *H = w.med_hist + (u64)t * 2048u;
-    const u32 rank = (PASS == 0) ? (u32)((n - 1) >> 1) : S.sel_rank;
-    const u32 prefix = (PASS == 0) ? 0u : S.sel_base;
-    u32 c[PER], local = 0;
+        __syncthreads();
+        u32 *H = w.med_hist + (u64)t * 2048u;
+        for (u32 i = tid; i < 2048; i += EXCP_THREADS) {
+            const u32 v = hist[i];
+            if (v) { atomicAdd(&H[i], v); hist[i] = 0; }
+        }
+        // The last of the tensor's workgroups sees everybody's counts: they are only ever touched by device-scope
+        // atomics, which are done (vmcnt) before the ticket is drawn.  (A __threadfence here would write back the
+        // whole L2 for every workgroup: 302 us a pass instead of 53 for 1.07e9 elements in 4080 workgroups.)
+        const u32 parts = (te - 1u) / SEL_TILES - tb / SEL_TILES + 1u;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) s_ticket = parts == 1u ? 0u : atomicAdd(&w.sel_ticket[t], 1u);
+        __syncthreads();
+        if (s_ticket != parts - 1u) continue;
+        u32 c[8], local = 0;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) { c[i] = H[tid * PER + i]; local += c[i]; H[tid * PER + i] = 0; }
-    s_sum[tid] = local;
-    __syncthreads();
-    for (int off = 1; off < EXCP_THREADS; off <<= 1) {
-        u32 v = (tid >= (u32)off) ? s_sum[tid - off] : 0u;
+        for (int i = 0; i < 8; ++i) c[i] = __hip_atomic_load(&H[tid * 8 + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (state == MED_PENDING) {
+            // the counted bracket values join the listed candidates, each with its multiplicity
+            for (u32 q = 0; q < S.natoms; ++q) {
+                const u32 rel = S.atom_key[q] - base, bin = rel >> cshift;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) if ((u64)rel < (1ull << cwidth) && bin == tid * 8u + (u32)i) c[i] += S.atom_cnt[q];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { local += c[i]; H[tid * 8 + i] = 0; }
+        u32 incl = local;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const u32 v = __shfl_up(incl, off, WAVE);
+            if (lane >= (u32)off) incl += v;
+        }
+        if (lane == 63u) s_wave[wave] = incl;
+        if (tid == 0) w.sel_ticket[t] = 0;
         __syncthreads();
-        s_sum[tid] += v;
+        u32 before = incl - local;
+        for (u32 q = 0; q < wave; ++q) before += s_wave[q];
+        const u32 want = (state == MED_FALLBACK && pass == 0u) ? (u32)((D.n - 1ull) >> 1) : rank;
+        if (want >= before && want < before + local) {            // exactly one thread
+            u32 r = want - before;
+            u32 i = 0;
+#pragma unroll
+            for (u32 q = 0; q < 7; ++q) if (i == q && r >= c[q]) { r -= c[q]; ++i; }
+            const u32 bin = tid * 8u + i;
+            u32 nb;
+            bool done;
+            if (state == MED_PENDING) {
+                nb = base + (bin << cshift);
+                done = cshift == 0u;
+                S.sel_width = cshift;
+            } else {
+                nb = pass == 0u ? bin : (base << (pass == 2u ? 9u : 11u)) | bin;
+                done = pass == 2u;
+            }
+            S.sel_base = nb;
+            S.sel_rank = r;
+            if (done) { S.med_bits = nb; S.med_state = MED_KNOWN; S.t_w = __fmul_rn(g.alpha, u2f(nb)); }
+        }
         __syncthreads();
-    }
-    const u32 before = s_sum[tid] - local;
-    if (rank >= before && rank < before + local) {           // exactly one thread
-        u32 r = rank - before;
-        int i = 0;
-        while (r >= c[i]) { r -= c[i]; ++i; }
-        const u32 bin = tid * PER + i;
-        const u32 np = (PASS == 2) ? ((prefix << 9) | bin) : ((prefix << 11) | bin);
-        S.sel_base = np;
-        S.sel_rank = r;
-        if (PASS == 2) { S.med_bits = np; S.med_state = MED_KNOWN; S.t_w = __fmul_rn(g.alpha, u2f(np)); }
     }
 }
 
@@ -672,28 +710,27 @@ void launch_zero_u32(u32 *p, u64 count, hipStream_t s) {
     hipLaunchKernelGGL(k_zero_u32, dim3((u32)blocks), dim3(256), 0, s, p, count);
 }
 
-// phase 0: sample, 1: streaming pass, 2: its records added up, bracket check, thresholds, 3: candidate
-// histogram, 4: candidate resolve, 5..7: fallback histograms, 8..10: fallback resolves
+// phase 0: sample and bracket, 1: streaming pass, 2: its records added up, bracket check, thresholds, and the
+// passes that find the median
 void launch_stats(const Workspace &w, const GroupParams &g, int phase, hipStream_t s) {
     if (!g.ntensors) return;
-    const dim3 block(EXCP_THREADS), per_tensor(g.ntensors);
+    const dim3 block(EXCP_THREADS);
     const dim3 stream_grid(excp_grid(w, EXCP_STATS_PER_CU));
     switch (phase) {
-        case 0: hipLaunchKernelGGL(k_median_sample, per_tensor, dim3(MED_THREADS), 0, s, w, g); break;
+        case 0:
+            hipLaunchKernelGGL(k_median_sample, dim3(g.ntensors * EXCP_SAMPLE_PARTS), block, 0, s, w, g);
+            hipLaunchKernelGGL(k_median_bracket, dim3(g.ntensors), dim3(MED_THREADS), 0, s, w, g);
+            break;
         case 1:
             if (!g.ntiles) break;
             if (g.flags & 0x30u) hipLaunchKernelGGL(k_stats_stream<true>, stream_grid, block, 0, s, w, g);
             else hipLaunchKernelGGL(k_stats_stream<false>, stream_grid, block, 0, s, w, g);
             break;
-        case 2: hipLaunchKernelGGL(k_stats_finish, per_tensor, block, 0, s, w, g, stream_grid.x); break;
-        case 3: if (g.ntiles) hipLaunchKernelGGL(k_cand_hist, dim3((g.ntiles + CAND_TILES - 1) / CAND_TILES), block, 0, s, w, g); break;
-        case 4: hipLaunchKernelGGL(k_cand_resolve, per_tensor, block, 0, s, w, g); break;
-        case 5: if (g.ntiles) hipLaunchKernelGGL(k_full_hist<0>, stream_grid, block, 0, s, w, g); break;
-        case 6: if (g.ntiles) hipLaunchKernelGGL(k_full_hist<1>, stream_grid, block, 0, s, w, g); break;
-        case 7: if (g.ntiles) hipLaunchKernelGGL(k_full_hist<2>, stream_grid, block, 0, s, w, g); break;
-        case 8: hipLaunchKernelGGL(k_full_resolve<0>, per_tensor, block, 0, s, w, g); break;
-        case 9: hipLaunchKernelGGL(k_full_resolve<1>, per_tensor, block, 0, s, w, g); break;
-        case 10: hipLaunchKernelGGL(k_full_resolve<2>, per_tensor, block, 0, s, w, g); break;
-        default: break;
+        default:
+            hipLaunchKernelGGL(k_stats_finish, dim3(g.ntensors), block, 0, s, w, g, stream_grid.x);
+            if (!g.ntiles) break;
+            for (u32 pass = 0; pass < 3u; ++pass)
+                hipLaunchKernelGGL(k_median_select, dim3((g.ntiles + sel_tiles(g.ntiles) - 1u) / sel_tiles(g.ntiles)), block, 0, s, w, g, pass, sel_tiles(g.ntiles));
+            break;
     }
 }
