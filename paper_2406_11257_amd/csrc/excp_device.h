@@ -73,9 +73,13 @@ struct TState {
 struct SegState {
     u64 len;
     u32 chunk_begin;            // first chunk of this stream in the group's chunk list
-    u32 pad;
-    float C[EXCP_MAX_K + 1];    // current centres (K used)
-    u32 cut[EXCP_MAX_K + 1];    // cut[k], 1 <= k < K: smallest key whose nearest centre has index >= k
+    u32 row_begin;              // first row of this stream in the table of bucket counts (a row per EXCP_SUPER_CHUNKS chunks)
+    u32 bin_lo, bin_hi;         // the bins of km_bsum that are not all zero lie in [bin_lo, bin_hi]
+    u32 acc_lo, acc_hi;         // sums of any of the stream's values have no other bins than [acc_lo, acc_hi]
+    // centres (K used) and cut keys (cut[k], 1 <= k < K: smallest key whose nearest centre has index >= k) by the
+    // parity of the iteration that made them: iteration i reads those of i - 1 and writes its own
+    float C[2][EXCP_MAX_K + 1];
+    u32 cut[2][EXCP_MAX_K + 1];
 };
 
 // Host-filled description of one tensor of a decompress group.
@@ -129,8 +133,10 @@ struct GroupParams {
     int nbits, K, iters;
     u32 flags;
     u32 ntensors, ntiles;
-    u32 wide;                   // per-bucket kernels with sixteen waves: 1 = tied data (16-bit weights), 2 = a very large
-                                // tensor in the group (then also one bucket per workgroup)
+    u32 unit_chunks;            // chunks of a stream that make up one work unit of a Lloyd iteration
+    u32 wide;                   // per-bucket kernels with sixteen waves: 1 = for the residual streams (16-bit weights: tied
+                                // data), 2 = for all, one bucket per workgroup (a very large tensor in the group)
+    u64 max_units;              // work units the group's streams can have at most (0: every stream is small enough for one workgroup)
 };
 
 #define EXCP_RAW_BITS    32u       // "code" width of a blob written without quantisation: fp32 values, no codebooks
@@ -161,17 +167,15 @@ struct Workspace {
     // survivor passes
     u32 *chunk_total;         // [1]
     u32 *seg_chunk_begin;     // [segments + 1] first chunk of every survivor stream
+    u32 *seg_unit_begin;      // [segments + 1] first work unit of every survivor stream in a Lloyd iteration
     float *pw, *pm, *pv;      // survivors partitioned into value-ordered buckets (same offsets as xw/xm/xv)
     u32 *km_split;            // [segment][EXCP_KM_MAP_WORDS] value -> bucket map: 4 parameters, then 4096 bucket bytes
-    u32 *km_cnt;              // [chunk][256] bucket counts, then positions, of every chunk
+    u32 *km_cnt;              // [row][256] bucket counts, then positions: a row per EXCP_SUPER_CHUNKS chunks of a stream
     u32 *km_begin;            // [segment][257] first position of every bucket
-    u32 *km_part;             // [segment][16][256] bucket counts, then first positions, of each sixteenth of a stream's chunks
-    u64 *km_bsum;             // [segment][256][EXCP_ABSM_BINS] exact signed sum of every bucket
+    u64 *km_bsum;             // [segment][EXCP_ABSM_BINS][257] exact signed sum of every bucket, then of all buckets before it
     u32 *km_min, *km_max;     // [segment][256] smallest / largest key of every bucket
-    u64 *km_acc;              // [segment][EXCP_MAX_K][EXCP_ABSM_BINS + 1] per-centre exact sum and count
-    void *km_items;           // work items of the Lloyd accumulation (cut buckets in pieces)
-    u32 *km_item_count;       // [2] lengths of the two work lists used by alternate iterations
-    u32 km_item_cap;
+    u32 *km_mag;              // [segment][256] smallest non-zero magnitude (bit pattern) of every bucket
+    u64 *km_acc;              // [segment][3][EXCP_ABSM_BINS + 1][K] per-centre exact sum and count, by iteration modulo 3
     double *part_obj;         // [chunk]
     u32 max_chunks;
     // decode
@@ -191,6 +195,9 @@ struct Workspace {
 // measured on its own).
 static inline u32 excp_grid(const Workspace &w, u32 per_cu) { return (u32)w.cus * per_cu; }
 
+// Whether one workgroup takes a tensor's streams through all Lloyd iterations.
+static __host__ __device__ inline bool excp_lloyd_alone(u64 n, u32 K) { return n * (K - 1u) <= (1ull << 27); }
+
 void launch_zero_u32(u32 *p, u64 count, hipStream_t s);
 void launch_copy_probe(const void *src, void *dst, u64 bytes, hipStream_t s);
 void launch_stats(const Workspace &w, const GroupParams &g, int phase, hipStream_t s);
@@ -198,9 +205,7 @@ void launch_mask_compact(const Workspace &w, const GroupParams &g, int phase, hi
 void launch_layout(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_km_partition(const Workspace &w, const GroupParams &g, int phase, hipStream_t s);
 void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s);
-void launch_km_classify(const Workspace &w, const GroupParams &g, int iteration, hipStream_t s);
-void launch_km_iter(const Workspace &w, const GroupParams &g, int iteration, hipStream_t s);
-void launch_km_update(const Workspace &w, const GroupParams &g, hipStream_t s);
+void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_assign_pack(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_finalize(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_decode_from_compress(const Workspace &w, const GroupParams &g, hipStream_t s);

@@ -17,15 +17,16 @@ namespace {
 
 constexpr u32 kMaxGroupTensors = 1024;   // tensors processed together (== EXCP_MAX_GROUP_TENSORS of the kernels)
 constexpr u32 kMaxBatchTensors = 4096;   // tensors per compress / decompress call
+constexpr u64 kAccSegCentres = 3ull * kMaxGroupTensors * 85;   // streams x centres whose accumulators the workspace holds
 
 enum Stage {
-    ST_SAMPLE = 0, ST_STATS, ST_SELECT, ST_MASK_COMPACT, ST_MASK_SCAN, ST_MASK_GATHER, ST_LAYOUT, ST_KM_SAMPLE, ST_KM_COUNT, ST_KM_SCAN,
-    ST_KM_SCATTER, ST_KM_BUCKET_STATS, ST_KM_INIT, ST_KM_CLASSIFY, ST_KM_ITER, ST_KM_UPDATE, ST_ASSIGN_PACK, ST_FINALIZE,
+    ST_SAMPLE = 0, ST_STATS, ST_SELECT, ST_MASK_COMPACT, ST_MASK_SCAN, ST_MASK_GATHER, ST_LAYOUT, ST_KM_SAMPLE, ST_KM_SCAN,
+    ST_KM_SCATTER, ST_KM_BUCKET_STATS, ST_KM_INIT, ST_KM_ITER, ST_ASSIGN_PACK, ST_FINALIZE,
     ST_DECODE_PREP, ST_DECODE_MAIN, ST_EXPORT_DENSE, ST_DECODE_DENSE, ST_MISC, ST_COUNT
 };
 const char *kStageNames[ST_COUNT] = {
-    "median_sample", "stats_stream", "select_candidates", "mask_slots", "mask_scan", "mask_gather", "layout", "km_sample", "km_count", "km_scan",
-    "km_scatter", "km_bucket_stats", "km_init", "km_classify", "km_iter", "km_update", "assign_pack", "finalize",
+    "median_sample", "stats_stream", "select_candidates", "mask_slots", "mask_scan", "mask_gather", "layout", "km_sample", "km_scan",
+    "km_scatter", "km_bucket_stats", "km_init", "km_iter", "assign_pack", "finalize",
     "decode_prep", "decode_main", "export_dense", "decode_dense", "misc"};
 
 struct Span { int stage; hipEvent_t a, b; };
@@ -360,23 +361,20 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.mask_bo, 2 * max_tiles * 32);
     ok = ok && dev_alloc(c, &w.chunk_total, 4);
     ok = ok && dev_alloc(c, &w.seg_chunk_begin, 3ull * kMaxGroupTensors + 4);
+    ok = ok && dev_alloc(c, &w.seg_unit_begin, 3ull * kMaxGroupTensors + 4);
     const u64 nseg_max = 3ull * kMaxGroupTensors;
-    const u64 acc_words = nseg_max * EXCP_MAX_K * (EXCP_ABSM_BINS + 1);
+    const u64 acc_words = kAccSegCentres * 3 * (EXCP_ABSM_BINS + 1);
     ok = ok && dev_alloc(c, &w.pw, G);
     ok = ok && dev_alloc(c, &w.pm, G);
     ok = ok && dev_alloc(c, &w.pv, G);
     ok = ok && dev_alloc(c, &w.km_split, nseg_max * EXCP_KM_MAP_WORDS);
-    ok = ok && dev_alloc(c, &w.km_cnt, chunks_group * 256);
+    ok = ok && dev_alloc(c, &w.km_cnt, (chunks_group / EXCP_SUPER_CHUNKS + nseg_max + 1) * 256);
     ok = ok && dev_alloc(c, &w.km_begin, nseg_max * 257);
-    ok = ok && dev_alloc(c, &w.km_part, nseg_max * 16 * 256);
-    ok = ok && dev_alloc(c, &w.km_bsum, nseg_max * 256 * EXCP_ABSM_BINS);
+    ok = ok && dev_alloc(c, &w.km_bsum, nseg_max * 257 * EXCP_ABSM_BINS);
     ok = ok && dev_alloc(c, &w.km_min, nseg_max * 256);
     ok = ok && dev_alloc(c, &w.km_max, nseg_max * 256);
+    ok = ok && dev_alloc(c, &w.km_mag, nseg_max * 256);
     ok = ok && dev_alloc(c, &w.km_acc, acc_words);
-    const u64 item_cap = chunks_group + nseg_max * 256;
-    ok = ok && dev_alloc(c, (unsigned char **)&w.km_items, item_cap * 16);
-    ok = ok && dev_alloc(c, &w.km_item_count, 4);
-    w.km_item_cap = (u32)(item_cap > 0xffffffffull ? 0xffffffffull : item_cap);
     ok = ok && dev_alloc(c, &w.part_obj, chunks_group);
     // per-tile survivor counts of decode; a chain reconstruction keeps those of all its checkpoints
     ok = ok && dev_alloc(c, &w.dec_cnt_w, max_tiles * EXCP_MAX_CHAIN);
@@ -403,8 +401,6 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     if (ok) {
         launch_zero_u32(w.med_hist, (u64)kMaxGroupTensors * 2048, c->stream);
         launch_zero_u32(w.sel_ticket, kMaxGroupTensors, c->stream);
-        launch_zero_u32((u32 *)w.km_acc, 2 * acc_words, c->stream);
-        launch_zero_u32(w.km_item_count, 4, c->stream);
         launch_zero_u32((u32 *)w.err_flag, 4, c->stream);
         ok = hipStreamSynchronize(c->stream) == hipSuccess;
     }
@@ -493,7 +489,8 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
     }
     if (hipSetDevice(c->device) != hipSuccess) return EXCP_E_HIP;
     const u64 cap_elems = c->max_group;
-    const u32 tcap = kMaxGroupTensors;
+    // (the accumulators of the Lloyd iterations hold 3 x 1024 streams of up to 85 centres: six-bit codes and fewer)
+    const u32 tcap = (u32)std::min<u64>(kMaxGroupTensors, kAccSegCentres / (3ull * (u64)std::max(K, 1)));
     std::vector<Group> &groups = c->groups;
     std::vector<u32> &tb_offsets = c->tb_offsets;
     groups.clear(); tb_offsets.clear();
@@ -543,6 +540,18 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         p.ntensors = g.count; p.ntiles = g.ntiles;
         u64 largest = 0;
         for (u32 q = 0; q < g.count; ++q) largest = std::max<u64>(largest, tensors[g.first + q].n);
+        if (!raw) {
+            // Work units of a Lloyd iteration of the streams too large for one workgroup: about 8192 values in cut
+            // buckets (at most K - 1 of 256 are cut), more where that would make more than two units per compute
+            // unit (a third of a tensor's values survive in its three streams at the usual thresholds).
+            u64 large_chunks = 0;
+            for (u32 q = 0; q < g.count; ++q)
+                if (!excp_lloyd_alone(tensors[g.first + q].n, (u32)K)) large_chunks += tensors[g.first + q].n / EXCP_CHUNK / 2;
+            p.unit_chunks = (u32)std::max<u64>(std::max<u64>(256u / (u32)std::max(K - 1, 1), 1), large_chunks / (2ull * (u64)w.cus));
+            const u64 per = (u64)p.unit_chunks * EXCP_CHUNK;
+            for (u32 q = 0; q < g.count; ++q)
+                if (!excp_lloyd_alone(tensors[g.first + q].n, (u32)K)) p.max_units += 3ull * ((tensors[g.first + q].n + per - 1) / per);
+        }
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
         { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, s); }
         { StageTimer t(c, ST_STATS); launch_stats(w, p, 1, s); }
@@ -550,26 +559,18 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         { StageTimer t(c, ST_MASK_COMPACT); launch_mask_compact(w, p, 0, s); }
         { StageTimer t(c, ST_MASK_SCAN); launch_mask_compact(w, p, 1, s); }
         { StageTimer t(c, ST_LAYOUT); launch_layout(w, p, s); }
-        if (!raw) {
-            // the value -> bucket maps come from the slots, and the count table is cleared, before the pass
-            // that makes the dense survivor arrays: that pass also takes the bucket counts
-            { StageTimer t(c, ST_KM_SAMPLE); launch_km_partition(w, p, 0, s); }
-            { StageTimer t(c, ST_KM_COUNT); launch_km_partition(w, p, 1, s); }
-        }
+        // the value -> bucket maps come from the slots, before the pass that makes the dense survivor arrays:
+        // that pass also takes the bucket counts
+        if (!raw) { StageTimer t(c, ST_KM_SAMPLE); launch_km_partition(w, p, 0, s); }
         { StageTimer t(c, ST_MASK_GATHER); launch_mask_compact(w, p, 2, s); }
         if (raw) {
             StageTimer t(c, ST_ASSIGN_PACK); launch_store_raw(w, p, s);
         } else {
-            { StageTimer t(c, ST_KM_SCAN); launch_km_partition(w, p, 2, s); }
-            { StageTimer t(c, ST_KM_SCATTER); launch_km_partition(w, p, 3, s); }
-            { StageTimer t(c, ST_KM_BUCKET_STATS); launch_km_partition(w, p, 4, s); }
+            { StageTimer t(c, ST_KM_SCAN); launch_km_partition(w, p, 1, s); }
+            { StageTimer t(c, ST_KM_SCATTER); launch_km_partition(w, p, 2, s); }
+            { StageTimer t(c, ST_KM_BUCKET_STATS); launch_km_partition(w, p, 3, s); }
             { StageTimer t(c, ST_KM_INIT); launch_km_init(w, p, s); }
-            for (int it = 0; it < lloyd_iters; ++it) {
-                // classification also moves the centres by the previous iteration's totals
-                { StageTimer t(c, ST_KM_CLASSIFY); launch_km_classify(w, p, it, s); }
-                { StageTimer t(c, ST_KM_ITER); launch_km_iter(w, p, it, s); }
-            }
-            if (lloyd_iters > 0) { StageTimer t(c, ST_KM_UPDATE); launch_km_update(w, p, s); }
+            { StageTimer t(c, ST_KM_ITER); launch_km_iter(w, p, s); }
             { StageTimer t(c, ST_ASSIGN_PACK); launch_assign_pack(w, p, s); }
         }
         { StageTimer t(c, ST_FINALIZE); launch_finalize(w, p, s); }

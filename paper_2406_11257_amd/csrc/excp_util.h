@@ -153,64 +153,44 @@ __device__ __forceinline__ float val_of(u32 k) {
     return u2f((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-// Index of the nearest centre of x among centres in ascending order (Sec. 3.3 leaves the rule
-// open; this is the rule the library fixes).  a = last centre <= x, b = the next one; the two
-// distances are evaluated in fp64 with one rounding each, b wins only if strictly nearer, and
-// among centres of equal value the lowest index is taken.  dist_out receives (x - C[pick])^2.
-__device__ __forceinline__ int nearest_centre(float x, const float *C, int K, double *dist_out) {
-    int lo = 0, hi = K;                    // count of centres <= x by bisection
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (C[mid] <= x) lo = mid + 1; else hi = mid;
-    }
-    int j = lo - 1;                        // largest index with C[j] <= x, or -1
-    int a = j < 0 ? 0 : j;
-    int b = (j + 1 < K) ? j + 1 : K - 1;
-    double xd = (double)x;
-    double da = fabs(xd - (double)C[a]);
-    double db = fabs((double)C[b] - xd);
-    int pick = (db < da) ? b : a;
-    float cv = C[pick];
-    while (pick > 0 && C[pick - 1] == cv) --pick;
-    if (dist_out) { double d = xd - (double)cv; *dist_out = d * d; }
-    return pick;
-}
-
+// The nearest centre of x among centres in ascending order (Sec. 3.3 leaves the rule open; this is the
+// rule the library fixes): a = last centre <= x, b = the next one; the two distances are evaluated in
+// fp64 with one rounding each, b wins only if strictly nearer, and among centres of equal value the lowest
+// index is taken.
 // The nearest-centre rule is monotone in the value, so it is fully described by K - 1 cut keys:
 // cut[k] = smallest key (order-preserving bit pattern) of a finite value whose nearest centre has
-// index >= k, or 0xffffffff when no finite value reaches k.  Found by bisection with the rule
-// itself, so "number of cut keys <= key(x)" IS nearest_centre(x), bit for bit.  Threads 1..K-1 of
-// the workgroup each find one; entries from K up to 255 are set to 0xffffffff.  C and cut are LDS
-// arrays of 256 entries; the caller synchronises before and after.
+// index >= k, or 0xffffffff when no finite value reaches k; then "number of cut keys <= key(x)" IS
+// nearest_centre(x), bit for bit.  With a = C[k-1] < b = C[k] a value in [a, b] reaches k exactly if
+// |b - x| < |x - a| in the rule's arithmetic; smaller ones do not, larger ones do.  Where C[k-1] equals
+// C[k] the lowest index of the run takes everything, so reaching k means reaching the first index after
+// the run.  The border lies next to the midpoint: a bracket of five keys around it is probed first, and
+// the bisection goes on from what the probes have proved.  Threads 1..K-1 of the workgroup each find one;
+// entries from K up to 255 are set to 0xffffffff.  C and cut are LDS arrays of 256 entries; the caller
+// synchronises before and after.
 __device__ __forceinline__ void compute_cut_keys(const float *C, int K, u32 *cut) {
     const u32 k = threadIdx.x;
     if (k == 0 || k > 255u) return;
     u32 res = 0xffffffffu;
-    if ((int)k < K) {
-        constexpr u32 KEY_LO = 0x00800000u, KEY_HI = 0xff7fffffu;          // keys of -FLT_MAX and +FLT_MAX
-        auto reaches = [&](u32 key) { return (u32)nearest_centre(val_of(key), C, K, nullptr) >= k; };
-        // The border between centres k-1 and k lies next to their midpoint, so a bracket of a few keys
-        // around the midpoint is probed first; whatever the probes say, the bisection below starts
-        // from a bracket they have proved (every key below lo stays below k, hi reaches k), so the
-        // result is that of a bisection over all finite keys.
-        const u32 mk = key_of((float)(0.5 * ((double)C[k - 1] + (double)C[k])));
-        const u32 p_lo = mk - KEY_LO > 2u ? mk - 2u : KEY_LO, p_hi = KEY_HI - mk > 2u ? mk + 2u : KEY_HI;
-        u32 lo = KEY_LO, hi = KEY_HI;
-        bool any = true;
+    u32 j = k;
+    while (j < (u32)K && !(C[j - 1u] < C[j])) ++j;
+    if (j < (u32)K) {
+        const double a = (double)C[j - 1u], b = (double)C[j];
+        auto reaches = [&](u32 key) { const double x = (double)val_of(key); return fabs(b - x) < fabs(x - a); };
+        u32 lo = key_of(C[j - 1u]) + 1u, hi = key_of(C[j]);               // invariant: hi reaches, nothing below lo does
+        if (lo > hi) lo = hi;
+        const u32 mk = min(max(key_of((float)(0.5 * (a + b))), lo), hi);
+        const u32 p_hi = hi - mk > 2u ? mk + 2u : hi, p_lo = mk - lo > 2u ? mk - 2u : lo;
         if (reaches(p_hi)) {
-            if (reaches(p_lo)) hi = p_lo; else { lo = p_lo + 1u; hi = p_hi; }
-        } else if (p_hi < KEY_HI && reaches(KEY_HI)) {
-            lo = p_hi + 1u;
+            hi = p_hi;
+            if (p_lo < hi) { if (reaches(p_lo)) hi = p_lo; else lo = p_lo + 1u; }
         } else {
-            any = false;                                                   // no finite value reaches k
+            lo = p_hi + 1u;
         }
-        if (any) {
-            while (lo < hi) {                                              // invariant: hi reaches k
-                const u32 mid = lo + ((hi - lo) >> 1);
-                if (reaches(mid)) hi = mid; else lo = mid + 1u;
-            }
-            res = hi;
+        while (lo < hi) {
+            const u32 mid = lo + ((hi - lo) >> 1);
+            if (reaches(mid)) hi = mid; else lo = mid + 1u;
         }
+        res = hi;
     }
     cut[k] = res;
 }
@@ -223,19 +203,28 @@ __device__ __forceinline__ u32 centre_by_cuts(const u32 *cut, u32 kp2, u32 key) 
     return lo;
 }
 
-// Signed bins -> the exact sum rounded once (to nearest, ties to even) to fp64.
-// Everything stays in registers (fixed indices after unrolling): this runs once per centre and
-// iteration on the critical path between two small kernels.
-__device__ inline double signed_bins_to_double(const u64 *bins) {
-    // base-256 digits of the sum (bin g has weight 2^(8g)), what is left over in a signed top word
+// Signed bins (bin g has weight 2^(8g - 149)) -> the exact sum rounded once (to nearest, ties to even) to fp64.
+// Everything stays in registers (fixed indices after unrolling): this runs once per centre and iteration on the
+// critical path of a Lloyd iteration.  `stride`: distance between the bins of one sum; bins outside [g0, g1]
+// (the same in the whole wave) are zero and not read.
+__device__ __forceinline__ double signed_bins_to_double(const u64 *bins, u32 stride = 1u, u32 g0 = 0u, u32 g1 = EXCP_ABSM_BINS - 1u) {
+    // eight bins make a word and what goes into the next one: Horner's scheme in 128 bits (|sum| < 2^121)
     u64 W[6] = {0, 0, 0, 0, 0, 0};
     long long carry = 0;
 #pragma unroll
-    for (int g = 0; g < EXCP_ABSM_BINS; ++g) {
-        const u64 b = bins[g];
-        const long long t = (long long)(b & 255ull) + carry;       // |carry| < 2^57: no overflow
-        carry = (t >> 8) + ((long long)b >> 8);
-        W[g >> 3] |= (u64)(t & 255) << (8 * (g & 7));
+    for (u32 h = 0; h < EXCP_ABSM_BINS / 8u; ++h) {
+        __int128 t = carry;
+        if (8u * h <= g1 && 8u * h + 7u >= g0) {
+            u64 b[8];
+#pragma unroll
+            for (u32 j = 0; j < 8; ++j) b[j] = 8u * h + j >= g0 && 8u * h + j <= g1 ? bins[(8u * h + j) * stride] : 0ull;
+            __int128 v = (long long)b[7];
+#pragma unroll
+            for (int j = 6; j >= 0; --j) v = (v << 8) + (long long)b[j];
+            t += v;
+        }
+        W[h] = (u64)t;
+        carry = (long long)(t >> 64);
     }
     W[5] = (u64)carry;
     const bool neg = carry < 0;

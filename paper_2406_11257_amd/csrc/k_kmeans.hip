@@ -42,65 +42,17 @@ __device__ __forceinline__ float *seg_part(const Workspace &w, u32 sidx) {
     return basep + w.desc[t].elem_off;
 }
 
+// A launch over some of the group's streams: all of them, the residual streams, or the moment streams.
+enum { STREAMS_ALL = 0, STREAMS_W = 1, STREAMS_MV = 2 };
+__device__ __forceinline__ u32 stream_of(u32 idx, u32 sel) {
+    return sel == STREAMS_ALL ? idx : (sel == STREAMS_W ? 3u * idx : 3u * (idx >> 1) + 1u + (idx & 1u));
+}
+static u32 stream_count(u32 ntensors, u32 sel) { return ntensors * (sel == STREAMS_ALL ? 3u : (sel == STREAMS_W ? 1u : 2u)); }
+
 // Four consecutive floats at an address that is only known to be 4-byte aligned.
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // ---------------------------------------------------------------- exact signed accumulation
-// Adds the values x[j] (j < N) with sel[j] set, for the whole wave, to a set of signed bins through
-// add(bin, delta): sum_g bins[g] * 2^(8g-149) grows by exactly the sum of the selected values.
-template <int N, class Add>
-__device__ __forceinline__ void wave_exact_add(const float (&x)[N], const bool (&sel)[N], Add add) {
-    const u32 lane = lane_id();
-    u32 pmax = 0, any = 0;
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-        u32 mb = f2u(x[j]) & 0x7fffffffu;
-        u32 e = mb >> 23;
-        u32 pos = (e ? e : 1u) - 1u;
-        if (sel[j] && mb) { pmax = max(pmax, pos); any = 1; }
-    }
-    if (!__any(any)) return;
-    pmax = wave_max_u32(pmax);
-    const u32 B = pmax > 39u ? pmax - 39u : 0u;
-    u64 pL = 0, pH = 0, nL = 0, nH = 0;
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-        u32 u = f2u(x[j]);
-        u32 mb = u & 0x7fffffffu;
-        u32 e = mb >> 23;
-        u32 mant = (mb & 0x7fffffu) | (e ? 0x800000u : 0u);
-        u32 pos = (e ? e : 1u) - 1u;
-        if (sel[j] && mant) {
-            const bool neg = u >> 31;
-            if (pos >= B) {
-                u64 term = (u64)mant << (pos - B);
-                if (neg) { nL += term & 0xffffffffull; nH += term >> 32; }
-                else { pL += term & 0xffffffffull; pH += term >> 32; }
-            } else {
-                u64 d = (u64)mant << (pos & 7u);
-                add(pos >> 3, neg ? (u64)0 - d : d);
-            }
-        }
-    }
-#pragma unroll
-    for (int sgn = 0; sgn < 2; ++sgn) {
-        u64 aL = sgn ? nL : pL, aH = sgn ? nH : pH;
-        if (!__any(aL != 0 || aH != 0)) continue;
-        aL = wave_sum_u64(aL);
-        aH = wave_sum_u64(aH);
-        if (lane == 0) {
-            u64 lo64 = aL + (aH << 32);
-            u64 hi64 = (aH >> 32) + (lo64 < aL ? 1ull : 0ull);
-            u64 piece[3] = {lo64 & 0xffffffffull, lo64 >> 32, hi64};
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                u32 p = B + 32u * q;
-                if (piece[q]) { u64 d = piece[q] << (p & 7u); add(p >> 3, sgn ? (u64)0 - d : d); }
-            }
-        }
-    }
-}
-
 // Adds v * 2^(bitpos - 149) to a set of signed bins (bin g has weight 2^(8g - 149)), with integer atomics.
 __device__ __forceinline__ void file_i64(u64 *bins, long long v, u32 bitpos) {
     const bool neg = v < 0;
@@ -113,6 +65,9 @@ __device__ __forceinline__ void file_i64(u64 *bins, long long v, u32 bitpos) {
         if (piece) atomicAdd(&bins[p >> 3], neg ? (u64)0 - d : d);
     }
 }
+
+// Position of a magnitude's lowest mantissa bit: value = mantissa * 2^(pos - 149).
+__device__ __forceinline__ u32 bit_pos(u32 mag) { const u32 e = mag >> 23; return (e ? e : 1u) - 1u; }
 
 // Exact summation of values that are neighbours in magnitude.  A value inside the window of 24 bit
 // positions [B, B + 24) is a whole multiple of the unit 2^(B-149) below 2^47 units, so up to sixteen of
@@ -167,6 +122,11 @@ __global__ __launch_bounds__(SM_THREADS) void k_km_sample(Workspace w, GroupPara
     const u32 ns = len < SAMPLE ? (u32)len : SAMPLE;
     if (tid < 4) s_ext[tid] = (tid & 1u) ? 0u : 0xffffffffu;
     s_coarse[tid] = at_of(pre[coarse_sub(tid)]);
+    {   // the stream's rows of the count table start at zero (the counts are taken by k_mask_gather)
+        const u32 rows = (u32)((len + EXCP_SUPER_CHUNKS * EXCP_CHUNK - 1u) / (EXCP_SUPER_CHUNKS * EXCP_CHUNK));
+        u32 *row0 = w.km_cnt + (u64)w.seg[sidx].row_begin * NBKT;
+        for (u64 i = tid; i < (u64)rows * NBKT; i += SM_THREADS) row0[i] = 0;
+    }
     for (u32 c = tid; c < EXCP_KM_CELLS; c += SM_THREADS) cnt[c] = 0;
     __syncthreads();
     u32 mn[2] = {0xffffffffu, 0xffffffffu}, mx[2] = {0u, 0u};
@@ -310,90 +270,39 @@ __device__ __forceinline__ void load_chunk(const EXCP_GLOBAL float *gx, u32 clen
 }
 __device__ __forceinline__ u32 chunk_elem(u32 it) { return ((it >> 2) * EXCP_THREADS + threadIdx.x) * 4u + (it & 3u); }
 
-// ---------------------------------------------------------------- P1: bucket counts
-// Taken by the pass that makes the dense survivor arrays (k_mask_gather), per 16 chunks of a stream, into
-// the row of the first of them; the table is cleared here before that pass.
-__global__ __launch_bounds__(EXCP_THREADS) void k_km_clear_counts(Workspace w, GroupParams g) {
-    const u64 words = (u64)*w.chunk_total * NBKT;
-    for (u64 i = (u64)blockIdx.x * EXCP_THREADS + threadIdx.x; i < words; i += (u64)gridDim.x * EXCP_THREADS) w.km_cnt[i] = 0;
-}
-
-// ---------------------------------------------------------------- P2: offsets of every (chunk, bucket)
-// A stream's chunks are cut into sixteen parts so that sixteen workgroups share the walk over a long
-// stream's count table: (a) per-bucket totals of every part, (b) per stream: bucket totals, their
-// scan, and the first position of every (part, bucket), (c) per part: counts -> positions.
-constexpr u32 SCAN_PARTS = 16;
-
-__device__ __forceinline__ void scan_part_range(const Workspace &w, u32 sidx, u32 part, u32 &a0, u32 &a1) {
-    const u32 c0 = w.seg[sidx].chunk_begin, c1 = w.seg_chunk_begin[sidx + 1];
-    const u32 per = (c1 - c0 + SCAN_PARTS - 1u) / SCAN_PARTS;
-    a0 = min(c0 + part * per, c1);
-    a1 = min(a0 + per, c1);
-}
-
-// 1024 threads: thread (q, b) owns bucket b over one quarter of the part's chunks.
-__global__ __launch_bounds__(1024) void k_km_scan_parts(Workspace w, GroupParams g) {
-    __shared__ u32 tot[4][NBKT];
-    const u32 sidx = blockIdx.x / SCAN_PARTS, part = blockIdx.x % SCAN_PARTS;
-    const u32 tid = threadIdx.x, q = tid >> 8, b = tid & 255u;
-    if (w.seg[sidx].len == 0) return;
-    u32 p0, p1;
-    scan_part_range(w, sidx, part, p0, p1);
-    const u32 nq = (p1 - p0 + 3u) / 4u;
-    const u32 a0 = min(p0 + q * nq, p1), a1 = min(a0 + nq, p1);
-    const u32 *cnt = w.km_cnt;
+// ---------------------------------------------------------------- P1, P2: bucket counts, positions
+// The counts are taken by the pass that makes the dense survivor arrays (k_mask_gather), per 16 chunks of a
+// stream, a row each.  One workgroup per stream turns them into positions: bucket totals, their scan, then
+// every row's first position in every bucket.  Thread (q, b) owns bucket b over one quarter of the rows.
+// (The table used to have a row per chunk, fifteen of sixteen of them empty, and took three launches to walk.)
+__global__ __launch_bounds__(1024) void k_km_scan(Workspace w, GroupParams g) {
+    __shared__ u32 tot[4][NBKT], s_wave[4];
+    const u32 sidx = blockIdx.x, tid = threadIdx.x, q = tid >> 8, b = tid & 255u, lane = tid & 63u;
+    const u64 len = w.seg[sidx].len;
+    if (len == 0) return;
+    const u32 rows = (u32)((len + EXCP_SUPER_CHUNKS * EXCP_CHUNK - 1u) / (EXCP_SUPER_CHUNKS * EXCP_CHUNK));
+    const u32 nq = (rows + 3u) / 4u, a0 = min(q * nq, rows), a1 = min(a0 + nq, rows);
+    u32 *cnt = w.km_cnt + (u64)w.seg[sidx].row_begin * NBKT;
     u32 s = 0;
 #pragma unroll 16
     for (u32 c = a0; c < a1; ++c) s += cnt[(u64)c * NBKT + b];
     tot[q][b] = s;
     __syncthreads();
-    if (q == 0) w.km_part[((u64)sidx * SCAN_PARTS + part) * NBKT + b] = tot[0][b] + tot[1][b] + tot[2][b] + tot[3][b];
-}
-
-// One workgroup of 256 threads per stream; thread b owns bucket b.
-__global__ __launch_bounds__(NBKT) void k_km_scan(Workspace w, GroupParams g) {
-    __shared__ u32 begin[NBKT + 1];
-    const u32 sidx = blockIdx.x, b = threadIdx.x;
-    if (w.seg[sidx].len == 0) return;
-    u32 *part = w.km_part + (u64)sidx * SCAN_PARTS * NBKT;
-    u32 pt[SCAN_PARTS], total = 0;
+    const u32 total = tot[0][b] + tot[1][b] + tot[2][b] + tot[3][b];
+    u32 incl = total;                                     // (the four quarters scan the same 256 totals)
 #pragma unroll
-    for (u32 p = 0; p < SCAN_PARTS; ++p) { pt[p] = part[p * NBKT + b]; total += pt[p]; }
-    begin[b + 1] = total;
-    if (b == 0) begin[0] = 0;
-    __syncthreads();
-    // inclusive scan of begin[1..256]
-    for (u32 off = 1; off < NBKT; off <<= 1) {
-        const u32 v = b >= off ? begin[b + 1 - off] : 0u;
-        __syncthreads();
-        begin[b + 1] += v;
-        __syncthreads();
+    for (int off = 1; off < 64; off <<= 1) {
+        const u32 v = __shfl_up(incl, off, WAVE);
+        if (lane >= (u32)off) incl += v;
     }
-    w.km_begin[(u64)sidx * (NBKT + 1) + b + 1] = begin[b + 1];
-    if (b == 0) w.km_begin[(u64)sidx * (NBKT + 1)] = 0;
-    u32 run = begin[b];
-#pragma unroll
-    for (u32 p = 0; p < SCAN_PARTS; ++p) { part[p * NBKT + b] = run; run += pt[p]; }
-}
-
-// 1024 threads: thread (q, b) turns the counts of bucket b into positions over one quarter of the
-// part's chunks (its start: the part's first position plus the quarters before it).
-__global__ __launch_bounds__(1024) void k_km_scan_apply(Workspace w, GroupParams g) {
-    __shared__ u32 tot[4][NBKT];
-    const u32 sidx = blockIdx.x / SCAN_PARTS, part = blockIdx.x % SCAN_PARTS;
-    const u32 tid = threadIdx.x, q = tid >> 8, b = tid & 255u;
-    if (w.seg[sidx].len == 0) return;
-    u32 p0, p1;
-    scan_part_range(w, sidx, part, p0, p1);
-    const u32 nq = (p1 - p0 + 3u) / 4u;
-    const u32 a0 = min(p0 + q * nq, p1), a1 = min(a0 + nq, p1);
-    u32 *cnt = w.km_cnt;
-    u32 s = 0;
-#pragma unroll 16
-    for (u32 c = a0; c < a1; ++c) s += cnt[(u64)c * NBKT + b];
-    tot[q][b] = s;
+    if (q == 0 && lane == 63u) s_wave[b >> 6] = incl;
     __syncthreads();
-    u32 run = w.km_part[((u64)sidx * SCAN_PARTS + part) * NBKT + b];
+    u32 run = incl - total;
+    for (u32 v = 0; v < (b >> 6); ++v) run += s_wave[v];
+    if (q == 0) {
+        w.km_begin[(u64)sidx * (NBKT + 1) + b] = run;
+        if (b == NBKT - 1u) w.km_begin[(u64)sidx * (NBKT + 1) + NBKT] = run + total;
+    }
     for (u32 qq = 0; qq < q; ++qq) run += tot[qq][b];
 #pragma unroll 16
     for (u32 c = a0; c < a1; ++c) {
@@ -432,7 +341,7 @@ __global__ __launch_bounds__(SC_THREADS, 1) void k_km_scatter(Workspace w, Group
     const u32 G = gridDim.x, bid = blockIdx.x;
     const u32 nseg = 3u * g.ntensors;
     // Equal shares of the chunk list, their ends moved back to where the bucket counts were taken: the first
-    // of every 16 chunks of a stream (the counts of a unit sit in that chunk's row, the rows between are zero).
+    // of every 16 chunks of a stream.
     auto snapped = [&](u32 c) -> u32 {
         if (c >= total) return total;
         const u32 c0 = w.seg_chunk_begin[find_owner(w.seg_chunk_begin, nseg, c)];
@@ -467,7 +376,7 @@ __global__ __launch_bounds__(SC_THREADS, 1) void k_km_scatter(Workspace w, Group
         };
         if (tid < NBKT) {
             // a ring index is the value's place inside its line, so that whole lines sit in one quarter of the ring
-            const u32 gp = w.km_cnt[(u64)c * NBKT + tid];
+            const u32 gp = w.km_cnt[(u64)(w.seg[sidx].row_begin + (c - chunk0) / EXCP_SUPER_CHUNKS) * NBKT + tid];
             gpos[tid] = gp;
             ctr[tid] = ((gp + misalign) & 31u) << 16;
         }
@@ -613,23 +522,22 @@ __global__ __launch_bounds__(SC_THREADS, 1) void k_km_scatter(Workspace w, Group
 // values met holds practically all of them; inside it a lane adds sixteen values at a time exactly in
 // fp64 and keeps the running total in two integer counters, with no cross-lane traffic; the rest
 // (rare) is filed one by one.
-// (sixteen for 16-bit weights, whose residuals are heavily tied, and for groups with a tensor so large
+// (sixteen for the residuals of 16-bit weights, which are heavily tied, and for groups with a tensor so large
 // that its buckets alone are millions of values; four otherwise, which is faster when the buckets are
 // small and even)
 template <u32 BS_WAVES, u32 BPW>
-__global__ __launch_bounds__(BS_WAVES * 64) void k_km_bucket_stats(Workspace w, GroupParams g) {
+__global__ __launch_bounds__(BS_WAVES * 64) void k_km_bucket_stats(Workspace w, GroupParams g, u32 sel, u32 nseg) {
     __shared__ u64 bins[BPW][EXCP_ABSM_BINS];
-    __shared__ u32 s_min[BPW], s_max[BPW];
+    __shared__ u32 s_min[BPW], s_max[BPW], s_mag[BPW];
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const u32 nseg = 3u * g.ntensors;
     // a workgroup walks over sets of BPW buckets (many sets are tiny: one workgroup each would be
     // bound by the rate at which workgroups can be started)
     for (u64 first = (u64)blockIdx.x * BPW; first < (u64)nseg * NBKT; first += (u64)gridDim.x * BPW) {
-    const u32 sidx = (u32)(first / NBKT), b0 = (u32)(first % NBKT);
+    const u32 sidx = stream_of((u32)(first / NBKT), sel), b0 = (u32)(first % NBKT);
     if (w.seg[sidx].len == 0) continue;                    // the same for the whole workgroup
     __syncthreads();                                       // the previous set has left the LDS tables
     if (tid < BPW * EXCP_ABSM_BINS) (&bins[0][0])[tid] = 0;
-    if (tid < BPW) { s_min[tid] = 0xffffffffu; s_max[tid] = 0; }
+    if (tid < BPW) { s_min[tid] = 0xffffffffu; s_max[tid] = 0; s_mag[tid] = 0xffffffffu; }
     __syncthreads();
     const u32 *begin = w.km_begin + (u64)sidx * (NBKT + 1);
     const EXCP_GLOBAL float *part = gptr(seg_part(w, sidx));
@@ -657,7 +565,7 @@ __global__ __launch_bounds__(BS_WAVES * 64) void k_km_bucket_stats(Workspace w, 
         u32 thr_lo, span;
         window_range(B, thr_lo, span);
         WindowSum S;
-        u32 kmin = 0xffffffffu, kmax = 0;
+        u32 kmin = 0xffffffffu, kmax = 0, mag = 0xffffffffu;       // mag: smallest magnitude less one (zero wraps to the largest)
         // Tied data (the sixteen-wave form): a large bucket is mostly one value.  The wave takes its
         // first value as that one and only counts its repetitions; count times value joins the sums
         // at the end.
@@ -671,6 +579,7 @@ __global__ __launch_bounds__(BS_WAVES * 64) void k_km_bucket_stats(Workspace w, 
             if (BS_WAVES == 16u && u == dom) { ++ndom; return; }
             const u32 k = key_of(xv);
             kmin = min(kmin, k); kmax = max(kmax, k);
+            mag = min(mag, mb - 1u);
             if (mb - thr_lo < span) {
                 S.part += (double)xv;
             } else if (mb) {
@@ -711,62 +620,124 @@ __global__ __launch_bounds__(BS_WAVES * 64) void k_km_bucket_stats(Workspace w, 
             if (dom >> 31) { S.lo -= tl; S.hi -= th; } else { S.lo += tl; S.hi += th; }
             const u32 k = key_of(u2f(dom));
             kmin = min(kmin, k); kmax = max(kmax, k);
+            mag = min(mag, mb - 1u);
         }
         const long long tL = (long long)wave_sum_u64((u64)S.lo), tH = (long long)wave_sum_u64((u64)S.hi);
 #pragma unroll
         for (int m = 32; m >= 1; m >>= 1) {
             kmin = min(kmin, (u32)__shfl_xor(kmin, m, WAVE));
             kmax = max(kmax, (u32)__shfl_xor(kmax, m, WAVE));
+            mag = min(mag, (u32)__shfl_xor(mag, m, WAVE));
         }
         if (lane == 0) {
-            atomicMin(&s_min[j], kmin); atomicMax(&s_max[j], kmax);
+            atomicMin(&s_min[j], kmin); atomicMax(&s_max[j], kmax); atomicMin(&s_mag[j], mag);
             file_i64(mybins, tL, B); file_i64(mybins, tH, B + 32u);
         }
     }
     __syncthreads();
     if (tid < BPW * EXCP_ABSM_BINS)
-        w.km_bsum[((u64)sidx * NBKT + b0) * EXCP_ABSM_BINS + tid] = (&bins[0][0])[tid];
-    if (tid < BPW) { w.km_min[(u64)sidx * NBKT + b0 + tid] = s_min[tid]; w.km_max[(u64)sidx * NBKT + b0 + tid] = s_max[tid]; }
+        w.km_bsum[((u64)sidx * EXCP_ABSM_BINS + tid / BPW) * (NBKT + 1) + b0 + tid % BPW] = bins[tid % BPW][tid / BPW];
+    if (tid < BPW) {
+        const u64 at = (u64)sidx * NBKT + b0 + tid;
+        w.km_min[at] = s_min[tid]; w.km_max[at] = s_max[tid];
+        w.km_mag[at] = s_mag[tid] + 1u;                    // (0: nothing but zeros, or nothing at all)
+    }
     if (BS_WAVES != 4u) break;                             // the sixteen-wave forms are launched one workgroup per set
     }
 }
 
-// ---------------------------------------------------------------- P6: initial centres
-// One workgroup per (stream, rank): radix select inside the bucket that holds the rank; the bits
-// that the bucket's minimum and maximum key share are known and skipped.
-// (1024 threads for 16-bit weights -- a bucket of tied values can be most of a stream -- and for very
-// large tensors; 256 otherwise)
+// ---------------------------------------------------------------- P5: initial centres, bucket prefix sums
+// Per stream K workgroups, one per initial centre, and one that makes the prefix sums of the bucket totals.
+//
+// A centre: radix select inside the bucket that holds its rank, 11 bits a digit (the bits that the bucket's
+// smallest and largest key share are known and skipped), the digit's histogram scanned by the whole
+// workgroup.  Values that fit the workgroup's registers are read once.
+// (1024 threads for the residuals of 16-bit weights -- a bucket of tied values can be most of a stream -- and for
+// groups with a tensor of 2^28 elements; 256 otherwise: with 1024 for everybody the 14 000 workgroups of a 410M-shaped
+// checkpoint take 347 us instead of 167, and 22 instead of 33 for a 16.8 M-element tensor)
+//
+// The prefix sums turn the total of any run of buckets into one difference; the workgroup of centre k also
+// clears its share of the accumulators of the Lloyd iterations.
 template <u32 INIT_THREADS>
-__global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupParams g) {
-    __shared__ u32 hist[256];
-    __shared__ u32 s_pick[2];
+__global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupParams g, u32 sel) {
+    __shared__ u32 hist[2048];
+    __shared__ u32 s_wave[INIT_THREADS / 64], s_pick[2];
     const u32 K = (u32)g.K;
-    const u32 sidx = blockIdx.x / K, k = blockIdx.x % K, tid = threadIdx.x;
+    const u32 sidx = stream_of(blockIdx.x / (K + 1u), sel), k = blockIdx.x % (K + 1u), tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     SegState &S = w.seg[sidx];
     const u64 len = S.len;
-    if (len == 0) { if (tid == 0) S.C[k] = 0.f; return; }
+    if (len == 0) return;
+    if (k == K) {
+        // a wave takes a bin: four consecutive buckets per lane
+        u64 *bs = w.km_bsum + (u64)sidx * EXCP_ABSM_BINS * (NBKT + 1);
+        if (tid < 2) { s_pick[tid] = tid ? 0u : 64u; s_wave[tid] = tid ? 0u : 255u; }
+        __syncthreads();
+        if (tid < NBKT) {                      // lowest and highest bit position of any value
+            const u32 kn = w.km_min[(u64)sidx * NBKT + tid], kx = w.km_max[(u64)sidx * NBKT + tid];
+            if (kn <= kx) {                    // (an empty bucket has no extremes)
+                const u32 a = f2u(val_of(kn)) & 0x7fffffffu, c = f2u(val_of(kx)) & 0x7fffffffu;
+                atomicMin(&s_wave[0], bit_pos(w.km_mag[(u64)sidx * NBKT + tid]));
+                atomicMax(&s_wave[1], bit_pos(max(a, c)));
+            }
+        }
+        for (u32 bin = wave; bin < EXCP_ABSM_BINS; bin += INIT_THREADS / 64u) {
+            u64 *row = bs + (u64)bin * (NBKT + 1);
+            u64 v[4], sum = 0;
+#pragma unroll
+            for (u32 q = 0; q < 4; ++q) { v[q] = row[4u * lane + q]; sum += v[q]; }
+            if (!__any((v[0] | v[1] | v[2] | v[3]) != 0ull)) {      // nothing in this bin: it is its own prefix sum
+                if (lane == 63u) row[NBKT] = 0;
+                continue;
+            }
+            u64 incl = sum;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const u32 ulo = __shfl_up((u32)incl, off, WAVE), uhi = __shfl_up((u32)(incl >> 32), off, WAVE);
+                if (lane >= (u32)off) incl += ((u64)uhi << 32) | ulo;
+            }
+            u64 run = incl - sum;
+#pragma unroll
+            for (u32 q = 0; q < 4; ++q) { row[4u * lane + q] = run; run += v[q]; }
+            if (lane == 63u) { row[NBKT] = run; atomicMin(&s_pick[0], bin); atomicMax(&s_pick[1], bin); }
+        }
+        __syncthreads();
+        if (tid == 0) {
+            S.bin_lo = s_pick[0]; S.bin_hi = s_pick[1];
+            // (windows begin up to 19 positions below a value, and sums reach up to 64 positions above one)
+            S.acc_lo = s_wave[0] > 19u ? (s_wave[0] - 19u) >> 3 : 0u;
+            S.acc_hi = min(s_wave[1] / 8u + 9u, EXCP_ABSM_BINS - 1u);
+        }
+        return;
+    }
+    {
+        constexpr u32 SHARE = 3u * (EXCP_ABSM_BINS + 1u);
+        u64 *acc = w.km_acc + ((u64)sidx * K + k) * SHARE;
+        if (tid < SHARE) acc[tid] = 0;
+    }
     const u32 *begin = w.km_begin + (u64)sidx * (NBKT + 1);
     const u32 r = (u32)(((u64)(2 * k + 1) * len) / (2ull * K));
-    u32 lo = 0, hi = NBKT;                  // begin[lo] <= r < begin[hi]
-    while (hi - lo > 1) { u32 mid = (lo + hi) >> 1; if (begin[mid] <= r) lo = mid; else hi = mid; }
-    const u32 b = lo, p0 = begin[b], p1 = begin[b + 1];
+    // the bucket that holds the rank: begin[b] <= r < begin[b + 1] (empty buckets repeat an entry)
+    if (tid < NBKT) { if (begin[tid] <= r && r < begin[tid + 1]) s_pick[0] = tid; }
+    __syncthreads();
+    const u32 b = s_pick[0], p0 = begin[b], p1 = begin[b + 1], cntb = p1 - p0;
     u32 rank = r - p0;
     const u32 kmin = w.km_min[(u64)sidx * NBKT + b], kmax = w.km_max[(u64)sidx * NBKT + b];
-    const EXCP_GLOBAL float *gpart = gptr(seg_part(w, sidx));
+    const EXCP_GLOBAL float *gpart = gptr(seg_part(w, sidx)) + p0;
     u32 diff = kmin ^ kmax;
-    if (diff == 0) { if (tid == 0) S.C[k] = val_of(kmin); return; }
+    float *out = &S.C[1][k];                 // (read by iteration 0, whose predecessor has parity 1)
+    if (diff == 0) { if (tid == 0) *out = val_of(kmin); return; }
     // A bucket far above the average size holds tied values (a continuous distribution fills the
     // buckets evenly).  Such a bucket is mostly ONE value, its smallest or its largest key, with a few
     // strays beside it: one cheap pass counts the two extremes, and if the rank falls among them the
     // answer is known without any digit-by-digit selection.
-    const bool crowded = (u64)(p1 - p0) > 3ull * (len / NBKT + 1ull);
+    const bool crowded = (u64)cntb > 3ull * (len / NBKT + 1ull);
     if (crowded) {
         __shared__ u32 s_ext[2];
         if (tid == 0) { s_ext[0] = 0u; s_ext[1] = 0u; }
         __syncthreads();
         u32 c_lo = 0, c_hi = 0;
-        for (u32 q0 = p0; q0 < p1; q0 += 16u * INIT_THREADS) {
-            if (q0 + 16u * INIT_THREADS <= p1) {
+        for (u32 q0 = 0; q0 < cntb; q0 += 16u * INIT_THREADS) {
+            if (q0 + 16u * INIT_THREADS <= cntb) {
                 f4u q[4];
 #pragma unroll
                 for (u32 j = 0; j < 4; ++j) q[j] = *(const EXCP_GLOBAL f4u *)(gpart + q0 + (j * INIT_THREADS + tid) * 4u);
@@ -779,343 +750,526 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
                     }
                 }
             } else {
-                for (u32 p = q0 + tid; p < p1; p += INIT_THREADS) {
+                for (u32 p = q0 + tid; p < cntb; p += INIT_THREADS) {
                     const u32 key = key_of(gpart[p]);
                     c_lo += key == kmin; c_hi += key == kmax;
                 }
             }
         }
         c_lo = wave_sum_u32(c_lo); c_hi = wave_sum_u32(c_hi);
-        if ((tid & 63u) == 0u) { atomicAdd(&s_ext[0], c_lo); atomicAdd(&s_ext[1], c_hi); }
+        if (lane == 0u) { atomicAdd(&s_ext[0], c_lo); atomicAdd(&s_ext[1], c_hi); }
         __syncthreads();
-        if (rank < s_ext[0]) { if (tid == 0) S.C[k] = val_of(kmin); return; }
-        if (rank >= (p1 - p0) - s_ext[1]) { if (tid == 0) S.C[k] = val_of(kmax); return; }
+        if (rank < s_ext[0]) { if (tid == 0) *out = val_of(kmin); return; }
+        if (rank >= cntb - s_ext[1]) { if (tid == 0) *out = val_of(kmax); return; }
     }
-    int hb = 31 - __clz((int)diff);          // highest bit in which keys of this bucket differ
-    u32 prefix = kmin >> (hb + 1 > 31 ? 31 : hb + 1);
-    if (hb == 31) prefix = 0;
-    int top = hb;                            // bits [0, top] still unknown
+    const u32 hb = 31u - (u32)__clz((int)diff);           // highest bit in which keys of this bucket differ
+    u32 prefix = hb == 31u ? 0u : kmin >> (hb + 1u);
+    int top = (int)hb;                                    // bits [0, top] still unknown
+    const bool once = cntb <= 16u * INIT_THREADS;         // all of it in registers
+    u32 held[16];
+    if (once) {
+#pragma unroll
+        for (u32 j = 0; j < 16; ++j) { const u32 p = j * INIT_THREADS + tid; held[j] = p < cntb ? key_of(gpart[p]) : 0u; }
+    }
     while (top >= 0) {
-        const int width = top + 1 < 8 ? top + 1 : 8;
-        const int shift = top + 1 - width;
-        if (tid < 256u) hist[tid] = 0;
+        const u32 width = top + 1 < 11 ? (u32)top + 1u : 11u, shift = (u32)top + 1u - width;
+        for (u32 i = tid; i < 2048u; i += INIT_THREADS) hist[i] = 0;
         __syncthreads();
         // (in a crowded bucket the lanes mostly hit the same bin: the increments are grouped per wave)
-        auto tally = [&](float xv, bool in) {
-            const u32 key = key_of(xv);
+        auto tally = [&](u32 key, bool in) {
             const bool match = in && ((top == 31) ? true : ((key >> (top + 1)) == prefix));
             const u32 bin = (key >> shift) & ((1u << width) - 1u);
             if (crowded) hist_add_tied(hist, bin, match);
             else if (match) atomicAdd(&hist[bin], 1u);
         };
-        // sixteen values per thread and round, every load of a round issued before its use
-        for (u32 q0 = p0; q0 < p1; q0 += 16u * INIT_THREADS) {
-            if (q0 + 16u * INIT_THREADS <= p1) {
-                f4u q[4];
+        if (once) {
 #pragma unroll
-                for (u32 j = 0; j < 4; ++j) q[j] = *(const EXCP_GLOBAL f4u *)(gpart + q0 + (j * INIT_THREADS + tid) * 4u);
+            for (u32 j = 0; j < 16; ++j) if (j * INIT_THREADS < cntb) tally(held[j], j * INIT_THREADS + tid < cntb);
+        } else {
+            // sixteen values per thread and round, every load of a round issued before its use
+            for (u32 q0 = 0; q0 < cntb; q0 += 16u * INIT_THREADS) {
+                if (q0 + 16u * INIT_THREADS <= cntb) {
+                    f4u q[4];
 #pragma unroll
-                for (u32 j = 0; j < 4; ++j) { tally(q[j].x, true); tally(q[j].y, true); tally(q[j].z, true); tally(q[j].w, true); }
-            } else {
-                for (u32 pp = q0; pp < p1; pp += INIT_THREADS) {       // the same trip count in every lane
-                    const u32 p = pp + tid;
-                    tally(p < p1 ? gpart[p] : 0.f, p < p1);
+                    for (u32 j = 0; j < 4; ++j) q[j] = *(const EXCP_GLOBAL f4u *)(gpart + q0 + (j * INIT_THREADS + tid) * 4u);
+#pragma unroll
+                    for (u32 j = 0; j < 4; ++j) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) tally(key_of(q[j][e]), true);
+                    }
+                } else {
+                    u32 x[16];
+#pragma unroll
+                    for (u32 j = 0; j < 16; ++j) { const u32 p = q0 + j * INIT_THREADS + tid; x[j] = p < cntb ? key_of(gpart[p]) : 0u; }
+#pragma unroll
+                    for (u32 j = 0; j < 16; ++j) if (q0 + j * INIT_THREADS < cntb) tally(x[j], q0 + j * INIT_THREADS + tid < cntb);
                 }
             }
         }
         __syncthreads();
-        if (tid == 0) {
-            u32 rr = rank, bin = 0;
-            const u32 nb = 1u << width;
-            while (bin + 1 < nb && rr >= hist[bin]) { rr -= hist[bin]; ++bin; }
-            s_pick[0] = bin; s_pick[1] = rr;
+        constexpr u32 PER = 2048u / INIT_THREADS;
+        u32 c[PER], local = 0;
+#pragma unroll
+        for (u32 i = 0; i < PER; ++i) { c[i] = hist[tid * PER + i]; local += c[i]; }
+        u32 incl = local;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const u32 v = __shfl_up(incl, off, WAVE);
+            if (lane >= (u32)off) incl += v;
+        }
+        if (lane == 63u) s_wave[wave] = incl;
+        __syncthreads();
+        u32 before = incl - local;
+        for (u32 q = 0; q < wave; ++q) before += s_wave[q];
+        if (rank >= before && rank < before + local) {                  // exactly one thread
+            u32 rr = rank - before, i = 0;
+#pragma unroll
+            for (u32 q = 0; q + 1u < PER; ++q) if (i == q && rr >= c[q]) { rr -= c[q]; ++i; }
+            s_pick[0] = tid * PER + i; s_pick[1] = rr;
         }
         __syncthreads();
-        prefix = (top == 31 && width == 32) ? s_pick[0] : ((prefix << width) | s_pick[0]);
+        prefix = (prefix << width) | s_pick[0];
         rank = s_pick[1];
-        top = shift - 1;
-        __syncthreads();
+        top = (int)shift - 1;
     }
-    if (tid == 0) S.C[k] = val_of(prefix);
+    if (tid == 0) *out = val_of(prefix);
 }
 
-// New centres of one stream from the iteration's totals: centre = fp32(exact sum / count), a
-// cluster without members keeps its centre; then the centres are put back in ascending order; the
-// totals are cleared for the next iteration.
-// Called by the whole workgroup (it holds barriers); the totals of sixteen centres at a time are
-// fetched into LDS side by side, so that no thread walks a chain of dependent global reads.
-// lds_C (optional) receives the centres as well.
-__device__ __forceinline__ void move_centres(const Workspace &w, const GroupParams &g, u32 sidx, float *lds_C) {
-    constexpr u32 STRIDE = EXCP_ABSM_BINS + 1, BATCH = 16;
-    __shared__ u64 s_acc[BATCH * STRIDE];
-    __shared__ float s_new[EXCP_MAX_K + 1];
-    SegState &S = w.seg[sidx];
-    const u32 K = (u32)g.K, tid = threadIdx.x;
-    u64 *acc = w.km_acc + (u64)sidx * EXCP_MAX_K * STRIDE;
-    for (u32 k0 = 0; k0 < K; k0 += BATCH) {
-        const u32 nk = min(BATCH, K - k0);
-        __syncthreads();
-        for (u32 i = tid; i < nk * STRIDE; i += EXCP_THREADS) {
-            s_acc[i] = acc[(u64)k0 * STRIDE + i];
-            acc[(u64)k0 * STRIDE + i] = 0;
-        }
-        __syncthreads();
-        if (tid < nk) {
-            const u64 *a = s_acc + tid * STRIDE;
-            const u64 cnt = a[EXCP_ABSM_BINS];
-            float c = S.C[k0 + tid];
-            if (cnt) {
-                const double sum = signed_bins_to_double(a);
-                c = (float)(sum / (double)cnt);
-            }
-            s_new[k0 + tid] = c;
-        }
-    }
-    __syncthreads();
-    // Back into ascending order (stable; nothing moves unless a run of equal centres was torn apart:
-    // the lowest of them takes all their members and may pass the ones left behind).
-    float c = 0.f; u32 rank = 0;
-    if (tid < K) {
-        c = s_new[tid];
-        for (u32 j = 0; j < K; ++j) {
-            const float cj = s_new[j];
-            rank += (cj < c || (cj == c && j < tid)) ? 1u : 0u;
-        }
-    }
-    __syncthreads();
-    if (tid < K) {
-        S.C[rank] = c;
-        if (lds_C) lds_C[rank] = c;
-    }
-}
+// ---------------------------------------------------------------- P6: Lloyd iterations
+// An iteration assigns every value to its nearest centre and adds it, exactly, to that centre's total -- where a
+// cluster border cuts a bucket by reading the bucket, and otherwise not at all: the buckets lying wholly in a
+// centre's cell are one difference of prefix sums.  What it costs is the chain of dependent steps (centres from
+// totals, cut keys, which buckets are cut, their values, sums), so a stream goes through it in one of two ways:
+//
+//   one workgroup per stream, all iterations in one launch (k_km_lloyd): no launch gaps, totals in LDS;
+//   one launch per iteration, many workgroups per stream (k_km_iter), for streams whose cut buckets hold so many
+//   values that one compute unit would read them for longer than a launch takes.
+//
+// The line (excp_lloyd_alone) is drawn on the tensor's size, which the host knows, so that a group without large
+// tensors launches nothing for them: up to n (K - 1) / 256 = 2^20 values could lie in cut buckets (a third of
+// that at the usual keep rates), which one compute unit reads in about 10 us.
+constexpr u32 LLOYD_THREADS = 512, LLOYD_WAVES = LLOYD_THREADS / 64;
+constexpr u32 LLOYD_FEW = 4 * LLOYD_THREADS;              // up to here a value per thread is quicker than a bucket per wave
 
-// ---------------------------------------------------------------- P5a: one Lloyd accumulation
-// Classification (one workgroup per stream): every bucket is compared with the current centres.
-// A bucket whose smallest and largest value go to the same centre adds its stored totals to that
-// centre; a bucket that a cluster border cuts is split into work items of at most 16384 values.
-constexpr u32 KM_ITEM = 16384;                   // values per work item
-struct KmItem { u32 sidx, p0, p1, range; };      // range = alo | ahi << 8
+struct LloydShared {
+    float C[EXCP_MAX_K + 1], fresh[EXCP_MAX_K + 1];
+    u32 cut[EXCP_MAX_K + 1];
+    u32 first[EXCP_MAX_K + 1], last[EXCP_MAX_K + 1];      // per centre: the buckets whose smallest value goes to it
+    u32 begin[NBKT + 1];                                  // first position of every bucket
+    u32 off[NBKT + 1];                                    // cut buckets back to back: first place of every bucket
+    u32 range[NBKT];                                      // per bucket: centres at its two ends, lowest and highest bit position
+                                                          // (alo | ahi << 8 | pos_lo << 16 | pos_hi << 24)
+    u32 wave[4];
+    u32 unsorted;
+};
 
-__global__ __launch_bounds__(EXCP_THREADS) void k_km_classify(Workspace w, GroupParams g, u32 parity, u32 do_update) {
-    __shared__ float s_C[EXCP_MAX_K + 1];
-    __shared__ u32 s_cut[EXCP_MAX_K + 1];
-    __shared__ u32 s_scan[EXCP_THREADS];
-    __shared__ u32 s_base;
-    const u32 sidx = blockIdx.x, tid = threadIdx.x;
-    SegState &S = w.seg[sidx];
-    // the work list of the next iteration (the other of two) starts empty; nobody reads it now
-    if (sidx == 0 && tid == 0) w.km_item_count[parity ^ 1u] = 0;
-    if (S.len == 0) return;
-    const int K = g.K;
-    u32 kp2 = 1; while (kp2 < (u32)K) kp2 <<= 1;
-    if (do_update) move_centres(w, g, sidx, s_C);          // the previous iteration's totals
-    else for (u32 k = tid; k < (u32)K; k += EXCP_THREADS) s_C[k] = S.C[k];
-    __syncthreads();
-    compute_cut_keys(s_C, K, s_cut);
-    __syncthreads();
-    if (tid >= 1) S.cut[tid] = s_cut[tid];
+// A stream as a workgroup keeps it through an iteration: thread b < 256 owns bucket b (its extremes, and the
+// positions of its smallest non-zero and its largest magnitude: lo | hi << 8).
+struct LloydStream { u32 kmin, kmax, pos, alo, acc_lo, acc_hi, bin_lo, bin_hi; const u64 *bs; };
+
+// `slot`: the parity of the centres (and, with cuts, the cut keys) to begin with.  All loads first, then LDS.
+__device__ __forceinline__ LloydStream lloyd_open(const Workspace &w, u32 sidx, u32 K, u32 slot, bool cuts, LloydShared &L) {
+    const u32 tid = threadIdx.x;
+    const SegState &S = w.seg[sidx];
+    LloydStream st;
+    st.bs = w.km_bsum + (u64)sidx * EXCP_ABSM_BINS * (NBKT + 1);
+    const u32 b = min(tid, NBKT - 1u);
     const u32 *begin = w.km_begin + (u64)sidx * (NBKT + 1);
-    u64 *acc = w.km_acc + (u64)sidx * EXCP_MAX_K * (EXCP_ABSM_BINS + 1);     // [K][bins + count]
-    const u32 b = tid;
-    const u32 p0 = begin[b], p1 = begin[b + 1], cntb = p1 - p0;
-    u32 alo = 0, ahi = 0;
-    if (cntb) {
-        alo = centre_by_cuts(s_cut, kp2, w.km_min[(u64)sidx * NBKT + b]);
-        ahi = centre_by_cuts(s_cut, kp2, w.km_max[(u64)sidx * NBKT + b]);
+    st.kmin = w.km_min[(u64)sidx * NBKT + b]; st.kmax = w.km_max[(u64)sidx * NBKT + b];
+    const u32 b0 = begin[b], b1 = begin[b + 1u], mag = w.km_mag[(u64)sidx * NBKT + b];
+    const float c = S.C[slot][b];
+    const u32 cut = S.cut[slot][b];
+    st.acc_lo = (u32)__builtin_amdgcn_readfirstlane((int)S.acc_lo); st.acc_hi = (u32)__builtin_amdgcn_readfirstlane((int)S.acc_hi);
+    st.bin_lo = (u32)__builtin_amdgcn_readfirstlane((int)S.bin_lo); st.bin_hi = (u32)__builtin_amdgcn_readfirstlane((int)S.bin_hi);
+    st.alo = 0; st.pos = 0;
+    if (tid < NBKT) {
+        L.begin[tid] = b0;
+        if (tid == NBKT - 1u) L.begin[NBKT] = b1;
+        if (tid < K) L.C[tid] = c;
+        if (cuts) L.cut[tid] = cut;
+        if (b1 > b0) {
+            const u32 a = f2u(val_of(st.kmin)) & 0x7fffffffu, z = f2u(val_of(st.kmax)) & 0x7fffffffu;
+            st.pos = bit_pos(mag) | (bit_pos(max(a, z)) << 8);
+        }
     }
-    const bool cut = cntb && alo != ahi;
-    if (cntb && !cut) {
-        u64 *dst = acc + (u64)alo * (EXCP_ABSM_BINS + 1);
-        const u64 *src = w.km_bsum + ((u64)sidx * NBKT + b) * EXCP_ABSM_BINS;
-        u64 tot[EXCP_ABSM_BINS];                   // all reads first: they must not queue behind the atomics
-#pragma unroll
-        for (int q = 0; q < EXCP_ABSM_BINS; ++q) tot[q] = src[q];
-#pragma unroll
-        for (int q = 0; q < EXCP_ABSM_BINS; ++q) if (tot[q]) atomicAdd(&dst[q], tot[q]);
-        atomicAdd(&dst[EXCP_ABSM_BINS], (u64)cntb);
-    }
-    const u32 nitems = cut ? (cntb + KM_ITEM - 1) / KM_ITEM : 0u;
-    s_scan[tid] = nitems;
-    __syncthreads();
-    for (u32 off = 1; off < EXCP_THREADS; off <<= 1) {
-        u32 v = (tid >= off) ? s_scan[tid - off] : 0u;
-        __syncthreads();
-        s_scan[tid] += v;
-        __syncthreads();
-    }
-    if (tid == EXCP_THREADS - 1) s_base = s_scan[tid] ? atomicAdd(&w.km_item_count[parity], s_scan[tid]) : 0u;
-    __syncthreads();
-    u32 at = s_base + s_scan[tid] - nitems;
-    KmItem *items = (KmItem *)w.km_items;
-    for (u32 q = 0; q < nitems; ++q, ++at) {
-        if (at >= w.km_item_cap) { atomicExch(w.err_flag, 1); break; }
-        u32 a0 = p0 + q * KM_ITEM, a1 = a0 + KM_ITEM < p1 ? a0 + KM_ITEM : p1;
-        items[at] = KmItem{sidx, a0, a1, alo | (ahi << 8)};
-    }
+    return st;
 }
 
-// Work items: the values of a cut bucket are assigned one by one and added, exactly, to their
-// centres.  Sums are gathered in LDS per item and flushed with a few integer atomics.
-constexpr u32 ITEM_R = 8;      // centres per item held in LDS; wider ranges go straight to global memory
+// The accumulators' bins that the stream can use, and the counts, set to zero.
+__device__ __forceinline__ void lloyd_clear(u64 *acc, const LloydStream &st, u32 K) {
+    for (u32 j = st.acc_lo * K + threadIdx.x; j < (st.acc_hi + 1u) * K; j += LLOYD_THREADS) acc[j] = 0;
+    if (threadIdx.x < K) acc[EXCP_ABSM_BINS * K + threadIdx.x] = 0;
+}
 
-__global__ __launch_bounds__(EXCP_THREADS, 4) void k_km_iter(Workspace w, GroupParams g, u32 parity) {
-    __shared__ float s_C[EXCP_MAX_K + 1];
-    __shared__ u32 s_cut[EXCP_MAX_K + 1];
-    __shared__ u64 s_bins[ITEM_R][EXCP_ABSM_BINS + 1];
+// Centres and cut keys of iteration i from L.C and, for i >= 1, st.alo (the centre that the smallest value of
+// the thread's bucket went to in iteration i - 1) and `acc` (LDS, [bin][K], then [K] counts: what iteration i - 1 moved
+// between centres).  A bucket counts wholly for its alo -- one difference of prefix sums for all of a centre's
+// buckets -- and the values of a cut bucket above a border are moved on by acc.  Thread k owns centre k.
+// An empty cluster keeps its centre; afterwards the centres are put back in ascending order (stable; nothing
+// moves unless a run of equal centres was torn apart: the lowest of them takes all their members and may pass
+// the ones left behind).  Begins and ends with a barrier.
+__device__ __forceinline__ void lloyd_centres(const LloydStream &st, u32 K, u32 i, u64 *acc, LloydShared &L) {
+    const u32 tid = threadIdx.x, g0 = st.bin_lo, g1 = st.bin_hi, alo = st.alo;
+    const u64 *bs = st.bs;
+    __syncthreads();
+    if (i > 0u) {
+        if (tid < K) { L.first[tid] = 0xffffffffu; L.last[tid] = 0u; }
+        if (tid == 0) L.unsorted = 0u;
+        __syncthreads();
+        if (tid < NBKT && L.begin[tid + 1u] > L.begin[tid]) { atomicMin(&L.first[alo], tid); atomicMax(&L.last[alo], tid); }
+        __syncthreads();
+        if (g0 <= g1) {
+            for (u32 j = tid; j < (g1 - g0 + 1u) * K; j += LLOYD_THREADS) {
+                const u32 q = g0 + j / K, k = j % K;
+                const u32 f = L.first[k], l = L.last[k] + 1u;
+                if (f < l) acc[q * K + k] += bs[q * (NBKT + 1u) + l] - bs[q * (NBKT + 1u) + f];
+            }
+        }
+        __syncthreads();
+        float c = 0.f;
+        if (tid < K) {
+            c = L.C[tid];
+            const u32 f = L.first[tid], l = L.last[tid] + 1u;      // (first = 2^32 - 1: no bucket)
+            u64 cnt = acc[EXCP_ABSM_BINS * K + tid];
+            if (f < l) cnt += L.begin[l] - L.begin[f];
+            if (cnt) c = (float)(signed_bins_to_double(acc + tid, K, st.acc_lo, st.acc_hi) / (double)cnt);
+            L.fresh[tid] = c;
+        }
+        __syncthreads();
+        if (tid + 1u < K && !(c <= L.fresh[tid + 1u])) L.unsorted = 1u;
+        lloyd_clear(acc, st, K);
+        __syncthreads();
+        u32 rank = tid;
+        if (L.unsorted && tid < K) {
+            rank = 0;
+#pragma unroll 1
+            for (u32 j = 0; j < K; ++j) {
+                const float cj = L.fresh[j];
+                rank += (cj < c || (cj == c && j < tid)) ? 1u : 0u;
+            }
+        }
+        if (tid < K) L.C[rank] = c;
+        __syncthreads();
+    }
+    compute_cut_keys(L.C, (int)K, L.cut);
+    __syncthreads();
+}
+
+// Which buckets the present cut keys cut, laid back to back; returns how many values those hold.
+__device__ __forceinline__ u32 lloyd_cut_buckets(LloydStream &st, u32 kp2, LloydShared &L) {
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const int K = g.K;
-    u32 kp2 = 1; while (kp2 < (u32)K) kp2 <<= 1;
-    u32 nitems = w.km_item_count[parity];
-    if (nitems > w.km_item_cap) nitems = w.km_item_cap;
-    const KmItem *items = (const KmItem *)w.km_items;
-    u32 cur = 0xffffffffu;
-    for (u32 it = blockIdx.x; it < nitems; it += gridDim.x) {
-        const KmItem I = items[it];
-        const u32 c_lo = I.range & 255u, c_hi = I.range >> 8;
-        u64 *acc = w.km_acc + (u64)I.sidx * EXCP_MAX_K * (EXCP_ABSM_BINS + 1);
-        if (c_hi - c_lo <= 2u) {
-            // ---- one or two borders inside the item (the usual case): per-lane totals of all values and
-            // of the values at or above each border; cluster totals are differences.
-            // A value inside the window of 24 bit positions [B, B + 24) is a whole multiple of the unit
-            // 2^(B-149) below 2^47 units, so a lane adds sixteen of them (one round of loads) exactly in
-            // fp64, whatever their signs; the round's sum is then split into two integers (units below
-            // 2^32, and signed multiples of 2^32) that go on in integer counters.  Values outside the
-            // window (rare: a bucket's values are neighbours) are filed one by one.
-            const u32 cut1 = w.seg[I.sidx].cut[c_lo + 1];
-            const u32 cut2 = (c_hi - c_lo == 2u) ? w.seg[I.sidx].cut[c_lo + 2] : 0xffffffffu;
-            const EXCP_GLOBAL float *part = gptr(seg_part(w, I.sidx));
-            const u32 blocks = (I.p1 - I.p0 + 255u) >> 8, per = (blocks + 3u) >> 2;
-            const u32 p0 = min(I.p0 + wave * per * 256u, I.p1), p1 = min(p0 + per * 256u, I.p1);
-            if (p0 >= p1) continue;                        // nothing for this wave (no barrier on this path)
-            u32 pm = 0;
-            {
-                const u32 i = p0 + lane;
-                const u32 mb = (i < p1) ? (f2u(part[i]) & 0x7fffffffu) : 0u;
-                const u32 e = mb >> 23;
-                pm = wave_max_u32((e ? e : 1u) - 1u);
-            }
-            const u32 B = pm + 4u > 23u ? pm + 4u - 23u : 0u;       // the window's top: 4 binary orders above the first values
-            u32 thr_lo, span;
-            window_range(B, thr_lo, span);
-            WindowSum S[3];                                // [0] all values, [1] values at or above border 1, [2] at or above border 2
-            u32 cnt1 = 0, cnt2 = 0;
-            auto take = [&](float xv) {
-                const u32 u = f2u(xv), mb = u & 0x7fffffffu;
-                const u32 key = key_of(xv);
-                const bool up1 = key >= cut1, up2 = key >= cut2;
-                cnt1 += up1; cnt2 += up2;
-                if (mb - thr_lo < span) {
-                    const double xd = (double)xv;
-                    S[0].part += xd; S[1].part += up1 ? xd : 0.0; S[2].part += up2 ? xd : 0.0;
-                } else if (mb) {
-                    const u32 e = mb >> 23;
-                    const u32 mant = (mb & 0x7fffffu) | (e ? 0x800000u : 0u);
-                    const u32 pos = (e ? e : 1u) - 1u;
-                    const u64 dd = (u64)mant << (pos & 7u);
-                    const u32 cl = c_lo + (up1 ? 1u : 0u) + (up2 ? 1u : 0u);
-                    atomicAdd(&acc[(u64)cl * (EXCP_ABSM_BINS + 1) + (pos >> 3)], (u >> 31) ? (u64)0 - dd : dd);
-                }
-            };
-            auto flush = [&]() { S[0].fold(B); S[1].fold(B); S[2].fold(B); };     // after at most sixteen values
-            // four 16-byte loads in flight per lane
-            constexpr u32 LOADS = 4;
-            u32 p = p0;
-            for (; p + LOADS * 256u <= p1; p += LOADS * 256u) {
-                f4u q[LOADS];
+    u32 size = 0, incl = 0;
+    if (tid < NBKT) {
+        const u32 cntb = L.begin[tid + 1u] - L.begin[tid];
+        u32 alo = 0, ahi = 0;
+        if (cntb) { alo = centre_by_cuts(L.cut, kp2, st.kmin); ahi = centre_by_cuts(L.cut, kp2, st.kmax); }
+        if (alo != ahi) size = cntb;
+        st.alo = alo;
+        L.range[tid] = alo | (ahi << 8) | (st.pos << 16);
+        incl = size;
 #pragma unroll
-                for (u32 j = 0; j < LOADS; ++j) q[j] = *(const EXCP_GLOBAL f4u *)(part + p + j * 256u + lane * 4u);
-#pragma unroll
-                for (u32 j = 0; j < LOADS; ++j) { take(q[j].x); take(q[j].y); take(q[j].z); take(q[j].w); }
-                flush();
-            }
-            for (u32 n4 = 0; p < p1; p += 256u) {
-                const u32 i = p + lane * 4u;
-                if (p + 256u <= p1) {
-                    const f4u q = *(const EXCP_GLOBAL f4u *)(part + i);
-                    take(q.x); take(q.y); take(q.z); take(q.w);
-                } else {
-#pragma unroll
-                    for (u32 e = 0; e < 4; ++e) if (i + e < p1) take(part[i + e]);
-                }
-                if (++n4 == 4u) { flush(); n4 = 0; }
-            }
-            flush();
-            long long tL[3], tH[3];
-#pragma unroll
-            for (int s3 = 0; s3 < 3; ++s3) { tL[s3] = (long long)wave_sum_u64((u64)S[s3].lo); tH[s3] = (long long)wave_sum_u64((u64)S[s3].hi); }
-            cnt1 = wave_sum_u32(cnt1); cnt2 = wave_sum_u32(cnt2);
-            if (lane == 0) {
-                // cluster c_lo + j receives set j minus set j + 1
-                const u32 cnt[4] = {p1 - p0, cnt1, cnt2, 0u};
-#pragma unroll
-                for (u32 j = 0; j < 3; ++j) {
-                    if (c_lo + j > c_hi) break;
-                    u64 *dst = acc + (u64)(c_lo + j) * (EXCP_ABSM_BINS + 1);
-                    file_i64(dst, tL[j], B); file_i64(dst, tH[j], B + 32u);
-                    if (j < 2 && c_lo + j < c_hi) { file_i64(dst, -tL[j + 1], B); file_i64(dst, -tH[j + 1], B + 32u); }
-                    const u32 nxt = (c_lo + j < c_hi) ? cnt[j + 1] : 0u;
-                    if (cnt[j] - nxt) atomicAdd(&dst[EXCP_ABSM_BINS], (u64)(cnt[j] - nxt));
-                }
-            }
-            continue;
+        for (int off = 1; off < 64; off <<= 1) {
+            const u32 v = __shfl_up(incl, off, WAVE);
+            if (lane >= (u32)off) incl += v;
         }
-        // ---- three or more borders inside one item (degenerate data): per-cluster accumulation
-        __syncthreads();
-        if (I.sidx != cur) {
-            for (u32 k = tid; k < (u32)K; k += EXCP_THREADS) s_C[k] = w.seg[I.sidx].C[k];
-            for (u32 k = tid; k <= EXCP_MAX_K; k += EXCP_THREADS) s_cut[k] = w.seg[I.sidx].cut[k];
-            cur = I.sidx;
-        }
-        for (u32 i = tid; i < ITEM_R * (EXCP_ABSM_BINS + 1); i += EXCP_THREADS) (&s_bins[0][0])[i] = 0;
-        __syncthreads();
-        const bool in_lds = (c_hi - c_lo) < ITEM_R;
-        const float *__restrict__ part = seg_part(w, I.sidx);
-        for (u32 p = I.p0 + wave * 512; p < I.p1; p += 4 * 512) {
-            float x[8]; bool ok[8]; u32 a[8];
+        if (lane == 63u) L.wave[wave] = incl;
+    }
+    __syncthreads();
+    if (tid < NBKT) {
+        u32 before = incl - size;
+        for (u32 v = 0; v < wave; ++v) before += L.wave[v];
+        L.off[tid] = before;
+        if (tid == NBKT - 1u) L.off[NBKT] = before + size;
+    }
+    __syncthreads();
+    return L.off[NBKT];
+}
+
+// The same for a whole workgroup and few values (places [x0, x1), some per thread): every thread looks its value's bucket up.
+__device__ __forceinline__ void lloyd_few(const EXCP_GLOBAL float *part, u32 x0, u32 x1, u32 K, u32 kp2, u64 *acc, const LloydShared &L) {
+    for (u32 q = x0 + threadIdx.x; q < x1; q += LLOYD_THREADS) {
+        u32 b = 0;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                u32 i = p + j * 64 + lane;
-                ok[j] = i < I.p1;
-                x[j] = ok[j] ? part[i] : 0.f;
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) a[j] = ok[j] ? centre_by_cuts(s_cut, kp2, key_of(x[j])) : 0xffffffffu;
-            for (u32 cl = c_lo; cl <= c_hi; ++cl) {
-                bool sel[8]; u32 n = 0;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) { sel[j] = a[j] == cl; n += __popcll(ballot64(sel[j])); }
-                if (n == 0) continue;
-                if (in_lds) {
-                    u64 *dst = s_bins[cl - c_lo];
-                    auto add = [&](u32 bin, u64 d) { atomicAdd(&dst[bin], d); };
-                    wave_exact_add<8>(x, sel, add);
-                    if (lane == 0) atomicAdd(&dst[EXCP_ABSM_BINS], (u64)n);
-                } else {
-                    u64 *dst = acc + (u64)cl * (EXCP_ABSM_BINS + 1);
-                    auto add = [&](u32 bin, u64 d) { atomicAdd(&dst[bin], d); };
-                    wave_exact_add<8>(x, sel, add);
-                    if (lane == 0) atomicAdd(&dst[EXCP_ABSM_BINS], (u64)n);
-                }
-            }
-        }
-        __syncthreads();
-        if (in_lds) {
-            for (u32 i = tid; i < ITEM_R * (EXCP_ABSM_BINS + 1); i += EXCP_THREADS) {
-                u64 v = (&s_bins[0][0])[i];
-                u32 cl = c_lo + i / (EXCP_ABSM_BINS + 1);
-                if (v && cl <= c_hi) atomicAdd(&acc[(u64)cl * (EXCP_ABSM_BINS + 1) + i % (EXCP_ABSM_BINS + 1)], v);
-            }
-        }
+        for (u32 step = NBKT / 2; step >= 1u; step >>= 1) if (L.off[b + step] <= q) b += step;
+        const u32 bits = f2u(part[L.begin[b] + (q - L.off[b])]), mb = bits & 0x7fffffffu;
+        const u32 c_lo = L.range[b] & 255u, cl = centre_by_cuts(L.cut, kp2, key_of(u2f(bits)));
+        if (cl == c_lo) continue;
+        const u32 e = mb >> 23, pb = bit_pos(mb);
+        const u64 d = (u64)((mb & 0x7fffffu) | (e ? 0x800000u : 0u)) << (pb & 7u), dd = (bits >> 31) ? (u64)0 - d : d;
+        atomicAdd(&acc[(pb >> 3) * K + cl], dd);
+        atomicAdd(&acc[(pb >> 3) * K + c_lo], (u64)0 - dd);
+        atomicAdd(&acc[EXCP_ABSM_BINS * K + cl], 1ull);
+        atomicAdd(&acc[EXCP_ABSM_BINS * K + c_lo], ~0ull);
     }
 }
 
-// ---------------------------------------------------------------- P5b: move the centres
-// After the last iteration (earlier ones are moved by the next classification kernel).
-__global__ __launch_bounds__(EXCP_THREADS) void k_km_update(Workspace w, GroupParams g) {
-    const u32 sidx = blockIdx.x, tid = threadIdx.x;
-    if (sidx == 0 && tid < 2) w.km_item_count[tid] = 0;    // both work lists start empty next time
-    if (w.seg[sidx].len == 0) return;
-    move_centres(w, g, sidx, nullptr);
+__device__ __forceinline__ void lloyd_file(u64 *acc, u32 K, u32 cl, long long v, u32 bitpos) {      // v * 2^(bitpos - 149) onto cluster cl
+    const bool neg = v < 0;
+    const u64 mag = neg ? (u64)0 - (u64)v : (u64)v;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const u64 piece = (mag >> (32 * h)) & 0xffffffffull;
+        const u32 p = bitpos + 32u * (u32)h;
+        const u64 d = piece << (p & 7u);
+        if (piece) atomicAdd(&acc[(p >> 3) * K + cl], neg ? (u64)0 - d : d);
+    }
+}
+
+// One wave, values [p0, p1) of a bucket that one or two borders cut (centres c_lo .. c_lo + 1 or c_lo + 2): the sum
+// and number of the values above each border.  Values compare with a border as floats: no border lies between -0
+// and +0, which are equally far from any centre.
+// WIDE = false: the bucket's magnitudes span at most eight binary orders.  A value is then a whole multiple below
+// 2^32 of the unit 2^(pos_lo - 149), and the 2^21 values a piece may hold add exactly in fp64 in any order.
+// WIDE = true: sixteen values at a time are added in a window of 24 positions below the largest magnitude (see
+// WindowSum); values below it are filed one by one.
+template <bool WIDE>
+__device__ __forceinline__ void lloyd_borders(const EXCP_GLOBAL float *part, u32 p0, u32 p1, u32 c_lo, bool two, u32 pos_lo, u32 pos_hi, u32 K,
+                                              u64 *acc, const LloydShared &L) {
+    const u32 lane = lane_id();
+    const float inf = __uint_as_float(0x7f800000u);
+    const float t1 = val_of(L.cut[c_lo + 1u]), t2 = two ? val_of(L.cut[c_lo + 2u]) : inf;
+    const u32 B = WIDE ? (pos_hi > 23u ? pos_hi - 23u : 0u) : pos_lo;
+    u32 thr_lo, span;
+    window_range(B, thr_lo, span);
+    WindowSum S1, S2;
+    u32 cnt1 = 0, cnt2 = 0;
+    auto take = [&](float x) {
+        const bool u1 = x >= t1;
+        cnt1 += u1;
+        if (!WIDE) {
+            S1.part += (double)(u1 ? x : 0.f);
+            if (two) { const bool u2 = x >= t2; cnt2 += u2; S2.part += (double)(u2 ? x : 0.f); }
+        } else {
+            const u32 bits = f2u(x), mb = bits & 0x7fffffffu;
+            const bool in = mb - thr_lo < span, u2 = x >= t2;
+            cnt2 += u2;
+            S1.part += (double)(u1 && in ? x : 0.f);
+            S2.part += (double)(u2 && in ? x : 0.f);
+            if (u1 && !in && mb) {
+                const u32 e = mb >> 23, pb = bit_pos(mb), cl = c_lo + (u2 ? 2u : 1u);
+                const u64 d = (u64)((mb & 0x7fffffu) | (e ? 0x800000u : 0u)) << (pb & 7u), dd = (bits >> 31) ? (u64)0 - d : d;
+                atomicAdd(&acc[(pb >> 3) * K + cl], dd);
+                atomicAdd(&acc[(pb >> 3) * K + c_lo], (u64)0 - dd);
+            }
+        }
+    };
+    u32 p = p0;
+    if (p + 1024u <= p1) {
+        // four 16-byte loads in flight per lane, the next four asked for before these are used
+        f4u nx[4];
+#pragma unroll
+        for (u32 j = 0; j < 4; ++j) nx[j] = *(const EXCP_GLOBAL f4u *)(part + p + j * 256u + lane * 4u);
+#pragma unroll 1
+        for (; p + 1024u <= p1; p += 1024u) {
+            f4u q[4];
+#pragma unroll
+            for (u32 j = 0; j < 4; ++j) q[j] = nx[j];
+            if (p + 2048u <= p1) {
+#pragma unroll
+                for (u32 j = 0; j < 4; ++j) nx[j] = *(const EXCP_GLOBAL f4u *)(part + p + 1024u + j * 256u + lane * 4u);
+            }
+#pragma unroll
+            for (u32 j = 0; j < 4; ++j) { take(q[j].x); take(q[j].y); take(q[j].z); take(q[j].w); }
+            if (WIDE) { S1.fold(B); S2.fold(B); }
+        }
+    }
+    if (p < p1) {                                         // fewer than 1024 left: sixteen per lane at most, side by side
+        float x[16];
+#pragma unroll
+        for (u32 j = 0; j < 16; ++j) if (p + j * 64u < p1) x[j] = p + j * 64u + lane < p1 ? part[p + j * 64u + lane] : -inf;
+#pragma unroll
+        for (u32 j = 0; j < 16; ++j) if (p + j * 64u < p1) take(x[j]);
+        if (WIDE) { S1.fold(B); S2.fold(B); }
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) { cnt1 += __shfl_xor(cnt1, m, WAVE); cnt2 += __shfl_xor(cnt2, m, WAVE); }
+    // lane j files what cluster c_lo + j receives
+    const u32 n = lane == 0u ? 0u - cnt1 : (lane == 1u ? cnt1 - cnt2 : cnt2);
+    if (!WIDE) {
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) S1.part += shfl_xor_f64(S1.part, m);
+        if (two) {
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) S2.part += shfl_xor_f64(S2.part, m);
+        }
+        const long long m1 = (long long)ldexp(S1.part, 149 - (int)B), m2 = (long long)ldexp(S2.part, 149 - (int)B);
+        const long long v = lane == 0u ? -m1 : (lane == 1u ? m1 - m2 : m2);
+        if (lane < 3u && v) lloyd_file(acc, K, c_lo + lane, v, B);
+    } else {
+        const long long l1 = (long long)wave_sum_u64((u64)S1.lo), h1 = (long long)wave_sum_u64((u64)S1.hi);
+        const long long l2 = (long long)wave_sum_u64((u64)S2.lo), h2 = (long long)wave_sum_u64((u64)S2.hi);
+        const long long vl = lane == 0u ? -l1 : (lane == 1u ? l1 - l2 : l2), vh = lane == 0u ? -h1 : (lane == 1u ? h1 - h2 : h2);
+        if (lane < 3u && vl) lloyd_file(acc, K, c_lo + lane, vl, B);
+        if (lane < 3u && vh) lloyd_file(acc, K, c_lo + lane, vh, B + 32u);
+    }
+    if (lane < 3u && n) atomicAdd(&acc[EXCP_ABSM_BINS * K + c_lo + lane], (u64)(long long)(int)n);
+}
+
+// One wave, values [p0, p1) of a bucket that three or more borders cut: value by value.  What leaves c_lo is kept per
+// lane where the bucket spans at most 39 binary orders (units of its lowest position, in two 32-bit halves),
+// because all lanes would queue at that one centre.
+__device__ __forceinline__ void lloyd_many(const EXCP_GLOBAL float *part, u32 p0, u32 p1, u32 c_lo, u32 c_hi, u32 pos_lo, u32 pos_hi, u32 K,
+                                           u64 *acc, const LloydShared &L) {
+    const u32 lane = lane_id();
+    const bool near = pos_hi - pos_lo <= 39u;
+    u32 top = 1; while (2u * top <= c_hi - c_lo) top <<= 1;
+    long long outL = 0, outH = 0;
+    u32 n_out = 0;
+#pragma unroll 1
+    for (u32 p = p0; p < p1; p += 256u) {
+        float x[4];
+        u32 cl[4];
+#pragma unroll
+        for (u32 j = 0; j < 4; ++j) { const u32 at = p + j * 64u + lane; x[j] = at < p1 ? part[at] : 0.f; cl[j] = c_lo; }
+#pragma unroll 1
+        for (u32 step = top; step >= 1u; step >>= 1) {    // number of cut keys <= key, beginning at c_lo
+#pragma unroll
+            for (u32 j = 0; j < 4; ++j) { const u32 c = cl[j] + step; if (c <= c_hi && L.cut[c] <= key_of(x[j])) cl[j] = c; }
+        }
+#pragma unroll
+        for (u32 j = 0; j < 4; ++j) {
+            if (p + j * 64u + lane >= p1 || cl[j] == c_lo) continue;
+            const u32 bits = f2u(x[j]), mb = bits & 0x7fffffffu;
+            const u32 e = mb >> 23, pb = bit_pos(mb), mant = (mb & 0x7fffffu) | (e ? 0x800000u : 0u);
+            const bool neg = bits >> 31;
+            ++n_out;
+            atomicAdd(&acc[EXCP_ABSM_BINS * K + cl[j]], 1ull);
+            if (!mant) continue;
+            const u64 d = (u64)mant << (pb & 7u), dd = neg ? (u64)0 - d : d;
+            atomicAdd(&acc[(pb >> 3) * K + cl[j]], dd);
+            if (near) {
+                const u64 term = (u64)mant << (pb - pos_lo);
+                const long long tl = (long long)(term & 0xffffffffull), th = (long long)(term >> 32);
+                outL += neg ? -tl : tl; outH += neg ? -th : th;
+            } else {
+                atomicAdd(&acc[(pb >> 3) * K + c_lo], (u64)0 - dd);
+            }
+        }
+    }
+    outL = (long long)wave_sum_u64((u64)outL); outH = (long long)wave_sum_u64((u64)outH);
+    n_out = wave_sum_u32(n_out);
+    if (lane == 0u && n_out) {
+        if (outL) lloyd_file(acc, K, c_lo, -outL, pos_lo);
+        if (outH) lloyd_file(acc, K, c_lo, -outH, pos_lo + 32u);
+        atomicAdd(&acc[EXCP_ABSM_BINS * K + c_lo], (u64)0 - (u64)n_out);
+    }
+}
+
+// One wave moves the values at places [q0, q1) of the cut buckets on to their centres in `acc` (LDS): the sum and
+// number of the values above a border go from the centre below it to the one above it.
+__device__ __forceinline__ void lloyd_share(const EXCP_GLOBAL float *part, u32 q0, u32 q1, u32 K, u64 *acc, const LloydShared &L) {
+    while (q0 < q1) {
+        u32 b = 0;                                        // last bucket with off[b] <= q0: it holds place q0
+#pragma unroll 1
+        for (u32 step = NBKT / 2; step >= 1u; step >>= 1) if (L.off[b + step] <= q0) b += step;
+        b = (u32)__builtin_amdgcn_readfirstlane((int)b);
+        const u32 stop = min(q1, min(L.off[b + 1u], q0 + (1u << 21)));
+        const u32 p0 = L.begin[b] + (q0 - L.off[b]), p1 = p0 + (stop - q0);
+        const u32 r = (u32)__builtin_amdgcn_readfirstlane((int)L.range[b]);
+        const u32 c_lo = r & 255u, c_hi = (r >> 8) & 255u, pos_lo = (r >> 16) & 255u, pos_hi = r >> 24;
+        q0 = stop;
+        if (c_hi - c_lo > 2u) lloyd_many(part, p0, p1, c_lo, c_hi, pos_lo, pos_hi, K, acc, L);
+        else if (pos_hi - pos_lo <= 8u) lloyd_borders<false>(part, p0, p1, c_lo, c_hi - c_lo == 2u, pos_lo, pos_hi, K, acc, L);
+        else lloyd_borders<true>(part, p0, p1, c_lo, c_hi - c_lo == 2u, pos_lo, pos_hi, K, acc, L);
+    }
+}
+
+// One workgroup takes a stream through all its iterations; the final centres and cut keys end in the slots of
+// parity `iters`.  KMAX: the centres the LDS accumulators are laid out for.
+template <u32 KMAX>
+__global__ __launch_bounds__(LLOYD_THREADS, KMAX > 63u ? 1 : 2) void k_km_lloyd(Workspace w, GroupParams g) {
+    __shared__ LloydShared L;
+    __shared__ u64 acc[(EXCP_ABSM_BINS + 1u) * KMAX];
+    const u32 sidx = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, K = (u32)g.K, iters = (u32)g.iters;
+    SegState &S = w.seg[sidx];
+    if (S.len == 0 || !excp_lloyd_alone(w.desc[sidx / 3u].n, K)) return;
+    u32 kp2 = 1; while (kp2 < K) kp2 <<= 1;
+    LloydStream st = lloyd_open(w, sidx, K, 1u, false, L);
+    lloyd_clear(acc, st, K);
+    const EXCP_GLOBAL float *part = gptr(seg_part(w, sidx));
+    for (u32 i = 0;; ++i) {
+        lloyd_centres(st, K, i, acc, L);
+        if (i == iters) break;
+        const u32 T = lloyd_cut_buckets(st, kp2, L);
+        if (T <= LLOYD_FEW) {
+            lloyd_few(part, 0u, T, K, kp2, acc, L);
+        } else {
+            const u32 q0 = (u32)(((u64)T * wave) / LLOYD_WAVES), q1 = (u32)(((u64)T * (wave + 1u)) / LLOYD_WAVES);
+            lloyd_share(part, q0, q1, K, acc, L);
+        }
+    }
+    if (tid < K) S.C[iters & 1u][tid] = L.C[tid];
+    if (tid <= EXCP_MAX_K) S.cut[iters & 1u][tid] = tid ? L.cut[tid] : 0u;
+}
+
+// One iteration of the larger streams.  A work unit is a stream's share of its cut buckets that belongs to
+// unit_chunks of its chunks, a workgroup each (the grid is the most units the group can have; those beyond the
+// units there are have nothing to do).  Every workgroup of a stream computes the centres for itself, adds its share
+// up in LDS, and hands the sums over.  The launch after the last iteration (i == iters) only makes the final
+// centres.
+template <u32 KMAX>
+__global__ __launch_bounds__(LLOYD_THREADS, KMAX > 63u ? 1 : 2) void k_km_iter(Workspace w, GroupParams g, u32 i) {
+    __shared__ LloydShared L;
+    __shared__ u64 acc[(EXCP_ABSM_BINS + 1u) * KMAX];
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, u = blockIdx.x;
+    const u32 K = (u32)g.K, nseg = 3u * g.ntensors, accw = (EXCP_ABSM_BINS + 1u) * K;
+    if (u >= w.seg_unit_begin[nseg]) return;
+    // the stream that holds unit u: 64 entries of the table are compared at once
+    u32 sidx = 0;
+#pragma unroll 1
+    for (u32 span = nseg; span > 1u;) {
+        const u32 step = (span + 63u) / 64u;
+        const u64 le = ballot64(lane * step < span && w.seg_unit_begin[min(sidx + lane * step, nseg)] <= u);
+        const u32 pick = (u32)__popcll(le) - 1u;          // (entry 0 of the span is <= u)
+        span = min(step, span - pick * step);
+        sidx += pick * step;
+    }
+    sidx = (u32)__builtin_amdgcn_readfirstlane((int)sidx);
+    const u32 u_first = u - w.seg_unit_begin[sidx], nu = w.seg_unit_begin[sidx + 1u] - (u - u_first);
+    if (i == (u32)g.iters && u_first != 0u) return;
+    u32 kp2 = 1; while (kp2 < K) kp2 <<= 1;
+    SegState &S = w.seg[sidx];
+    u64 *gacc = w.km_acc + (u64)sidx * 3u * accw;         // [3][bins + count][K]
+    LloydStream st = lloyd_open(w, sidx, K, (i + 1u) & 1u, i > 0u, L);
+    if (i == 0u) {
+        lloyd_clear(acc, st, K);
+    } else {
+        const u64 *old = gacc + ((i - 1u) % 3u) * accw;
+        const u32 j1 = (st.acc_hi + 1u) * K;
+        for (u32 j0 = st.acc_lo * K + tid; j0 < j1; j0 += 4u * LLOYD_THREADS) {
+            u64 v[4];
+#pragma unroll
+            for (u32 q = 0; q < 4; ++q) v[q] = j0 + q * LLOYD_THREADS < j1 ? old[j0 + q * LLOYD_THREADS] : 0ull;
+#pragma unroll
+            for (u32 q = 0; q < 4; ++q) if (j0 + q * LLOYD_THREADS < j1) acc[j0 + q * LLOYD_THREADS] = v[q];
+        }
+        if (tid < K) acc[EXCP_ABSM_BINS * K + tid] = old[EXCP_ABSM_BINS * K + tid];
+        __syncthreads();
+        if (tid < NBKT && L.begin[tid + 1u] > L.begin[tid]) st.alo = centre_by_cuts(L.cut, kp2, st.kmin);
+    }
+    lloyd_centres(st, K, i, acc, L);
+    if (u_first == 0u) {
+        // one workgroup per stream keeps what the next iteration starts from, and clears the accumulators
+        // of the iteration after it (they were read by the previous launch for the last time)
+        if (tid < K) S.C[i & 1u][tid] = L.C[tid];
+        if (tid <= EXCP_MAX_K) S.cut[i & 1u][tid] = tid ? L.cut[tid] : 0u;
+        u64 *nxt = gacc + ((i + 1u) % 3u) * accw;
+        for (u32 j = st.acc_lo * K + tid; j < (st.acc_hi + 1u) * K; j += LLOYD_THREADS) nxt[j] = 0;
+        if (tid < K) nxt[EXCP_ABSM_BINS * K + tid] = 0;
+    }
+    if (i == (u32)g.iters) return;
+    const u32 T = lloyd_cut_buckets(st, kp2, L);
+    const u32 x0 = (u32)(((u64)T * u_first) / nu), x1 = (u32)(((u64)T * (u_first + 1u)) / nu);
+    if (x1 - x0 <= LLOYD_FEW) {
+        lloyd_few(gptr(seg_part(w, sidx)), x0, x1, K, kp2, acc, L);
+    } else {
+        const u32 q0 = x0 + (u32)(((u64)(x1 - x0) * wave) / LLOYD_WAVES), q1 = x0 + (u32)(((u64)(x1 - x0) * (wave + 1u)) / LLOYD_WAVES);
+        lloyd_share(gptr(seg_part(w, sidx)), q0, q1, K, acc, L);
+    }
+    __syncthreads();
+    u64 *now = gacc + (i % 3u) * accw;
+    for (u32 j = st.acc_lo * K + tid; j < (st.acc_hi + 1u) * K; j += LLOYD_THREADS) { const u64 v = acc[j]; if (v) atomicAdd(&now[j], v); }
+    if (tid < K) { const u64 v = acc[EXCP_ABSM_BINS * K + tid]; if (v) atomicAdd(&now[EXCP_ABSM_BINS * K + tid], v); }
 }
 
 // The codes of a thread's 32 values of a whole chunk, ORed into the chunk's bit stream in LDS; returns
@@ -1208,9 +1362,8 @@ __global__ __launch_bounds__(EXCP_THREADS, 5) void k_assign_pack(Workspace w, Gr
             len = w.seg[sidx].len; chunk0 = w.seg[sidx].chunk_begin; data = gptr(seg_data(w, sidx));
             nwords = excp_words(len * nbits);
             out = (u64 *)(w.desc[t].blob + (which == 0 ? T.off_cw : (which == 1 ? T.off_cm : T.off_cv)));
-            for (u32 k = tid; k < (u32)K; k += EXCP_THREADS) s_C[k] = w.seg[sidx].C[k];
-            __syncthreads();
-            compute_cut_keys(s_C, K, s_cut);       // the final centres' cut keys
+            if (tid < (u32)K) s_C[tid] = w.seg[sidx].C[g.iters & 1][tid];        // the final centres and their cut keys
+            s_cut[tid] = w.seg[sidx].cut[g.iters & 1][tid];
             __syncthreads();
         }
         const u64 ebase = (u64)(c - chunk0) * EXCP_CHUNK;
@@ -1315,7 +1468,8 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_finalize(Workspace w, GroupPar
     float *books = (float *)(D.blob + EXCP_HEADER);
     for (u32 i = tid; i < 3u * E; i += EXCP_THREADS) {
         u32 which = i / E, e = i % E;
-        books[i] = (e == 0) ? 0.f : w.seg[3u * t + which].C[e - 1];
+        const SegState &S = w.seg[3u * t + which];
+        books[i] = (e == 0 || S.len == 0) ? 0.f : S.C[g.iters & 1][e - 1];
     }
     if (tid == 0) {
         int status = T.status;
@@ -1345,42 +1499,45 @@ void launch_km_partition(const Workspace &w, const GroupParams &g, int phase, hi
     const u32 nseg = 3 * g.ntensors;
     switch (phase) {
         case 0: hipLaunchKernelGGL(k_km_sample, dim3(nseg), dim3(SM_THREADS), 0, s, w, g); break;
-        case 1: hipLaunchKernelGGL(k_km_clear_counts, dim3(excp_grid(w, 8)), dim3(EXCP_THREADS), 0, s, w, g); break;
-        case 2:
-            hipLaunchKernelGGL(k_km_scan_parts, dim3(nseg * SCAN_PARTS), dim3(1024), 0, s, w, g);
-            hipLaunchKernelGGL(k_km_scan, dim3(nseg), dim3(NBKT), 0, s, w, g);
-            hipLaunchKernelGGL(k_km_scan_apply, dim3(nseg * SCAN_PARTS), dim3(1024), 0, s, w, g);
+        case 1: hipLaunchKernelGGL(k_km_scan, dim3(nseg), dim3(1024), 0, s, w, g); break;
+        case 2: hipLaunchKernelGGL(k_km_scatter, dim3(excp_grid(w, 1)), dim3(SC_THREADS), 0, s, w, g); break;
+        default:
+            if (g.wide == 2u) {
+                hipLaunchKernelGGL((k_km_bucket_stats<16, 1>), dim3(nseg * NBKT), dim3(1024), 0, s, w, g, (u32)STREAMS_ALL, nseg);
+            } else {
+                const u32 sel = g.wide ? STREAMS_MV : STREAMS_ALL, ns = stream_count(g.ntensors, sel);
+                if (g.wide) hipLaunchKernelGGL((k_km_bucket_stats<16, 4>), dim3(g.ntensors * (NBKT / 4)), dim3(1024), 0, s, w, g, (u32)STREAMS_W, g.ntensors);
+                hipLaunchKernelGGL((k_km_bucket_stats<4, 4>), dim3(std::min(ns * (NBKT / 4), excp_grid(w, 32))), dim3(256), 0, s, w, g, sel, ns);
+            }
             break;
-        case 3: hipLaunchKernelGGL(k_km_scatter, dim3(excp_grid(w, 1)), dim3(SC_THREADS), 0, s, w, g); break;
-        case 4:
-            if (g.wide == 2u) hipLaunchKernelGGL((k_km_bucket_stats<16, 1>), dim3(nseg * NBKT), dim3(1024), 0, s, w, g);
-            else if (g.wide) hipLaunchKernelGGL((k_km_bucket_stats<16, 4>), dim3(nseg * (NBKT / 4)), dim3(1024), 0, s, w, g);
-            else hipLaunchKernelGGL((k_km_bucket_stats<4, 4>), dim3(std::min(nseg * (NBKT / 4), excp_grid(w, 32))), dim3(256), 0, s, w, g);
-            break;
-        default: break;
     }
 }
 
 void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s) {
     if (!g.ntensors) return;
-    if (g.wide) hipLaunchKernelGGL(k_km_init<1024>, dim3(3 * g.ntensors * (u32)g.K), dim3(1024), 0, s, w, g);
-    else hipLaunchKernelGGL(k_km_init<256>, dim3(3 * g.ntensors * (u32)g.K), dim3(256), 0, s, w, g);
+    const u32 per = (u32)g.K + 1u;
+    if (g.wide == 2u) {
+        hipLaunchKernelGGL(k_km_init<1024>, dim3(3 * g.ntensors * per), dim3(1024), 0, s, w, g, (u32)STREAMS_ALL);
+    } else {
+        const u32 sel = g.wide ? STREAMS_MV : STREAMS_ALL;
+        if (g.wide) hipLaunchKernelGGL(k_km_init<1024>, dim3(g.ntensors * per), dim3(1024), 0, s, w, g, (u32)STREAMS_W);
+        hipLaunchKernelGGL(k_km_init<256>, dim3(stream_count(g.ntensors, sel) * per), dim3(256), 0, s, w, g, sel);
+    }
 }
 
-void launch_km_classify(const Workspace &w, const GroupParams &g, int iteration, hipStream_t s) {
-    if (!g.ntensors) return;
-    hipLaunchKernelGGL(k_km_classify, dim3(3 * g.ntensors), dim3(EXCP_THREADS), 0, s, w, g,
-                       (u32)(iteration & 1), (u32)(iteration > 0));
+// All iterations: the streams that one workgroup takes through them, then, if the group has larger ones, a launch
+// per iteration and one for the final centres.
+template <u32 KMAX>
+static void launch_lloyd(const Workspace &w, const GroupParams &g, hipStream_t s) {
+    hipLaunchKernelGGL(k_km_lloyd<KMAX>, dim3(3 * g.ntensors), dim3(LLOYD_THREADS), 0, s, w, g);
+    if (!g.max_units) return;
+    for (u32 i = 0; i <= (u32)g.iters; ++i) hipLaunchKernelGGL(k_km_iter<KMAX>, dim3((u32)g.max_units), dim3(LLOYD_THREADS), 0, s, w, g, i);
 }
-
-void launch_km_iter(const Workspace &w, const GroupParams &g, int iteration, hipStream_t s) {
+void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s) {
     if (!g.ntensors) return;
-    hipLaunchKernelGGL(k_km_iter, dim3(excp_grid(w, 20)), dim3(EXCP_THREADS), 0, s, w, g, (u32)(iteration & 1));
-}
-
-void launch_km_update(const Workspace &w, const GroupParams &g, hipStream_t s) {
-    if (!g.ntensors) return;
-    hipLaunchKernelGGL(k_km_update, dim3(3 * g.ntensors), dim3(EXCP_THREADS), 0, s, w, g);
+    if (g.K <= 15) launch_lloyd<15>(w, g, s);
+    else if (g.K <= 63) launch_lloyd<63>(w, g, s);
+    else launch_lloyd<EXCP_MAX_K>(w, g, s);
 }
 
 void launch_assign_pack(const Workspace &w, const GroupParams &g, hipStream_t s) {

@@ -309,8 +309,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_scan(Workspace w, GroupPa
 // The same pass counts, for the value partition of the codebook stage, how many of the values it moves
 // fall into each of the 256 value buckets (the map k_km_sample made from the slots): the values are in
 // registers here, and a pass of its own would read them all again.  Counts are kept per 16 chunks
-// (131 072 positions) of a stream, in the row of the first of those chunks; the scatter's workgroups
-// begin only at such positions.  A workgroup adds up in LDS as long as its batches stay inside one tensor
+// (131 072 positions) of a stream, a row each; the scatter's workgroups begin only at such positions.  A workgroup adds up in LDS as long as its batches stay inside one tensor
 // and one such unit per stream, and hands the sums over when that changes.
 constexpr u32 GATHER_SUBS = 32;
 constexpr u32 SUPER_SHIFT = 17;                          // log2 of the positions per counted unit
@@ -338,11 +337,11 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_gather(Workspace w, Group
 #pragma unroll
             for (u32 k = 0; k < 3; ++k) {
                 if (!live[k]) continue;
-                const u32 row0 = w.seg[3u * cur_t + k].chunk_begin + cur_sc[k] * EXCP_SUPER_CHUNKS;
+                const u32 row0 = w.seg[3u * cur_t + k].row_begin + cur_sc[k];
 #pragma unroll
                 for (u32 u = 0; u < 2; ++u) {
                     const u32 h = s_hist[k][u][tid];
-                    if (h) { atomicAdd(&w.km_cnt[(u64)(row0 + u * EXCP_SUPER_CHUNKS) * 256u + tid], h); s_hist[k][u][tid] = 0; }
+                    if (h) { atomicAdd(&w.km_cnt[(u64)(row0 + u) * 256u + tid], h); s_hist[k][u][tid] = 0; }
                 }
             }
         }
@@ -418,7 +417,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_gather(Workspace w, Group
                 for (u32 k = 0; k < 3; ++k) {
                     const u32 sg = 3u * tj + k;
                     g_live[k] = w.seg[sg].len != 0;
-                    g_row[k] = w.seg[sg].chunk_begin;
+                    g_row[k] = w.seg[sg].row_begin;
                     const u32 *mp = w.km_split + (u64)sg * EXCP_KM_MAP_WORDS;
                     if (g_live[k]) { g_par[k][0] = mp[0]; g_par[k][1] = mp[1]; g_par[k][2] = mp[2]; g_par[k][3] = mp[3]; }
                     g_cells[k] = gptr((const unsigned char *)(mp + 4));
@@ -428,7 +427,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_gather(Workspace w, Group
                 if (in_lds) {
                     if (live[k]) atomicAdd(&s_hist[k][(place >> SUPER_SHIFT) != cur_sc[k] ? 1u : 0u][((const unsigned char *)(s_map[k] + 4))[cell_of(x, par[k])]], 1u);
                 } else if (g_live[k]) {
-                    const u32 row = g_row[k] + (place >> SUPER_SHIFT) * EXCP_SUPER_CHUNKS;
+                    const u32 row = g_row[k] + (place >> SUPER_SHIFT);
                     atomicAdd(&w.km_cnt[(u64)row * 256u + g_cells[k][cell_of(x, g_par[k])]], 1u);
                 }
             };
@@ -560,11 +559,11 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_bitmap_o_elems(Workspace 
 // After the masks: blob section offsets, capacity check, survivor stream lengths and the chunk
 // list of the survivor passes.  One workgroup; tensors and streams are few.
 __global__ __launch_bounds__(EXCP_THREADS) void k_layout(Workspace w, GroupParams g, u32 *seg_chunk_begin) {
-    __shared__ u32 s_sum[EXCP_THREADS];
+    __shared__ u32 s_sum[3][EXCP_THREADS / 64];
     const u32 tid = threadIdx.x;
     const u32 nseg = 3u * g.ntensors;
     const u32 per = (nseg + EXCP_THREADS - 1) / EXCP_THREADS;
-    u32 local = 0;
+    u32 local[3] = {0u, 0u, 0u};                          // chunks, rows of the count table, work units
     for (u32 q = 0; q < per; ++q) {
         u32 sidx = tid * per + q;
         if (sidx >= nseg) break;
@@ -601,25 +600,42 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_layout(Workspace w, GroupParam
             if (off > D.blob_cap || S.nonfinite) len = 0;
         }
         w.seg[sidx].len = len;
-        local += (u32)((len + EXCP_CHUNK - 1) / EXCP_CHUNK);
+        const u32 chunks = (u32)((len + EXCP_CHUNK - 1) / EXCP_CHUNK);
+        local[0] += chunks;
+        local[1] += (chunks + EXCP_SUPER_CHUNKS - 1u) / EXCP_SUPER_CHUNKS;
+        if (g.max_units && !excp_lloyd_alone(D.n, (u32)g.K)) local[2] += (chunks + g.unit_chunks - 1u) / g.unit_chunks;
     }
-    s_sum[tid] = local;
+    u32 run[3], total[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        u32 incl = local[q];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const u32 v = __shfl_up(incl, off, WAVE);
+            if ((tid & 63u) >= (u32)off) incl += v;
+        }
+        if ((tid & 63u) == 63u) s_sum[q][tid >> 6] = incl;
+        run[q] = incl - local[q];
+    }
     __syncthreads();
-    for (int off = 1; off < EXCP_THREADS; off <<= 1) {
-        u32 v = (tid >= (u32)off) ? s_sum[tid - off] : 0u;
-        __syncthreads();
-        s_sum[tid] += v;
-        __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        total[q] = 0;
+        for (u32 v = 0; v < EXCP_THREADS / 64; ++v) { if (v < (tid >> 6)) run[q] += s_sum[q][v]; total[q] += s_sum[q][v]; }
     }
-    u32 run = s_sum[tid] - local;
     for (u32 q = 0; q < per; ++q) {
         u32 sidx = tid * per + q;
         if (sidx >= nseg) break;
-        seg_chunk_begin[sidx] = run;
-        w.seg[sidx].chunk_begin = run;
-        run += (u32)((w.seg[sidx].len + EXCP_CHUNK - 1) / EXCP_CHUNK);
+        seg_chunk_begin[sidx] = run[0];
+        w.seg_unit_begin[sidx] = run[2];
+        w.seg[sidx].chunk_begin = run[0];
+        w.seg[sidx].row_begin = run[1];
+        const u32 chunks = (u32)((w.seg[sidx].len + EXCP_CHUNK - 1) / EXCP_CHUNK);
+        run[0] += chunks;
+        run[1] += (chunks + EXCP_SUPER_CHUNKS - 1u) / EXCP_SUPER_CHUNKS;
+        if (g.max_units && !excp_lloyd_alone(w.desc[sidx / 3u].n, (u32)g.K)) run[2] += (chunks + g.unit_chunks - 1u) / g.unit_chunks;
     }
-    if (tid == EXCP_THREADS - 1) { seg_chunk_begin[nseg] = s_sum[tid]; *w.chunk_total = s_sum[tid]; }
+    if (tid == EXCP_THREADS - 1) { seg_chunk_begin[nseg] = total[0]; w.seg_unit_begin[nseg] = total[2]; *w.chunk_total = total[0]; }
 }
 
 }  // namespace
