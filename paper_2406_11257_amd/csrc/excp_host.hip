@@ -797,7 +797,10 @@ int excp_reconstruct_chain(excp_ctx *c, int count, const excp_chain *chains) {
             launch_decode_scan(w, g.ndescs, 0, s);
             if (moments) { launch_decode_count(w, g.ndescs, dtiles, 1, s); launch_decode_scan(w, g.ndescs, 1, s); }
         }
-        { StageTimer t(c, ST_DECODE_MAIN); launch_decode_chain(w, g.count, g.ntiles, s); }
+        bool w16[2] = {false, false};                      // weight storage met in the group (a blob that says otherwise is refused)
+        for (u32 q = 0; q < g.count; ++q) w16[(chains[g.first + q].flags & 0x30u) != 0] = true;
+        for (int k = 0; k < 2; ++k)
+            if (w16[k]) { StageTimer t(c, ST_DECODE_MAIN); launch_decode_chain(w, g.count, g.ntiles, k == 1, s); }
         if (moments) {      // the last checkpoints' moments
             StageTimer t(c, ST_DECODE_MAIN);
             launch_decode_main(w, g.ndescs, dtiles, true, s);

@@ -31,6 +31,24 @@ __device__ __forceinline__ u32 wave_sum_u32(u32 v) {
     for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, WAVE);
     return v;
 }
+// Inclusive sum over the lanes up to the calling one, by moves between registers (no trip through LDS, as
+// shuffles take): four shifts within rows of sixteen lanes, then a row's last lane into the rows above it.
+// Every lane of the wave must be active.
+__device__ __forceinline__ u32 wave_incl_scan_u32(u32 v) {
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);      // row_shr:1
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);      // row_shr:2
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);      // row_shr:4
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);      // row_shr:8
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
+    return v;
+}
+// LDS that only the calling wave uses: what it wrote before is what its lanes read after.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 __device__ __forceinline__ u32 wave_max_u32(u32 v) {
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) v = max(v, (u32)__shfl_xor(v, m, WAVE));

@@ -75,45 +75,77 @@ __global__ void k_decode_parse(Workspace w, u32 ntensors, u32 allow_raw) {
 }
 
 // which == 0: per-tile popcount of bitmap_w.  which == 1: per-tile popcount of the bitmap_o bits
-// that belong to the tile's survivors (needs the scanned bitmap_w counts).  One wave per tile.
+// that belong to the tile's survivors (needs the scanned bitmap_w counts).  A wave takes a contiguous
+// range of tiles.  The bitmap is 1/128 of what the main pass moves, so what bounds this one is latency:
+// the tensor is looked up when it changes, its description comes through the scalar unit, and eight tiles
+// of bitmap_w (eight loads in flight, two counts to a word in the wave's sum) go together.
 template <int WHICH>
 __global__ __launch_bounds__(EXCP_THREADS) void k_decode_count(Workspace w, u32 ntensors, u32 ntiles) {
     __shared__ u32 s_tiles[EXCP_MAX_GROUP_TENSORS + 1];
-    const u32 lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const u32 wpb = EXCP_THREADS / 64;
+    const u32 lane = threadIdx.x & 63u;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     load_tile_table(s_tiles, w.tile_begin, ntensors);
-    for (u32 tile = blockIdx.x * wpb + wave; tile < ntiles; tile += gridDim.x * wpb) {
-        const u32 t = find_owner(s_tiles, ntensors, tile);
-        const DDesc &D = w.ddesc[t];
-        const DState &S = w.dst[t];
-        u32 cnt = 0;
-        if (S.status == 0) {
-            const u32 ltile = tile - D.tile_begin;
-            if (WHICH == 0) {
-                const u64 *bm = (const u64 *)(D.blob + S.off_bw);
-                const u64 word = (u64)ltile * 64 + lane;
-                if (word < excp_words(D.n)) {
-                    u64 v = bm[word];
-                    // bits beyond n must be clear in a well-formed blob; ignore them here
-                    u64 rem = D.n - word * 64;
-                    if (rem < 64) v &= (1ull << rem) - 1ull;
-                    cnt = __popcll(v);
-                }
-            } else if (wants_moments(D)) {                              // only where moments are wanted
-                const u64 *bm = (const u64 *)(D.blob + S.off_bo);
-                u64 p0 = w.dec_cnt_w[tile];
-                u64 p1 = (tile + 1 < D.tile_begin + D.tile_count) ? (u64)w.dec_cnt_w[tile + 1] : S.pop_w;
-                if (p1 > S.n_w) p1 = S.n_w;          // damaged blob: stay inside the bitmap
-                if (p0 > p1) p0 = p1;
-                if (S.flags & 8u) {                  // one bit per element: the tile's own range
-                    p0 = (u64)ltile * EXCP_TILE;
-                    p1 = (D.n - p0 < (u64)EXCP_TILE) ? D.n : p0 + EXCP_TILE;
-                }
-                cnt = popcount_range_lane(bm, p0, p1, lane);
-            }
-            cnt = wave_sum_u32(cnt);
+    const u32 nwaves = gridDim.x * (EXCP_THREADS / 64), wid = blockIdx.x * (EXCP_THREADS / 64) + wave;
+    const u32 t_lo = (u32)(((u64)wid * ntiles) / nwaves), t_hi = (u32)(((u64)(wid + 1u) * ntiles) / nwaves);
+    u32 t = 0, first = 0, end = 0;                         // the tensor in hand, its first tile, one past its last
+    for (u32 tile = t_lo; tile < t_hi;) {
+        if (tile >= end) {
+            t = (u32)__builtin_amdgcn_readfirstlane((int)find_owner(s_tiles, ntensors, tile));
+            first = (u32)__builtin_amdgcn_readfirstlane((int)s_tiles[t]);
+            end = (u32)__builtin_amdgcn_readfirstlane((int)s_tiles[t + 1u]);
         }
-        if (lane == 0) { if (WHICH == 0) w.dec_cnt_w[tile] = cnt; else w.dec_cnt_o[tile] = cnt; }
+        const EXCP_CONSTANT DDesc *D = (const EXCP_CONSTANT DDesc *)(uintptr_t)(w.ddesc + t);
+        const EXCP_CONSTANT DState *S = (const EXCP_CONSTANT DState *)(uintptr_t)(w.dst + t);
+        const u32 ltile = tile - first;
+        if (WHICH == 0) {
+            constexpr u32 AT_ONCE = 8;
+            const u32 group = min(AT_ONCE, min(end, t_hi) - tile);
+            u64 v[AT_ONCE];
+            if (S->status == 0) {
+                const EXCP_GLOBAL u64 *bm = gptr((const u64 *)(D->blob + S->off_bw));
+                const u64 n = D->n, nwords = excp_words(n), word0 = (u64)ltile * 64u + lane;
+                if (ltile * (u64)EXCP_TILE + AT_ONCE * EXCP_TILE <= n) {         // (words of tiles past `group` are counted by another wave too)
+#pragma unroll
+                    for (u32 k = 0; k < AT_ONCE; ++k) v[k] = bm[word0 + 64u * k];
+                } else {
+#pragma unroll
+                    for (u32 k = 0; k < AT_ONCE; ++k) {
+                        // bits beyond n must be clear in a well-formed blob; ignore them here
+                        const u64 word = word0 + 64u * k;
+                        v[k] = word < nwords ? bm[word] : 0ull;
+                        if (word < nwords && n - word * 64u < 64u) v[k] &= (1ull << (n - word * 64u)) - 1ull;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (u32 k = 0; k < AT_ONCE; ++k) v[k] = 0ull;
+            }
+            u32 mine = 0;                                  // lane k: the count of tile + k
+#pragma unroll
+            for (u32 k = 0; k < AT_ONCE; k += 2) {
+                const u32 sum = (u32)__builtin_amdgcn_readlane((int)wave_incl_scan_u32((u32)__popcll(v[k]) | (u32)__popcll(v[k + 1]) << 16), 63);
+                if (lane == k) mine = sum & 0xffffu;
+                if (lane == k + 1u) mine = sum >> 16;
+            }
+            if (lane < group) w.dec_cnt_w[tile + lane] = mine;
+            tile += group;
+        } else {
+            u32 cnt = 0;
+            if (S->status == 0 && (D->m_out != nullptr || D->v_out != nullptr || D->cm != nullptr || D->cv != nullptr)) {
+                const u64 *bm = (const u64 *)(D->blob + S->off_bo);          // (only where moments are wanted)
+                u64 p0 = w.dec_cnt_w[tile];
+                u64 p1 = (tile + 1u < end) ? (u64)w.dec_cnt_w[tile + 1] : S->pop_w;
+                if (p1 > S->n_w) p1 = S->n_w;        // damaged blob: stay inside the bitmap
+                if (p0 > p1) p0 = p1;
+                if (S->flags & 8u) {                 // one bit per element: the tile's own range
+                    p0 = (u64)ltile * EXCP_TILE;
+                    p1 = (D->n - p0 < (u64)EXCP_TILE) ? D->n : p0 + EXCP_TILE;
+                }
+                cnt = wave_sum_u32(popcount_range_lane(bm, p0, p1, lane));
+            }
+            if (lane == 0) w.dec_cnt_o[tile] = cnt;
+            ++tile;
+        }
     }
 }
 
@@ -508,126 +540,181 @@ __global__ __launch_bounds__(EXCP_THREADS, 8) void k_export_dense(Workspace w, u
 // A lane keeps its sixteen weights in registers and adds, checkpoint after checkpoint, the centre
 // of every kept element (one fp32 addition per checkpoint, exactly what applying Alg. 2 again and
 // again computes); W_0 is read once and the result written once, whatever the length of the chain.
-__global__ __launch_bounds__(EXCP_THREADS, 8) void k_decode_chain(Workspace w, u32 ntensors, u32 ntiles) {
-    __shared__ float s_book[256];
-    __shared__ u32 s_tiles[EXCP_MAX_GROUP_TENSORS + 1];
-    __shared__ u32 s_cw[DEC_CODE_WORDS];
-    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    load_tile_table(s_tiles, w.chain_tile_begin, ntensors);
-    for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const u32 t = find_owner(s_tiles, ntensors, tile);
-        const CDesc &C = w.cdesc[t];
-        if (C.W_out == nullptr) continue;
-        bool good = true;                                  // every checkpoint of the chain parsed and counted fine
-        const u32 wt = excp_wtype(w.dst[C.first_desc].flags);      // ... and all store their weights alike
-        for (u32 j = 0; j < C.steps; ++j)
-            good = good && w.dst[C.first_desc + j].status == 0 && excp_wtype(w.dst[C.first_desc + j].flags) == wt;
-        if (!good) continue;                               // same decision for the whole workgroup
-        const bool bf = wt == 2u;
-        const u64 n = C.n;
-        const u32 ltile = tile - C.tile_begin;
-        const u64 base = (u64)ltile * EXCP_TILE;
-        const u32 rem = (n - base < (u64)EXCP_TILE) ? (u32)(n - base) : EXCP_TILE;
-        float wp[4][4];
-        if (wt == 0u) {
-            const EXCP_GLOBAL float *W0 = gptr(C.W0) + base;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const u32 off = wave * 1024u + (u32)k * 256u + lane * 4u;
-                if (off + 4u <= rem) {
-                    const f4u x = *(const EXCP_GLOBAL f4u *)(W0 + off);
-                    wp[k][0] = x.x; wp[k][1] = x.y; wp[k][2] = x.z; wp[k][3] = x.w;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) wp[k][j] = (off + (u32)j < rem) ? W0[off + (u32)j] : 0.f;
-                }
-            }
-        }
-        if (wt != 0u) {                                    // 16-bit weights: the registers hold the widened values
-#pragma unroll
-            for (int k = 0; k < 4; ++k) load_weights4(C.W0, base, wave * 1024u + (u32)k * 256u + lane * 4u, rem, wt, wp[k]);
-        }
-        for (u32 step = 0; step < C.steps; ++step) {
-            const DDesc &D = w.ddesc[C.first_desc + step];
-            const DState &S = w.dst[C.first_desc + step];
-            const u32 nbits = S.nbits, E = 1u << nbits, cmask = E - 1u;
-            const unsigned char *blob = D.blob;
-            u64 myword = 0;
-            {
-                const u64 wword = (u64)ltile * 64 + lane;
-                const u32 bits_here = (lane * 64u < rem) ? min(64u, rem - lane * 64u) : 0u;
-                if (bits_here) myword = gptr((const u64 *)(blob + S.off_bw))[wword];
-                if (bits_here < 64u) myword &= (1ull << bits_here) - 1ull;
-            }
-            const u32 pc = __popcll(myword);
-            u32 incl = pc;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const u32 v = __shfl_up(incl, off, WAVE);
-                if (lane >= (u32)off) incl += v;
-            }
-            const u32 excl = incl - pc;
-            const u32 cnt = __shfl(incl, 63, WAVE);
-            const u32 q_tile = w.dec_cnt_w[D.tile_begin + ltile];
-            const u64 wbit0 = (u64)q_tile * nbits;
-            const u32 woff = (u32)(wbit0 & 31ull);
-            __syncthreads();                               // the previous checkpoint's LDS readers are done
-            {
-                const EXCP_GLOBAL float *book = gptr((const float *)(blob + EXCP_HEADER));
-                for (u32 i = tid; i < E; i += EXCP_THREADS) s_book[i] = book[i];
-            }
-            stage_words(s_cw, gptr((const u32 *)(blob + S.off_cw)) + (wbit0 >> 5), (woff + cnt * nbits + 31u) >> 5);
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const u32 wq = wave * 16u + (u32)k * 4u + (lane >> 4);
-                const u32 sub = (lane & 15u) * 4u;
-                const u32 wlo = __shfl((u32)myword, wq, WAVE), whi = __shfl((u32)(myword >> 32), wq, WAVE);
-                const u32 wex = __shfl(excl, wq, WAVE);
-                const u64 word = ((u64)whi << 32) | wlo;
-                const u32 nib = (u32)(word >> sub) & 15u;
-                const u32 r = wex + __popcll(word & ((1ull << sub) - 1ull));
-                u32 f = window32(s_cw, woff + r * nbits);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const bool kept = (nib >> j) & 1u;
-                    const float c = s_book[f & cmask];
-                    float sum = wp[k][j] + c;
-                    if (wt != 0u) sum = w16_widen(w16_narrow(sum, bf), bf);   // every checkpoint rounds into the storage format
-                    wp[k][j] = kept ? sum : wp[k][j];
-                    f = kept ? (f >> nbits) : f;
-                }
-            }
-        }
-        if (wt != 0u) {
-            EXCP_GLOBAL unsigned short *Ho = gptr((unsigned short *)C.W_out) + base;
-            const bool vec = ((uintptr_t)C.W_out & 7u) == 0u;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const u32 off = wave * 1024u + (u32)k * 256u + lane * 4u;
-                us4 o16;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) o16[j] = (unsigned short)w16_narrow(wp[k][j], bf);
-                if (vec && off + 4u <= rem) *(EXCP_GLOBAL us4 *)(Ho + off) = o16;
-                else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) if (off + (u32)j < rem) Ho[off + (u32)j] = o16[j];
-                }
-            }
-            continue;
-        }
-        EXCP_GLOBAL float *Wo = gptr(C.W_out) + base;
+//
+// A checkpoint moves only 0.3 bytes per element, so from two checkpoints on the arithmetic of the rank and
+// code look-ups bounds this kernel, not memory.  Each wave takes a quarter of a tile (1024 elements) for
+// itself, with no barrier anywhere: bits and ranks go round the wave once per checkpoint, packed as
+// "sixteen bits, survivors before them" (one exchange then gives a lane all it needs for four elements), and
+// a code leaves its window by a bit-field extract whose width is 0 where the element is pruned.  While one
+// checkpoint is worked on, the codes of the next and the bitmap word of the one after it are on their way.
+// (A 410M-shaped checkpoint, eight steps of 4 bits: 2463 -> 1133 us, of which the floor of the bytes is 800 for all.)
+struct ChainBits {
+    u32 pk;                                                // lane's 16-bit piece of the quarter's bitmap, survivors before it << 16
+    u32 q, kept, nbits;                                    // survivors of the tensor before the quarter, in it (the same in every lane)
+    u32 code; float centre;                                // the first 64 words of codes and of the codebook, one per lane
+};
+#define CHAIN_CODE_WORDS 260   // u32 words of 1024 codes of 8 bits, one for the first bit's place, one for the window's second half
+
+// One wave's quarter of a tile through all checkpoints.
+template <bool W16>
+__device__ __forceinline__ void chain_quarter(const Workspace &w, const EXCP_CONSTANT CDesc *C, u32 tile, u32 wave, u32 wt, float *book, u32 *codes) {
+    const bool bf = wt == 2u;
+    const u32 steps = C->steps;
+    u32 lane = threadIdx.x & 63u;
+    asm volatile("" : "+v"(lane));                         // (keeps what follows from the lane out of the registers held over all tiles)
+    const u32 sh4 = (lane & 3u) * 4u, below4 = (1u << sh4) - 1u;   // the lane's four bits in their piece
+    const u32 ltile = tile - C->tile_begin;
+    const u64 base = (u64)ltile * EXCP_TILE;
+    const u32 rem = (C->n - base < (u64)EXCP_TILE) ? (u32)(C->n - base) : EXCP_TILE;
+    if (wave * 1024u >= rem) return;
+    const EXCP_CONSTANT DDesc *D0 = (const EXCP_CONSTANT DDesc *)(uintptr_t)(w.ddesc + C->first_desc);
+    const EXCP_CONSTANT DState *S0 = (const EXCP_CONSTANT DState *)(uintptr_t)(w.dst + C->first_desc);
+    const EXCP_CONSTANT u32 *counts = (const EXCP_CONSTANT u32 *)(uintptr_t)w.dec_cnt_w;
+    const u32 bits_here = (lane * 64u < rem) ? min(64u, rem - lane * 64u) : 0u;
+    const u32 my_word = min(lane, (rem - 1u) >> 6);
+    const u32 from1 = lane & ~3u;                          // four times the lane / 4 of pk that the lane's elements of batch 0 belong to
+    const u32 from4 = (wave * 16u + (lane >> 2)) * 4u;     // exchanges take lane numbers times four
+    // the lane's word of the tile's bitmap (what lies past the last element is dropped in bits_of)
+    auto load_word = [&](u32 step) { return gptr((const u64 *)(D0[step].blob + S0[step].off_bw))[(u64)ltile * 64u + my_word]; };
+    auto bits_of = [&](u32 step, u64 word) {
+        word &= bits_here < 64u ? (1ull << bits_here) - 1ull : ~0ull;
+        const u32 pc = (u32)__popcll(word), excl = wave_incl_scan_u32(pc) - pc;
+        const u32 q0 = (u32)__builtin_amdgcn_readlane((int)excl, (int)(wave * 16u));
+        const u32 q1 = (u32)__builtin_amdgcn_readlane((int)(excl + pc), (int)(wave * 16u + 15u));
+        // the lane's piece: quarter (lane & 3) of word wave * 16 + lane / 4
+        const u32 lo = (u32)__builtin_amdgcn_ds_bpermute((int)from4, (int)(u32)word);
+        const u32 hi = (u32)__builtin_amdgcn_ds_bpermute((int)from4, (int)(u32)(word >> 32));
+        const u32 before = (u32)__builtin_amdgcn_ds_bpermute((int)from4, (int)excl) - q0;
+        const u32 half = (lane & 2u) ? hi : lo, skip = (lane & 2u) ? (u32)__popc(lo) : 0u;
+        const u32 piece = (lane & 1u) ? half >> 16 : half & 0xffffu, skip2 = (lane & 1u) ? (u32)__popc(half & 0xffffu) : 0u;
+        ChainBits B;
+        B.pk = piece | (before + skip + skip2) << 16;
+        B.nbits = S0[step].nbits; B.q = counts[D0[step].tile_begin + ltile] + q0; B.kept = q1 - q0;
+        const unsigned char *blob = D0[step].blob;
+        const u64 bit0 = (u64)B.q * B.nbits;
+        const u32 words = ((u32)(bit0 & 31ull) + B.kept * B.nbits + 31u) >> 5;
+        // (no survivors: any word of the blob will do)
+        const EXCP_GLOBAL u32 *cw = gptr((const u32 *)(words ? blob + S0[step].off_cw + (bit0 >> 5) * 4u : blob));
+        B.code = cw[lane < words ? lane : 0u];
+        B.centre = gptr((const float *)(blob + EXCP_HEADER))[min(lane, (1u << B.nbits) - 1u)];
+        return B;
+    };
+    u64 word = load_word(0);
+    float wp[4][4];
+    if (!W16) {
+        const EXCP_GLOBAL float *W0 = gptr(C->W0) + base;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const u32 off = wave * 1024u + (u32)k * 256u + lane * 4u;
             if (off + 4u <= rem) {
-                f4u y; y.x = wp[k][0]; y.y = wp[k][1]; y.z = wp[k][2]; y.w = wp[k][3];
-                *(EXCP_GLOBAL f4u *)(Wo + off) = y;
+                const f4u x = *(const EXCP_GLOBAL f4u *)(W0 + off);
+                wp[k][0] = x.x; wp[k][1] = x.y; wp[k][2] = x.z; wp[k][3] = x.w;
             } else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) if (off + (u32)j < rem) Wo[off + (u32)j] = wp[k][j];
+                for (int j = 0; j < 4; ++j) wp[k][j] = (off + (u32)j < rem) ? W0[off + (u32)j] : 0.f;
             }
         }
+    } else {                                           // 16-bit weights: the registers hold the widened values
+#pragma unroll
+        for (int k = 0; k < 4; ++k) load_weights4(C->W0, base, wave * 1024u + (u32)k * 256u + lane * 4u, rem, wt, wp[k]);
+    }
+    ChainBits B = bits_of(0, word);
+    wave_lds_fence();                                      // (loads in the order in which the loop waits for them)
+    word = load_word(min(1u, steps - 1u));
+    for (u32 step = 0; step < steps; ++step) {
+        const u32 pk = B.pk, nbits = B.nbits;
+        const u64 bit0 = (u64)B.q * nbits;
+        const u32 woff = (u32)(bit0 & 31ull), words = (woff + B.kept * nbits + 31u) >> 5;
+        codes[lane] = B.code;
+        book[lane] = B.centre;
+        if (words > 64u || nbits > 6u) {
+            const EXCP_GLOBAL u32 *cw = gptr((const u32 *)(D0[step].blob + S0[step].off_cw)) + (bit0 >> 5);
+            const EXCP_GLOBAL float *centres = gptr((const float *)(D0[step].blob + EXCP_HEADER));
+#pragma unroll 1
+            for (u32 i = 64u + lane; i < words; i += 64u) codes[i] = cw[i];
+#pragma unroll 1
+            for (u32 i = 64u + lane; i < (1u << nbits); i += 64u) book[i] = centres[i];
+        }
+        wave_lds_fence();
+        // (past the last checkpoint the last one's bits are looked at again: no branch round a load)
+        B = bits_of(min(step + 1u, steps - 1u), word);
+        word = load_word(min(step + 2u, steps - 1u));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const u32 p = (u32)__builtin_amdgcn_ds_bpermute((int)(from1 + (u32)k * 64u), (int)pk);
+            const u32 r = (u32)__popc(p & below4) + (p >> 16);        // quarter rank of the lane's first survivor
+            const u32 nib = p >> sh4;
+            const u32 f = window32(codes, woff + r * nbits);
+            u32 at = 0;                                               // first bit of the element's code in the window
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                u32 kept = (u32)__builtin_amdgcn_sbfe((int)nib, (u32)j, 1u);   // all ones or 0
+                asm("" : "+v"(kept));                          // (a mask, not a comparison: one bit-field insert below)
+                const u32 width = kept & nbits;
+                float sum = wp[k][j] + book[__builtin_amdgcn_ubfe(f, at, width)];
+                if (W16) sum = w16_widen(w16_narrow(sum, bf), bf);   // every checkpoint rounds into the storage format
+                wp[k][j] = u2f((f2u(sum) & kept) | (f2u(wp[k][j]) & ~kept));
+                at += width;
+            }
+        }
+        // The wave's reads of these codes are done.  (It also keeps the loads for the next checkpoint above it:
+        // without a fence the compiler moves them round the loop, to where they are waited for.)
+        wave_lds_fence();
+    }
+    if (W16) {
+        EXCP_GLOBAL unsigned short *Ho = gptr((unsigned short *)C->W_out) + base;
+        const bool vec = ((uintptr_t)C->W_out & 7u) == 0u;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const u32 off = wave * 1024u + (u32)k * 256u + lane * 4u;
+            us4 o16;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o16[j] = (unsigned short)w16_narrow(wp[k][j], bf);
+            if (vec && off + 4u <= rem) *(EXCP_GLOBAL us4 *)(Ho + off) = o16;
+            else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) if (off + (u32)j < rem) Ho[off + (u32)j] = o16[j];
+            }
+        }
+        return;
+    }
+    EXCP_GLOBAL float *Wo = gptr(C->W_out) + base;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const u32 off = wave * 1024u + (u32)k * 256u + lane * 4u;
+        if (off + 4u <= rem) {
+            f4u y; y.x = wp[k][0]; y.y = wp[k][1]; y.z = wp[k][2]; y.w = wp[k][3];
+            *(EXCP_GLOBAL f4u *)(Wo + off) = y;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) if (off + (u32)j < rem) Wo[off + (u32)j] = wp[k][j];
+        }
+    }
+}
+
+// W16: takes the chains of 16-bit weights, or else those of fp32 weights.
+template <bool W16>
+__global__ __launch_bounds__(EXCP_THREADS, W16 ? 6 : 8) void k_decode_chain(Workspace w, u32 ntensors, u32 ntiles) {
+    __shared__ float s_book[EXCP_THREADS / 64][256];
+    __shared__ u32 s_code[EXCP_THREADS / 64][CHAIN_CODE_WORDS];
+    __shared__ u32 s_tiles[EXCP_MAX_GROUP_TENSORS + 1];
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    load_tile_table(s_tiles, w.chain_tile_begin, ntensors);
+    u32 t = 0, end = 0, wt = 0;
+    bool good = false;                                     // the tensor is wanted, every checkpoint of its chain parsed and counted fine
+    for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        if (tile >= end) {                                 // (a workgroup's tiles only go up)
+            t = (u32)__builtin_amdgcn_readfirstlane((int)find_owner(s_tiles, ntensors, tile));
+            end = (u32)__builtin_amdgcn_readfirstlane((int)s_tiles[t + 1u]);
+            const EXCP_CONSTANT CDesc *Ct = (const EXCP_CONSTANT CDesc *)(uintptr_t)(w.cdesc + t);
+            const EXCP_CONSTANT DState *S = (const EXCP_CONSTANT DState *)(uintptr_t)(w.dst + Ct->first_desc);
+            wt = excp_wtype(S->flags);
+            good = Ct->W_out != nullptr && (wt != 0u) == W16;       // ... and all store their weights alike
+            for (u32 j = 0; j < Ct->steps; ++j) good = good && S[j].status == 0 && excp_wtype(S[j].flags) == wt;
+        }
+        if (!good) continue;
+        const EXCP_CONSTANT CDesc *C = (const EXCP_CONSTANT CDesc *)(uintptr_t)(w.cdesc + t);
+        chain_quarter<W16>(w, C, tile, wave, wt, s_book[wave], s_code[wave]);
     }
 }
 
@@ -876,7 +963,7 @@ void launch_decode_from_compress(const Workspace &w, const GroupParams &g, hipSt
 void launch_decode_count(const Workspace &w, u32 ntensors, u32 ntiles, int which, hipStream_t s) {
     if (!ntiles) return;
     u32 blocks = (ntiles + 3) / 4;
-    if (blocks > 4096) blocks = 4096;
+    if (blocks > excp_grid(w, 8)) blocks = excp_grid(w, 8);
     if (which == 0) hipLaunchKernelGGL(k_decode_count<0>, dim3(blocks), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);
     else hipLaunchKernelGGL(k_decode_count<1>, dim3(blocks), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);
 }
@@ -938,11 +1025,12 @@ void launch_decode_finish(const Workspace &w, u32 ntensors, hipStream_t s) {
     if (!ntensors) return;
     hipLaunchKernelGGL(k_decode_finish, dim3((ntensors + 255) / 256), dim3(256), 0, s, w, ntensors, w.rec_base);
 }
-void launch_decode_chain(const Workspace &w, u32 ntensors, u32 ntiles, hipStream_t s) {
+void launch_decode_chain(const Workspace &w, u32 ntensors, u32 ntiles, bool w16, hipStream_t s) {
     if (!ntiles) return;
     u32 blocks = excp_grid(w, 64);
     if (blocks > ntiles) blocks = ntiles;
-    hipLaunchKernelGGL(k_decode_chain, dim3(blocks), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);
+    if (w16) hipLaunchKernelGGL(k_decode_chain<true>, dim3(blocks), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);
+    else hipLaunchKernelGGL(k_decode_chain<false>, dim3(blocks), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);
 }
 void launch_chain_finish(const Workspace &w, u32 ntensors, hipStream_t s) {
     if (!ntensors) return;
