@@ -333,12 +333,7 @@ __device__ __forceinline__ void decode_tiles(const Workspace &w, u32 ntensors, u
             if (bits_here < 64u) myword &= (1ull << bits_here) - 1ull;
         }
         const u32 pc = __popcll(myword);
-        u32 incl = pc;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const u32 v = __shfl_up(incl, off, WAVE);
-            if (lane >= (u32)off) incl += v;
-        }
+        u32 incl = wave_incl_scan_u32(pc);
         const u32 excl = incl - pc;
         const u32 cnt = __shfl(incl, 63, WAVE);            // survivors of this tile
         const u32 q_tile = w.dec_cnt_w[tile];              // survivors before this tile
@@ -381,12 +376,7 @@ __device__ __forceinline__ void decode_tiles(const Workspace &w, u32 ntensors, u
                     if (i == 0u) word &= ~((1u << ooff) - 1u);     // bits of earlier tiles' survivors
                     if (nw2m && i + 1u == owords && (obits_total & 31u)) word &= (1u << (obits_total & 31u)) - 1u;   // bits past the last element
                     const u32 opc = __popc(word);
-                    u32 oincl = opc;
-#pragma unroll
-                    for (int off = 1; off < 64; off <<= 1) {
-                        const u32 v = __shfl_up(oincl, off, WAVE);
-                        if (lane >= (u32)off) oincl += v;
-                    }
+                    u32 oincl = wave_incl_scan_u32(opc);
                     if (i < DEC_OBIT_WORDS) { s_ow[i] = word; s_oex[i] = carry + oincl - opc; }
                     carry += __shfl(oincl, 63, WAVE);
                 }

@@ -181,12 +181,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_km_sample(Workspace w, GroupPara
     }
 #pragma unroll
     for (int sg = 0; sg < 2; ++sg) {
-        u32 lo = mn[sg], hi = mx[sg];
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) {
-            lo = min(lo, (u32)__shfl_xor(lo, m, WAVE));
-            hi = max(hi, (u32)__shfl_xor(hi, m, WAVE));
-        }
+        const u32 lo = wave_min_u32(mn[sg]), hi = wave_max_u32(mx[sg]);
         if ((tid & 63u) == 0) { atomicMin(&s_ext[2 * sg], lo); atomicMax(&s_ext[2 * sg + 1], hi); }
     }
     __syncthreads();
@@ -219,12 +214,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_km_sample(Workspace w, GroupPara
         local[q] = cnt[tid * PER + q];
         sum += local[q] >= heavy_min ? (1u << 16) : local[q];
     }
-    u32 incl = sum;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const u32 v = __shfl_up(incl, off, WAVE);
-        if (lane_id() >= (u32)off) incl += v;
-    }
+    u32 incl = wave_incl_scan_u32(sum);
     if (lane_id() == 63u) s_wave[tid >> 6] = incl;
     __syncthreads();
     u32 run = incl - sum, total = 0;
@@ -289,12 +279,7 @@ __global__ __launch_bounds__(1024) void k_km_scan(Workspace w, GroupParams g) {
     tot[q][b] = s;
     __syncthreads();
     const u32 total = tot[0][b] + tot[1][b] + tot[2][b] + tot[3][b];
-    u32 incl = total;                                     // (the four quarters scan the same 256 totals)
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const u32 v = __shfl_up(incl, off, WAVE);
-        if (lane >= (u32)off) incl += v;
-    }
+    u32 incl = wave_incl_scan_u32(total);                                     // (the four quarters scan the same 256 totals)
     if (q == 0 && lane == 63u) s_wave[b >> 6] = incl;
     __syncthreads();
     u32 run = incl - total;
@@ -623,12 +608,7 @@ __global__ __launch_bounds__(BS_WAVES * 64) void k_km_bucket_stats(Workspace w, 
             mag = min(mag, mb - 1u);
         }
         const long long tL = (long long)wave_sum_u64((u64)S.lo), tH = (long long)wave_sum_u64((u64)S.hi);
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) {
-            kmin = min(kmin, (u32)__shfl_xor(kmin, m, WAVE));
-            kmax = max(kmax, (u32)__shfl_xor(kmax, m, WAVE));
-            mag = min(mag, (u32)__shfl_xor(mag, m, WAVE));
-        }
+        kmin = wave_min_u32(kmin); kmax = wave_max_u32(kmax); mag = wave_min_u32(mag);
         if (lane == 0) {
             atomicMin(&s_min[j], kmin); atomicMax(&s_max[j], kmax); atomicMin(&s_mag[j], mag);
             file_i64(mybins, tL, B); file_i64(mybins, tH, B + 32u);
@@ -689,12 +669,7 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
                 if (lane == 63u) row[NBKT] = 0;
                 continue;
             }
-            u64 incl = sum;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const u32 ulo = __shfl_up((u32)incl, off, WAVE), uhi = __shfl_up((u32)(incl >> 32), off, WAVE);
-                if (lane >= (u32)off) incl += ((u64)uhi << 32) | ulo;
-            }
+            const u64 incl = wave_incl_scan_u64(sum);
             u64 run = incl - sum;
 #pragma unroll
             for (u32 q = 0; q < 4; ++q) { row[4u * lane + q] = run; run += v[q]; }
@@ -811,12 +786,7 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
         u32 c[PER], local = 0;
 #pragma unroll
         for (u32 i = 0; i < PER; ++i) { c[i] = hist[tid * PER + i]; local += c[i]; }
-        u32 incl = local;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const u32 v = __shfl_up(incl, off, WAVE);
-            if (lane >= (u32)off) incl += v;
-        }
+        u32 incl = wave_incl_scan_u32(local);
         if (lane == 63u) s_wave[wave] = incl;
         __syncthreads();
         u32 before = incl - local;
@@ -966,12 +936,7 @@ __device__ __forceinline__ u32 lloyd_cut_buckets(LloydStream &st, u32 kp2, Lloyd
         if (alo != ahi) size = cntb;
         st.alo = alo;
         L.range[tid] = alo | (ahi << 8) | (st.pos << 16);
-        incl = size;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const u32 v = __shfl_up(incl, off, WAVE);
-            if (lane >= (u32)off) incl += v;
-        }
+        incl = wave_incl_scan_u32(size);
         if (lane == 63u) L.wave[wave] = incl;
     }
     __syncthreads();
@@ -1081,17 +1046,12 @@ __device__ __forceinline__ void lloyd_borders(const EXCP_GLOBAL float *part, u32
         for (u32 j = 0; j < 16; ++j) if (p + j * 64u < p1) take(x[j]);
         if (WIDE) { S1.fold(B); S2.fold(B); }
     }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) { cnt1 += __shfl_xor(cnt1, m, WAVE); cnt2 += __shfl_xor(cnt2, m, WAVE); }
+    cnt1 = wave_sum_u32(cnt1); cnt2 = wave_sum_u32(cnt2);
     // lane j files what cluster c_lo + j receives
     const u32 n = lane == 0u ? 0u - cnt1 : (lane == 1u ? cnt1 - cnt2 : cnt2);
     if (!WIDE) {
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) S1.part += shfl_xor_f64(S1.part, m);
-        if (two) {
-#pragma unroll
-            for (int m = 32; m >= 1; m >>= 1) S2.part += shfl_xor_f64(S2.part, m);
-        }
+        S1.part = wave_sum_f64(S1.part);
+        if (two) S2.part = wave_sum_f64(S2.part);
         const long long m1 = (long long)ldexp(S1.part, 149 - (int)B), m2 = (long long)ldexp(S2.part, 149 - (int)B);
         const long long v = lane == 0u ? -m1 : (lane == 1u ? m1 - m2 : m2);
         if (lane < 3u && v) lloyd_file(acc, K, c_lo + lane, v, B);

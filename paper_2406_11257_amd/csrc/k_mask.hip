@@ -608,12 +608,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_layout(Workspace w, GroupParam
     u32 run[3], total[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        u32 incl = local[q];
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const u32 v = __shfl_up(incl, off, WAVE);
-            if ((tid & 63u) >= (u32)off) incl += v;
-        }
+        u32 incl = wave_incl_scan_u32(local[q]);
         if ((tid & 63u) == 63u) s_sum[q][tid >> 6] = incl;
         run[q] = incl - local[q];
     }

@@ -106,12 +106,7 @@ __global__ __launch_bounds__(MED_THREADS) void k_median_bracket(Workspace w, Gro
         // both histograms scanned together, 16 bits each (at most 8192 keys)
         const u32 *h1 = apart ? hist[1] : hist[0];
         const u32 c0 = hist[0][2u * tid] | (h1[2u * tid] << 16), c1 = hist[0][2u * tid + 1u] | (h1[2u * tid + 1u] << 16);
-        u32 incl = c0 + c1;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const u32 v = __shfl_up(incl, off, WAVE);
-            if (lane >= (u32)off) incl += v;
-        }
+        u32 incl = wave_incl_scan_u32(c0 + c1);
         if (lane == 63u) s_wave[wave] = incl;
         __syncthreads();
         u32 before = incl - c0 - c1;
@@ -645,12 +640,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_median_select(Workspace w, Gro
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) { local += c[i]; H[tid * 8 + i] = 0; }
-        u32 incl = local;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const u32 v = __shfl_up(incl, off, WAVE);
-            if (lane >= (u32)off) incl += v;
-        }
+        u32 incl = wave_incl_scan_u32(local);
         if (lane == 63u) s_wave[wave] = incl;
         if (tid == 0) w.sel_ticket[t] = 0;
         __syncthreads();
