@@ -10,6 +10,8 @@
 // every slot to its place in the dense survivor arrays; k_mask_bitmap_o then assembles bitmap_o from
 // the sub-tiles' local bit streams.  The extra copy costs 8 bytes per survivor; it replaces a chained
 // scan whose waits cost more than that.
+#include <algorithm>
+
 #include "excp_util.h"
 
 namespace {
@@ -303,7 +305,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_scan(Workspace w, GroupPa
 }
 
 // Pass B: one wave per sub-tile copies the slot to its place in the dense survivor arrays.  A workgroup takes a
-// contiguous range of batches of 32 consecutive sub-tiles; a batch's counts, prefixes and tensor data are
+// contiguous range of batches of up to 32 consecutive sub-tiles; a batch's counts, prefixes and tensor data are
 // fetched once, side by side, into LDS, so that a wave's copies do not wait behind a chain of dependent
 // look-ups.
 // The same pass counts, for the value partition of the codebook stage, how many of the values it moves
@@ -311,11 +313,14 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_scan(Workspace w, GroupPa
 // registers here, and a pass of its own would read them all again.  Counts are kept per 16 chunks
 // (131 072 positions) of a stream, a row each; the scatter's workgroups begin only at such positions.  A workgroup adds up in LDS as long as its batches stay inside one tensor
 // and one such unit per stream, and hands the sums over when that changes.
-constexpr u32 GATHER_SUBS = 32;
+// A wave takes its sub-tiles of a batch one after the other, so a batch has as many as leave four batches to a
+// compute unit, and at least one for each of the four waves (with 32 always, a 16.8 M-element tensor was 256
+// workgroups of eight round trips each: 51 -> 29 us, and the 14M shape's small tensors 126 -> 35 us).
+constexpr u32 GATHER_SUBS = 32;                          // most sub-tiles of a batch
 constexpr u32 SUPER_SHIFT = 17;                          // log2 of the positions per counted unit
 static_assert((1u << SUPER_SHIFT) == EXCP_SUPER_CHUNKS * EXCP_CHUNK, "counted unit = EXCP_SUPER_CHUNKS chunks");
 
-__global__ __launch_bounds__(EXCP_THREADS) void k_mask_gather(Workspace w, GroupParams g) {
+__global__ __launch_bounds__(EXCP_THREADS) void k_mask_gather(Workspace w, GroupParams g, u32 subs) {
     __shared__ u32 s_tiles[EXCP_MAX_GROUP_TENSORS + 1];
     __shared__ u32 s_tw[GATHER_SUBS], s_to[GATHER_SUBS], s_pw[GATHER_SUBS], s_po[GATHER_SUBS], s_t[GATHER_SUBS];
     __shared__ u64 s_slot[GATHER_SUBS], s_eoff[GATHER_SUBS];
@@ -325,7 +330,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_gather(Workspace w, Group
     const u32 nsub = 2u * g.ntiles;
     const bool counting = (g.flags & 4u) == 0u;          // (no codebooks without quantisation)
     load_tile_table(s_tiles, w.tile_begin, g.ntensors);
-    const u32 nbatch = (nsub + GATHER_SUBS - 1u) / GATHER_SUBS;
+    const u32 nbatch = (nsub + subs - 1u) / subs;
     const u32 b_lo = (u32)(((u64)blockIdx.x * nbatch) / gridDim.x), b_hi = (u32)(((u64)(blockIdx.x + 1u) * nbatch) / gridDim.x);
     for (u32 i = tid; i < 3u * 2u * 256u; i += EXCP_THREADS) (&s_hist[0][0][0])[i] = 0;
     u32 cur_t = 0xffffffffu, cur_sc[3] = {0u, 0u, 0u};   // what the LDS counts belong to
@@ -348,9 +353,9 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_gather(Workspace w, Group
         __syncthreads();
     };
     for (u32 batch = b_lo; batch < b_hi; ++batch) {
-        const u32 sub0 = batch * GATHER_SUBS;
+        const u32 sub0 = batch * subs;
         __syncthreads();
-        if (tid < GATHER_SUBS) {
+        if (tid < subs) {
             const u32 sub = sub0 + tid;
             u32 tw = 0, to = 0;
             if (sub < nsub) {
@@ -365,7 +370,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_gather(Workspace w, Group
             s_tw[tid] = tw; s_to[tid] = to;
         }
         __syncthreads();
-        const u32 nvalid = min(GATHER_SUBS, nsub - sub0);
+        const u32 nvalid = min(subs, nsub - sub0);
         const u32 t0 = s_t[0];
         const bool one_tensor = t0 == s_t[nvalid - 1u];
         if (counting) {
@@ -650,9 +655,10 @@ void launch_mask_compact(const Workspace &w, const GroupParams &g, int phase, hi
         hipLaunchKernelGGL(k_mask_scan_parts, dim3(g.ntensors * MSCAN_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
         hipLaunchKernelGGL(k_mask_scan, dim3(g.ntensors * MSCAN_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
     } else {
-        u32 grid = (nsub + 31) / 32;
+        const u32 subs = std::min(std::max(nsub / excp_grid(w, 4) & ~3u, 4u), GATHER_SUBS);
+        u32 grid = (nsub + subs - 1u) / subs;
         if (grid > excp_grid(w, 48)) grid = excp_grid(w, 48);
-        hipLaunchKernelGGL(k_mask_gather, dim3(grid), dim3(EXCP_THREADS), 0, s, w, g);
+        hipLaunchKernelGGL(k_mask_gather, dim3(grid), dim3(EXCP_THREADS), 0, s, w, g, subs);
         u32 grid_o = (g.ntiles + 3) / 4;
         if (grid_o > excp_grid(w, 16)) grid_o = excp_grid(w, 16);
         if (g.flags & 8u) hipLaunchKernelGGL(k_mask_bitmap_o_elems, dim3(grid_o), dim3(EXCP_THREADS), 0, s, w, g);
