@@ -143,22 +143,19 @@ void make_groups(int count, u64 cap_elems, u32 tcap, GetN get_n, std::vector<Gro
     }
 }
 
-void run_decode_prep_and_main(excp_ctx *c, const Workspace &w, u32 ntensors, u32 ntiles, bool moments) {
-    {
-        StageTimer t(c, ST_DECODE_PREP);
-        launch_decode_count(w, ntensors, ntiles, 0, c->stream);
-        launch_decode_scan(w, ntensors, 0, c->stream);
-        if (moments) {
-            launch_decode_count(w, ntensors, ntiles, 1, c->stream);
-            launch_decode_scan(w, ntensors, 1, c->stream);
-        }
-    }
-    {
-        StageTimer t(c, ST_DECODE_MAIN);
-        launch_decode_main(w, ntensors, ntiles, moments, c->stream);
-        launch_decode_main16(w, ntensors, ntiles, moments, c->stream);  // blobs of 16-bit weights, if any
-        launch_decode_raw(w, ntensors, ntiles, moments, c->stream);     // blobs written without quantisation, if any
-    }
+// `w32`, `w16`: the group has tensors of fp32 / of 16-bit weights (blobs of the other kind are refused).
+void run_decode_main(excp_ctx *c, const Workspace &w, u32 ntensors, u32 ntiles, bool moments, bool w32, bool w16) {
+    StageTimer t(c, ST_DECODE_MAIN);
+    if (w32) launch_decode_main(w, ntensors, ntiles, moments, c->stream);
+    if (w16) launch_decode_main16(w, ntensors, ntiles, moments, c->stream);
+    launch_decode_raw(w, ntensors, ntiles, moments, c->stream);     // blobs written without quantisation, if any
+}
+
+// The most tiles a tensor of [first, first + count) has.
+u32 largest_tiles(const DDesc *d, u32 count) {
+    u32 largest = 0;
+    for (u32 q = 0; q < count; ++q) largest = std::max(largest, d[q].tile_count);
+    return largest;
 }
 
 // Shared by the two calls that work on the per-element code tensors of Sec. 4.2.  `fill` writes the
@@ -199,18 +196,12 @@ int run_dense(excp_ctx *c, int count, bool exporting, Fill fill) {
         w.rec_dev = c->w.rec_dev + g.first;
         w.rec_base = 0;
         if (exporting) {
-            { StageTimer t(c, ST_MISC); launch_decode_parse(w, g.count, false, s); }
             bool moments = false;
             for (u32 q = 0; q < g.count; ++q)
                 moments = moments || c->h_ddesc[g.first + q].cm != nullptr || c->h_ddesc[g.first + q].cv != nullptr;
             {
                 StageTimer t(c, ST_DECODE_PREP);
-                launch_decode_count(w, g.count, g.ntiles, 0, s);
-                launch_decode_scan(w, g.count, 0, s);
-                if (moments) {
-                    launch_decode_count(w, g.count, g.ntiles, 1, s);
-                    launch_decode_scan(w, g.count, 1, s);
-                }
+                launch_decode_prep(w, g.count, g.ntiles, largest_tiles(c->h_ddesc + g.first, g.count), false, moments, s);
             }
             { StageTimer t(c, ST_EXPORT_DENSE); launch_export_dense(w, g.count, g.ntiles, moments, s); }
         } else {
@@ -644,11 +635,17 @@ int excp_decompress_tensors(excp_ctx *c, int count, const excp_blob *blobs) {
         w.tile_begin = c->tile_begin_all + tb_offsets[gi];
         w.rec_dev = c->w.rec_dev + g.first;
         w.rec_base = 0;
-        { StageTimer t(c, ST_MISC); launch_decode_parse(w, g.count, true, s); }
-        bool moments = false;
-        for (u32 q = 0; q < g.count; ++q)
-            moments = moments || blobs[g.first + q].m_out != nullptr || blobs[g.first + q].v_out != nullptr;
-        run_decode_prep_and_main(c, w, g.count, g.ntiles, moments);
+        bool moments = false, w32 = false, w16 = false;
+        for (u32 q = 0; q < g.count; ++q) {
+            const excp_blob &b = blobs[g.first + q];
+            moments = moments || b.m_out != nullptr || b.v_out != nullptr;
+            if (b.flags & 0x30u) w16 = true; else w32 = true;
+        }
+        {
+            StageTimer t(c, ST_DECODE_PREP);
+            launch_decode_prep(w, g.count, g.ntiles, largest_tiles(c->h_ddesc + g.first, g.count), true, moments, s);
+        }
+        run_decode_main(c, w, g.count, g.ntiles, moments, w32, w16);
         { StageTimer t(c, ST_MISC); launch_decode_finish(w, g.count, s); }
     }
     if (count) {
@@ -790,12 +787,9 @@ int excp_reconstruct_chain(excp_ctx *c, int count, const excp_chain *chains) {
         bool moments = false;
         for (u32 q = 0; q < g.count; ++q)
             moments = moments || chains[g.first + q].m_out != nullptr || chains[g.first + q].v_out != nullptr;
-        { StageTimer t(c, ST_MISC); launch_decode_parse(w, g.ndescs, false, s); }
         {
             StageTimer t(c, ST_DECODE_PREP);
-            launch_decode_count(w, g.ndescs, dtiles, 0, s);
-            launch_decode_scan(w, g.ndescs, 0, s);
-            if (moments) { launch_decode_count(w, g.ndescs, dtiles, 1, s); launch_decode_scan(w, g.ndescs, 1, s); }
+            launch_decode_prep(w, g.ndescs, dtiles, largest_tiles(c->h_ddesc + g.first_desc, g.ndescs), false, moments, s);
         }
         bool w16[2] = {false, false};                      // weight storage met in the group (a blob that says otherwise is refused)
         for (u32 q = 0; q < g.count; ++q) w16[(chains[g.first + q].flags & 0x30u) != 0] = true;
@@ -803,8 +797,8 @@ int excp_reconstruct_chain(excp_ctx *c, int count, const excp_chain *chains) {
             if (w16[k]) { StageTimer t(c, ST_DECODE_MAIN); launch_decode_chain(w, g.count, g.ntiles, k == 1, s); }
         if (moments) {      // the last checkpoints' moments
             StageTimer t(c, ST_DECODE_MAIN);
-            launch_decode_main(w, g.ndescs, dtiles, true, s);
-            launch_decode_main16(w, g.ndescs, dtiles, true, s);
+            if (w16[0]) launch_decode_main(w, g.ndescs, dtiles, true, s);
+            if (w16[1]) launch_decode_main16(w, g.ndescs, dtiles, true, s);
         }
         { StageTimer t(c, ST_MISC); launch_chain_finish(w, g.count, s); }
     }
@@ -921,15 +915,9 @@ int excp_decompress_step_static(int hip_device, void *hip_stream, const void *W_
     // written first, the state and every count of the tiles in use are written by the kernels before
     // they are read, and the record is written last.
     launch_decode_single_setup(w, d, s);
-    launch_decode_parse(w, 1, true, s);
-    launch_decode_count(w, 1, ntiles, 0, s);
-    launch_decode_scan(w, 1, 0, s);
-    if (moments) {
-        launch_decode_count(w, 1, ntiles, 1, s);
-        launch_decode_scan(w, 1, 1, s);
-    }
-    launch_decode_main(w, 1, ntiles, moments, s);
-    launch_decode_main16(w, 1, ntiles, moments, s);
+    launch_decode_prep(w, 1, ntiles, ntiles, true, moments, s);
+    if (d.wtype == 0u) launch_decode_main(w, 1, ntiles, moments, s);
+    else launch_decode_main16(w, 1, ntiles, moments, s);
     launch_decode_raw(w, 1, ntiles, moments, s);
     launch_decode_finish(w, 1, s);
     if (hipGetLastError() != hipSuccess) { (void)hipStreamSynchronize(s); return EXCP_E_HIP; }

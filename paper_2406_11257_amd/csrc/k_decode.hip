@@ -40,15 +40,11 @@ __device__ __forceinline__ bool wants_moments(const DDesc &D) {
     return D.m_out != nullptr || D.v_out != nullptr || D.cm != nullptr || D.cv != nullptr;
 }
 
-// Validate the header of every blob and derive the section offsets.
-__global__ void k_decode_parse(Workspace w, u32 ntensors, u32 allow_raw) {
-    const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ntensors) return;
-    const DDesc &D = w.ddesc[t];
-    DState &S = w.dst[t];
+// Validates the header of a blob and derives the section offsets.  Returns the kind of blob, 0 if it is damaged.
+__device__ __forceinline__ u32 parse_header(const DDesc &D, DState &S, bool allow_raw) {
     S.status = 0; S.pop_w = 0; S.pop_o = 0;
     S.n_w = 0; S.n_o = 0; S.nbits = 4; S.blob_bytes = 0; S.flags = 0; S.pad = 0;
-    if (D.blob_bytes < EXCP_HEADER) { S.status = -4; return; }
+    if (D.blob_bytes < EXCP_HEADER) { S.status = -4; return 0u; }
     const u32 *h = (const u32 *)D.blob;
     const u64 *h64 = (const u64 *)D.blob;
     const u32 nbits = h[2];
@@ -56,7 +52,7 @@ __global__ void k_decode_parse(Workspace w, u32 ntensors, u32 allow_raw) {
     const bool raw = (h[3] & 4u) != 0u;                   // written without quantisation: fp32 values, no codebooks
     const bool nw2m = (h[3] & 8u) != 0u;                  // bitmap_o over all elements, not over the kept residuals
     bool ok = h[0] == EXCP_MAGIC && h[1] == EXCP_VERSION && h[3] < 64u && (h[3] & 0x30u) != 0x30u;
-    ok = ok && (raw ? (nbits == EXCP_RAW_BITS && allow_raw != 0u) : (nbits >= 2u && nbits <= 8u));
+    ok = ok && (raw ? (nbits == EXCP_RAW_BITS && allow_raw) : (nbits >= 2u && nbits <= 8u));
     ok = ok && n == D.n && nw <= n && no <= (nw2m ? n : nw);
     ok = ok && (D.wtype == 3u || D.wtype == excp_wtype(h[3]));      // the caller's arrays are what the blob expects
     u64 off = EXCP_HEADER;
@@ -69,9 +65,91 @@ __global__ void k_decode_parse(Workspace w, u32 ntensors, u32 allow_raw) {
         S.off_cv = off; off += excp_pad16(8ull * excp_words(no * nbits));
         ok = (off == total) && (total <= D.blob_bytes);
     }
-    if (!ok) { S.status = -4; return; }
+    if (!ok) { S.status = -4; return 0u; }
     S.n_w = nw; S.n_o = no; S.nbits = nbits; S.blob_bytes = total; S.flags = h[3];
-    atomicOr(w.dec_kinds, blob_kind(nbits, h[3]));
+    return blob_kind(nbits, h[3]);
+}
+__global__ void k_decode_parse(Workspace w, u32 ntensors, u32 allow_raw) {
+    const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= ntensors) return;
+    const u32 kind = parse_header(w.ddesc[t], w.dst[t], allow_raw != 0u);
+    if (kind) atomicOr(w.dec_kinds, kind);
+}
+
+// All that has to be known before the main pass, for groups of tensors of at most PREP_TILES tiles each, in one
+// launch: a workgroup per tensor parses the header, counts, and scans the counts.  Small tensors are bound by the
+// number of launches: parsing, counting and scanning are five (eight with the moments), of 2 to 4 us each and
+// as much again between them.  Four tiles to a wave, so that a tensor is one round of loads.
+constexpr u32 PREP_WAVES = 8, PREP_TILES = 4 * PREP_WAVES;
+
+__global__ __launch_bounds__(PREP_WAVES * 64) void k_decode_prep(Workspace w, u32 allow_raw, u32 moments) {
+    __shared__ DState S;
+    __shared__ u32 s_cnt[PREP_TILES], s_excl[PREP_TILES + 1];
+    const u32 t = blockIdx.x, tid = threadIdx.x, lane = tid & 63u;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const DDesc &D = w.ddesc[t];
+    const u32 ntiles = D.tile_count;
+    if (tid == 0) {
+        (void)parse_header(D, S, allow_raw != 0u);
+        if (t == 0) *w.dec_kinds = 7u;                     // (the main passes look at every tensor)
+    }
+    __syncthreads();
+    const u64 n = D.n;
+    // exclusive scan of s_cnt into s_excl and the table; returns the total (in the first wave)
+    auto scan = [&](u32 *table) {
+        __syncthreads();
+        u32 total = 0;
+        if (wave == 0u) {
+            const u32 c = lane < ntiles ? s_cnt[lane] : 0u, incl = wave_incl_scan_u32(c);
+            if (lane < ntiles) { s_excl[lane] = incl - c; table[D.tile_begin + lane] = incl - c; }
+            total = last_lane_u32(incl);
+            if (lane == 0u) s_excl[ntiles] = total;
+        }
+        return total;
+    };
+    {
+        u64 v[4] = {0ull, 0ull, 0ull, 0ull};
+        if (S.status == 0) {
+            const EXCP_GLOBAL u64 *bm = gptr((const u64 *)(D.blob + S.off_bw));
+#pragma unroll
+            for (u32 k = 0; k < 4; ++k) {
+                const u64 word = (wave * 4u + k) * 64u + lane;
+                if (word < excp_words(n)) {
+                    v[k] = bm[word];
+                    if (n - word * 64u < 64u) v[k] &= (1ull << (n - word * 64u)) - 1ull;       // (bits beyond n are ignored)
+                }
+            }
+        }
+#pragma unroll
+        for (u32 k = 0; k < 4; ++k) {
+            const u32 c = wave_sum_u32((u32)__popcll(v[k]));
+            if (lane == 0u) s_cnt[wave * 4u + k] = c;
+        }
+        const u32 total = scan(w.dec_cnt_w);
+        if (tid == 0) { S.pop_w = total; if (S.status == 0 && total != S.n_w) S.status = -4; }
+    }
+    __syncthreads();
+    if (moments && wants_moments(D)) {
+#pragma unroll
+        for (u32 k = 0; k < 4; ++k) {
+            const u32 tile = wave * 4u + k;
+            u32 c = 0;
+            if (tile < ntiles && S.status == 0) {
+                u64 p0 = s_excl[tile], p1 = s_excl[tile + 1u];
+                if (S.flags & 8u) {                        // one bit per element: the tile's own range
+                    p0 = (u64)tile * EXCP_TILE;
+                    p1 = (n - p0 < (u64)EXCP_TILE) ? n : p0 + EXCP_TILE;
+                }
+                c = popcount_range_lane((const u64 *)(D.blob + S.off_bo), p0, p1, lane);
+            }
+            c = wave_sum_u32(c);
+            if (lane == 0u) s_cnt[tile] = c;
+        }
+        __syncthreads();                                   // (the counts above are read before they are scanned over)
+        const u32 total = scan(w.dec_cnt_o);
+        if (tid == 0) { S.pop_o = total; if (S.status == 0 && total != S.n_o) S.status = -4; }
+    }
+    if (tid == 0) w.dst[t] = S;
 }
 
 // which == 0: per-tile popcount of bitmap_w.  which == 1: per-tile popcount of the bitmap_o bits
@@ -940,10 +1018,19 @@ void launch_decode_single_setup(const Workspace &w, const DDesc &d, hipStream_t 
     hipLaunchKernelGGL(k_decode_single_setup, dim3(1), dim3(64), 0, s, w, d);
 }
 
-void launch_decode_parse(const Workspace &w, u32 ntensors, bool allow_raw, hipStream_t s) {
+// Headers, counts and scans of a group whose largest tensor has `largest` tiles.
+void launch_decode_prep(const Workspace &w, u32 ntensors, u32 ntiles, u32 largest, bool allow_raw, bool moments, hipStream_t s) {
     if (!ntensors) return;
+    if (largest <= PREP_TILES) {
+        hipLaunchKernelGGL(k_decode_prep, dim3(ntensors), dim3(PREP_WAVES * 64), 0, s, w, allow_raw ? 1u : 0u, moments ? 1u : 0u);
+        return;
+    }
     launch_zero_u32(w.dec_kinds, 1, s);
     hipLaunchKernelGGL(k_decode_parse, dim3((ntensors + 255) / 256), dim3(256), 0, s, w, ntensors, allow_raw ? 1u : 0u);
+    for (int which = 0; which < (moments ? 2 : 1); ++which) {
+        launch_decode_count(w, ntensors, ntiles, which, s);
+        launch_decode_scan(w, ntensors, which, s);
+    }
 }
 void launch_decode_from_compress(const Workspace &w, const GroupParams &g, hipStream_t s) {
     if (!g.ntensors) return;
