@@ -174,6 +174,7 @@ struct Workspace {
     u32 *km_begin;            // [segment][257] first position of every bucket
     u64 *km_bsum;             // [segment][EXCP_ABSM_BINS][257] exact signed sum of every bucket, then of all buckets before it
     u32 *km_min, *km_max;     // [segment][256] smallest / largest key of every bucket
+    u32 *km_dom, *km_less;    // [segment][256] repetitions of every bucket's first value, values below it (sixteen-wave form only)
     u32 *km_mag;              // [segment][256] smallest non-zero magnitude (bit pattern) of every bucket
     u64 *km_acc;              // [segment][3][EXCP_ABSM_BINS + 1][K] per-centre exact sum and count, by iteration modulo 3
     double *part_obj;         // [chunk]

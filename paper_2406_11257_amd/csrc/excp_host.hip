@@ -365,6 +365,8 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.km_min, nseg_max * 256);
     ok = ok && dev_alloc(c, &w.km_max, nseg_max * 256);
     ok = ok && dev_alloc(c, &w.km_mag, nseg_max * 256);
+    ok = ok && dev_alloc(c, &w.km_dom, nseg_max * 256);
+    ok = ok && dev_alloc(c, &w.km_less, nseg_max * 256);
     ok = ok && dev_alloc(c, &w.km_acc, acc_words);
     ok = ok && dev_alloc(c, &w.part_obj, chunks_group);
     // per-tile survivor counts of decode; a chain reconstruction keeps those of all its checkpoints

@@ -501,68 +501,91 @@ __global__ __launch_bounds__(SC_THREADS, 1) void k_km_scatter(Workspace w, Group
 }
 
 // ---------------------------------------------------------------- P4: exact totals per bucket
-// One workgroup per four buckets of a stream (per bucket in the sixteen-wave form); its waves share every bucket,
-// so that one very large bucket (tied values) does not leave a single wave working alone.  Values of a bucket
+// A workgroup takes four neighbouring buckets of a stream (or one): a wave each
+// where they are small, and otherwise its waves share every bucket, so that one very large bucket (tied values)
+// does not leave a single wave working alone.  Consecutive workgroups take different streams: the sets of one large
+// tensor would otherwise be the last ones running.  Values of a bucket
 // are neighbours in value, hence in exponent: a window of 24 bit positions placed from the first
 // values met holds practically all of them; inside it a lane adds sixteen values at a time exactly in
 // fp64 and keeps the running total in two integer counters, with no cross-lane traffic; the rest
 // (rare) is filed one by one.
-// (sixteen for the residuals of 16-bit weights, which are heavily tied, and for groups with a tensor so large
+// (sixteen waves for the residuals of 16-bit weights, which are heavily tied, and for groups with a tensor so large
 // that its buckets alone are millions of values; four otherwise, which is faster when the buckets are
 // small and even)
+constexpr u32 BESIDE_MAX = 1024;                           // values per wave up to which a set's buckets go side by side
 template <u32 BS_WAVES, u32 BPW>
-__global__ __launch_bounds__(BS_WAVES * 64) void k_km_bucket_stats(Workspace w, GroupParams g, u32 sel, u32 nseg) {
+__global__ __launch_bounds__(BS_WAVES * 64, BS_WAVES == 16u ? 8 : 5) void k_km_bucket_stats(Workspace w, GroupParams g, u32 sel, u32 nseg) {
     __shared__ u64 bins[BPW][EXCP_ABSM_BINS];
-    __shared__ u32 s_min[BPW], s_max[BPW], s_mag[BPW];
-    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    __shared__ u32 s_min[BPW], s_max[BPW], s_mag[BPW], s_ndom[BPW], s_less[BPW];
+    constexpr bool TIED = BS_WAVES == 16u;
+    const u32 tid = threadIdx.x, lane = tid & 63u;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     // a workgroup walks over sets of BPW buckets (many sets are tiny: one workgroup each would be
     // bound by the rate at which workgroups can be started)
-    for (u64 first = (u64)blockIdx.x * BPW; first < (u64)nseg * NBKT; first += (u64)gridDim.x * BPW) {
-    const u32 sidx = stream_of((u32)(first / NBKT), sel), b0 = (u32)(first % NBKT);
-    if (w.seg[sidx].len == 0) continue;                    // the same for the whole workgroup
+    for (u32 set = blockIdx.x; set < nseg * (NBKT / BPW); set += gridDim.x) {
+    const u32 sidx = stream_of(set % nseg, sel), b0 = set / nseg * BPW;
+    const EXCP_CONSTANT SegState *seg = (const EXCP_CONSTANT SegState *)(uintptr_t)(w.seg + sidx);
+    const EXCP_CONSTANT u32 *begin = (const EXCP_CONSTANT u32 *)(uintptr_t)(w.km_begin + (u64)sidx * (NBKT + 1));
+    if (seg->len == 0) continue;                           // the same for the whole workgroup
     __syncthreads();                                       // the previous set has left the LDS tables
-    if (tid < BPW * EXCP_ABSM_BINS) (&bins[0][0])[tid] = 0;
-    if (tid < BPW) { s_min[tid] = 0xffffffffu; s_max[tid] = 0; s_mag[tid] = 0xffffffffu; }
-    __syncthreads();
-    const u32 *begin = w.km_begin + (u64)sidx * (NBKT + 1);
+    for (u32 i = tid; i < BPW * EXCP_ABSM_BINS; i += BS_WAVES * 64u) (&bins[0][0])[i] = 0;
+    if (tid < BPW) { s_min[tid] = 0xffffffffu; s_max[tid] = 0; s_mag[tid] = 0xffffffffu; s_ndom[tid] = 0; s_less[tid] = 0; }
     const EXCP_GLOBAL float *part = gptr(seg_part(w, sidx));
-    // Small buckets (the four together at most SOLO_MAX values: small tensors, small models): a wave
-    // takes a whole bucket, the four side by side, instead of four rounds of memory round trips.
-    constexpr u32 SOLO_MAX = 4096;
-    const bool solo = BS_WAVES == BPW && begin[b0 + BPW] - begin[b0] <= SOLO_MAX;
-    for (u32 jj = 0; jj < (solo ? 1u : BPW); ++jj) {
-        const u32 j = solo ? wave : jj;
+    // Small buckets: all of them side by side, a wave each (four in the sixteen-wave form), instead of a round of
+    // memory round trips for each.
+    const bool beside = BPW > 1u && begin[b0 + BPW] - begin[b0] <= BESIDE_MAX * BS_WAVES;
+    constexpr u32 FEW = BS_WAVES / BPW;
+    __syncthreads();
+    for (u32 jj = 0; jj < (beside ? 1u : BPW); ++jj) {
+        const u32 j = beside ? wave / FEW : jj, share = beside ? wave % FEW : wave;
         const u32 q0 = begin[b0 + j], q1 = begin[b0 + j + 1];
         // this wave's share, cut at multiples of 256 values from the bucket's start
-        const u32 blocks = (q1 - q0 + 255u) >> 8, per = (blocks + BS_WAVES - 1u) / BS_WAVES;
-        const u32 p0 = solo ? q0 : min(q0 + wave * per * 256u, q1), p1 = solo ? q1 : min(p0 + per * 256u, q1);
+        const u32 blocks = (q1 - q0 + 255u) >> 8, per = beside ? (blocks + FEW - 1u) / FEW : (blocks + BS_WAVES - 1u) / BS_WAVES;
+        const u32 p0 = min(q0 + share * per * 256u, q1), p1 = min(p0 + per * 256u, q1);
         if (p0 >= p1) continue;
         u64 *mybins = bins[j];
-        // window base from the first (up to) 64 values: top 4 binary orders above their largest
-        u32 pm = 0;
-        {
-            const u32 i = p0 + lane;
-            const u32 mb = (i < p1) ? (f2u(part[i]) & 0x7fffffffu) : 0u;
-            const u32 e = mb >> 23;
-            pm = wave_max_u32((e ? e : 1u) - 1u);
-        }
+        // Rounds of 1024 values, sixteen per lane, in four 16-byte loads (the other waves hide their latency).  A
+        // lane's values past the end are the share's first one again, and are not taken.
+        f4u q[4];
+        auto load = [&](u32 p) {
+            if (p + 1024u <= p1) {
+#pragma unroll
+                for (u32 r = 0; r < 4; ++r) q[r] = *(const EXCP_GLOBAL f4u *)(part + p + r * 256u + lane * 4u);
+            } else {
+#pragma unroll
+                for (u32 r = 0; r < 4; ++r) {
+                    const u32 i = p + r * 256u + lane * 4u;
+#pragma unroll
+                    for (u32 e = 0; e < 4; ++e) q[r][e] = part[i + e < p1 ? i + e : p0];
+                }
+            }
+        };
+        load(p0);
+        // Tied data (the sixteen-wave form): a large bucket is mostly one value.  The bucket's first value is taken
+        // for that one; its repetitions are only counted, and count times value joins the sums at the end.  How
+        // many there are, and how many values are smaller, also answers most questions for an order statistic
+        // of the bucket (k_km_init).
+        u32 dom = 0, ndom = 0, less = 0;                   // bit pattern of the repeated value; this lane's counts
+        if (TIED) dom = (u32)__builtin_amdgcn_readfirstlane((int)f2u(part[q0]));
+        const u32 domkey = key_of(u2f(dom));
+        // window base from the first round: top 4 binary orders above its largest value
+        u32 top = 0;
+#pragma unroll
+        for (u32 r = 0; r < 4; ++r)
+#pragma unroll
+            for (u32 e = 0; e < 4; ++e) top = max(top, f2u(q[r][e]) & 0x7fffffffu);
+        const u32 pm = bit_pos(wave_max_u32(top));
         const u32 B = pm + 4u > 23u ? pm + 4u - 23u : 0u;
         u32 thr_lo, span;
         window_range(B, thr_lo, span);
+        const bool apart = (dom & 0x7fffffffu) - thr_lo < span;    // inside the window: summed by its count
         WindowSum S;
         u32 kmin = 0xffffffffu, kmax = 0, mag = 0xffffffffu;       // mag: smallest magnitude less one (zero wraps to the largest)
-        // Tied data (the sixteen-wave form): a large bucket is mostly one value.  The wave takes its
-        // first value as that one and only counts its repetitions; count times value joins the sums
-        // at the end.
-        u32 dom = 0xffffffffu, ndom = 0;                   // bit pattern of the repeated value; this lane's count
-        if (BS_WAVES == 16u) {
-            const u32 head = f2u(part[p0]);
-            if ((head & 0x7fffffffu) - thr_lo < span && (head & 0x7fffffffu)) dom = head;     // inside the window, not zero
-        }
         auto take = [&](float xv) {
             const u32 u = f2u(xv), mb = u & 0x7fffffffu;
-            if (BS_WAVES == 16u && u == dom) { ++ndom; return; }
+            if (TIED && u == dom) { ++ndom; if (apart) return; }
             const u32 k = key_of(xv);
+            if (TIED) less += k < domkey;
             kmin = min(kmin, k); kmax = max(kmax, k);
             mag = min(mag, mb - 1u);
             if (mb - thr_lo < span) {
@@ -570,34 +593,28 @@ __global__ __launch_bounds__(BS_WAVES * 64) void k_km_bucket_stats(Workspace w, 
             } else if (mb) {
                 const u32 e = mb >> 23;
                 const u32 mant = (mb & 0x7fffffu) | (e ? 0x800000u : 0u);
-                const u32 pos = (e ? e : 1u) - 1u;
+                const u32 pos = bit_pos(mb);
                 const u64 d = (u64)mant << (pos & 7u);
                 atomicAdd(&mybins[pos >> 3], (u >> 31) ? (u64)0 - d : d);
             }
         };
-        // four 16-byte loads in flight per lane: the share of a wave in a large bucket is a chain of
-        // round trips otherwise.  Sixteen values per round: one fold of the fp64 partial sum.
         u32 p = p0;
         for (; p + 1024u <= p1; p += 1024u) {
-            f4u q[4];
-#pragma unroll
-            for (u32 r = 0; r < 4; ++r) q[r] = *(const EXCP_GLOBAL f4u *)(part + p + r * 256u + lane * 4u);
 #pragma unroll
             for (u32 r = 0; r < 4; ++r) { take(q[r].x); take(q[r].y); take(q[r].z); take(q[r].w); }
             S.fold(B);
+            if (p + 1024u < p1) load(p + 1024u);
         }
-        for (; p < p1; p += 256u) {                       // (at most four rounds of four values)
-            const u32 i = p + lane * 4u;
-            if (p + 256u <= p1) {
-                const f4u q = *(const EXCP_GLOBAL f4u *)(part + i);
-                take(q.x); take(q.y); take(q.z); take(q.w);
-            } else {
+        if (p < p1) {
 #pragma unroll
-                for (u32 e = 0; e < 4; ++e) if (i + e < p1) take(part[i + e]);
+            for (u32 r = 0; r < 4; ++r) {
+                const u32 i = p + r * 256u + lane * 4u;
+#pragma unroll
+                for (u32 e = 0; e < 4; ++e) if (i + e < p1) take(q[r][e]);
             }
+            S.fold(B);
         }
-        S.fold(B);
-        if (BS_WAVES == 16u && ndom) {
+        if (TIED && ndom && apart) {
             const u32 mb = dom & 0x7fffffffu, e = mb >> 23;
             const u32 mant = (mb & 0x7fffffu) | (e ? 0x800000u : 0u);
             const u64 term = (u64)mant << (((e ? e : 1u) - 1u) - B);                      // below 2^47 units
@@ -609,20 +626,22 @@ __global__ __launch_bounds__(BS_WAVES * 64) void k_km_bucket_stats(Workspace w, 
         }
         const long long tL = (long long)wave_sum_u64((u64)S.lo), tH = (long long)wave_sum_u64((u64)S.hi);
         kmin = wave_min_u32(kmin); kmax = wave_max_u32(kmax); mag = wave_min_u32(mag);
+        if (TIED) { ndom = wave_sum_u32(ndom); less = wave_sum_u32(less); }
         if (lane == 0) {
+            if (TIED) { atomicAdd(&s_ndom[j], ndom); atomicAdd(&s_less[j], less); }
             atomicMin(&s_min[j], kmin); atomicMax(&s_max[j], kmax); atomicMin(&s_mag[j], mag);
             file_i64(mybins, tL, B); file_i64(mybins, tH, B + 32u);
         }
     }
     __syncthreads();
-    if (tid < BPW * EXCP_ABSM_BINS)
-        w.km_bsum[((u64)sidx * EXCP_ABSM_BINS + tid / BPW) * (NBKT + 1) + b0 + tid % BPW] = bins[tid % BPW][tid / BPW];
+    for (u32 i = tid; i < BPW * EXCP_ABSM_BINS; i += BS_WAVES * 64u)
+        w.km_bsum[((u64)sidx * EXCP_ABSM_BINS + i / BPW) * (NBKT + 1) + b0 + i % BPW] = bins[i % BPW][i / BPW];
     if (tid < BPW) {
         const u64 at = (u64)sidx * NBKT + b0 + tid;
         w.km_min[at] = s_min[tid]; w.km_max[at] = s_max[tid];
         w.km_mag[at] = s_mag[tid] + 1u;                    // (0: nothing but zeros, or nothing at all)
+        if (TIED) { w.km_less[at] = s_less[tid]; w.km_dom[at] = s_ndom[tid]; }
     }
-    if (BS_WAVES != 4u) break;                             // the sixteen-wave forms are launched one workgroup per set
     }
 }
 
@@ -701,6 +720,10 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
     u32 diff = kmin ^ kmax;
     float *out = &S.C[1][k];                 // (read by iteration 0, whose predecessor has parity 1)
     if (diff == 0) { if (tid == 0) *out = val_of(kmin); return; }
+    // Tied data: the rank usually falls among the repetitions of the bucket's first value, which have been counted.
+    // (The K ranks of a stream often ask for the same few large buckets: reading those for each of them took most
+    // of this kernel's time, 468 of now 148 us for a 410M-shaped checkpoint in bf16.)
+    if (INIT_THREADS == 1024u && rank - w.km_less[(u64)sidx * NBKT + b] < w.km_dom[(u64)sidx * NBKT + b]) { if (tid == 0) *out = gpart[0]; return; }
     // A bucket far above the average size holds tied values (a continuous distribution fills the
     // buckets evenly).  Such a bucket is mostly ONE value, its smallest or its largest key, with a few
     // strays beside it: one cheap pass counts the two extremes, and if the rank falls among them the
@@ -1467,7 +1490,12 @@ void launch_km_partition(const Workspace &w, const GroupParams &g, int phase, hi
             } else {
                 const u32 sel = g.wide ? STREAMS_MV : STREAMS_ALL, ns = stream_count(g.ntensors, sel);
                 if (g.wide) hipLaunchKernelGGL((k_km_bucket_stats<16, 4>), dim3(g.ntensors * (NBKT / 4)), dim3(1024), 0, s, w, g, (u32)STREAMS_W, g.ntensors);
-                hipLaunchKernelGGL((k_km_bucket_stats<4, 4>), dim3(std::min(ns * (NBKT / 4), excp_grid(w, 32))), dim3(256), 0, s, w, g, sel, ns);
+                // (sets of four buckets, unless that leaves compute units without work: the 192 sets of one 16.8 M-element
+                // tensor took 34 us, its 768 buckets 15)
+                if (ns * (NBKT / 4) < excp_grid(w, 4))
+                    hipLaunchKernelGGL((k_km_bucket_stats<4, 1>), dim3(ns * NBKT), dim3(256), 0, s, w, g, sel, ns);
+                else
+                    hipLaunchKernelGGL((k_km_bucket_stats<4, 4>), dim3(std::min(ns * (NBKT / 4), excp_grid(w, 40))), dim3(256), 0, s, w, g, sel, ns);
             }
             break;
     }
