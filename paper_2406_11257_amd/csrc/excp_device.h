@@ -35,7 +35,8 @@ struct TDesc {
     u64 cand_off;      // start and capacity of this tensor's median-candidate list
     u64 cand_cap;
     u32 cand_lists;    // a tensor's candidate list is cut into this many lists (1 .. 16), each with a counter of its
-    u32 pad0;          // own, so that thousands of workgroups do not queue at one address
+                       // own, so that thousands of workgroups do not queue at one address
+    u32 turn;          // of the group's i-th entry: the tensor whose turn is i-th where the large ones go first
     u32 tile_begin;    // first tile of this tensor in the group's tile list
     u32 tile_count;
 };

@@ -499,13 +499,19 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             d.Wp = (const float *)t.W_prev_recon; d.W = (const float *)t.W_t; d.m = t.m_t; d.v = t.v_t; d.n = t.n;
             d.blob = (unsigned char *)t.blob; d.blob_cap = t.blob_cap; d.W_out = (float *)t.W_recon_out;
             d.elem_off = elem_off; d.tile_begin = tile;
-            d.cand_lists = (u32)std::min<u64>(std::max<u64>(t.n / c->cand_list_elems, 1), 16); d.pad0 = 0;
+            d.cand_lists = (u32)std::min<u64>(std::max<u64>(t.n / c->cand_list_elems, 1), 16);
             d.cand_off = cand_off; d.cand_cap = (t.n / 12 + 4096 + d.cand_lists - 1) / d.cand_lists * d.cand_lists;
             cand_off += d.cand_cap;
             d.tile_count = (u32)((t.n + EXCP_TILE - 1) / EXCP_TILE);
             c->h_tile_begin[tb_off + q] = tile;
             elem_off += t.n; tile += d.tile_count;
         }
+        // the tensors by size, powers of two apart, the largest first
+        u32 at[65] = {0};
+        auto size_class = [&](u32 q) { const u64 n = tensors[g.first + q].n; return n ? (u32)__builtin_clzll(n) : 64u; };
+        for (u32 q = 0; q < g.count; ++q) ++at[size_class(q)];
+        for (u32 k = 0, sum = 0; k < 65; ++k) { const u32 here = at[k]; at[k] = sum; sum += here; }
+        for (u32 q = 0; q < g.count; ++q) c->h_desc[g.first + at[size_class(q)]++].turn = q;
         c->h_tile_begin[tb_off + g.count] = tile;
         tb_off += g.count + 1;
     }

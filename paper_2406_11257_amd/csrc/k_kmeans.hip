@@ -47,6 +47,13 @@ enum { STREAMS_ALL = 0, STREAMS_W = 1, STREAMS_MV = 2 };
 __device__ __forceinline__ u32 stream_of(u32 idx, u32 sel) {
     return sel == STREAMS_ALL ? idx : (sel == STREAMS_W ? 3u * idx : 3u * (idx >> 1) + 1u + (idx & 1u));
 }
+// The stream whose turn is `turn` where those of large tensors go first: what is long and starts last keeps a few
+// compute units working while the others are done.  (410M-shaped checkpoint: bucket totals 469 -> 327 us, part of which
+// is owed to the shorter rounds of small buckets, initial centres 188 -> 121, Lloyd iterations of the streams that one
+// workgroup takes 387 -> 244.)
+__device__ __forceinline__ u32 stream_in_turn(const Workspace &w, u32 turn) {
+    return 3u * ((const EXCP_CONSTANT TDesc *)(uintptr_t)(w.desc + turn / 3u))->turn + turn % 3u;
+}
 static u32 stream_count(u32 ntensors, u32 sel) { return ntensors * (sel == STREAMS_ALL ? 3u : (sel == STREAMS_W ? 1u : 2u)); }
 
 // Four consecutive floats at an address that is only known to be 4-byte aligned.
@@ -503,8 +510,8 @@ __global__ __launch_bounds__(SC_THREADS, 1) void k_km_scatter(Workspace w, Group
 // ---------------------------------------------------------------- P4: exact totals per bucket
 // A workgroup takes four neighbouring buckets of a stream (or one): a wave each
 // where they are small, and otherwise its waves share every bucket, so that one very large bucket (tied values)
-// does not leave a single wave working alone.  Consecutive workgroups take different streams: the sets of one large
-// tensor would otherwise be the last ones running.  Values of a bucket
+// does not leave a single wave working alone.  The large tensors' sets come first (in a 410M-shaped checkpoint, whose
+// last tensor is one of the two large ones, compute units stood idle for a third of the time).  Values of a bucket
 // are neighbours in value, hence in exponent: a window of 24 bit positions placed from the first
 // values met holds practically all of them; inside it a lane adds sixteen values at a time exactly in
 // fp64 and keeps the running total in two integer counters, with no cross-lane traffic; the rest
@@ -523,7 +530,8 @@ __global__ __launch_bounds__(BS_WAVES * 64, BS_WAVES == 16u ? 8 : 5) void k_km_b
     // a workgroup walks over sets of BPW buckets (many sets are tiny: one workgroup each would be
     // bound by the rate at which workgroups can be started)
     for (u32 set = blockIdx.x; set < nseg * (NBKT / BPW); set += gridDim.x) {
-    const u32 sidx = stream_of(set % nseg, sel), b0 = set / nseg * BPW;
+    const u32 sets = NBKT / BPW, b0 = set % sets * BPW;
+    const u32 sidx = stream_in_turn(w, stream_of(set / sets, sel));
     const EXCP_CONSTANT SegState *seg = (const EXCP_CONSTANT SegState *)(uintptr_t)(w.seg + sidx);
     const EXCP_CONSTANT u32 *begin = (const EXCP_CONSTANT u32 *)(uintptr_t)(w.km_begin + (u64)sidx * (NBKT + 1));
     if (seg->len == 0) continue;                           // the same for the whole workgroup
@@ -554,6 +562,7 @@ __global__ __launch_bounds__(BS_WAVES * 64, BS_WAVES == 16u ? 8 : 5) void k_km_b
             } else {
 #pragma unroll
                 for (u32 r = 0; r < 4; ++r) {
+                    if (p + r * 256u >= p1) { q[r] = q[0]; continue; }       // (the same in the whole wave)
                     const u32 i = p + r * 256u + lane * 4u;
 #pragma unroll
                     for (u32 e = 0; e < 4; ++e) q[r][e] = part[i + e < p1 ? i + e : p0];
@@ -608,6 +617,7 @@ __global__ __launch_bounds__(BS_WAVES * 64, BS_WAVES == 16u ? 8 : 5) void k_km_b
         if (p < p1) {
 #pragma unroll
             for (u32 r = 0; r < 4; ++r) {
+                if (p + r * 256u >= p1) break;             // (most buckets of a small tensor hold a handful of values)
                 const u32 i = p + r * 256u + lane * 4u;
 #pragma unroll
                 for (u32 e = 0; e < 4; ++e) if (i + e < p1) take(q[r][e]);
@@ -653,7 +663,7 @@ __global__ __launch_bounds__(BS_WAVES * 64, BS_WAVES == 16u ? 8 : 5) void k_km_b
 // workgroup.  Values that fit the workgroup's registers are read once.
 // (1024 threads for the residuals of 16-bit weights -- a bucket of tied values can be most of a stream -- and for
 // groups with a tensor of 2^28 elements; 256 otherwise: with 1024 for everybody the 14 000 workgroups of a 410M-shaped
-// checkpoint take 347 us instead of 167, and 22 instead of 33 for a 16.8 M-element tensor)
+// checkpoint took 347 us instead of 167, and 22 instead of 33 for a 16.8 M-element tensor)
 //
 // The prefix sums turn the total of any run of buckets into one difference; the workgroup of centre k also
 // clears its share of the accumulators of the Lloyd iterations.
@@ -662,7 +672,7 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
     __shared__ u32 hist[2048];
     __shared__ u32 s_wave[INIT_THREADS / 64], s_pick[2];
     const u32 K = (u32)g.K;
-    const u32 sidx = stream_of(blockIdx.x / (K + 1u), sel), k = blockIdx.x % (K + 1u), tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const u32 sidx = stream_in_turn(w, stream_of(blockIdx.x / (K + 1u), sel)), k = blockIdx.x % (K + 1u), tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     SegState &S = w.seg[sidx];
     const u64 len = S.len;
     if (len == 0) return;
@@ -1163,7 +1173,7 @@ template <u32 KMAX>
 __global__ __launch_bounds__(LLOYD_THREADS, KMAX > 63u ? 1 : 2) void k_km_lloyd(Workspace w, GroupParams g) {
     __shared__ LloydShared L;
     __shared__ u64 acc[(EXCP_ABSM_BINS + 1u) * KMAX];
-    const u32 sidx = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, K = (u32)g.K, iters = (u32)g.iters;
+    const u32 sidx = stream_in_turn(w, blockIdx.x), tid = threadIdx.x, wave = tid >> 6, K = (u32)g.K, iters = (u32)g.iters;
     SegState &S = w.seg[sidx];
     if (S.len == 0 || !excp_lloyd_alone(w.desc[sidx / 3u].n, K)) return;
     u32 kp2 = 1; while (kp2 < K) kp2 <<= 1;
