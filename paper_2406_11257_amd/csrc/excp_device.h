@@ -197,6 +197,13 @@ struct Workspace {
 // measured on its own).
 static inline u32 excp_grid(const Workspace &w, u32 per_cu) { return (u32)w.cus * per_cu; }
 
+// Lists that a tensor's median candidates are filed in, and the places they have together: a twelfth of the tensor and
+// 4096, rounded down to a multiple of the lists, so that the tensors of a group never have more than excp_cand_words,
+// which the workspace sets aside.
+static inline u32 excp_cand_lists(u64 n, u64 list_elems) { return n / list_elems < 1 ? 1u : (n / list_elems > 16 ? 16u : (u32)(n / list_elems)); }
+static inline u64 excp_cand_cap(u64 n, u32 lists) { return (n / 12 + 4096) / lists * lists; }
+static inline u64 excp_cand_words(u64 group_elems, u32 group_tensors) { return group_elems / 12 + 4096ull * group_tensors; }
+
 // Whether one workgroup takes a tensor's streams through all Lloyd iterations.
 static __host__ __device__ inline bool excp_lloyd_alone(u64 n, u32 K) { return n * (K - 1u) <= (1ull << 27); }
 

@@ -345,7 +345,7 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.sample, (u64)kMaxGroupTensors * 8192);
     ok = ok && dev_alloc(c, &w.sample_mmax, (u64)kMaxGroupTensors * EXCP_SAMPLE_PARTS);
     ok = ok && dev_alloc(c, &w.sel_ticket, kMaxGroupTensors);
-    ok = ok && dev_alloc(c, &w.cand, G / 12 + 4096ull * kMaxGroupTensors + 16);
+    ok = ok && dev_alloc(c, &w.cand, excp_cand_words(G, kMaxGroupTensors));
     ok = ok && dev_alloc(c, &w.tile_status, 2 * max_tiles);      // one word per 2048-element sub-tile
     ok = ok && dev_alloc(c, &w.mask_prefix, 2 * max_tiles);
     ok = ok && dev_alloc(c, &w.mask_part, (u64)kMaxGroupTensors * 16);
@@ -499,8 +499,8 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             d.Wp = (const float *)t.W_prev_recon; d.W = (const float *)t.W_t; d.m = t.m_t; d.v = t.v_t; d.n = t.n;
             d.blob = (unsigned char *)t.blob; d.blob_cap = t.blob_cap; d.W_out = (float *)t.W_recon_out;
             d.elem_off = elem_off; d.tile_begin = tile;
-            d.cand_lists = (u32)std::min<u64>(std::max<u64>(t.n / c->cand_list_elems, 1), 16);
-            d.cand_off = cand_off; d.cand_cap = (t.n / 12 + 4096 + d.cand_lists - 1) / d.cand_lists * d.cand_lists;
+            d.cand_lists = excp_cand_lists(t.n, c->cand_list_elems);
+            d.cand_off = cand_off; d.cand_cap = excp_cand_cap(t.n, d.cand_lists);
             cand_off += d.cand_cap;
             d.tile_count = (u32)((t.n + EXCP_TILE - 1) / EXCP_TILE);
             c->h_tile_begin[tb_off + q] = tile;

@@ -1,0 +1,29 @@
+// What the host hands out of a context's workspace, against what it allocates.  Compiled and run by
+// tests/test_host_sizes.py with the rules of excp_device.h; needs no GPU.
+#include <stdio.h>
+
+#include "../paper_2406_11257_amd/csrc/excp_device.h"
+
+static int fails = 0;
+#define CHECK(c, ...) do { if (!(c)) { printf("FAIL line %d: %s: ", __LINE__, #c); printf(__VA_ARGS__); printf("\n"); ++fails; } } while (0)
+
+int main() {
+    // Median candidates: groups as full as they get, in a context of exactly their size, at the list length the library
+    // begins with and at ones a caller may set.
+    for (u64 per : {1ull << 20, 1ull << 26, 65536ull, 1000ull, 1ull})
+        for (u64 n0 : {1ull, 4096ull, 100000ull, 1048572ull, 2097152ull, 2097156ull, 4194304ull, 8388608ull})
+            for (u64 step : {0ull, 1ull, 11ull}) {
+                u64 elems = 0, used = 0;
+                for (u32 q = 0; q < 1024; ++q) {
+                    const u64 n = n0 + step * (q % 12);
+                    const u32 lists = excp_cand_lists(n, per);
+                    const u64 cap = excp_cand_cap(n, lists);
+                    CHECK(lists >= 1 && lists <= 16 && cap % lists == 0 && cap / lists > 0, "%u lists of %llu", lists, cap);
+                    elems += n; used += cap;
+                }
+                CHECK(used <= excp_cand_words(elems, 1024), "%llu of %llu (n %llu, %llu to a list)", used, excp_cand_words(elems, 1024), n0, per);
+            }
+    if (fails) return 1;
+    printf("ok\n");
+    return 0;
+}
