@@ -243,11 +243,12 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_stats_stream(Workspace w, Grou
     // Room for `cnt` candidates: one lane asks.  A tensor's list is cut into L lists with a counter each, so that
     // the workgroups do not queue at one address; one that finds its list full moves on to the next, so the lists
     // fail only when all of them are full.  Returns the place in the group's candidate array, 0xffffffff if none.
-    auto reserve = [&](u32 cnt) -> u32 {
+    // `turn`: what the list to begin with is chosen by.
+    auto reserve = [&](u32 cnt, u32 turn) -> u32 {
         const TDesc &D = w.desc[t];
         const u32 L = D.cand_lists, cap = (u32)(D.cand_cap / L);
         u32 *ctr = w.cand_ctr + (u64)t * 512u;
-        u32 j = (L == 1u) ? 0u : (b * 4u + wave) % L;
+        u32 j = excp_cand_first(turn, L);
         for (u32 attempt = 0; attempt < L; ++attempt, j = (j + 1u == L ? 0u : j + 1u)) {
             const u32 at = atomicAdd(&ctr[j * 32u], cnt);
             if ((u64)at + cnt <= cap) {
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_stats_stream(Workspace w, Grou
     };
     auto flush_wave = [&]() {      // a wave's staging area is full: its candidates go to a list
         u32 at = 0;
-        if (lane == 0) at = reserve(wcount);
+        if (lane == 0) at = reserve(wcount, b + wave);
         at = __shfl(at, 0, WAVE);
         if (at != 0xffffffffu) {
             EXCP_GLOBAL u32 *dst = gptr(w.cand) + w.desc[t].cand_off + at;
@@ -294,7 +295,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_stats_stream(Workspace w, Grou
             if (c) { atomicAdd(&w.st[t].absm[tid], c); bins[tid] = 0; }
         }
         if (tid == 0) {
-            s_place = total ? reserve(total) : 0xffffffffu;   // one reservation for the whole workgroup
+            s_place = total ? reserve(total, b) : 0xffffffffu;   // one reservation for the whole workgroup
             StatPart P;
             P.L = s_L; P.H = s_H; P.clt = s_lt; P.nf = s_nf; P.cc = s_cc; P.pad = 0;
 #pragma unroll

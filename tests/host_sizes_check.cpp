@@ -1,4 +1,4 @@
-// What the host hands out of a context's workspace, against what it allocates.  Compiled and run by
+// What is handed out of a context's workspace, against what is allocated, and how evenly.  Compiled and run by
 // tests/test_host_sizes.py with the rules of excp_device.h; needs no GPU.
 #include <stdio.h>
 
@@ -23,6 +23,13 @@ int main() {
                 }
                 CHECK(used <= excp_cand_words(elems, 1024), "%llu of %llu (n %llu, %llu to a list)", used, excp_cand_words(elems, 1024), n0, per);
             }
+    // The lists that consecutive workgroups try first: every list by as many of them.
+    for (u32 lists = 1; lists <= 16; ++lists) {
+        u32 first[16] = {0}, least = ~0u, most = 0;
+        for (u32 b = 100; b < 100 + 64 * lists; ++b) ++first[excp_cand_first(b, lists)];
+        for (u32 j = 0; j < lists; ++j) { least = first[j] < least ? first[j] : least; most = first[j] > most ? first[j] : most; }
+        CHECK(least == 64 && most == 64, "%u lists: %u to %u", lists, least, most);
+    }
     if (fails) return 1;
     printf("ok\n");
     return 0;
