@@ -1,5 +1,5 @@
 """Chains of checkpoints (Alg. 3) where the one-pass kernel divides its work: quarters of 1024 elements, tiles of 4096,
-more tiles than are counted at once, every element kept (more code words than a wave loads at once) and few, and codebooks
+tensors of several tiles, every element kept (more code words than a wave loads at once) and few, and codebooks
 larger than a wave."""
 import numpy as np
 import pytest

@@ -1,5 +1,6 @@
 """Restoring groups of small tensors, whose headers, counts and scans are one launch, and groups just past that size (32
-tiles of 4096 elements), against the oracle: same values, same refusal of a blob whose bitmap and header disagree."""
+tiles of 4096 elements), against the oracle: same values, same refusal of a blob whose bitmap and header disagree.  And
+groups of so many tiles that a wave counts several, across the borders of tensors."""
 import numpy as np
 import pytest
 import torch
@@ -49,3 +50,37 @@ def test_small_groups_and_the_first_larger_one(largest, flags):
             for got, want in zip(out, O.decompress_step(Wp, blob)):
                 assert got.cpu().numpy().tobytes() == want.tobytes()
     ctx.close()
+
+
+def test_waves_that_count_several_tiles_across_tensors():
+    # 256 compute units count 8192 tiles at once.  About twice and three times as many tiles, in tensors of 1 to 199, the
+    # borders anywhere in a wave's range; then fewer than there are waves.
+    for sizes in ([4096 * (1 + (37 * i) % 199) - (i % 3) * 17 for i in range(170)], [4096 * (1 + (53 * i) % 97) - (i % 5) for i in range(500)],
+                  [33 * 4096 + 1, 70_000, 5, 4096 * 9]):
+        ctx = X.Context(max(sizes), sum(sizes))
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(len(sizes))
+        comp, dec, outs = [], [], []
+        for n in sizes:
+            Wp = torch.empty(n, device="cuda").normal_(0, 0.02, generator=gen)
+            W = Wp + torch.empty(n, device="cuda").normal_(0, 1e-4, generator=gen)
+            m = torch.empty(n, device="cuda").normal_(0, 5e-5, generator=gen)
+            v = m * m * torch.empty(n, device="cuda").normal_(generator=gen).exp() + 1e-16
+            comp.append((Wp, W, m, v, torch.zeros(X.excp_blob_bound(n, 4), dtype=torch.uint8, device="cuda"), torch.zeros_like(Wp)))
+        print(len(sizes), sum((n + 4095) // 4096 for n in sizes), flush=True)
+        ctx.excp_compress_tensors(comp, 5e-5, 2.0, 4, 1, 0)
+        rc, stats = ctx.excp_collect(check=False)
+        assert rc == 0
+        for moments in (True, False):
+            outs = [[torch.full((n,), 3.0, device="cuda") if k == 0 or moments else None for k in range(3)] for n in sizes]
+            ctx.excp_decompress_tensors([(c[0], c[4], int(st.blob_bytes), n, *o) for c, st, n, o in zip(comp, stats, sizes, outs)])
+            rc, _ = ctx.excp_collect(check=False)
+            assert rc == 0
+            # every tensor's weights as the compress call left them (its counts come from the mask pass), and some tensors
+            # in full against the oracle
+            assert all(torch.equal(o[0], c[5]) for c, o in zip(comp, outs))
+            for i in range(0, len(sizes), 19) if moments else ():
+                ref = O.decompress_step(comp[i][0].cpu().numpy(), comp[i][4][:stats[i].blob_bytes].cpu().numpy().tobytes())
+                for got, want in zip(outs[i], ref):
+                    assert got.cpu().numpy().tobytes() == want.tobytes()
+        ctx.close()
