@@ -91,7 +91,7 @@ extern "C" {
                                   is being enqueued, the call waits for what it had enqueued, and the context
                                   refuses further work with this code: destroy it */
 #define EXCP_E_STATE      -6   /* call order violated (batch pending / nothing to collect) */
-#define EXCP_E_INTERNAL   -7   /* an internal work list overflowed (should not happen) */
+#define EXCP_E_INTERNAL   -7   /* not returned: no internal work list is left that could overflow */
 
 /* flags of the compress calls (stored in the blob header, which is where the readers take them from;
  * only the storage of the weight arrays is stated again by whoever reads a blob, see excp_blob) */

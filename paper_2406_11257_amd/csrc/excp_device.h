@@ -179,15 +179,13 @@ struct Workspace {
     u32 *km_mag;              // [segment][256] smallest non-zero magnitude (bit pattern) of every bucket
     u64 *km_acc;              // [segment][3][EXCP_ABSM_BINS + 1][K] per-centre exact sum and count, by iteration modulo 3
     double *part_obj;         // [chunk]
-    u32 max_chunks;
     // decode
     DDesc *ddesc; DState *dst;
     CDesc *cdesc; u32 *chain_tile_begin;   // chain reconstruction: tensors and their tile table
     u32 *dec_cnt_w, *dec_cnt_o;   // per tile counts -> exclusive bases
     u64 *dec_part;                // [descriptor][16] tile-count totals of each sixteenth of a tensor's tiles
     u32 *dec_kinds;               // [1] kinds of blob in the group being decoded: 1 fp32 weights, 2 16-bit weights, 4 unquantised
-    // flags
-    int *err_flag;
+    // results
     HostRec *rec_dev;
     u32 rec_base;             // index of this group's first tensor in rec_dev
     int cus;                  // compute units of the device

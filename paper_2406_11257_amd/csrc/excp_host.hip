@@ -48,8 +48,6 @@ struct excp_ctx {
     CDesc *cdesc_all = nullptr; CDesc *h_cdesc = nullptr;
     u32 *tile_begin_all = nullptr;
     TDesc *h_desc = nullptr; DDesc *h_ddesc = nullptr; u32 *h_tile_begin = nullptr; HostRec *h_rec = nullptr;
-    int *h_err = nullptr;
-    u64 status_words = 0;
     u64 ws_bytes = 0;
     std::vector<void *> allocs;
     // pending batch
@@ -214,7 +212,6 @@ int run_dense(excp_ctx *c, int count, bool exporting, Fill fill) {
         if (hipMemcpyAsync(c->h_rec, c->w.rec_dev, sizeof(HostRec) * count, hipMemcpyDeviceToHost, s) != hipSuccess)
             return enqueue_failed(c);
     }
-    if (hipMemcpyAsync(c->h_err, c->w.err_flag, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess) return enqueue_failed(c);
     if (hipGetLastError() != hipSuccess) return enqueue_failed(c);
     c->pending = 2;
     c->pending_count = count;
@@ -327,7 +324,6 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     const u64 G = max_group_elems;
     const u64 max_tiles = G / EXCP_TILE + kMaxGroupTensors + 1;
     const u64 chunks_group = 3 * (G / EXCP_CHUNK) + 3 * kMaxGroupTensors + 3;
-    c->status_words = max_tiles;
     c->max_tiles = max_tiles;
     bool ok = true;
     ok = ok && dev_alloc(c, &c->desc_all, kMaxBatchTensors);
@@ -374,16 +370,13 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.dec_cnt_o, max_tiles * EXCP_MAX_CHAIN);
     ok = ok && dev_alloc(c, &w.dec_kinds, 4);
     ok = ok && dev_alloc(c, &w.dec_part, (u64)kMaxGroupTensors * 16);
-    ok = ok && dev_alloc(c, &w.err_flag, 4);
     ok = ok && dev_alloc(c, &w.rec_dev, kMaxBatchTensors);
-    w.max_chunks = (u32)(chunks_group > 0xffffffffull ? 0xffffffffull : chunks_group);
     if (ok) {
         ok = hipHostMalloc((void **)&c->h_desc, sizeof(TDesc) * kMaxBatchTensors) == hipSuccess &&
              hipHostMalloc((void **)&c->h_ddesc, sizeof(DDesc) * kMaxBatchTensors) == hipSuccess &&
              hipHostMalloc((void **)&c->h_cdesc, sizeof(CDesc) * kMaxBatchTensors) == hipSuccess &&
              hipHostMalloc((void **)&c->h_tile_begin, sizeof(u32) * (kMaxBatchTensors * 2 + 16)) == hipSuccess &&
-             hipHostMalloc((void **)&c->h_rec, sizeof(HostRec) * kMaxBatchTensors) == hipSuccess &&
-             hipHostMalloc((void **)&c->h_err, 16) == hipSuccess;
+             hipHostMalloc((void **)&c->h_rec, sizeof(HostRec) * kMaxBatchTensors) == hipSuccess;
     }
     if (ok) {
         hipDeviceProp_t prop;
@@ -394,7 +387,6 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     if (ok) {
         launch_zero_u32(w.med_hist, (u64)kMaxGroupTensors * 2048, c->stream);
         launch_zero_u32(w.sel_ticket, kMaxGroupTensors, c->stream);
-        launch_zero_u32((u32 *)w.err_flag, 4, c->stream);
         ok = hipStreamSynchronize(c->stream) == hipSuccess;
     }
     if (!ok) { excp_destroy(c); return EXCP_E_HIP; }
@@ -412,7 +404,6 @@ void excp_destroy(excp_ctx *c) {
     if (c->h_cdesc) (void)hipHostFree(c->h_cdesc);
     if (c->h_tile_begin) (void)hipHostFree(c->h_tile_begin);
     if (c->h_rec) (void)hipHostFree(c->h_rec);
-    if (c->h_err) (void)hipHostFree(c->h_err);
     for (auto &s : c->spans) { (void)hipEventDestroy(s.a); (void)hipEventDestroy(s.b); }
     for (auto e : c->free_events) (void)hipEventDestroy(e);
     delete c;
@@ -588,7 +579,6 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         if (hipMemcpyAsync(c->h_rec, c->w.rec_dev, sizeof(HostRec) * count, hipMemcpyDeviceToHost, s) != hipSuccess)
             return enqueue_failed(c);
     }
-    if (hipMemcpyAsync(c->h_err, c->w.err_flag, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess) return enqueue_failed(c);
     if (hipGetLastError() != hipSuccess) return enqueue_failed(c);
     c->pending = 1;
     c->pending_count = count;
@@ -660,7 +650,6 @@ int excp_decompress_tensors(excp_ctx *c, int count, const excp_blob *blobs) {
         if (hipMemcpyAsync(c->h_rec, c->w.rec_dev, sizeof(HostRec) * count, hipMemcpyDeviceToHost, s) != hipSuccess)
             return enqueue_failed(c);
     }
-    if (hipMemcpyAsync(c->h_err, c->w.err_flag, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess) return enqueue_failed(c);
     if (hipGetLastError() != hipSuccess) return enqueue_failed(c);
     c->pending = 2;
     c->pending_count = count;
@@ -814,7 +803,6 @@ int excp_reconstruct_chain(excp_ctx *c, int count, const excp_chain *chains) {
         if (hipMemcpyAsync(c->h_rec, c->w.rec_dev, sizeof(HostRec) * count, hipMemcpyDeviceToHost, s) != hipSuccess)
             return enqueue_failed(c);
     }
-    if (hipMemcpyAsync(c->h_err, c->w.err_flag, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess) return enqueue_failed(c);
     if (hipGetLastError() != hipSuccess) return enqueue_failed(c);
     c->pending = 2;
     c->pending_count = count;
@@ -840,11 +828,6 @@ int excp_collect(excp_ctx *c, excp_stats *stats) {
     c->spans.clear();
     if (e != hipSuccess) return EXCP_E_HIP;
     int first = EXCP_OK;
-    if (*c->h_err) {
-        first = EXCP_E_INTERNAL;
-        launch_zero_u32((u32 *)c->w.err_flag, 4, c->stream);
-        (void)hipStreamSynchronize(c->stream);
-    }
     for (int i = 0; i < c->pending_count; ++i) {
         const HostRec &r = c->h_rec[i];
         if (stats) {

@@ -13,7 +13,6 @@ __device__ __forceinline__ u32 lane_id() { return threadIdx.x & 63u; }
 __device__ __forceinline__ u32 lanes_below(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi((u32)(m >> 32), __builtin_amdgcn_mbcnt_lo((u32)m, 0u));
 }
-__device__ __forceinline__ u64 lanemask_lt() { return (1ull << lane_id()) - 1ull; }
 
 __device__ __forceinline__ u64 shfl_xor_u64(u64 v, int m) {
     u32 lo = (u32)v, hi = (u32)(v >> 32);
@@ -177,9 +176,6 @@ __device__ __forceinline__ u32 cell_of(float x, const u32 *map) {
     const u32 amin = neg ? map[0] : map[2], sh = neg ? map[1] : map[3];
     const u32 c = min((max(a, amin) - amin) >> sh, HALF_CELLS - 1u);
     return neg ? (c ^ (HALF_CELLS - 1u)) : (c | HALF_CELLS);
-}
-__device__ __forceinline__ u32 bucket_of(float x, const u32 *map) {
-    return ((const unsigned char *)(map + 4))[cell_of(x, map)];
 }
 
 // Order-preserving map of fp32 bit patterns to unsigned keys (and back).

@@ -1465,8 +1465,6 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_finalize(Workspace w, GroupPar
         books[i] = (e == 0 || S.len == 0) ? 0.f : S.C[g.iters & 1][e - 1];
     }
     if (tid == 0) {
-        int status = T.status;
-        if (*w.err_flag) status = -7;
         T.obj[0] = s_obj[0]; T.obj[1] = s_obj[1]; T.obj[2] = s_obj[2];
         u32 *h = (u32 *)D.blob;
         u64 *h64 = (u64 *)D.blob;
@@ -1481,7 +1479,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_finalize(Workspace w, GroupPar
         R.n = D.n; R.n_w = T.n_w; R.n_o = T.n_o; R.blob_bytes = T.blob_bytes; R.nonfinite = T.nonfinite;
         R.abs_sum = T.abs_sum; R.obj[0] = s_obj[0]; R.obj[1] = s_obj[1]; R.obj[2] = s_obj[2];
         R.med = u2f(T.med_bits); R.mean32 = T.mean32; R.t_w = T.t_w; R.r_o = T.r_o;
-        R.status = status; R.pad = 0;
+        R.status = T.status; R.pad = 0;
     }
 }
 
