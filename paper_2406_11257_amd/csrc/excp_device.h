@@ -39,7 +39,10 @@ struct TDesc {
     u32 turn;          // of the group's i-th entry: the tensor whose turn is i-th where the large ones go first
     u32 tile_begin;    // first tile of this tensor in the group's tile list
     u32 tile_count;
+    u32 acc_slot;      // place of its streams' accumulators where many workgroups take a Lloyd iteration; EXCP_NO_SLOT:
+    u32 pad;           // its streams are never taken that way
 };
+#define EXCP_NO_SLOT 0xffffffffu
 
 // What one workgroup of the statistics pass found out about a tensor: units of the exact sum of |m| (low and
 // high 32-bit halves added up), keys below the median's bracket, non-finite values, keys equal to a one-value
@@ -66,7 +69,8 @@ struct TState {
     // tied data (16-bit weights): values inside the median bracket that the sample shows to be heavily
     // repeated are counted, not listed among the candidates
     u32 natoms, atom_key[4], atom_cnt[4];
-    u32 pad2[2];
+    u32 lloyd_shared;           // many workgroups take each of the tensor's streams through a Lloyd iteration
+    u32 pad2;
     StatPart part;              // of a tensor whose tiles all belong to one workgroup of the statistics pass
 };
 
@@ -75,6 +79,8 @@ struct SegState {
     u64 len;
     u32 chunk_begin;            // first chunk of this stream in the group's chunk list
     u32 row_begin;              // first row of this stream in the table of bucket counts (a row per EXCP_SUPER_CHUNKS chunks)
+    u32 work;                   // what a Lloyd iteration is expected to cost, in values of cut buckets
+    u32 pad;
     u32 bin_lo, bin_hi;         // the bins of km_bsum that are not all zero lie in [bin_lo, bin_hi]
     u32 acc_lo, acc_hi;         // sums of any of the stream's values have no other bins than [acc_lo, acc_hi]
     // centres (K used) and cut keys (cut[k], 1 <= k < K: smallest key whose nearest centre has index >= k) by the
@@ -134,10 +140,13 @@ struct GroupParams {
     int nbits, K, iters;
     u32 flags;
     u32 ntensors, ntiles;
-    u32 unit_chunks;            // chunks of a stream that make up one work unit of a Lloyd iteration
     u32 wide;                   // per-bucket kernels with sixteen waves: 1 = for the residual streams (16-bit weights: tied
                                 // data), 2 = for all, one bucket per workgroup (a very large tensor in the group)
-    u64 max_units;              // work units the group's streams can have at most (0: every stream is small enough for one workgroup)
+    u32 alone_work;             // SegState::work of a tensor's streams up to which one workgroup takes each of them through its
+                                // Lloyd iterations
+    u32 together;               // all of the group's tensors go the same way
+    u32 slots;                  // tensors with an acc_slot
+    u32 pad;
 };
 
 #define EXCP_RAW_BITS    32u       // "code" width of a blob written without quantisation: fp32 values, no codebooks
@@ -168,7 +177,8 @@ struct Workspace {
     // survivor passes
     u32 *chunk_total;         // [1]
     u32 *seg_chunk_begin;     // [segments + 1] first chunk of every survivor stream
-    u32 *seg_unit_begin;      // [segments + 1] first work unit of every survivor stream in a Lloyd iteration
+    u32 *lloyd_shared;        // [1] TState::lloyd_shared of some tensor of the group
+    u32 *seg_unit_begin;      // [segments + 1] first work unit of every survivor stream in a Lloyd iteration that many workgroups take
     float *pw, *pm, *pv;      // survivors partitioned into value-ordered buckets (same offsets as xw/xm/xv)
     u32 *km_split;            // [segment][EXCP_KM_MAP_WORDS] value -> bucket map: 4 parameters, then 4096 bucket bytes
     u32 *km_cnt;              // [row][256] bucket counts, then positions: a row per EXCP_SUPER_CHUNKS chunks of a stream
@@ -177,7 +187,7 @@ struct Workspace {
     u32 *km_min, *km_max;     // [segment][256] smallest / largest key of every bucket
     u32 *km_dom, *km_less;    // [segment][256] repetitions of every bucket's first value, values below it (sixteen-wave form only)
     u32 *km_mag;              // [segment][256] smallest non-zero magnitude (bit pattern) of every bucket
-    u64 *km_acc;              // [segment][3][EXCP_ABSM_BINS + 1][K] per-centre exact sum and count, by iteration modulo 3
+    u64 *km_acc;              // [TDesc::acc_slot][stream][3][EXCP_ABSM_BINS + 1][K] per-centre exact sum and count, by iteration modulo 3
     double *part_obj;         // [chunk]
     // decode
     DDesc *ddesc; DState *dst;
@@ -206,8 +216,9 @@ static inline u64 excp_cand_words(u64 group_elems, u32 group_tensors) { return g
 // for the pass, 16.8 M 41.2 -> 39.0 and 41.5 -> 37.4 for the select, whose waves share the lists out.)
 static __host__ __device__ inline u32 excp_cand_first(u32 workgroup, u32 lists) { return workgroup % lists; }
 
-// Whether one workgroup takes a tensor's streams through all Lloyd iterations.
-static __host__ __device__ inline bool excp_lloyd_alone(u64 n, u32 K) { return n * (K - 1u) <= (1ull << 27); }
+// Tensors so small that one workgroup takes their streams through all Lloyd iterations whatever the values are
+// (unless their group goes together and has others).
+static inline bool excp_lloyd_small(u64 n, u32 K) { return n <= (K > 3u ? 1ull << 17 : 1ull << 22) && n * (K - 1u) <= (1ull << 24); }
 
 void launch_zero_u32(u32 *p, u64 count, hipStream_t s);
 void launch_copy_probe(const void *src, void *dst, u64 bytes, hipStream_t s);

@@ -18,6 +18,9 @@ namespace {
 constexpr u32 kMaxGroupTensors = 1024;   // tensors processed together (== EXCP_MAX_GROUP_TENSORS of the kernels)
 constexpr u32 kMaxBatchTensors = 4096;   // tensors per compress / decompress call
 constexpr u64 kAccSegCentres = 3ull * kMaxGroupTensors * 85;   // streams x centres whose accumulators the workspace holds
+// GroupParams::alone_work (see the Lloyd iterations in k_kmeans.hip): groups that go together; others, by the number of centres.
+constexpr u32 kAloneTogether = 24576, kAloneFew = 196608, kAloneMany = 131072;
+constexpr u64 kNoLimit = ~0ull;
 
 enum Stage {
     ST_SAMPLE = 0, ST_STATS, ST_SELECT, ST_MASK_COMPACT, ST_MASK_SCAN, ST_MASK_GATHER, ST_LAYOUT, ST_KM_SAMPLE, ST_KM_SCAN,
@@ -123,17 +126,19 @@ u64 blob_size_host(u64 n, u64 nw, u64 no, int nbits, u32 flags = 0) {
     return s;
 }
 
-// Split [0, count) into groups: at most kMaxGroupTensors tensors, cap_elems elements, tcap tensors.
-template <class GetN>
-void make_groups(int count, u64 cap_elems, u32 tcap, GetN get_n, std::vector<Group> &out) {
+// Split [0, count) into groups: at most kMaxGroupTensors tensors, cap_elems elements, and cap_some of the tensors that
+// `some` holds for.
+template <class GetN, class Some>
+void make_groups(int count, u64 cap_elems, GetN get_n, u64 cap_some, Some some, std::vector<Group> &out) {
     u32 i = 0;
     while (i < (u32)count) {
         Group g{i, 0, 0};
-        u64 elems = 0;
-        while (i < (u32)count && g.count < tcap) {
+        u64 elems = 0, of_some = 0;
+        while (i < (u32)count && g.count < kMaxGroupTensors) {
             u64 n = get_n(i);
-            if (g.count && elems + n > cap_elems) break;
-            elems += n;
+            const bool is_some = some(i);
+            if (g.count && (elems + n > cap_elems || (is_some && of_some >= cap_some))) break;
+            elems += n; of_some += is_some ? 1 : 0;
             g.ntiles += (u32)((n + EXCP_TILE - 1) / EXCP_TILE);
             ++g.count; ++i;
         }
@@ -164,7 +169,7 @@ int run_dense(excp_ctx *c, int count, bool exporting, Fill fill) {
     std::vector<Group> &groups = c->groups;
     std::vector<u32> &tb_offsets = c->tb_offsets;
     groups.clear(); tb_offsets.clear();
-    make_groups(count, c->max_group, kMaxGroupTensors, [&](u32 i) { DDesc d; fill(i, d); return (u64)d.n; }, groups);
+    make_groups(count, c->max_group, [&](u32 i) { DDesc d; fill(i, d); return (u64)d.n; }, kNoLimit, [](u32) { return false; }, groups);
     u32 tb_off = 0;
     for (const Group &g : groups) {
         u32 tile = 0;
@@ -348,6 +353,7 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.mask_bo, 2 * max_tiles * 32);
     ok = ok && dev_alloc(c, &w.chunk_total, 4);
     ok = ok && dev_alloc(c, &w.seg_chunk_begin, 3ull * kMaxGroupTensors + 4);
+    ok = ok && dev_alloc(c, &w.lloyd_shared, 1);
     ok = ok && dev_alloc(c, &w.seg_unit_begin, 3ull * kMaxGroupTensors + 4);
     const u64 nseg_max = 3ull * kMaxGroupTensors;
     const u64 acc_words = kAccSegCentres * 3 * (EXCP_ABSM_BINS + 1);
@@ -473,17 +479,27 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
     }
     if (hipSetDevice(c->device) != hipSuccess) return EXCP_E_HIP;
     const u64 cap_elems = c->max_group;
-    // (the accumulators of the Lloyd iterations hold 3 x 1024 streams of up to 85 centres: six-bit codes and fewer)
-    const u32 tcap = (u32)std::min<u64>(kMaxGroupTensors, kAccSegCentres / (3ull * (u64)std::max(K, 1)));
+    // (the accumulators of the Lloyd iterations hold 3 x 1024 streams of up to 85 centres -- six-bit codes and fewer --
+    // or 341 tensors of 255; small tensors have none)
+    const u64 acc_slots = kAccSegCentres / (3ull * (u64)std::max(K, 1));
+    auto small = [&](u32 i) { return raw || excp_lloyd_small(tensors[i].n, (u32)K); };
     std::vector<Group> &groups = c->groups;
     std::vector<u32> &tb_offsets = c->tb_offsets;
     groups.clear(); tb_offsets.clear();
-    make_groups(count, cap_elems, tcap, [&](u32 i) { return (u64)tensors[i].n; }, groups);
+    make_groups(count, cap_elems, [&](u32 i) { return (u64)tensors[i].n; }, acc_slots, [&](u32 i) { return !small(i); }, groups);
 
+    // Groups with larger tensors beside no more streams than compute units take all of them the same way through the
+    // Lloyd iterations (see k_kmeans.hip).
+    auto lloyd_together = [&](const Group &g) {
+        bool any = false;
+        for (u32 q = 0; q < g.count; ++q) any = any || !small(g.first + q);
+        return any && 3u * g.count <= (u32)c->w.cus;
+    };
     u32 tb_off = 0;
     for (const Group &g : groups) {
-        u64 elem_off = 0, cand_off = 0; u32 tile = 0;
+        u64 elem_off = 0, cand_off = 0; u32 tile = 0, slot = 0;
         tb_offsets.push_back(tb_off);
+        const bool together = lloyd_together(g);
         for (u32 q = 0; q < g.count; ++q) {
             const excp_tensor &t = tensors[g.first + q];
             TDesc &d = c->h_desc[g.first + q];
@@ -494,6 +510,7 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             d.cand_off = cand_off; d.cand_cap = excp_cand_cap(t.n, d.cand_lists);
             cand_off += d.cand_cap;
             d.tile_count = (u32)((t.n + EXCP_TILE - 1) / EXCP_TILE);
+            d.acc_slot = t.n && (together || !small(g.first + q)) ? slot++ : EXCP_NO_SLOT; d.pad = 0;
             c->h_tile_begin[tb_off + q] = tile;
             elem_off += t.n; tile += d.tile_count;
         }
@@ -531,16 +548,9 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         u64 largest = 0;
         for (u32 q = 0; q < g.count; ++q) largest = std::max<u64>(largest, tensors[g.first + q].n);
         if (!raw) {
-            // Work units of a Lloyd iteration of the streams too large for one workgroup: about 8192 values in cut
-            // buckets (at most K - 1 of 256 are cut), more where that would make more than two units per compute
-            // unit (a third of a tensor's values survive in its three streams at the usual thresholds).
-            u64 large_chunks = 0;
-            for (u32 q = 0; q < g.count; ++q)
-                if (!excp_lloyd_alone(tensors[g.first + q].n, (u32)K)) large_chunks += tensors[g.first + q].n / EXCP_CHUNK / 2;
-            p.unit_chunks = (u32)std::max<u64>(std::max<u64>(256u / (u32)std::max(K - 1, 1), 1), large_chunks / (2ull * (u64)w.cus));
-            const u64 per = (u64)p.unit_chunks * EXCP_CHUNK;
-            for (u32 q = 0; q < g.count; ++q)
-                if (!excp_lloyd_alone(tensors[g.first + q].n, (u32)K)) p.max_units += 3ull * ((tensors[g.first + q].n + per - 1) / per);
+            p.together = lloyd_together(g) ? 1u : 0u;
+            p.alone_work = p.together ? kAloneTogether : (K < 63 ? kAloneFew : kAloneMany);
+            for (u32 q = 0; q < g.count; ++q) p.slots += c->h_desc[g.first + q].acc_slot != EXCP_NO_SLOT ? 1u : 0u;
         }
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
         { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, s); }
@@ -601,7 +611,7 @@ int excp_decompress_tensors(excp_ctx *c, int count, const excp_blob *blobs) {
     std::vector<Group> &groups = c->groups;
     std::vector<u32> &tb_offsets = c->tb_offsets;
     groups.clear(); tb_offsets.clear();
-    make_groups(count, c->max_group, kMaxGroupTensors, [&](u32 i) { return (u64)blobs[i].n; }, groups);
+    make_groups(count, c->max_group, [&](u32 i) { return (u64)blobs[i].n; }, kNoLimit, [](u32) { return false; }, groups);
     u32 tb_off = 0;
     for (const Group &g : groups) {
         u32 tile = 0;

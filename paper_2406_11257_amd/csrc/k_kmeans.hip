@@ -665,8 +665,8 @@ __global__ __launch_bounds__(BS_WAVES * 64, BS_WAVES == 16u ? 8 : 5) void k_km_b
 // groups with a tensor of 2^28 elements; 256 otherwise: with 1024 for everybody the 14 000 workgroups of a 410M-shaped
 // checkpoint took 347 us instead of 167, and 22 instead of 33 for a 16.8 M-element tensor)
 //
-// The prefix sums turn the total of any run of buckets into one difference; the workgroup of centre k also
-// clears its share of the accumulators of the Lloyd iterations.
+// The prefix sums turn the total of any run of buckets into one difference; the workgroup that makes them also decides
+// how the stream goes through the Lloyd iterations, and the workgroup of centre k clears its share of their accumulators.
 template <u32 INIT_THREADS>
 __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupParams g, u32 sel) {
     __shared__ u32 hist[2048];
@@ -679,7 +679,7 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
     if (k == K) {
         // a wave takes a bin: four consecutive buckets per lane
         u64 *bs = w.km_bsum + (u64)sidx * EXCP_ABSM_BINS * (NBKT + 1);
-        if (tid < 2) { s_pick[tid] = tid ? 0u : 64u; s_wave[tid] = tid ? 0u : 255u; }
+        if (tid < 2) { s_pick[tid] = tid ? 0u : 64u; s_wave[tid] = tid ? 0u : 255u; s_wave[2] = 0u; }
         __syncthreads();
         if (tid < NBKT) {                      // lowest and highest bit position of any value
             const u32 kn = w.km_min[(u64)sidx * NBKT + tid], kx = w.km_max[(u64)sidx * NBKT + tid];
@@ -687,6 +687,11 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
                 const u32 a = f2u(val_of(kn)) & 0x7fffffffu, c = f2u(val_of(kx)) & 0x7fffffffu;
                 atomicMin(&s_wave[0], bit_pos(w.km_mag[(u64)sidx * NBKT + tid]));
                 atomicMax(&s_wave[1], bit_pos(max(a, c)));
+                if (kn < kx) {                 // (a bucket of one value is never cut)
+                    const u32 *begin = w.km_begin + (u64)sidx * (NBKT + 1);
+                    // (of tied data: what is not a repetition of the bucket's first value)
+                    atomicMax(&s_wave[2], begin[tid + 1u] - begin[tid] - (INIT_THREADS == 1024u ? w.km_dom[(u64)sidx * NBKT + tid] : 0u));
+                }
             }
         }
         for (u32 bin = wave; bin < EXCP_ABSM_BINS; bin += INIT_THREADS / 64u) {
@@ -710,13 +715,20 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
             // (windows begin up to 19 positions below a value, and sums reach up to 64 positions above one)
             S.acc_lo = s_wave[0] > 19u ? (s_wave[0] - 19u) >> 3 : 0u;
             S.acc_hi = min(s_wave[1] / 8u + 9u, EXCP_ABSM_BINS - 1u);
+            // one workgroup or many (see P6)
+            const u64 even = (len * (K - 1u)) / NBKT, crowded = (u64)s_wave[2] * (K > 3u ? 8u : 1u);
+            S.work = (u32)min(max(even, crowded), 0xffffffffull);
+            if (S.work > g.alone_work && w.desc[sidx / 3u].acc_slot != EXCP_NO_SLOT) {
+                atomicOr(&w.st[sidx / 3u].lloyd_shared, 1u);
+                atomicOr(w.lloyd_shared, 1u);
+            }
         }
         return;
     }
     {
         constexpr u32 SHARE = 3u * (EXCP_ABSM_BINS + 1u);
-        u64 *acc = w.km_acc + ((u64)sidx * K + k) * SHARE;
-        if (tid < SHARE) acc[tid] = 0;
+        const u32 slot = w.desc[sidx / 3u].acc_slot;
+        if (slot != EXCP_NO_SLOT && tid < SHARE) w.km_acc[((3ull * slot + sidx % 3u) * K + k) * SHARE + tid] = 0;
     }
     const u32 *begin = w.km_begin + (u64)sidx * (NBKT + 1);
     const u32 r = (u32)(((u64)(2 * k + 1) * len) / (2ull * K));
@@ -845,14 +857,35 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
 // totals, cut keys, which buckets are cut, their values, sums), so a stream goes through it in one of two ways:
 //
 //   one workgroup per stream, all iterations in one launch (k_km_lloyd): no launch gaps, totals in LDS;
-//   one launch per iteration, many workgroups per stream (k_km_iter), for streams whose cut buckets hold so many
-//   values that one compute unit would read them for longer than a launch takes.
+//   one launch per iteration, many workgroups per stream (k_km_iter), where the cut buckets hold so many values that
+//   one compute unit would read them for longer than a launch takes.
 //
-// The line (excp_lloyd_alone) is drawn on the tensor's size, which the host knows, so that a group without large
-// tensors launches nothing for them: up to n (K - 1) / 256 = 2^20 values could lie in cut buckets (a third of
-// that at the usual keep rates), which one compute unit reads in about 10 us.
+// What decides is the number of values that an iteration is expected to read (SegState::work, from the filled buckets): K - 1
+// even shares of 256, or the largest bucket that holds more than one value, if that is more.  The values of a crowded
+// bucket (residuals of a sign-like update, values bunched beside outliers) count eight times from four centres on, since
+// most centres then lie in that bucket, and its values go one by one; of tied data only what is not a repetition of a
+// bucket's first value counts.  A tensor's streams go the same way.  The host launches the iterations of the second
+// way wherever a tensor is too large for excp_lloyd_small (2^17 elements, up to where one workgroup is no slower whatever
+// the values are: 130 000 bunched ones take it 1.1 ms, which the former work lists needed as well); where no stream takes
+// it they are empty, 1.6 us each.
+//   Up to 85 tensors on 256 compute units the group goes together, beyond 24 576 (one tensor, 4 bits, ten iterations, us
+//   alone / shared: 1 M elements 163 / 178, 1.5 M 186 / 188, 2.5 M 207 / 174, 10 M 340 / 169; 8 bits: 140 000 elements
+//   737 / 346, 2.5 M 1565 / 194; the 14M shape 248 -> 192).  Bunched values, 4 bits: 1 M elements 8095 -> 211, 9 M 74451 -> 543.
+//   More tensors fill the GPU as they are, one workgroup a stream, and the line lies at 196 608 (300 tensors of 600 000
+//   elements, 4 bits: 338 alone, 522 shared; the 410M shape 440, and 499 with the line at 65 536), from six bits on at
+//   131 072 (the 410M shape in 7 bits 1943, and 2406 with the line at 196 608).
 constexpr u32 LLOYD_THREADS = 512, LLOYD_WAVES = LLOYD_THREADS / 64;
 constexpr u32 LLOYD_FEW = 4 * LLOYD_THREADS;              // up to here a value per thread is quicker than a bucket per wave
+
+// Workgroups of the form for up to KMAX centres that a compute unit holds, and values in cut buckets that are worth one
+// (more centres, more borders to a bucket: 5 bits, 1.5 M elements 236 us with 8192, 169 with 4096).
+constexpr u32 lloyd_per_cu(u32 KMAX) { return KMAX > 63u ? 1u : 2u; }
+constexpr u32 lloyd_unit(u32 KMAX) { return KMAX > 15u ? 4096u : 8192u; }
+
+// Whether many workgroups take the stream's iterations.
+__device__ __forceinline__ bool lloyd_shared(const Workspace &w, const GroupParams &g, u32 sidx) {
+    return (g.together ? *w.lloyd_shared : w.st[sidx / 3u].lloyd_shared) != 0u;
+}
 
 struct LloydShared {
     float C[EXCP_MAX_K + 1], fresh[EXCP_MAX_K + 1];
@@ -1167,15 +1200,50 @@ __device__ __forceinline__ void lloyd_share(const EXCP_GLOBAL float *part, u32 q
     }
 }
 
+// The work units of the streams that many workgroups take (one workgroup makes the table): lloyd_unit values of cut buckets
+// each, more where that would make more units than the GPU holds at once (one more costs a second round: 8 bits, 2.5 M
+// elements 300 instead of 194 us), and one at least for every stream.
+template <u32 KMAX>
+__device__ __forceinline__ void lloyd_units(const Workspace &w, const GroupParams &g) {
+    __shared__ u64 s_work[LLOYD_WAVES];
+    __shared__ u32 s_streams[LLOYD_WAVES], s_units[LLOYD_WAVES];
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, nseg = 3u * g.ntensors;
+    const u32 per = (nseg + LLOYD_THREADS - 1u) / LLOYD_THREADS, s0 = min(tid * per, nseg), s1 = min(s0 + per, nseg);
+    auto work_of = [&](u32 s) { return w.seg[s].len != 0 && lloyd_shared(w, g, s) ? max(w.seg[s].work, 1u) : 0u; };
+    u64 work = 0;
+    u32 streams = 0;
+    for (u32 s = s0; s < s1; ++s) { const u32 x = work_of(s); work += x; streams += x != 0u; }
+    work = wave_sum_u64(work); streams = wave_sum_u32(streams);
+    if (lane == 0u) { s_work[wave] = work; s_streams[wave] = streams; }
+    __syncthreads();
+    work = 0; streams = 0;
+#pragma unroll
+    for (u32 v = 0; v < LLOYD_WAVES; ++v) { work += s_work[v]; streams += s_streams[v]; }
+    // whole units: a stream's last one is extra, so there is room for one a stream
+    const u32 at_once = lloyd_per_cu(KMAX) * (u32)w.cus, whole = max(at_once - min(streams, at_once / 2u), streams);
+    const u64 unit = max((u64)lloyd_unit(KMAX), work / whole + 1u);
+    auto units_of = [&](u32 s) { return (u32)((work_of(s) + unit - 1u) / unit); };
+    u32 units = 0;
+    for (u32 s = s0; s < s1; ++s) units += units_of(s);
+    const u32 incl = wave_incl_scan_u32(units);
+    if (lane == 63u) s_units[wave] = incl;
+    __syncthreads();
+    u32 run = incl - units;
+    for (u32 v = 0; v < wave; ++v) run += s_units[v];
+    for (u32 s = s0; s < s1; ++s) { w.seg_unit_begin[s] = run; run += units_of(s); }
+    if (tid == LLOYD_THREADS - 1u) w.seg_unit_begin[nseg] = run;
+}
+
 // One workgroup takes a stream through all its iterations; the final centres and cut keys end in the slots of
 // parity `iters`.  KMAX: the centres the LDS accumulators are laid out for.
 template <u32 KMAX>
-__global__ __launch_bounds__(LLOYD_THREADS, KMAX > 63u ? 1 : 2) void k_km_lloyd(Workspace w, GroupParams g) {
+__global__ __launch_bounds__(LLOYD_THREADS, lloyd_per_cu(KMAX)) void k_km_lloyd(Workspace w, GroupParams g) {
     __shared__ LloydShared L;
     __shared__ u64 acc[(EXCP_ABSM_BINS + 1u) * KMAX];
+    if (blockIdx.x == 3u * g.ntensors) { lloyd_units<KMAX>(w, g); return; }
     const u32 sidx = stream_in_turn(w, blockIdx.x), tid = threadIdx.x, wave = tid >> 6, K = (u32)g.K, iters = (u32)g.iters;
     SegState &S = w.seg[sidx];
-    if (S.len == 0 || !excp_lloyd_alone(w.desc[sidx / 3u].n, K)) return;
+    if (S.len == 0 || lloyd_shared(w, g, sidx)) return;
     u32 kp2 = 1; while (kp2 < K) kp2 <<= 1;
     LloydStream st = lloyd_open(w, sidx, K, 1u, false, L);
     lloyd_clear(acc, st, K);
@@ -1195,13 +1263,12 @@ __global__ __launch_bounds__(LLOYD_THREADS, KMAX > 63u ? 1 : 2) void k_km_lloyd(
     if (tid <= EXCP_MAX_K) S.cut[iters & 1u][tid] = tid ? L.cut[tid] : 0u;
 }
 
-// One iteration of the larger streams.  A work unit is a stream's share of its cut buckets that belongs to
-// unit_chunks of its chunks, a workgroup each (the grid is the most units the group can have; those beyond the
-// units there are have nothing to do).  Every workgroup of a stream computes the centres for itself, adds its share
-// up in LDS, and hands the sums over.  The launch after the last iteration (i == iters) only makes the final
-// centres.
+// One iteration of the streams that many workgroups take: a workgroup for each work unit, which is an even share of the
+// stream's cut buckets (the grid is the most units the group can have; those beyond the units there are have nothing
+// to do).  Every workgroup of a stream computes the centres for itself, adds its share up in LDS, and hands the sums over.
+// The launch after the last iteration (i == iters) only makes the final centres.
 template <u32 KMAX>
-__global__ __launch_bounds__(LLOYD_THREADS, KMAX > 63u ? 1 : 2) void k_km_iter(Workspace w, GroupParams g, u32 i) {
+__global__ __launch_bounds__(LLOYD_THREADS, lloyd_per_cu(KMAX)) void k_km_iter(Workspace w, GroupParams g, u32 i) {
     __shared__ LloydShared L;
     __shared__ u64 acc[(EXCP_ABSM_BINS + 1u) * KMAX];
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, u = blockIdx.x;
@@ -1222,7 +1289,7 @@ __global__ __launch_bounds__(LLOYD_THREADS, KMAX > 63u ? 1 : 2) void k_km_iter(W
     if (i == (u32)g.iters && u_first != 0u) return;
     u32 kp2 = 1; while (kp2 < K) kp2 <<= 1;
     SegState &S = w.seg[sidx];
-    u64 *gacc = w.km_acc + (u64)sidx * 3u * accw;         // [3][bins + count][K]
+    u64 *gacc = w.km_acc + (3ull * w.desc[sidx / 3u].acc_slot + sidx % 3u) * 3u * accw;      // [3][bins + count][K]
     LloydStream st = lloyd_open(w, sidx, K, (i + 1u) & 1u, i > 0u, L);
     if (i == 0u) {
         lloyd_clear(acc, st, K);
@@ -1521,13 +1588,14 @@ void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s) {
     }
 }
 
-// All iterations: the streams that one workgroup takes through them, then, if the group has larger ones, a launch
-// per iteration and one for the final centres.
+// All iterations: the streams that one workgroup takes through them, then, if the group may have others, a launch per
+// iteration and one for the final centres.
 template <u32 KMAX>
 static void launch_lloyd(const Workspace &w, const GroupParams &g, hipStream_t s) {
-    hipLaunchKernelGGL(k_km_lloyd<KMAX>, dim3(3 * g.ntensors), dim3(LLOYD_THREADS), 0, s, w, g);
-    if (!g.max_units) return;
-    for (u32 i = 0; i <= (u32)g.iters; ++i) hipLaunchKernelGGL(k_km_iter<KMAX>, dim3((u32)g.max_units), dim3(LLOYD_THREADS), 0, s, w, g, i);
+    hipLaunchKernelGGL(k_km_lloyd<KMAX>, dim3(3 * g.ntensors + (g.slots ? 1 : 0)), dim3(LLOYD_THREADS), 0, s, w, g);
+    if (!g.slots) return;
+    const u32 units = excp_grid(w, lloyd_per_cu(KMAX)) + 6 * g.slots;   // (as many as there can be: see lloyd_units)
+    for (u32 i = 0; i <= (u32)g.iters; ++i) hipLaunchKernelGGL(k_km_iter<KMAX>, dim3(units), dim3(LLOYD_THREADS), 0, s, w, g, i);
 }
 void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s) {
     if (!g.ntensors) return;

@@ -564,11 +564,11 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_bitmap_o_elems(Workspace 
 // After the masks: blob section offsets, capacity check, survivor stream lengths and the chunk
 // list of the survivor passes.  One workgroup; tensors and streams are few.
 __global__ __launch_bounds__(EXCP_THREADS) void k_layout(Workspace w, GroupParams g, u32 *seg_chunk_begin) {
-    __shared__ u32 s_sum[3][EXCP_THREADS / 64];
+    __shared__ u32 s_sum[2][EXCP_THREADS / 64];
     const u32 tid = threadIdx.x;
     const u32 nseg = 3u * g.ntensors;
     const u32 per = (nseg + EXCP_THREADS - 1) / EXCP_THREADS;
-    u32 local[3] = {0u, 0u, 0u};                          // chunks, rows of the count table, work units
+    u32 local[2] = {0u, 0u};                              // chunks, rows of the count table
     for (u32 q = 0; q < per; ++q) {
         u32 sidx = tid * per + q;
         if (sidx >= nseg) break;
@@ -608,18 +608,17 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_layout(Workspace w, GroupParam
         const u32 chunks = (u32)((len + EXCP_CHUNK - 1) / EXCP_CHUNK);
         local[0] += chunks;
         local[1] += (chunks + EXCP_SUPER_CHUNKS - 1u) / EXCP_SUPER_CHUNKS;
-        if (g.max_units && !excp_lloyd_alone(D.n, (u32)g.K)) local[2] += (chunks + g.unit_chunks - 1u) / g.unit_chunks;
     }
-    u32 run[3], total[3];
+    u32 run[2], total[2];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
+    for (int q = 0; q < 2; ++q) {
         u32 incl = wave_incl_scan_u32(local[q]);
         if ((tid & 63u) == 63u) s_sum[q][tid >> 6] = incl;
         run[q] = incl - local[q];
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
+    for (int q = 0; q < 2; ++q) {
         total[q] = 0;
         for (u32 v = 0; v < EXCP_THREADS / 64; ++v) { if (v < (tid >> 6)) run[q] += s_sum[q][v]; total[q] += s_sum[q][v]; }
     }
@@ -627,15 +626,13 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_layout(Workspace w, GroupParam
         u32 sidx = tid * per + q;
         if (sidx >= nseg) break;
         seg_chunk_begin[sidx] = run[0];
-        w.seg_unit_begin[sidx] = run[2];
         w.seg[sidx].chunk_begin = run[0];
         w.seg[sidx].row_begin = run[1];
         const u32 chunks = (u32)((w.seg[sidx].len + EXCP_CHUNK - 1) / EXCP_CHUNK);
         run[0] += chunks;
         run[1] += (chunks + EXCP_SUPER_CHUNKS - 1u) / EXCP_SUPER_CHUNKS;
-        if (g.max_units && !excp_lloyd_alone(w.desc[sidx / 3u].n, (u32)g.K)) run[2] += (chunks + g.unit_chunks - 1u) / g.unit_chunks;
     }
-    if (tid == EXCP_THREADS - 1) { seg_chunk_begin[nseg] = total[0]; w.seg_unit_begin[nseg] = total[2]; *w.chunk_total = total[0]; }
+    if (tid == EXCP_THREADS - 1) { seg_chunk_begin[nseg] = total[0]; *w.chunk_total = total[0]; *w.lloyd_shared = 0u; }
 }
 
 }  // namespace

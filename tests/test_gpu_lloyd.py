@@ -1,7 +1,8 @@
 """Lloyd iterations (Sec. 3.3) against the oracle, blob for blob, where the kernels divide the work differently: streams
-that one workgroup takes through all iterations and larger ones with a launch per iteration (the line lies at
-n (K - 1) = 2^27 for a tensor of n values and K centres), few and many values in cut buckets, buckets with one, two and
-many borders, values of both signs in one bucket, and buckets whose values lie many binary orders apart."""
+that one workgroup takes through all iterations and others with a launch per iteration (the line lies at the values that
+an iteration is expected to read, and differs with the number of tensors), few and many values in cut buckets, buckets with
+one, two and many borders, crowded ones, values of both signs in one bucket, and buckets whose values lie many binary
+orders apart."""
 import numpy as np
 import pytest
 
@@ -62,3 +63,71 @@ def test_a_launch_per_iteration_with_fifteen_centres(ctx, kind):
 def test_no_iterations_and_the_usual_thresholds(ctx):
     check(ctx, [draw(n, n, "spread") for n in (1, 700, 600_000)], 8, 0, alpha=5e-5, beta=2.0)
     check(ctx, [draw(n, n, "spread") for n in (1, 700, 600_000)], 8, 10, alpha=5e-5, beta=2.0)
+
+
+def skewed(n, seed, kind):
+    """Residuals and moments that the value -> bucket map cannot spread: nearly all in one bucket, most centres with them."""
+    g = np.random.default_rng(seed)
+    sign = g.choice([-1.0, 1.0], n)
+    if kind == "sign step":                 # +-lr as fp32 weights round it, and a few smaller steps
+        Wp = (g.standard_normal(n) * 0.02).astype(f32)
+        d = sign * 1e-4 * np.where(g.random(n) < 0.02, g.random(n), 1.0)
+    else:                                   # "bunched": one thirtieth of an octave, a few values far away
+        Wp = np.zeros(n, f32)
+        d = sign * np.where(g.random(n) < 0.002, 2.0 ** (-40 * g.random(n) - 13), (1 + 0.02 * g.random(n)) * 2.0 ** -13)
+    W = (Wp + d).astype(f32)
+    m = (d * 0.1).astype(f32)
+    return Wp, W, m, (m.astype(np.float64) ** 2 * np.exp(g.normal(0, 1, n)) + 1e-16).astype(f32)
+
+
+@pytest.mark.parametrize("kind", ["sign step", "bunched"])
+def test_crowded_buckets_on_both_sides_of_the_lines(ctx, kind):
+    # one workgroup a stream up to 2^17 elements (2^24 / 254 in 8 bits, 2^22 in 2); beyond, the filled buckets decide
+    for nbits, sizes in ((4, [131_072, 5]), (4, [131_073, 3000, 7]), (4, [700_001]), (8, [66_052]), (8, [66_053, 400]), (2, [300_000]), (2, [4_194_305]), (6, [200_001])):
+        print(kind, nbits, sizes, flush=True)
+        check(ctx, [skewed(n, n + nbits, kind) for n in sizes], nbits, 3)
+
+
+@pytest.mark.parametrize("nbits, n", [(2, 4_200_001), (3, 1_200_001), (4, 460_001), (5, 210_001), (6, 300_001), (7, 140_001), (8, 70_001)])
+def test_even_buckets_of_one_tensor_in_both_ways(ctx, nbits, n):
+    # alone at the usual thresholds, or shared where every value is kept
+    check(ctx, [draw(n, nbits, "spread")], nbits, 2)
+    check(ctx, [draw(n, nbits, "spread"), draw(100, 3, "spread")], nbits, 2, alpha=5e-5, beta=2.0)
+
+
+def test_both_ways_in_one_group(ctx):
+    # more streams than compute units: tensors go either way by themselves
+    sizes = [140_001, 700, 100_003, 1, 140_002] + [300 + 7 * i for i in range(90)]
+    check(ctx, [draw(n, n, "spread") for n in sizes], 8, 2)
+    check(ctx, [skewed(n, n, "bunched") if i < 3 else draw(n, n, "gap") for i, n in enumerate(sizes)], 8, 2)
+
+
+def test_more_large_tensors_of_wide_codes_than_accumulators():
+    # 341 tensors of 255 centres have accumulators; smaller ones do without, and cost no group of their own
+    ctx = X.Context(70_000, 27_000_000)
+    small, large = [draw(n, n, "spread") for n in (2000, 3001)], draw(66_100, 1, "spread")
+    ctx.excp_set_profiling(True)
+    try:
+        for cases, groups in (([small[i & 1] for i in range(700)], 1), ([large] * 120 + [small[0]] * 600, 1), ([large] * 341 + [small[0]], 1),
+                              ([small[1]] + [large] * 342, 2)):
+            rc, out = gpu_compress(ctx, cases, 0.0, 0.0, 8, 1, want_recon=False)
+            assert rc == 0 and ctx.stage_times()["layout"][1] == groups
+            for i in (0, len(cases) // 2, len(cases) - 1):
+                assert out[i]["blob"] == O.compress_step(*cases[i], 0.0, 0.0, 8, 1).blob
+    finally:
+        ctx.close()
+
+
+def test_crowded_buckets_cost_no_multiple_of_even_ones(ctx):
+    # (one workgroup for all of a million bunched values took 55 times as long as for even ones)
+    ctx.excp_set_profiling(True)
+    try:
+        ms = {}
+        for kind in ("even", "sign step", "bunched"):
+            case = draw(1_000_003, 4, "spread") if kind == "even" else skewed(1_000_003, 4, kind)
+            for _ in range(3):
+                gpu_compress(ctx, [case], 0.0, 0.0, 4, 10, want_recon=False)
+                ms[kind] = min(ms.get(kind, 1e9), ctx.stage_times()["km_iter"][0])
+        assert max(ms.values()) < 10 * ms["even"], ms
+    finally:
+        ctx.excp_set_profiling(False)
