@@ -675,24 +675,23 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
     const u32 sidx = stream_in_turn(w, stream_of(blockIdx.x / (K + 1u), sel)), k = blockIdx.x % (K + 1u), tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     SegState &S = w.seg[sidx];
     const u64 len = S.len;
+    const u32 slot = ((const EXCP_CONSTANT TDesc *)(uintptr_t)(w.desc + sidx / 3u))->acc_slot;
     if (len == 0) return;
     if (k == K) {
         // a wave takes a bin: four consecutive buckets per lane
         u64 *bs = w.km_bsum + (u64)sidx * EXCP_ABSM_BINS * (NBKT + 1);
         if (tid < 2) { s_pick[tid] = tid ? 0u : 64u; s_wave[tid] = tid ? 0u : 255u; s_wave[2] = 0u; }
         __syncthreads();
-        if (tid < NBKT) {                      // lowest and highest bit position of any value
-            const u32 kn = w.km_min[(u64)sidx * NBKT + tid], kx = w.km_max[(u64)sidx * NBKT + tid];
-            if (kn <= kx) {                    // (an empty bucket has no extremes)
-                const u32 a = f2u(val_of(kn)) & 0x7fffffffu, c = f2u(val_of(kx)) & 0x7fffffffu;
-                atomicMin(&s_wave[0], bit_pos(w.km_mag[(u64)sidx * NBKT + tid]));
-                atomicMax(&s_wave[1], bit_pos(max(a, c)));
-                if (kn < kx) {                 // (a bucket of one value is never cut)
-                    const u32 *begin = w.km_begin + (u64)sidx * (NBKT + 1);
-                    // (of tied data: what is not a repetition of the bucket's first value)
-                    atomicMax(&s_wave[2], begin[tid + 1u] - begin[tid] - (INIT_THREADS == 1024u ? w.km_dom[(u64)sidx * NBKT + tid] : 0u));
-                }
-            }
+        if (tid < NBKT) {                      // lowest and highest bit position of any value, largest bucket of several
+            const u32 at = sidx * NBKT + tid, kn = w.km_min[at], kx = w.km_max[at], low = w.km_mag[at];
+            const u32 b0 = w.km_begin[sidx * (NBKT + 1u) + tid], b1 = w.km_begin[sidx * (NBKT + 1u) + tid + 1u];
+            // (of tied data: what is not a repetition of the bucket's first value; a bucket of one value is never cut)
+            const u32 most = b1 - b0 - (INIT_THREADS == 1024u ? w.km_dom[at] : 0u);
+            const bool any = kn <= kx;         // (an empty bucket has no extremes)
+            const u32 a = f2u(val_of(kn)) & 0x7fffffffu, c = f2u(val_of(kx)) & 0x7fffffffu;
+            // (reduced in the wave first: an atomic whose lanes differ is a loop over them: three of those, 3000 streams 476 us, now 329)
+            const u32 p0 = wave_min_u32(any ? bit_pos(low) : 255u), p1 = wave_max_u32(any ? bit_pos(max(a, c)) : 0u), p2 = wave_max_u32(kn < kx ? most : 0u);
+            if (lane == 0u) { atomicMin(&s_wave[0], p0); atomicMax(&s_wave[1], p1); atomicMax(&s_wave[2], p2); }
         }
         for (u32 bin = wave; bin < EXCP_ABSM_BINS; bin += INIT_THREADS / 64u) {
             u64 *row = bs + (u64)bin * (NBKT + 1);
@@ -718,7 +717,7 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
             // one workgroup or many (see P6)
             const u64 even = (len * (K - 1u)) / NBKT, crowded = (u64)s_wave[2] * (K > 3u ? 8u : 1u);
             S.work = (u32)min(max(even, crowded), 0xffffffffull);
-            if (S.work > g.alone_work && w.desc[sidx / 3u].acc_slot != EXCP_NO_SLOT) {
+            if (S.work > g.alone_work && slot != EXCP_NO_SLOT) {
                 atomicOr(&w.st[sidx / 3u].lloyd_shared, 1u);
                 atomicOr(w.lloyd_shared, 1u);
             }
@@ -727,7 +726,6 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
     }
     {
         constexpr u32 SHARE = 3u * (EXCP_ABSM_BINS + 1u);
-        const u32 slot = w.desc[sidx / 3u].acc_slot;
         if (slot != EXCP_NO_SLOT && tid < SHARE) w.km_acc[((3ull * slot + sidx % 3u) * K + k) * SHARE + tid] = 0;
     }
     const u32 *begin = w.km_begin + (u64)sidx * (NBKT + 1);
@@ -735,9 +733,12 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
     // the bucket that holds the rank: begin[b] <= r < begin[b + 1] (empty buckets repeat an entry)
     if (tid < NBKT) { if (begin[tid] <= r && r < begin[tid + 1]) s_pick[0] = tid; }
     __syncthreads();
-    const u32 b = s_pick[0], p0 = begin[b], p1 = begin[b + 1], cntb = p1 - p0;
+    // (the same in every lane, and through the scalar unit: left to the compiler, whether it is depends on stores nearby)
+    const u32 b = (u32)__builtin_amdgcn_readfirstlane((int)s_pick[0]);
+    const EXCP_CONSTANT u32 *ends = (const EXCP_CONSTANT u32 *)(uintptr_t)begin;
+    const u32 p0 = ends[b], p1 = ends[b + 1], cntb = p1 - p0;
     u32 rank = r - p0;
-    const u32 kmin = w.km_min[(u64)sidx * NBKT + b], kmax = w.km_max[(u64)sidx * NBKT + b];
+    const u32 kmin = ((const EXCP_CONSTANT u32 *)(uintptr_t)w.km_min)[(u64)sidx * NBKT + b], kmax = ((const EXCP_CONSTANT u32 *)(uintptr_t)w.km_max)[(u64)sidx * NBKT + b];
     const EXCP_GLOBAL float *gpart = gptr(seg_part(w, sidx)) + p0;
     u32 diff = kmin ^ kmax;
     float *out = &S.C[1][k];                 // (read by iteration 0, whose predecessor has parity 1)

@@ -621,7 +621,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_median_select(Workspace w, Gro
         }
         // The last of the tensor's workgroups sees everybody's counts: they are only ever touched by device-scope
         // atomics, which are done (vmcnt) before the ticket is drawn.  (A __threadfence here would write back the
-        // whole L2 for every workgroup: 302 us a pass instead of 53 for 1.07e9 elements in 4080 workgroups.)
+        // whole L2 for every workgroup: 302 us a pass instead of 53 for 1.07e9 elements with 64 tiles to a workgroup.)
         const u32 parts = (te - 1u) / SEL_TILES - tb / SEL_TILES + 1u;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();

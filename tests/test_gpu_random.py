@@ -28,7 +28,7 @@ def ctx():
 def ctx_wide():
     """The same limits, with the size thresholds of the library lowered so that every batch runs the
     kernel forms that otherwise only tensors of 2^28 elements (per-bucket totals and initial centres with
-    sixteen waves, one workgroup per bucket) or 2^27 elements (several median-candidate lists) reach."""
+    sixteen waves, one workgroup per bucket) or 2^21 elements (several median-candidate lists) reach."""
     c = X.Context(1 << 21, 4 << 20)
     c.excp_set_param(X.EXCP_PARAM_WIDE_ELEMS, 1)
     c.excp_set_param(X.EXCP_PARAM_CAND_LIST_ELEMS, 65536)
