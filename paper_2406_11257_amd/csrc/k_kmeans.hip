@@ -745,7 +745,7 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
     if (diff == 0) { if (tid == 0) *out = val_of(kmin); return; }
     // Tied data: the rank usually falls among the repetitions of the bucket's first value, which have been counted.
     // (The K ranks of a stream often ask for the same few large buckets: reading those for each of them took most
-    // of this kernel's time, 468 of now 148 us for a 410M-shaped checkpoint in bf16.)
+    // of this kernel's time: a 410M-shaped checkpoint in bf16 468 us, 164 now.)
     if (INIT_THREADS == 1024u && rank - w.km_less[(u64)sidx * NBKT + b] < w.km_dom[(u64)sidx * NBKT + b]) { if (tid == 0) *out = gpart[0]; return; }
     // A bucket far above the average size holds tied values (a continuous distribution fills the
     // buckets evenly).  Such a bucket is mostly ONE value, its smallest or its largest key, with a few
@@ -880,7 +880,7 @@ constexpr u32 LLOYD_FEW = 4 * LLOYD_THREADS;              // up to here a value 
 
 // Workgroups of the form for up to KMAX centres that a compute unit holds, and values in cut buckets that are worth one
 // (more centres, more borders to a bucket: 5 bits, 1.5 M elements 236 us with 8192, 169 with 4096).
-constexpr u32 lloyd_per_cu(u32 KMAX) { return KMAX > 63u ? 1u : 2u; }
+constexpr u32 lloyd_per_cu(u32 KMAX) { return KMAX > 63u ? 1u : 2u; }        // (two waves per SIMD each)
 constexpr u32 lloyd_unit(u32 KMAX) { return KMAX > 15u ? 4096u : 8192u; }
 
 // Whether many workgroups take the stream's iterations.
@@ -1132,16 +1132,40 @@ __device__ __forceinline__ void lloyd_borders(const EXCP_GLOBAL float *part, u32
     if (lane < 3u && n) atomicAdd(&acc[EXCP_ABSM_BINS * K + c_lo + lane], (u64)(long long)(int)n);
 }
 
-// One wave, values [p0, p1) of a bucket that three or more borders cut: value by value.  What leaves c_lo is kept per
-// lane where the bucket spans at most 39 binary orders (units of its lowest position, in two 32-bit halves),
-// because all lanes would queue at that one centre.
+// One wave, values [p0, p1) of a bucket that three or more borders cut: value by value.  Where the bucket spans at most
+// seven binary orders a value is below 2^31 units of its lowest position; its centre's sum and number then share a
+// word of the wave's own table (sum in the low 48 bits, number above), one LDS atomic a value instead of two, and what the
+// centres received leaves c_lo when the table is emptied, every 8192 values at the latest.  (Atomics on LDS bound this:
+// a 410M shape of bunched values, all kept, 3.8 -> 2.7 ms an iteration; ten of 9 M residuals of a sign-like update 251 ->
+// 230 us.)  Elsewhere what leaves c_lo is kept per lane where the bucket spans at most 39 binary orders (in two 32-bit
+// halves), because all lanes would queue at that one centre.
 __device__ __forceinline__ void lloyd_many(const EXCP_GLOBAL float *part, u32 p0, u32 p1, u32 c_lo, u32 c_hi, u32 pos_lo, u32 pos_hi, u32 K,
-                                           u64 *acc, const LloydShared &L) {
+                                           u64 *acc, u64 *mine, const LloydShared &L) {
     const u32 lane = lane_id();
-    const bool near = pos_hi - pos_lo <= 39u;
+    const bool near = pos_hi - pos_lo <= 39u, packed = pos_hi - pos_lo <= 7u;
     u32 top = 1; while (2u * top <= c_hi - c_lo) top <<= 1;
+    if (packed) {
+        for (u32 c = c_lo + 1u + lane; c <= c_hi; c += 64u) mine[c] = 0;
+        wave_lds_fence();
+    }
     long long outL = 0, outH = 0;
     u32 n_out = 0;
+    // the wave's table goes to the centres, and as much leaves c_lo
+    auto empty = [&]() {
+        wave_lds_fence();
+        for (u32 c = c_lo + 1u + lane; c <= c_hi; c += 64u) {
+            const u64 word = mine[c];
+            if (!word) continue;
+            const long long sum = (long long)(word << 16) >> 16;
+            const u32 n = (u32)((word - (u64)sum) >> 48);
+            mine[c] = 0;
+            if (sum) lloyd_file(acc, K, c, sum, pos_lo);
+            atomicAdd(&acc[EXCP_ABSM_BINS * K + c], (u64)n);
+            outL += sum; n_out += n;
+        }
+        wave_lds_fence();
+    };
+    u32 held = 0;                                         // values that may be in the table
 #pragma unroll 1
     for (u32 p = p0; p < p1; p += 256u) {
         float x[4];
@@ -1153,12 +1177,21 @@ __device__ __forceinline__ void lloyd_many(const EXCP_GLOBAL float *part, u32 p0
 #pragma unroll
             for (u32 j = 0; j < 4; ++j) { const u32 c = cl[j] + step; if (c <= c_hi && L.cut[c] <= key_of(x[j])) cl[j] = c; }
         }
+        if (packed) {
+            held += 256u;
+            if (held > 8192u) { empty(); held = 256u; }
+        }
 #pragma unroll
         for (u32 j = 0; j < 4; ++j) {
             if (p + j * 64u + lane >= p1 || cl[j] == c_lo) continue;
             const u32 bits = f2u(x[j]), mb = bits & 0x7fffffffu;
             const u32 e = mb >> 23, pb = bit_pos(mb), mant = (mb & 0x7fffffu) | (e ? 0x800000u : 0u);
             const bool neg = bits >> 31;
+            if (packed) {
+                const u64 term = mant ? (u64)mant << (pb - pos_lo) : 0ull;
+                atomicAdd(&mine[cl[j]], (neg ? (u64)0 - term : term) + (1ull << 48));
+                continue;
+            }
             ++n_out;
             atomicAdd(&acc[EXCP_ABSM_BINS * K + cl[j]], 1ull);
             if (!mant) continue;
@@ -1173,6 +1206,7 @@ __device__ __forceinline__ void lloyd_many(const EXCP_GLOBAL float *part, u32 p0
             }
         }
     }
+    if (packed) empty();
     outL = (long long)wave_sum_u64((u64)outL); outH = (long long)wave_sum_u64((u64)outH);
     n_out = wave_sum_u32(n_out);
     if (lane == 0u && n_out) {
@@ -1184,7 +1218,7 @@ __device__ __forceinline__ void lloyd_many(const EXCP_GLOBAL float *part, u32 p0
 
 // One wave moves the values at places [q0, q1) of the cut buckets on to their centres in `acc` (LDS): the sum and
 // number of the values above a border go from the centre below it to the one above it.
-__device__ __forceinline__ void lloyd_share(const EXCP_GLOBAL float *part, u32 q0, u32 q1, u32 K, u64 *acc, const LloydShared &L) {
+__device__ __forceinline__ void lloyd_share(const EXCP_GLOBAL float *part, u32 q0, u32 q1, u32 K, u64 *acc, u64 *mine, const LloydShared &L) {
     while (q0 < q1) {
         u32 b = 0;                                        // last bucket with off[b] <= q0: it holds place q0
 #pragma unroll 1
@@ -1195,7 +1229,7 @@ __device__ __forceinline__ void lloyd_share(const EXCP_GLOBAL float *part, u32 q
         const u32 r = (u32)__builtin_amdgcn_readfirstlane((int)L.range[b]);
         const u32 c_lo = r & 255u, c_hi = (r >> 8) & 255u, pos_lo = (r >> 16) & 255u, pos_hi = r >> 24;
         q0 = stop;
-        if (c_hi - c_lo > 2u) lloyd_many(part, p0, p1, c_lo, c_hi, pos_lo, pos_hi, K, acc, L);
+        if (c_hi - c_lo > 2u) lloyd_many(part, p0, p1, c_lo, c_hi, pos_lo, pos_hi, K, acc, mine, L);
         else if (pos_hi - pos_lo <= 8u) lloyd_borders<false>(part, p0, p1, c_lo, c_hi - c_lo == 2u, pos_lo, pos_hi, K, acc, L);
         else lloyd_borders<true>(part, p0, p1, c_lo, c_hi - c_lo == 2u, pos_lo, pos_hi, K, acc, L);
     }
@@ -1238,9 +1272,9 @@ __device__ __forceinline__ void lloyd_units(const Workspace &w, const GroupParam
 // One workgroup takes a stream through all its iterations; the final centres and cut keys end in the slots of
 // parity `iters`.  KMAX: the centres the LDS accumulators are laid out for.
 template <u32 KMAX>
-__global__ __launch_bounds__(LLOYD_THREADS, lloyd_per_cu(KMAX)) void k_km_lloyd(Workspace w, GroupParams g) {
+__global__ __launch_bounds__(LLOYD_THREADS, 2u * lloyd_per_cu(KMAX)) void k_km_lloyd(Workspace w, GroupParams g) {
     __shared__ LloydShared L;
-    __shared__ u64 acc[(EXCP_ABSM_BINS + 1u) * KMAX];
+    __shared__ u64 acc[(EXCP_ABSM_BINS + 1u) * KMAX], mine[LLOYD_WAVES][KMAX + 1u];
     if (blockIdx.x == 3u * g.ntensors) { lloyd_units<KMAX>(w, g); return; }
     const u32 sidx = stream_in_turn(w, blockIdx.x), tid = threadIdx.x, wave = tid >> 6, K = (u32)g.K, iters = (u32)g.iters;
     SegState &S = w.seg[sidx];
@@ -1257,7 +1291,7 @@ __global__ __launch_bounds__(LLOYD_THREADS, lloyd_per_cu(KMAX)) void k_km_lloyd(
             lloyd_few(part, 0u, T, K, kp2, acc, L);
         } else {
             const u32 q0 = (u32)(((u64)T * wave) / LLOYD_WAVES), q1 = (u32)(((u64)T * (wave + 1u)) / LLOYD_WAVES);
-            lloyd_share(part, q0, q1, K, acc, L);
+            lloyd_share(part, q0, q1, K, acc, mine[wave], L);
         }
     }
     if (tid < K) S.C[iters & 1u][tid] = L.C[tid];
@@ -1269,9 +1303,9 @@ __global__ __launch_bounds__(LLOYD_THREADS, lloyd_per_cu(KMAX)) void k_km_lloyd(
 // to do).  Every workgroup of a stream computes the centres for itself, adds its share up in LDS, and hands the sums over.
 // The launch after the last iteration (i == iters) only makes the final centres.
 template <u32 KMAX>
-__global__ __launch_bounds__(LLOYD_THREADS, lloyd_per_cu(KMAX)) void k_km_iter(Workspace w, GroupParams g, u32 i) {
+__global__ __launch_bounds__(LLOYD_THREADS, 2u * lloyd_per_cu(KMAX)) void k_km_iter(Workspace w, GroupParams g, u32 i) {
     __shared__ LloydShared L;
-    __shared__ u64 acc[(EXCP_ABSM_BINS + 1u) * KMAX];
+    __shared__ u64 acc[(EXCP_ABSM_BINS + 1u) * KMAX], mine[LLOYD_WAVES][KMAX + 1u];
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, u = blockIdx.x;
     const u32 K = (u32)g.K, nseg = 3u * g.ntensors, accw = (EXCP_ABSM_BINS + 1u) * K;
     if (u >= w.seg_unit_begin[nseg]) return;
@@ -1325,7 +1359,7 @@ __global__ __launch_bounds__(LLOYD_THREADS, lloyd_per_cu(KMAX)) void k_km_iter(W
         lloyd_few(gptr(seg_part(w, sidx)), x0, x1, K, kp2, acc, L);
     } else {
         const u32 q0 = x0 + (u32)(((u64)(x1 - x0) * wave) / LLOYD_WAVES), q1 = x0 + (u32)(((u64)(x1 - x0) * (wave + 1u)) / LLOYD_WAVES);
-        lloyd_share(gptr(seg_part(w, sidx)), q0, q1, K, acc, L);
+        lloyd_share(gptr(seg_part(w, sidx)), q0, q1, K, acc, mine[wave], L);
     }
     __syncthreads();
     u64 *now = gacc + (i % 3u) * accw;
