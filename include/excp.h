@@ -293,8 +293,8 @@ int excp_decompress_step_static(int hip_device, void *hip_stream, const void *W_
                                 uint32_t flags);
 
 /* Per-stage timing.  When enabled, HIP events bracket every kernel stage of the next batches;
- * after excp_collect, excp_stage_ms returns the summed milliseconds of stage `i` and how often it was
- * launched (once per tensor group, whatever the number of kernels it consists of)
+ * after excp_collect, excp_stage_ms returns the summed milliseconds of stage `i` and how many spans of it
+ * were timed (a span may be several kernels: all Lloyd iterations of a group are one)
  * (0 <= i < excp_stage_count()); excp_stage_name names it. */
 int         excp_set_profiling(excp_ctx *ctx, int enabled);
 int         excp_stage_count(void);

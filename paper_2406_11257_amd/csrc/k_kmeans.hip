@@ -866,15 +866,17 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
 // bucket (residuals of a sign-like update, values bunched beside outliers) count eight times from four centres on, since
 // most centres then lie in that bucket, and its values go one by one; of tied data only what is not a repetition of a
 // bucket's first value counts.  A tensor's streams go the same way.  The host launches the iterations of the second
-// way wherever a tensor is too large for excp_lloyd_small (2^17 elements, up to where one workgroup is no slower whatever
-// the values are: 130 000 bunched ones take it 1.1 ms, which the former work lists needed as well); where no stream takes
-// it they are empty, 1.6 us each.
+// way wherever a tensor is too large for excp_lloyd_small; where no stream takes it they are empty, 1.6 us each.  (2^17
+// elements: one workgroup needs 0.43 ms for 130 000 residuals of a sign-like update, the former work lists needed 0.81; 2^22
+// for three centres, of whose borders a bucket holds two at most.)
 //   Up to 85 tensors on 256 compute units the group goes together, beyond 24 576 (one tensor, 4 bits, ten iterations, us
 //   alone / shared: 1 M elements 163 / 178, 1.5 M 186 / 188, 2.5 M 207 / 174, 10 M 340 / 169; 8 bits: 140 000 elements
-//   737 / 346, 2.5 M 1565 / 194; the 14M shape 248 -> 192).  Bunched values, 4 bits: 1 M elements 8095 -> 211, 9 M 74451 -> 543.
+//   737 / 346, 2.5 M 1565 / 194; the 14M shape 248 -> 192).  Bunched values, 4 bits: 1 M elements 8095 -> 201, 9 M 74451 -> 473.
 //   More tensors fill the GPU as they are, one workgroup a stream, and the line lies at 196 608 (300 tensors of 600 000
 //   elements, 4 bits: 338 alone, 522 shared; the 410M shape 440, and 499 with the line at 65 536), from six bits on at
 //   131 072 (the 410M shape in 7 bits 1943, and 2406 with the line at 196 608).
+//   Not in the rule: how the values of a crowded bucket are spread.  A 410M shape of bunched values, all kept, is the one
+//   input met that the former work lists took through these iterations faster (2.0 against 2.7 ms each; the call 116 and 113).
 constexpr u32 LLOYD_THREADS = 512, LLOYD_WAVES = LLOYD_THREADS / 64;
 constexpr u32 LLOYD_FEW = 4 * LLOYD_THREADS;              // up to here a value per thread is quicker than a bucket per wave
 

@@ -42,7 +42,7 @@ def draw(n, seed, kind):
 
 @pytest.mark.parametrize("kind", ["spread", "few values", "half still", "bunched", "missed"])
 def test_median_and_mean_are_exact(ctx, kind):
-    # around one sub-tile, the sample's size, one workgroup's share, one list, two lists, eight lists
+    # around one sub-tile, the sample's size, one workgroup's share, one list, two lists, seven lists
     sizes = [1, 63, 4096, 8191, 8192, 8193, 40961, (1 << 20) - 1, (1 << 21) + 3, 4096 * 2048 - 4095]
     cases = [draw(n, 50 + i, kind) for i, n in enumerate(sizes)]
     print(kind, sizes, flush=True)
