@@ -220,6 +220,16 @@ static __host__ __device__ inline u32 excp_cand_first(u32 workgroup, u32 lists) 
 // (unless their group goes together and has others).
 static inline bool excp_lloyd_small(u64 n, u32 K) { return n <= (K > 3u ? 1ull << 17 : 1ull << 22) && n * (K - 1u) <= (1ull << 24); }
 
+// A work unit of a Lloyd iteration that many workgroups take, in SegState::work: `least`, or so much that the units of
+// `streams` streams with `work` in all -- each has one that is not whole -- are at_once at most, or two a stream.  And
+// the workgroups of a launch, at least as many as there can be units.
+static __host__ __device__ inline u64 excp_lloyd_unit(u64 work, u32 streams, u32 at_once, u32 least) {
+    const u32 spare = at_once - (streams < at_once / 2u ? streams : at_once / 2u), whole = spare > streams ? spare : streams;
+    const u64 fit = work / whole + 1ull;
+    return fit > least ? fit : least;
+}
+static inline u32 excp_lloyd_grid(u32 at_once, u32 slots) { return at_once + 6u * slots; }
+
 void launch_zero_u32(u32 *p, u64 count, hipStream_t s);
 void launch_copy_probe(const void *src, void *dst, u64 bytes, hipStream_t s);
 void launch_stats(const Workspace &w, const GroupParams &g, int phase, hipStream_t s);

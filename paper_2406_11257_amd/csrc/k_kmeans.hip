@@ -1256,9 +1256,7 @@ __device__ __forceinline__ void lloyd_units(const Workspace &w, const GroupParam
     work = 0; streams = 0;
 #pragma unroll
     for (u32 v = 0; v < LLOYD_WAVES; ++v) { work += s_work[v]; streams += s_streams[v]; }
-    // whole units: a stream's last one is extra, so there is room for one a stream
-    const u32 at_once = lloyd_per_cu(KMAX) * (u32)w.cus, whole = max(at_once - min(streams, at_once / 2u), streams);
-    const u64 unit = max((u64)lloyd_unit(KMAX), work / whole + 1u);
+    const u64 unit = excp_lloyd_unit(work, streams, lloyd_per_cu(KMAX) * (u32)w.cus, lloyd_unit(KMAX));
     auto units_of = [&](u32 s) { return (u32)((work_of(s) + unit - 1u) / unit); };
     u32 units = 0;
     for (u32 s = s0; s < s1; ++s) units += units_of(s);
@@ -1631,7 +1629,7 @@ template <u32 KMAX>
 static void launch_lloyd(const Workspace &w, const GroupParams &g, hipStream_t s) {
     hipLaunchKernelGGL(k_km_lloyd<KMAX>, dim3(3 * g.ntensors + (g.slots ? 1 : 0)), dim3(LLOYD_THREADS), 0, s, w, g);
     if (!g.slots) return;
-    const u32 units = excp_grid(w, lloyd_per_cu(KMAX)) + 6 * g.slots;   // (as many as there can be: see lloyd_units)
+    const u32 units = excp_lloyd_grid(excp_grid(w, lloyd_per_cu(KMAX)), g.slots);
     for (u32 i = 0; i <= (u32)g.iters; ++i) hipLaunchKernelGGL(k_km_iter<KMAX>, dim3(units), dim3(LLOYD_THREADS), 0, s, w, g, i);
 }
 void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s) {

@@ -30,6 +30,28 @@ int main() {
         for (u32 j = 0; j < lists; ++j) { least = first[j] < least ? first[j] : least; most = first[j] > most ? first[j] : most; }
         CHECK(least == 64 && most == 64, "%u lists: %u to %u", lists, least, most);
     }
+    // The units of a Lloyd iteration: never more than the launch has workgroups, and one round of them for few streams.
+    u64 seed = 1;
+    auto random = [&]() { seed = seed * 6364136223846793005ull + 1442695040888963407ull; return (u32)(seed >> 33); };
+    for (u32 at_once : {256u, 512u, 304u})
+        for (u32 least : {4096u, 8192u})
+            for (u32 slots : {1u, 2u, 40u, 85u, 86u, 171u, 341u, 1024u})
+                for (u32 shape = 0; shape < 12; ++shape) {
+                    static u32 x[3072];
+                    u64 work = 0, units = 0;
+                    u32 streams = 0;
+                    for (u32 s = 0; s < 3 * slots; ++s) {
+                        const u32 r = random();
+                        x[s] = shape == 0 ? 1u : shape == 1 ? 0xffffffffu : shape == 2 ? (s ? 0u : 0xffffffffu) : shape == 3 ? least + 1u : shape == 4 ? (s ? 1u : 0xffffffffu)
+                               : shape == 5 ? s % 3u == 0u ? 24577u : 0u : r >> (r % 31u);
+                        work += x[s]; streams += x[s] != 0;
+                    }
+                    if (!streams) continue;
+                    const u64 unit = excp_lloyd_unit(work, streams, at_once, least);
+                    for (u32 s = 0; s < 3 * slots; ++s) units += (x[s] + unit - 1) / unit;
+                    CHECK(unit >= least && units >= streams && units <= excp_lloyd_grid(at_once, slots), "%llu units, %u slots, shape %u", units, slots, shape);
+                    CHECK(units <= (2 * streams <= at_once ? at_once : 2u * streams), "%llu units, %u streams, %u at once", units, streams, at_once);
+                }
     if (fails) return 1;
     printf("ok\n");
     return 0;
