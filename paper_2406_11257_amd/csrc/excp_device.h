@@ -9,7 +9,7 @@
 
 #define EXCP_TILE        4096u     // elements per tile of the full-tensor passes (256 threads x 16)
 #define EXCP_CHUNK       8192u     // survivors per chunk of the survivor passes
-#define EXCP_SUPER_CHUNKS 16u      // chunks per unit of the bucket counts (and of the scatter's workgroup ranges)
+#define EXCP_UNIT_SHIFT 17u        // log2 of the largest unit of the bucket counts, in positions of a stream (see excp_unit_shift)
 #define EXCP_THREADS     256
 #define EXCP_SAMPLE_PARTS 16u      // workgroups that draw a tensor's sample of residuals
 #define EXCP_STATS_PER_CU 8u       // workgroups per compute unit of the statistics pass
@@ -78,7 +78,7 @@ struct TState {
 struct SegState {
     u64 len;
     u32 chunk_begin;            // first chunk of this stream in the group's chunk list
-    u32 row_begin;              // first row of this stream in the table of bucket counts (a row per EXCP_SUPER_CHUNKS chunks)
+    u32 row_begin;              // first row of this stream in the table of bucket counts (a row per unit: GroupParams::unit_shift)
     u32 work;                   // what a Lloyd iteration is expected to cost, in values of cut buckets
     u32 pad;
     u32 bin_lo, bin_hi;         // the bins of km_bsum that are not all zero lie in [bin_lo, bin_hi]
@@ -146,7 +146,7 @@ struct GroupParams {
                                 // Lloyd iterations
     u32 together;               // all of the group's tensors go the same way
     u32 slots;                  // tensors with an acc_slot
-    u32 pad;
+    u32 unit_shift;             // log2 of the positions of a stream whose bucket counts share a row
 };
 
 #define EXCP_RAW_BITS    32u       // "code" width of a blob written without quantisation: fp32 values, no codebooks
@@ -181,7 +181,7 @@ struct Workspace {
     u32 *seg_unit_begin;      // [segments + 1] first work unit of every survivor stream in a Lloyd iteration that many workgroups take
     float *pw, *pm, *pv;      // survivors partitioned into value-ordered buckets (same offsets as xw/xm/xv)
     u32 *km_split;            // [segment][EXCP_KM_MAP_WORDS] value -> bucket map: 4 parameters, then 4096 bucket bytes
-    u32 *km_cnt;              // [row][256] bucket counts, then positions: a row per EXCP_SUPER_CHUNKS chunks of a stream
+    u32 *km_cnt;              // [row][256] bucket counts, then positions: a row per unit of a stream (GroupParams::unit_shift)
     u32 *km_begin;            // [segment][257] first position of every bucket
     u64 *km_bsum;             // [segment][EXCP_ABSM_BINS][257] exact signed sum of every bucket, then of all buckets before it
     u32 *km_min, *km_max;     // [segment][256] smallest / largest key of every bucket
@@ -215,6 +215,26 @@ static inline u64 excp_cand_words(u64 group_elems, u32 group_tensors) { return g
 // every fourth list for a start, those filled and the others were found by failing there: 3 M elements 28.6 -> 18.5 us
 // for the pass, 16.8 M 41.2 -> 39.0 and 41.5 -> 37.4 for the select, whose waves share the lists out.)
 static __host__ __device__ inline u32 excp_cand_first(u32 workgroup, u32 lists) { return workgroup % lists; }
+
+// Sub-tiles to a batch of the gather pass: as many as leave four batches to a compute unit, four at least, so that each of a
+// workgroup's waves has one, and EXCP_GATHER_SUBS at most.  (With 32 always, a 16.8 M-element tensor was 256 workgroups of eight
+// round trips each: 51 -> 29 us, and the 14M shape's small tensors 126 -> 35 us.)
+#define EXCP_GATHER_SUBS 32u
+static inline u32 excp_gather_subs(u32 ntiles, u32 cus) {
+    const u32 subs = 2u * ntiles / (4u * cus) & ~3u;
+    return subs < 4u ? 4u : (subs > EXCP_GATHER_SUBS ? EXCP_GATHER_SUBS : subs);
+}
+// Rows that the table of bucket counts has, and log2 of the positions that share a row in a group of `elems` elements:
+// the scatter's workgroups begin at rows, so it is the smallest power of two that leaves one row to a compute unit
+// when half the elements survive in the three streams together (a third of the weights, a tenth of the moments twice),
+// between 2^14 (64 positions to a bucket: below that most of a workgroup's lines are partial ones) and 2^17, not less than a
+// batch of the gather pass can span, and so much that the rows fit the table.
+static inline u64 excp_count_rows(u64 group_elems, u32 group_tensors) { return 3 * (group_elems >> EXCP_UNIT_SHIFT) + 3ull * group_tensors + 4; }
+static inline u32 excp_unit_shift(u64 elems, u32 tensors, u32 subs, u32 cus, u64 rows) {
+    u32 s = 14;
+    while (s < EXCP_UNIT_SHIFT && ((elems >> s) > 4ull * cus || (u64)subs * 2048u > (1ull << s) || 3 * (elems >> s) + 3ull * tensors > rows)) ++s;
+    return s;
+}
 
 // Tensors so small that one workgroup takes their streams through all Lloyd iterations whatever the values are
 // (unless their group goes together and has others).

@@ -361,7 +361,7 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.pm, G);
     ok = ok && dev_alloc(c, &w.pv, G);
     ok = ok && dev_alloc(c, &w.km_split, nseg_max * EXCP_KM_MAP_WORDS);
-    ok = ok && dev_alloc(c, &w.km_cnt, (chunks_group / EXCP_SUPER_CHUNKS + nseg_max + 1) * 256);
+    ok = ok && dev_alloc(c, &w.km_cnt, excp_count_rows(G, kMaxGroupTensors) * 256);
     ok = ok && dev_alloc(c, &w.km_begin, nseg_max * 257);
     ok = ok && dev_alloc(c, &w.km_bsum, nseg_max * 257 * EXCP_ABSM_BINS);
     ok = ok && dev_alloc(c, &w.km_min, nseg_max * 256);
@@ -552,6 +552,9 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             p.alone_work = p.together ? kAloneTogether : (K < 63 ? kAloneFew : kAloneMany);
             for (u32 q = 0; q < g.count; ++q) p.slots += c->h_desc[g.first + q].acc_slot != EXCP_NO_SLOT ? 1u : 0u;
         }
+        u64 elems = 0;
+        for (u32 q = 0; q < g.count; ++q) elems += tensors[g.first + q].n;
+        p.unit_shift = excp_unit_shift(elems, g.count, excp_gather_subs(g.ntiles, (u32)w.cus), (u32)w.cus, excp_count_rows(c->max_group, kMaxGroupTensors));
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
         { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, s); }
         { StageTimer t(c, ST_STATS); launch_stats(w, p, 1, s); }

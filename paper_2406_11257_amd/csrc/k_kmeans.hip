@@ -130,7 +130,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_km_sample(Workspace w, GroupPara
     if (tid < 4) s_ext[tid] = (tid & 1u) ? 0u : 0xffffffffu;
     s_coarse[tid] = at_of(pre[coarse_sub(tid)]);
     {   // the stream's rows of the count table start at zero (the counts are taken by k_mask_gather)
-        const u32 rows = (u32)((len + EXCP_SUPER_CHUNKS * EXCP_CHUNK - 1u) / (EXCP_SUPER_CHUNKS * EXCP_CHUNK));
+        const u32 rows = (u32)((len + (1ull << g.unit_shift) - 1u) >> g.unit_shift);
         u32 *row0 = w.km_cnt + (u64)w.seg[sidx].row_begin * NBKT;
         for (u64 i = tid; i < (u64)rows * NBKT; i += SM_THREADS) row0[i] = 0;
     }
@@ -268,38 +268,50 @@ __device__ __forceinline__ void load_chunk(const EXCP_GLOBAL float *gx, u32 clen
 __device__ __forceinline__ u32 chunk_elem(u32 it) { return ((it >> 2) * EXCP_THREADS + threadIdx.x) * 4u + (it & 3u); }
 
 // ---------------------------------------------------------------- P1, P2: bucket counts, positions
-// The counts are taken by the pass that makes the dense survivor arrays (k_mask_gather), per 16 chunks of a
-// stream, a row each.  One workgroup per stream turns them into positions: bucket totals, their scan, then
-// every row's first position in every bucket.  Thread (q, b) owns bucket b over one quarter of the rows.
-// (The table used to have a row per chunk, fifteen of sixteen of them empty, and took three launches to walk.)
-__global__ __launch_bounds__(1024) void k_km_scan(Workspace w, GroupParams g) {
-    __shared__ u32 tot[4][NBKT], s_wave[4];
-    const u32 sidx = blockIdx.x, tid = threadIdx.x, q = tid >> 8, b = tid & 255u, lane = tid & 63u;
+// The counts are taken by the pass that makes the dense survivor arrays (k_mask_gather), per unit of a
+// stream (2 to 16 chunks, by the size of the group), a row each.  One workgroup per stream turns them into positions:
+// bucket totals, their scan, then every row's first position in every bucket.  A wave reads a row, four buckets to
+// a lane, and owns a sixteenth of the rows; what bounds it is the number of loads that wait for one another.  (With a bucket
+// to a thread and a quarter of the rows each, 354 rows of a 16.8 M-element tensor took 14.4 us.)
+constexpr u32 SCAN_PARTS = 16;
+__global__ __launch_bounds__(SCAN_PARTS * 64) void k_km_scan(Workspace w, GroupParams g) {
+    __shared__ __attribute__((aligned(16))) u32 tot[SCAN_PARTS][NBKT];
+    __shared__ __attribute__((aligned(16))) u32 first[NBKT];
+    __shared__ u32 s_wave[4];
+    typedef u32 u4 __attribute__((ext_vector_type(4)));
+    const u32 sidx = blockIdx.x, tid = threadIdx.x, lane = tid & 63u;
+    const u32 part = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const u64 len = w.seg[sidx].len;
     if (len == 0) return;
-    const u32 rows = (u32)((len + EXCP_SUPER_CHUNKS * EXCP_CHUNK - 1u) / (EXCP_SUPER_CHUNKS * EXCP_CHUNK));
-    const u32 nq = (rows + 3u) / 4u, a0 = min(q * nq, rows), a1 = min(a0 + nq, rows);
-    u32 *cnt = w.km_cnt + (u64)w.seg[sidx].row_begin * NBKT;
-    u32 s = 0;
-#pragma unroll 16
-    for (u32 c = a0; c < a1; ++c) s += cnt[(u64)c * NBKT + b];
-    tot[q][b] = s;
+    const u32 rows = (u32)((len + (1ull << g.unit_shift) - 1u) >> g.unit_shift);
+    const u32 per = (rows + SCAN_PARTS - 1u) / SCAN_PARTS, a0 = min(part * per, rows), a1 = min(a0 + per, rows);
+    EXCP_GLOBAL u4 *cnt = gptr((u4 *)(w.km_cnt + (u64)w.seg[sidx].row_begin * NBKT)) + lane;      // (rows are 1 KB)
+    u4 s = {0u, 0u, 0u, 0u};
+#pragma unroll 8
+    for (u32 c = a0; c < a1; ++c) s += cnt[(u64)c * (NBKT / 4u)];
+    *(u4 *)&tot[part][4u * lane] = s;
     __syncthreads();
-    const u32 total = tot[0][b] + tot[1][b] + tot[2][b] + tot[3][b];
-    u32 incl = wave_incl_scan_u32(total);                                     // (the four quarters scan the same 256 totals)
-    if (q == 0 && lane == 63u) s_wave[b >> 6] = incl;
-    __syncthreads();
-    u32 run = incl - total;
-    for (u32 v = 0; v < (b >> 6); ++v) run += s_wave[v];
-    if (q == 0) {
-        w.km_begin[(u64)sidx * (NBKT + 1) + b] = run;
-        if (b == NBKT - 1u) w.km_begin[(u64)sidx * (NBKT + 1) + NBKT] = run + total;
+    u32 total = 0, incl = 0;
+    if (tid < NBKT) {
+        for (u32 q = 0; q < SCAN_PARTS; ++q) total += tot[q][tid];
+        incl = wave_incl_scan_u32(total);
+        if (lane == 63u) s_wave[part] = incl;
     }
-    for (u32 qq = 0; qq < q; ++qq) run += tot[qq][b];
-#pragma unroll 16
+    __syncthreads();
+    if (tid < NBKT) {
+        u32 run = incl - total;
+        for (u32 v = 0; v < part; ++v) run += s_wave[v];
+        first[tid] = run;
+        w.km_begin[(u64)sidx * (NBKT + 1) + tid] = run;
+        if (tid == NBKT - 1u) w.km_begin[(u64)sidx * (NBKT + 1) + NBKT] = run + total;
+    }
+    __syncthreads();
+    u4 run = *(const u4 *)&first[4u * lane];
+    for (u32 q = 0; q < part; ++q) run += *(const u4 *)&tot[q][4u * lane];
+#pragma unroll 8
     for (u32 c = a0; c < a1; ++c) {
-        const u32 v = cnt[(u64)c * NBKT + b];
-        cnt[(u64)c * NBKT + b] = run;
+        const u4 v = cnt[(u64)c * (NBKT / 4u)];
+        cnt[(u64)c * (NBKT / 4u)] = run;
         run += v;
     }
 }
@@ -333,11 +345,12 @@ __global__ __launch_bounds__(SC_THREADS, 1) void k_km_scatter(Workspace w, Group
     const u32 G = gridDim.x, bid = blockIdx.x;
     const u32 nseg = 3u * g.ntensors;
     // Equal shares of the chunk list, their ends moved back to where the bucket counts were taken: the first
-    // of every 16 chunks of a stream.
+    // chunk of a unit.
+    const u32 unit_chunks = (1u << g.unit_shift) / EXCP_CHUNK;
     auto snapped = [&](u32 c) -> u32 {
         if (c >= total) return total;
         const u32 c0 = w.seg_chunk_begin[find_owner(w.seg_chunk_begin, nseg, c)];
-        return c0 + ((c - c0) & ~(EXCP_SUPER_CHUNKS - 1u));
+        return c0 + ((c - c0) & ~(unit_chunks - 1u));
     };
     const u32 lo = snapped((u32)(((u64)bid * total) / G)), hi = snapped((u32)(((u64)(bid + 1) * total) / G));
     if (lo >= hi) return;
@@ -368,7 +381,7 @@ __global__ __launch_bounds__(SC_THREADS, 1) void k_km_scatter(Workspace w, Group
         };
         if (tid < NBKT) {
             // a ring index is the value's place inside its line, so that whole lines sit in one quarter of the ring
-            const u32 gp = w.km_cnt[(u64)(w.seg[sidx].row_begin + (c - chunk0) / EXCP_SUPER_CHUNKS) * NBKT + tid];
+            const u32 gp = w.km_cnt[(u64)(w.seg[sidx].row_begin + (c - chunk0) / unit_chunks) * NBKT + tid];
             gpos[tid] = gp;
             ctr[tid] = ((gp + misalign) & 31u) << 16;
         }
@@ -1592,7 +1605,7 @@ void launch_km_partition(const Workspace &w, const GroupParams &g, int phase, hi
     const u32 nseg = 3 * g.ntensors;
     switch (phase) {
         case 0: hipLaunchKernelGGL(k_km_sample, dim3(nseg), dim3(SM_THREADS), 0, s, w, g); break;
-        case 1: hipLaunchKernelGGL(k_km_scan, dim3(nseg), dim3(1024), 0, s, w, g); break;
+        case 1: hipLaunchKernelGGL(k_km_scan, dim3(nseg), dim3(SCAN_PARTS * 64), 0, s, w, g); break;
         case 2: hipLaunchKernelGGL(k_km_scatter, dim3(excp_grid(w, 1)), dim3(SC_THREADS), 0, s, w, g); break;
         default:
             if (g.wide == 2u) {

@@ -310,15 +310,11 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_scan(Workspace w, GroupPa
 // look-ups.
 // The same pass counts, for the value partition of the codebook stage, how many of the values it moves
 // fall into each of the 256 value buckets (the map k_km_sample made from the slots): the values are in
-// registers here, and a pass of its own would read them all again.  Counts are kept per 16 chunks
-// (131 072 positions) of a stream, a row each; the scatter's workgroups begin only at such positions.  A workgroup adds up in LDS as long as its batches stay inside one tensor
+// registers here, and a pass of its own would read them all again.  Counts are kept per unit of 2^14 to 2^17
+// positions of a stream (excp_unit_shift), a row each; the scatter's workgroups begin only at such positions.  A workgroup adds up in LDS as long as its batches stay inside one tensor
 // and one such unit per stream, and hands the sums over when that changes.
-// A wave takes its sub-tiles of a batch one after the other, so a batch has as many as leave four batches to a
-// compute unit, and at least one for each of the four waves (with 32 always, a 16.8 M-element tensor was 256
-// workgroups of eight round trips each: 51 -> 29 us, and the 14M shape's small tensors 126 -> 35 us).
-constexpr u32 GATHER_SUBS = 32;                          // most sub-tiles of a batch
-constexpr u32 SUPER_SHIFT = 17;                          // log2 of the positions per counted unit
-static_assert((1u << SUPER_SHIFT) == EXCP_SUPER_CHUNKS * EXCP_CHUNK, "counted unit = EXCP_SUPER_CHUNKS chunks");
+// A wave takes its sub-tiles of a batch one after the other (how many a batch has: excp_gather_subs).
+constexpr u32 GATHER_SUBS = EXCP_GATHER_SUBS;
 
 __global__ __launch_bounds__(EXCP_THREADS) void k_mask_gather(Workspace w, GroupParams g, u32 subs) {
     __shared__ u32 s_tiles[EXCP_MAX_GROUP_TENSORS + 1];
@@ -375,7 +371,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_gather(Workspace w, Group
         const bool one_tensor = t0 == s_t[nvalid - 1u];
         if (counting) {
             if (one_tensor) {
-                const u32 sc[3] = {s_pw[0] >> SUPER_SHIFT, s_po[0] >> SUPER_SHIFT, s_po[0] >> SUPER_SHIFT};
+                const u32 sc[3] = {s_pw[0] >> g.unit_shift, s_po[0] >> g.unit_shift, s_po[0] >> g.unit_shift};
                 if (t0 != cur_t || sc[0] != cur_sc[0] || sc[1] != cur_sc[1]) {
                     flush();
                     if (t0 != cur_t) {
@@ -430,9 +426,9 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_gather(Workspace w, Group
             }
             auto count = [&](u32 k, float x, u32 place) {
                 if (in_lds) {
-                    if (live[k]) atomicAdd(&s_hist[k][(place >> SUPER_SHIFT) != cur_sc[k] ? 1u : 0u][((const unsigned char *)(s_map[k] + 4))[cell_of(x, par[k])]], 1u);
+                    if (live[k]) atomicAdd(&s_hist[k][(place >> g.unit_shift) != cur_sc[k] ? 1u : 0u][((const unsigned char *)(s_map[k] + 4))[cell_of(x, par[k])]], 1u);
                 } else if (g_live[k]) {
-                    const u32 row = g_row[k] + (place >> SUPER_SHIFT);
+                    const u32 row = g_row[k] + (place >> g.unit_shift);
                     atomicAdd(&w.km_cnt[(u64)row * 256u + g_cells[k][cell_of(x, g_par[k])]], 1u);
                 }
             };
@@ -569,6 +565,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_layout(Workspace w, GroupParam
     const u32 nseg = 3u * g.ntensors;
     const u32 per = (nseg + EXCP_THREADS - 1) / EXCP_THREADS;
     u32 local[2] = {0u, 0u};                              // chunks, rows of the count table
+    const u32 unit_chunks = (1u << g.unit_shift) / EXCP_CHUNK;
     for (u32 q = 0; q < per; ++q) {
         u32 sidx = tid * per + q;
         if (sidx >= nseg) break;
@@ -607,7 +604,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_layout(Workspace w, GroupParam
         w.seg[sidx].len = len;
         const u32 chunks = (u32)((len + EXCP_CHUNK - 1) / EXCP_CHUNK);
         local[0] += chunks;
-        local[1] += (chunks + EXCP_SUPER_CHUNKS - 1u) / EXCP_SUPER_CHUNKS;
+        local[1] += (chunks + unit_chunks - 1u) / unit_chunks;
     }
     u32 run[2], total[2];
 #pragma unroll
@@ -630,7 +627,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_layout(Workspace w, GroupParam
         w.seg[sidx].row_begin = run[1];
         const u32 chunks = (u32)((w.seg[sidx].len + EXCP_CHUNK - 1) / EXCP_CHUNK);
         run[0] += chunks;
-        run[1] += (chunks + EXCP_SUPER_CHUNKS - 1u) / EXCP_SUPER_CHUNKS;
+        run[1] += (chunks + unit_chunks - 1u) / unit_chunks;
     }
     if (tid == EXCP_THREADS - 1) { seg_chunk_begin[nseg] = total[0]; *w.chunk_total = total[0]; *w.lloyd_shared = 0u; }
 }
@@ -652,7 +649,7 @@ void launch_mask_compact(const Workspace &w, const GroupParams &g, int phase, hi
         hipLaunchKernelGGL(k_mask_scan_parts, dim3(g.ntensors * MSCAN_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
         hipLaunchKernelGGL(k_mask_scan, dim3(g.ntensors * MSCAN_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
     } else {
-        const u32 subs = std::min(std::max(nsub / excp_grid(w, 4) & ~3u, 4u), GATHER_SUBS);
+        const u32 subs = excp_gather_subs(g.ntiles, (u32)w.cus);
         u32 grid = (nsub + subs - 1u) / subs;
         if (grid > excp_grid(w, 48)) grid = excp_grid(w, 48);
         hipLaunchKernelGGL(k_mask_gather, dim3(grid), dim3(EXCP_THREADS), 0, s, w, g, subs);
