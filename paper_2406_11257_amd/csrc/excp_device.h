@@ -80,7 +80,7 @@ struct SegState {
     u32 chunk_begin;            // first chunk of this stream in the group's chunk list
     u32 row_begin;              // first row of this stream in the table of bucket counts (a row per unit: GroupParams::unit_shift)
     u32 work;                   // what a Lloyd iteration is expected to cost, in values of cut buckets
-    u32 pad;
+    u32 crowded;                // a bucket holds far more than its share of the values
     u32 bin_lo, bin_hi;         // the bins of km_bsum that are not all zero lie in [bin_lo, bin_hi]
     u32 acc_lo, acc_hi;         // sums of any of the stream's values have no other bins than [acc_lo, acc_hi]
     // centres (K used) and cut keys (cut[k], 1 <= k < K: smallest key whose nearest centre has index >= k) by the
@@ -147,6 +147,8 @@ struct GroupParams {
     u32 together;               // all of the group's tensors go the same way
     u32 slots;                  // tensors with an acc_slot
     u32 unit_shift;             // log2 of the positions of a stream whose bucket counts share a row
+    u32 fine;                   // the first `fine` tensors in order of size have cells inside their buckets (k_km_cells)
+    u32 fine_size;              // ... by the workgroups of size 0, 1 or 2
 };
 
 #define EXCP_RAW_BITS    32u       // "code" width of a blob written without quantisation: fp32 values, no codebooks
@@ -187,6 +189,10 @@ struct Workspace {
     u32 *km_min, *km_max;     // [segment][256] smallest / largest key of every bucket
     u32 *km_dom, *km_less;    // [segment][256] repetitions of every bucket's first value, values below it (sixteen-wave form only)
     u32 *km_mag;              // [segment][256] smallest non-zero magnitude (bit pattern) of every bucket
+    u32 *km_fine;             // [segment][256] the cells inside every bucket (see k_km_cells); 0: none
+    u32 *fine_begin;          // [which][fine_stride] first value of every cell, counted from its bucket's first
+    u64 *fine_above;          // [which][fine_stride] exact sum of the bucket's values in higher cells
+    u64 fine_stride;
     u64 *km_acc;              // [TDesc::acc_slot][stream][3][EXCP_ABSM_BINS + 1][K] per-centre exact sum and count, by iteration modulo 3
     double *part_obj;         // [chunk]
     // decode
@@ -236,6 +242,29 @@ static inline u32 excp_unit_shift(u64 elems, u32 tensors, u32 subs, u32 cus, u64
     return s;
 }
 
+// Cells inside a bucket of 256 values or more: the largest power of two that leaves them 64 values each on average, 512
+// at most.  A bucket's entries in the tables begin at (its tensor's elem_off >> 6) + 258 x tensor + (its first
+// position >> 6) + its number, and are one more than its cells, so no two buckets' overlap.
+#define EXCP_FINE_SHIFT 6u
+static inline u64 excp_fine_words(u64 group_elems, u32 group_tensors) { return (group_elems >> EXCP_FINE_SHIFT) + 258ull * group_tensors + 1; }
+static __host__ __device__ inline u64 excp_fine_at(u64 elem_off, u32 tensor, u32 position, u32 bucket) {
+    return (elem_off >> EXCP_FINE_SHIFT) + 258ull * tensor + (position >> EXCP_FINE_SHIFT) + bucket;
+}
+static __host__ __device__ inline u32 excp_fine_cells_log2(u32 size) {
+    u32 k = 0;
+    while (k < 9u && (size >> (EXCP_FINE_SHIFT + 1u) >> k)) ++k;
+    return k;
+}
+// Tensors whose buckets may be worth cells (2^17 is a power of two because the host lists the tensors by powers of two), and
+// the largest ones whose buckets, a third of the values kept, nearly all fit a workgroup of k_km_cells in its three sizes.
+// A group of more elements in all goes without cells: 2 to 4 us a million elements are then more than the 125 us that the
+// iterations and initial centres gain (40 tensors of 600 000: totals and cells 112 instead of 34 us, iterations 57 instead
+// of 151; 80 of 3 M: 1081 and 149, 64 and 253).  So does one of 16-bit weights, whose few distinct residuals are shared in any case.
+static __host__ __device__ inline bool excp_fine_tensor(u64 n) { return n >= 1ull << 17; }
+#define EXCP_FINE_SMALL (1ull << 21)
+#define EXCP_FINE_MIDDLE (9ull << 21)
+#define EXCP_FINE_LARGEST (25ull << 20)
+
 // Tensors so small that one workgroup takes their streams through all Lloyd iterations whatever the values are
 // (unless their group goes together and has others).
 static inline bool excp_lloyd_small(u64 n, u32 K) { return n <= (K > 3u ? 1ull << 17 : 1ull << 22) && n * (K - 1u) <= (1ull << 24); }
@@ -256,8 +285,11 @@ void launch_stats(const Workspace &w, const GroupParams &g, int phase, hipStream
 void launch_mask_compact(const Workspace &w, const GroupParams &g, int phase, hipStream_t s);
 void launch_layout(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_km_partition(const Workspace &w, const GroupParams &g, int phase, hipStream_t s);
+void launch_km_cells(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s);
-void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s);
+// A stream of the context's own beside the caller's, and the events that order the two.
+struct SideStream { hipStream_t stream; hipEvent_t fork, join; };
+void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s, const SideStream &side);
 void launch_assign_pack(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_finalize(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_decode_from_compress(const Workspace &w, const GroupParams &g, hipStream_t s);

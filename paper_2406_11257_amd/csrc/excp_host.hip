@@ -19,7 +19,7 @@ constexpr u32 kMaxGroupTensors = 1024;   // tensors processed together (== EXCP_
 constexpr u32 kMaxBatchTensors = 4096;   // tensors per compress / decompress call
 constexpr u64 kAccSegCentres = 3ull * kMaxGroupTensors * 85;   // streams x centres whose accumulators the workspace holds
 // GroupParams::alone_work (see the Lloyd iterations in k_kmeans.hip): groups that go together; others, by the number of centres.
-constexpr u32 kAloneTogether = 24576, kAloneFew = 196608, kAloneMany = 131072;
+constexpr u32 kAloneTogether = 24576, kAloneCells = 98304, kAloneFew = 196608, kAloneMany = 131072;
 constexpr u64 kNoLimit = ~0ull;
 
 enum Stage {
@@ -43,6 +43,7 @@ constexpr size_t kEventPool = 8192;      // events made by excp_set_profiling: 4
 struct excp_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
+    SideStream side{nullptr, nullptr, nullptr};
     u64 max_tensor = 0, max_group = 0, max_tiles = 0;
     Workspace w{};
     // per-batch arrays (device) and their pinned staging (host)
@@ -109,6 +110,7 @@ struct StageTimer {
 // no further work: what state the device tables are in is unknown.
 int enqueue_failed(excp_ctx *c) {
     (void)hipStreamSynchronize(c->stream);
+    (void)hipStreamSynchronize(c->side.stream);
     (void)hipGetLastError();
     for (auto &sp : c->spans) { c->free_events.push_back(sp.a); c->free_events.push_back(sp.b); }
     c->spans.clear();
@@ -369,6 +371,10 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.km_mag, nseg_max * 256);
     ok = ok && dev_alloc(c, &w.km_dom, nseg_max * 256);
     ok = ok && dev_alloc(c, &w.km_less, nseg_max * 256);
+    ok = ok && dev_alloc(c, &w.km_fine, nseg_max * 256);
+    w.fine_stride = excp_fine_words(G, kMaxGroupTensors);
+    ok = ok && dev_alloc(c, &w.fine_begin, 3 * w.fine_stride);
+    ok = ok && dev_alloc(c, &w.fine_above, 3 * w.fine_stride);
     ok = ok && dev_alloc(c, &w.km_acc, acc_words);
     ok = ok && dev_alloc(c, &w.part_obj, chunks_group);
     // per-tile survivor counts of decode; a chain reconstruction keeps those of all its checkpoints
@@ -389,6 +395,9 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
         ok = hipGetDeviceProperties(&prop, hip_device) == hipSuccess && prop.multiProcessorCount > 0;
         w.cus = ok ? prop.multiProcessorCount : 0;
     }
+    ok = ok && hipStreamCreateWithFlags(&c->side.stream, hipStreamNonBlocking) == hipSuccess &&
+         hipEventCreateWithFlags(&c->side.fork, hipEventDisableTiming) == hipSuccess &&
+         hipEventCreateWithFlags(&c->side.join, hipEventDisableTiming) == hipSuccess;
     ok = ok && dev_alloc(c, &w.stat_part, 2ull * excp_grid(w, EXCP_STATS_PER_CU));
     if (ok) {
         launch_zero_u32(w.med_hist, (u64)kMaxGroupTensors * 2048, c->stream);
@@ -404,6 +413,9 @@ void excp_destroy(excp_ctx *c) {
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
+    if (c->side.stream) { (void)hipStreamSynchronize(c->side.stream); (void)hipStreamDestroy(c->side.stream); }
+    if (c->side.fork) (void)hipEventDestroy(c->side.fork);
+    if (c->side.join) (void)hipEventDestroy(c->side.join);
     for (void *p : c->allocs) (void)hipFree(p);
     if (c->h_desc) (void)hipHostFree(c->h_desc);
     if (c->h_ddesc) (void)hipHostFree(c->h_ddesc);
@@ -545,16 +557,17 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         GroupParams p{};
         p.alpha = alpha; p.beta = beta; p.nbits = nbits; p.K = K; p.iters = lloyd_iters; p.flags = flags;
         p.ntensors = g.count; p.ntiles = g.ntiles;
-        u64 largest = 0;
-        for (u32 q = 0; q < g.count; ++q) largest = std::max<u64>(largest, tensors[g.first + q].n);
+        u64 largest = 0, elems = 0;
+        for (u32 q = 0; q < g.count; ++q) { largest = std::max<u64>(largest, tensors[g.first + q].n); elems += tensors[g.first + q].n; }
+        const bool w16 = (flags & 0x30u) != 0;
         if (!raw) {
             p.together = lloyd_together(g) ? 1u : 0u;
-            p.alone_work = p.together ? kAloneTogether : (K < 63 ? kAloneFew : kAloneMany);
+            for (u32 q = 0; q < g.count; ++q) p.fine += p.together && !w16 && elems <= EXCP_FINE_LARGEST && excp_fine_tensor(tensors[g.first + q].n) ? 1u : 0u;
+            p.alone_work = p.fine ? kAloneCells : (p.together ? kAloneTogether : (K < 63 ? kAloneFew : kAloneMany));
             for (u32 q = 0; q < g.count; ++q) p.slots += c->h_desc[g.first + q].acc_slot != EXCP_NO_SLOT ? 1u : 0u;
         }
-        u64 elems = 0;
-        for (u32 q = 0; q < g.count; ++q) elems += tensors[g.first + q].n;
         p.unit_shift = excp_unit_shift(elems, g.count, excp_gather_subs(g.ntiles, (u32)w.cus), (u32)w.cus, excp_count_rows(c->max_group, kMaxGroupTensors));
+        p.fine_size = largest <= EXCP_FINE_SMALL ? 0u : (largest <= EXCP_FINE_MIDDLE ? 1u : 2u);
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
         { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, s); }
         { StageTimer t(c, ST_STATS); launch_stats(w, p, 1, s); }
@@ -571,9 +584,9 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         } else {
             { StageTimer t(c, ST_KM_SCAN); launch_km_partition(w, p, 1, s); }
             { StageTimer t(c, ST_KM_SCATTER); launch_km_partition(w, p, 2, s); }
-            { StageTimer t(c, ST_KM_BUCKET_STATS); launch_km_partition(w, p, 3, s); }
+            { StageTimer t(c, ST_KM_BUCKET_STATS); launch_km_partition(w, p, 3, s); launch_km_cells(w, p, s); }
             { StageTimer t(c, ST_KM_INIT); launch_km_init(w, p, s); }
-            { StageTimer t(c, ST_KM_ITER); launch_km_iter(w, p, s); }
+            { StageTimer t(c, ST_KM_ITER); launch_km_iter(w, p, s, c->side); }
             { StageTimer t(c, ST_ASSIGN_PACK); launch_assign_pack(w, p, s); }
         }
         { StageTimer t(c, ST_FINALIZE); launch_finalize(w, p, s); }

@@ -201,13 +201,11 @@ __device__ __forceinline__ float val_of(u32 k) {
 // the bisection goes on from what the probes have proved.  Threads 1..K-1 of the workgroup each find one;
 // entries from K up to 255 are set to 0xffffffff.  C and cut are LDS arrays of 256 entries; the caller
 // synchronises before and after.
-__device__ __forceinline__ void compute_cut_keys(const float *C, int K, u32 *cut) {
-    const u32 k = threadIdx.x;
-    if (k == 0 || k > 255u) return;
+__device__ __forceinline__ u32 cut_key(const float *C, u32 K, u32 k) {
     u32 res = 0xffffffffu;
     u32 j = k;
-    while (j < (u32)K && !(C[j - 1u] < C[j])) ++j;
-    if (j < (u32)K) {
+    while (j < K && !(C[j - 1u] < C[j])) ++j;
+    if (j < K) {
         const double a = (double)C[j - 1u], b = (double)C[j];
         auto reaches = [&](u32 key) { const double x = (double)val_of(key); return fabs(b - x) < fabs(x - a); };
         u32 lo = key_of(C[j - 1u]) + 1u, hi = key_of(C[j]);               // invariant: hi reaches, nothing below lo does
@@ -226,7 +224,12 @@ __device__ __forceinline__ void compute_cut_keys(const float *C, int K, u32 *cut
         }
         res = hi;
     }
-    cut[k] = res;
+    return res;
+}
+__device__ __forceinline__ void compute_cut_keys(const float *C, int K, u32 *cut) {
+    const u32 k = threadIdx.x;
+    if (k == 0 || k > 255u) return;
+    cut[k] = cut_key(C, (u32)K, k);
 }
 
 // Number of cut keys <= key, i.e. the index of the nearest centre.  kp2 = smallest power of two >= K.

@@ -28,7 +28,9 @@
 namespace {
 
 constexpr u32 NBKT = 256;
-constexpr u32 SAMPLE = 8192;
+// Samples of a stream: 32 to a bucket, whose sizes then differ by 18 %, or 64 and 12 % where buckets are cut into cells (of 25 M
+// elements a few did not fit the workgroups otherwise).
+__device__ __forceinline__ u32 sample_size(const GroupParams &g) { return g.fine ? 16384u : 8192u; }
 constexpr u32 PER_THREAD = EXCP_CHUNK / EXCP_THREADS;   // 32
 
 __device__ __forceinline__ const float *seg_data(const Workspace &w, u32 sidx) {
@@ -98,94 +100,111 @@ __device__ __forceinline__ void window_range(u32 B, u32 &lo, u32 &span) {
 }
 
 // ---------------------------------------------------------------- P0: value -> bucket map from a sample
-// One workgroup per stream.  The sample fixes the magnitude range of each sign (hence offset and
-// shift of the cells); the cells' sample counts, scanned, give every cell its bucket so that the
-// buckets hold about equal shares of the sample.
-// 1024 threads, eight samples each: the kernel is one chain of dependent look-ups per sample, so what counts is how
-// many of them are in flight (256 threads with four rounds of eight: 97 us for a 16.8 M-element tensor).
-constexpr u32 SM_THREADS = 1024, SM_COARSE = 1024;
+// The sample is drawn by sixteen workgroups per stream: a survivor's address is a chain of look-ups, each of its own cache
+// line, and one compute unit takes about a line a cycle.  (One workgroup that did all: 32 us for a 16.8 M-element tensor.)
+// The stream is read where the mask pass left it, in the sub-tile slots (the dense copy is made
+// afterwards, by the pass that also counts the buckets this map defines): survivor p of the stream
+// sits in the sub-tile whose scanned count is the last one <= p.  The samples lie in the array that the dense copy
+// will take, which has room for them: a stream has no fewer places than values.
+constexpr u32 DRAW_PARTS = 16;
+__device__ __forceinline__ float *seg_sample(const Workspace &w, u32 sidx) { return const_cast<float *>(seg_data(w, sidx)); }
 
-__global__ __launch_bounds__(SM_THREADS) void k_km_sample(Workspace w, GroupParams g) {
-    __shared__ float smp[SAMPLE];
-    __shared__ u32 cnt[EXCP_KM_CELLS];
-    __shared__ u32 s_coarse[SM_COARSE];
-    __shared__ u32 s_map[4];
-    __shared__ u32 s_ext[4];                       // min / max magnitude of the negative, of the positive samples
-    __shared__ u32 s_wave[SM_THREADS / 64];
-    constexpr u32 PER_S = SAMPLE / SM_THREADS;
-    const u32 sidx = blockIdx.x, tid = threadIdx.x;
+template <u32 DRAW_PER>                                    // samples of a thread
+__global__ __launch_bounds__(EXCP_THREADS) void k_km_draw(Workspace w, GroupParams g) {
+    constexpr u32 COARSE = 256;
+    __shared__ u32 s_coarse[COARSE];
+    const u32 sidx = blockIdx.x / DRAW_PARTS, part = blockIdx.x % DRAW_PARTS, tid = threadIdx.x;
     const u64 len = w.seg[sidx].len;
-    if (len == 0) return;
-    // The stream is read where the mask pass left it, in the sub-tile slots (the dense copy is made
-    // afterwards, by the pass that also counts the buckets this map defines): survivor p of the stream
-    // sits in the sub-tile whose scanned count is the last one <= p.  Every (nsub / 1024)-th scanned count
-    // is fetched first, side by side; a search then takes ten steps in LDS and only the rest in memory.
+    const u32 ns = (u32)min(len, (u64)sample_size(g));
+    {   // the stream's rows of the count table start at zero (the counts are taken by k_mask_gather)
+        const u32 rows = (u32)((len + (1ull << g.unit_shift) - 1u) >> g.unit_shift);
+        u32 *row0 = w.km_cnt + (u64)w.seg[sidx].row_begin * NBKT;
+        for (u64 i = part * EXCP_THREADS + tid; i < (u64)rows * NBKT; i += DRAW_PARTS * EXCP_THREADS) row0[i] = 0;
+    }
+    const u32 i0 = (u32)(((u64)ns * part) / DRAW_PARTS), i1 = (u32)(((u64)ns * (part + 1u)) / DRAW_PARTS);
+    if (i0 >= i1) return;
     const u32 ts = sidx / 3u, which = sidx % 3u;
     const u32 sub_first = 2u * w.tile_begin[ts], nsub = 2u * w.tile_begin[ts + 1u] - sub_first;
     const u64 *pre = w.mask_prefix + sub_first;
     const float *__restrict__ slots = (which == 0 ? w.pw : (which == 1 ? w.pm : w.pv)) + w.desc[ts].elem_off;
     auto at_of = [&](u64 packed) { return which == 0 ? (u32)(packed >> 32) : (u32)packed; };
-    auto coarse_sub = [&](u32 k) { return (u32)(((u64)k * nsub) / SM_COARSE); };
-    const u32 ns = len < SAMPLE ? (u32)len : SAMPLE;
-    if (tid < 4) s_ext[tid] = (tid & 1u) ? 0u : 0xffffffffu;
+    // every (nsub / 256)-th scanned count is fetched first; a search then takes eight steps in LDS and only the rest in memory
+    auto coarse_sub = [&](u32 k) { return (u32)(((u64)k * nsub) / COARSE); };
     s_coarse[tid] = at_of(pre[coarse_sub(tid)]);
-    {   // the stream's rows of the count table start at zero (the counts are taken by k_mask_gather)
-        const u32 rows = (u32)((len + (1ull << g.unit_shift) - 1u) >> g.unit_shift);
-        u32 *row0 = w.km_cnt + (u64)w.seg[sidx].row_begin * NBKT;
-        for (u64 i = tid; i < (u64)rows * NBKT; i += SM_THREADS) row0[i] = 0;
-    }
-    for (u32 c = tid; c < EXCP_KM_CELLS; c += SM_THREADS) cnt[c] = 0;
     __syncthreads();
-    u32 mn[2] = {0xffffffffu, 0xffffffffu}, mx[2] = {0u, 0u};
-    {
-        u32 pos[PER_S], lo[PER_S], hi[PER_S];
+    u32 pos[DRAW_PER], lo[DRAW_PER], hi[DRAW_PER];
 #pragma unroll
-        for (u32 k = 0; k < PER_S; ++k) {
-            const u32 i = min(tid + k * SM_THREADS, ns - 1u);
-            pos[k] = (u32)(((u64)i * len) / ns);
-            lo[k] = 0;
-        }
+    for (u32 k = 0; k < DRAW_PER; ++k) {
+        const u32 i = min(i0 + tid + k * EXCP_THREADS, i1 - 1u);
+        pos[k] = (u32)(((u64)i * len) / ns);
+        lo[k] = 0;
+    }
 #pragma unroll
-        for (u32 step = SM_COARSE / 2; step >= 1u; step >>= 1) {
+    for (u32 step = COARSE / 2; step >= 1u; step >>= 1) {
 #pragma unroll
-            for (u32 k = 0; k < PER_S; ++k) if (s_coarse[lo[k] + step] <= pos[k]) lo[k] += step;
-        }
+        for (u32 k = 0; k < DRAW_PER; ++k) if (s_coarse[lo[k] + step] <= pos[k]) lo[k] += step;
+    }
 #pragma unroll
-        for (u32 k = 0; k < PER_S; ++k) {               // invariant: prefix(lo) <= pos < prefix(hi)
-            hi[k] = lo[k] + 1u < SM_COARSE ? max(coarse_sub(lo[k] + 1u), coarse_sub(lo[k]) + 1u) : nsub;
-            lo[k] = coarse_sub(lo[k]);
-        }
-        bool more = true;
-        while (more) {
-            more = false;
-            u32 mid[PER_S];
-            u64 pv[PER_S];
+    for (u32 k = 0; k < DRAW_PER; ++k) {            // invariant: prefix(lo) <= pos < prefix(hi)
+        hi[k] = lo[k] + 1u < COARSE ? max(coarse_sub(lo[k] + 1u), coarse_sub(lo[k]) + 1u) : nsub;
+        lo[k] = coarse_sub(lo[k]);
+    }
+    bool more = true;
+    while (more) {
+        more = false;
+        u32 mid[DRAW_PER];
+        u64 pv[DRAW_PER];
 #pragma unroll
-            for (u32 k = 0; k < PER_S; ++k) { mid[k] = (lo[k] + hi[k]) >> 1; pv[k] = hi[k] - lo[k] > 1u ? pre[mid[k]] : 0ull; }
+        for (u32 k = 0; k < DRAW_PER; ++k) { mid[k] = (lo[k] + hi[k]) >> 1; pv[k] = hi[k] - lo[k] > 1u ? pre[mid[k]] : 0ull; }
 #pragma unroll
-            for (u32 k = 0; k < PER_S; ++k) {
-                if (hi[k] - lo[k] > 1u) {
-                    if (at_of(pv[k]) <= pos[k]) lo[k] = mid[k]; else hi[k] = mid[k];
-                    more = more || hi[k] - lo[k] > 1u;
-                }
-            }
-        }
-        u32 at[PER_S];
-#pragma unroll
-        for (u32 k = 0; k < PER_S; ++k) at[k] = at_of(pre[lo[k]]);
-        float v[PER_S];
-#pragma unroll
-        for (u32 k = 0; k < PER_S; ++k) v[k] = slots[(u64)lo[k] * 2048u + (pos[k] - at[k])];
-#pragma unroll
-        for (u32 k = 0; k < PER_S; ++k) {
-            const u32 i = tid + k * SM_THREADS;
-            if (i < ns) {
-                smp[i] = v[k];
-                const u32 bits = f2u(v[k]), a = bits & 0x7fffffffu, sg = bits >> 31;
-                if (sg) { mn[0] = min(mn[0], a); mx[0] = max(mx[0], a); } else { mn[1] = min(mn[1], a); mx[1] = max(mx[1], a); }
+        for (u32 k = 0; k < DRAW_PER; ++k) {
+            if (hi[k] - lo[k] > 1u) {
+                if (at_of(pv[k]) <= pos[k]) lo[k] = mid[k]; else hi[k] = mid[k];
+                more = more || hi[k] - lo[k] > 1u;
             }
         }
     }
+    u32 at[DRAW_PER];
+#pragma unroll
+    for (u32 k = 0; k < DRAW_PER; ++k) at[k] = at_of(pre[lo[k]]);
+    float *smp = seg_sample(w, sidx);
+#pragma unroll
+    for (u32 k = 0; k < DRAW_PER; ++k) {
+        const float x = slots[(u64)lo[k] * 2048u + (pos[k] - at[k])];
+        if (i0 + tid + k * EXCP_THREADS < i1) smp[i0 + tid + k * EXCP_THREADS] = x;
+    }
+}
+
+// One workgroup per stream.  The sample fixes the magnitude range of each sign (hence offset and
+// shift of the cells); the cells' sample counts, scanned, give every cell its bucket so that the
+// buckets hold about equal shares of the sample.
+constexpr u32 SM_THREADS = 1024;
+
+__global__ __launch_bounds__(SM_THREADS) void k_km_sample(Workspace w, GroupParams g) {
+    __shared__ u32 cnt[EXCP_KM_CELLS];
+    __shared__ u32 s_map[4];
+    __shared__ u32 s_ext[4];                       // min / max magnitude of the negative, of the positive samples
+    __shared__ u32 s_wave[SM_THREADS / 64];
+    constexpr u32 PER_S = 16384 / SM_THREADS;
+    const u32 sidx = blockIdx.x, tid = threadIdx.x;
+    const u64 len = w.seg[sidx].len;
+    if (len == 0) return;
+    const u32 ns = (u32)min(len, (u64)sample_size(g));
+    const float *smp = seg_sample(w, sidx);
+    if (tid < 4) s_ext[tid] = (tid & 1u) ? 0u : 0xffffffffu;
+    for (u32 c = tid; c < EXCP_KM_CELLS; c += SM_THREADS) cnt[c] = 0;
+    float v[PER_S];
+#pragma unroll
+    for (u32 k = 0; k < PER_S; ++k) v[k] = tid + k * SM_THREADS < ns ? smp[tid + k * SM_THREADS] : 0.f;
+    u32 mn[2] = {0xffffffffu, 0xffffffffu}, mx[2] = {0u, 0u};
+#pragma unroll
+    for (u32 k = 0; k < PER_S; ++k) {
+        if (tid + k * SM_THREADS < ns) {
+            const u32 bits = f2u(v[k]), a = bits & 0x7fffffffu, sg = bits >> 31;
+            if (sg) { mn[0] = min(mn[0], a); mx[0] = max(mx[0], a); } else { mn[1] = min(mn[1], a); mx[1] = max(mx[1], a); }
+        }
+    }
+    __syncthreads();
 #pragma unroll
     for (int sg = 0; sg < 2; ++sg) {
         const u32 lo = wave_min_u32(mn[sg]), hi = wave_max_u32(mx[sg]);
@@ -204,7 +223,8 @@ __global__ __launch_bounds__(SM_THREADS) void k_km_sample(Workspace w, GroupPara
         s_map[2 * tid] = amin; s_map[2 * tid + 1] = sh;
     }
     __syncthreads();
-    for (u32 i = tid; i < ns; i += SM_THREADS) atomicAdd(&cnt[cell_of(smp[i], s_map)], 1u);
+#pragma unroll
+    for (u32 k = 0; k < PER_S; ++k) if (tid + k * SM_THREADS < ns) atomicAdd(&cnt[cell_of(v[k], s_map)], 1u);
     __syncthreads();
     // Exclusive scan over the cells (four consecutive cells per thread), then bucket = share of the sample
     // below.  A cell that alone holds more than 1/64 of the sample is a tied value (a continuous
@@ -277,7 +297,7 @@ constexpr u32 SCAN_PARTS = 16;
 __global__ __launch_bounds__(SCAN_PARTS * 64) void k_km_scan(Workspace w, GroupParams g) {
     __shared__ __attribute__((aligned(16))) u32 tot[SCAN_PARTS][NBKT];
     __shared__ __attribute__((aligned(16))) u32 first[NBKT];
-    __shared__ u32 s_wave[4];
+    __shared__ u32 s_wave[4], s_most[4];
     typedef u32 u4 __attribute__((ext_vector_type(4)));
     const u32 sidx = blockIdx.x, tid = threadIdx.x, lane = tid & 63u;
     const u32 part = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
@@ -295,9 +315,11 @@ __global__ __launch_bounds__(SCAN_PARTS * 64) void k_km_scan(Workspace w, GroupP
     if (tid < NBKT) {
         for (u32 q = 0; q < SCAN_PARTS; ++q) total += tot[q][tid];
         incl = wave_incl_scan_u32(total);
-        if (lane == 63u) s_wave[part] = incl;
+        const u32 most = wave_max_u32(total);
+        if (lane == 63u) { s_wave[part] = incl; s_most[part] = most; }
     }
     __syncthreads();
+    if (tid == 0) w.seg[sidx].crowded = (u64)max(max(s_most[0], s_most[1]), max(s_most[2], s_most[3])) > 3ull * (len / NBKT) + 1024ull ? 1u : 0u;
     if (tid < NBKT) {
         u32 run = incl - total;
         for (u32 v = 0; v < part; ++v) run += s_wave[v];
@@ -668,6 +690,162 @@ __global__ __launch_bounds__(BS_WAVES * 64, BS_WAVES == 16u ? 8 : 5) void k_km_b
     }
 }
 
+// ---------------------------------------------------------------- P4b: cells inside the buckets
+// What a Lloyd iteration reads is a bucket for every border, and an initial centre a bucket for its rank.  Where a group has
+// no more streams than the GPU has compute units, its larger buckets are therefore put in order once more, in up to 512 cells of
+// 64 to 128 values, with the exact sum of what lies above every cell: then one workgroup takes a stream through
+// all its iterations, whatever its length, instead of a launch per iteration in which many read the buckets.  (One
+// 16.8 M-element tensor, 4 bits, ten iterations: cells 33 us; iterations 154 -> 43, initial centres 35 -> 12.  Where the line
+// lies: excp_fine_tensor.)
+//
+// A workgroup per bucket: its values are read into registers, counted and added up per cell in LDS, and written back through
+// LDS in the order of their cells.  The cells are equal ranges of the (order-preserving) key between the bucket's extremes,
+// without the gap round zero that a bucket of both signs has.  Sums are in units of the bucket's lowest bit position, so the
+// bucket may span FINE_SPAN binary orders (24 of the mantissa, 16 of the number of values, 23: 63 bits).  A bucket that
+// spans more or is larger than the workgroup's registers gets no cells; it is read as a whole, as before.
+constexpr u32 FINE_SPAN = 23, FINE_LEAST = 256;            // smaller buckets are one cell without any table
+// km_fine: cells' log2 | shift << 4 | largest cell << 9 | FINE_NEAR: the values span eight binary orders at most | FINE_VALID
+constexpr u32 FINE_VALID = 1u << 31, FINE_NEAR = 1u << 30, NEAR_SPAN = 8;
+__device__ __forceinline__ u32 fine_log2(u32 info) { return info & 15u; }
+__device__ __forceinline__ u32 fine_shift(u32 info) { return (info >> 4) & 31u; }
+__device__ __forceinline__ u32 fine_most(u32 info) { return (info >> 9) & 0xffffu; }
+// A key without the gap between the largest negative and the smallest positive value of magnitude `mag` (bit pattern) or more.
+__device__ __forceinline__ u32 closed_key(u32 key, u32 mag) {
+    const u32 a = 0x7fffffffu - mag, b = 0x80000000u + mag;          // keys of -mag and +mag (of -0 and +0 for mag = 0)
+    return key <= a ? key : (key < b ? a + 1u : key - b + a + 2u);
+}
+// A value of magnitude pattern mb in units of 2^(pos_lo - 149).
+__device__ __forceinline__ u64 value_units(u32 bits, u32 pos_lo) {
+    const u32 mb = bits & 0x7fffffffu, e = mb >> 23;
+    const u64 d = mb ? (u64)((mb & 0x7fffffu) | (e ? 0x800000u : 0u)) << (bit_pos(mb) - pos_lo) : 0ull;
+    return (bits >> 31) ? (u64)0 - d : d;
+}
+
+template <u32 THREADS, u32 STAGE>
+struct CellsShared {
+    float stage[STAGE];                                    // values on their way back
+    u64 sum[512];
+    u32 cnt[512];
+    u32 wave_cnt[8];
+    u64 wave_sum[8];
+    u32 most;
+};
+// A bucket of at most THREADS x PER values.
+template <u32 THREADS, u32 STAGE, u32 PER>
+__device__ __forceinline__ void cells_of_bucket(EXCP_GLOBAL float *part, u32 size, u32 kmin, u32 kmax, u32 mag, u32 *info, u32 *begin, u64 *above, CellsShared<THREADS, STAGE> &A) {
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, pos_lo = bit_pos(mag);
+    float v[PER];
+#pragma unroll
+    for (u32 j = 0; j < PER; ++j) v[j] = j * THREADS + tid < size ? part[j * THREADS + tid] : 0.f;
+    const u32 k0 = closed_key(kmin, mag), range = closed_key(kmax, mag) - k0;
+    const u32 lg = excp_fine_cells_log2(size), bits = 32u - (u32)__clz((int)(range | 1u)), shift = bits > lg ? bits - lg : 0u;
+    if (tid < 512u) { A.cnt[tid] = 0; A.sum[tid] = 0; }
+    if (tid == 0) A.most = 0;
+    __syncthreads();
+    // (nearly every bucket has values of one sign only)
+    const bool both = kmin < 0x80000000u && kmax >= 0x80000000u;
+    const u32 flip = kmin < 0x80000000u ? 0xffffffffu : 0x80000000u;
+    auto cell_in = [&](float x) { return both ? (closed_key(key_of(x), mag) - k0) >> shift : ((f2u(x) ^ flip) - kmin) >> shift; };
+    // Where the bucket spans eight binary orders and one sign, as nearly all do, a cell's sum of magnitudes (24 + 8 + 16 bits)
+    // and its number of values share a word and an atomic.
+    const bool near = bit_pos(max(f2u(val_of(kmin)) & 0x7fffffffu, f2u(val_of(kmax)) & 0x7fffffffu)) - pos_lo <= NEAR_SPAN, packed = near && !both;
+    u32 place[PER / 2u];                                   // arrivals in the cells, then places in the bucket, two to a register
+#pragma unroll
+    for (u32 j = 0; j < PER; ++j) {
+        if (j % 2u == 0u) place[j / 2u] = 0;
+        asm volatile("" : "+v"(v[j]));
+        if (j * THREADS + tid < size) {
+            const u32 cell = cell_in(v[j]);
+            if (packed) {
+                place[j / 2u] |= (u32)(atomicAdd(&A.sum[cell], value_units(f2u(v[j]) & 0x7fffffffu, pos_lo) | 1ull << 48) >> 48) << (16u * (j % 2u));
+            } else {
+                place[j / 2u] |= atomicAdd(&A.cnt[cell], 1u) << (16u * (j % 2u));
+                atomicAdd(&A.sum[cell], value_units(f2u(v[j]), pos_lo));
+            }
+        }
+        if (j % 2u == 1u) asm volatile("" : "+v"(place[j / 2u]));
+    }
+    __syncthreads();
+    u32 cnt = 0, incl = 0;
+    u64 incls = 0;
+    if (tid < 512u) {
+        u64 sum = A.sum[tid];
+        cnt = A.cnt[tid];
+        if (packed) { cnt = (u32)(sum >> 48); sum &= (1ull << 48) - 1ull; if (kmin < 0x80000000u) sum = (u64)0 - sum; }
+        incl = wave_incl_scan_u32(cnt); incls = wave_incl_scan_u64(sum);
+        const u32 most = wave_max_u32(cnt);
+        if (lane == 63u) { A.wave_cnt[wave] = incl; A.wave_sum[wave] = incls; atomicMax(&A.most, most); }
+    }
+    __syncthreads();
+    if (tid < 512u) {
+        u64 all = 0;
+#pragma unroll
+        for (u32 q = 0; q < 8; ++q) { if (q < wave) { incl += A.wave_cnt[q]; incls += A.wave_sum[q]; } all += A.wave_sum[q]; }
+        A.cnt[tid] = incl - cnt;
+        if (tid < 1u << lg) { begin[tid] = incl - cnt; above[tid] = all - incls; }
+        if (tid == 0) { begin[1u << lg] = size; *info = FINE_VALID | (near ? FINE_NEAR : 0u) | lg | shift << 4 | A.most << 9; }
+    }
+    __syncthreads();
+#pragma unroll
+    for (u32 j = 0; j < PER; ++j) {
+        // (past the end: a place that no round has, as the largest bucket is smaller.  The cell is worked out again: kept, the
+        // forty-eight of them would not fit the registers.)
+        asm volatile("" : "+v"(v[j]));
+        const u32 to = j * THREADS + tid < size ? A.cnt[cell_in(v[j])] : 0xffffu;
+        place[j / 2u] += to << (16u * (j % 2u));
+        if (j % 2u == 1u) asm volatile("" : "+v"(place[j / 2u]));
+    }
+#pragma unroll 1
+    for (u32 r0 = 0; r0 < size; r0 += STAGE) {
+        if (r0) __syncthreads();
+#pragma unroll
+        for (u32 j = 0; j < PER; ++j) {
+            const u32 to = (place[j / 2u] >> (16u * (j % 2u)) & 0xffffu) - r0;
+            if (to < STAGE) A.stage[to] = v[j];
+        }
+        __syncthreads();
+        const u32 n = min(size - r0, STAGE);
+        for (u32 i = tid; i < n; i += THREADS) part[r0 + i] = A.stage[i];
+    }
+}
+
+template <u32 THREADS, u32 MOST, u32 STAGE>
+__global__ __launch_bounds__(THREADS) void k_km_cells(Workspace w, GroupParams g) {
+    __shared__ CellsShared<THREADS, STAGE> A;
+    const u32 sidx = stream_in_turn(w, blockIdx.x / NBKT), b = blockIdx.x % NBKT, tid = threadIdx.x, t = sidx / 3u;
+    if (w.seg[sidx].len == 0) return;
+    const u32 at = sidx * NBKT + b;
+    const EXCP_CONSTANT u32 *ends = (const EXCP_CONSTANT u32 *)(uintptr_t)(w.km_begin + (u64)sidx * (NBKT + 1u));
+    const u32 q0 = ends[b], size = ends[b + 1u] - q0;
+    const u32 kmin = w.km_min[at], kmax = w.km_max[at], mag = w.km_mag[at];
+    const u32 top = max(f2u(val_of(kmin)) & 0x7fffffffu, f2u(val_of(kmax)) & 0x7fffffffu);
+    static_assert(MOST / STAGE * STAGE == MOST && MOST < 0xffffu, "places have 16 bits");
+    // (the values of a crowded stream are not spread by keys either, and the many workgroups that share its iterations would meet at
+    // the same centres if its buckets were in order: 300 000 residuals of a sign-like update, 8 bits, 386 -> 821 us)
+    if (size < FINE_LEAST || size > MOST || kmin >= kmax || w.seg[sidx].crowded || bit_pos(top) - bit_pos(mag) > FINE_SPAN) {
+        if (tid == 0) w.km_fine[at] = 0u;
+        return;
+    }
+    const u64 e = (u64)(sidx % 3u) * w.fine_stride + excp_fine_at(w.desc[t].elem_off, t, q0, b);
+    EXCP_GLOBAL float *part = gptr(seg_part(w, sidx)) + q0;
+    // (registers by the size of the bucket: with those of the largest for all of them, the 5000 values of a moment bucket
+    // took as long as the 22 700 of a residual one)
+#define EXCP_CELLS(PER) cells_of_bucket<THREADS, STAGE, PER>(part, size, kmin, kmax, mag, &w.km_fine[at], &w.fine_begin[e], &w.fine_above[e], A)
+    if (size <= 2u * THREADS) EXCP_CELLS(2);
+    else if (size <= 6u * THREADS) EXCP_CELLS(6);
+    else if (size <= 16u * THREADS) EXCP_CELLS(16);
+    else if (MOST > 16u * THREADS) {
+        if (size <= 24u * THREADS) EXCP_CELLS(24);
+        else if (size <= 40u * THREADS) EXCP_CELLS(40);
+        else if (MOST > 40u * THREADS) {
+            if (size <= 56u * THREADS) EXCP_CELLS(56);
+            else if (size <= 76u * THREADS) EXCP_CELLS(76);
+            else EXCP_CELLS(MOST / THREADS);
+        }
+    }
+#undef EXCP_CELLS
+}
+
 // ---------------------------------------------------------------- P5: initial centres, bucket prefix sums
 // Per stream K workgroups, one per initial centre, and one that makes the prefix sums of the bucket totals.
 //
@@ -680,9 +858,17 @@ __global__ __launch_bounds__(BS_WAVES * 64, BS_WAVES == 16u ? 8 : 5) void k_km_b
 //
 // The prefix sums turn the total of any run of buckets into one difference; the workgroup that makes them also decides
 // how the stream goes through the Lloyd iterations, and the workgroup of centre k clears its share of their accumulators.
+// The cells of bucket `at` as a Lloyd iteration sees them: those of its table, one (the bucket itself) where it has few
+// values, or 0.  `span`: binary orders between its values.
+__device__ __forceinline__ u32 fine_info(const Workspace &w, const GroupParams &g, u32 sidx, u32 at, u32 size, u32 span) {
+    if (size < FINE_LEAST) return span <= FINE_SPAN ? FINE_VALID | (span <= NEAR_SPAN ? FINE_NEAR : 0u) | size << 9 : 0u;
+    return g.fine && excp_fine_tensor(w.desc[sidx / 3u].n) ? w.km_fine[at] : 0u;
+}
+constexpr u32 FINE_COST = 24;                             // a value of a cell, which sixteen lanes read, in SegState::work
+
 template <u32 INIT_THREADS>
 __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupParams g, u32 sel) {
-    __shared__ u32 hist[2048];
+    __shared__ __attribute__((aligned(16))) u32 hist[2048];
     __shared__ u32 s_wave[INIT_THREADS / 64], s_pick[2];
     const u32 K = (u32)g.K;
     const u32 sidx = stream_in_turn(w, stream_of(blockIdx.x / (K + 1u), sel)), k = blockIdx.x % (K + 1u), tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
@@ -693,7 +879,8 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
     if (k == K) {
         // a wave takes a bin: four consecutive buckets per lane
         u64 *bs = w.km_bsum + (u64)sidx * EXCP_ABSM_BINS * (NBKT + 1);
-        if (tid < 2) { s_pick[tid] = tid ? 0u : 64u; s_wave[tid] = tid ? 0u : 255u; s_wave[2] = 0u; }
+        __shared__ u32 s_whole, s_cell;
+        if (tid < 2) { s_pick[tid] = tid ? 0u : 64u; s_wave[tid] = tid ? 0u : 255u; s_wave[2] = 0u; s_whole = 0u; s_cell = 0u; }
         __syncthreads();
         if (tid < NBKT) {                      // lowest and highest bit position of any value, largest bucket of several
             const u32 at = sidx * NBKT + tid, kn = w.km_min[at], kx = w.km_max[at], low = w.km_mag[at];
@@ -702,9 +889,12 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
             const u32 most = b1 - b0 - (INIT_THREADS == 1024u ? w.km_dom[at] : 0u);
             const bool any = kn <= kx;         // (an empty bucket has no extremes)
             const u32 a = f2u(val_of(kn)) & 0x7fffffffu, c = f2u(val_of(kx)) & 0x7fffffffu;
+            // a border in a bucket with cells costs a cell, in another the bucket
+            const u32 info = fine_info(w, g, sidx, at, b1 - b0, any ? bit_pos(max(a, c)) - bit_pos(low) : 0u);
+            const u32 whole = info ? 0u : b1 - b0, ps = wave_sum_u32(whole), pc = wave_max_u32(kn < kx && info ? fine_most(info) : 0u);
             // (reduced in the wave first: an atomic whose lanes differ is a loop over them: three of those, 3000 streams 476 us, now 329)
-            const u32 p0 = wave_min_u32(any ? bit_pos(low) : 255u), p1 = wave_max_u32(any ? bit_pos(max(a, c)) : 0u), p2 = wave_max_u32(kn < kx ? most : 0u);
-            if (lane == 0u) { atomicMin(&s_wave[0], p0); atomicMax(&s_wave[1], p1); atomicMax(&s_wave[2], p2); }
+            const u32 p0 = wave_min_u32(any ? bit_pos(low) : 255u), p1 = wave_max_u32(any ? bit_pos(max(a, c)) : 0u), p2 = wave_max_u32(kn < kx && !info ? most : 0u);
+            if (lane == 0u) { atomicMin(&s_wave[0], p0); atomicMax(&s_wave[1], p1); atomicMax(&s_wave[2], p2); atomicAdd(&s_whole, ps); atomicMax(&s_cell, pc); }
         }
         for (u32 bin = wave; bin < EXCP_ABSM_BINS; bin += INIT_THREADS / 64u) {
             u64 *row = bs + (u64)bin * (NBKT + 1);
@@ -728,8 +918,8 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
             S.acc_lo = s_wave[0] > 19u ? (s_wave[0] - 19u) >> 3 : 0u;
             S.acc_hi = min(s_wave[1] / 8u + 9u, EXCP_ABSM_BINS - 1u);
             // one workgroup or many (see P6)
-            const u64 even = (len * (K - 1u)) / NBKT, crowded = (u64)s_wave[2] * (K > 3u ? 8u : 1u);
-            S.work = (u32)min(max(even, crowded), 0xffffffffull);
+            const u64 even = ((u64)s_whole * (K - 1u)) / NBKT, crowded = (u64)s_wave[2] * (K > 3u && (!g.fine || (u64)s_wave[2] > 3ull * (len / NBKT + 1ull)) ? 8u : 1u), cells = (u64)s_cell * FINE_COST;
+            S.work = (u32)min(max(max(even, crowded), cells), 0xffffffffull);
             if (S.work > g.alone_work && slot != EXCP_NO_SLOT) {
                 atomicOr(&w.st[sidx / 3u].lloyd_shared, 1u);
                 atomicOr(w.lloyd_shared, 1u);
@@ -749,17 +939,47 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
     // (the same in every lane, and through the scalar unit: left to the compiler, whether it is depends on stores nearby)
     const u32 b = (u32)__builtin_amdgcn_readfirstlane((int)s_pick[0]);
     const EXCP_CONSTANT u32 *ends = (const EXCP_CONSTANT u32 *)(uintptr_t)begin;
-    const u32 p0 = ends[b], p1 = ends[b + 1], cntb = p1 - p0;
-    u32 rank = r - p0;
+    u32 p0 = ends[b], cntb = ends[b + 1] - p0, rank = r - p0;
     const u32 kmin = ((const EXCP_CONSTANT u32 *)(uintptr_t)w.km_min)[(u64)sidx * NBKT + b], kmax = ((const EXCP_CONSTANT u32 *)(uintptr_t)w.km_max)[(u64)sidx * NBKT + b];
-    const EXCP_GLOBAL float *gpart = gptr(seg_part(w, sidx)) + p0;
     u32 diff = kmin ^ kmax;
     float *out = &S.C[1][k];                 // (read by iteration 0, whose predecessor has parity 1)
     if (diff == 0) { if (tid == 0) *out = val_of(kmin); return; }
     // Tied data: the rank usually falls among the repetitions of the bucket's first value, which have been counted.
     // (The K ranks of a stream often ask for the same few large buckets: reading those for each of them took most
     // of this kernel's time: a 410M-shaped checkpoint in bf16 468 us, 164 now.)
-    if (INIT_THREADS == 1024u && rank - w.km_less[(u64)sidx * NBKT + b] < w.km_dom[(u64)sidx * NBKT + b]) { if (tid == 0) *out = gpart[0]; return; }
+    // (k_km_cells moves values within a bucket: the first one is no longer the one that was counted where it has run.)
+    const u32 info = g.fine && excp_fine_tensor(((const EXCP_CONSTANT TDesc *)(uintptr_t)(w.desc + sidx / 3u))->n)
+                         ? ((const EXCP_CONSTANT u32 *)(uintptr_t)w.km_fine)[(u64)sidx * NBKT + b] : 0u;
+    if (INIT_THREADS == 1024u && !info && rank - w.km_less[(u64)sidx * NBKT + b] < w.km_dom[(u64)sidx * NBKT + b]) { if (tid == 0) *out = gptr(seg_part(w, sidx))[p0]; return; }
+    if (info) {                                           // the cell that holds the rank
+        const u64 e = (u64)(sidx % 3u) * w.fine_stride + excp_fine_at(w.desc[sidx / 3u].elem_off, sidx / 3u, p0, b);
+        for (u32 c = tid; c < 1u << fine_log2(info); c += INIT_THREADS) {
+            const u32 c0 = w.fine_begin[e + c], c1 = w.fine_begin[e + c + 1u];
+            if (c0 <= rank && rank < c1) { s_pick[0] = c0; s_pick[1] = c1; }
+        }
+        __syncthreads();
+        const u32 c0 = (u32)__builtin_amdgcn_readfirstlane((int)s_pick[0]), c1 = (u32)__builtin_amdgcn_readfirstlane((int)s_pick[1]);
+        p0 += c0; cntb = c1 - c0; rank -= c0;
+    }
+    const EXCP_GLOBAL float *gpart = gptr(seg_part(w, sidx)) + p0;
+    if (cntb <= 256u) {
+        // few values: each counts those before it in the order
+        const u32 mine = tid < cntb ? key_of(gpart[tid]) : 0xffffffffu;
+        if (tid < 256u) hist[tid] = mine;
+        __syncthreads();
+        if (tid < cntb) {
+            u32 less = 0;
+            typedef u32 u4 __attribute__((ext_vector_type(4)));
+#pragma unroll 2
+            for (u32 j = 0; j < cntb; j += 4u) {
+                const u4 o = *(const u4 *)&hist[j];
+#pragma unroll
+                for (u32 e = 0; e < 4; ++e) less += (o[e] < mine || (o[e] == mine && j + e < tid)) ? 1u : 0u;
+            }
+            if (less == rank) *out = val_of(mine);
+        }
+        return;
+    }
     // A bucket far above the average size holds tied values (a continuous distribution fills the
     // buckets evenly).  Such a bucket is mostly ONE value, its smallest or its largest key, with a few
     // strays beside it: one cheap pass counts the two extremes, and if the rank falls among them the
@@ -878,13 +1098,13 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
 // even shares of 256, or the largest bucket that holds more than one value, if that is more.  The values of a crowded
 // bucket (residuals of a sign-like update, values bunched beside outliers) count eight times from four centres on, since
 // most centres then lie in that bucket, and its values go one by one; of tied data only what is not a repetition of a
-// bucket's first value counts.  A tensor's streams go the same way.  The host launches the iterations of the second
-// way wherever a tensor is too large for excp_lloyd_small; where no stream takes it they are empty, 1.6 us each.  (2^17
-// elements: one workgroup needs 0.43 ms for 130 000 residuals of a sign-like update, the former work lists needed 0.81; 2^22
-// for three centres, of whose borders a bucket holds two at most.)
-//   Up to 85 tensors on 256 compute units the group goes together, beyond 24 576 (one tensor, 4 bits, ten iterations, us
-//   alone / shared: 1 M elements 163 / 178, 1.5 M 186 / 188, 2.5 M 207 / 174, 10 M 340 / 169; 8 bits: 140 000 elements
-//   737 / 346, 2.5 M 1565 / 194; the 14M shape 248 -> 192).  Bunched values, 4 bits: 1 M elements 8095 -> 201, 9 M 74451 -> 473.
+// bucket's first value counts.  A tensor's streams go the same way, unless buckets have cells; then each by itself, buckets
+// with cells count by their largest cell, and the line lies at 98 304 (one bucket of 50 000 values without cells costs an
+// iteration 8 us, a launch 14).  The host launches the iterations of the second way wherever a tensor is too large for
+// excp_lloyd_small; where no stream takes it they are empty.  (2^17 elements: one workgroup needs 0.43 ms for 130 000 residuals
+// of a sign-like update, the former work lists needed 0.81; 2^22 for three centres, of whose borders a bucket holds two at most.)
+//   Without cells (excp_fine_tensor), up to 85 tensors on 256 compute units go together, the line at 24 576.  (One tensor, 4 bits,
+//   ten iterations, us alone / shared: 1 M elements 163 / 178, 2.5 M 207 / 174, 10 M 340 / 169.)
 //   More tensors fill the GPU as they are, one workgroup a stream, and the line lies at 196 608 (300 tensors of 600 000
 //   elements, 4 bits: 338 alone, 522 shared; the 410M shape 440, and 499 with the line at 65 536), from six bits on at
 //   131 072 (the 410M shape in 7 bits 1943, and 2406 with the line at 196 608).
@@ -900,6 +1120,7 @@ constexpr u32 lloyd_unit(u32 KMAX) { return KMAX > 15u ? 4096u : 8192u; }
 
 // Whether many workgroups take the stream's iterations.
 __device__ __forceinline__ bool lloyd_shared(const Workspace &w, const GroupParams &g, u32 sidx) {
+    if (g.fine) return w.seg[sidx].work > g.alone_work;
     return (g.together ? *w.lloyd_shared : w.st[sidx / 3u].lloyd_shared) != 0u;
 }
 
@@ -1007,15 +1228,16 @@ __device__ __forceinline__ void lloyd_centres(const LloydStream &st, u32 K, u32 
     __syncthreads();
 }
 
-// Which buckets the present cut keys cut, laid back to back; returns how many values those hold.
-__device__ __forceinline__ u32 lloyd_cut_buckets(LloydStream &st, u32 kp2, LloydShared &L) {
+// Which buckets the present cut keys cut, laid back to back; returns how many values those hold.  `fine`: those with cells are
+// left out.
+__device__ __forceinline__ u32 lloyd_cut_buckets(LloydStream &st, u32 kp2, LloydShared &L, const u32 *fine) {
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     u32 size = 0, incl = 0;
     if (tid < NBKT) {
         const u32 cntb = L.begin[tid + 1u] - L.begin[tid];
         u32 alo = 0, ahi = 0;
         if (cntb) { alo = centre_by_cuts(L.cut, kp2, st.kmin); ahi = centre_by_cuts(L.cut, kp2, st.kmax); }
-        if (alo != ahi) size = cntb;
+        if (alo != ahi && !(fine && fine[tid])) size = cntb;
         st.alo = alo;
         L.range[tid] = alo | (ahi << 8) | (st.pos << 16);
         incl = wave_incl_scan_u32(size);
@@ -1284,32 +1506,292 @@ __device__ __forceinline__ void lloyd_units(const Workspace &w, const GroupParam
 
 // One workgroup takes a stream through all its iterations; the final centres and cut keys end in the slots of
 // parity `iters`.  KMAX: the centres the LDS accumulators are laid out for.
+//
+// Centre k has the buckets whose smallest value goes to it, [first[k], first[k + 1]): one difference of prefix sums.  What
+// border k, the one below centre k, cuts off the bucket before first[k] -- the sum and number of its values from the cut key up
+// -- goes from centre k - 1 to centre k: of a bucket with cells the stored sum of the higher cells and the values of one
+// cell.  Sixteen lanes take a border (eight beyond 63 centres).  Buckets without cells go the way of k_km_iter.
+// What bounds an iteration is its chain of steps, so there is little in it: two round trips to memory (a cell's place, its
+// values), prefix sums out of LDS, as integers of 128 bits where the stream's binary orders allow, and for up to 63 centres
+// everything from the sums to the next cut keys in one wave, without barriers.
+// (us, ten iterations: 1414 values, 15 centres 57 -> 31; 5.8 M values, 154 in eleven launches -> 43; 8.7 M, 255 centres 247
+// -> 158.)
+constexpr u32 P128_BINS = 15;                             // acc_hi - acc_lo up to which sums fit 127 bits (see lloyd_wide)
+template <u32 KMAX>
+struct LloydAlone {
+    LloydShared L;
+    u64 acc[(EXCP_ABSM_BINS + 1u) * KMAX], mine[LLOYD_WAVES][KMAX + 1u];
+    __int128 before[NBKT + 1u];                           // sum of the buckets before, in units of 2^(8 acc_lo - 149)
+    u64 sum[KMAX + 1u];                                   // per border: what goes to centre k, in units of 2^(pos - 149)
+    u32 cnt[KMAX + 1u], pos[KMAX + 1u], first[KMAX + 1u];
+    u64 up[KMAX > 63u ? KMAX + 1u : 1u];                  // beyond 63 centres: the border's cell, values and sum of the higher ones
+    u32 p0[KMAX > 63u ? KMAX + 1u : 1u], p1[KMAX > 63u ? KMAX + 1u : 1u], above[KMAX > 63u ? KMAX + 1u : 1u];     // p1: top bit set where FINE_NEAR
+    u32 fine[NBKT], kmin[NBKT], kmax[NBKT], mag[NBKT];    // per bucket: cells (fine_info), extremes (an empty one: the next one's smallest key)
+    u32 edge[4];
+    u32 coarse, disorder;
+};
+// v * 2^(bitpos - 149) onto one column of the accumulators, which only the calling thread uses.
+__device__ __forceinline__ void column_add(u64 *col, u32 stride, long long v, u32 bitpos) {
+    const bool neg = v < 0;
+    const u64 mag = neg ? (u64)0 - (u64)v : (u64)v;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const u64 piece = (mag >> (32 * h)) & 0xffffffffull;
+        const u32 p = bitpos + 32u * (u32)h;
+        const u64 d = piece << (p & 7u);
+        if (piece) col[(p >> 3) * stride] += neg ? (u64)0 - d : d;
+    }
+}
+// Bins [g0, g1] as one integer in units of 2^(8 g0 - 149), which it must fit.
+__device__ __forceinline__ __int128 bins_to_i128(const u64 *bins, u32 stride, u32 g0, u32 g1) {
+    unsigned __int128 t = 0;
+    for (u32 q = g1 + 1u; q-- > g0;) t = (t << 8) + (unsigned __int128)(__int128)(long long)bins[q * stride];
+    return (__int128)t;
+}
+// t * 2^(base - 149), rounded once (to nearest, ties to even).
+__device__ __forceinline__ double i128_to_double(__int128 t, u32 base) {
+    const bool neg = t < 0;
+    const unsigned __int128 mag = neg ? (unsigned __int128)0 - (unsigned __int128)t : (unsigned __int128)t;
+    const u64 hi = (u64)(mag >> 64), lo = (u64)mag;
+    const int msb = hi ? 127 - __clzll((long long)hi) : 63 - __clzll((long long)(lo | 1ull));
+    double m;
+    if (msb <= 52) {
+        m = ldexp((double)lo, (int)base - 149);
+    } else {
+        const int sh = msb - 52;                          // 1 .. 75
+        u64 mant = (u64)(mag >> sh);
+        const unsigned __int128 below = mag << (128 - sh);
+        const u64 top = (u64)(below >> 64);
+        if ((top >> 63) && ((top << 1) | (u64)below | (mant & 1ull))) ++mant;
+        m = ldexp((double)mant, sh + (int)base - 149);
+    }
+    return neg ? -m : m;
+}
+
 template <u32 KMAX>
 __global__ __launch_bounds__(LLOYD_THREADS, 2u * lloyd_per_cu(KMAX)) void k_km_lloyd(Workspace w, GroupParams g) {
-    __shared__ LloydShared L;
-    __shared__ u64 acc[(EXCP_ABSM_BINS + 1u) * KMAX], mine[LLOYD_WAVES][KMAX + 1u];
-    if (blockIdx.x == 3u * g.ntensors) { lloyd_units<KMAX>(w, g); return; }
-    const u32 sidx = stream_in_turn(w, blockIdx.x), tid = threadIdx.x, wave = tid >> 6, K = (u32)g.K, iters = (u32)g.iters;
+    constexpr bool ONE_WAVE = KMAX <= 63u;
+    constexpr u32 ROW = ONE_WAVE ? 16u : 8u, BATCH = 8u;  // lanes to a border, loads of a lane in flight
+    __shared__ LloydAlone<KMAX> A;
+    LloydShared &L = A.L;
+    const u32 sidx = stream_in_turn(w, blockIdx.x), tid = threadIdx.x, lane = tid & 63u, K = (u32)g.K, iters = (u32)g.iters;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     SegState &S = w.seg[sidx];
     if (S.len == 0 || lloyd_shared(w, g, sidx)) return;
     u32 kp2 = 1; while (kp2 < K) kp2 <<= 1;
+    const bool centre = tid < K;
     LloydStream st = lloyd_open(w, sidx, K, 1u, false, L);
-    lloyd_clear(acc, st, K);
     const EXCP_GLOBAL float *part = gptr(seg_part(w, sidx));
+    const u64 e0 = (u64)(sidx % 3u) * w.fine_stride + excp_fine_at(w.desc[sidx / 3u].elem_off, sidx / 3u, 0u, 0u);
+    const EXCP_GLOBAL u32 *fb = gptr((const u32 *)w.fine_begin) + e0;
+    const EXCP_GLOBAL u64 *fa = gptr((const u64 *)w.fine_above) + e0;
+    // Prefix sums in 128 bits: the highest value's lowest bit is at 8 (acc_hi - 9) + 7, six more where acc_hi is the last bin,
+    // the unit's at 8 acc_lo, and 24 + 31 bits come on top for the mantissa and the number of values.
+    const bool narrow = st.acc_hi - st.acc_lo <= P128_BINS;
+    const u32 base = 8u * st.acc_lo;
+    if (narrow && tid <= NBKT) {
+        __int128 t = 0;
+        if (st.bin_lo <= st.bin_hi) {
+            unsigned __int128 u = 0;
+#pragma unroll 4
+            for (u32 q = st.bin_hi + 1u; q-- > st.bin_lo;) u = (u << 8) + (unsigned __int128)(__int128)(long long)st.bs[q * (NBKT + 1u) + tid];
+            t = (__int128)(u << (8u * (st.bin_lo - st.acc_lo)));
+        }
+        A.before[tid] = t;
+    }
+    if (tid < NBKT) { A.kmin[tid] = st.kmin; A.kmax[tid] = st.kmax; A.mag[tid] = w.km_mag[(u64)sidx * NBKT + tid]; }
+    if (tid <= KMAX) { A.sum[tid] = 0; A.cnt[tid] = 0; A.first[tid] = tid ? NBKT : 0u; A.pos[tid] = base; }
+    if (tid <= EXCP_MAX_K) L.cut[tid] = 0xffffffffu;
+    if (tid == 0) { A.coarse = 0; A.disorder = 0; }
+    __syncthreads();
+    u32 least = 0xffffffffu;
+    if (tid < NBKT) {
+        const u32 b = NBKT - 1u - tid, size = L.begin[b + 1u] - L.begin[b];     // from the last bucket to the first
+        least = size ? A.kmin[b] : 0xffffffffu;
+        const u32 top = size ? max(f2u(val_of(A.kmin[b])) & 0x7fffffffu, f2u(val_of(A.kmax[b])) & 0x7fffffffu) : 0u;
+        A.fine[b] = fine_info(w, g, sidx, sidx * NBKT + b, size, size ? bit_pos(top) - bit_pos(A.mag[b]) : 0u);
+#define EXCP_MOVE(CTRL, ROWS) dpp_u32<CTRL, ROWS>(0xffffffffu, least)
+        EXCP_WAVE_SCAN(least, EXCP_FOLD_MIN, EXCP_MOVE);
+#undef EXCP_MOVE
+        if (lane == 63u) A.edge[wave] = least;
+    }
+    __syncthreads();
+    if (tid < NBKT) {
+        for (u32 v = 0; v < wave; ++v) least = min(least, A.edge[v]);
+        A.kmin[NBKT - 1u - tid] = least;
+    }
+    __syncthreads();
     for (u32 i = 0;; ++i) {
-        lloyd_centres(st, K, i, acc, L);
+        // (a) the cut keys
+        if ((!ONE_WAVE || wave == 0u) && centre && tid) L.cut[tid] = cut_key(L.C, K, tid);
         if (i == iters) break;
-        const u32 T = lloyd_cut_buckets(st, kp2, L);
-        if (T <= LLOYD_FEW) {
-            lloyd_few(part, 0u, T, K, kp2, acc, L);
-        } else {
-            const u32 q0 = (u32)(((u64)T * wave) / LLOYD_WAVES), q1 = (u32)(((u64)T * (wave + 1u)) / LLOYD_WAVES);
-            lloyd_share(part, q0, q1, K, acc, mine[wave], L);
+        if ((!ONE_WAVE || wave == 0u) && tid == 0) A.coarse = 0;
+        // The cell that a border c cuts: its values [p0, p1), and what lies above it in its bucket.  f: the first bucket whose
+        // smallest key is not below c.
+        auto find_cell = [&](u32 c, u32 f, u32 &p0, u32 &p1, bool &near, u32 &pos, u64 &up, u32 &above) {
+            if (!(f && c <= A.kmax[f - 1u])) return;
+            const u32 b = f - 1u, info = A.fine[b], mag = A.mag[b], q0 = L.begin[b], q1 = L.begin[b + 1u];
+            if (info == 0u) { A.coarse = 1u; return; }
+            p0 = q0; p1 = q1; near = (info & FINE_NEAR) != 0u;
+            pos = bit_pos(mag);
+            if (q1 - q0 >= FINE_LEAST) {
+                const u32 e = (q0 >> EXCP_FINE_SHIFT) + b + ((closed_key(c, mag) - closed_key(A.kmin[b], mag)) >> fine_shift(info));
+                const u32 c0 = fb[e], c1 = fb[e + 1u];
+                up = fa[e];
+                p0 = q0 + c0; p1 = q0 + c1; above = q1 - p1;
+            }
+        };
+        if (!ONE_WAVE) {
+            // (a thread per border: the look-ups of all borders are one round trip.  The barrier: A.coarse is set from here on.)
+            __syncthreads();
+            if (centre && tid) {
+                const u32 c = L.cut[tid];
+                u32 f = 0, p0 = 0, p1 = 0, pos = base, above = 0;
+                u64 up = 0;
+                bool near = true;
+#pragma unroll
+                for (u32 step = NBKT / 2; step >= 1u; step >>= 1) if (A.kmin[f + step - 1u] < c) f += step;
+                if (f == NBKT - 1u && A.kmin[f] < c) f = NBKT;
+                find_cell(c, f, p0, p1, near, pos, up, above);
+                A.first[tid] = f; A.p0[tid] = p0; A.p1[tid] = p1 | (near ? 1u << 31 : 0u); A.pos[tid] = pos; A.up[tid] = up; A.above[tid] = above;
+            }
+        }
+        __syncthreads();
+        // (b) what the borders cut off
+        const u32 l = tid & (ROW - 1u);
+        for (u32 k0 = 1; k0 < K; k0 += LLOYD_THREADS / ROW) {
+            const u32 k = k0 + tid / ROW;
+            u64 sum = 0, up = 0;
+            u32 cnt = 0, above = 0, f = NBKT, pos = base;
+            if (k < K) {
+                const u32 c = L.cut[k];
+                u32 p0 = 0, p1 = 0;
+                bool near = true;
+                if (ONE_WAVE) {
+                    // the bucket by two steps of sixteen
+                    const u32 shift = lane & ~(ROW - 1u);
+                    f = 16u * (u32)__popc((u32)(ballot64(A.kmin[16u * l + 15u] < c) >> shift) & 0xffffu);
+                    if (f < NBKT) f += (u32)__popc((u32)(ballot64(A.kmin[f + l] < c) >> shift) & 0xffffu);
+                    find_cell(c, f, p0, p1, near, pos, up, above);
+                } else {
+                    p0 = A.p0[k]; p1 = A.p1[k] & 0x7fffffffu; near = A.p1[k] >> 31; pos = A.pos[k]; up = A.up[k]; above = A.above[k];
+                }
+                // Values below 2^32 units (eight binary orders) add exactly in fp64, and compare with the border as floats: none
+                // lies between -0 and +0, which are equally far from any centre.  (Eight instructions a value; as integers it was
+                // thirty-five, and with 255 centres that was what an iteration waited for: 27 us, now 14.)
+                const float t = val_of(c), inf = u2f(0x7f800000u);
+                double part_sum = 0.0;
+                if (near) {
+                    for (u32 p = p0 + l; p < p1; p += BATCH * ROW) {
+                        float x[BATCH];
+#pragma unroll
+                        for (u32 j = 0; j < BATCH; ++j) x[j] = part[min(p + ROW * j, p1 - 1u)];
+#pragma unroll
+                        for (u32 j = 0; j < BATCH; ++j) {
+                            const bool in = (p + ROW * j < p1 ? x[j] : -inf) >= t;
+                            part_sum += (double)(in ? x[j] : 0.f);
+                            cnt += in;
+                        }
+                    }
+                    sum = (u64)(long long)ldexp(part_sum, 149 - (int)pos);
+                } else {
+                    for (u32 p = p0 + l; p < p1; p += ROW) {
+                        const float x = part[p];
+                        if (x >= t) { sum += value_units(f2u(x), pos); ++cnt; }
+                    }
+                }
+            }
+            // the row's sum, in its last lane
+            sum += dpp_u64<0x111, 0xf>(sum); sum += dpp_u64<0x112, 0xf>(sum); sum += dpp_u64<0x114, 0xf>(sum);
+            cnt += dpp_u32<0x111, 0xf>(0u, cnt); cnt += dpp_u32<0x112, 0xf>(0u, cnt); cnt += dpp_u32<0x114, 0xf>(0u, cnt);
+            if (ROW == 16u) { sum += dpp_u64<0x118, 0xf>(sum); cnt += dpp_u32<0x118, 0xf>(0u, cnt); }
+            if (l == ROW - 1u && k < K) {
+                if (ONE_WAVE) { A.first[k] = f; A.pos[k] = pos; }
+                A.sum[k] = sum + up; A.cnt[k] = cnt + above;
+            }
+        }
+        if (!narrow) {
+            __syncthreads();
+            for (u32 j = tid; j < (st.acc_hi + 1u - st.acc_lo) * K; j += LLOYD_THREADS) {
+                const u32 q = st.acc_lo + j / K, k = j % K;
+                const u32 f = A.first[k], l1 = k + 1u < K ? A.first[k + 1u] : NBKT;
+                A.acc[q * K + k] = q >= st.bin_lo && q <= st.bin_hi ? st.bs[q * (NBKT + 1u) + l1] - st.bs[q * (NBKT + 1u) + f] : 0ull;
+            }
+        }
+        __syncthreads();
+        const bool coarse = A.coarse != 0u;               // some border cuts a bucket without cells
+        if (coarse) {
+            if (narrow) for (u32 j = tid; j < (st.acc_hi + 1u - st.acc_lo) * K; j += LLOYD_THREADS) A.acc[st.acc_lo * K + j] = 0;
+            if (centre) A.acc[EXCP_ABSM_BINS * K + tid] = 0;
+            const u32 T = lloyd_cut_buckets(st, kp2, L, A.fine);         // (its barriers are passed before anything is added)
+            if (T <= LLOYD_FEW) {
+                lloyd_few(part, 0u, T, K, kp2, A.acc, L);
+            } else {
+                const u32 q0 = (u32)(((u64)T * wave) / LLOYD_WAVES), q1 = (u32)(((u64)T * (wave + 1u)) / LLOYD_WAVES);
+                lloyd_share(part, q0, q1, K, A.acc, A.mine[wave], L);
+            }
+            __syncthreads();
+        }
+        // (c) the centres.  An empty cluster keeps its centre; afterwards the centres are put back in ascending order (stable;
+        // nothing moves unless a run of equal centres was torn apart).
+        if (!ONE_WAVE || wave == 0u) {
+            float c = 0.f;
+            if (centre) {
+                const u32 f = A.first[tid], l1 = tid + 1u < K ? A.first[tid + 1u] : NBKT;
+                u64 cnt = (u64)(L.begin[l1] - L.begin[f]) + A.cnt[tid] - A.cnt[tid + 1u];
+                if (coarse) cnt += A.acc[EXCP_ABSM_BINS * K + tid];
+                const long long in = (long long)A.sum[tid], out = (long long)A.sum[tid + 1u];
+                c = L.C[tid];
+                if (cnt) {
+                    double total;
+                    if (narrow) {
+                        unsigned __int128 t = (unsigned __int128)(A.before[l1] - A.before[f]);
+                        t += (unsigned __int128)(__int128)in << (A.pos[tid] - base);
+                        t -= (unsigned __int128)(__int128)out << (A.pos[tid + 1u] - base);
+                        if (coarse) t += (unsigned __int128)bins_to_i128(A.acc + tid, K, st.acc_lo, st.acc_hi);
+                        total = i128_to_double((__int128)t, base);
+                    } else {
+                        column_add(A.acc + tid, K, in, A.pos[tid]);
+                        column_add(A.acc + tid, K, -out, A.pos[tid + 1u]);
+                        total = signed_bins_to_double(A.acc + tid, K, st.acc_lo, st.acc_hi);
+                    }
+                    c = (float)(total / (double)cnt);
+                }
+                L.fresh[tid] = c;
+            }
+            if (ONE_WAVE) wave_lds_fence(); else __syncthreads();
+            bool unsorted = tid + 1u < K && !(c <= L.fresh[tid + 1u]);
+            if (ONE_WAVE) {
+                unsorted = __any(unsorted);
+            } else {
+                if (unsorted) A.disorder = 1u;
+                __syncthreads();
+                unsorted = A.disorder != 0u;
+            }
+            if (centre) {
+                u32 rank = tid;
+                if (unsorted) {
+                    rank = 0;
+#pragma unroll 1
+                    for (u32 j = 0; j < K; ++j) {
+                        const float cj = L.fresh[j];
+                        rank += (cj < c || (cj == c && j < tid)) ? 1u : 0u;
+                    }
+                }
+                L.C[rank] = c;
+            }
+            if (ONE_WAVE) wave_lds_fence();
+            else { __syncthreads(); if (tid == 0) A.disorder = 0u; }
         }
     }
-    if (tid < K) S.C[iters & 1u][tid] = L.C[tid];
+    __syncthreads();
+    if (centre) S.C[iters & 1u][tid] = L.C[tid];
     if (tid <= EXCP_MAX_K) S.cut[iters & 1u][tid] = tid ? L.cut[tid] : 0u;
 }
+
+// What the streams that many workgroups take are cut into.
+template <u32 KMAX>
+__global__ __launch_bounds__(LLOYD_THREADS) void k_km_units(Workspace w, GroupParams g) { lloyd_units<KMAX>(w, g); }
 
 // One iteration of the streams that many workgroups take: a workgroup for each work unit, which is an even share of the
 // stream's cut buckets (the grid is the most units the group can have; those beyond the units there are have nothing
@@ -1366,7 +1848,7 @@ __global__ __launch_bounds__(LLOYD_THREADS, 2u * lloyd_per_cu(KMAX)) void k_km_i
         if (tid < K) nxt[EXCP_ABSM_BINS * K + tid] = 0;
     }
     if (i == (u32)g.iters) return;
-    const u32 T = lloyd_cut_buckets(st, kp2, L);
+    const u32 T = lloyd_cut_buckets(st, kp2, L, nullptr);
     const u32 x0 = (u32)(((u64)T * u_first) / nu), x1 = (u32)(((u64)T * (u_first + 1u)) / nu);
     if (x1 - x0 <= LLOYD_FEW) {
         lloyd_few(gptr(seg_part(w, sidx)), x0, x1, K, kp2, acc, L);
@@ -1604,7 +2086,10 @@ void launch_km_partition(const Workspace &w, const GroupParams &g, int phase, hi
     if (!g.ntensors) return;
     const u32 nseg = 3 * g.ntensors;
     switch (phase) {
-        case 0: hipLaunchKernelGGL(k_km_sample, dim3(nseg), dim3(SM_THREADS), 0, s, w, g); break;
+        case 0:
+            if (g.fine) hipLaunchKernelGGL(k_km_draw<4>, dim3(nseg * DRAW_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
+            else hipLaunchKernelGGL(k_km_draw<2>, dim3(nseg * DRAW_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
+            hipLaunchKernelGGL(k_km_sample, dim3(nseg), dim3(SM_THREADS), 0, s, w, g); break;
         case 1: hipLaunchKernelGGL(k_km_scan, dim3(nseg), dim3(SCAN_PARTS * 64), 0, s, w, g); break;
         case 2: hipLaunchKernelGGL(k_km_scatter, dim3(excp_grid(w, 1)), dim3(SC_THREADS), 0, s, w, g); break;
         default:
@@ -1624,6 +2109,17 @@ void launch_km_partition(const Workspace &w, const GroupParams &g, int phase, hi
     }
 }
 
+// Cells for the group's larger tensors, by the largest (EXCP_FINE_): registers for buckets of 8192 values, which the tensors
+// are not expected to exceed, of 40 960 in sixteen waves, or of 53 248 in eight, which take longer (16.8 M elements 40
+// instead of 31 us).
+void launch_km_cells(const Workspace &w, const GroupParams &g, hipStream_t s) {
+    if (!g.fine) return;
+    const dim3 grid(3u * g.fine * NBKT);
+    if (g.fine_size == 0u) hipLaunchKernelGGL((k_km_cells<512, 8192, 8192>), grid, dim3(512), 0, s, w, g);
+    else if (g.fine_size == 1u) hipLaunchKernelGGL((k_km_cells<1024, 40960, 20480>), grid, dim3(1024), 0, s, w, g);
+    else hipLaunchKernelGGL((k_km_cells<512, 53248, 26624>), grid, dim3(512), 0, s, w, g);
+}
+
 void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s) {
     if (!g.ntensors) return;
     const u32 per = (u32)g.K + 1u;
@@ -1636,20 +2132,31 @@ void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s) {
     }
 }
 
-// All iterations: the streams that one workgroup takes through them, then, if the group may have others, a launch per
-// iteration and one for the final centres.
+// All iterations: the streams that one workgroup takes through them, and, if the group may have others, a launch per
+// iteration and one for the final centres.  The two kinds have nothing to do with each other and neither fills the GPU, so one
+// goes to a stream of its own: the launches, where cells make it likely that no stream takes them (then they are empty, 4.5 us
+// each, which pass beside the first kind), otherwise the single one (the 410M shape: 219 us beside 186), because what begins on
+// the other stream begins some 15 us later.
 template <u32 KMAX>
-static void launch_lloyd(const Workspace &w, const GroupParams &g, hipStream_t s) {
-    hipLaunchKernelGGL(k_km_lloyd<KMAX>, dim3(3 * g.ntensors + (g.slots ? 1 : 0)), dim3(LLOYD_THREADS), 0, s, w, g);
-    if (!g.slots) return;
-    const u32 units = excp_lloyd_grid(excp_grid(w, lloyd_per_cu(KMAX)), g.slots);
-    for (u32 i = 0; i <= (u32)g.iters; ++i) hipLaunchKernelGGL(k_km_iter<KMAX>, dim3(units), dim3(LLOYD_THREADS), 0, s, w, g, i);
+static void launch_lloyd(const Workspace &w, const GroupParams &g, hipStream_t s, const SideStream &side) {
+    const hipStream_t many = g.fine ? side.stream : s, one = g.fine || !g.slots ? s : side.stream;
+    if (g.slots) {
+        (void)hipEventRecord(side.fork, s);
+        (void)hipStreamWaitEvent(side.stream, side.fork, 0);
+        if (one != s) hipLaunchKernelGGL(k_km_lloyd<KMAX>, dim3(3 * g.ntensors), dim3(LLOYD_THREADS), 0, one, w, g);
+        hipLaunchKernelGGL(k_km_units<KMAX>, dim3(1), dim3(LLOYD_THREADS), 0, many, w, g);
+        const u32 units = excp_lloyd_grid(excp_grid(w, lloyd_per_cu(KMAX)), g.slots);
+        for (u32 i = 0; i <= (u32)g.iters; ++i) hipLaunchKernelGGL(k_km_iter<KMAX>, dim3(units), dim3(LLOYD_THREADS), 0, many, w, g, i);
+        (void)hipEventRecord(side.join, side.stream);
+    }
+    if (one == s) hipLaunchKernelGGL(k_km_lloyd<KMAX>, dim3(3 * g.ntensors), dim3(LLOYD_THREADS), 0, s, w, g);
+    if (g.slots) (void)hipStreamWaitEvent(s, side.join, 0);
 }
-void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s) {
+void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s, const SideStream &side) {
     if (!g.ntensors) return;
-    if (g.K <= 15) launch_lloyd<15>(w, g, s);
-    else if (g.K <= 63) launch_lloyd<63>(w, g, s);
-    else launch_lloyd<EXCP_MAX_K>(w, g, s);
+    if (g.K <= 15) launch_lloyd<15>(w, g, s, side);
+    else if (g.K <= 63) launch_lloyd<63>(w, g, s, side);
+    else launch_lloyd<EXCP_MAX_K>(w, g, s, side);
 }
 
 void launch_assign_pack(const Workspace &w, const GroupParams &g, hipStream_t s) {
