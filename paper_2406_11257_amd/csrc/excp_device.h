@@ -179,6 +179,7 @@ struct Workspace {
     // survivor passes
     u32 *chunk_total;         // [1]
     u32 *seg_chunk_begin;     // [segments + 1] first chunk of every survivor stream
+    u32 *scan_ticket;         // [1] tensors whose survivors have been counted (0 between launches)
     u32 *lloyd_shared;        // [1] TState::lloyd_shared of some tensor of the group
     u32 *seg_unit_begin;      // [segments + 1] first work unit of every survivor stream in a Lloyd iteration that many workgroups take
     float *pw, *pm, *pv;      // survivors partitioned into value-ordered buckets (same offsets as xw/xm/xv)
@@ -202,7 +203,7 @@ struct Workspace {
     u64 *dec_part;                // [descriptor][16] tile-count totals of each sixteenth of a tensor's tiles
     u32 *dec_kinds;               // [1] kinds of blob in the group being decoded: 1 fp32 weights, 2 16-bit weights, 4 unquantised
     // results
-    HostRec *rec_dev;
+    HostRec *rec_dev;         // (host memory, except in the static call)
     u32 rec_base;             // index of this group's first tensor in rec_dev
     int cus;                  // compute units of the device
 };
@@ -281,9 +282,8 @@ static inline u32 excp_lloyd_grid(u32 at_once, u32 slots) { return at_once + 6u 
 
 void launch_zero_u32(u32 *p, u64 count, hipStream_t s);
 void launch_copy_probe(const void *src, void *dst, u64 bytes, hipStream_t s);
-void launch_stats(const Workspace &w, const GroupParams &g, int phase, hipStream_t s);
+void launch_stats(const Workspace &w, const GroupParams &g, int phase, const TDesc *single, hipStream_t s);
 void launch_mask_compact(const Workspace &w, const GroupParams &g, int phase, hipStream_t s);
-void launch_layout(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_km_partition(const Workspace &w, const GroupParams &g, int phase, hipStream_t s);
 void launch_km_cells(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s);
@@ -291,10 +291,10 @@ void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s);
 struct SideStream { hipStream_t stream; hipEvent_t fork, join; };
 void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s, const SideStream &side);
 void launch_assign_pack(const Workspace &w, const GroupParams &g, hipStream_t s);
-void launch_finalize(const Workspace &w, const GroupParams &g, hipStream_t s);
-void launch_decode_from_compress(const Workspace &w, const GroupParams &g, hipStream_t s);
-void launch_decode_prep(const Workspace &w, u32 ntensors, u32 ntiles, u32 largest, bool allow_raw, bool moments, hipStream_t s);
-void launch_decode_single_setup(const Workspace &w, const DDesc &d, hipStream_t s);
+void launch_finalize(const Workspace &w, const GroupParams &g, bool decode, hipStream_t s);
+void launch_decode_prep(const Workspace &w, u32 ntensors, u32 ntiles, u32 largest, bool allow_raw, bool moments, bool records, const DDesc *single, hipStream_t s);
+static inline bool excp_prep_small(u32 largest) { return largest <= 32u; }      // tiles of the largest tensor of a group that takes one launch
+void launch_decode_small(const Workspace &w, u32 ntensors, u32 ntiles, bool moments, bool w16, hipStream_t s);
 void launch_decode_main16(const Workspace &w, u32 ntensors, u32 ntiles, bool moments, hipStream_t s);
 void launch_decode_raw(const Workspace &w, u32 ntensors, u32 ntiles, bool moments, hipStream_t s);
 void launch_store_raw(const Workspace &w, const GroupParams &g, hipStream_t s);

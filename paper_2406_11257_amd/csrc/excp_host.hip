@@ -47,11 +47,11 @@ struct excp_ctx {
     u64 max_tensor = 0, max_group = 0, max_tiles = 0;
     Workspace w{};
     // per-batch arrays (device) and their pinned staging (host)
-    TDesc *desc_all = nullptr; TState *st_all = nullptr; u32 *cand_ctr_all = nullptr;
-    DDesc *ddesc_all = nullptr; DState *dst_all = nullptr;
-    CDesc *cdesc_all = nullptr; CDesc *h_cdesc = nullptr;
-    u32 *tile_begin_all = nullptr;
-    TDesc *h_desc = nullptr; DDesc *h_ddesc = nullptr; u32 *h_tile_begin = nullptr; HostRec *h_rec = nullptr;
+    TState *st_all = nullptr; u32 *cand_ctr_all = nullptr;
+    DDesc *ddesc_all = nullptr; DState *dst_all = nullptr;       // (ddesc_all: of the blobs that a compress call decodes itself)
+    // descriptors and tile tables of a call, one after the other (see Staged): pinned, and the device's copy
+    unsigned char *h_stage = nullptr, *d_stage = nullptr;
+    HostRec *h_rec = nullptr;
     u64 ws_bytes = 0;
     std::vector<void *> allocs;
     // pending batch
@@ -74,6 +74,24 @@ struct excp_ctx {
 };
 
 namespace {
+
+// What a call stages lies back to back, so that it is one copy whatever its parts; a call about one tensor whose first
+// kernel takes the description as an argument copies nothing.
+constexpr size_t kStageBytes = kMaxBatchTensors * (sizeof(DDesc) + sizeof(CDesc) > sizeof(TDesc) ? sizeof(DDesc) + sizeof(CDesc) : sizeof(TDesc)) +
+                               (kMaxBatchTensors * 2 + 16) * sizeof(u32) + 64;
+template <class T>
+struct Staged { T *h, *d; };
+struct Staging {
+    excp_ctx *c;
+    size_t used = 0;
+    template <class T>
+    Staged<T> take(size_t count) {
+        const size_t at = used;
+        used = (used + count * sizeof(T) + 15) & ~(size_t)15;
+        return {(T *)(c->h_stage + at), (T *)(c->d_stage + at)};
+    }
+    bool copy() const { return used == 0 || hipMemcpyAsync(c->d_stage, c->h_stage, used, hipMemcpyHostToDevice, c->stream) == hipSuccess; }
+};
 
 template <class T>
 bool dev_alloc(excp_ctx *c, T **p, u64 count) {
@@ -149,8 +167,9 @@ void make_groups(int count, u64 cap_elems, GetN get_n, u64 cap_some, Some some, 
 }
 
 // `w32`, `w16`: the group has tensors of fp32 / of 16-bit weights (blobs of the other kind are refused).
-void run_decode_main(excp_ctx *c, const Workspace &w, u32 ntensors, u32 ntiles, bool moments, bool w32, bool w16) {
+void run_decode_main(excp_ctx *c, const Workspace &w, u32 ntensors, u32 ntiles, bool small, bool moments, bool w32, bool w16) {
     StageTimer t(c, ST_DECODE_MAIN);
+    if (small && w32 != w16) { launch_decode_small(w, ntensors, ntiles, moments, w16, c->stream); return; }
     if (w32) launch_decode_main(w, ntensors, ntiles, moments, c->stream);
     if (w16) launch_decode_main16(w, ntensors, ntiles, moments, c->stream);
     launch_decode_raw(w, ntensors, ntiles, moments, c->stream);     // blobs written without quantisation, if any
@@ -172,52 +191,47 @@ int run_dense(excp_ctx *c, int count, bool exporting, Fill fill) {
     std::vector<u32> &tb_offsets = c->tb_offsets;
     groups.clear(); tb_offsets.clear();
     make_groups(count, c->max_group, [&](u32 i) { DDesc d; fill(i, d); return (u64)d.n; }, kNoLimit, [](u32) { return false; }, groups);
+    Staging stage{c};
+    const Staged<DDesc> descs = stage.take<DDesc>(count);
+    const Staged<u32> tiles = stage.take<u32>(count + groups.size());
     u32 tb_off = 0;
     for (const Group &g : groups) {
         u32 tile = 0;
         tb_offsets.push_back(tb_off);
         for (u32 q = 0; q < g.count; ++q) {
-            DDesc &d = c->h_ddesc[g.first + q];
+            DDesc &d = descs.h[g.first + q];
             fill(g.first + q, d);
             d.tile_begin = tile; d.tile_count = (u32)((d.n + EXCP_TILE - 1) / EXCP_TILE);
-            c->h_tile_begin[tb_off + q] = tile;
+            tiles.h[tb_off + q] = tile;
             tile += d.tile_count;
         }
-        c->h_tile_begin[tb_off + g.count] = tile;
+        tiles.h[tb_off + g.count] = tile;
         tb_off += g.count + 1;
     }
     hipStream_t s = c->stream;
-    if (count) {
-        if (hipMemcpyAsync(c->ddesc_all, c->h_ddesc, sizeof(DDesc) * count, hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(c->tile_begin_all, c->h_tile_begin, sizeof(u32) * tb_off, hipMemcpyHostToDevice, s) != hipSuccess)
-            return enqueue_failed(c);
-    }
+    if (count && !stage.copy()) return enqueue_failed(c);
     for (size_t gi = 0; gi < groups.size(); ++gi) {
         const Group &g = groups[gi];
         Workspace w = c->w;
-        w.ddesc = c->ddesc_all + g.first;
+        w.ddesc = descs.d + g.first;
         w.dst = c->dst_all + g.first;
-        w.tile_begin = c->tile_begin_all + tb_offsets[gi];
+        w.tile_begin = tiles.d + tb_offsets[gi];
         w.rec_dev = c->w.rec_dev + g.first;
         w.rec_base = 0;
         if (exporting) {
             bool moments = false;
             for (u32 q = 0; q < g.count; ++q)
-                moments = moments || c->h_ddesc[g.first + q].cm != nullptr || c->h_ddesc[g.first + q].cv != nullptr;
+                moments = moments || descs.h[g.first + q].cm != nullptr || descs.h[g.first + q].cv != nullptr;
             {
                 StageTimer t(c, ST_DECODE_PREP);
-                launch_decode_prep(w, g.count, g.ntiles, largest_tiles(c->h_ddesc + g.first, g.count), false, moments, s);
+                launch_decode_prep(w, g.count, g.ntiles, largest_tiles(descs.h + g.first, g.count), false, moments, true, nullptr, s);
             }
             { StageTimer t(c, ST_EXPORT_DENSE); launch_export_dense(w, g.count, g.ntiles, moments, s); }
         } else {
             { StageTimer t(c, ST_MISC); launch_dense_parse(w, g.count, s); }
             { StageTimer t(c, ST_DECODE_DENSE); launch_decode_dense(w, g.count, g.ntiles, s); }
+            { StageTimer t(c, ST_MISC); launch_decode_finish(w, g.count, s); }      // (codes out of range are found by the pass)
         }
-        { StageTimer t(c, ST_MISC); launch_decode_finish(w, g.count, s); }
-    }
-    if (count) {
-        if (hipMemcpyAsync(c->h_rec, c->w.rec_dev, sizeof(HostRec) * count, hipMemcpyDeviceToHost, s) != hipSuccess)
-            return enqueue_failed(c);
     }
     if (hipGetLastError() != hipSuccess) return enqueue_failed(c);
     c->pending = 2;
@@ -333,13 +347,11 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     const u64 chunks_group = 3 * (G / EXCP_CHUNK) + 3 * kMaxGroupTensors + 3;
     c->max_tiles = max_tiles;
     bool ok = true;
-    ok = ok && dev_alloc(c, &c->desc_all, kMaxBatchTensors);
+    ok = ok && dev_alloc(c, &c->d_stage, kStageBytes);
     ok = ok && dev_alloc(c, &c->st_all, kMaxBatchTensors);
     ok = ok && dev_alloc(c, &c->cand_ctr_all, (u64)kMaxBatchTensors * 512);
     ok = ok && dev_alloc(c, &c->ddesc_all, kMaxBatchTensors);
     ok = ok && dev_alloc(c, &c->dst_all, kMaxBatchTensors);
-    ok = ok && dev_alloc(c, &c->cdesc_all, kMaxBatchTensors);
-    ok = ok && dev_alloc(c, &c->tile_begin_all, (u64)kMaxBatchTensors * 2 + 16);
     ok = ok && dev_alloc(c, &w.seg, 3ull * kMaxGroupTensors);
     ok = ok && dev_alloc(c, &w.xw, G);
     ok = ok && dev_alloc(c, &w.xm, G);
@@ -355,6 +367,7 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.mask_bo, 2 * max_tiles * 32);
     ok = ok && dev_alloc(c, &w.chunk_total, 4);
     ok = ok && dev_alloc(c, &w.seg_chunk_begin, 3ull * kMaxGroupTensors + 4);
+    ok = ok && dev_alloc(c, &w.scan_ticket, 1);
     ok = ok && dev_alloc(c, &w.lloyd_shared, 1);
     ok = ok && dev_alloc(c, &w.seg_unit_begin, 3ull * kMaxGroupTensors + 4);
     const u64 nseg_max = 3ull * kMaxGroupTensors;
@@ -382,13 +395,11 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.dec_cnt_o, max_tiles * EXCP_MAX_CHAIN);
     ok = ok && dev_alloc(c, &w.dec_kinds, 4);
     ok = ok && dev_alloc(c, &w.dec_part, (u64)kMaxGroupTensors * 16);
-    ok = ok && dev_alloc(c, &w.rec_dev, kMaxBatchTensors);
     if (ok) {
-        ok = hipHostMalloc((void **)&c->h_desc, sizeof(TDesc) * kMaxBatchTensors) == hipSuccess &&
-             hipHostMalloc((void **)&c->h_ddesc, sizeof(DDesc) * kMaxBatchTensors) == hipSuccess &&
-             hipHostMalloc((void **)&c->h_cdesc, sizeof(CDesc) * kMaxBatchTensors) == hipSuccess &&
-             hipHostMalloc((void **)&c->h_tile_begin, sizeof(u32) * (kMaxBatchTensors * 2 + 16)) == hipSuccess &&
-             hipHostMalloc((void **)&c->h_rec, sizeof(HostRec) * kMaxBatchTensors) == hipSuccess;
+        // (the kernels write the results where the host reads them: no copy back)
+        ok = hipHostMalloc((void **)&c->h_stage, kStageBytes) == hipSuccess &&
+             hipHostMalloc((void **)&c->h_rec, sizeof(HostRec) * kMaxBatchTensors) == hipSuccess &&
+             hipHostGetDevicePointer((void **)&w.rec_dev, c->h_rec, 0) == hipSuccess;
     }
     if (ok) {
         hipDeviceProp_t prop;
@@ -402,6 +413,7 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     if (ok) {
         launch_zero_u32(w.med_hist, (u64)kMaxGroupTensors * 2048, c->stream);
         launch_zero_u32(w.sel_ticket, kMaxGroupTensors, c->stream);
+        launch_zero_u32(w.scan_ticket, 1, c->stream);
         ok = hipStreamSynchronize(c->stream) == hipSuccess;
     }
     if (!ok) { excp_destroy(c); return EXCP_E_HIP; }
@@ -417,10 +429,7 @@ void excp_destroy(excp_ctx *c) {
     if (c->side.fork) (void)hipEventDestroy(c->side.fork);
     if (c->side.join) (void)hipEventDestroy(c->side.join);
     for (void *p : c->allocs) (void)hipFree(p);
-    if (c->h_desc) (void)hipHostFree(c->h_desc);
-    if (c->h_ddesc) (void)hipHostFree(c->h_ddesc);
-    if (c->h_cdesc) (void)hipHostFree(c->h_cdesc);
-    if (c->h_tile_begin) (void)hipHostFree(c->h_tile_begin);
+    if (c->h_stage) (void)hipHostFree(c->h_stage);
     if (c->h_rec) (void)hipHostFree(c->h_rec);
     for (auto &s : c->spans) { (void)hipEventDestroy(s.a); (void)hipEventDestroy(s.b); }
     for (auto e : c->free_events) (void)hipEventDestroy(e);
@@ -507,6 +516,9 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         for (u32 q = 0; q < g.count; ++q) any = any || !small(g.first + q);
         return any && 3u * g.count <= (u32)c->w.cus;
     };
+    Staging stage{c};
+    const Staged<TDesc> descs = stage.take<TDesc>(count);
+    const Staged<u32> tiles = stage.take<u32>(count + groups.size());
     u32 tb_off = 0;
     for (const Group &g : groups) {
         u64 elem_off = 0, cand_off = 0; u32 tile = 0, slot = 0;
@@ -514,7 +526,7 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         const bool together = lloyd_together(g);
         for (u32 q = 0; q < g.count; ++q) {
             const excp_tensor &t = tensors[g.first + q];
-            TDesc &d = c->h_desc[g.first + q];
+            TDesc &d = descs.h[g.first + q];
             d.Wp = (const float *)t.W_prev_recon; d.W = (const float *)t.W_t; d.m = t.m_t; d.v = t.v_t; d.n = t.n;
             d.blob = (unsigned char *)t.blob; d.blob_cap = t.blob_cap; d.W_out = (float *)t.W_recon_out;
             d.elem_off = elem_off; d.tile_begin = tile;
@@ -523,7 +535,7 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             cand_off += d.cand_cap;
             d.tile_count = (u32)((t.n + EXCP_TILE - 1) / EXCP_TILE);
             d.acc_slot = t.n && (together || !small(g.first + q)) ? slot++ : EXCP_NO_SLOT; d.pad = 0;
-            c->h_tile_begin[tb_off + q] = tile;
+            tiles.h[tb_off + q] = tile;
             elem_off += t.n; tile += d.tile_count;
         }
         // the tensors by size, powers of two apart, the largest first
@@ -531,27 +543,22 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         auto size_class = [&](u32 q) { const u64 n = tensors[g.first + q].n; return n ? (u32)__builtin_clzll(n) : 64u; };
         for (u32 q = 0; q < g.count; ++q) ++at[size_class(q)];
         for (u32 k = 0, sum = 0; k < 65; ++k) { const u32 here = at[k]; at[k] = sum; sum += here; }
-        for (u32 q = 0; q < g.count; ++q) c->h_desc[g.first + at[size_class(q)]++].turn = q;
-        c->h_tile_begin[tb_off + g.count] = tile;
+        for (u32 q = 0; q < g.count; ++q) descs.h[g.first + at[size_class(q)]++].turn = q;
+        tiles.h[tb_off + g.count] = tile;
         tb_off += g.count + 1;
     }
     hipStream_t s = c->stream;
-    if (count) {
-        if (hipMemcpyAsync(c->desc_all, c->h_desc, sizeof(TDesc) * count, hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(c->tile_begin_all, c->h_tile_begin, sizeof(u32) * tb_off, hipMemcpyHostToDevice, s) != hipSuccess)
-            return enqueue_failed(c);
-        launch_zero_u32((u32 *)c->st_all, (u64)count * sizeof(TState) / 4, s);
-        launch_zero_u32(c->cand_ctr_all, (u64)count * 512, s);
-    }
+    const bool single = count == 1;
+    if (!single && !stage.copy()) return enqueue_failed(c);
     for (size_t gi = 0; gi < groups.size(); ++gi) {
         const Group &g = groups[gi];
         Workspace w = c->w;
-        w.desc = c->desc_all + g.first;
+        w.desc = descs.d + g.first;
         w.st = c->st_all + g.first;
         w.cand_ctr = c->cand_ctr_all + (u64)g.first * 512;
         w.ddesc = c->ddesc_all + g.first;
         w.dst = c->dst_all + g.first;
-        w.tile_begin = c->tile_begin_all + tb_offsets[gi];
+        w.tile_begin = tiles.d + tb_offsets[gi];
         w.rec_base = 0;
         w.rec_dev = c->w.rec_dev + g.first;
         GroupParams p{};
@@ -564,17 +571,16 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             p.together = lloyd_together(g) ? 1u : 0u;
             for (u32 q = 0; q < g.count; ++q) p.fine += p.together && !w16 && elems <= EXCP_FINE_LARGEST && excp_fine_tensor(tensors[g.first + q].n) ? 1u : 0u;
             p.alone_work = p.fine ? kAloneCells : (p.together ? kAloneTogether : (K < 63 ? kAloneFew : kAloneMany));
-            for (u32 q = 0; q < g.count; ++q) p.slots += c->h_desc[g.first + q].acc_slot != EXCP_NO_SLOT ? 1u : 0u;
+            for (u32 q = 0; q < g.count; ++q) p.slots += descs.h[g.first + q].acc_slot != EXCP_NO_SLOT ? 1u : 0u;
         }
         p.unit_shift = excp_unit_shift(elems, g.count, excp_gather_subs(g.ntiles, (u32)w.cus), (u32)w.cus, excp_count_rows(c->max_group, kMaxGroupTensors));
         p.fine_size = largest <= EXCP_FINE_SMALL ? 0u : (largest <= EXCP_FINE_MIDDLE ? 1u : 2u);
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
-        { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, s); }
-        { StageTimer t(c, ST_STATS); launch_stats(w, p, 1, s); }
-        { StageTimer t(c, ST_SELECT); launch_stats(w, p, 2, s); }
+        { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, single ? descs.h : nullptr, s); }
+        { StageTimer t(c, ST_STATS); launch_stats(w, p, 1, nullptr, s); }
+        { StageTimer t(c, ST_SELECT); launch_stats(w, p, 2, nullptr, s); }
         { StageTimer t(c, ST_MASK_COMPACT); launch_mask_compact(w, p, 0, s); }
         { StageTimer t(c, ST_MASK_SCAN); launch_mask_compact(w, p, 1, s); }
-        { StageTimer t(c, ST_LAYOUT); launch_layout(w, p, s); }
         // the value -> bucket maps come from the slots, before the pass that makes the dense survivor arrays:
         // that pass also takes the bucket counts
         if (!raw) { StageTimer t(c, ST_KM_SAMPLE); launch_km_partition(w, p, 0, s); }
@@ -589,21 +595,15 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             { StageTimer t(c, ST_KM_ITER); launch_km_iter(w, p, s, c->side); }
             { StageTimer t(c, ST_ASSIGN_PACK); launch_assign_pack(w, p, s); }
         }
-        { StageTimer t(c, ST_FINALIZE); launch_finalize(w, p, s); }
         bool any_out = false;
         for (u32 q = 0; q < g.count; ++q) any_out = any_out || tensors[g.first + q].W_recon_out != nullptr;
+        { StageTimer t(c, ST_FINALIZE); launch_finalize(w, p, any_out, s); }
         if (any_out) {
-            // (the per-tile survivor counts come from the mask pass: no bitmap counting here)
-            { StageTimer t(c, ST_MISC); launch_decode_from_compress(w, p, s); }
             StageTimer t(c, ST_DECODE_MAIN);
             if (raw) launch_decode_raw(w, g.count, g.ntiles, false, s);
             else if (flags & 0x30u) launch_decode_main16(w, g.count, g.ntiles, false, s);
             else launch_decode_main(w, g.count, g.ntiles, false, s);
         }
-    }
-    if (count) {
-        if (hipMemcpyAsync(c->h_rec, c->w.rec_dev, sizeof(HostRec) * count, hipMemcpyDeviceToHost, s) != hipSuccess)
-            return enqueue_failed(c);
     }
     if (hipGetLastError() != hipSuccess) return enqueue_failed(c);
     c->pending = 1;
@@ -628,35 +628,35 @@ int excp_decompress_tensors(excp_ctx *c, int count, const excp_blob *blobs) {
     std::vector<u32> &tb_offsets = c->tb_offsets;
     groups.clear(); tb_offsets.clear();
     make_groups(count, c->max_group, [&](u32 i) { return (u64)blobs[i].n; }, kNoLimit, [](u32) { return false; }, groups);
+    Staging stage{c};
+    const Staged<DDesc> descs = stage.take<DDesc>(count);
+    const Staged<u32> tiles = stage.take<u32>(count + groups.size());
     u32 tb_off = 0;
     for (const Group &g : groups) {
         u32 tile = 0;
         tb_offsets.push_back(tb_off);
         for (u32 q = 0; q < g.count; ++q) {
             const excp_blob &b = blobs[g.first + q];
-            DDesc &d = c->h_ddesc[g.first + q];
+            DDesc &d = descs.h[g.first + q];
             d.Wp = (const float *)b.W_prev_recon; d.blob = (const unsigned char *)b.blob; d.blob_bytes = b.blob_bytes; d.n = b.n;
             d.W_out = (float *)b.W_recon_out; d.m_out = b.m_out; d.v_out = b.v_out;
             d.cw = d.cm = d.cv = d.head = nullptr; d.wtype = (b.flags >> 4) & 3u; d.pad = 0;
             d.tile_begin = tile; d.tile_count = (u32)((b.n + EXCP_TILE - 1) / EXCP_TILE);
-            c->h_tile_begin[tb_off + q] = tile;
+            tiles.h[tb_off + q] = tile;
             tile += d.tile_count;
         }
-        c->h_tile_begin[tb_off + g.count] = tile;
+        tiles.h[tb_off + g.count] = tile;
         tb_off += g.count + 1;
     }
     hipStream_t s = c->stream;
-    if (count) {
-        if (hipMemcpyAsync(c->ddesc_all, c->h_ddesc, sizeof(DDesc) * count, hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(c->tile_begin_all, c->h_tile_begin, sizeof(u32) * tb_off, hipMemcpyHostToDevice, s) != hipSuccess)
-            return enqueue_failed(c);
-    }
+    const bool single = count == 1;
+    if (!single && !stage.copy()) return enqueue_failed(c);
     for (size_t gi = 0; gi < groups.size(); ++gi) {
         const Group &g = groups[gi];
         Workspace w = c->w;
-        w.ddesc = c->ddesc_all + g.first;
+        w.ddesc = descs.d + g.first;
         w.dst = c->dst_all + g.first;
-        w.tile_begin = c->tile_begin_all + tb_offsets[gi];
+        w.tile_begin = tiles.d + tb_offsets[gi];
         w.rec_dev = c->w.rec_dev + g.first;
         w.rec_base = 0;
         bool moments = false, w32 = false, w16 = false;
@@ -665,16 +665,12 @@ int excp_decompress_tensors(excp_ctx *c, int count, const excp_blob *blobs) {
             moments = moments || b.m_out != nullptr || b.v_out != nullptr;
             if (b.flags & 0x30u) w16 = true; else w32 = true;
         }
+        const u32 largest = largest_tiles(descs.h + g.first, g.count);
         {
             StageTimer t(c, ST_DECODE_PREP);
-            launch_decode_prep(w, g.count, g.ntiles, largest_tiles(c->h_ddesc + g.first, g.count), true, moments, s);
+            launch_decode_prep(w, g.count, g.ntiles, largest, true, moments, true, single ? descs.h : nullptr, s);
         }
-        run_decode_main(c, w, g.count, g.ntiles, moments, w32, w16);
-        { StageTimer t(c, ST_MISC); launch_decode_finish(w, g.count, s); }
-    }
-    if (count) {
-        if (hipMemcpyAsync(c->h_rec, c->w.rec_dev, sizeof(HostRec) * count, hipMemcpyDeviceToHost, s) != hipSuccess)
-            return enqueue_failed(c);
+        run_decode_main(c, w, g.count, g.ntiles, excp_prep_small(largest), moments, w32, w16);
     }
     if (hipGetLastError() != hipSuccess) return enqueue_failed(c);
     c->pending = 2;
@@ -752,6 +748,10 @@ int excp_reconstruct_chain(excp_ctx *c, int count, const excp_chain *chains) {
     // any tensor the context accepts fits with its whole chain).
     std::vector<CGroup> &groups = c->cgroups;
     groups.clear();
+    Staging stage{c};
+    const Staged<DDesc> descs = stage.take<DDesc>(total_descs);
+    const Staged<CDesc> cdescs = stage.take<CDesc>(count);
+    const Staged<u32> tiles = stage.take<u32>(kMaxBatchTensors * 2 + 16);
     u32 tb_off = 0, desc_off = 0;
     for (u32 i = 0; i < (u32)count;) {
         CGroup g{i, 0, desc_off, 0, 0, 0, 0};
@@ -767,52 +767,48 @@ int excp_reconstruct_chain(excp_ctx *c, int count, const excp_chain *chains) {
         u32 dtile = 0, ctile = 0, d = 0;
         for (u32 q = 0; q < g.count; ++q) {
             const excp_chain &ch = chains[g.first + q];
-            const u32 tiles = (u32)((ch.n + EXCP_TILE - 1) / EXCP_TILE);
-            CDesc &cd = c->h_cdesc[g.first + q];
+            const u32 ntiles = (u32)((ch.n + EXCP_TILE - 1) / EXCP_TILE);
+            CDesc &cd = cdescs.h[g.first + q];
             cd.W0 = (const float *)ch.W0; cd.W_out = (float *)ch.W_out; cd.n = ch.n; cd.first_desc = d; cd.steps = (u32)ch.steps;
-            cd.tile_begin = ctile; cd.tile_count = tiles;
-            c->h_tile_begin[g.tb_chain + q] = ctile;
-            ctile += tiles;
+            cd.tile_begin = ctile; cd.tile_count = ntiles;
+            tiles.h[g.tb_chain + q] = ctile;
+            ctile += ntiles;
             for (int j = 0; j < ch.steps; ++j, ++d) {
-                DDesc &dd = c->h_ddesc[desc_off + d];
+                DDesc &dd = descs.h[desc_off + d];
                 const bool last = j + 1 == ch.steps;
                 dd.Wp = nullptr; dd.blob = (const unsigned char *)ch.blobs[j]; dd.blob_bytes = ch.blob_bytes[j]; dd.n = ch.n;
                 dd.W_out = nullptr; dd.m_out = last ? ch.m_out : nullptr; dd.v_out = last ? ch.v_out : nullptr;
                 dd.cw = dd.cm = dd.cv = dd.head = nullptr; dd.wtype = (ch.flags >> 4) & 3u; dd.pad = 0;
-                dd.tile_begin = dtile; dd.tile_count = tiles;
-                c->h_tile_begin[g.tb_desc + d] = dtile;
-                dtile += tiles;
+                dd.tile_begin = dtile; dd.tile_count = ntiles;
+                tiles.h[g.tb_desc + d] = dtile;
+                dtile += ntiles;
             }
         }
-        c->h_tile_begin[g.tb_desc + g.ndescs] = dtile;
-        c->h_tile_begin[g.tb_chain + g.count] = ctile;
+        tiles.h[g.tb_desc + g.ndescs] = dtile;
+        tiles.h[g.tb_chain + g.count] = ctile;
         tb_off += g.ndescs + g.count + 2;
         desc_off += g.ndescs;
         groups.push_back(g);
     }
     hipStream_t s = c->stream;
-    if (count) {
-        if (hipMemcpyAsync(c->ddesc_all, c->h_ddesc, sizeof(DDesc) * desc_off, hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(c->cdesc_all, c->h_cdesc, sizeof(CDesc) * count, hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(c->tile_begin_all, c->h_tile_begin, sizeof(u32) * tb_off, hipMemcpyHostToDevice, s) != hipSuccess)
-            return enqueue_failed(c);
-    }
+    stage.used = (size_t)((unsigned char *)(tiles.h + tb_off) - c->h_stage);
+    if (count && !stage.copy()) return enqueue_failed(c);
     for (const CGroup &g : groups) {
         Workspace w = c->w;
-        w.ddesc = c->ddesc_all + g.first_desc;
+        w.ddesc = descs.d + g.first_desc;
         w.dst = c->dst_all + g.first_desc;
-        w.tile_begin = c->tile_begin_all + g.tb_desc;
-        w.cdesc = c->cdesc_all + g.first;
-        w.chain_tile_begin = c->tile_begin_all + g.tb_chain;
+        w.tile_begin = tiles.d + g.tb_desc;
+        w.cdesc = cdescs.d + g.first;
+        w.chain_tile_begin = tiles.d + g.tb_chain;
         w.rec_dev = c->w.rec_dev + g.first;
         w.rec_base = 0;
-        const u32 dtiles = c->h_tile_begin[g.tb_desc + g.ndescs];
+        const u32 dtiles = tiles.h[g.tb_desc + g.ndescs];
         bool moments = false;
         for (u32 q = 0; q < g.count; ++q)
             moments = moments || chains[g.first + q].m_out != nullptr || chains[g.first + q].v_out != nullptr;
         {
             StageTimer t(c, ST_DECODE_PREP);
-            launch_decode_prep(w, g.ndescs, dtiles, largest_tiles(c->h_ddesc + g.first_desc, g.ndescs), false, moments, s);
+            launch_decode_prep(w, g.ndescs, dtiles, largest_tiles(descs.h + g.first_desc, g.ndescs), false, moments, false, nullptr, s);
         }
         bool w16[2] = {false, false};                      // weight storage met in the group (a blob that says otherwise is refused)
         for (u32 q = 0; q < g.count; ++q) w16[(chains[g.first + q].flags & 0x30u) != 0] = true;
@@ -824,10 +820,6 @@ int excp_reconstruct_chain(excp_ctx *c, int count, const excp_chain *chains) {
             if (w16[1]) launch_decode_main16(w, g.ndescs, dtiles, true, s);
         }
         { StageTimer t(c, ST_MISC); launch_chain_finish(w, g.count, s); }
-    }
-    if (count) {
-        if (hipMemcpyAsync(c->h_rec, c->w.rec_dev, sizeof(HostRec) * count, hipMemcpyDeviceToHost, s) != hipSuccess)
-            return enqueue_failed(c);
     }
     if (hipGetLastError() != hipSuccess) return enqueue_failed(c);
     c->pending = 2;
@@ -928,15 +920,16 @@ int excp_decompress_step_static(int hip_device, void *hip_stream, const void *W_
     const u32 ntiles = d.tile_count;
     const bool moments = m_out != nullptr || v_out != nullptr;
 
-    // Nothing of the previous call is relied on: the descriptor, the tile table and the kinds word are
-    // written first, the state and every count of the tiles in use are written by the kernels before
-    // they are read, and the record is written last.
-    launch_decode_single_setup(w, d, s);
-    launch_decode_prep(w, 1, ntiles, ntiles, true, moments, s);
-    if (d.wtype == 0u) launch_decode_main(w, 1, ntiles, moments, s);
-    else launch_decode_main16(w, 1, ntiles, moments, s);
-    launch_decode_raw(w, 1, ntiles, moments, s);
-    launch_decode_finish(w, 1, s);
+    // Nothing of the previous call is relied on: the descriptor, the tile table and the kinds word are written by the first launch,
+    // the state, every count of the tiles in use and the record by the kernels before they are read.
+    launch_decode_prep(w, 1, ntiles, ntiles, true, moments, true, &d, s);
+    if (excp_prep_small(ntiles)) {
+        launch_decode_small(w, 1, ntiles, moments, d.wtype != 0u, s);
+    } else {
+        if (d.wtype == 0u) launch_decode_main(w, 1, ntiles, moments, s);
+        else launch_decode_main16(w, 1, ntiles, moments, s);
+        launch_decode_raw(w, 1, ntiles, moments, s);
+    }
     if (hipGetLastError() != hipSuccess) { (void)hipStreamSynchronize(s); return EXCP_E_HIP; }
     HostRec rec;
     memset(&rec, 0, sizeof(rec));

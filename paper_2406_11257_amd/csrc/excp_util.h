@@ -139,6 +139,12 @@ __device__ __forceinline__ void store_weight(float *p, u64 idx, u32 wt, float x)
     else ((unsigned short *)p)[idx] = (unsigned short)w16_narrow(x, wt == 2u);
 }
 
+// Which decoder takes a blob: 1 = codes and fp32 weights, 2 = codes and 16-bit weights, 4 = written
+// without quantisation (either weight storage).
+__device__ __forceinline__ u32 blob_kind(u32 nbits, u32 flags) {
+    return nbits == EXCP_RAW_BITS ? 4u : (excp_wtype(flags) != 0u ? 2u : 1u);
+}
+
 // Four consecutive weights of a tile: elements [off, off + 4) of the tile that starts at `tile0` (an
 // element pointer into an array of type wt), of which `rem` exist; one 16-byte (fp32) or 8-byte
 // (16-bit, if the array is 8-byte aligned) load where all four exist, else one by one; missing ones are 0.

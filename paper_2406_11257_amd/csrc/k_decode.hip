@@ -7,6 +7,8 @@
 // range of bitmap_o and a second scan.  The main pass is then independent per tile.
 #include "excp_util.h"
 
+#include <algorithm>
+
 namespace {
 
 __device__ __forceinline__ u64 range_mask(u32 lo_bit, u32 hi_bit) {   // bits [lo_bit, hi_bit), hi_bit <= 64
@@ -28,12 +30,6 @@ __device__ __forceinline__ u32 popcount_range_lane(const u64 *__restrict__ bm, u
         cnt += __popcll(word & range_mask(lo, hi));
     }
     return cnt;
-}
-
-// Which decoder takes a blob: 1 = codes and fp32 weights, 2 = codes and 16-bit weights, 4 = written
-// without quantisation (either weight storage).
-__device__ __forceinline__ u32 blob_kind(u32 nbits, u32 flags) {
-    return nbits == EXCP_RAW_BITS ? 4u : (excp_wtype(flags) != 0u ? 2u : 1u);
 }
 
 __device__ __forceinline__ bool wants_moments(const DDesc &D) {
@@ -76,6 +72,12 @@ __global__ void k_decode_parse(Workspace w, u32 ntensors, u32 allow_raw) {
     if (kind) atomicOr(w.dec_kinds, kind);
 }
 
+__device__ __forceinline__ void decode_record(const Workspace &w, u32 t, u64 n, const DState &S) {
+    HostRec R{};
+    R.n = n; R.n_w = S.n_w; R.n_o = S.n_o; R.blob_bytes = S.blob_bytes; R.status = S.status;
+    w.rec_dev[w.rec_base + t] = R;
+}
+
 // All that has to be known before the main pass, for groups of tensors of at most PREP_TILES tiles each, in one
 // launch: a workgroup per tensor parses the header, counts, and scans the counts.  Small tensors are bound by the
 // number of launches: parsing, counting and scanning are five (eight with the moments), of 2 to 4 us each and
@@ -83,18 +85,22 @@ __global__ void k_decode_parse(Workspace w, u32 ntensors, u32 allow_raw) {
 // one round of loads; larger tensors would leave the one workgroup behind the general path's many.
 constexpr u32 PREP_WAVES = 8, PREP_TILES = 4 * PREP_WAVES;
 
-__global__ __launch_bounds__(PREP_WAVES * 64) void k_decode_prep(Workspace w, u32 allow_raw, u32 moments) {
+// `single`: the only tensor's description comes as an argument and is left where the main pass looks for it.  `records`: the
+// results for the host are known here and written at once.
+__global__ __launch_bounds__(PREP_WAVES * 64) void k_decode_prep(Workspace w, u32 allow_raw, u32 moments, u32 records, DDesc one, u32 single) {
+    __shared__ DDesc D;
     __shared__ DState S;
     __shared__ u32 s_cnt[PREP_TILES], s_excl[PREP_TILES + 1];
     const u32 t = blockIdx.x, tid = threadIdx.x, lane = tid & 63u;
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-    const DDesc &D = w.ddesc[t];
-    const u32 ntiles = D.tile_count;
     if (tid == 0) {
+        if (single) { D = one; w.ddesc[0] = one; w.tile_begin[0] = 0u; w.tile_begin[1] = one.tile_count; }
+        else D = w.ddesc[t];
         (void)parse_header(D, S, allow_raw != 0u);
         if (t == 0) *w.dec_kinds = 7u;                     // (the main passes look at every tensor)
     }
     __syncthreads();
+    const u32 ntiles = D.tile_count;
     const u64 n = D.n;
     // exclusive scan of s_cnt into s_excl and the table; returns the total (in the first wave)
     auto scan = [&](u32 *table) {
@@ -150,7 +156,10 @@ __global__ __launch_bounds__(PREP_WAVES * 64) void k_decode_prep(Workspace w, u3
         const u32 total = scan(w.dec_cnt_o);
         if (tid == 0) { S.pop_o = total; if (S.status == 0 && total != S.n_o) S.status = -4; }
     }
-    if (tid == 0) w.dst[t] = S;
+    if (tid == 0) {
+        w.dst[t] = S;
+        if (records) decode_record(w, t, D.n, S);
+    }
 }
 
 // which == 0: per-tile popcount of bitmap_w.  which == 1: per-tile popcount of the bitmap_o bits
@@ -811,15 +820,9 @@ __global__ void k_chain_finish(Workspace w, u32 ntensors, u32 rec_base) {
     R.status = status; R.pad = 0;
 }
 
-__global__ void k_decode_finish(Workspace w, u32 ntensors, u32 rec_base) {
+__global__ void k_decode_finish(Workspace w, u32 ntensors) {
     const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ntensors) return;
-    const DState &S = w.dst[t];
-    HostRec &R = w.rec_dev[rec_base + t];
-    R.n = w.ddesc[t].n; R.n_w = S.n_w; R.n_o = S.n_o; R.blob_bytes = S.blob_bytes; R.nonfinite = 0;
-    R.abs_sum = 0.0; R.obj[0] = R.obj[1] = R.obj[2] = 0.0;
-    R.med = R.mean32 = R.t_w = R.r_o = 0.f;
-    R.status = S.status; R.pad = 0;
+    if (t < ntensors) decode_record(w, t, w.ddesc[t].n, w.dst[t]);
 }
 
 // Export: header and codebooks of every well-formed blob, verbatim (one workgroup per tensor).
@@ -982,67 +985,48 @@ __global__ void k_dense_status(Workspace w, u32 ntensors) {
     if (t < ntensors && w.dst[t].status == -40) w.dst[t].status = -4;
 }
 
-// Decode state for a blob the compress path has just written (no header parsing needed).
-__global__ void k_decode_from_compress(Workspace w, GroupParams g) {
-    const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= g.ntensors) return;
-    const TDesc &C = w.desc[t];
-    const TState &T = w.st[t];
-    DDesc &D = w.ddesc[t];
-    DState &S = w.dst[t];
-    D.Wp = C.Wp; D.blob = C.blob; D.blob_bytes = T.blob_bytes; D.n = C.n;
-    D.W_out = C.W_out; D.m_out = nullptr; D.v_out = nullptr;
-    D.cw = nullptr; D.cm = nullptr; D.cv = nullptr; D.head = nullptr; D.wtype = excp_wtype(g.flags); D.pad = 0;
-    D.tile_begin = C.tile_begin; D.tile_count = C.tile_count;
-    S.n_w = T.n_w; S.n_o = T.n_o; S.blob_bytes = T.blob_bytes; S.nbits = (u32)g.nbits;
-    S.off_bw = EXCP_HEADER + excp_books_bytes((u32)g.nbits);
-    S.off_bo = T.off_bo; S.off_cw = T.off_cw; S.off_cm = T.off_cm; S.off_cv = T.off_cv;
-    S.status = (T.status == 0 && C.W_out != nullptr) ? 0 : 1;    // 1 = skip silently
-    S.pop_w = 0; S.pop_o = 0; S.flags = g.flags; S.pad = 0;
-    if (t == 0) *w.dec_kinds = blob_kind((u32)g.nbits, g.flags);
+// The first launch of a large group: no kinds of blob met yet, and a single tensor's description, which comes as an argument,
+// where the others look for it.
+__global__ void k_decode_setup(Workspace w, DDesc d, u32 single) {
+    if (threadIdx.x != 0) return;
+    *w.dec_kinds = 0u;
+    if (single) { w.ddesc[0] = d; w.tile_begin[0] = 0u; w.tile_begin[1] = d.tile_count; }
 }
 
-// The compress path already knows how many survivors precede every tile: the exclusive scan of its
-// mask pass, taken at the tile's first sub-tile.
-__global__ void k_decode_counts_from_mask(Workspace w, u32 ntiles) {
-    const u32 tile = blockIdx.x * blockDim.x + threadIdx.x;
-    if (tile < ntiles) w.dec_cnt_w[tile] = (u32)(w.mask_prefix[2ull * tile] >> 32);
-}
-
-// The descriptor of a single-tensor call arrives as a kernel argument and is written into the tables
-// the decoders read (for callers that have no staging memory to copy it from).
-__global__ void k_decode_single_setup(Workspace w, DDesc d) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        w.ddesc[0] = d;
-        w.tile_begin[0] = 0u;
-        w.tile_begin[1] = d.tile_count;
-    }
+template <bool MOMENTS, bool W16>
+__global__ __launch_bounds__(EXCP_THREADS) void k_decode_small(Workspace w, u32 ntensors, u32 ntiles) {
+    decode_tiles<MOMENTS, false, false, W16 ? 1 : 0>(w, ntensors, ntiles);
+    decode_tiles<MOMENTS, false, true, 2>(w, ntensors, ntiles);
 }
 
 }  // namespace
 
-void launch_decode_single_setup(const Workspace &w, const DDesc &d, hipStream_t s) {
-    hipLaunchKernelGGL(k_decode_single_setup, dim3(1), dim3(64), 0, s, w, d);
-}
-
-// Headers, counts and scans of a group whose largest tensor has `largest` tiles.
-void launch_decode_prep(const Workspace &w, u32 ntensors, u32 ntiles, u32 largest, bool allow_raw, bool moments, hipStream_t s) {
+// Headers, counts and scans of a group whose largest tensor has `largest` tiles.  `single`: the description of its only tensor,
+// not in the tables yet.  `records`: nothing can change the results after this, they go to the host.
+void launch_decode_prep(const Workspace &w, u32 ntensors, u32 ntiles, u32 largest, bool allow_raw, bool moments, bool records, const DDesc *single, hipStream_t s) {
     if (!ntensors) return;
-    if (largest <= PREP_TILES) {
-        hipLaunchKernelGGL(k_decode_prep, dim3(ntensors), dim3(PREP_WAVES * 64), 0, s, w, allow_raw ? 1u : 0u, moments ? 1u : 0u);
+    if (excp_prep_small(largest)) {
+        hipLaunchKernelGGL(k_decode_prep, dim3(ntensors), dim3(PREP_WAVES * 64), 0, s, w, allow_raw ? 1u : 0u, moments ? 1u : 0u, records ? 1u : 0u,
+                           single ? *single : DDesc{}, single ? 1u : 0u);
         return;
     }
-    launch_zero_u32(w.dec_kinds, 1, s);
+    hipLaunchKernelGGL(k_decode_setup, dim3(1), dim3(64), 0, s, w, single ? *single : DDesc{}, single ? 1u : 0u);
     hipLaunchKernelGGL(k_decode_parse, dim3((ntensors + 255) / 256), dim3(256), 0, s, w, ntensors, allow_raw ? 1u : 0u);
     for (int which = 0; which < (moments ? 2 : 1); ++which) {
         launch_decode_count(w, ntensors, ntiles, which, s);
         launch_decode_scan(w, ntensors, which, s);
     }
+    if (records) hipLaunchKernelGGL(k_decode_finish, dim3((ntensors + 255) / 256), dim3(256), 0, s, w, ntensors);
 }
-void launch_decode_from_compress(const Workspace &w, const GroupParams &g, hipStream_t s) {
-    if (!g.ntensors) return;
-    hipLaunchKernelGGL(k_decode_from_compress, dim3((g.ntensors + 255) / 256), dim3(256), 0, s, w, g);
-    if (g.ntiles) hipLaunchKernelGGL(k_decode_counts_from_mask, dim3((g.ntiles + 255) / 256), dim3(256), 0, s, w, g.ntiles);
+// The main pass of a small group, of blobs written with and without quantisation in one launch: a launch that finds nothing to do
+// is a tenth of such a call.
+void launch_decode_small(const Workspace &w, u32 ntensors, u32 ntiles, bool moments, bool w16, hipStream_t s) {
+    if (!ntiles) return;
+    const dim3 grid(std::min(ntiles, excp_grid(w, 64))), block(EXCP_THREADS);
+    if (moments && w16) hipLaunchKernelGGL((k_decode_small<true, true>), grid, block, 0, s, w, ntensors, ntiles);
+    else if (moments) hipLaunchKernelGGL((k_decode_small<true, false>), grid, block, 0, s, w, ntensors, ntiles);
+    else if (w16) hipLaunchKernelGGL((k_decode_small<false, true>), grid, block, 0, s, w, ntensors, ntiles);
+    else hipLaunchKernelGGL((k_decode_small<false, false>), grid, block, 0, s, w, ntensors, ntiles);
 }
 void launch_decode_count(const Workspace &w, u32 ntensors, u32 ntiles, int which, hipStream_t s) {
     if (!ntiles) return;
@@ -1107,7 +1091,7 @@ void launch_decode_dense(const Workspace &w, u32 ntensors, u32 ntiles, hipStream
 }
 void launch_decode_finish(const Workspace &w, u32 ntensors, hipStream_t s) {
     if (!ntensors) return;
-    hipLaunchKernelGGL(k_decode_finish, dim3((ntensors + 255) / 256), dim3(256), 0, s, w, ntensors, w.rec_base);
+    hipLaunchKernelGGL(k_decode_finish, dim3((ntensors + 255) / 256), dim3(256), 0, s, w, ntensors);
 }
 void launch_decode_chain(const Workspace &w, u32 ntensors, u32 ntiles, bool w16, hipStream_t s) {
     if (!ntiles) return;

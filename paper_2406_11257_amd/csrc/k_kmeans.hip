@@ -2035,8 +2035,31 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_store_raw(Workspace w, GroupPa
 }
 
 // ---------------------------------------------------------------- header, codebooks, results
-__global__ __launch_bounds__(EXCP_THREADS) void k_finalize(Workspace w, GroupParams g, u32 rec_base) {
+// A workgroup per tensor; `decode`: and what the decoders need to make W_hat of the blob just written, without parsing it -- its
+// state, and, by the workgroups beyond, how many survivors precede every tile, which the scan of the mask pass knows.
+__global__ __launch_bounds__(EXCP_THREADS) void k_finalize(Workspace w, GroupParams g, u32 rec_base, u32 decode) {
     __shared__ double s_obj[3];
+    if (blockIdx.x >= g.ntensors) {
+        const u32 tile = (blockIdx.x - g.ntensors) * EXCP_THREADS + threadIdx.x;
+        if (tile < g.ntiles) w.dec_cnt_w[tile] = (u32)(w.mask_prefix[2ull * tile] >> 32);
+        return;
+    }
+    if (decode && threadIdx.x == EXCP_THREADS - 1u) {
+        const u32 t = blockIdx.x;
+        const TDesc &C = w.desc[t];
+        const TState &T = w.st[t];
+        DDesc D{};
+        DState S{};
+        D.Wp = C.Wp; D.blob = C.blob; D.blob_bytes = T.blob_bytes; D.n = C.n; D.W_out = C.W_out;
+        D.wtype = excp_wtype(g.flags); D.tile_begin = C.tile_begin; D.tile_count = C.tile_count;
+        S.n_w = T.n_w; S.n_o = T.n_o; S.blob_bytes = T.blob_bytes; S.nbits = (u32)g.nbits;
+        S.off_bw = EXCP_HEADER + excp_books_bytes((u32)g.nbits);
+        S.off_bo = T.off_bo; S.off_cw = T.off_cw; S.off_cm = T.off_cm; S.off_cv = T.off_cv;
+        S.status = (T.status == 0 && C.W_out != nullptr) ? 0 : 1;    // 1 = skip silently
+        S.flags = g.flags;
+        w.ddesc[t] = D; w.dst[t] = S;
+        if (t == 0) *w.dec_kinds = blob_kind((u32)g.nbits, g.flags);
+    }
     const u32 t = blockIdx.x, tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const TDesc &D = w.desc[t];
     TState &T = w.st[t];
@@ -2168,7 +2191,8 @@ void launch_store_raw(const Workspace &w, const GroupParams &g, hipStream_t s) {
     hipLaunchKernelGGL(k_store_raw, dim3(excp_grid(w, 16)), dim3(EXCP_THREADS), 0, s, w, g);
 }
 
-void launch_finalize(const Workspace &w, const GroupParams &g, hipStream_t s) {
+void launch_finalize(const Workspace &w, const GroupParams &g, bool decode, hipStream_t s) {
     if (!g.ntensors) return;
-    hipLaunchKernelGGL(k_finalize, dim3(g.ntensors), dim3(EXCP_THREADS), 0, s, w, g, w.rec_base);
+    const u32 counts = decode ? (g.ntiles + EXCP_THREADS - 1u) / EXCP_THREADS : 0u;
+    hipLaunchKernelGGL(k_finalize, dim3(g.ntensors + counts), dim3(EXCP_THREADS), 0, s, w, g, w.rec_base, decode ? 1u : 0u);
 }

@@ -261,8 +261,88 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_scan_parts(Workspace w, G
     if (tid == 0) w.mask_part[(u64)t * MSCAN_PARTS + part] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
 }
 
+// After the masks: blob section offsets, capacity check, survivor stream lengths and the chunk
+// list of the survivor passes.  One workgroup; tensors and streams are few.  The counts come from other workgroups of the launch:
+// they are written and read past the caches that the compute dies do not share.
+__device__ __forceinline__ u64 load_count(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void layout(const Workspace &w, const GroupParams &g) {
+    u32 *seg_chunk_begin = w.seg_chunk_begin;
+    __shared__ u32 s_sum[2][EXCP_THREADS / 64];
+    const u32 tid = threadIdx.x;
+    const u32 nseg = 3u * g.ntensors;
+    const u32 per = (nseg + EXCP_THREADS - 1) / EXCP_THREADS;
+    u32 local[2] = {0u, 0u};                              // chunks, rows of the count table
+    const u32 unit_chunks = (1u << g.unit_shift) / EXCP_CHUNK;
+    for (u32 q = 0; q < per; ++q) {
+        u32 sidx = tid * per + q;
+        if (sidx >= nseg) break;
+        u32 t = sidx / 3u, which = sidx % 3u;
+        TState &S = w.st[t];
+        const TDesc &D = w.desc[t];
+        if (which == 0) {
+            const u64 n = D.n, nw = load_count(&S.n_w), no = load_count(&S.n_o), nb = (u64)g.nbits;
+            u64 off = EXCP_HEADER + excp_books_bytes((u32)g.nbits) + excp_pad16(8ull * excp_words(n));
+            S.off_bo = off; off += excp_pad16(8ull * excp_words((g.flags & 8u) ? n : nw));
+            S.off_cw = off; off += excp_pad16(8ull * excp_words(nw * nb));
+            S.off_cm = off; off += excp_pad16(8ull * excp_words(no * nb));
+            S.off_cv = off; off += excp_pad16(8ull * excp_words(no * nb));
+            S.blob_bytes = off;
+            int status = 0;
+            if (off > D.blob_cap) status = -2;
+            if (S.nonfinite) status = -3;
+            S.status = status;
+        }
+    }
+    for (u32 q = 0; q < per; ++q) {
+        u32 sidx = tid * per + q;
+        if (sidx >= nseg) break;
+        u32 t = sidx / 3u, which = sidx % 3u;
+        TState &S = w.st[t];
+        // the status is recomputed here: (t, 1) and (t, 2) may belong to another thread than (t, 0)
+        u64 len = load_count(which == 0 ? &S.n_w : &S.n_o);
+        const TDesc &D = w.desc[t];
+        {
+            const u64 n = D.n, nw = load_count(&S.n_w), no = load_count(&S.n_o), nb = (u64)g.nbits;
+            u64 off = EXCP_HEADER + excp_books_bytes((u32)g.nbits) + excp_pad16(8ull * excp_words(n));
+            off += excp_pad16(8ull * excp_words((g.flags & 8u) ? n : nw)) + excp_pad16(8ull * excp_words(nw * nb)) +
+                   2ull * excp_pad16(8ull * excp_words(no * nb));
+            if (off > D.blob_cap || S.nonfinite) len = 0;
+        }
+        w.seg[sidx].len = len;
+        const u32 chunks = (u32)((len + EXCP_CHUNK - 1) / EXCP_CHUNK);
+        local[0] += chunks;
+        local[1] += (chunks + unit_chunks - 1u) / unit_chunks;
+    }
+    u32 run[2], total[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        u32 incl = wave_incl_scan_u32(local[q]);
+        if ((tid & 63u) == 63u) s_sum[q][tid >> 6] = incl;
+        run[q] = incl - local[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        total[q] = 0;
+        for (u32 v = 0; v < EXCP_THREADS / 64; ++v) { if (v < (tid >> 6)) run[q] += s_sum[q][v]; total[q] += s_sum[q][v]; }
+    }
+    for (u32 q = 0; q < per; ++q) {
+        u32 sidx = tid * per + q;
+        if (sidx >= nseg) break;
+        seg_chunk_begin[sidx] = run[0];
+        w.seg[sidx].chunk_begin = run[0];
+        w.seg[sidx].row_begin = run[1];
+        const u32 chunks = (u32)((w.seg[sidx].len + EXCP_CHUNK - 1) / EXCP_CHUNK);
+        run[0] += chunks;
+        run[1] += (chunks + unit_chunks - 1u) / unit_chunks;
+    }
+    if (tid == EXCP_THREADS - 1) { seg_chunk_begin[nseg] = total[0]; *w.chunk_total = total[0]; *w.lloyd_shared = 0u; }
+}
+
+// (The workgroup that finds a tensor's totals draws a ticket; the last one goes on with the layout.)
 __global__ __launch_bounds__(EXCP_THREADS) void k_mask_scan(Workspace w, GroupParams g) {
     __shared__ u64 s_sum[EXCP_THREADS];
+    __shared__ u32 s_ticket;
     const u32 t = blockIdx.x / MSCAN_PARTS, part = blockIdx.x % MSCAN_PARTS, tid = threadIdx.x;
     const TDesc &D = w.desc[t];
     const u32 nsub = 2u * D.tile_count;
@@ -273,7 +353,10 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_scan(Workspace w, GroupPa
     for (u32 q = 0; q < part; ++q) carry += w.mask_part[(u64)t * MSCAN_PARTS + q];
     if (part == MSCAN_PARTS - 1u && tid == 0) {
         const u64 total = carry + w.mask_part[(u64)t * MSCAN_PARTS + part];
-        w.st[t].n_w = total >> 32; w.st[t].n_o = total & 0xffffffffull;
+        __hip_atomic_store(&w.st[t].n_w, total >> 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&w.st[t].n_o, total & 0xffffffffull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // (both have arrived before the ticket is drawn)
+        s_ticket = atomicAdd(w.scan_ticket, 1u);
     }
     for (u32 base = s0; base < s1; base += EXCP_THREADS * 4) {
         // four consecutive sub-tiles per thread
@@ -302,6 +385,11 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_scan(Workspace w, GroupPa
         carry += s_sum[EXCP_THREADS - 1];
         __syncthreads();
     }
+    if (part != MSCAN_PARTS - 1u) return;
+    __syncthreads();
+    if (s_ticket != g.ntensors - 1u) return;
+    if (tid == 0) *w.scan_ticket = 0u;
+    layout(w, g);
 }
 
 // Pass B: one wave per sub-tile copies the slot to its place in the dense survivor arrays.  A workgroup takes a
@@ -557,85 +645,10 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_bitmap_o_elems(Workspace 
     }
 }
 
-// After the masks: blob section offsets, capacity check, survivor stream lengths and the chunk
-// list of the survivor passes.  One workgroup; tensors and streams are few.
-__global__ __launch_bounds__(EXCP_THREADS) void k_layout(Workspace w, GroupParams g, u32 *seg_chunk_begin) {
-    __shared__ u32 s_sum[2][EXCP_THREADS / 64];
-    const u32 tid = threadIdx.x;
-    const u32 nseg = 3u * g.ntensors;
-    const u32 per = (nseg + EXCP_THREADS - 1) / EXCP_THREADS;
-    u32 local[2] = {0u, 0u};                              // chunks, rows of the count table
-    const u32 unit_chunks = (1u << g.unit_shift) / EXCP_CHUNK;
-    for (u32 q = 0; q < per; ++q) {
-        u32 sidx = tid * per + q;
-        if (sidx >= nseg) break;
-        u32 t = sidx / 3u, which = sidx % 3u;
-        TState &S = w.st[t];
-        const TDesc &D = w.desc[t];
-        if (which == 0) {
-            const u64 n = D.n, nw = S.n_w, no = S.n_o, nb = (u64)g.nbits;
-            u64 off = EXCP_HEADER + excp_books_bytes((u32)g.nbits) + excp_pad16(8ull * excp_words(n));
-            S.off_bo = off; off += excp_pad16(8ull * excp_words((g.flags & 8u) ? n : nw));
-            S.off_cw = off; off += excp_pad16(8ull * excp_words(nw * nb));
-            S.off_cm = off; off += excp_pad16(8ull * excp_words(no * nb));
-            S.off_cv = off; off += excp_pad16(8ull * excp_words(no * nb));
-            S.blob_bytes = off;
-            int status = 0;
-            if (off > D.blob_cap) status = -2;
-            if (S.nonfinite) status = -3;
-            S.status = status;
-        }
-    }
-    for (u32 q = 0; q < per; ++q) {
-        u32 sidx = tid * per + q;
-        if (sidx >= nseg) break;
-        u32 t = sidx / 3u, which = sidx % 3u;
-        TState &S = w.st[t];
-        // the status is recomputed here: (t, 1) and (t, 2) may belong to another thread than (t, 0)
-        u64 len = which == 0 ? S.n_w : S.n_o;
-        const TDesc &D = w.desc[t];
-        {
-            const u64 n = D.n, nw = S.n_w, no = S.n_o, nb = (u64)g.nbits;
-            u64 off = EXCP_HEADER + excp_books_bytes((u32)g.nbits) + excp_pad16(8ull * excp_words(n));
-            off += excp_pad16(8ull * excp_words((g.flags & 8u) ? n : nw)) + excp_pad16(8ull * excp_words(nw * nb)) +
-                   2ull * excp_pad16(8ull * excp_words(no * nb));
-            if (off > D.blob_cap || S.nonfinite) len = 0;
-        }
-        w.seg[sidx].len = len;
-        const u32 chunks = (u32)((len + EXCP_CHUNK - 1) / EXCP_CHUNK);
-        local[0] += chunks;
-        local[1] += (chunks + unit_chunks - 1u) / unit_chunks;
-    }
-    u32 run[2], total[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        u32 incl = wave_incl_scan_u32(local[q]);
-        if ((tid & 63u) == 63u) s_sum[q][tid >> 6] = incl;
-        run[q] = incl - local[q];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        total[q] = 0;
-        for (u32 v = 0; v < EXCP_THREADS / 64; ++v) { if (v < (tid >> 6)) run[q] += s_sum[q][v]; total[q] += s_sum[q][v]; }
-    }
-    for (u32 q = 0; q < per; ++q) {
-        u32 sidx = tid * per + q;
-        if (sidx >= nseg) break;
-        seg_chunk_begin[sidx] = run[0];
-        w.seg[sidx].chunk_begin = run[0];
-        w.seg[sidx].row_begin = run[1];
-        const u32 chunks = (u32)((w.seg[sidx].len + EXCP_CHUNK - 1) / EXCP_CHUNK);
-        run[0] += chunks;
-        run[1] += (chunks + unit_chunks - 1u) / unit_chunks;
-    }
-    if (tid == EXCP_THREADS - 1) { seg_chunk_begin[nseg] = total[0]; *w.chunk_total = total[0]; *w.lloyd_shared = 0u; }
-}
-
 }  // namespace
 
 void launch_mask_compact(const Workspace &w, const GroupParams &g, int phase, hipStream_t s) {
-    if (!g.ntiles) return;
+    if (!g.ntiles && phase != 1) return;                   // (the scan also makes the layout, of empty tensors too)
     const u32 nsub = 2u * g.ntiles;
     if (phase == 0) {
         u32 grid = excp_grid(w, 20);
@@ -658,8 +671,4 @@ void launch_mask_compact(const Workspace &w, const GroupParams &g, int phase, hi
         if (g.flags & 8u) hipLaunchKernelGGL(k_mask_bitmap_o_elems, dim3(grid_o), dim3(EXCP_THREADS), 0, s, w, g);
         else hipLaunchKernelGGL(k_mask_bitmap_o, dim3(grid_o), dim3(EXCP_THREADS), 0, s, w, g);
     }
-}
-
-void launch_layout(const Workspace &w, const GroupParams &g, hipStream_t s) {
-    hipLaunchKernelGGL(k_layout, dim3(1), dim3(EXCP_THREADS), 0, s, w, g, w.seg_chunk_begin);
 }

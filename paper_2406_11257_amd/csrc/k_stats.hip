@@ -31,12 +31,22 @@ enum { MED_PENDING = 0, MED_KNOWN = 1, MED_FALLBACK = 2 };
 // The sample (all residual magnitudes of a tensor that is no larger): sixteen workgroups per tensor, because
 // what it costs is the latency of 8192 loads from as many pages, and one compute unit overlaps few of those
 // (16.8 M elements: 40 us of loads from one workgroup).
-__global__ __launch_bounds__(EXCP_THREADS) void k_median_sample(Workspace w, GroupParams g) {
+// The first kernel of a call also sets the tensor's state and candidate counters to zero, and where a call is about one tensor
+// brings its description along as an argument and leaves it where the others look for it (no copy to wait for).
+__global__ __launch_bounds__(EXCP_THREADS) void k_median_sample(Workspace w, GroupParams g, TDesc one, u32 single) {
     constexpr u32 PART = MED_SAMPLE / EXCP_SAMPLE_PARTS, PER = PART / EXCP_THREADS;
     __shared__ u32 s_mmax;
     const u32 t = blockIdx.x / EXCP_SAMPLE_PARTS, part = blockIdx.x % EXCP_SAMPLE_PARTS, tid = threadIdx.x;
-    const TDesc &D = w.desc[t];
-    const u64 n = D.n;
+    struct { const float *W, *Wp, *m; } D;
+    u64 n;
+    if (single) { D.W = one.W; D.Wp = one.Wp; D.m = one.m; n = one.n; }
+    else { D.W = w.desc[t].W; D.Wp = w.desc[t].Wp; D.m = w.desc[t].m; n = w.desc[t].n; }
+    if (part == 0u) {
+        u32 *st = (u32 *)&w.st[t], *ctr = w.cand_ctr + (u64)t * 512u;
+        for (u32 i = tid; i < sizeof(TState) / 4u; i += EXCP_THREADS) st[i] = 0u;
+        for (u32 i = tid; i < 512u; i += EXCP_THREADS) ctr[i] = 0u;
+        if (single && tid == 0) { w.desc[0] = one; w.tile_begin[0] = 0u; w.tile_begin[1] = one.tile_count; }
+    }
     const u32 ns = n < MED_SAMPLE ? (u32)n : MED_SAMPLE;
     if (part * PART >= ns) return;
     if (tid == 0) s_mmax = 0;
@@ -701,15 +711,15 @@ void launch_zero_u32(u32 *p, u64 count, hipStream_t s) {
     hipLaunchKernelGGL(k_zero_u32, dim3((u32)blocks), dim3(256), 0, s, p, count);
 }
 
-// phase 0: sample and bracket, 1: streaming pass, 2: its records added up, bracket check, thresholds, and the
+// phase 0: sample and bracket (`single`: the description of a call's only tensor, not in the tables yet), 1: streaming pass, 2: its records added up, bracket check, thresholds, and the
 // passes that find the median
-void launch_stats(const Workspace &w, const GroupParams &g, int phase, hipStream_t s) {
+void launch_stats(const Workspace &w, const GroupParams &g, int phase, const TDesc *single, hipStream_t s) {
     if (!g.ntensors) return;
     const dim3 block(EXCP_THREADS);
     const dim3 stream_grid(excp_grid(w, EXCP_STATS_PER_CU));
     switch (phase) {
         case 0:
-            hipLaunchKernelGGL(k_median_sample, dim3(g.ntensors * EXCP_SAMPLE_PARTS), block, 0, s, w, g);
+            hipLaunchKernelGGL(k_median_sample, dim3(g.ntensors * EXCP_SAMPLE_PARTS), block, 0, s, w, g, single ? *single : TDesc{}, single ? 1u : 0u);
             hipLaunchKernelGGL(k_median_bracket, dim3(g.ntensors), dim3(MED_THREADS), 0, s, w, g);
             break;
         case 1:
