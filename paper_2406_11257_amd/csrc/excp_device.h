@@ -11,6 +11,7 @@
 #define EXCP_CHUNK       8192u     // survivors per chunk of the survivor passes
 #define EXCP_UNIT_SHIFT 17u        // log2 of the largest unit of the bucket counts, in positions of a stream (see excp_unit_shift)
 #define EXCP_THREADS     256
+#define EXCP_SMALL_ELEMS 8192u     // elements up to which a workgroup holds a tensor (groups that have no larger ones: k_small.hip)
 #define EXCP_SAMPLE_PARTS 16u      // workgroups that draw a tensor's sample of residuals
 #define EXCP_STATS_PER_CU 8u       // workgroups per compute unit of the statistics pass
 #define EXCP_ABSM_BINS   40        // u64 accumulators, 8 binary exponents apart, for the exact sum of |m|
@@ -291,6 +292,8 @@ void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s);
 struct SideStream { hipStream_t stream; hipEvent_t fork, join; };
 void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s, const SideStream &side);
 void launch_assign_pack(const Workspace &w, const GroupParams &g, hipStream_t s);
+void launch_small_front(const Workspace &w, const GroupParams &g, const TDesc *single, hipStream_t s);
+void launch_small_codes(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_finalize(const Workspace &w, const GroupParams &g, bool decode, hipStream_t s);
 void launch_decode_prep(const Workspace &w, u32 ntensors, u32 ntiles, u32 largest, bool allow_raw, bool moments, bool records, const DDesc *single, hipStream_t s);
 static inline bool excp_prep_small(u32 largest) { return largest <= 32u; }      // tiles of the largest tensor of a group that takes one launch

@@ -576,6 +576,13 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         p.unit_shift = excp_unit_shift(elems, g.count, excp_gather_subs(g.ntiles, (u32)w.cus), (u32)w.cus, excp_count_rows(c->max_group, kMaxGroupTensors));
         p.fine_size = largest <= EXCP_FINE_SMALL ? 0u : (largest <= EXCP_FINE_MIDDLE ? 1u : 2u);
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
+        // Small tensors only, compressed the usual way (the ablations of the median, of quantisation and of the momentum check
+        // take the general kernels).
+        if (largest <= EXCP_SMALL_ELEMS && (flags & ~(2u | 0x30u)) == 0) {
+            { StageTimer t(c, ST_STATS); launch_small_front(w, p, single ? descs.h : nullptr, s); }
+            { StageTimer t(c, ST_KM_ITER); launch_small_codes(w, p, s); }
+            continue;
+        }
         { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, single ? descs.h : nullptr, s); }
         { StageTimer t(c, ST_STATS); launch_stats(w, p, 1, nullptr, s); }
         { StageTimer t(c, ST_SELECT); launch_stats(w, p, 2, nullptr, s); }

@@ -193,6 +193,14 @@ __device__ __forceinline__ float val_of(u32 k) {
     return u2f((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
+// Position of a magnitude's lowest mantissa bit: value = mantissa * 2^(pos - 149).
+__device__ __forceinline__ u32 bit_pos(u32 mag) { const u32 e = mag >> 23; return (e ? e : 1u) - 1u; }
+
+// A key without the gap between the largest negative and the smallest positive value of magnitude `mag` (bit pattern) or more.
+__device__ __forceinline__ u32 closed_key(u32 key, u32 mag) {
+    const u32 a = 0x7fffffffu - mag, b = 0x80000000u + mag;          // keys of -mag and +mag (of -0 and +0 for mag = 0)
+    return key <= a ? key : (key < b ? a + 1u : key - b + a + 2u);
+}
 // The nearest centre of x among centres in ascending order (Sec. 3.3 leaves the rule open; this is the
 // rule the library fixes): a = last centre <= x, b = the next one; the two distances are evaluated in
 // fp64 with one rounding each, b wins only if strictly nearer, and among centres of equal value the lowest
@@ -309,4 +317,24 @@ __device__ __forceinline__ double signed_bins_to_double(const u64 *bins, u32 str
         mag = ldexp((double)mant, msb - 52 - 149);
     }
     return neg ? -mag : mag;
+}
+
+// t * 2^(base - 149), rounded once (to nearest, ties to even).
+__device__ __forceinline__ double i128_to_double(__int128 t, u32 base) {
+    const bool neg = t < 0;
+    const unsigned __int128 mag = neg ? (unsigned __int128)0 - (unsigned __int128)t : (unsigned __int128)t;
+    const u64 hi = (u64)(mag >> 64), lo = (u64)mag;
+    const int msb = hi ? 127 - __clzll((long long)hi) : 63 - __clzll((long long)(lo | 1ull));
+    double m;
+    if (msb <= 52) {
+        m = ldexp((double)lo, (int)base - 149);
+    } else {
+        const int sh = msb - 52;                          // 1 .. 75
+        u64 mant = (u64)(mag >> sh);
+        const unsigned __int128 below = mag << (128 - sh);
+        const u64 top = (u64)(below >> 64);
+        if ((top >> 63) && ((top << 1) | (u64)below | (mant & 1ull))) ++mant;
+        m = ldexp((double)mant, sh + (int)base - 149);
+    }
+    return neg ? -m : m;
 }

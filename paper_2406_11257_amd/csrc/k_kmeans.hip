@@ -75,9 +75,6 @@ __device__ __forceinline__ void file_i64(u64 *bins, long long v, u32 bitpos) {
     }
 }
 
-// Position of a magnitude's lowest mantissa bit: value = mantissa * 2^(pos - 149).
-__device__ __forceinline__ u32 bit_pos(u32 mag) { const u32 e = mag >> 23; return (e ? e : 1u) - 1u; }
-
 // Exact summation of values that are neighbours in magnitude.  A value inside the window of 24 bit
 // positions [B, B + 24) is a whole multiple of the unit 2^(B-149) below 2^47 units, so up to sixteen of
 // them add exactly in fp64, whatever their signs; such a partial sum is then split into two integers
@@ -709,11 +706,6 @@ constexpr u32 FINE_VALID = 1u << 31, FINE_NEAR = 1u << 30, NEAR_SPAN = 8;
 __device__ __forceinline__ u32 fine_log2(u32 info) { return info & 15u; }
 __device__ __forceinline__ u32 fine_shift(u32 info) { return (info >> 4) & 31u; }
 __device__ __forceinline__ u32 fine_most(u32 info) { return (info >> 9) & 0xffffu; }
-// A key without the gap between the largest negative and the smallest positive value of magnitude `mag` (bit pattern) or more.
-__device__ __forceinline__ u32 closed_key(u32 key, u32 mag) {
-    const u32 a = 0x7fffffffu - mag, b = 0x80000000u + mag;          // keys of -mag and +mag (of -0 and +0 for mag = 0)
-    return key <= a ? key : (key < b ? a + 1u : key - b + a + 2u);
-}
 // A value of magnitude pattern mb in units of 2^(pos_lo - 149).
 __device__ __forceinline__ u64 value_units(u32 bits, u32 pos_lo) {
     const u32 mb = bits & 0x7fffffffu, e = mb >> 23;
@@ -1548,26 +1540,6 @@ __device__ __forceinline__ __int128 bins_to_i128(const u64 *bins, u32 stride, u3
     for (u32 q = g1 + 1u; q-- > g0;) t = (t << 8) + (unsigned __int128)(__int128)(long long)bins[q * stride];
     return (__int128)t;
 }
-// t * 2^(base - 149), rounded once (to nearest, ties to even).
-__device__ __forceinline__ double i128_to_double(__int128 t, u32 base) {
-    const bool neg = t < 0;
-    const unsigned __int128 mag = neg ? (unsigned __int128)0 - (unsigned __int128)t : (unsigned __int128)t;
-    const u64 hi = (u64)(mag >> 64), lo = (u64)mag;
-    const int msb = hi ? 127 - __clzll((long long)hi) : 63 - __clzll((long long)(lo | 1ull));
-    double m;
-    if (msb <= 52) {
-        m = ldexp((double)lo, (int)base - 149);
-    } else {
-        const int sh = msb - 52;                          // 1 .. 75
-        u64 mant = (u64)(mag >> sh);
-        const unsigned __int128 below = mag << (128 - sh);
-        const u64 top = (u64)(below >> 64);
-        if ((top >> 63) && ((top << 1) | (u64)below | (mant & 1ull))) ++mant;
-        m = ldexp((double)mant, sh + (int)base - 149);
-    }
-    return neg ? -m : m;
-}
-
 template <u32 KMAX>
 __global__ __launch_bounds__(LLOYD_THREADS, 2u * lloyd_per_cu(KMAX)) void k_km_lloyd(Workspace w, GroupParams g) {
     constexpr bool ONE_WAVE = KMAX <= 63u;

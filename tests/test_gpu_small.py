@@ -1,0 +1,123 @@
+"""Groups of small tensors (k_small.hip) against the oracle, blob for blob and with W_hat: sizes from none to the most elements
+a workgroup holds and one more (which takes the general kernels), every code width, the weights' storages, ties, values many
+binary orders apart, subnormal ones, crowded cells, the error paths, and W_hat written over W_prev."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2406_11257_amd as X
+
+pytestmark = pytest.mark.gpu
+f32 = np.float32
+KIND = {0: torch.float32, X.EXCP_FLAG_W_F16: torch.float16, X.EXCP_FLAG_W_BF16: torch.bfloat16}
+
+
+def draw(n, seed, kind, flags=0):
+    g = np.random.default_rng(seed)
+    scale = 1e-3 if flags & 0x30 else 1e-4
+    if kind == "spread":
+        d = g.laplace(0, scale, n)
+    elif kind == "tied":
+        d = g.integers(-4, 5, n) * 2.0 ** -10 + np.where(g.random(n) < 0.05, g.normal(0, 1e-3, n), 0.0)
+    elif kind == "far apart":               # more binary orders than 128-bit sums hold, subnormal values among them
+        d = 2.0 ** g.uniform(-140, -5, n) * g.choice([-1.0, 1.0], n)
+    elif kind == "crowded":                 # nearly all in one cell
+        d = np.where(g.random(n) < 0.02, g.uniform(-1, 1, n), 1e-4 * (1 + 1e-5 * g.standard_normal(n)))
+    else:                                   # "equal"
+        d = np.full(n, 2.0 ** -9)
+    Wp = np.zeros(n, f32) if kind == "far apart" else O.narrow((g.standard_normal(n) * 0.02).astype(f32), flags)
+    Wp = O.narrow(np.asarray(Wp, f32), flags) if kind == "far apart" else Wp
+    W = O.narrow((O.widen(Wp, flags) + d.astype(f32)).astype(f32), flags)
+    m = (g.standard_normal(n) * 5e-5).astype(f32)
+    if kind == "far apart": m = (2.0 ** g.uniform(-140, 0, n) * g.choice([-1.0, 1.0], n)).astype(f32)
+    v = (m.astype(np.float64) ** 2 * g.lognormal(0, 1, n) + 1e-16).astype(f32)
+    return Wp, W, m, v
+
+
+def put_w(a, flags):
+    return torch.from_numpy(np.ascontiguousarray(a).view(f32 if not flags & 0x30 else np.int16)).cuda().view(KIND[flags & 0x30])
+
+
+def run(ctx, cases, nbits, iters, alpha, beta, flags, in_place=False):
+    items, outs = [], []
+    for Wp, W, m, v in cases:
+        n = m.size
+        wp = put_w(Wp, flags)
+        out = wp if in_place else torch.zeros_like(wp)
+        items.append((wp, put_w(W, flags), torch.from_numpy(m).cuda(), torch.from_numpy(v).cuda(),
+                      torch.full((X.excp_blob_bound(n, nbits),), 0xAB, dtype=torch.uint8, device="cuda"), out))
+        outs.append(out)
+    ctx.excp_compress_tensors(items, alpha, beta, nbits, iters, flags)
+    rc, stats = ctx.excp_collect(check=False)
+    return rc, stats, items, outs
+
+
+def check(ctx, cases, nbits, iters, alpha=5e-5, beta=2.0, flags=0, in_place=False):
+    rc, stats, items, outs = run(ctx, cases, nbits, iters, alpha, beta, flags, in_place)
+    assert rc == 0
+    for c, st, it, out in zip(cases, stats, items, outs):
+        ref = O.compress_step(*c, alpha, beta, nbits, iters, flags=flags)
+        blob = it[4][:st.blob_bytes].cpu().numpy().tobytes()
+        assert (st.n_w, st.n_o) == (ref.n_w, ref.n_o)
+        assert blob == ref.blob
+        assert f32(st.median_abs_dw).tobytes() == f32(ref.median).tobytes() and st.abs_sum_m == ref.abs_sum_m
+        np.testing.assert_allclose([st.obj_w, st.obj_m, st.obj_v], [ref.obj[k] for k in "wmv"], rtol=1e-12)        # (8192 non-negative terms in fp64)
+        want = O.decompress_step(c[0], ref.blob)[0]
+        assert out.view(torch.int16 if flags & 0x30 else torch.int32).cpu().numpy().tobytes() == np.ascontiguousarray(want).tobytes()
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = X.Context(20_000, 400_000)
+    yield c
+    c.close()
+
+
+SIZES = [0, 1, 2, 63, 64, 65, 127, 1000, 4095, 4096, 4097, 8191, 8192]
+
+
+@pytest.mark.parametrize("kind", ["spread", "tied", "far apart", "crowded", "equal"])
+@pytest.mark.parametrize("nbits", [2, 4, 6, 7, 8])
+def test_sizes_widths_and_values(ctx, kind, nbits):
+    for alpha, beta, iters in ((5e-5, 2.0, 10), (0.0, 0.0, 3)):
+        print(kind, nbits, alpha, flush=True)
+        check(ctx, [draw(n, 31 * n + nbits, kind) for n in SIZES], nbits, iters, alpha, beta)
+
+
+@pytest.mark.parametrize("flags", [X.EXCP_FLAG_W_F16, X.EXCP_FLAG_W_BF16, X.EXCP_FLAG_NO_M2W])
+@pytest.mark.parametrize("kind", ["spread", "tied"])
+def test_storages_and_the_scalar_threshold(ctx, kind, flags):
+    for nbits in (3, 8):
+        check(ctx, [draw(n, n + nbits, kind, flags) for n in SIZES], nbits, 5, 5e-5 if flags != X.EXCP_FLAG_NO_M2W else 0.5, 1.0, flags)
+
+
+@pytest.mark.parametrize("n", [1, 777, 8192, 8193])
+def test_alone_and_over_the_previous_weights(ctx, n):
+    check(ctx, [draw(n, n, "spread")], 4, 10, in_place=True)
+    check(ctx, [draw(n, n, "spread")], 4, 0)
+
+
+def test_one_larger_tensor_takes_all_the_general_way(ctx):
+    check(ctx, [draw(n, n, "spread") for n in (100, 8192, 8193)], 4, 10)
+
+
+def test_errors_stay_with_their_tensor(ctx):
+    cases = [draw(500, i, "spread") for i in range(4)]
+    cases[1][3][7] = np.inf
+    cases[2][1][9] = np.nan
+    rc, stats, items, outs = run(ctx, cases, 4, 5, 5e-5, 2.0, 0)
+    assert rc == X.EXCP_E_NONFINITE
+    assert [s.status for s in stats] == [0, X.EXCP_E_NONFINITE, X.EXCP_E_NONFINITE, 0] and stats[1].nonfinite == 1 and stats[2].nonfinite == 1
+    for i in (0, 3):
+        assert items[i][4][:stats[i].blob_bytes].cpu().numpy().tobytes() == O.compress_step(*cases[i], 5e-5, 2.0, 4, 5).blob
+    assert not outs[1].any() and not outs[2].any()          # nothing is reconstructed from a tensor that failed
+    # capacity: exactly enough, and sixteen bytes less
+    c = draw(3000, 5, "spread")
+    size = len(O.compress_step(*c, 0.0, 0.0, 4, 2).blob)
+    for cap, want in ((size, 0), (size - 16, X.EXCP_E_CAP)):
+        blob = torch.full((size + 64,), 0xAB, dtype=torch.uint8, device="cuda")
+        t = [torch.from_numpy(a).cuda() for a in c]
+        ctx.excp_compress_tensors([(*t, blob[:cap], None)], 0.0, 0.0, 4, 2)
+        rc, st = ctx.excp_collect(check=False)
+        assert rc == want and st[0].blob_bytes == size and (blob[cap:] == 0xAB).all()
