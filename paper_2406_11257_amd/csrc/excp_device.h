@@ -11,7 +11,7 @@
 #define EXCP_CHUNK       8192u     // survivors per chunk of the survivor passes
 #define EXCP_UNIT_SHIFT 17u        // log2 of the largest unit of the bucket counts, in positions of a stream (see excp_unit_shift)
 #define EXCP_THREADS     256
-#define EXCP_SMALL_ELEMS 8192u     // elements up to which a workgroup holds a tensor (groups that have no larger ones: k_small.hip)
+#define EXCP_SMALL_ELEMS 8192u     // elements up to which a workgroup holds a tensor (k_small.hip)
 #define EXCP_SAMPLE_PARTS 16u      // workgroups that draw a tensor's sample of residuals
 #define EXCP_STATS_PER_CU 8u       // workgroups per compute unit of the statistics pass
 #define EXCP_ABSM_BINS   40        // u64 accumulators, 8 binary exponents apart, for the exact sum of |m|
@@ -41,7 +41,8 @@ struct TDesc {
     u32 tile_begin;    // first tile of this tensor in the group's tile list
     u32 tile_count;
     u32 acc_slot;      // place of its streams' accumulators where many workgroups take a Lloyd iteration; EXCP_NO_SLOT:
-    u32 pad;           // its streams are never taken that way
+                       // its streams are never taken that way
+    u32 rec;           // its record among the group's, in the order of the call
 };
 #define EXCP_NO_SLOT 0xffffffffu
 

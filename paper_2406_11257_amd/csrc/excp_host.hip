@@ -61,7 +61,7 @@ struct excp_ctx {
     // per-call lists; their storage is reserved in excp_create so that no call allocates
     std::vector<Group> groups;
     std::vector<CGroup> cgroups;
-    std::vector<u32> tb_offsets;
+    std::vector<u32> tb_offsets, order, big;
     // size thresholds of the kernel forms (excp_set_param)
     u64 wide_elems = 1ull << 28;        // a group with a tensor this large takes the sixteen-wave per-bucket kernels
     u64 cand_list_elems = 1ull << 20;   // one median-candidate list per this many elements of a tensor (1 .. 16 lists)
@@ -338,6 +338,8 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
         c->groups.reserve(kMaxBatchTensors);
         c->cgroups.reserve(kMaxBatchTensors);
         c->tb_offsets.reserve(kMaxBatchTensors);
+        c->order.reserve(kMaxBatchTensors);
+        c->big.reserve(kMaxBatchTensors);
         c->spans.reserve(kEventPool / 2);
         c->free_events.reserve(kEventPool);
     } catch (...) { delete c; return EXCP_E_HIP; }
@@ -511,21 +513,34 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
 
     // Groups with larger tensors beside no more streams than compute units take all of them the same way through the
     // Lloyd iterations (see k_kmeans.hip).
-    auto lloyd_together = [&](const Group &g) {
+    auto lloyd_together = [&](const Group &g, u32 count) {
         bool any = false;
         for (u32 q = 0; q < g.count; ++q) any = any || !small(g.first + q);
-        return any && 3u * g.count <= (u32)c->w.cus;
+        return any && 3u * count <= (u32)c->w.cus;
     };
+    // In a group the tensors that a workgroup holds (k_small.hip) come last; the general kernels see only those before.  (The
+    // ablations of the median, of quantisation and of the momentum check take the general kernels in any case.)
+    const bool usual = (flags & ~(EXCP_FLAG_NO_M2W | 0x30u)) == 0;
+    std::vector<u32> &order = c->order, &big = c->big;
+    order.clear(); big.clear();
+    for (Group &g : groups) {
+        for (u32 q = 0; q < g.count; ++q) if (!usual || tensors[g.first + q].n > EXCP_SMALL_ELEMS) order.push_back(g.first + q);
+        big.push_back((u32)order.size() - g.first);
+        if (usual) for (u32 q = 0; q < g.count; ++q) if (tensors[g.first + q].n <= EXCP_SMALL_ELEMS) order.push_back(g.first + q);
+    }
     Staging stage{c};
     const Staged<TDesc> descs = stage.take<TDesc>(count);
     const Staged<u32> tiles = stage.take<u32>(count + groups.size());
     u32 tb_off = 0;
-    for (const Group &g : groups) {
+    for (size_t gi = 0; gi < groups.size(); ++gi) {
+        Group &g = groups[gi];
+        const u32 nbig = big[gi];
         u64 elem_off = 0, cand_off = 0; u32 tile = 0, slot = 0;
         tb_offsets.push_back(tb_off);
-        const bool together = lloyd_together(g);
+        const bool together = lloyd_together(g, nbig);
         for (u32 q = 0; q < g.count; ++q) {
-            const excp_tensor &t = tensors[g.first + q];
+            const u32 i = order[g.first + q];
+            const excp_tensor &t = tensors[i];
             TDesc &d = descs.h[g.first + q];
             d.Wp = (const float *)t.W_prev_recon; d.W = (const float *)t.W_t; d.m = t.m_t; d.v = t.v_t; d.n = t.n;
             d.blob = (unsigned char *)t.blob; d.blob_cap = t.blob_cap; d.W_out = (float *)t.W_recon_out;
@@ -534,18 +549,21 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             d.cand_off = cand_off; d.cand_cap = excp_cand_cap(t.n, d.cand_lists);
             cand_off += d.cand_cap;
             d.tile_count = (u32)((t.n + EXCP_TILE - 1) / EXCP_TILE);
-            d.acc_slot = t.n && (together || !small(g.first + q)) ? slot++ : EXCP_NO_SLOT; d.pad = 0;
+            d.acc_slot = q < nbig && t.n && (together || !small(i)) ? slot++ : EXCP_NO_SLOT; d.rec = i - g.first;
+            elem_off += t.n;
+            if (q >= nbig) continue;
             tiles.h[tb_off + q] = tile;
-            elem_off += t.n; tile += d.tile_count;
+            tile += d.tile_count;
         }
+        g.ntiles = tile;
         // the tensors by size, powers of two apart, the largest first
         u32 at[65] = {0};
-        auto size_class = [&](u32 q) { const u64 n = tensors[g.first + q].n; return n ? (u32)__builtin_clzll(n) : 64u; };
-        for (u32 q = 0; q < g.count; ++q) ++at[size_class(q)];
+        auto size_class = [&](u32 q) { const u64 n = descs.h[g.first + q].n; return n ? (u32)__builtin_clzll(n) : 64u; };
+        for (u32 q = 0; q < nbig; ++q) ++at[size_class(q)];
         for (u32 k = 0, sum = 0; k < 65; ++k) { const u32 here = at[k]; at[k] = sum; sum += here; }
-        for (u32 q = 0; q < g.count; ++q) descs.h[g.first + at[size_class(q)]++].turn = q;
-        tiles.h[tb_off + g.count] = tile;
-        tb_off += g.count + 1;
+        for (u32 q = 0; q < nbig; ++q) descs.h[g.first + at[size_class(q)]++].turn = q;
+        tiles.h[tb_off + nbig] = tile;
+        tb_off += nbig + 1;
     }
     hipStream_t s = c->stream;
     const bool single = count == 1;
@@ -563,26 +581,38 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         w.rec_dev = c->w.rec_dev + g.first;
         GroupParams p{};
         p.alpha = alpha; p.beta = beta; p.nbits = nbits; p.K = K; p.iters = lloyd_iters; p.flags = flags;
-        p.ntensors = g.count; p.ntiles = g.ntiles;
+        const u32 nbig = big[gi];
+        p.ntensors = nbig; p.ntiles = g.ntiles;
         u64 largest = 0, elems = 0;
-        for (u32 q = 0; q < g.count; ++q) { largest = std::max<u64>(largest, tensors[g.first + q].n); elems += tensors[g.first + q].n; }
+        bool any_out = false;
+        for (u32 q = 0; q < nbig; ++q) {
+            const TDesc &d = descs.h[g.first + q];
+            largest = std::max(largest, d.n); elems += d.n; any_out = any_out || d.W_out != nullptr;
+        }
         const bool w16 = (flags & 0x30u) != 0;
         if (!raw) {
-            p.together = lloyd_together(g) ? 1u : 0u;
-            for (u32 q = 0; q < g.count; ++q) p.fine += p.together && !w16 && elems <= EXCP_FINE_LARGEST && excp_fine_tensor(tensors[g.first + q].n) ? 1u : 0u;
+            p.together = lloyd_together(g, nbig) ? 1u : 0u;
+            for (u32 q = 0; q < nbig; ++q) p.fine += p.together && !w16 && elems <= EXCP_FINE_LARGEST && excp_fine_tensor(descs.h[g.first + q].n) ? 1u : 0u;
             p.alone_work = p.fine ? kAloneCells : (p.together ? kAloneTogether : (K < 63 ? kAloneFew : kAloneMany));
-            for (u32 q = 0; q < g.count; ++q) p.slots += descs.h[g.first + q].acc_slot != EXCP_NO_SLOT ? 1u : 0u;
+            for (u32 q = 0; q < nbig; ++q) p.slots += descs.h[g.first + q].acc_slot != EXCP_NO_SLOT ? 1u : 0u;
         }
-        p.unit_shift = excp_unit_shift(elems, g.count, excp_gather_subs(g.ntiles, (u32)w.cus), (u32)w.cus, excp_count_rows(c->max_group, kMaxGroupTensors));
+        p.unit_shift = excp_unit_shift(elems, nbig, excp_gather_subs(g.ntiles, (u32)w.cus), (u32)w.cus, excp_count_rows(c->max_group, kMaxGroupTensors));
         p.fine_size = largest <= EXCP_FINE_SMALL ? 0u : (largest <= EXCP_FINE_MIDDLE ? 1u : 2u);
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
-        // Small tensors only, compressed the usual way (the ablations of the median, of quantisation and of the momentum check
-        // take the general kernels).
-        if (largest <= EXCP_SMALL_ELEMS && (flags & ~(2u | 0x30u)) == 0) {
-            { StageTimer t(c, ST_STATS); launch_small_front(w, p, single ? descs.h : nullptr, s); }
-            { StageTimer t(c, ST_KM_ITER); launch_small_codes(w, p, s); }
-            continue;
+        // The small tensors: two launches, beside the larger ones on the context's own stream.  (They depend on nothing but what was
+        // enqueued before this group; the 14M shape has 50 of them among 76, TODO.)
+        const u32 nsmall = g.count - nbig;
+        if (nsmall) {
+            Workspace ws = w;
+            GroupParams ps = p;
+            ws.desc = w.desc + nbig; ws.st = w.st + nbig;
+            ps.ntensors = nsmall;
+            const hipStream_t to = nbig ? c->side.stream : s;
+            if (nbig) { (void)hipEventRecord(c->side.fork, s); (void)hipStreamWaitEvent(c->side.stream, c->side.fork, 0); }
+            launch_small_front(ws, ps, single ? descs.h : nullptr, to);
+            launch_small_codes(ws, ps, to);
         }
+        if (!nbig) continue;
         { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, single ? descs.h : nullptr, s); }
         { StageTimer t(c, ST_STATS); launch_stats(w, p, 1, nullptr, s); }
         { StageTimer t(c, ST_SELECT); launch_stats(w, p, 2, nullptr, s); }
@@ -602,14 +632,16 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             { StageTimer t(c, ST_KM_ITER); launch_km_iter(w, p, s, c->side); }
             { StageTimer t(c, ST_ASSIGN_PACK); launch_assign_pack(w, p, s); }
         }
-        bool any_out = false;
-        for (u32 q = 0; q < g.count; ++q) any_out = any_out || tensors[g.first + q].W_recon_out != nullptr;
         { StageTimer t(c, ST_FINALIZE); launch_finalize(w, p, any_out, s); }
         if (any_out) {
             StageTimer t(c, ST_DECODE_MAIN);
-            if (raw) launch_decode_raw(w, g.count, g.ntiles, false, s);
-            else if (flags & 0x30u) launch_decode_main16(w, g.count, g.ntiles, false, s);
-            else launch_decode_main(w, g.count, g.ntiles, false, s);
+            if (raw) launch_decode_raw(w, nbig, g.ntiles, false, s);
+            else if (flags & 0x30u) launch_decode_main16(w, nbig, g.ntiles, false, s);
+            else launch_decode_main(w, nbig, g.ntiles, false, s);
+        }
+        if (nsmall && !p.slots) {                            // (else the stream was joined by the Lloyd iterations)
+            (void)hipEventRecord(c->side.join, c->side.stream);
+            (void)hipStreamWaitEvent(s, c->side.join, 0);
         }
     }
     if (hipGetLastError() != hipSuccess) return enqueue_failed(c);

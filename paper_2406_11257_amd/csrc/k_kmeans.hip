@@ -2067,7 +2067,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_finalize(Workspace w, GroupPar
         hf[14] = T.t_w; hf[15] = T.r_o;
         h64[8] = T.blob_bytes;
         h[18] = (u32)g.iters; h[19] = 0u;
-        HostRec &R = w.rec_dev[rec_base + t];
+        HostRec &R = w.rec_dev[rec_base + D.rec];
         R.n = D.n; R.n_w = T.n_w; R.n_o = T.n_o; R.blob_bytes = T.blob_bytes; R.nonfinite = T.nonfinite;
         R.abs_sum = T.abs_sum; R.obj[0] = s_obj[0]; R.obj[1] = s_obj[1]; R.obj[2] = s_obj[2];
         R.med = u2f(T.med_bits); R.mean32 = T.mean32; R.t_w = T.t_w; R.r_o = T.r_o;

@@ -1,5 +1,5 @@
-// Tensors of at most EXCP_SMALL_ELEMS elements, when a group has no larger ones: Alg. 1 in two launches instead of
-// some twenty-five.  Such a call moves a few hundred KB; what it costs is launches, and inside them chains of dependent steps
+// Tensors of at most EXCP_SMALL_ELEMS elements: Alg. 1 in two launches instead of some twenty-five, beside which a group's larger
+// tensors go their way.  A call about such tensors moves a few hundred KB; what it costs is launches, and inside them chains of dependent steps
 // with a wave or two at work.  Here a workgroup holds a whole tensor in registers (k_small_front: statistics, masks,
 // compaction, header), and then one holds a whole survivor stream (k_small_codes: initial centres, Lloyd iterations,
 // codes, and for the residuals W_hat), everything they look up in LDS.  (us a call, before and now: a norm vector of 4096
@@ -31,9 +31,9 @@ __global__ __launch_bounds__(SM) void k_small_front(Workspace w, GroupParams g, 
     const float *pW, *pP, *pM, *pV;
     unsigned char *blob;
     u64 blob_cap, elem_off;
-    u32 n;
-    if (single) { pW = one.W; pP = one.Wp; pM = one.m; pV = one.v; n = (u32)one.n; blob = one.blob; blob_cap = one.blob_cap; elem_off = one.elem_off; }
-    else { const TDesc &D = w.desc[t]; pW = D.W; pP = D.Wp; pM = D.m; pV = D.v; n = (u32)D.n; blob = D.blob; blob_cap = D.blob_cap; elem_off = D.elem_off; }
+    u32 n, rec;
+    if (single) { pW = one.W; pP = one.Wp; pM = one.m; pV = one.v; n = (u32)one.n; blob = one.blob; blob_cap = one.blob_cap; elem_off = one.elem_off; rec = one.rec; }
+    else { const TDesc &D = w.desc[t]; pW = D.W; pP = D.Wp; pM = D.m; pV = D.v; n = (u32)D.n; blob = D.blob; blob_cap = D.blob_cap; elem_off = D.elem_off; rec = D.rec; }
     const u32 wt = excp_wtype(g.flags);
 
     float d[PER], mv[PER], vv[PER];
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(SM) void k_small_front(Workspace w, GroupParams g, 
     HostRec R{};
     R.n = n; R.n_w = n_w; R.n_o = n_o; R.blob_bytes = off; R.nonfinite = s_nf; R.abs_sum = s_abs;
     R.med = u2f(s_med); R.mean32 = s_mean; R.t_w = t_w; R.r_o = n ? r_o : 0.f; R.status = S.status;
-    w.rec_dev[w.rec_base + t] = R;
+    w.rec_dev[w.rec_base + rec] = R;
 }
 
 // ---------------------------------------------------------------- codebook, codes, W_hat
@@ -510,7 +510,7 @@ __global__ __launch_bounds__(SM) void k_small_codes(Workspace w, GroupParams g) 
         if (tid == 0) {
             obj = 0.0;
             for (u32 q = 0; q < SM_WAVES; ++q) obj += A.wave_obj[q];
-            w.rec_dev[w.rec_base + t].obj[which] = obj;
+            w.rec_dev[w.rec_base + D.rec].obj[which] = obj;
         }
     }
     float *books = (float *)(D.blob + EXCP_HEADER) + which * E;
