@@ -600,7 +600,7 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         p.fine_size = largest <= EXCP_FINE_SMALL ? 0u : (largest <= EXCP_FINE_MIDDLE ? 1u : 2u);
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
         // The small tensors: two launches, beside the larger ones on the context's own stream.  (They depend on nothing but what was
-        // enqueued before this group; the 14M shape has 50 of them among 76, TODO.)
+        // enqueued before this group; the 14M shape has 50 of them among 76: 535 -> 526 us; the 410M shape 194 among 292: 5337 -> 5027.)
         const u32 nsmall = g.count - nbig;
         if (nsmall) {
             Workspace ws = w;
