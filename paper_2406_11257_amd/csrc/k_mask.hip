@@ -17,14 +17,20 @@
 namespace {
 
 constexpr u32 SUB = 2048;          // elements per sub-tile
-constexpr u32 QUARTER = 512;       // elements a wave holds at once: 8 batches of 64
-constexpr int NBATCH = 8;          // 64-element batches per quarter
+constexpr u32 QUARTER = 512;       // elements a wave holds at once
+constexpr u32 GROUP = 256;         // elements decided together, four consecutive ones to a lane
 constexpr u32 BO_WORDS = SUB / 64; // M_o words kept per sub-tile
+constexpr u32 STAGE = QUARTER + 64; // survivors of a stream that wait in LDS for whole lines: less than a line, and a quarter's
 
-// The bits of one quarter as they arrive (weights as stored: fp32 bit patterns, or 16-bit values).
-struct Regs {
-    u32 w[NBATCH], p[NBATCH];
-    float m[NBATCH], v[NBATCH];
+// Four consecutive values at an address that is only known to be 4-byte aligned.
+typedef float f4m __attribute__((ext_vector_type(4), aligned(4)));
+typedef u32 u4m __attribute__((ext_vector_type(4), aligned(4)));
+
+// The bits of one quarter as they arrive (weights as stored: fp32 bit patterns, or 16-bit values): element
+// 256 h + 4 lane + j in [h][j].
+template <bool W16> struct Regs {
+    u32 w[2][W16 ? 2 : 4], p[2][W16 ? 2 : 4];
+    float m[2][4], v[2][4];
 };
 
 // What a wave needs to know about the sub-tile it works on (all of it the same in every lane).
@@ -34,121 +40,197 @@ struct SubTile {
     float T_keep, T_drop;          // t_w^2 with the estimate's guard band on either side
     bool T_ok;                     // t_w^2 is a positive normal number: the estimate may be used at all
     EXCP_GLOBAL float *sw, *sm, *sv;   // the sub-tile's slot in the three survivor areas
-    u64 *bm;                       // the tensor's keep bitmap (inside its blob)
-    u64 *bo;                       // the sub-tile's 32 local M_o words
 };
 
-// Loads of one quarter (512 elements starting at element `first` of the tensor) that lies wholly
-// inside the tensor: one base per array, the batches are immediate offsets.
+// Loads of one quarter (512 elements starting at element `first` of the tensor) that lies wholly inside the tensor, sixteen
+// bytes a lane (eight of 16-bit weights, whose arrays have to be 8-byte aligned for that).
 template <bool W16>
-__device__ __forceinline__ void load_quarter(Regs &R, const TDesc &D, u64 first, u32 lane) {
+__device__ __forceinline__ void load_quarter(Regs<W16> &R, const TDesc &D, u64 first, u32 lane) {
     const EXCP_GLOBAL float *gM = gptr(D.m) + first, *gV = gptr(D.v) + first;
-    if (W16) {
-        const EXCP_GLOBAL unsigned short *hW = gptr((const unsigned short *)D.W) + first;
-        const EXCP_GLOBAL unsigned short *hP = gptr((const unsigned short *)D.Wp) + first;
 #pragma unroll
-        for (int j = 0; j < NBATCH; ++j) { R.w[j] = hW[j * 64 + lane]; R.p[j] = hP[j * 64 + lane]; }
-    } else {
-        const EXCP_GLOBAL u32 *gW = gptr((const u32 *)D.W) + first, *gP = gptr((const u32 *)D.Wp) + first;
+    for (int h = 0; h < 2; ++h) {
+        const u32 off = (u32)h * GROUP + lane * 4u;
+        if constexpr (W16) {
+            const EXCP_GLOBAL unsigned short *hW = gptr((const unsigned short *)D.W) + first + off;
+            const EXCP_GLOBAL unsigned short *hP = gptr((const unsigned short *)D.Wp) + first + off;
+            typedef u32 u2 __attribute__((ext_vector_type(2)));
+            const u2 a = __builtin_nontemporal_load((const EXCP_GLOBAL u2 *)hW), b = __builtin_nontemporal_load((const EXCP_GLOBAL u2 *)hP);
+            R.w[h][0] = a.x; R.w[h][1] = a.y; R.p[h][0] = b.x; R.p[h][1] = b.y;
+        } else {
+            const u4m a = __builtin_nontemporal_load((const EXCP_GLOBAL u4m *)(gptr((const u32 *)D.W) + first + off)), b = __builtin_nontemporal_load((const EXCP_GLOBAL u4m *)(gptr((const u32 *)D.Wp) + first + off));
 #pragma unroll
-        for (int j = 0; j < NBATCH; ++j) { R.w[j] = gW[j * 64 + lane]; R.p[j] = gP[j * 64 + lane]; }
+            for (int j = 0; j < 4; ++j) { R.w[h][j] = a[j]; R.p[h][j] = b[j]; }
+        }
+        const f4m m = __builtin_nontemporal_load((const EXCP_GLOBAL f4m *)(gM + off)), v = __builtin_nontemporal_load((const EXCP_GLOBAL f4m *)(gV + off));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { R.m[h][j] = m[j]; R.v[h][j] = v[j]; }
     }
+}
+
+// The same for 16-bit weights at any address.
+template <bool W16>
+__device__ __forceinline__ void load_quarter_halves(Regs<W16> &R, const TDesc &D, u64 first, u32 lane) {
+    if constexpr (W16) {
 #pragma unroll
-    for (int j = 0; j < NBATCH; ++j) { R.m[j] = gM[j * 64 + lane]; R.v[j] = gV[j * 64 + lane]; }
+        for (int h = 0; h < 2; ++h) {
+            const u64 at = first + (u32)h * GROUP + lane * 4u;
+            const EXCP_GLOBAL unsigned short *hW = gptr((const unsigned short *)D.W) + at, *hP = gptr((const unsigned short *)D.Wp) + at;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) { R.w[h][j] = (u32)hW[2 * j] | (u32)hW[2 * j + 1] << 16; R.p[h][j] = (u32)hP[2 * j] | (u32)hP[2 * j + 1] << 16; }
+            const f4m m = *(const EXCP_GLOBAL f4m *)(gptr(D.m) + at), v = *(const EXCP_GLOBAL f4m *)(gptr(D.v) + at);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { R.m[h][j] = m[j]; R.v[h][j] = v[j]; }
+        }
+    }
 }
 
 // The same for a quarter of which only `rem` elements exist (a tensor's ragged end; rem may be 0).
 template <bool W16>
-__device__ __forceinline__ void load_quarter_ragged(Regs &R, const TDesc &D, u64 first, u32 rem, u32 lane) {
+__device__ __forceinline__ void load_quarter_ragged(Regs<W16> &R, const TDesc &D, u64 first, u32 rem, u32 lane) {
 #pragma unroll
-    for (int j = 0; j < NBATCH; ++j) {
-        const u32 e = (u32)j * 64u + lane;
-        const bool ok = e < rem;
-        const u64 idx = first + e;
-        R.w[j] = ok ? (W16 ? (u32)((const unsigned short *)D.W)[idx] : ((const u32 *)D.W)[idx]) : 0u;
-        R.p[j] = ok ? (W16 ? (u32)((const unsigned short *)D.Wp)[idx] : ((const u32 *)D.Wp)[idx]) : 0u;
-        R.m[j] = ok ? D.m[idx] : 0.f;
-        R.v[j] = ok ? D.v[idx] : 1.f;
+    for (int h = 0; h < 2; ++h) {
+        u32 w[4], p[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const u32 e = (u32)h * GROUP + lane * 4u + (u32)j;
+            const bool ok = e < rem;
+            const u64 idx = first + e;
+            w[j] = ok ? (W16 ? (u32)((const unsigned short *)D.W)[idx] : ((const u32 *)D.W)[idx]) : 0u;
+            p[j] = ok ? (W16 ? (u32)((const unsigned short *)D.Wp)[idx] : ((const u32 *)D.Wp)[idx]) : 0u;
+            R.m[h][j] = ok ? D.m[idx] : 0.f;
+            R.v[h][j] = ok ? D.v[idx] : 1.f;
+        }
+#pragma unroll
+        for (int j = 0; j < (W16 ? 2 : 4); ++j) {
+            R.w[h][j] = W16 ? w[2 * j & 3] | w[2 * j + 1 & 3] << 16 : w[j];
+            R.p[h][j] = W16 ? p[2 * j & 3] | p[2 * j + 1 & 3] << 16 : p[j];
+        }
     }
 }
 
-// Quarter r (0..3) of a sub-tile: decisions, bitmap words, survivors to their ranks.  All lanes of the
+// OR over groups of eight lanes, in all of them: neighbours, pairs, then the two quads.
+__device__ __forceinline__ u32 or_of_eight(u32 x) {
+    x |= dpp_u32<0xb1, 0xf>(0u, x);           // quad_perm 1 0 3 2
+    x |= dpp_u32<0x4e, 0xf>(0u, x);           // quad_perm 2 3 0 1
+    x |= dpp_u32<0x141, 0xf>(0u, x);          // row_half_mirror
+    return x;
+}
+
+// Survivors of one stream on their way from LDS to the sub-tile's slot: whole lines of 256 bytes as they fill up, past the
+// caches like the loads.  What bounds this pass is memory: the 16 bytes an element that it reads would take 1218 us for 4e8 elements, the
+// 2 bytes that it writes as much as 280 more.  (One element to a lane, survivors stored where they belong a batch at a time,
+// everything through the caches: 1625 us; four to a lane and whole lines 1577; stores past the caches 1566; loads as well 1500, but
+// 1800 with stores through them.)
+struct Outlet { u32 held, done; };             // values waiting in LDS; values written (a multiple of 64)
+__device__ __forceinline__ void drain(EXCP_GLOBAL float *slot, float *stage, Outlet &o, u32 lane) {
+    wave_lds_fence();
+    const u32 lines = o.held >> 6;
+    if (lines) {                               // (the same in the whole wave)
+        for (u32 k = 0; k < lines; ++k) __builtin_nontemporal_store(stage[k * 64u + lane], &slot[o.done + k * 64u + lane]);
+        const float rest = stage[lines * 64u + lane];          // (less than a line is left; the lanes beyond it move what nobody reads)
+        wave_lds_fence();
+        stage[lane] = rest;
+        o.done += lines * 64u; o.held &= 63u;
+        wave_lds_fence();
+    }
+}
+
+// Quarter r (0..3) of a sub-tile: decisions, bitmap words, survivors.  All lanes of the
 // wave are active throughout: every decision is first a wave-wide bit mask (the ballot of one
 // comparison), the masks are combined as 64-bit integers, and only the final masks become lane
 // predicates again.  rem = elements of the quarter that exist (FULL: all 512).
-// cw_run / co_run / nf_run: kept residuals, kept moments and non-finite v of the sub-tile so far.
+// word: lane l keeps the 32-bit bitmap word of elements 256 (l & 7) + 32 (l >> 3) of the sub-tile (oword: of M_o where that has a
+// bit per element).
 template <bool NW2M, bool W16, bool FULL>
-__device__ __forceinline__ void mask_quarter(const Regs &R, const SubTile &S, u32 r, u32 rem, u32 flags, u32 *my_bo,
-                                             u32 lane, u32 &cw_run, u32 &co_run, u32 &nf_run) {
+__device__ __forceinline__ void mask_quarter(const Regs<W16> &R, const SubTile &S, u32 r, u32 rem, u32 flags, u32 *my_bo, float *stage,
+                                             u32 lane, Outlet &ow, Outlet &oo, u32 &nf_run, u32 &word, u32 &oword) {
     const bool bf = W16 && excp_wtype(flags) == 2u;
-    u32 w_lo = 0, w_hi = 0, o_lo = 0, o_hi = 0;          // lane j: the j-th bitmap word of this quarter
+    float *st_w = stage, *st_m = stage + STAGE, *st_v = stage + 2u * STAGE;
 #pragma unroll
-    for (int j = 0; j < NBATCH; ++j) {
-        // lanes whose element exists (all of them, except at a tensor's ragged end)
-        const u32 left = FULL ? 64u : (rem > (u32)j * 64u ? rem - (u32)j * 64u : 0u);
-        const u64 valid = left >= 64u ? ~0ull : ((1ull << left) - 1ull);
-        const float wv = W16 ? w16_widen(R.w[j], bf) : u2f(R.w[j]);
-        const float pv = W16 ? w16_widen(R.p[j], bf) : u2f(R.p[j]);
-        const float d = wv - pv;                          // the residual
-        const float ad = fabsf(d), vv = R.v[j], mv = R.m[j];
-        u64 bw;
-        if (flags & 2u) {
-            bw = ballot64(ad > S.t_w);                    // ablation: the same scalar threshold for every element
-        } else {
-            // (d^2 may underflow where d^2 v does not: every factor and product must be a positive normal number)
-            const float dd = ad * ad, x = dd * vv;
-            const u64 b_keep = ballot64(x > S.T_keep), b_drop = ballot64(x < S.T_drop);
-            const u64 b_trust = ballot64(__builtin_amdgcn_classf(vv, 0x100)) & ballot64(__builtin_amdgcn_classf(dd, 0x100)) &
-                                ballot64(__builtin_amdgcn_classf(x, 0x100));
-            const u64 amb = S.T_ok ? (~(b_keep | b_drop) | ~b_trust) : ~0ull;
-            bw = b_keep;
-            if (amb & valid) {
-                // sqrtf and '/' are the correctly rounded forms (the build passes
-                // -fhip-fp32-correctly-rounded-divide-sqrt); __fsqrt_rn is NOT on this target
-                const u64 b_exact = ballot64(ad > S.t_w / sqrtf(vv));
-                bw = (b_keep & ~amb) | (b_exact & amb);
+    for (int h = 0; h < 2; ++h) {
+        u64 bw[4], bo[4];
+        float d[4];
+        u32 nw = 0, no = 0;                               // the lane's four keep bits, M_o bits
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const u32 e = (u32)h * GROUP + lane * 4u + (u32)j;
+            const u64 valid = FULL ? ~0ull : ballot64(e < rem);
+            const float wv = W16 ? w16_widen(R.w[h][j / 2] >> (16 * (j & 1)) & 0xffffu, bf) : u2f(R.w[h][j]);
+            const float pv = W16 ? w16_widen(R.p[h][j / 2] >> (16 * (j & 1)) & 0xffffu, bf) : u2f(R.p[h][j]);
+            d[j] = wv - pv;                               // the residual
+            const float ad = fabsf(d[j]), vv = R.v[h][j], mv = R.m[h][j];
+            u64 keep;
+            if (flags & 2u) {
+                keep = ballot64(ad > S.t_w);              // ablation: the same scalar threshold for every element
+            } else {
+                // (d^2 may underflow where d^2 v does not: every factor and product must be a positive normal number)
+                const float dd = ad * ad, x = dd * vv;
+                const u64 b_keep = ballot64(x > S.T_keep), b_drop = ballot64(x < S.T_drop);
+                const u64 b_trust = ballot64(__builtin_amdgcn_classf(vv, 0x100)) & ballot64(__builtin_amdgcn_classf(dd, 0x100)) &
+                                    ballot64(__builtin_amdgcn_classf(x, 0x100));
+                const u64 amb = S.T_ok ? (~(b_keep | b_drop) | ~b_trust) : ~0ull;
+                keep = b_keep;
+                if (amb & valid) {
+                    // sqrtf and '/' are the correctly rounded forms (the build passes
+                    // -fhip-fp32-correctly-rounded-divide-sqrt); __fsqrt_rn is NOT on this target
+                    const u64 b_exact = ballot64(ad > S.t_w / sqrtf(vv));
+                    keep = (b_keep & ~amb) | (b_exact & amb);
+                }
             }
+            bw[j] = keep & valid;
+            nf_run += (u32)__popcll(ballot64((f2u(vv) & 0x7f800000u) == 0x7f800000u) & valid);
+            bo[j] = ballot64(fabsf(mv) > S.r_o) & (NW2M ? valid : bw[j]);
+            nw |= __builtin_amdgcn_inverse_ballot_w64(bw[j]) ? 1u << j : 0u;
+            no |= __builtin_amdgcn_inverse_ballot_w64(bo[j]) ? 1u << j : 0u;
         }
-        bw &= valid;
-        nf_run += (u32)__popcll(ballot64((f2u(vv) & 0x7f800000u) == 0x7f800000u) & valid);
-        const u64 bo = ballot64(fabsf(mv) > S.r_o) & (NW2M ? valid : bw);
-        if (lane == (u32)j) { w_lo = (u32)bw; w_hi = (u32)(bw >> 32); }
-        const u32 rk = cw_run + __builtin_amdgcn_mbcnt_hi((u32)(bw >> 32), __builtin_amdgcn_mbcnt_lo((u32)bw, 0u));
-        if (__builtin_amdgcn_inverse_ballot_w64(bw)) S.sw[rk] = d;
-        if (__builtin_amdgcn_inverse_ballot_w64(bo)) {
-            const u32 ro = co_run + __builtin_amdgcn_mbcnt_hi((u32)(bo >> 32), __builtin_amdgcn_mbcnt_lo((u32)bo, 0u));
-            S.sm[ro] = mv; S.sv[ro] = vv;
-            if (!NW2M) atomicOr(&my_bo[rk >> 5], 1u << (rk & 31u));
+        const u32 at = 2u * r + (u32)h;                   // which 256 elements of the sub-tile
+        const u32 wd = or_of_eight(nw << (4u * (lane & 7u)));
+        if ((lane & 7u) == at) word = wd;
+        if (NW2M) { const u32 od = or_of_eight(no << (4u * (lane & 7u))); if ((lane & 7u) == at) oword = od; }
+        // places among the group's survivors: both streams' counts in one scan
+        const u32 c = (u32)__popc(nw) | (u32)__popc(no) << 16, incl = wave_incl_scan_u32(c), excl = incl - c, all = last_lane_u32(incl);
+        const u32 rw = ow.held + (excl & 0xffffu), ro = oo.held + (excl >> 16);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const u32 kw = rw + (u32)__popc(nw & ((1u << j) - 1u)), ko = ro + (u32)__popc(no & ((1u << j) - 1u));
+            if (__builtin_amdgcn_inverse_ballot_w64(bw[j])) st_w[kw] = d[j];
+            if (__builtin_amdgcn_inverse_ballot_w64(bo[j])) { st_m[ko] = R.m[h][j]; st_v[ko] = R.v[h][j]; }
         }
-        if (NW2M && lane == (u32)j) { o_lo = (u32)bo; o_hi = (u32)(bo >> 32); }
-        cw_run += (u32)__popcll(bw);
-        co_run += (u32)__popcll(bo);
+        if (!NW2M && no) {
+            // the lane's M_o bits in the order of its survivors, at their rank in the sub-tile
+            u32 bits = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bits |= (no >> j & 1u) << __popc(nw & ((1u << j) - 1u));
+            const u32 rk = ow.done + rw, sh = rk & 31u;
+            atomicOr(&my_bo[rk >> 5], bits << sh);
+            if (sh > 28u && bits >> (32u - sh)) atomicOr(&my_bo[(rk >> 5) + 1u], bits >> (32u - sh));
+        }
+        ow.held += all & 0xffffu; oo.held += all >> 16;
     }
-    // the quarter's eight words of the keep bitmap; words past the last element carry an all-zero
-    // ballot: that is the section's 16-byte padding
-    const u64 nwords = excp_words(S.n), word = ((S.base + (u64)r * QUARTER) >> 6) + lane;
-    if (lane < (u32)NBATCH && (FULL || word < nwords + (nwords & 1ull))) S.bm[word] = (u64)w_lo | ((u64)w_hi << 32);
-    if (NW2M && lane < (u32)NBATCH) S.bo[r * NBATCH + lane] = (u64)o_lo | ((u64)o_hi << 32);
+    drain(S.sw, st_w, ow, lane);
+    Outlet ov = oo;
+    drain(S.sm, st_m, oo, lane);
+    drain(S.sv, st_v, ov, lane);
 }
 
 // Pass A.  A wave owns whole sub-tiles (a contiguous range of the group's sub-tile list) and walks each
-// in four quarters of 512 elements; lane l of batch j holds element 64 j + l, so a wave ballot is one
-// word of a bitmap.  Nothing is shared between waves: no barrier after the tile table is loaded.
-// While one quarter is worked on the next is already on its way from memory (two register sets).
+// in four quarters of 512 elements, four consecutive elements to a lane.  Nothing is shared between waves: no barrier after
+// the tile table is loaded.  While one quarter is worked on the next is already on its way from memory (two register sets).
 //
 // Per element: the residual; the keep decision |d| > t_w / sqrt(v) with correctly rounded sqrt and
 // divide -- taken from the estimate d^2 v against t_w^2 when that is not within 1e-5 of the boundary
 // (the estimate's own error is below 3e-7) and from the exact expression otherwise, so it is always
-// that of the exact expression; the M_o decision.  Survivors go straight to their rank in the
-// sub-tile's slot (ballot + lane count); the M_o bit of a kept residual is ORed into the wave's own
-// LDS words at the residual's rank.
+// that of the exact expression; the M_o decision.  Survivors go to their rank in LDS and from there, as whole lines, to
+// the sub-tile's slot; the M_o bits of kept residuals are ORed into the wave's own
+// LDS words at the residuals' ranks.
 //
 // NW2M (Table "vit", no weights-to-momentum check): M_o(i) = |m_i| > r_o for every element, kept
-// weight or not; the sub-tile's M_o words are then indexed by element and are the ballots themselves.
+// weight or not; the sub-tile's M_o words are then indexed by element.
 // W16: the two weight arrays hold 16-bit values (fp16 or bf16 by the flags), widened as they are used.
 template <bool NW2M, bool W16>
-__global__ __launch_bounds__(EXCP_THREADS, 5) void k_mask_slots(Workspace w, GroupParams g) {
-    __shared__ u32 s_bo[EXCP_THREADS / 64][SUB / 32];      // per wave: M_o bits of its sub-tile's kept residuals, by rank
+__global__ __launch_bounds__(EXCP_THREADS, 4) void k_mask_slots(Workspace w, GroupParams g) {
+    __shared__ u32 s_bo[EXCP_THREADS / 64][SUB / 32 + 1];  // per wave: M_o bits of its sub-tile's kept residuals, by rank
+    __shared__ float s_stage[EXCP_THREADS / 64][3 * STAGE];
     __shared__ u32 s_tiles[EXCP_MAX_GROUP_TENSORS + 1];
     const u32 lane = threadIdx.x & 63u;
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -158,9 +240,11 @@ __global__ __launch_bounds__(EXCP_THREADS, 5) void k_mask_slots(Workspace w, Gro
     const u32 sub_lo = (u32)(((u64)wid * nsub) / nwaves), sub_hi = (u32)(((u64)(wid + 1u) * nsub) / nwaves);
     if (sub_lo >= sub_hi) return;
     u32 *my_bo = s_bo[wave];
+    float *stage = s_stage[wave];
     my_bo[lane] = 0u;
+    if (lane == 0u) my_bo[SUB / 32] = 0u;
     u32 t = 0, first_sub = 0, end_sub = 0;                // the tensor in hand, its first sub-tile, one past its last
-    Regs A, B;
+    Regs<W16> A, B;
     for (u32 sub = sub_lo; sub < sub_hi; ++sub) {
         if (sub >= end_sub) {                             // (looked up again only when a tensor's sub-tiles run out)
             t = (u32)__builtin_amdgcn_readfirstlane((int)find_owner(s_tiles, g.ntensors, sub >> 1));
@@ -181,37 +265,51 @@ __global__ __launch_bounds__(EXCP_THREADS, 5) void k_mask_slots(Workspace w, Gro
         S.T_keep = T * 1.00001f; S.T_drop = T * 0.99999f; S.T_ok = __builtin_amdgcn_classf(T, 0x100);
         const u64 slot = D.elem_off + S.base;
         S.sw = gptr(w.pw) + slot; S.sm = gptr(w.pm) + slot; S.sv = gptr(w.pv) + slot;
-        S.bm = (u64 *)(D.blob + EXCP_HEADER + excp_books_bytes((u32)g.nbits));
-        S.bo = w.mask_bo + (u64)sub * BO_WORDS;
-        u32 cw_run = 0, co_run = 0, nf_run = 0;
-        if (S.base + SUB <= S.n) {
+        Outlet ow = {0u, 0u}, oo = {0u, 0u};
+        u32 nf_run = 0, word = 0, oword = 0;
+        if (S.base + SUB <= S.n && (!W16 || (((uintptr_t)D.W | (uintptr_t)D.Wp) & 7u) == 0u)) {
             load_quarter<W16>(A, D, S.base, lane);
             load_quarter<W16>(B, D, S.base + QUARTER, lane);
-            mask_quarter<NW2M, W16, true>(A, S, 0u, QUARTER, g.flags, my_bo, lane, cw_run, co_run, nf_run);
+            mask_quarter<NW2M, W16, true>(A, S, 0u, QUARTER, g.flags, my_bo, stage, lane, ow, oo, nf_run, word, oword);
             load_quarter<W16>(A, D, S.base + 2u * QUARTER, lane);
-            mask_quarter<NW2M, W16, true>(B, S, 1u, QUARTER, g.flags, my_bo, lane, cw_run, co_run, nf_run);
+            mask_quarter<NW2M, W16, true>(B, S, 1u, QUARTER, g.flags, my_bo, stage, lane, ow, oo, nf_run, word, oword);
             load_quarter<W16>(B, D, S.base + 3u * QUARTER, lane);
-            mask_quarter<NW2M, W16, true>(A, S, 2u, QUARTER, g.flags, my_bo, lane, cw_run, co_run, nf_run);
-            mask_quarter<NW2M, W16, true>(B, S, 3u, QUARTER, g.flags, my_bo, lane, cw_run, co_run, nf_run);
+            mask_quarter<NW2M, W16, true>(A, S, 2u, QUARTER, g.flags, my_bo, stage, lane, ow, oo, nf_run, word, oword);
+            mask_quarter<NW2M, W16, true>(B, S, 3u, QUARTER, g.flags, my_bo, stage, lane, ow, oo, nf_run, word, oword);
         } else {
 #pragma unroll 1
             for (u32 r = 0; r < 4u; ++r) {
                 const u64 first = S.base + (u64)r * QUARTER;
                 const u32 rem = S.n > first ? (S.n - first < (u64)QUARTER ? (u32)(S.n - first) : QUARTER) : 0u;
-                load_quarter_ragged<W16>(A, D, first, rem, lane);
-                mask_quarter<NW2M, W16, false>(A, S, r, rem, g.flags, my_bo, lane, cw_run, co_run, nf_run);
+                if (W16 && rem == QUARTER) load_quarter_halves(A, D, first, lane);      // (arrays of 16-bit weights that are not 8-byte aligned)
+                else load_quarter_ragged<W16>(A, D, first, rem, lane);
+                mask_quarter<NW2M, W16, false>(A, S, r, rem, g.flags, my_bo, stage, lane, ow, oo, nf_run, word, oword);
             }
         }
-        // the sub-tile is complete: its M_o words (by survivor rank) and its counts
-        if (!NW2M) {
-            const u64 word = (u64)my_bo[2u * (lane & 31u)] | ((u64)my_bo[2u * (lane & 31u) + 1u] << 32);
-            if (lane < ((cw_run + 63u) >> 6)) S.bo[lane] = word;
+        // the sub-tile is complete: what is left of the survivors, its bitmap words, its M_o words (by survivor rank), its counts
+        if (lane < ow.held) S.sw[ow.done + lane] = stage[lane];
+        if (lane < oo.held) { S.sm[oo.done + lane] = stage[STAGE + lane]; S.sv[oo.done + lane] = stage[2u * STAGE + lane]; }
+        const u32 cw = ow.done + ow.held, co = oo.done + oo.held;
+        const u32 mine = (lane & 7u) * 8u + (lane >> 3);  // 32-bit word of the sub-tile that this lane has
+        const u64 nwords = excp_words(S.n), first_word = S.base >> 6;
+        EXCP_GLOBAL u32 *bm = gptr((u32 *)(D.blob + EXCP_HEADER + excp_books_bytes((u32)g.nbits))) + 2u * first_word;
+        // (words past the last element are zero: that is the section's 16-byte padding)
+        if (first_word + (mine >> 1) < nwords + (nwords & 1ull)) bm[mine] = word;
+        u64 *bo = w.mask_bo + (u64)sub * BO_WORDS;
+        if (NW2M) {
+            ((u32 *)bo)[mine] = oword;
+        } else {
+            wave_lds_fence();
+            const u64 bits = (u64)my_bo[2u * (lane & 31u)] | ((u64)my_bo[2u * (lane & 31u) + 1u] << 32);
+            if (lane < ((cw + 63u) >> 6)) bo[lane] = bits;
+            wave_lds_fence();
             my_bo[lane] = 0u;
         }
         if (lane == 0u) {
-            w.tile_status[sub] = ((u64)cw_run << 32) | (u64)co_run;
+            w.tile_status[sub] = ((u64)cw << 32) | (u64)co;
             if (nf_run) atomicAdd(&w.st[t].nonfinite, (u64)nf_run);
         }
+        wave_lds_fence();
     }
 }
 
@@ -651,13 +749,16 @@ void launch_mask_compact(const Workspace &w, const GroupParams &g, int phase, hi
     if (!g.ntiles && phase != 1) return;                   // (the scan also makes the layout, of empty tensors too)
     const u32 nsub = 2u * g.ntiles;
     if (phase == 0) {
-        u32 grid = excp_grid(w, 20);
-        if (grid > nsub) grid = nsub;
+        // Where there are fewer sub-tiles than waves of twenty workgroups a compute unit, eight, and a sub-tile to each wave at least:
+        // twice as many as fit at once, without a last round that is nearly empty (16.8 M elements 78 -> 63 us, 14 M 73 -> 54,
+        // 25 M 98 -> 97; 4e8 elements 1500 with twenty, 1554 with eight).
+        const u32 per_cu = nsub < excp_grid(w, 80) ? 8u : 20u;
+        const dim3 grid(std::min(excp_grid(w, per_cu), (nsub + 3u) / 4u)), block(EXCP_THREADS);
         const bool nw2m = (g.flags & 8u) != 0, w16 = (g.flags & 0x30u) != 0;
-        if (nw2m && w16) hipLaunchKernelGGL((k_mask_slots<true, true>), dim3(grid), dim3(EXCP_THREADS), 0, s, w, g);
-        else if (nw2m) hipLaunchKernelGGL((k_mask_slots<true, false>), dim3(grid), dim3(EXCP_THREADS), 0, s, w, g);
-        else if (w16) hipLaunchKernelGGL((k_mask_slots<false, true>), dim3(grid), dim3(EXCP_THREADS), 0, s, w, g);
-        else hipLaunchKernelGGL((k_mask_slots<false, false>), dim3(grid), dim3(EXCP_THREADS), 0, s, w, g);
+        if (nw2m && w16) hipLaunchKernelGGL((k_mask_slots<true, true>), grid, block, 0, s, w, g);
+        else if (nw2m) hipLaunchKernelGGL((k_mask_slots<true, false>), grid, block, 0, s, w, g);
+        else if (w16) hipLaunchKernelGGL((k_mask_slots<false, true>), grid, block, 0, s, w, g);
+        else hipLaunchKernelGGL((k_mask_slots<false, false>), grid, block, 0, s, w, g);
     } else if (phase == 1) {
         hipLaunchKernelGGL(k_mask_scan_parts, dim3(g.ntensors * MSCAN_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
         hipLaunchKernelGGL(k_mask_scan, dim3(g.ntensors * MSCAN_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
