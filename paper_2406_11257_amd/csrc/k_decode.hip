@@ -637,7 +637,7 @@ __global__ __launch_bounds__(EXCP_THREADS, 8) void k_export_dense(Workspace w, u
 // "sixteen bits, survivors before them" (one exchange then gives a lane all it needs for four elements), and
 // a code leaves its window by a bit-field extract whose width is 0 where the element is pruned.  While one
 // checkpoint is worked on, the codes of the next and the bitmap word of the one after it are on their way.
-// (A 410M-shaped checkpoint, eight steps of 4 bits: 2463 -> 1133 us in three launches; the bytes alone take about 890.)
+// (A 410M-shaped checkpoint, eight steps of 4 bits: 2463 -> 1133 us in three launches, 1064 with the weights past the caches; the bytes alone take about 890.)
 struct ChainBits {
     u32 pk;                                                // lane's 16-bit piece of the quarter's bitmap, survivors before it << 16
     u32 q, kept, nbits;                                    // survivors of the tensor before the quarter, in it (the same in every lane)
