@@ -599,6 +599,7 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         p.unit_shift = excp_unit_shift(elems, nbig, excp_gather_subs(g.ntiles, (u32)w.cus), (u32)w.cus, excp_count_rows(c->max_group, kMaxGroupTensors));
         p.fine_size = largest <= EXCP_FINE_SMALL ? 0u : (largest <= EXCP_FINE_MIDDLE ? 1u : 2u);
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
+        { StageTimer t(c, ST_LAYOUT); }                      // (made inside the mask scan and k_small_front: the span, one a group, is empty)
         // The small tensors: two launches, beside the larger ones on the context's own stream.  (They depend on nothing but what was
         // enqueued before this group; the 14M shape has 50 of them among 76: 535 -> 526 us; the 410M shape 194 among 292: 5337 -> 5027.)
         const u32 nsmall = g.count - nbig;
@@ -609,8 +610,14 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             ps.ntensors = nsmall;
             const hipStream_t to = nbig ? c->side.stream : s;
             if (nbig) { (void)hipEventRecord(c->side.fork, s); (void)hipStreamWaitEvent(c->side.stream, c->side.fork, 0); }
-            launch_small_front(ws, ps, single ? descs.h : nullptr, to);
-            launch_small_codes(ws, ps, to);
+            if (nbig) {
+                launch_small_front(ws, ps, single ? descs.h : nullptr, to);
+                launch_small_codes(ws, ps, to);
+            } else {
+                StageTimer t(c, ST_MISC);
+                launch_small_front(ws, ps, single ? descs.h : nullptr, to);
+                launch_small_codes(ws, ps, to);
+            }
         }
         if (!nbig) continue;
         { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, single ? descs.h : nullptr, s); }
