@@ -944,13 +944,14 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
                          ? ((const EXCP_CONSTANT u32 *)(uintptr_t)w.km_fine)[(u64)sidx * NBKT + b] : 0u;
     if (INIT_THREADS == 1024u && !info && rank - w.km_less[(u64)sidx * NBKT + b] < w.km_dom[(u64)sidx * NBKT + b]) { if (tid == 0) *out = gptr(seg_part(w, sidx))[p0]; return; }
     if (info) {                                           // the cell that holds the rank
+        __shared__ u32 s_ends[2];                         // (not s_pick: a wave may still have to read the bucket from there)
         const u64 e = (u64)(sidx % 3u) * w.fine_stride + excp_fine_at(w.desc[sidx / 3u].elem_off, sidx / 3u, p0, b);
         for (u32 c = tid; c < 1u << fine_log2(info); c += INIT_THREADS) {
             const u32 c0 = w.fine_begin[e + c], c1 = w.fine_begin[e + c + 1u];
-            if (c0 <= rank && rank < c1) { s_pick[0] = c0; s_pick[1] = c1; }
+            if (c0 <= rank && rank < c1) { s_ends[0] = c0; s_ends[1] = c1; }
         }
         __syncthreads();
-        const u32 c0 = (u32)__builtin_amdgcn_readfirstlane((int)s_pick[0]), c1 = (u32)__builtin_amdgcn_readfirstlane((int)s_pick[1]);
+        const u32 c0 = (u32)__builtin_amdgcn_readfirstlane((int)s_ends[0]), c1 = (u32)__builtin_amdgcn_readfirstlane((int)s_ends[1]);
         p0 += c0; cntb = c1 - c0; rank -= c0;
     }
     const EXCP_GLOBAL float *gpart = gptr(seg_part(w, sidx)) + p0;
