@@ -258,6 +258,30 @@ static __host__ __device__ inline u32 excp_fine_cells_log2(u32 size) {
     while (k < 9u && (size >> (EXCP_FINE_SHIFT + 1u) >> k)) ++k;
     return k;
 }
+// A key (see key_of) without the gap between the largest negative and the smallest positive value of magnitude `mag` (bit
+// pattern) or more.
+static __host__ __device__ inline u32 excp_closed_key(u32 key, u32 mag) {
+    const u32 a = 0x7fffffffu - mag, b = 0x80000000u + mag;          // keys of -mag and +mag (of -0 and +0 for mag = 0)
+    return key <= a ? key : (key < b ? a + 1u : key - b + a + 2u);
+}
+// The cells of a bucket: 2^log2 equal ranges of the closed key between its extremes.  `gap`: the keys have the gap between
+// them.  A zero lies inside it, on the far side of the other values, so this is so not only where there are both signs.
+struct CellMap { u32 kmin, mag, k0, shift, flip; bool gap; };
+static __host__ __device__ inline CellMap excp_cell_map(u32 kmin, u32 kmax, u32 mag, u32 log2) {
+    CellMap M;
+    M.kmin = kmin; M.mag = mag; M.k0 = excp_closed_key(kmin, mag);
+    const u32 range = excp_closed_key(kmax, mag) - M.k0, bits = 32u - (u32)__builtin_clz(range | 1u);
+    M.shift = bits > log2 ? bits - log2 : 0u;
+    M.gap = kmin <= 0x80000000u && kmax >= 0x7fffffffu;
+    M.flip = kmin < 0x80000000u ? 0xffffffffu : 0x80000000u;         // without the gap: from a value's bits to its key
+    return M;
+}
+static __host__ __device__ inline u32 excp_cell_of_key(const CellMap &M, u32 key) { return (excp_closed_key(key, M.mag) - M.k0) >> M.shift; }
+// (of a value by its bits; nearly every bucket has no gap, and there the plain difference of the keys is the same)
+static __host__ __device__ inline u32 excp_cell_of_bits(const CellMap &M, u32 bits) {
+    if (M.gap) return excp_cell_of_key(M, (bits & 0x80000000u) ? ~bits : bits | 0x80000000u);
+    return ((bits ^ M.flip) - M.kmin) >> M.shift;
+}
 // Tensors whose buckets may be worth cells (2^17 is a power of two because the host lists the tensors by powers of two), and
 // the largest ones whose buckets, a third of the values kept, nearly all fit a workgroup of k_km_cells in its three sizes.
 // A group of more elements in all goes without cells: 2 to 4 us a million elements are then more than the 125 us that the

@@ -196,11 +196,6 @@ __device__ __forceinline__ float val_of(u32 k) {
 // Position of a magnitude's lowest mantissa bit: value = mantissa * 2^(pos - 149).
 __device__ __forceinline__ u32 bit_pos(u32 mag) { const u32 e = mag >> 23; return (e ? e : 1u) - 1u; }
 
-// A key without the gap between the largest negative and the smallest positive value of magnitude `mag` (bit pattern) or more.
-__device__ __forceinline__ u32 closed_key(u32 key, u32 mag) {
-    const u32 a = 0x7fffffffu - mag, b = 0x80000000u + mag;          // keys of -mag and +mag (of -0 and +0 for mag = 0)
-    return key <= a ? key : (key < b ? a + 1u : key - b + a + 2u);
-}
 // The nearest centre of x among centres in ascending order (Sec. 3.3 leaves the rule open; this is the
 // rule the library fixes): a = last centre <= x, b = the next one; the two distances are evaluated in
 // fp64 with one rounding each, b wins only if strictly nearer, and among centres of equal value the lowest

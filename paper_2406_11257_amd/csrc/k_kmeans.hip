@@ -729,18 +729,15 @@ __device__ __forceinline__ void cells_of_bucket(EXCP_GLOBAL float *part, u32 siz
     float v[PER];
 #pragma unroll
     for (u32 j = 0; j < PER; ++j) v[j] = j * THREADS + tid < size ? part[j * THREADS + tid] : 0.f;
-    const u32 k0 = closed_key(kmin, mag), range = closed_key(kmax, mag) - k0;
-    const u32 lg = excp_fine_cells_log2(size), bits = 32u - (u32)__clz((int)(range | 1u)), shift = bits > lg ? bits - lg : 0u;
+    const u32 lg = excp_fine_cells_log2(size);
+    const CellMap map = excp_cell_map(kmin, kmax, mag, lg);
     if (tid < 512u) { A.cnt[tid] = 0; A.sum[tid] = 0; }
     if (tid == 0) A.most = 0;
     __syncthreads();
-    // (nearly every bucket has values of one sign only)
-    const bool both = kmin < 0x80000000u && kmax >= 0x80000000u;
-    const u32 flip = kmin < 0x80000000u ? 0xffffffffu : 0x80000000u;
-    auto cell_in = [&](float x) { return both ? (closed_key(key_of(x), mag) - k0) >> shift : ((f2u(x) ^ flip) - kmin) >> shift; };
-    // Where the bucket spans eight binary orders and one sign, as nearly all do, a cell's sum of magnitudes (24 + 8 + 16 bits)
-    // and its number of values share a word and an atomic.
-    const bool near = bit_pos(max(f2u(val_of(kmin)) & 0x7fffffffu, f2u(val_of(kmax)) & 0x7fffffffu)) - pos_lo <= NEAR_SPAN, packed = near && !both;
+    auto cell_in = [&](float x) { return excp_cell_of_bits(map, f2u(x)); };
+    // Where the bucket spans eight binary orders and has values of one sign and no zero, as nearly all do, a cell's sum of
+    // magnitudes (24 + 8 + 16 bits) and its number of values share a word and an atomic.
+    const bool near = bit_pos(max(f2u(val_of(kmin)) & 0x7fffffffu, f2u(val_of(kmax)) & 0x7fffffffu)) - pos_lo <= NEAR_SPAN, packed = near && !map.gap;
     u32 place[PER / 2u];                                   // arrivals in the cells, then places in the bucket, two to a register
 #pragma unroll
     for (u32 j = 0; j < PER; ++j) {
@@ -775,7 +772,7 @@ __device__ __forceinline__ void cells_of_bucket(EXCP_GLOBAL float *part, u32 siz
         for (u32 q = 0; q < 8; ++q) { if (q < wave) { incl += A.wave_cnt[q]; incls += A.wave_sum[q]; } all += A.wave_sum[q]; }
         A.cnt[tid] = incl - cnt;
         if (tid < 1u << lg) { begin[tid] = incl - cnt; above[tid] = all - incls; }
-        if (tid == 0) { begin[1u << lg] = size; *info = FINE_VALID | (near ? FINE_NEAR : 0u) | lg | shift << 4 | A.most << 9; }
+        if (tid == 0) { begin[1u << lg] = size; *info = FINE_VALID | (near ? FINE_NEAR : 0u) | lg | map.shift << 4 | A.most << 9; }
     }
     __syncthreads();
 #pragma unroll
@@ -1608,7 +1605,7 @@ __global__ __launch_bounds__(LLOYD_THREADS, 2u * lloyd_per_cu(KMAX)) void k_km_l
             p0 = q0; p1 = q1; near = (info & FINE_NEAR) != 0u;
             pos = bit_pos(mag);
             if (q1 - q0 >= FINE_LEAST) {
-                const u32 e = (q0 >> EXCP_FINE_SHIFT) + b + ((closed_key(c, mag) - closed_key(A.kmin[b], mag)) >> fine_shift(info));
+                const u32 e = (q0 >> EXCP_FINE_SHIFT) + b + ((excp_closed_key(c, mag) - excp_closed_key(A.kmin[b], mag)) >> fine_shift(info));
                 const u32 c0 = fb[e], c1 = fb[e + 1u];
                 up = fa[e];
                 p0 = q0 + c0; p1 = q0 + c1; above = q1 - p1;

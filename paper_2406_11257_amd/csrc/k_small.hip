@@ -316,14 +316,14 @@ __global__ __launch_bounds__(SM) void k_small_codes(Workspace w, GroupParams g) 
         const u32 base = bit_pos(mag), span = bit_pos(top) - base;
         const bool wide = span > WIDE_SPAN;               // more binary orders than 128 bits hold: sums in bins instead
         // the values by cell: equal ranges of the key
-        const u32 k0 = closed_key(kmin, mag), range = closed_key(kmax, mag) - k0, rbits = 32u - (u32)__clz((int)(range | 1u));
+        const u32 k0 = excp_closed_key(kmin, mag), range = excp_closed_key(kmax, mag) - k0, rbits = 32u - (u32)__clz((int)(range | 1u));
         const u32 shift = rbits > 12u ? rbits - 12u : 0u;
         u32 cell[PER];                                    // cell << 16 | arrival
 #pragma unroll
         for (u32 j = 0; j < PER; ++j) {
             cell[j] = 0;
             if (j * SM + tid >= len) continue;
-            const u32 c = (closed_key(key_of(v[j]), mag) - k0) >> shift;
+            const u32 c = (excp_closed_key(key_of(v[j]), mag) - k0) >> shift;
             cell[j] = c << 16 | atomicAdd(&A.begin[c], 1u);
             if (!wide) {
                 const CellSum q = halves(f2u(v[j]), base);
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(SM) void k_small_codes(Workspace w, GroupParams g) 
         }
         // the cell that a key of the stream's range belongs to: no smaller value lies in a higher one, no larger one in a lower
         auto cell_of_key = [&](u32 key) -> u32 {
-            if (!ties) return (closed_key(key, mag) - k0) >> shift;
+            if (!ties) return (excp_closed_key(key, mag) - k0) >> shift;
             u32 p = 0;                                    // number of values below the key (the key is not above all of them)
 #pragma unroll
             for (u32 step = EXCP_SMALL_ELEMS / 2u; step >= 1u; step >>= 1) if (p + step <= len && A.sorted[p + step - 1u] < key) p += step;

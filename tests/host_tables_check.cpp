@@ -1,5 +1,5 @@
-// Tables that groups of tensors share: rows of bucket counts, and the cells inside buckets.  Compiled and run by
-// tests/test_host_tables.py with the rules of excp_device.h; needs no GPU.
+// Tables that groups of tensors share: rows of bucket counts, and the cells inside buckets; and the cell of a value.  Compiled
+// and run by tests/test_host_tables.py with the rules of excp_device.h; needs no GPU.
 #include <stdio.h>
 
 #include <algorithm>
@@ -50,6 +50,40 @@ int main() {
                 end = at + (1u << lg) + 1;
             }
             elem_off += n[t];
+        }
+    }
+    // The cell that a value is filed in is the one that a border of the same key is looked up in, inside the table, and higher for
+    // higher values: buckets of one sign, of both, with zeros of either sign beside them, of nothing but zeros.
+    for (u32 shape = 0; shape < 600; ++shape) {
+        std::vector<u32> bits;                            // of the bucket's values
+        const u32 low = shape % 7 == 0 ? random() % 1000u : (1u + random() % 230u) << 23 | (random() & 0x7fffffu), orders = 1u + random() % 10u;
+        const u32 signs = shape % 3, zeros = shape / 3 % 4, count = shape % 11 == 0 ? 0u : 300u;      // signs: +, -, both; zeros: none, +0, -0, both
+        for (u32 i = 0; i < count; ++i) bits.push_back((low + random() % (orders << 23)) | (signs == 1 || (signs == 2 && i % 2) ? 0x80000000u : 0u));
+        if (zeros & 1u) bits.push_back(0u);
+        if (zeros & 2u) bits.push_back(0x80000000u);
+        if (bits.empty()) continue;
+        auto key = [](u32 b) { return b >> 31 ? ~b : b | 0x80000000u; };
+        std::sort(bits.begin(), bits.end(), [&](u32 a, u32 b) { return key(a) < key(b); });
+        const u32 kmin = key(bits.front()), kmax = key(bits.back());
+        u32 mag = 0;
+        for (u32 b : bits) if (b & 0x7fffffffu) mag = mag ? std::min(mag, b & 0x7fffffffu) : b & 0x7fffffffu;
+        if (kmin >= kmax) continue;
+        // places on a line without the gap: magnitudes count from the smallest one, zero lies between the signs
+        auto place = [&](u32 b) -> long long {
+            const long long a = (long long)(b & 0x7fffffffu) - mag + 1;
+            return (b & 0x7fffffffu) || !mag ? (b >> 31 ? -a : a) : 0;
+        };
+        for (u32 lg = 1; lg <= 9; ++lg) {
+            const CellMap M = excp_cell_map(kmin, kmax, mag, lg);
+            const unsigned long long range = (unsigned long long)(place(bits.back()) - place(bits.front()));
+            u32 shift = 0, last = 0;
+            while (range >> shift >> lg) ++shift;
+            CHECK(M.shift == shift, "shape %u, 2^%u cells: shift %u, not %u", shape, lg, M.shift, shift);
+            for (u32 b : bits) {
+                const u32 in = excp_cell_of_bits(M, b), want = (u32)((unsigned long long)(place(b) - place(bits.front())) >> shift);
+                CHECK(in == want && in < 1u << lg && in >= last && excp_cell_of_key(M, key(b)) == want, "shape %u, value %08x: cell %u of 2^%u, not %u", shape, b, in, lg, want);
+                last = in;
+            }
         }
     }
     if (fails) return 1;

@@ -30,13 +30,13 @@ def draw(n, seed, kind):
     return np.zeros(n, f32), d.astype(f32), m.astype(f32), v.astype(f32)
 
 
-def check(cases, nbits, iters, alpha=0.0, beta=0.0):
+def check(cases, nbits, iters, alpha=0.0, beta=0.0, flags=0):
     sizes = [c[0].size for c in cases]
     ctx = X.Context(max(sizes), sum(sizes))
-    rc, out = gpu_compress(ctx, cases, alpha, beta, nbits, iters)
+    rc, out = gpu_compress(ctx, cases, alpha, beta, nbits, iters, flags=flags)
     assert rc == 0
     for c, o in zip(cases, out):
-        assert o["blob"] == O.compress_step(*c, alpha, beta, nbits, iters).blob
+        assert o["blob"] == O.compress_step(*c, alpha, beta, nbits, iters, flags=flags).blob
     ctx.close()
 
 
@@ -65,6 +65,27 @@ def test_more_elements_than_go_with_cells():
     rc, out = gpu_compress(ctx, cases, 5e-5, 2.0, 4, 2, want_recon=False)
     assert rc == 0 and out[3]["blob"] == O.compress_step(*cases[3], 5e-5, 2.0, 4, 2).blob
     ctx.close()
+
+
+def with_zeros(n, zeros, sign):
+    """Second moments of one sign, `zeros` of them zero (of the same sign): fewer than a bucket's share, so that they lie in the
+    lowest (highest) bucket beside other values.  The ablations keep such elements."""
+    Wp, W, m, v = draw(n, n + zeros, "both signs")
+    v[np.random.default_rng(zeros).choice(n, zeros, replace=False)] = 0.0
+    return Wp, W, m, (v if sign > 0 else -v)
+
+
+@pytest.mark.parametrize("flags", [X.EXCP_FLAG_NO_W2M, X.EXCP_FLAG_NO_M2W])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_zeros_beside_values_of_one_sign(sign, flags):
+    for zeros in (1, 20, 400):
+        print(sign, flags, zeros, flush=True)
+        check([with_zeros(262_144, zeros, sign)], 8, 3, flags=flags)
+
+
+def test_zeros_in_a_bucket_of_512_cells():
+    # 9 M moments, every one kept: the lowest bucket has more than 512 x 64 values; next to no residuals
+    check([with_zeros(9_000_000, 100, 1)], 8, 1, alpha=1e6, flags=X.EXCP_FLAG_NO_W2M)
 
 
 def test_repeated_calls_on_one_context():
