@@ -182,6 +182,7 @@ struct Workspace {
     u32 *chunk_total;         // [1]
     u32 *seg_chunk_begin;     // [segments + 1] first chunk of every survivor stream
     u32 *scan_ticket;         // [1] tensors whose survivors have been counted (0 between launches)
+    u32 *no_cells;            // [1] the group's survivors or a stream's buckets are too many or too large for cells (see k_km_scan)
     u32 *lloyd_shared;        // [1] TState::lloyd_shared of some tensor of the group
     u32 *seg_unit_begin;      // [segments + 1] first work unit of every survivor stream in a Lloyd iteration that many workgroups take
     float *pw, *pm, *pv;      // survivors partitioned into value-ordered buckets (same offsets as xw/xm/xv)
@@ -291,6 +292,19 @@ static __host__ __device__ inline bool excp_fine_tensor(u64 n) { return n >= 1ul
 #define EXCP_FINE_SMALL (1ull << 21)
 #define EXCP_FINE_MIDDLE (9ull << 21)
 #define EXCP_FINE_LARGEST (25ull << 20)
+static inline u32 excp_fine_size(u64 largest) { return largest <= EXCP_FINE_SMALL ? 0u : (largest <= EXCP_FINE_MIDDLE ? 1u : 2u); }
+// Values that a bucket may have, by GroupParams::fine_size, and chunks of survivors that a group may: beyond either the
+// group goes without cells (k_km_scan), which is what these sizes come to where more than a third is kept.  Where every element
+// is (alpha = 0; beta = 0 with no check of the weights that drops any) that is known before the call, and the group does not
+// set out for cells: `whole` of the three streams, and buckets a third above the average.  (Everything kept, 4 bits, us a
+// call without cells / with what was made of them before: 2 M elements 488 / 532, 10 M 744 / 845, 3 x 8 M 1210 / 1384, 40 x 500 000
+// 1191 / 1296; with cells that fit, 4 M 532 / 445, 10 x 500 000 585 / 547.)
+static __host__ __device__ constexpr u32 excp_cells_most(u32 fine_size) { return fine_size == 0u ? 8192u : (fine_size == 1u ? 40960u : 53248u); }
+#define EXCP_FINE_CHUNKS 4096u
+static inline bool excp_fine_group(u64 elems, u64 largest, u32 whole) {
+    return elems <= EXCP_FINE_LARGEST && (whole == 0u || (whole * elems <= (u64)EXCP_FINE_CHUNKS * EXCP_CHUNK &&
+                                                          largest + largest / 3u <= 256ull * excp_cells_most(excp_fine_size(largest))));
+}
 
 // Tensors so small that one workgroup takes their streams through all Lloyd iterations whatever the values are
 // (unless their group goes together and has others).

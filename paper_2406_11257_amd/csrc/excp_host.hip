@@ -371,6 +371,7 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.seg_chunk_begin, 3ull * kMaxGroupTensors + 4);
     ok = ok && dev_alloc(c, &w.scan_ticket, 1);
     ok = ok && dev_alloc(c, &w.lloyd_shared, 1);
+    ok = ok && dev_alloc(c, &w.no_cells, 1);
     ok = ok && dev_alloc(c, &w.seg_unit_begin, 3ull * kMaxGroupTensors + 4);
     const u64 nseg_max = 3ull * kMaxGroupTensors;
     const u64 acc_words = kAccSegCentres * 3 * (EXCP_ABSM_BINS + 1);
@@ -592,12 +593,14 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         const bool w16 = (flags & 0x30u) != 0;
         if (!raw) {
             p.together = lloyd_together(g, nbig) ? 1u : 0u;
-            for (u32 q = 0; q < nbig; ++q) p.fine += p.together && !w16 && elems <= EXCP_FINE_LARGEST && excp_fine_tensor(descs.h[g.first + q].n) ? 1u : 0u;
+            const u32 whole = (alpha == 0.f ? 1u : 0u) + (beta == 0.f && (alpha == 0.f || (flags & EXCP_FLAG_NO_W2M)) ? 2u : 0u);
+            const bool cells = p.together && !w16 && excp_fine_group(elems, largest, whole);
+            for (u32 q = 0; q < nbig; ++q) p.fine += cells && excp_fine_tensor(descs.h[g.first + q].n) ? 1u : 0u;
             p.alone_work = p.fine ? kAloneCells : (p.together ? kAloneTogether : (K < 63 ? kAloneFew : kAloneMany));
             for (u32 q = 0; q < nbig; ++q) p.slots += descs.h[g.first + q].acc_slot != EXCP_NO_SLOT ? 1u : 0u;
         }
         p.unit_shift = excp_unit_shift(elems, nbig, excp_gather_subs(g.ntiles, (u32)w.cus), (u32)w.cus, excp_count_rows(c->max_group, kMaxGroupTensors));
-        p.fine_size = largest <= EXCP_FINE_SMALL ? 0u : (largest <= EXCP_FINE_MIDDLE ? 1u : 2u);
+        p.fine_size = excp_fine_size(largest);
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
         { StageTimer t(c, ST_LAYOUT); }                      // (made inside the mask scan and k_small_front: the span, one a group, is empty)
         // The small tensors: two launches, beside the larger ones on the context's own stream.  (They depend on nothing but what was

@@ -316,7 +316,14 @@ __global__ __launch_bounds__(SCAN_PARTS * 64) void k_km_scan(Workspace w, GroupP
         if (lane == 63u) { s_wave[part] = incl; s_most[part] = most; }
     }
     __syncthreads();
-    if (tid == 0) w.seg[sidx].crowded = (u64)max(max(s_most[0], s_most[1]), max(s_most[2], s_most[3])) > 3ull * (len / NBKT) + 1024ull ? 1u : 0u;
+    if (tid == 0) {
+        const u32 most = max(max(s_most[0], s_most[1]), max(s_most[2], s_most[3]));
+        const bool crowded = (u64)most > 3ull * (len / NBKT) + 1024ull;
+        w.seg[sidx].crowded = crowded ? 1u : 0u;
+        // (a stream whose buckets do not fit the workgroups has its iterations shared out; they are what is waited for, so cells
+        // in the buckets of others would gain nothing.  A crowded stream goes without by itself.)
+        if (!crowded && most > excp_cells_most(g.fine_size)) *w.no_cells = 1u;
+    }
     if (tid < NBKT) {
         u32 run = incl - total;
         for (u32 v = 0; v < part; ++v) run += s_wave[v];
@@ -811,7 +818,7 @@ __global__ __launch_bounds__(THREADS) void k_km_cells(Workspace w, GroupParams g
     static_assert(MOST / STAGE * STAGE == MOST && MOST < 0xffffu, "places have 16 bits");
     // (the values of a crowded stream are not spread by keys either, and the many workgroups that share its iterations would meet at
     // the same centres if its buckets were in order: 300 000 residuals of a sign-like update, 8 bits, 386 -> 821 us)
-    if (size < FINE_LEAST || size > MOST || kmin >= kmax || w.seg[sidx].crowded || bit_pos(top) - bit_pos(mag) > FINE_SPAN) {
+    if (size < FINE_LEAST || size > MOST || kmin >= kmax || *w.no_cells || w.seg[sidx].crowded || bit_pos(top) - bit_pos(mag) > FINE_SPAN) {
         if (tid == 0) w.km_fine[at] = 0u;
         return;
     }
@@ -2108,9 +2115,9 @@ void launch_km_partition(const Workspace &w, const GroupParams &g, int phase, hi
 void launch_km_cells(const Workspace &w, const GroupParams &g, hipStream_t s) {
     if (!g.fine) return;
     const dim3 grid(3u * g.fine * NBKT);
-    if (g.fine_size == 0u) hipLaunchKernelGGL((k_km_cells<512, 8192, 8192>), grid, dim3(512), 0, s, w, g);
-    else if (g.fine_size == 1u) hipLaunchKernelGGL((k_km_cells<1024, 40960, 20480>), grid, dim3(1024), 0, s, w, g);
-    else hipLaunchKernelGGL((k_km_cells<512, 53248, 26624>), grid, dim3(512), 0, s, w, g);
+    if (g.fine_size == 0u) hipLaunchKernelGGL((k_km_cells<512, excp_cells_most(0u), 8192>), grid, dim3(512), 0, s, w, g);
+    else if (g.fine_size == 1u) hipLaunchKernelGGL((k_km_cells<1024, excp_cells_most(1u), 20480>), grid, dim3(1024), 0, s, w, g);
+    else hipLaunchKernelGGL((k_km_cells<512, excp_cells_most(2u), 26624>), grid, dim3(512), 0, s, w, g);
 }
 
 void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s) {

@@ -27,6 +27,14 @@ int main() {
                     CHECK(need <= have, "%llu rows of %llu: %llu elements, %u tensors, 2^%u", need, have, elems, tensors, s);
                     CHECK(s >= 14 && s <= EXCP_UNIT_SHIFT && (u64)subs * 2048 <= 1ull << s && subs >= 4 && subs % 4 == 0, "2^%u, %u sub-tiles", s, subs);
                 }
+    // A group that is known to keep whole streams sets out for cells only if they are not too many and buckets a third above the
+    // average fit; a single tensor without a known share, up to the largest of the rule.
+    for (u64 n : {131072ull, 1500000ull, 1700000ull, 2097152ull, 2097153ull, 7000000ull, 8000000ull, 16777216ull, 26214400ull, 26214401ull})
+        for (u32 count : {1u, 3u, 40u})
+            for (u32 whole = 0; whole <= 3; ++whole) {
+                const bool fits = n / 256 * 4 / 3 <= excp_cells_most(excp_fine_size(n)), want = n * count <= 26214400ull && (!whole || (fits && whole * n * count <= 33554432ull));
+                CHECK(excp_fine_group(n * count, n, whole) == want, "%u tensors of %llu elements, %u whole streams", count, n, whole);
+            }
     // No two buckets' entries in the cell tables overlap, and none lies outside.
     for (u32 shape = 0; shape < 40; ++shape) {
         const u32 tensors = shape % 4 == 0 ? 1u : 1u + random() % 90u;
