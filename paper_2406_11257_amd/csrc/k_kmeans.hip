@@ -710,6 +710,11 @@ __global__ __launch_bounds__(BS_WAVES * 64, BS_WAVES == 16u ? 8 : 5) void k_km_b
 constexpr u32 FINE_SPAN = 23, FINE_LEAST = 256;            // smaller buckets are one cell without any table
 // km_fine: cells' log2 | shift << 4 | largest cell << 9 | FINE_NEAR: the values span eight binary orders at most | FINE_VALID
 constexpr u32 FINE_VALID = 1u << 31, FINE_NEAR = 1u << 30, NEAR_SPAN = 8;
+// Values over more than eight binary orders lie bunched in a few cells, and add up in integers, thirty-five instructions each: with a
+// cell of more than so many the bucket is read as a whole by the workgroup sooner than a cell by its border's few lanes.  (500 000
+// elements, all kept, 8 bits, a middle bucket of 2000 values in 21 binary orders: 600 us with its cells, 492 without, 495 before there
+// were any.)
+constexpr u32 FAR_MOST = 256;
 __device__ __forceinline__ u32 fine_log2(u32 info) { return info & 15u; }
 __device__ __forceinline__ u32 fine_shift(u32 info) { return (info >> 4) & 31u; }
 __device__ __forceinline__ u32 fine_most(u32 info) { return (info >> 9) & 0xffffu; }
@@ -773,6 +778,10 @@ __device__ __forceinline__ void cells_of_bucket(EXCP_GLOBAL float *part, u32 siz
         if (lane == 63u) { A.wave_cnt[wave] = incl; A.wave_sum[wave] = incls; atomicMax(&A.most, most); }
     }
     __syncthreads();
+    if (!near && A.most > FAR_MOST) {                      // (the same in the whole workgroup)
+        if (tid == 0) *info = 0u;
+        return;
+    }
     if (tid < 512u) {
         u64 all = 0;
 #pragma unroll
@@ -1672,9 +1681,13 @@ __global__ __launch_bounds__(LLOYD_THREADS, 2u * lloyd_per_cu(KMAX)) void k_km_l
                     }
                     sum = (u64)(long long)ldexp(part_sum, 149 - (int)pos);
                 } else {
-                    for (u32 p = p0 + l; p < p1; p += ROW) {
-                        const float x = part[p];
-                        if (x >= t) { sum += value_units(f2u(x), pos); ++cnt; }
+                    for (u32 p = p0 + l; p < p1; p += BATCH / 2u * ROW) {
+                        float x[BATCH / 2u];
+#pragma unroll
+                        for (u32 j = 0; j < BATCH / 2u; ++j) x[j] = part[min(p + ROW * j, p1 - 1u)];
+#pragma unroll
+                        for (u32 j = 0; j < BATCH / 2u; ++j)
+                            if (p + ROW * j < p1 && x[j] >= t) { sum += value_units(f2u(x[j]), pos); ++cnt; }
                     }
                 }
             }
@@ -1689,10 +1702,15 @@ __global__ __launch_bounds__(LLOYD_THREADS, 2u * lloyd_per_cu(KMAX)) void k_km_l
         }
         if (!narrow) {
             __syncthreads();
-            for (u32 j = tid; j < (st.acc_hi + 1u - st.acc_lo) * K; j += LLOYD_THREADS) {
-                const u32 q = st.acc_lo + j / K, k = j % K;
-                const u32 f = A.first[k], l1 = k + 1u < K ? A.first[k + 1u] : NBKT;
-                A.acc[q * K + k] = q >= st.bin_lo && q <= st.bin_hi ? st.bs[q * (NBKT + 1u) + l1] - st.bs[q * (NBKT + 1u) + f] : 0ull;
+            // (a wave takes a bin, a lane every 64th centre: the loads of a bin are on their way together)
+            for (u32 q = st.acc_lo + wave; q <= st.acc_hi; q += LLOYD_WAVES) {
+                const bool any = q >= st.bin_lo && q <= st.bin_hi;
+                const u64 *row = st.bs + q * (NBKT + 1u);
+#pragma unroll
+                for (u32 j = 0; j < (KMAX + 63u) / 64u; ++j) {
+                    const u32 k = j * 64u + lane;
+                    if (k < K) A.acc[q * K + k] = any ? row[k + 1u < K ? A.first[k + 1u] : NBKT] - row[A.first[k]] : 0ull;
+                }
             }
         }
         __syncthreads();

@@ -78,6 +78,13 @@ def test_groups_that_turn_out_to_keep_too_much_for_cells(sizes):
     ctx.close()
 
 
+@pytest.mark.parametrize("n, seed", [(131_072, 2), (131_072, 5), (500_000, 1)])
+def test_a_bucket_over_many_orders_with_a_large_cell_and_without(n, seed):
+    # everything kept: the middle bucket of the residuals spans ten binary orders and its largest cell has some 230 of 513 values,
+    # or sixteen orders and a cell of some 1000 of 1953
+    check([draw(n, seed, "both signs")], 8, 3)
+
+
 def with_zeros(n, zeros, sign):
     """Second moments of one sign, `zeros` of them zero (of the same sign): fewer than a bucket's share, so that they lie in the
     lowest (highest) bucket beside other values.  The ablations keep such elements."""
