@@ -151,6 +151,7 @@ struct GroupParams {
     u32 unit_shift;             // log2 of the positions of a stream whose bucket counts share a row
     u32 fine;                   // the first `fine` tensors in order of size have cells inside their buckets (k_km_cells)
     u32 fine_size;              // ... by the workgroups of size 0, 1 or 2
+    u32 samples;                // values of a stream that its value -> bucket map is made from
 };
 
 #define EXCP_RAW_BITS    32u       // "code" width of a blob written without quantisation: fp32 values, no codebooks
@@ -304,6 +305,18 @@ static __host__ __device__ constexpr u32 excp_cells_most(u32 fine_size) { return
 static inline bool excp_fine_group(u64 elems, u64 largest, u32 whole) {
     return elems <= EXCP_FINE_LARGEST && (whole == 0u || (whole * elems <= (u64)EXCP_FINE_CHUNKS * EXCP_CHUNK &&
                                                           largest + largest / 3u <= 256ull * excp_cells_most(excp_fine_size(largest))));
+}
+
+// Samples of a stream, from which its buckets are made: 32 to a bucket, whose sizes then differ by 18 %, or 64 and 12 % where
+// cells are made and a bucket sixty per cent above the average of the largest tensor, a third of it kept, would fill more than three
+// quarters of a workgroup (from 14.7 M elements on; of 25 M a few buckets did not fit otherwise).  More samples cost more to draw, and of
+// a sign-like update they are more likely to meet one of the few strays, whose range then leaves all other values in two
+// buckets: with 64 to a bucket whenever cells are made, such an update of 10 M elements took 4313 us instead of 1103 before there
+// were cells, sixty tensors of 11 M in all 1576 instead of 1113; with 32, 1091 and 1160.)
+#define EXCP_SAMPLES_FEW  8192u
+#define EXCP_SAMPLES_MANY 16384u
+static inline u32 excp_samples(bool cells, u64 largest) {
+    return cells && largest / 480u > excp_cells_most(excp_fine_size(largest)) / 4u * 3u ? EXCP_SAMPLES_MANY : EXCP_SAMPLES_FEW;
 }
 
 // Tensors so small that one workgroup takes their streams through all Lloyd iterations whatever the values are

@@ -28,9 +28,6 @@
 namespace {
 
 constexpr u32 NBKT = 256;
-// Samples of a stream: 32 to a bucket, whose sizes then differ by 18 %, or 64 and 12 % where buckets are cut into cells (of 25 M
-// elements a few did not fit the workgroups otherwise).
-__device__ __forceinline__ u32 sample_size(const GroupParams &g) { return g.fine ? 16384u : 8192u; }
 constexpr u32 PER_THREAD = EXCP_CHUNK / EXCP_THREADS;   // 32
 
 __device__ __forceinline__ const float *seg_data(const Workspace &w, u32 sidx) {
@@ -112,7 +109,7 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_km_draw(Workspace w, GroupPara
     __shared__ u32 s_coarse[COARSE];
     const u32 sidx = blockIdx.x / DRAW_PARTS, part = blockIdx.x % DRAW_PARTS, tid = threadIdx.x;
     const u64 len = w.seg[sidx].len;
-    const u32 ns = (u32)min(len, (u64)sample_size(g));
+    const u32 ns = (u32)min(len, (u64)g.samples);
     {   // the stream's rows of the count table start at zero (the counts are taken by k_mask_gather)
         const u32 rows = (u32)((len + (1ull << g.unit_shift) - 1u) >> g.unit_shift);
         u32 *row0 = w.km_cnt + (u64)w.seg[sidx].row_begin * NBKT;
@@ -182,11 +179,11 @@ __global__ __launch_bounds__(SM_THREADS) void k_km_sample(Workspace w, GroupPara
     __shared__ u32 s_map[4];
     __shared__ u32 s_ext[4];                       // min / max magnitude of the negative, of the positive samples
     __shared__ u32 s_wave[SM_THREADS / 64];
-    constexpr u32 PER_S = 16384 / SM_THREADS;
+    constexpr u32 PER_S = EXCP_SAMPLES_MANY / SM_THREADS;
     const u32 sidx = blockIdx.x, tid = threadIdx.x;
     const u64 len = w.seg[sidx].len;
     if (len == 0) return;
-    const u32 ns = (u32)min(len, (u64)sample_size(g));
+    const u32 ns = (u32)min(len, (u64)g.samples);
     const float *smp = seg_sample(w, sidx);
     if (tid < 4) s_ext[tid] = (tid & 1u) ? 0u : 0xffffffffu;
     for (u32 c = tid; c < EXCP_KM_CELLS; c += SM_THREADS) cnt[c] = 0;
@@ -2106,8 +2103,8 @@ void launch_km_partition(const Workspace &w, const GroupParams &g, int phase, hi
     const u32 nseg = 3 * g.ntensors;
     switch (phase) {
         case 0:
-            if (g.fine) hipLaunchKernelGGL(k_km_draw<4>, dim3(nseg * DRAW_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
-            else hipLaunchKernelGGL(k_km_draw<2>, dim3(nseg * DRAW_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
+            if (g.samples > EXCP_SAMPLES_FEW) hipLaunchKernelGGL(k_km_draw<EXCP_SAMPLES_MANY / (DRAW_PARTS * EXCP_THREADS)>, dim3(nseg * DRAW_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
+            else hipLaunchKernelGGL(k_km_draw<EXCP_SAMPLES_FEW / (DRAW_PARTS * EXCP_THREADS)>, dim3(nseg * DRAW_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
             hipLaunchKernelGGL(k_km_sample, dim3(nseg), dim3(SM_THREADS), 0, s, w, g); break;
         case 1: hipLaunchKernelGGL(k_km_scan, dim3(nseg), dim3(SCAN_PARTS * 64), 0, s, w, g); break;
         case 2: hipLaunchKernelGGL(k_km_scatter, dim3(excp_grid(w, 1)), dim3(SC_THREADS), 0, s, w, g); break;

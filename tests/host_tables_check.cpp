@@ -1,5 +1,6 @@
 // Tables that groups of tensors share: rows of bucket counts, and the cells inside buckets; and the cell of a value.  Compiled
 // and run by tests/test_host_tables.py with the rules of excp_device.h; needs no GPU.
+#include <math.h>
 #include <stdio.h>
 
 #include <algorithm>
@@ -35,6 +36,12 @@ int main() {
                 const bool fits = n / 256 * 4 / 3 <= excp_cells_most(excp_fine_size(n)), want = n * count <= 26214400ull && (!whole || (fits && whole * n * count <= 33554432ull));
                 CHECK(excp_fine_group(n * count, n, whole) == want, "%u tensors of %llu elements, %u whole streams", count, n, whole);
             }
+    // A third of the largest tensor kept, its buckets fit the workgroups also where they are four deviations above the average.
+    for (u64 n = 131072; n <= EXCP_FINE_LARGEST; n += n / 50) {
+        const u32 samples = excp_samples(true, n);
+        const double largest = (double)n / 3 / 256 * (1 + 4 / sqrt(samples / 256.0));
+        CHECK(largest <= excp_cells_most(excp_fine_size(n)) && excp_samples(false, n) == EXCP_SAMPLES_FEW && samples <= EXCP_SAMPLES_MANY, "%llu elements, %u samples: %g", n, samples, largest);
+    }
     // No two buckets' entries in the cell tables overlap, and none lies outside.
     for (u32 shape = 0; shape < 40; ++shape) {
         const u32 tensors = shape % 4 == 0 ? 1u : 1u + random() % 90u;

@@ -53,6 +53,10 @@ def test_buckets_on_both_sides_of_the_small_workgroup(n):
     check([draw(n, 3, "both signs"), draw(1000, 4, "one sign")], 4, 2)
 
 
+def test_a_tensor_whose_buckets_take_more_samples():
+    check([draw(14_800_001, 9, "both signs")], 4, 1, alpha=5e-5, beta=2.0)
+
+
 def test_small_tensors_beside_large_ones():
     check([draw(n, n, k) for n, k in ((300_000, "both signs"), (5, "one sign"), (131_072, "crowded"), (4096, "orders"), (70_001, "far apart"))], 6, 3)
 
