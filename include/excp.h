@@ -295,7 +295,10 @@ int excp_decompress_step_static(int hip_device, void *hip_stream, const void *W_
 /* Per-stage timing.  When enabled, HIP events bracket every kernel stage of the next batches;
  * after excp_collect, excp_stage_ms returns the summed milliseconds of stage `i` and how many spans of it
  * were timed (a span may be several kernels: all Lloyd iterations of a group are one)
- * (0 <= i < excp_stage_count()); excp_stage_name names it. */
+ * (0 <= i < excp_stage_count()); excp_stage_name names it.  Stages may add up to more than the call: tensors
+ * of up to 8192 elements go beside the larger ones of their group, on a stream of the context's own, and
+ * are timed there (one span a group, "misc"), and "km_iter" lasts until that stream is done too.  "layout"
+ * counts the groups; its work is done inside "mask_scan". */
 int         excp_set_profiling(excp_ctx *ctx, int enabled);
 int         excp_stage_count(void);
 const char *excp_stage_name(int i);

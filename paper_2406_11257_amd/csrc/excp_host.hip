@@ -106,19 +106,20 @@ bool dev_alloc(excp_ctx *c, T **p, u64 count) {
 }
 
 struct StageTimer {
-    excp_ctx *c; int stage; hipEvent_t a = nullptr, b = nullptr;
-    StageTimer(excp_ctx *ctx, int st) : c(ctx), stage(st) {
+    excp_ctx *c; int stage; hipStream_t on; hipEvent_t a = nullptr, b = nullptr;
+    StageTimer(excp_ctx *ctx, int st) : StageTimer(ctx, st, ctx->stream) {}
+    StageTimer(excp_ctx *ctx, int st, hipStream_t stream) : c(ctx), stage(st), on(stream) {
         if (!c->profiling) return;
         // events come from the pool excp_set_profiling made; a batch with more stages than the pool
         // holds leaves the rest untimed rather than create events in the middle of a step
         if (c->free_events.size() < 2) return;
         a = c->free_events.back(); c->free_events.pop_back();
         b = c->free_events.back(); c->free_events.pop_back();
-        (void)hipEventRecord(a, c->stream);
+        (void)hipEventRecord(a, on);
     }
     ~StageTimer() {
         if (!c->profiling || !a || !b) return;
-        (void)hipEventRecord(b, c->stream);
+        (void)hipEventRecord(b, on);
         c->spans.push_back({stage, a, b});
     }
 };
@@ -614,14 +615,9 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             ps.ntensors = nsmall;
             const hipStream_t to = nbig ? c->side.stream : s;
             if (nbig) { (void)hipEventRecord(c->side.fork, s); (void)hipStreamWaitEvent(c->side.stream, c->side.fork, 0); }
-            if (nbig) {
-                launch_small_front(ws, ps, single ? descs.h : nullptr, to);
-                launch_small_codes(ws, ps, to);
-            } else {
-                StageTimer t(c, ST_MISC);
-                launch_small_front(ws, ps, single ? descs.h : nullptr, to);
-                launch_small_codes(ws, ps, to);
-            }
+            StageTimer t(c, ST_MISC, to);
+            launch_small_front(ws, ps, single ? descs.h : nullptr, to);
+            launch_small_codes(ws, ps, to);
         }
         if (!nbig) continue;
         { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, single ? descs.h : nullptr, s); }

@@ -98,8 +98,37 @@ def test_alone_and_over_the_previous_weights(ctx, n):
     check(ctx, [draw(n, n, "spread")], 4, 0)
 
 
-def test_one_larger_tensor_takes_all_the_general_way(ctx):
-    check(ctx, [draw(n, n, "spread") for n in (100, 8192, 8193)], 4, 10)
+def test_small_tensors_beside_a_larger_one(ctx):
+    """The larger one takes the general kernels, the others their own on the context's second stream: timed there, in one span."""
+    cases = [draw(n, n, "spread") for n in (100, 8192, 8193)]
+    check(ctx, cases, 4, 10)
+    ctx.excp_set_profiling(True)
+    try:
+        for part, spans in ((cases, (1, 1, 1)), (cases[:2], (1, 1, 0)), (cases[2:], (1, 0, 1))):
+            check(ctx, part, 4, 10)
+            t = ctx.stage_times()
+            assert (t["layout"][1], t["misc"][1], t["mask_slots"][1]) == spans
+            assert t["misc"][0] > 0 or not spans[1]
+    finally:
+        ctx.excp_set_profiling(False)
+
+
+@pytest.mark.parametrize("nbits", [4, 8])
+def test_several_groups_of_small_and_larger_tensors(nbits):
+    """Groups follow one another through the same areas while small tensors go beside the larger ones: with larger tensors whose
+    Lloyd iterations may be shared out (they join the second stream themselves), without any such, and alone."""
+    r = np.random.default_rng(nbits)
+    sizes = [300_000, 8192, 100, 90_000, 5000, 8193, 8000, 20_000, 300_001, 1, 700, 60_000, 3000, 64, 8191, 30_000, 9000, 4096, 40_001, 2000]
+    cases = [draw(n, int(r.integers(1 << 30)), ("spread", "tied", "crowded")[i % 3]) for i, n in enumerate(sizes)]
+    c = X.Context(300_001, 310_000)
+    c.excp_set_profiling(True)
+    try:
+        for _ in range(3):
+            check(c, cases, nbits, 3, in_place=True)
+            t = c.stage_times()
+            assert t["layout"][1] >= 3 and t["misc"][1] >= 3
+    finally:
+        c.close()
 
 
 def test_errors_stay_with_their_tensor(ctx):
