@@ -90,9 +90,15 @@ def test_crowded_buckets_on_both_sides_of_the_lines(ctx, kind):
 
 @pytest.mark.parametrize("nbits, n", [(2, 4_200_001), (3, 1_200_001), (4, 460_001), (5, 210_001), (6, 300_001), (7, 140_001), (8, 70_001)])
 def test_even_buckets_of_one_tensor_in_both_ways(ctx, nbits, n):
-    # alone at the usual thresholds, or shared where every value is kept
+    # (by one workgroup a stream: at the usual thresholds, or because the larger buckets have cells)
     check(ctx, [draw(n, nbits, "spread")], nbits, 2)
     check(ctx, [draw(n, nbits, "spread"), draw(100, 3, "spread")], nbits, 2, alpha=5e-5, beta=2.0)
+
+
+@pytest.mark.parametrize("nbits", [3, 5, 8])
+def test_even_buckets_shared_out(ctx, nbits):
+    # everything kept and known beforehand to be more than cells are made for
+    check(ctx, [draw(1_700_001, nbits, "spread")], nbits, 2)
 
 
 def test_both_ways_in_one_group(ctx):
