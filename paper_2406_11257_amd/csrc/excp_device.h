@@ -247,6 +247,10 @@ static inline u32 excp_unit_shift(u64 elems, u32 tensors, u32 subs, u32 cus, u64
     return s;
 }
 
+// A tensor's area in the arrays of survivors (whole lines: it begins on a multiple of 64 elements), and what a group's take.
+static inline u64 excp_area_elems(u64 n) { return (n + 63) & ~63ull; }
+static inline u64 excp_survivor_elems(u64 group_elems, u32 group_tensors) { return group_elems + 63ull * group_tensors; }
+
 // Cells inside a bucket of 256 values or more: the largest power of two that leaves them 64 values each on average, 512
 // at most.  A bucket's entries in the tables begin at (its tensor's elem_off >> 6) + 258 x tensor + (its first
 // position >> 6) + its number, and are one more than its cells, so no two buckets' overlap.

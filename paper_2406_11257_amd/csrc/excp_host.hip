@@ -345,7 +345,7 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
         c->free_events.reserve(kEventPool);
     } catch (...) { delete c; return EXCP_E_HIP; }
     Workspace &w = c->w;
-    const u64 G = max_group_elems + 63ull * kMaxGroupTensors;      // (survivor areas: every tensor's begins on a multiple of 64)
+    const u64 G = excp_survivor_elems(max_group_elems, kMaxGroupTensors);
     const u64 max_tiles = G / EXCP_TILE + kMaxGroupTensors + 1;
     const u64 chunks_group = 3 * (G / EXCP_CHUNK) + 3 * kMaxGroupTensors + 3;
     c->max_tiles = max_tiles;
@@ -552,7 +552,7 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             cand_off += d.cand_cap;
             d.tile_count = (u32)((t.n + EXCP_TILE - 1) / EXCP_TILE);
             d.acc_slot = q < nbig && t.n && (together || !small(i)) ? slot++ : EXCP_NO_SLOT; d.rec = i - g.first;
-            elem_off += (t.n + 63) & ~63ull;              // (slots begin on whole lines)
+            elem_off += excp_area_elems(t.n);
             if (q >= nbig) continue;
             tiles.h[tb_off + q] = tile;
             tile += d.tile_count;

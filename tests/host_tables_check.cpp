@@ -9,6 +9,7 @@
 #include "../paper_2406_11257_amd/csrc/excp_device.h"
 
 static int fails = 0;
+static const u32 GROUP = 1024;                            // tensors that a group takes
 #define CHECK(c, ...) do { if (!(c)) { printf("FAIL line %d: %s: ", __LINE__, #c); printf(__VA_ARGS__); printf("\n"); ++fails; } } while (0)
 
 int main() {
@@ -21,7 +22,7 @@ int main() {
                 for (u64 elems : {(u64)tensors, G / 7 + tensors, G}) {
                     if (elems > G) continue;
                     const u32 ntiles = (u32)(elems / EXCP_TILE + tensors), subs = excp_gather_subs(ntiles, cus);
-                    const u64 have = excp_count_rows(G, 1024);
+                    const u64 have = excp_count_rows(G, GROUP);
                     const u32 s = excp_unit_shift(elems, tensors, subs, cus, have);
                     u64 need = 0;                                     // tensors of one element each but the last
                     need += 3ull * (tensors - 1) + 3 * ((elems - (tensors - 1) + (1ull << s) - 1) >> s);
@@ -42,15 +43,18 @@ int main() {
         const double largest = (double)n / 3 / 256 * (1 + 4 / sqrt(samples / 256.0));
         CHECK(largest <= excp_cells_most(excp_fine_size(n)) && excp_samples(false, n) == EXCP_SAMPLES_FEW && samples <= EXCP_SAMPLES_MANY, "%llu elements, %u samples: %g", n, samples, largest);
     }
-    // No two buckets' entries in the cell tables overlap, and none lies outside.
-    for (u32 shape = 0; shape < 40; ++shape) {
-        const u32 tensors = shape % 4 == 0 ? 1u : 1u + random() % 90u;
+    // No two buckets' entries in the cell tables overlap, and none lies outside; nor does a tensor's survivor area.  Areas begin on
+    // multiples of 64 elements, for which a context of G elements has 63 a tensor more.
+    for (u32 shape = 0; shape < 44; ++shape) {
+        const bool many = shape >= 40;                    // as many tensors as a group takes, all of odd length
+        const u32 tensors = many ? GROUP : (shape % 4 == 0 ? 1u : 1u + random() % 90u);
         std::vector<u64> n(tensors);
         u64 G = 0;
-        for (auto &x : n) { x = 1 + random() % (shape % 3 == 0 ? 300u : 400000u); G += x; }
-        const u64 words = excp_fine_words(G, 1024);
+        for (auto &x : n) { x = many ? 1u + 64u * (random() % (shape == 43 ? 3u : 300u)) : 1 + random() % (shape % 3 == 0 ? 300u : 400000u); G += x; }
+        const u64 area = excp_survivor_elems(G, GROUP), words = excp_fine_words(area, GROUP);
         u64 elem_off = 0, end = 0;
         for (u32 t = 0; t < tensors; ++t) {
+            CHECK(elem_off % 64 == 0 && elem_off + n[t] <= area, "tensor %u at %llu + %llu of %llu", t, elem_off, n[t], area);
             const u32 len = shape % 2 ? (u32)n[t] : (u32)(n[t] / 3);
             std::vector<u32> cut{0u, len};
             for (u32 b = 1; b < 256; ++b) cut.push_back(shape % 5 == 0 ? len : random() % (len + 1));
@@ -64,7 +68,7 @@ int main() {
                 CHECK(lg >= 1 && lg <= 9 && (size >> lg) >= 64 && (lg == 9 || (size >> lg) < 128), "%u values in 2^%u cells", size, lg);
                 end = at + (1u << lg) + 1;
             }
-            elem_off += n[t];
+            elem_off += excp_area_elems(n[t]);
         }
     }
     // The cell that a value is filed in is the one that a border of the same key is looked up in, inside the table, and higher for
