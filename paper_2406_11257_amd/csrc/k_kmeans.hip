@@ -1107,11 +1107,13 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
 // iteration 8 us, a launch 14).  The host launches the iterations of the second way wherever a tensor is too large for
 // excp_lloyd_small; where no stream takes it they are empty.  (2^17 elements: one workgroup needs 0.43 ms for 130 000 residuals
 // of a sign-like update, the former work lists needed 0.81; 2^22 for three centres, of whose borders a bucket holds two at most.)
-//   Without cells (excp_fine_tensor), up to 85 tensors on 256 compute units go together, the line at 24 576.  (One tensor, 4 bits,
-//   ten iterations, us alone / shared: 1 M elements 163 / 178, 2.5 M 207 / 174, 10 M 340 / 169.)
-//   More tensors fill the GPU as they are, one workgroup a stream, and the line lies at 196 608 (300 tensors of 600 000
-//   elements, 4 bits: 338 alone, 522 shared; the 410M shape 440, and 499 with the line at 65 536), from six bits on at
-//   131 072 (the 410M shape in 7 bits 1943, and 2406 with the line at 196 608).
+//   Without cells (excp_fine_group), up to 85 tensors on 256 compute units go together, the line at 24 576.  (One tensor, ten
+//   iterations, us alone / shared: 4 bits, 500 000 elements 152 / 181, 1.5 M 174 / 190, 2.5 M 194 / 178, 10 M 343 / 172; 8 bits,
+//   300 000 elements 834 / 750, 1 M 1056 / 227, 10 M 4020 / 222.)
+//   More tensors fill the GPU as they are, one workgroup a stream, and the line lies at 196 608 (4 bits: 300 tensors of 600 000
+//   elements 289 alone, 536 shared; the 410M shape 312, 326 with the line at 65 536, 1207 all alone, 285 all shared), from six bits
+//   on at 131 072 (7 bits: 300 tensors of 600 000 elements 1531 alone, 2498 shared; the 410M shape 1494, 1604 with the line at
+//   196 608, 9501 all alone).
 //   Not in the rule: how the values of a crowded bucket are spread.  A 410M shape of bunched values, all kept, is the one
 //   input met that the former work lists took through these iterations faster (2.0 against 2.7 ms each; the call 116 and 113).
 constexpr u32 LLOYD_THREADS = 512, LLOYD_WAVES = LLOYD_THREADS / 64;
