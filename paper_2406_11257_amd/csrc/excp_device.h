@@ -149,7 +149,7 @@ struct GroupParams {
     u32 together;               // all of the group's tensors go the same way
     u32 slots;                  // tensors with an acc_slot
     u32 unit_shift;             // log2 of the positions of a stream whose bucket counts share a row
-    u32 fine;                   // the first `fine` tensors in order of size have cells inside their buckets (k_km_cells)
+    u32 fine;                   // the first `fine` tensors in order of size may have cells inside their buckets (k_km_cells)
     u32 fine_size;              // ... by the workgroups of size 0, 1 or 2
     u32 samples;                // values of a stream that its value -> bucket map is made from
 };

@@ -704,7 +704,7 @@ __global__ __launch_bounds__(BS_WAVES * 64, BS_WAVES == 16u ? 8 : 5) void k_km_b
 // LDS in the order of their cells.  The cells are equal ranges of the (order-preserving) key between the bucket's extremes,
 // without the gap round zero that a bucket of both signs has.  Sums are in units of the bucket's lowest bit position, so the
 // bucket may span FINE_SPAN binary orders (24 of the mantissa, 16 of the number of values, 23: 63 bits).  A bucket that
-// spans more or is larger than the workgroup's registers gets no cells; it is read as a whole, as before.
+// spans more gets no cells and is read as a whole; with a bucket larger than the workgroup's registers the group has none (k_km_scan).
 constexpr u32 FINE_SPAN = 23, FINE_LEAST = 256;            // smaller buckets are one cell without any table
 // km_fine: cells' log2 | shift << 4 | largest cell << 9 | FINE_NEAR: the values span eight binary orders at most | FINE_VALID
 constexpr u32 FINE_VALID = 1u << 31, FINE_NEAR = 1u << 30, NEAR_SPAN = 8;

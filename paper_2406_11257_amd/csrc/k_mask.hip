@@ -67,7 +67,8 @@ __device__ __forceinline__ void load_quarter(Regs<W16> &R, const TDesc &D, u64 f
     }
 }
 
-// The same for 16-bit weights at any address.
+// The same for 16-bit weights at any address.  (Two-byte loads and no second register set: bf16 tensors of 16.8 M elements at an
+// odd offset take 54 us, 58 at an aligned one; 4e8 elements 1259.)
 template <bool W16>
 __device__ __forceinline__ void load_quarter_halves(Regs<W16> &R, const TDesc &D, u64 first, u32 lane) {
     if constexpr (W16) {

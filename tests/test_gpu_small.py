@@ -92,6 +92,18 @@ def test_storages_and_the_scalar_threshold(ctx, kind, flags):
         check(ctx, [draw(n, n + nbits, kind, flags) for n in SIZES], nbits, 5, 5e-5 if flags != X.EXCP_FLAG_NO_M2W else 0.5, 1.0, flags)
 
 
+@pytest.mark.parametrize("sign", [1, -1])
+def test_zeros_among_the_second_moments(ctx, sign):
+    # (kept where the threshold does not depend on them; nothing but zeros in the last)
+    cases = []
+    for n, zeros in ((100, 1), (4096, 20), (8192, 400), (8192, 8000), (700, 700)):
+        Wp, W, m, v = draw(n, n + zeros, "spread")
+        v[np.random.default_rng(zeros).choice(n, zeros, replace=False)] = 0.0
+        cases.append((Wp, W, m, v if sign > 0 else -v))
+    for nbits in (2, 4, 8):
+        check(ctx, cases, nbits, 4, 0.0, 0.0, X.EXCP_FLAG_NO_M2W)
+
+
 @pytest.mark.parametrize("n", [1, 777, 8192, 8193])
 def test_alone_and_over_the_previous_weights(ctx, n):
     check(ctx, [draw(n, n, "spread")], 4, 10, in_place=True)
