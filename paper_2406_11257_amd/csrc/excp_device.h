@@ -364,7 +364,7 @@ void launch_decode_count(const Workspace &w, u32 ntensors, u32 ntiles, int which
 void launch_decode_scan(const Workspace &w, u32 ntensors, int which, hipStream_t s);
 void launch_decode_main(const Workspace &w, u32 ntensors, u32 ntiles, bool moments, hipStream_t s);
 void launch_decode_finish(const Workspace &w, u32 ntensors, hipStream_t s);
-void launch_export_dense(const Workspace &w, u32 ntensors, u32 ntiles, bool moments, hipStream_t s);
+void launch_export_dense(const Workspace &w, u32 ntensors, u32 ntiles, hipStream_t s);
 void launch_dense_parse(const Workspace &w, u32 ntensors, hipStream_t s);
 void launch_decode_dense(const Workspace &w, u32 ntensors, u32 ntiles, hipStream_t s);
 void launch_decode_chain(const Workspace &w, u32 ntensors, u32 ntiles, bool w16, hipStream_t s);

@@ -227,7 +227,7 @@ int run_dense(excp_ctx *c, int count, bool exporting, Fill fill) {
                 StageTimer t(c, ST_DECODE_PREP);
                 launch_decode_prep(w, g.count, g.ntiles, largest_tiles(descs.h + g.first, g.count), false, moments, true, nullptr, s);
             }
-            { StageTimer t(c, ST_EXPORT_DENSE); launch_export_dense(w, g.count, g.ntiles, moments, s); }
+            { StageTimer t(c, ST_EXPORT_DENSE); launch_export_dense(w, g.count, g.ntiles, s); }
         } else {
             { StageTimer t(c, ST_MISC); launch_dense_parse(w, g.count, s); }
             { StageTimer t(c, ST_DECODE_DENSE); launch_decode_dense(w, g.count, g.ntiles, s); }

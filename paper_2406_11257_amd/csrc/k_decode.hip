@@ -328,32 +328,11 @@ __device__ __forceinline__ u32 window32(const u32 *s, u32 p) {
     return __builtin_amdgcn_alignbit(s[i + 1], s[i], p & 31u);
 }
 
-// The codes of four consecutive elements (the first has index e0, a multiple of 4; `left` of them
-// exist) into a per-element code tensor: half a byte each when nbits <= 4, else a byte each.
-__device__ __forceinline__ void store_codes4(unsigned char *dst, u64 e0, u32 left, u32 nbits, const u32 c[4]) {
-    if (left == 0u) return;
-    if (nbits <= 4u) {
-        const u32 v = c[0] | (c[1] << 4) | (c[2] << 8) | (c[3] << 12);
-        EXCP_GLOBAL unsigned char *p = gptr(dst) + (e0 >> 1);
-        if (left > 2u) *(EXCP_GLOBAL unsigned short *)p = (unsigned short)v;
-        else *p = (unsigned char)v;
-    } else {
-        const u32 v = c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
-        EXCP_GLOBAL unsigned char *p = gptr(dst) + e0;
-        if (left >= 4u) *(EXCP_GLOBAL u32 *)p = v;
-        else for (u32 j = 0; j < left; ++j) p[j] = (unsigned char)(v >> (8u * j));
-    }
-}
-
 // One tile (4096 elements) per workgroup iteration.  Each wave scans the tile's 64 bitmap words,
 // the workgroup stages the tile's contiguous run of packed codes (and, for the moments, the run of
 // bitmap_o bits of its survivors with their prefix counts) in LDS, then every lane reconstructs four
 // consecutive elements: the codes of its survivors are consecutive fields of the staged stream, so
 // one 32-bit window read per lane holds all of them.
-//
-// DENSE: the same walk writes, instead of the reconstructed values, the codes themselves as the
-// per-element code tensors of Sec. 4.2 (0 where pruned; two codes per byte when nbits <= 4, the
-// even element in the low four bits; one code per byte otherwise).
 //
 // RAW: blobs written without quantisation hold fp32 values where the others hold codes; a lane reads
 // its survivors' values straight from the blob (consecutive lanes, consecutive addresses).  Such
@@ -362,9 +341,9 @@ __device__ __forceinline__ void store_codes4(unsigned char *dst, u64 e0, u32 lef
 // WMODE: which weight storage this instantiation takes (blob flags bits 4-5): 0 = fp32 blobs only,
 // 1 = blobs of 16-bit weights only (fp16 / bf16: widened exactly, the sum rounded to nearest even
 // into the format, pruned positions keep their bits), 2 = both, decided per tensor.
-template <bool MOMENTS, bool DENSE, bool RAW, int WMODE>
+template <bool MOMENTS, bool RAW, int WMODE>
 __device__ __forceinline__ void decode_tiles(const Workspace &w, u32 ntensors, u32 ntiles) {
-    __shared__ float s_book[DENSE || RAW ? 1 : 3 * 256];
+    __shared__ float s_book[RAW ? 1 : 3 * 256];
     __shared__ u32 s_tiles[EXCP_MAX_GROUP_TENSORS + 1];
     __shared__ u32 s_cw[RAW ? 2 : DEC_CODE_WORDS];
     __shared__ u32 s_cm[MOMENTS && !RAW ? DEC_CODE_WORDS : 2], s_cv[MOMENTS && !RAW ? DEC_CODE_WORDS : 2];
@@ -388,16 +367,16 @@ __device__ __forceinline__ void decode_tiles(const Workspace &w, u32 ntensors, u
         const u64 base = (u64)ltile * EXCP_TILE;
         const u32 rem = (n - base < (u64)EXCP_TILE) ? (u32)(n - base) : EXCP_TILE;   // elements of this tile
         const unsigned char *blob = D.blob;
-        const bool has_w = DENSE ? D.cw != nullptr : D.W_out != nullptr;
-        const bool has_m = MOMENTS && (DENSE ? D.cm != nullptr : D.m_out != nullptr);
-        const bool has_v = MOMENTS && (DENSE ? D.cv != nullptr : D.v_out != nullptr);
+        const bool has_w = D.W_out != nullptr;
+        const bool has_m = MOMENTS && D.m_out != nullptr;
+        const bool has_v = MOMENTS && D.v_out != nullptr;
         const bool moments = has_m || has_v;
         if (!has_w && !moments) continue;                  // nothing to write for this one
 
         // previous weights of the lane's 4 x 4 elements: issued first, consumed last
         float wp[4][4];
         us4 hp[4];                                         // 16-bit weights stay as they are until the sum
-        if (!DENSE && has_w && WMODE != 0 && wt != 0u) {
+        if (has_w && WMODE != 0 && wt != 0u) {
             const EXCP_GLOBAL unsigned short *Hp = gptr((const unsigned short *)D.Wp) + base;
             const bool vec = ((uintptr_t)D.Wp & 7u) == 0u;
 #pragma unroll
@@ -409,7 +388,7 @@ __device__ __forceinline__ void decode_tiles(const Workspace &w, u32 ntensors, u
                     for (int j = 0; j < 4; ++j) hp[k][j] = (off + (u32)j < rem) ? Hp[off + (u32)j] : (unsigned short)0;
                 }
             }
-        } else if (!DENSE && has_w) {
+        } else if (has_w) {
             const EXCP_GLOBAL float *Wp = gptr(D.Wp) + base;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -450,7 +429,7 @@ __device__ __forceinline__ void decode_tiles(const Workspace &w, u32 ntensors, u
         }
 
         __syncthreads();                                   // the previous tile's LDS readers are done
-        if (!DENSE && !RAW && t != cur_t) {
+        if (!RAW && t != cur_t) {
             const EXCP_GLOBAL float *books = gptr((const float *)(blob + EXCP_HEADER));
             for (u32 i = tid; i < 3u * E; i += EXCP_THREADS) s_book[(i / E) * 256u + (i % E)] = books[i];
             cur_t = t;
@@ -496,18 +475,7 @@ __device__ __forceinline__ void decode_tiles(const Workspace &w, u32 ntensors, u
             const u32 r = wex + __popcll(word & ((1ull << sub) - 1ull));   // tile rank of the lane's first survivor
             u32 f = RAW ? 0u : window32(s_cw, woff + r * nbits);
             const EXCP_GLOBAL float *xw = gptr((const float *)(blob + S.off_cw)) + q_tile + r;   // RAW: the lane's first survivor
-            if (DENSE) {
-                if (has_w) {
-                    u32 c[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const bool kept = (nib >> j) & 1u;
-                        c[j] = kept ? (f & cmask) : 0u;
-                        f = kept ? (f >> nbits) : f;
-                    }
-                    store_codes4(D.cw, base + off, rem - min(rem, off), nbits, c);
-                }
-            } else if (has_w && WMODE != 0 && wt != 0u) {
+            if (has_w && WMODE != 0 && wt != 0u) {
                 us4 o16;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -554,22 +522,6 @@ __device__ __forceinline__ void decode_tiles(const Workspace &w, u32 ntensors, u
                 u32 fv = RAW ? 0u : window32(s_cv, moff + orank * nbits);
                 const EXCP_GLOBAL float *xm = gptr((const float *)(blob + S.off_cm)) + o_tile + orank;   // RAW
                 const EXCP_GLOBAL float *xv = gptr((const float *)(blob + S.off_cv)) + o_tile + orank;
-                if (DENSE) {
-                    u32 cm4[4], cv4[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const bool kept = (nib >> j) & 1u;
-                        const bool ko = (kept || nw2m) && (obits & 1u);
-                        cm4[j] = ko ? (fm & cmask) : 0u;
-                        cv4[j] = ko ? (fv & cmask) : 0u;
-                        obits = (kept || nw2m) ? (obits >> 1) : obits;
-                        fm = ko ? (fm >> nbits) : fm;
-                        fv = ko ? (fv >> nbits) : fv;
-                    }
-                    if (has_m) store_codes4(D.cm, base + off, rem - min(rem, off), nbits, cm4);
-                    if (has_v) store_codes4(D.cv, base + off, rem - min(rem, off), nbits, cv4);
-                    continue;
-                }
                 float om[4], ov[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -607,23 +559,219 @@ __device__ __forceinline__ void decode_tiles(const Workspace &w, u32 ntensors, u
 template <bool MOMENTS>
 __global__ __launch_bounds__(EXCP_THREADS, MOMENTS ? 6 : 8) void k_decode_main(Workspace w, u32 ntensors, u32 ntiles) {
     if ((*w.dec_kinds & 1u) == 0u) return;                 // no blob of fp32 weights in this group
-    decode_tiles<MOMENTS, false, false, 0>(w, ntensors, ntiles);
+    decode_tiles<MOMENTS, false, 0>(w, ntensors, ntiles);
 }
 // The same for blobs of 16-bit weights (most batches hold none).
 template <bool MOMENTS>
 __global__ __launch_bounds__(EXCP_THREADS, MOMENTS ? 6 : 8) void k_decode_main16(Workspace w, u32 ntensors, u32 ntiles) {
     if ((*w.dec_kinds & 2u) == 0u) return;
-    decode_tiles<MOMENTS, false, false, 1>(w, ntensors, ntiles);
+    decode_tiles<MOMENTS, false, 1>(w, ntensors, ntiles);
 }
 // Blobs written without quantisation (most batches hold none).
 template <bool MOMENTS>
 __global__ __launch_bounds__(EXCP_THREADS) void k_decode_raw(Workspace w, u32 ntensors, u32 ntiles) {
     if ((*w.dec_kinds & 4u) == 0u) return;
-    decode_tiles<MOMENTS, false, true, 2>(w, ntensors, ntiles);
+    decode_tiles<MOMENTS, true, 2>(w, ntensors, ntiles);
 }
-template <bool MOMENTS>
-__global__ __launch_bounds__(EXCP_THREADS, 8) void k_export_dense(Workspace w, u32 ntensors, u32 ntiles) {
-    decode_tiles<MOMENTS, true, false, 2>(w, ntensors, ntiles);
+// The codes themselves, as the per-element code tensors of Sec. 4.2: 0 where pruned; two codes per byte when nbits <= 4, the even
+// element in the low four bits; one code per byte otherwise.
+//
+// It reads and writes 2 bytes an element, so what bounds it is the instructions between.  A wave has a tile to itself and takes it
+// in four quarters, sixteen consecutive elements to a lane, without barriers.  Eight elements are a byte of the bitmap: their codes,
+// at most eight consecutive fields of the stream, are spread over the bytes of two registers, and the bitmap byte looks up
+// the byte selectors that put them in their elements' places (0 where pruned) -- twelve instructions for eight elements, where
+// taking one code after the other from a window is five for each.  The M_o bits go from survivors to elements four at a time by
+// a table too; their running count is then the moments' rank.  Everything of a tile that comes from memory is asked for as soon as
+// its place is known: bitmap; codes of the weights and bitmap_o; codes of the moments.  (333 M elements of 4 bits, all three: a tile to
+// a workgroup, four elements to a lane, one code after the other 545 us; now 188, 3.5 TB/s.  Stores past the caches 191, five or
+// seven workgroups to a compute unit 187 and 183.)
+constexpr u32 EXPORT_WAVES = EXCP_THREADS / 64, EXPORT_PER_CU = 12;
+constexpr u32 EXPORT_CODE_WORDS = 260;       // of 1024 codes of 8 bits, one for the first bit's place, two for what a window reads beyond
+
+__global__ __launch_bounds__(EXCP_THREADS, 6) void k_export_dense(Workspace w, u32 ntensors, u32 ntiles) {
+    __shared__ u64 s_pick[256];                            // per bitmap byte: selectors of the even elements, of the odd ones
+    __shared__ unsigned char s_deposit[256];               // (four bits to place << 4 | four bits of bitmap): the bits in their places
+    __shared__ u32 s_tiles[EXCP_MAX_GROUP_TENSORS + 1];
+    __shared__ u32 s_code[EXPORT_WAVES][3][EXPORT_CODE_WORDS], s_bo[EXPORT_WAVES][DEC_OBIT_WORDS];
+    const u32 tid = threadIdx.x, lane = tid & 63u;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    {
+        static_assert(EXCP_THREADS == 256, "a thread makes an entry of either table");
+        u32 pick[2] = {0u, 0u}, r = 0, place = 0, bits = tid >> 4;
+#pragma unroll
+        for (u32 j = 0; j < 8; ++j) {
+            const bool kept = tid >> j & 1u;
+            // code r of the eight is byte r / 2 of the register of the even ones (bytes 0 to 3) or odd ones (4 to 7); 12 gives zeros
+            pick[j & 1u] |= (kept ? (r & 1u) * 4u + (r >> 1) : 12u) << (8u * (j >> 1));
+            r += kept;
+        }
+#pragma unroll
+        for (u32 j = 0; j < 4; ++j) if (tid >> j & 1u) { place |= (bits & 1u) << j; bits >>= 1; }
+        s_pick[tid] = (u64)pick[1] << 32 | pick[0];
+        s_deposit[tid] = (unsigned char)place;
+    }
+    load_tile_table(s_tiles, w.tile_begin, ntensors);
+    u32 t = 0, first = 0, end = 0;                         // the tensor in hand, its first tile, one past its last
+    for (u32 tile = blockIdx.x * EXPORT_WAVES + wave; tile < ntiles; tile += gridDim.x * EXPORT_WAVES) {
+        if (tile >= end) {                                 // (a wave's tiles only go up)
+            t = (u32)__builtin_amdgcn_readfirstlane((int)find_owner(s_tiles, ntensors, tile));
+            first = (u32)__builtin_amdgcn_readfirstlane((int)s_tiles[t]);
+            end = (u32)__builtin_amdgcn_readfirstlane((int)s_tiles[t + 1u]);
+        }
+        const EXCP_CONSTANT DDesc *D = (const EXCP_CONSTANT DDesc *)(uintptr_t)(w.ddesc + t);
+        const EXCP_CONSTANT DState *S = (const EXCP_CONSTANT DState *)(uintptr_t)(w.dst + t);
+        if (S->status != 0 || S->nbits > 8u) continue;
+        unsigned char *const dst[3] = {D->cw, D->cm, D->cv};
+        const bool moments = dst[1] != nullptr || dst[2] != nullptr;
+        if (dst[0] == nullptr && !moments) continue;
+        const u32 nbits = S->nbits, ltile = tile - first;
+        const bool per_element = (S->flags & 8u) != 0u;    // M_o bits per element instead of per kept residual
+        const u64 n = D->n, base = (u64)ltile * EXCP_TILE;
+        const u32 rem = n - base < (u64)EXCP_TILE ? (u32)(n - base) : EXCP_TILE;
+        const unsigned char *blob = D->blob;
+        u32 *bo = s_bo[wave];
+        const EXCP_CONSTANT u32 *count_w = (const EXCP_CONSTANT u32 *)(uintptr_t)w.dec_cnt_w, *count_o = (const EXCP_CONSTANT u32 *)(uintptr_t)w.dec_cnt_o;
+        const u32 q_tile = count_w[tile];                  // survivors before the tile
+        // sixteen bits of a bitmap with a bit per element: those of the lane's elements in quarter q
+        auto bits_at = [&](u64 section, u32 q) {
+            const u32 off = q * 1024u + lane * 16u, left = rem > off ? min(rem - off, 16u) : 0u;
+            const u32 x = left ? (u32)gptr((const unsigned short *)(blob + section))[(u64)ltile * 256u + q * 64u + lane] : 0u;
+            return x & ((1u << left) - 1u);
+        };
+        u32 keep[4], rank[4], at[5];                       // the lane's bitmap bits, survivors in front of them in the tile; those before every quarter
+        u32 keep_o[4], rank_o[4], at_o[5];                 // the same of the moments
+#pragma unroll
+        for (u32 q = 0; q < 4; ++q) keep[q] = bits_at(S->off_bw, q);
+        if (moments && per_element) {
+#pragma unroll
+            for (u32 q = 0; q < 4; ++q) keep_o[q] = bits_at(S->off_bo, q);
+        }
+        auto ranks = [&](const u32 (&bits)[4], u32 (&r)[4], u32 (&begin)[5]) {
+            begin[0] = 0u;
+#pragma unroll
+            for (u32 q = 0; q < 4; ++q) {
+                const u32 pc = (u32)__popc(bits[q]), incl = wave_incl_scan_u32(pc);
+                r[q] = incl - pc + begin[q];
+                begin[q + 1u] = begin[q] + last_lane_u32(incl);
+            }
+        };
+        // a quarter's codes of one stream: where they begin, words, and the first 64 words, one to a lane (without any: any word of the blob)
+        struct Codes { u32 off, words, word; const EXCP_GLOBAL u32 *from; };
+        auto open = [&](u64 section, u64 before, u32 count) {
+            Codes c;
+            const u64 bit0 = before * nbits;
+            c.off = (u32)(bit0 & 31ull);
+            c.words = count ? (c.off + count * nbits + 31u) >> 5 : 0u;
+            c.from = gptr((const u32 *)(c.words ? blob + section + (bit0 >> 5) * 4u : blob));
+            c.word = c.from[lane < c.words ? lane : 0u];
+            return c;
+        };
+        Codes cw[4], cm[4], cv[4];
+        ranks(keep, rank, at);
+        if (dst[0] != nullptr) {
+#pragma unroll
+            for (u32 q = 0; q < 4; ++q) cw[q] = open(S->off_cw, (u64)q_tile + at[q], at[q + 1u] - at[q]);
+        }
+        if (moments) {
+            if (!per_element) {
+                // the survivors' M_o bits, then placed at their elements
+                const u32 ooff = q_tile & 31u, words = at[4] ? (ooff + at[4] + 31u) >> 5 : 0u;      // <= 129
+                const EXCP_GLOBAL u32 *from = gptr((const u32 *)(blob + S->off_bo)) + (q_tile >> 5);
+                u32 x[3];
+#pragma unroll
+                for (u32 k = 0; k < 3; ++k) x[k] = lane + 64u * k < words ? from[lane + 64u * k] : 0u;
+                wave_lds_fence();                          // (the tile before is done with them)
+#pragma unroll
+                for (u32 k = 0; k < 3; ++k) if (lane + 64u * k < DEC_OBIT_WORDS) bo[lane + 64u * k] = x[k];
+                wave_lds_fence();
+#pragma unroll
+                for (u32 q = 0; q < 4; ++q) {
+                    u32 bits = window32(bo, ooff + rank[q]), placed = 0;
+#pragma unroll
+                    for (u32 j = 0; j < 4; ++j) {
+                        const u32 four = keep[q] >> (4u * j) & 15u;
+                        placed |= (u32)s_deposit[(bits & 15u) << 4 | four] << (4u * j);
+                        bits >>= __popc(four);
+                    }
+                    keep_o[q] = placed;
+                }
+            }
+            ranks(keep_o, rank_o, at_o);
+            const u64 o_tile = count_o[tile];
+#pragma unroll
+            for (u32 q = 0; q < 4; ++q) {
+                const u32 count = at_o[q + 1u] - at_o[q];
+                if (dst[1] != nullptr) cm[q] = open(S->off_cm, o_tile + at_o[q], count);
+                if (dst[2] != nullptr) cv[q] = open(S->off_cv, o_tile + at_o[q], count);
+            }
+        }
+        const u32 one = (1u << nbits) - 1u, two = (1u << 2u * nbits) - 1u;
+#pragma unroll
+        for (u32 q = 0; q < 4; ++q) {
+            const u32 off = q * 1024u + lane * 16u;
+            if (q * 1024u >= rem) break;
+            const u32 left = rem > off ? min(rem - off, 16u) : 0u;
+            wave_lds_fence();                              // (the quarter before is done with its codes)
+#pragma unroll
+            for (u32 k = 0; k < 3; ++k) {
+                if (dst[k] == nullptr) continue;
+                const Codes &c = k == 0u ? cw[q] : (k == 1u ? cm[q] : cv[q]);
+                u32 *code = s_code[wave][k];
+                code[lane] = c.word;
+#pragma unroll 1
+                for (u32 i = 64u + lane; i < c.words; i += 64u) code[i] = c.from[i];
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (u32 k = 0; k < 3; ++k) {
+                if (dst[k] == nullptr) continue;
+                const Codes &c = k == 0u ? cw[q] : (k == 1u ? cm[q] : cv[q]);
+                const u32 *code = s_code[wave][k];
+                const u32 bits = k == 0u ? keep[q] : keep_o[q];
+                const u32 r = k == 0u ? rank[q] - at[q] : rank_o[q] - at_o[q];
+                u32 out[4];                                // the sixteen codes, two or one to a byte
+#pragma unroll
+                for (u32 h = 0; h < 2; ++h) {
+                    const u32 eight = bits >> (8u * h) & 255u;
+                    const u32 p = c.off + (r + (h ? (u32)__popc(bits & 255u) : 0u)) * nbits;
+                    const u64 pick = s_pick[eight];
+                    if (nbits <= 4u) {
+                        u32 x = window32(code, p);
+                        if (nbits < 4u) {                  // fields of two or three bits: half a byte apart
+                            const u32 four = (1u << 4u * nbits) - 1u, pair = two * 0x00010001u;
+                            x = (x & four) | (x << (16u - 4u * nbits) & four << 16);
+                            x = (x & pair) | (x << (8u - 2u * nbits) & pair << 8);
+                        }
+                        const u32 low = one * 0x01010101u, even = x & low, odd = x >> nbits & low;
+                        out[h] = __builtin_amdgcn_perm(odd, even, (u32)pick) | __builtin_amdgcn_perm(odd, even, (u32)(pick >> 32)) << 4;
+                    } else {
+                        u32 x[2];
+#pragma unroll
+                        for (u32 y = 0; y < 2; ++y) {      // four fields of five to eight bits, a byte apart
+                            x[y] = window32(code, p + 4u * nbits * y);
+                            x[y] = (x[y] & two) | (x[y] << (16u - 2u * nbits) & two << 16);
+                            x[y] = (x[y] & one * 0x00010001u) | (x[y] << (8u - nbits) & (one * 0x00010001u) << 8);
+                        }
+                        const u32 even = __builtin_amdgcn_perm(x[1], x[0], 0x06040200u), odd = __builtin_amdgcn_perm(x[1], x[0], 0x07050301u);
+                        const u32 e = __builtin_amdgcn_perm(odd, even, (u32)pick), o = __builtin_amdgcn_perm(odd, even, (u32)(pick >> 32));
+                        out[2u * h] = __builtin_amdgcn_perm(o, e, 0x05010400u);
+                        out[2u * h + 1u] = __builtin_amdgcn_perm(o, e, 0x07030602u);
+                    }
+                }
+                typedef u32 u2 __attribute__((ext_vector_type(2)));
+                typedef u32 u4 __attribute__((ext_vector_type(4)));
+                if (nbits <= 4u) {
+                    EXCP_GLOBAL unsigned char *to = gptr(dst[k]) + ((base + off) >> 1);
+                    if (left == 16u) { u2 x; x.x = out[0]; x.y = out[1]; *(EXCP_GLOBAL u2 *)to = x; }
+                    else for (u32 j = 0; j < (left + 1u) / 2u; ++j) to[j] = (unsigned char)(out[j >> 2 & 1u] >> (8u * (j & 3u)));
+                } else {
+                    EXCP_GLOBAL unsigned char *to = gptr(dst[k]) + base + off;
+                    if (left == 16u) { u4 x; x.x = out[0]; x.y = out[1]; x.z = out[2]; x.w = out[3]; *(EXCP_GLOBAL u4 *)to = x; }
+                    else for (u32 j = 0; j < left; ++j) to[j] = (unsigned char)(out[j >> 2 & 3u] >> (8u * (j & 3u)));
+                }
+            }
+        }
+    }
 }
 
 // Alg. 3: W_0 plus a chain of compressed checkpoints, oldest first, in ONE pass over the weights.
@@ -1002,8 +1150,8 @@ __global__ void k_decode_setup(Workspace w, DDesc d, u32 single) {
 
 template <bool MOMENTS, bool W16>
 __global__ __launch_bounds__(EXCP_THREADS) void k_decode_small(Workspace w, u32 ntensors, u32 ntiles) {
-    decode_tiles<MOMENTS, false, false, W16 ? 1 : 0>(w, ntensors, ntiles);
-    decode_tiles<MOMENTS, false, true, 2>(w, ntensors, ntiles);
+    decode_tiles<MOMENTS, false, W16 ? 1 : 0>(w, ntensors, ntiles);
+    decode_tiles<MOMENTS, true, 2>(w, ntensors, ntiles);
 }
 
 }  // namespace
@@ -1074,14 +1222,12 @@ void launch_decode_raw(const Workspace &w, u32 ntensors, u32 ntiles, bool moment
     if (moments) hipLaunchKernelGGL(k_decode_raw<true>, dim3(blocks), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);
     else hipLaunchKernelGGL(k_decode_raw<false>, dim3(blocks), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);
 }
-void launch_export_dense(const Workspace &w, u32 ntensors, u32 ntiles, bool moments, hipStream_t s) {
+void launch_export_dense(const Workspace &w, u32 ntensors, u32 ntiles, hipStream_t s) {
     if (!ntensors) return;
     hipLaunchKernelGGL(k_export_head, dim3(ntensors), dim3(EXCP_THREADS), 0, s, w, ntensors);
     if (!ntiles) return;
-    u32 blocks = excp_grid(w, 64);
-    if (blocks > ntiles) blocks = ntiles;
-    if (moments) hipLaunchKernelGGL(k_export_dense<true>, dim3(blocks), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);
-    else hipLaunchKernelGGL(k_export_dense<false>, dim3(blocks), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);
+    const u32 blocks = std::min((ntiles + EXPORT_WAVES - 1u) / EXPORT_WAVES, excp_grid(w, EXPORT_PER_CU));
+    hipLaunchKernelGGL(k_export_dense, dim3(blocks), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);
 }
 void launch_dense_parse(const Workspace &w, u32 ntensors, hipStream_t s) {
     if (!ntensors) return;
