@@ -204,8 +204,9 @@ struct Workspace {
     DDesc *ddesc; DState *dst;
     CDesc *cdesc; u32 *chain_tile_begin;   // chain reconstruction: tensors and their tile table
     u32 *dec_cnt_w, *dec_cnt_o;   // per tile counts -> exclusive bases
-    u64 *dec_part;                // [descriptor][16] tile-count totals of each sixteenth of a tensor's tiles
-    u32 *dec_kinds;               // [1] kinds of blob in the group being decoded: 1 fp32 weights, 2 16-bit weights, 4 unquantised
+    u32 *dec_part;                // [which][dec_part_stride] sums of the counts by runs of tiles (see k_decode_count)
+    u32 dec_part_stride;
+    u32 *dec_kinds;               // [0] kinds of blob in the group being decoded: 1 fp32 weights, 2 16-bit weights, 4 unquantised; [1], [2] of its making (0 between launches)
     // results
     HostRec *rec_dev;         // (host memory, except in the static call)
     u32 rec_base;             // index of this group's first tensor in rec_dev
@@ -246,6 +247,11 @@ static inline u32 excp_unit_shift(u64 elems, u32 tensors, u32 subs, u32 cus, u64
     while (s < EXCP_UNIT_SHIFT && ((elems >> s) > 4ull * cus || (u64)subs * 2048u > (1ull << s) || 3 * (elems >> s) + 3ull * tensors > rows)) ++s;
     return s;
 }
+
+// Tiles whose counts a workgroup of the restores' scan takes, and the runs that the tiles of a group are cut into: the first of every
+// tensor, and one for every multiple of that number.
+#define EXCP_SCAN_TILES 1024u
+static __host__ __device__ inline u32 excp_scan_runs(u32 tensors, u32 tiles) { return tensors + (tiles + EXCP_SCAN_TILES - 1u) / EXCP_SCAN_TILES; }
 
 // A tensor's area in the arrays of survivors (whole lines: it begins on a multiple of 64 elements), and what a group's take.
 static inline u64 excp_area_elems(u64 n) { return (n + 63) & ~63ull; }
@@ -360,8 +366,6 @@ void launch_decode_small(const Workspace &w, u32 ntensors, u32 ntiles, bool mome
 void launch_decode_main16(const Workspace &w, u32 ntensors, u32 ntiles, bool moments, hipStream_t s);
 void launch_decode_raw(const Workspace &w, u32 ntensors, u32 ntiles, bool moments, hipStream_t s);
 void launch_store_raw(const Workspace &w, const GroupParams &g, hipStream_t s);
-void launch_decode_count(const Workspace &w, u32 ntensors, u32 ntiles, int which, hipStream_t s);
-void launch_decode_scan(const Workspace &w, u32 ntensors, int which, hipStream_t s);
 void launch_decode_main(const Workspace &w, u32 ntensors, u32 ntiles, bool moments, hipStream_t s);
 void launch_decode_finish(const Workspace &w, u32 ntensors, hipStream_t s);
 void launch_export_dense(const Workspace &w, u32 ntensors, u32 ntiles, hipStream_t s);

@@ -248,9 +248,11 @@ int run_dense(excp_ctx *c, int count, bool exporting, Fill fill) {
 constexpr u64 kStaticMaxTiles = EXCP_STATIC_MAX_ELEMS / EXCP_TILE;
 struct StaticOffsets {
     static constexpr u64 ddesc = 0, dst = 256, tile_begin = 512, dec_kinds = 768, rec = 1024, dec_part = 1280,
-                         cnt_w = 1536, cnt_o = cnt_w + 4 * (kStaticMaxTiles + 64), end = cnt_o + 4 * (kStaticMaxTiles + 64);
+                         cnt_w = 2048, cnt_o = cnt_w + 4 * (kStaticMaxTiles + 64), end = cnt_o + 4 * (kStaticMaxTiles + 64);
 };
 static_assert(sizeof(DDesc) <= 256 && sizeof(DState) <= 256 && sizeof(HostRec) <= 256, "scratch slots are 256 bytes");
+constexpr u32 kStaticRuns = (StaticOffsets::cnt_w - StaticOffsets::dec_part) / (2 * sizeof(u32));
+static_assert(1 + kStaticMaxTiles / EXCP_SCAN_TILES <= kStaticRuns, "the runs of the largest tensor have their sums");
 static_assert(StaticOffsets::cnt_w % 256 == 0 && StaticOffsets::cnt_o % 256 == 0, "tables start on 256-byte boundaries");
 constexpr u64 kScratchBytes = StaticOffsets::end;
 
@@ -398,7 +400,8 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
     ok = ok && dev_alloc(c, &w.dec_cnt_w, max_tiles * EXCP_MAX_CHAIN);
     ok = ok && dev_alloc(c, &w.dec_cnt_o, max_tiles * EXCP_MAX_CHAIN);
     ok = ok && dev_alloc(c, &w.dec_kinds, 4);
-    ok = ok && dev_alloc(c, &w.dec_part, (u64)kMaxGroupTensors * 16);
+    w.dec_part_stride = excp_scan_runs(kMaxBatchTensors, (u32)std::min<u64>(max_tiles * EXCP_MAX_CHAIN, 0xffffffffull - EXCP_SCAN_TILES));
+    ok = ok && dev_alloc(c, &w.dec_part, 2ull * w.dec_part_stride);
     if (ok) {
         // (the kernels write the results where the host reads them: no copy back)
         ok = hipHostMalloc((void **)&c->h_stage, kStageBytes) == hipSuccess &&
@@ -418,6 +421,7 @@ int excp_create(excp_ctx **out, int hip_device, void *hip_stream, uint64_t max_t
         launch_zero_u32(w.med_hist, (u64)kMaxGroupTensors * 2048, c->stream);
         launch_zero_u32(w.sel_ticket, kMaxGroupTensors, c->stream);
         launch_zero_u32(w.scan_ticket, 1, c->stream);
+        launch_zero_u32(w.dec_kinds, 4, c->stream);
         ok = hipStreamSynchronize(c->stream) == hipSuccess;
     }
     if (!ok) { excp_destroy(c); return EXCP_E_HIP; }
@@ -789,8 +793,8 @@ int excp_reconstruct_chain(excp_ctx *c, int count, const excp_chain *chains) {
     if (total_descs > kMaxBatchTensors) return EXCP_E_ARG;
     if (hipSetDevice(c->device) != hipSuccess) return EXCP_E_HIP;
 
-    // Groups: at most kMaxGroupTensors descriptors (one per tensor and checkpoint) and as many
-    // descriptor tiles as the per-tile count tables hold (EXCP_MAX_CHAIN times a group's tiles, so
+    // Groups: at most kMaxGroupTensors tensors and as many
+    // descriptor tiles (a descriptor per tensor and checkpoint) as the per-tile count tables hold (EXCP_MAX_CHAIN times a group's tiles, so
     // any tensor the context accepts fits with its whole chain).
     std::vector<CGroup> &groups = c->cgroups;
     groups.clear();
@@ -805,7 +809,7 @@ int excp_reconstruct_chain(excp_ctx *c, int count, const excp_chain *chains) {
         while (i < (u32)count) {
             const excp_chain &ch = chains[i];
             const u64 tiles = (ch.n + EXCP_TILE - 1) / EXCP_TILE;
-            if (g.count && (g.ndescs + (u32)ch.steps > kMaxGroupTensors || dtiles + tiles * ch.steps > c->max_tiles * EXCP_MAX_CHAIN)) break;
+            if (g.count && (g.count == kMaxGroupTensors || dtiles + tiles * ch.steps > c->max_tiles * EXCP_MAX_CHAIN)) break;
             dtiles += tiles * ch.steps; g.ndescs += (u32)ch.steps; g.ntiles += (u32)tiles; ++g.count; ++i;
         }
         if (tb_off + g.ndescs + g.count + 2 > kMaxBatchTensors * 2 + 16) return EXCP_E_ARG;
@@ -862,8 +866,10 @@ int excp_reconstruct_chain(excp_ctx *c, int count, const excp_chain *chains) {
             if (w16[k]) { StageTimer t(c, ST_DECODE_MAIN); launch_decode_chain(w, g.count, g.ntiles, k == 1, s); }
         if (moments) {      // the last checkpoints' moments
             StageTimer t(c, ST_DECODE_MAIN);
-            if (w16[0]) launch_decode_main(w, g.ndescs, dtiles, true, s);
-            if (w16[1]) launch_decode_main16(w, g.ndescs, dtiles, true, s);
+            Workspace wl = w;
+            wl.tile_begin = w.chain_tile_begin;
+            if (w16[0]) launch_decode_main(wl, g.count, g.ntiles, true, s);
+            if (w16[1]) launch_decode_main16(wl, g.count, g.ntiles, true, s);
         }
         { StageTimer t(c, ST_MISC); launch_chain_finish(w, g.count, s); }
     }
@@ -952,7 +958,8 @@ int excp_decompress_step_static(int hip_device, void *hip_stream, const void *W_
     w.tile_begin = (u32 *)(sd.ptr + StaticOffsets::tile_begin);
     w.dec_kinds = (u32 *)(sd.ptr + StaticOffsets::dec_kinds);
     w.rec_dev = (HostRec *)(sd.ptr + StaticOffsets::rec);
-    w.dec_part = (u64 *)(sd.ptr + StaticOffsets::dec_part);
+    w.dec_part = (u32 *)(sd.ptr + StaticOffsets::dec_part);
+    w.dec_part_stride = kStaticRuns;
     w.dec_cnt_w = (u32 *)(sd.ptr + StaticOffsets::cnt_w);
     w.dec_cnt_o = (u32 *)(sd.ptr + StaticOffsets::cnt_o);
     w.rec_base = 0;

@@ -71,11 +71,26 @@ __device__ __forceinline__ u32 parse_header(const DDesc &D, DState &S, bool allo
     S.n_w = nw; S.n_o = no; S.nbits = nbits; S.blob_bytes = total; S.flags = h[3];
     return blob_kind(nbits, h[3]);
 }
-__global__ void k_decode_parse(Workspace w, u32 ntensors, u32 allow_raw) {
-    const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= ntensors) return;
-    const u32 kind = parse_header(w.ddesc[t], w.dst[t], allow_raw != 0u);
-    if (kind) atomicOr(w.dec_kinds, kind);
+// The first launch of a larger group: headers, kinds of blob, sums of counts at zero.  `single`: the only tensor's
+// description comes as an argument and is left where the others look for it.  (Blobs lie in as many pages, so many compute units
+// take a share: 2336 of them 49 us in one workgroup.  Its last workgroup, by ticket, hands the kinds over.)
+constexpr u32 PARSE_THREADS = 64;
+__global__ __launch_bounds__(PARSE_THREADS) void k_decode_parse(Workspace w, u32 ntensors, u32 parts, u32 allow_raw, DDesc one, u32 single) {
+    const u32 tid = threadIdx.x, i = blockIdx.x * PARSE_THREADS + tid;
+    if (single && i == 0u) { w.ddesc[0] = one; w.tile_begin[0] = 0u; w.tile_begin[1] = one.tile_count; }
+    for (u32 k = i; k < parts; k += gridDim.x * PARSE_THREADS) { w.dec_part[k] = 0u; w.dec_part[w.dec_part_stride + k] = 0u; }
+    u32 kind = 0;
+    if (i < ntensors) kind = single ? parse_header(one, w.dst[i], allow_raw != 0u) : parse_header(w.ddesc[i], w.dst[i], allow_raw != 0u);
+    u32 kinds = 0;
+#pragma unroll
+    for (u32 k = 1u; k <= 4u; k <<= 1) kinds |= ballot64(kind == k) ? k : 0u;
+    if (tid != 0) return;
+    if (kinds) atomicOr(&w.dec_kinds[1], kinds);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // (it has arrived before the ticket is drawn)
+    if (atomicAdd(&w.dec_kinds[2], 1u) == gridDim.x - 1u) {
+        w.dec_kinds[0] = atomicExch(&w.dec_kinds[1], 0u);
+        w.dec_kinds[2] = 0u;
+    }
 }
 
 __device__ __forceinline__ void decode_record(const Workspace &w, u32 t, u64 n, const DState &S) {
@@ -169,146 +184,184 @@ __global__ __launch_bounds__(PREP_WAVES * 64) void k_decode_prep(Workspace w, u3
 }
 
 // which == 0: per-tile popcount of bitmap_w.  which == 1: per-tile popcount of the bitmap_o bits
-// that belong to the tile's survivors (needs the scanned bitmap_w counts).  A wave takes a contiguous
-// range of tiles.  The bitmap is 1/128 of what the main pass moves, so what bounds this one is latency:
-// the tensor is looked up when it changes, its description comes through the scalar unit, and eight tiles
-// of bitmap_w (eight loads in flight, two counts to a word in the wave's sum) go together.  (Eight checkpoints of
-// the 410M shape, 405 MB of bitmaps: 296 -> 240 us in three launches; one checkpoint 41 -> 23 us.)  A wave that has fewer
-// (one, up to 8192 tiles in all) loads and adds up only those: 30 M elements 6.6 -> 5.0 us, 20 to 100 ragged tensors
-// 6.8 -> 5.8.
+// that belong to the tile's survivors (needs the scanned bitmap_w counts).  A wave takes a contiguous range of tiles, eight at a
+// time, each with eight lanes of its own that look their tensor up when it changes.  The bitmap is 1/128 of what the main pass moves, so what
+// bounds this one is latency, and what matters is that neighbouring tiles of different tensors do not wait for each other.  (Eight
+// checkpoints of the 410M shape, 405 MB of bitmaps, two thirds of the tensors one tile: with a wave for eight tiles of one tensor 234 us in
+// three launches, some of the waves with thirty-two tensors to look up one after the other; now 87 in one.)
+// The counts of a run of tiles, the first of a tensor up to a multiple of SCAN_BLOCK or SCAN_BLOCK more, are also added up in
+// dec_part, where the scan finds what lies before its run.
+constexpr u32 SCAN_BLOCK = EXCP_SCAN_TILES;
+// The run that a tile of a tensor beginning at `first` belongs to: the tensor's number, or that of the block behind all tensors.
+__device__ __forceinline__ u32 run_of(u32 tile, u32 t, u32 first, u32 ntensors) {
+    return tile / SCAN_BLOCK == first / SCAN_BLOCK ? t : ntensors + tile / SCAN_BLOCK;
+}
+__device__ __forceinline__ u32 sum_of_eight(u32 x) {       // in all of them: neighbours, pairs, then the two quads
+    x += dpp_u32<0xb1, 0xf>(0u, x);           // quad_perm 1 0 3 2
+    x += dpp_u32<0x4e, 0xf>(0u, x);           // quad_perm 2 3 0 1
+    x += dpp_u32<0x141, 0xf>(0u, x);          // row_half_mirror
+    return x;
+}
 template <int WHICH>
 __global__ __launch_bounds__(EXCP_THREADS) void k_decode_count(Workspace w, u32 ntensors, u32 ntiles) {
-    __shared__ u32 s_tiles[EXCP_MAX_GROUP_TENSORS + 1];
-    const u32 lane = threadIdx.x & 63u;
+    extern __shared__ u32 s_begin[];                       // [ntensors + 1]
+    __shared__ u32 s_run[EXCP_THREADS / 64], s_sum[EXCP_THREADS / 64];
+    const u32 lane = threadIdx.x & 63u, group = lane >> 3, l = lane & 7u;
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    load_tile_table(s_tiles, w.tile_begin, ntensors);
+    load_tile_table(s_begin, w.tile_begin, ntensors);
     const u32 nwaves = gridDim.x * (EXCP_THREADS / 64), wid = blockIdx.x * (EXCP_THREADS / 64) + wave;
     const u32 t_lo = (u32)(((u64)wid * ntiles) / nwaves), t_hi = (u32)(((u64)(wid + 1u) * ntiles) / nwaves);
-    u32 t = 0, first = 0, end = 0;                         // the tensor in hand, its first tile, one past its last
-    for (u32 tile = t_lo; tile < t_hi;) {
-        if (tile >= end) {
-            t = (u32)__builtin_amdgcn_readfirstlane((int)find_owner(s_tiles, ntensors, tile));
-            first = (u32)__builtin_amdgcn_readfirstlane((int)s_tiles[t]);
-            end = (u32)__builtin_amdgcn_readfirstlane((int)s_tiles[t + 1u]);
+    u32 *part = w.dec_part + (WHICH == 0 ? 0u : w.dec_part_stride), *table = WHICH == 0 ? w.dec_cnt_w : w.dec_cnt_o;
+    u32 t = 0, first = 0, end = 0;                         // the group's tensor, its first tile, one past its last
+    u64 n = 0, most = 0, pop = 0;                          // its elements; of its survivors: bits in bitmap_o, counted
+    bool good = false, per_element = false;
+    const EXCP_GLOBAL u64 *bm = nullptr;
+    u32 run = 0xffffffffu, sum = 0;                        // counts not yet handed over, and the run they belong to
+    for (u32 tile0 = t_lo; tile0 < t_hi; tile0 += 8u) {
+        const u32 tile = tile0 + group;
+        const bool have = tile < t_hi;
+        if (have && tile >= end) {
+            t = find_owner(s_begin, ntensors, tile);
+            first = s_begin[t]; end = s_begin[t + 1u];
+            const DDesc &D = w.ddesc[t];
+            const DState &S = w.dst[t];
+            n = D.n;
+            good = S.status == 0 && (WHICH == 0 || wants_moments(D));          // (bitmap_o only where moments are wanted)
+            bm = gptr((const u64 *)(D.blob + (WHICH == 0 ? S.off_bw : S.off_bo)));
+            if (WHICH == 1) { most = S.n_w; pop = S.pop_w; per_element = (S.flags & 8u) != 0u; }
         }
-        const EXCP_CONSTANT DDesc *D = (const EXCP_CONSTANT DDesc *)(uintptr_t)(w.ddesc + t);
-        const EXCP_CONSTANT DState *S = (const EXCP_CONSTANT DState *)(uintptr_t)(w.dst + t);
-        const u32 ltile = tile - first;
-        if (WHICH == 0) {
-            constexpr u32 AT_ONCE = 8;
-            const u32 group = min(AT_ONCE, min(end, t_hi) - tile);       // (the same in the whole wave)
-            u64 v[AT_ONCE];
-            if (S->status == 0) {
-                const EXCP_GLOBAL u64 *bm = gptr((const u64 *)(D->blob + S->off_bw));
-                const u64 n = D->n, nwords = excp_words(n), word0 = (u64)ltile * 64u + lane;
-                if (group == AT_ONCE && ltile * (u64)EXCP_TILE + AT_ONCE * EXCP_TILE <= n) {
+        u32 cnt = 0;
+        if (have && good) {
+            const u64 base = (u64)(tile - first) * EXCP_TILE;
+            if (WHICH == 0) {
+                const u64 word0 = (base >> 6) + 2u * l;
+                if (base + EXCP_TILE <= n) {
+                    typedef u64 pair __attribute__((ext_vector_type(2)));       // (sections begin at multiples of 16 bytes)
+                    pair v[4];
 #pragma unroll
-                    for (u32 k = 0; k < AT_ONCE; ++k) v[k] = bm[word0 + 64u * k];
+                    for (u32 k = 0; k < 4; ++k) v[k] = *(const EXCP_GLOBAL pair *)(bm + word0 + 16u * k);
+#pragma unroll
+                    for (u32 k = 0; k < 4; ++k) cnt += (u32)(__popcll(v[k].x) + __popcll(v[k].y));
                 } else {
+                    // bits beyond n must be clear in a well-formed blob; ignore them here
+                    const u64 nwords = excp_words(n);
 #pragma unroll
-                    for (u32 k = 0; k < AT_ONCE; ++k) {
-                        v[k] = 0ull;
-                        if (k >= group) continue;
-                        // bits beyond n must be clear in a well-formed blob; ignore them here
-                        const u64 word = word0 + 64u * k;
-                        if (word < nwords) v[k] = bm[word];
-                        if (word < nwords && n - word * 64u < 64u) v[k] &= (1ull << (n - word * 64u)) - 1ull;
+                    for (u32 k = 0; k < 8; ++k) {
+                        const u64 word = word0 + 16u * (k >> 1) + (k & 1u);
+                        if (word < nwords) cnt += (u32)__popcll(bm[word] & (n - word * 64u < 64u ? (1ull << (n - word * 64u)) - 1ull : ~0ull));
                     }
                 }
             } else {
+                u64 p0 = w.dec_cnt_w[tile], p1 = tile + 1u < end ? (u64)w.dec_cnt_w[tile + 1u] : pop;
+                p1 = min(p1, most);                        // damaged blob: stay inside the bitmap
+                p0 = min(p0, p1);
+                if (per_element) { p0 = base; p1 = min(n, base + EXCP_TILE); }      // one bit per element: the tile's own range
+                if (p0 < p1) {
+                    const u64 w0 = p0 >> 6, w1 = (p1 - 1u) >> 6;
+                    for (u64 wi = w0 + l; wi <= w1; wi += 32u) {
+                        u64 v[4];
 #pragma unroll
-                for (u32 k = 0; k < AT_ONCE; ++k) v[k] = 0ull;
-            }
-            u32 mine = 0;                                  // lane k: the count of tile + k
+                        for (u32 k = 0; k < 4; ++k) v[k] = wi + 8u * k <= w1 ? bm[wi + 8u * k] : 0ull;
 #pragma unroll
-            for (u32 k = 0; k < AT_ONCE; k += 2) {
-                if (k >= group) break;                     // (a mid-sized tensor leaves a wave one tile)
-                const u32 sum = (u32)__builtin_amdgcn_readlane((int)wave_incl_scan_u32((u32)__popcll(v[k]) | (u32)__popcll(v[k + 1]) << 16), 63);
-                if (lane == k) mine = sum & 0xffffu;
-                if (lane == k + 1u) mine = sum >> 16;
-            }
-            if (lane < group) w.dec_cnt_w[tile + lane] = mine;
-            tile += group;
-        } else {
-            u32 cnt = 0;
-            if (S->status == 0 && (D->m_out != nullptr || D->v_out != nullptr || D->cm != nullptr || D->cv != nullptr)) {
-                const u64 *bm = (const u64 *)(D->blob + S->off_bo);          // (only where moments are wanted)
-                u64 p0 = w.dec_cnt_w[tile];
-                u64 p1 = (tile + 1u < end) ? (u64)w.dec_cnt_w[tile + 1] : S->pop_w;
-                if (p1 > S->n_w) p1 = S->n_w;        // damaged blob: stay inside the bitmap
-                if (p0 > p1) p0 = p1;
-                if (S->flags & 8u) {                 // one bit per element: the tile's own range
-                    p0 = (u64)ltile * EXCP_TILE;
-                    p1 = (D->n - p0 < (u64)EXCP_TILE) ? D->n : p0 + EXCP_TILE;
+                        for (u32 k = 0; k < 4; ++k) {
+                            const u64 at = wi + 8u * k;
+                            cnt += (u32)__popcll(v[k] & range_mask(at == w0 ? (u32)(p0 & 63u) : 0u, at == w1 ? (u32)((p1 - 1u) & 63u) + 1u : 64u));
+                        }
+                    }
                 }
-                cnt = wave_sum_u32(popcount_range_lane(bm, p0, p1, lane));
             }
-            if (lane == 0) w.dec_cnt_o[tile] = cnt;
-            ++tile;
+        }
+        cnt = sum_of_eight(cnt);
+        if (have) {
+            if (l == 0u) table[tile] = cnt;
+            const u32 r = run_of(tile, t, first, ntensors);
+            if (r != run) {
+                if (l == 0u && sum) atomicAdd(&part[run], sum);
+                run = r; sum = 0;
+            }
+            sum += cnt;
         }
     }
-}
-
-// Exclusive scan of the per-tile counts of every tensor.  A tensor's tiles are cut into sixteen parts,
-// one workgroup each: first the parts' totals, then every workgroup scans its own part from the sum of
-// the parts before it.
-constexpr u32 DSCAN_PARTS = 16;
-
-__device__ __forceinline__ void dscan_range(u32 ntiles, u32 part, u32 &s0, u32 &s1) {
-    const u32 per = (ntiles + DSCAN_PARTS - 1u) / DSCAN_PARTS;
-    s0 = min(part * per, ntiles);
-    s1 = min(s0 + per, ntiles);
-}
-
-template <int WHICH>
-__global__ __launch_bounds__(EXCP_THREADS) void k_decode_scan_parts(Workspace w, u32 ntensors) {
-    __shared__ u64 s_sum[EXCP_THREADS / 64];
-    const u32 t = blockIdx.x / DSCAN_PARTS, part = blockIdx.x % DSCAN_PARTS, tid = threadIdx.x;
-    const DDesc &D = w.ddesc[t];
-    if (WHICH == 1 && !wants_moments(D)) return;
-    const u32 *cnt = (WHICH == 0 ? w.dec_cnt_w : w.dec_cnt_o) + D.tile_begin;
-    u32 s0, s1;
-    dscan_range(D.tile_count, part, s0, s1);
-    u64 local = 0;
-    for (u32 i = s0 + tid; i < s1; i += EXCP_THREADS) local += cnt[i];
-    local = wave_sum_u64(local);
-    if ((tid & 63u) == 0u) s_sum[tid >> 6] = local;
+    // Usually the workgroup's tiles are all of one run: then one atomic.  (One from every wave: 512 at the same address, 24 ragged
+    // tensors 53 instead of 8 us.)
+    const u32 first_run = (u32)__builtin_amdgcn_readfirstlane((int)run);
+    const bool one_run = __all(run == first_run || sum == 0u);
+    const u32 total = wave_sum_u32(l == 0u ? sum : 0u);
+    if (!one_run && l == 0u && sum) atomicAdd(&part[run], sum);
+    if (lane == 0u) { s_run[wave] = first_run; s_sum[wave] = one_run ? total : 0u; }
     __syncthreads();
-    if (tid == 0) w.dec_part[(u64)t * DSCAN_PARTS + part] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+    if (threadIdx.x != 0) return;
+#pragma unroll
+    for (u32 v = 0; v < EXCP_THREADS / 64; ++v) {
+        u32 mine = s_sum[v];
+#pragma unroll
+        for (u32 x = v + 1u; x < EXCP_THREADS / 64; ++x) if (s_run[x] == s_run[v]) { mine += s_sum[x]; s_sum[x] = 0u; }
+        if (mine) atomicAdd(&part[s_run[v]], mine);
+    }
 }
 
+// Exclusive scan of the per-tile counts of every tensor, a workgroup to a run of tiles (see k_decode_count): the first of every
+// tensor, then those that begin at a multiple of SCAN_BLOCK.  The workgroup of a tensor's last run checks the total against the header
+// and, where nothing can change the results after this, writes the record.
 template <int WHICH>
-__global__ __launch_bounds__(EXCP_THREADS) void k_decode_scan(Workspace w, u32 ntensors) {
-    __shared__ u32 s_sum[EXCP_THREADS];
-    const u32 t = blockIdx.x / DSCAN_PARTS, part = blockIdx.x % DSCAN_PARTS, tid = threadIdx.x;
+__global__ __launch_bounds__(EXCP_THREADS) void k_decode_scan(Workspace w, u32 ntensors, u32 records) {
+    __shared__ u32 s_wave[EXCP_THREADS / 64], s_before[EXCP_THREADS / 64], s_first[EXCP_THREADS / 64];
+    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const u32 *begin = w.tile_begin, *part = w.dec_part + (WHICH == 0 ? 0u : w.dec_part_stride);
+    u32 *table = WHICH == 0 ? w.dec_cnt_w : w.dec_cnt_o;
+    const bool inner = blockIdx.x >= ntensors;             // not a tensor's first run
+    const u32 s0 = inner ? (blockIdx.x - ntensors) * SCAN_BLOCK : begin[blockIdx.x];
+    u32 t = blockIdx.x;
+    if (inner) {                                           // the last tensor that begins before
+        u32 c = 0;
+        for (u32 i = tid; i < ntensors; i += EXCP_THREADS) c += begin[i] < s0;
+        c = wave_sum_u32(c);
+        if (lane == 0u) s_first[wave] = c;
+        __syncthreads();
+        c = (s_first[0] + s_first[1]) + (s_first[2] + s_first[3]);
+        if (c == 0u) return;
+        t = c - 1u;
+    }
     const DDesc &D = w.ddesc[t];
+    const u32 tb = begin[t], te = begin[t + 1u];
+    if (inner && te <= s0) return;                         // (tensors without tiles apart, one begins here: its own workgroup takes the run)
+    const u32 s1 = min(te, (s0 / SCAN_BLOCK + 1u) * SCAN_BLOCK);
+    const bool last = s1 == te;
+    if (WHICH == 1 && !wants_moments(D)) {                 // bitmap_o is not used for this one
+        if (records && last && tid == 0) decode_record(w, t, D.n, w.dst[t]);
+        return;
+    }
+    u32 v[SCAN_BLOCK / EXCP_THREADS], local = 0;
+#pragma unroll
+    for (u32 k = 0; k < SCAN_BLOCK / EXCP_THREADS; ++k) {
+        const u32 i = s0 + tid * (SCAN_BLOCK / EXCP_THREADS) + k;
+        v[k] = i < s1 ? table[i] : 0u;
+        local += v[k];
+    }
+    u32 before = 0;                                        // in the runs before this one
+    if (inner) {
+        if (tid == 0) before = part[t];
+        for (u32 b = tb / SCAN_BLOCK + 1u + tid; b < s0 / SCAN_BLOCK; b += EXCP_THREADS) before += part[ntensors + b];
+    }
+    before = wave_sum_u32(before);
+    const u32 incl = wave_incl_scan_u32(local);
+    if (lane == 63u) { s_before[wave] = before; s_wave[wave] = incl; }
+    __syncthreads();
+    const u32 carry = (s_before[0] + s_before[1]) + (s_before[2] + s_before[3]);
+    u32 excl = carry + incl - local;
+    for (u32 q = 0; q < wave; ++q) excl += s_wave[q];
+#pragma unroll
+    for (u32 k = 0; k < SCAN_BLOCK / EXCP_THREADS; ++k) {
+        const u32 i = s0 + tid * (SCAN_BLOCK / EXCP_THREADS) + k;
+        if (i < s1) table[i] = excl;
+        excl += v[k];
+    }
+    if (!last || tid != 0) return;
     DState &S = w.dst[t];
-    u32 *cnt = (WHICH == 0 ? w.dec_cnt_w : w.dec_cnt_o) + D.tile_begin;
-    if (WHICH == 1 && !wants_moments(D)) return;    // bitmap_o is not used for this one
-    u32 s0, s1;
-    dscan_range(D.tile_count, part, s0, s1);
-    u64 carry = 0;
-    for (u32 q = 0; q < part; ++q) carry += w.dec_part[(u64)t * DSCAN_PARTS + q];
-    if (part == DSCAN_PARTS - 1u && tid == 0) {
-        const u64 total = carry + w.dec_part[(u64)t * DSCAN_PARTS + part];
-        if (WHICH == 0) { S.pop_w = total; if (S.status == 0 && total != S.n_w) S.status = -4; }
-        else { S.pop_o = total; if (S.status == 0 && total != S.n_o) S.status = -4; }
-    }
-    for (u32 base = s0; base < s1; base += EXCP_THREADS) {
-        u32 i = base + tid;
-        u32 v = (i < s1) ? cnt[i] : 0u;
-        s_sum[tid] = v;
-        __syncthreads();
-        for (int off = 1; off < EXCP_THREADS; off <<= 1) {
-            u32 a = (tid >= (u32)off) ? s_sum[tid - off] : 0u;
-            __syncthreads();
-            s_sum[tid] += a;
-            __syncthreads();
-        }
-        if (i < s1) cnt[i] = (u32)(carry + s_sum[tid] - v);
-        carry += s_sum[EXCP_THREADS - 1];
-        __syncthreads();
-    }
+    const u64 total = (u64)carry + ((s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]));
+    if (WHICH == 0) { S.pop_w = total; if (S.status == 0 && total != S.n_w) S.status = -4; }
+    else { S.pop_o = total; if (S.status == 0 && total != S.n_o) S.status = -4; }
+    if (records) decode_record(w, t, D.n, S);
 }
 
 // Four consecutive floats at an address that is only known to be 4-byte aligned.
@@ -352,7 +405,8 @@ __device__ __forceinline__ void decode_tiles(const Workspace &w, u32 ntensors, u
     u32 cur_t = 0xffffffffu;
     load_tile_table(s_tiles, w.tile_begin, ntensors);
     for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const u32 t = find_owner(s_tiles, ntensors, tile);
+        const u32 owner = find_owner(s_tiles, ntensors, tile);
+        const u32 t = w.cdesc ? w.cdesc[owner].first_desc + w.cdesc[owner].steps - 1u : owner;      // (of a chain: the last checkpoint)
         const DDesc &D = w.ddesc[t];
         const DState &S = w.dst[t];
         if (S.status != 0) continue;                       // same decision for the whole workgroup
@@ -363,7 +417,7 @@ __device__ __forceinline__ void decode_tiles(const Workspace &w, u32 ntensors, u
         const bool bf = wt == 2u;
         const u32 nbits = S.nbits, E = RAW ? 0u : 1u << (nbits & 15u), cmask = E - 1u;
         const u64 n = D.n;
-        const u32 ltile = tile - D.tile_begin;
+        const u32 ltile = tile - s_tiles[owner], ctile = D.tile_begin + ltile;       // (in the tensor; in the tables of counts)
         const u64 base = (u64)ltile * EXCP_TILE;
         const u32 rem = (n - base < (u64)EXCP_TILE) ? (u32)(n - base) : EXCP_TILE;   // elements of this tile
         const unsigned char *blob = D.blob;
@@ -415,14 +469,14 @@ __device__ __forceinline__ void decode_tiles(const Workspace &w, u32 ntensors, u
         u32 incl = wave_incl_scan_u32(pc);
         const u32 excl = incl - pc;
         const u32 cnt = __shfl(incl, 63, WAVE);            // survivors of this tile
-        const u32 q_tile = w.dec_cnt_w[tile];              // survivors before this tile
+        const u32 q_tile = w.dec_cnt_w[ctile];             // survivors before this tile
         const u64 wbit0 = (u64)q_tile * nbits;
         const u32 woff = (u32)(wbit0 & 31ull);
         u32 o_tile = 0, ocnt = 0, moff = 0, ooff = 0;
         const bool nw2m = MOMENTS && (S.flags & 8u) != 0u;    // M_o bits per element instead of per kept residual
         if (MOMENTS && moments) {
-            o_tile = w.dec_cnt_o[tile];
-            const u32 o_next = (ltile + 1u < D.tile_count) ? w.dec_cnt_o[tile + 1] : (u32)S.pop_o;
+            o_tile = w.dec_cnt_o[ctile];
+            const u32 o_next = (ltile + 1u < D.tile_count) ? w.dec_cnt_o[ctile + 1u] : (u32)S.pop_o;
             ocnt = o_next - o_tile;
             moff = (u32)(((u64)o_tile * nbits) & 31ull);
             ooff = nw2m ? 0u : q_tile & 31u;
@@ -1140,14 +1194,6 @@ __global__ void k_dense_status(Workspace w, u32 ntensors) {
     if (t < ntensors && w.dst[t].status == -40) w.dst[t].status = -4;
 }
 
-// The first launch of a large group: no kinds of blob met yet, and a single tensor's description, which comes as an argument,
-// where the others look for it.
-__global__ void k_decode_setup(Workspace w, DDesc d, u32 single) {
-    if (threadIdx.x != 0) return;
-    *w.dec_kinds = 0u;
-    if (single) { w.ddesc[0] = d; w.tile_begin[0] = 0u; w.tile_begin[1] = d.tile_count; }
-}
-
 template <bool MOMENTS, bool W16>
 __global__ __launch_bounds__(EXCP_THREADS) void k_decode_small(Workspace w, u32 ntensors, u32 ntiles) {
     decode_tiles<MOMENTS, false, W16 ? 1 : 0>(w, ntensors, ntiles);
@@ -1156,6 +1202,15 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_decode_small(Workspace w, u32 
 
 }  // namespace
 
+// Per-tile counts of a bitmap and their scan.
+template <int WHICH>
+static void launch_decode_counts(const Workspace &w, u32 ntensors, u32 ntiles, bool records, hipStream_t s) {
+    if (ntiles) {
+        const u32 blocks = std::min((ntiles + 31u) / 32u, excp_grid(w, 8));            // eight tiles to a wave at least
+        hipLaunchKernelGGL(k_decode_count<WHICH>, dim3(blocks), dim3(EXCP_THREADS), (ntensors + 1u) * sizeof(u32), s, w, ntensors, ntiles);
+    }
+    hipLaunchKernelGGL(k_decode_scan<WHICH>, dim3(excp_scan_runs(ntensors, ntiles)), dim3(EXCP_THREADS), 0, s, w, ntensors, records ? 1u : 0u);
+}
 // Headers, counts and scans of a group whose largest tensor has `largest` tiles.  `single`: the description of its only tensor,
 // not in the tables yet.  `records`: nothing can change the results after this, they go to the host.
 void launch_decode_prep(const Workspace &w, u32 ntensors, u32 ntiles, u32 largest, bool allow_raw, bool moments, bool records, const DDesc *single, hipStream_t s) {
@@ -1165,13 +1220,10 @@ void launch_decode_prep(const Workspace &w, u32 ntensors, u32 ntiles, u32 larges
                            single ? *single : DDesc{}, single ? 1u : 0u);
         return;
     }
-    hipLaunchKernelGGL(k_decode_setup, dim3(1), dim3(64), 0, s, w, single ? *single : DDesc{}, single ? 1u : 0u);
-    hipLaunchKernelGGL(k_decode_parse, dim3((ntensors + 255) / 256), dim3(256), 0, s, w, ntensors, allow_raw ? 1u : 0u);
-    for (int which = 0; which < (moments ? 2 : 1); ++which) {
-        launch_decode_count(w, ntensors, ntiles, which, s);
-        launch_decode_scan(w, ntensors, which, s);
-    }
-    if (records) hipLaunchKernelGGL(k_decode_finish, dim3((ntensors + 255) / 256), dim3(256), 0, s, w, ntensors);
+    hipLaunchKernelGGL(k_decode_parse, dim3((ntensors + PARSE_THREADS - 1u) / PARSE_THREADS), dim3(PARSE_THREADS), 0, s, w, ntensors, excp_scan_runs(ntensors, ntiles), allow_raw ? 1u : 0u,
+                       single ? *single : DDesc{}, single ? 1u : 0u);
+    launch_decode_counts<0>(w, ntensors, ntiles, records && !moments, s);
+    if (moments) launch_decode_counts<1>(w, ntensors, ntiles, records, s);
 }
 // The main pass of a small group, of blobs written with and without quantisation in one launch: a launch that finds nothing to do
 // is a tenth of such a call.
@@ -1182,24 +1234,6 @@ void launch_decode_small(const Workspace &w, u32 ntensors, u32 ntiles, bool mome
     else if (moments) hipLaunchKernelGGL((k_decode_small<true, false>), grid, block, 0, s, w, ntensors, ntiles);
     else if (w16) hipLaunchKernelGGL((k_decode_small<false, true>), grid, block, 0, s, w, ntensors, ntiles);
     else hipLaunchKernelGGL((k_decode_small<false, false>), grid, block, 0, s, w, ntensors, ntiles);
-}
-void launch_decode_count(const Workspace &w, u32 ntensors, u32 ntiles, int which, hipStream_t s) {
-    if (!ntiles) return;
-    u32 blocks = (ntiles + 3) / 4;
-    if (blocks > excp_grid(w, 8)) blocks = excp_grid(w, 8);
-    if (which == 0) hipLaunchKernelGGL(k_decode_count<0>, dim3(blocks), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);
-    else hipLaunchKernelGGL(k_decode_count<1>, dim3(blocks), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);
-}
-void launch_decode_scan(const Workspace &w, u32 ntensors, int which, hipStream_t s) {
-    if (!ntensors) return;
-    const dim3 grid(ntensors * DSCAN_PARTS), block(EXCP_THREADS);
-    if (which == 0) {
-        hipLaunchKernelGGL(k_decode_scan_parts<0>, grid, block, 0, s, w, ntensors);
-        hipLaunchKernelGGL(k_decode_scan<0>, grid, block, 0, s, w, ntensors);
-    } else {
-        hipLaunchKernelGGL(k_decode_scan_parts<1>, grid, block, 0, s, w, ntensors);
-        hipLaunchKernelGGL(k_decode_scan<1>, grid, block, 0, s, w, ntensors);
-    }
 }
 void launch_decode_main(const Workspace &w, u32 ntensors, u32 ntiles, bool moments, hipStream_t s) {
     if (!ntiles) return;

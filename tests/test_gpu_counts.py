@@ -1,0 +1,64 @@
+"""Counts and scans of the restores where they are cut: a tensor of more tiles than a workgroup scans (4096) behind ragged ones,
+tensors of one tile side by side, and chains of more checkpoints than a group has tensors, with the last one's moments."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2406_11257_amd as X
+from gpu_util import gpu_compress, to_dev
+from test_gpu_parity import case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("flags", [0, X.EXCP_FLAG_NO_W2M])
+@pytest.mark.parametrize("sizes", [[70_001, 4097 * 4096 + 5, 0, 1, 33 * 4096, 4096], [40 * 4096] + [1 + 37 * i for i in range(120)] + [0, 9001]])
+def test_restore_of_tensors_on_both_sides_of_a_run(sizes, flags):
+    cases = [case(n, 300 + i) for i, n in enumerate(sizes)]
+    ctx = X.Context(max(sizes), sum(sizes))
+    rc, outs = gpu_compress(ctx, cases, iters=1, flags=flags)
+    assert rc == 0
+    res = [[torch.full((n,), 9.0, device="cuda") for _ in range(3)] for n in sizes]
+    for want in (3, 1):                                     # with the moments, and the weights alone
+        ctx.excp_decompress_tensors([(to_dev(c[0]), o["blob_dev"], int(o["stats"].blob_bytes), n, *(r[:want] + [None] * (3 - want)))
+                                     for c, o, n, r in zip(cases, outs, sizes, res)])
+        rc, stats = ctx.excp_collect(check=False)
+        assert rc == 0
+        for c, o, st, r in zip(cases, outs, stats, res):
+            assert (st.n_w, st.n_o, st.status) == (o["stats"].n_w, o["stats"].n_o, 0)
+            for got, ref in zip(r[:want], O.decompress_step(c[0], o["blob"])):
+                assert got.cpu().numpy().tobytes() == ref.tobytes()
+            for t in r:
+                t.fill_(9.0)
+    ctx.close()
+
+
+def test_more_checkpoints_than_tensors_of_a_group():
+    count, steps = 300, 4                                    # 1200 checkpoints
+    rng = np.random.default_rng(3)
+    sizes = [int(x) for x in np.exp(rng.uniform(0, np.log(9000), count))]
+    sizes[17], sizes[211] = 34 * 4096 + 1, 50 * 4096          # (beyond what one launch prepares)
+    ctx = X.Context(max(sizes), sum(sizes))
+    prev = [case(n, i)[0] for i, n in enumerate(sizes)]
+    first, blobs = list(prev), [[] for _ in sizes]
+    for step in range(steps):
+        cases = []
+        for i, n in enumerate(sizes):
+            _, _, m, v = case(n, 1000 * step + i)
+            cases.append((prev[i], (prev[i] + rng.laplace(0, 1e-4, n)).astype(np.float32), m, v))
+        rc, outs = gpu_compress(ctx, cases, iters=2)
+        assert rc == 0
+        for b, o in zip(blobs, outs):
+            b.append(o["blob"])
+        prev = [o["W_recon"] for o in outs]
+    res = [[torch.full((n,), 9.0, device="cuda") for _ in range(3)] for n in sizes]
+    ctx.excp_reconstruct_chain([(to_dev(W0), [torch.from_numpy(np.frombuffer(x, np.uint8).copy()).cuda() for x in b], [len(x) for x in b], *r)
+                                for W0, b, r in zip(first, blobs, res)])
+    rc, stats = ctx.excp_collect(check=False)
+    assert rc == 0 and all(st.status == 0 for st in stats)
+    for W, b, r in zip(prev, blobs, res):
+        _, m, v = O.decompress_step(W, b[-1])
+        for got, ref in zip(r, (W, m, v)):
+            assert got.cpu().numpy().tobytes() == np.ascontiguousarray(ref).tobytes()
+    ctx.close()
