@@ -214,8 +214,10 @@ __device__ __forceinline__ void mask_quarter(const Regs<W16> &R, const SubTile &
     drain(S.sv, st_v, ov, lane);
 }
 
-// Pass A.  A wave owns whole sub-tiles (a contiguous range of the group's sub-tile list) and walks each
-// in four quarters of 512 elements, four consecutive elements to a lane.  Nothing is shared between waves: no barrier after
+// Pass A.  A wave owns whole sub-tiles, neighbouring waves neighbouring ones, and walks each
+// in four quarters of 512 elements, four consecutive elements to a lane.  (A wave goes on as many sub-tiles further as there are waves:
+// those at work at a time lie together in all seven arrays, where a range of its own for every wave made as many regions.  410M shape
+// 1535 -> 1462 us, its weights in bf16 1240 -> 1139, 7B shape, four layers, 4014 -> 3975, 30 M elements 119 -> 116.)  Nothing is shared between waves: no barrier after
 // the tile table is loaded.  While one quarter is worked on the next is already on its way from memory (two register sets).
 //
 // Per element: the residual; the keep decision |d| > t_w / sqrt(v) with correctly rounded sqrt and
@@ -238,15 +240,13 @@ __global__ __launch_bounds__(EXCP_THREADS, 4) void k_mask_slots(Workspace w, Gro
     const u32 nsub = 2u * g.ntiles;
     load_tile_table(s_tiles, w.tile_begin, g.ntensors);
     const u32 nwaves = gridDim.x * (EXCP_THREADS / 64), wid = blockIdx.x * (EXCP_THREADS / 64) + wave;
-    const u32 sub_lo = (u32)(((u64)wid * nsub) / nwaves), sub_hi = (u32)(((u64)(wid + 1u) * nsub) / nwaves);
-    if (sub_lo >= sub_hi) return;
     u32 *my_bo = s_bo[wave];
     float *stage = s_stage[wave];
     my_bo[lane] = 0u;
     if (lane == 0u) my_bo[SUB / 32] = 0u;
     u32 t = 0, first_sub = 0, end_sub = 0;                // the tensor in hand, its first sub-tile, one past its last
     Regs<W16> A, B;
-    for (u32 sub = sub_lo; sub < sub_hi; ++sub) {
+    for (u32 sub = wid; sub < nsub; sub += nwaves) {
         if (sub >= end_sub) {                             // (looked up again only when a tensor's sub-tiles run out)
             t = (u32)__builtin_amdgcn_readfirstlane((int)find_owner(s_tiles, g.ntensors, sub >> 1));
             first_sub = (u32)__builtin_amdgcn_readfirstlane((int)(2u * s_tiles[t]));
