@@ -151,6 +151,7 @@ struct GroupParams {
     u32 unit_shift;             // log2 of the positions of a stream whose bucket counts share a row
     u32 fine;                   // the first `fine` tensors in order of size may have cells inside their buckets (k_km_cells)
     u32 fine_size;              // ... by the workgroups of size 0, 1 or 2
+    u64 largest;                // elements of the largest tensor
     u32 samples;                // values of a stream that its value -> bucket map is made from
 };
 
@@ -356,6 +357,7 @@ void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s);
 // A stream of the context's own beside the caller's, and the events that order the two.
 struct SideStream { hipStream_t stream; hipEvent_t fork, join; };
 void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s, const SideStream &side);
+void launch_bitmap_o(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_assign_pack(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_small_front(const Workspace &w, const GroupParams &g, const TDesc *single, hipStream_t s);
 void launch_small_codes(const Workspace &w, const GroupParams &g, hipStream_t s);

@@ -605,36 +605,40 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             for (u32 q = 0; q < nbig; ++q) p.slots += descs.h[g.first + q].acc_slot != EXCP_NO_SLOT ? 1u : 0u;
         }
         p.unit_shift = excp_unit_shift(elems, nbig, excp_gather_subs(g.ntiles, (u32)w.cus), (u32)w.cus, excp_count_rows(c->max_group, kMaxGroupTensors));
-        p.fine_size = excp_fine_size(largest);
+        p.fine_size = excp_fine_size(largest); p.largest = largest;
         p.samples = excp_samples(p.fine != 0u, largest);
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
         { StageTimer t(c, ST_LAYOUT); }                      // (made inside the mask scan and k_small_front: the span, one a group, is empty)
         // The small tensors: two launches, beside the larger ones on the context's own stream.  (They depend on nothing but what was
-        // enqueued before this group; the 14M shape has 50 of them among 76: 535 -> 526 us; the 410M shape 194 among 292: 5337 -> 5027.)
+        // enqueued before this group; the 14M shape has 50 of them among 76: 535 -> 526 us; the 410M shape 194 among 292: 5337 -> 5027.
+        // They are enqueued when the larger ones have something to do for a while: calls of the runtime take time too.)
         const u32 nsmall = g.count - nbig;
-        if (nsmall) {
+        if (nsmall && nbig) (void)hipEventRecord(c->side.fork, s);
+        auto launch_small = [&]() {
+            if (!nsmall) return;
             Workspace ws = w;
             GroupParams ps = p;
             ws.desc = w.desc + nbig; ws.st = w.st + nbig;
             ps.ntensors = nsmall;
             const hipStream_t to = nbig ? c->side.stream : s;
-            if (nbig) { (void)hipEventRecord(c->side.fork, s); (void)hipStreamWaitEvent(c->side.stream, c->side.fork, 0); }
+            if (nbig) (void)hipStreamWaitEvent(c->side.stream, c->side.fork, 0);
             StageTimer t(c, ST_MISC, to);
             launch_small_front(ws, ps, single ? descs.h : nullptr, to);
             launch_small_codes(ws, ps, to);
-        }
-        if (!nbig) continue;
+        };
+        if (!nbig) { launch_small(); continue; }
         { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, single ? descs.h : nullptr, s); }
         { StageTimer t(c, ST_STATS); launch_stats(w, p, 1, nullptr, s); }
         { StageTimer t(c, ST_SELECT); launch_stats(w, p, 2, nullptr, s); }
         { StageTimer t(c, ST_MASK_COMPACT); launch_mask_compact(w, p, 0, s); }
+        launch_small();
         { StageTimer t(c, ST_MASK_SCAN); launch_mask_compact(w, p, 1, s); }
         // the value -> bucket maps come from the slots, before the pass that makes the dense survivor arrays:
         // that pass also takes the bucket counts
         if (!raw) { StageTimer t(c, ST_KM_SAMPLE); launch_km_partition(w, p, 0, s); }
         { StageTimer t(c, ST_MASK_GATHER); launch_mask_compact(w, p, 2, s); }
         if (raw) {
-            StageTimer t(c, ST_ASSIGN_PACK); launch_store_raw(w, p, s);
+            StageTimer t(c, ST_ASSIGN_PACK); launch_store_raw(w, p, s); launch_bitmap_o(w, p, s);
         } else {
             { StageTimer t(c, ST_KM_SCAN); launch_km_partition(w, p, 1, s); }
             { StageTimer t(c, ST_KM_SCATTER); launch_km_partition(w, p, 2, s); }

@@ -286,8 +286,8 @@ __device__ __forceinline__ u32 chunk_elem(u32 it) { return ((it >> 2) * EXCP_THR
 // stream (2 to 16 chunks, by the size of the group), a row each.  One workgroup per stream turns them into positions:
 // bucket totals, their scan, then every row's first position in every bucket.  A wave reads a row, four buckets to
 // a lane, and owns a sixteenth of the rows; what bounds it is the number of loads that wait for one another.  (With a bucket
-// to a thread and a quarter of the rows each, 354 rows of a 16.8 M-element tensor took 14.4 us.)
-constexpr u32 SCAN_PARTS = 16, CROWD_MOST = 8192;
+// to a thread and a quarter of the rows each, 354 rows of a 16.8 M-element tensor took 14.4 us; with each row read twice 13.3, with up to 24 rows a wave held in registers 10.)
+constexpr u32 SCAN_PARTS = 16, SCAN_HELD = 24, CROWD_MOST = 8192;
 __global__ __launch_bounds__(SCAN_PARTS * 64) void k_km_scan(Workspace w, GroupParams g) {
     __shared__ __attribute__((aligned(16))) u32 tot[SCAN_PARTS][NBKT];
     __shared__ __attribute__((aligned(16))) u32 first[NBKT];
@@ -300,9 +300,17 @@ __global__ __launch_bounds__(SCAN_PARTS * 64) void k_km_scan(Workspace w, GroupP
     const u32 rows = (u32)((len + (1ull << g.unit_shift) - 1u) >> g.unit_shift);
     const u32 per = (rows + SCAN_PARTS - 1u) / SCAN_PARTS, a0 = min(part * per, rows), a1 = min(a0 + per, rows);
     EXCP_GLOBAL u4 *cnt = gptr((u4 *)(w.km_cnt + (u64)w.seg[sidx].row_begin * NBKT)) + lane;      // (rows are 1 KB)
-    u4 s = {0u, 0u, 0u, 0u};
+    u4 s = {0u, 0u, 0u, 0u}, held[SCAN_HELD];
+    const bool once = per <= SCAN_HELD;                    // the wave's rows stay in registers
+    if (once) {
+#pragma unroll
+        for (u32 c = 0; c < SCAN_HELD; ++c) held[c] = a0 + c < a1 ? cnt[(u64)(a0 + c) * (NBKT / 4u)] : (u4){0u, 0u, 0u, 0u};
+#pragma unroll
+        for (u32 c = 0; c < SCAN_HELD; ++c) s += held[c];
+    } else {
 #pragma unroll 8
-    for (u32 c = a0; c < a1; ++c) s += cnt[(u64)c * (NBKT / 4u)];
+        for (u32 c = a0; c < a1; ++c) s += cnt[(u64)c * (NBKT / 4u)];
+    }
     *(u4 *)&tot[part][4u * lane] = s;
     __syncthreads();
     u32 total = 0, incl = 0;
@@ -332,6 +340,14 @@ __global__ __launch_bounds__(SCAN_PARTS * 64) void k_km_scan(Workspace w, GroupP
     __syncthreads();
     u4 run = *(const u4 *)&first[4u * lane];
     for (u32 q = 0; q < part; ++q) run += *(const u4 *)&tot[q][4u * lane];
+    if (once) {
+#pragma unroll
+        for (u32 c = 0; c < SCAN_HELD; ++c) {
+            if (a0 + c < a1) cnt[(u64)(a0 + c) * (NBKT / 4u)] = run;
+            run += held[c];
+        }
+        return;
+    }
 #pragma unroll 8
     for (u32 c = a0; c < a1; ++c) {
         const u4 v = cnt[(u64)c * (NBKT / 4u)];
@@ -2154,21 +2170,23 @@ void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s) {
 // iteration and one for the final centres.  The two kinds have nothing to do with each other and neither fills the GPU, so one
 // goes to a stream of its own: the launches, where cells make it likely that no stream takes them (then they are empty, 4.5 us
 // each, which pass beside the first kind), otherwise the single one (the 410M shape: 219 us beside 186), because what begins on
-// the other stream begins some 15 us later.
+// the other stream begins some 15 us later.  Nothing of this needs bitmap_o, which is made beside, where there is less to do.
 template <u32 KMAX>
 static void launch_lloyd(const Workspace &w, const GroupParams &g, hipStream_t s, const SideStream &side) {
     const hipStream_t many = g.fine ? side.stream : s, one = g.fine || !g.slots ? s : side.stream;
     if (g.slots) {
         (void)hipEventRecord(side.fork, s);
         (void)hipStreamWaitEvent(side.stream, side.fork, 0);
-        if (one != s) hipLaunchKernelGGL(k_km_lloyd<KMAX>, dim3(3 * g.ntensors), dim3(LLOYD_THREADS), 0, one, w, g);
-        hipLaunchKernelGGL(k_km_units<KMAX>, dim3(1), dim3(LLOYD_THREADS), 0, many, w, g);
-        const u32 units = excp_lloyd_grid(excp_grid(w, lloyd_per_cu(KMAX)), g.slots);
-        for (u32 i = 0; i <= (u32)g.iters; ++i) hipLaunchKernelGGL(k_km_iter<KMAX>, dim3(units), dim3(LLOYD_THREADS), 0, many, w, g, i);
-        (void)hipEventRecord(side.join, side.stream);
     }
-    if (one == s) hipLaunchKernelGGL(k_km_lloyd<KMAX>, dim3(3 * g.ntensors), dim3(LLOYD_THREADS), 0, s, w, g);
-    if (g.slots) (void)hipStreamWaitEvent(s, side.join, 0);
+    // (first: the others are a dozen calls of the runtime, during which it would not yet have begun)
+    hipLaunchKernelGGL(k_km_lloyd<KMAX>, dim3(3 * g.ntensors), dim3(LLOYD_THREADS), 0, one, w, g);
+    launch_bitmap_o(w, g, one);
+    if (!g.slots) return;
+    hipLaunchKernelGGL(k_km_units<KMAX>, dim3(1), dim3(LLOYD_THREADS), 0, many, w, g);
+    const u32 units = excp_lloyd_grid(excp_grid(w, lloyd_per_cu(KMAX)), g.slots);
+    for (u32 i = 0; i <= (u32)g.iters; ++i) hipLaunchKernelGGL(k_km_iter<KMAX>, dim3(units), dim3(LLOYD_THREADS), 0, many, w, g, i);
+    (void)hipEventRecord(side.join, side.stream);
+    (void)hipStreamWaitEvent(s, side.join, 0);
 }
 void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s, const SideStream &side) {
     if (!g.ntensors) return;

@@ -335,9 +335,9 @@ __device__ __forceinline__ void store_batch(EXCP_GLOBAL float *dst, const float 
 
 // Exclusive scan of the sub-tile counts of every tensor; the totals are the tensor's n_w and n_o.
 // Counts are packed (survivors << 32 | moment survivors).  A tensor's sub-tiles are cut into sixteen
-// parts, one workgroup each: first the parts' totals, then every workgroup scans its own part from the
-// sum of the parts before it.
-constexpr u32 MSCAN_PARTS = 16;
+// parts, one workgroup each, which begins from the sum of the parts before it: it adds their counts up itself, or, where those are
+// more than MSCAN_DIRECT, their totals, which a launch before this one has made.  (16.8 M elements: 4.7 us and a launch less.)
+constexpr u32 MSCAN_PARTS = 16, MSCAN_DIRECT = 1u << 14;
 
 __device__ __forceinline__ void mscan_range(u32 nsub, u32 part, u32 &s0, u32 &s1) {
     const u32 per = ((nsub + MSCAN_PARTS - 1u) / MSCAN_PARTS + 3u) & ~3u;
@@ -439,24 +439,31 @@ __device__ __forceinline__ void layout(const Workspace &w, const GroupParams &g)
 }
 
 // (The workgroup that finds a tensor's totals draws a ticket; the last one goes on with the layout.)
-__global__ __launch_bounds__(EXCP_THREADS) void k_mask_scan(Workspace w, GroupParams g) {
-    __shared__ u64 s_sum[EXCP_THREADS];
+__global__ __launch_bounds__(EXCP_THREADS) void k_mask_scan(Workspace w, GroupParams g, u32 direct) {
+    __shared__ u64 s_wave[EXCP_THREADS / 64], s_before[EXCP_THREADS / 64];
     __shared__ u32 s_ticket;
-    const u32 t = blockIdx.x / MSCAN_PARTS, part = blockIdx.x % MSCAN_PARTS, tid = threadIdx.x;
+    const u32 t = blockIdx.x / MSCAN_PARTS, part = blockIdx.x % MSCAN_PARTS, tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const TDesc &D = w.desc[t];
     const u32 nsub = 2u * D.tile_count;
     u32 s0, s1;
     mscan_range(nsub, part, s0, s1);
-    u64 *cnt = w.tile_status + 2ull * D.tile_begin;
+    const u64 *cnt = w.tile_status + 2ull * D.tile_begin;
     u64 carry = 0;
-    for (u32 q = 0; q < part; ++q) carry += w.mask_part[(u64)t * MSCAN_PARTS + q];
-    if (part == MSCAN_PARTS - 1u && tid == 0) {
-        const u64 total = carry + w.mask_part[(u64)t * MSCAN_PARTS + part];
-        __hip_atomic_store(&w.st[t].n_w, total >> 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&w.st[t].n_o, total & 0xffffffffull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // (both have arrived before the ticket is drawn)
-        s_ticket = atomicAdd(w.scan_ticket, 1u);
+    if (direct) {
+        for (u32 i = tid; i < s0; i += 8u * EXCP_THREADS) {
+            u64 v[8];
+#pragma unroll
+            for (u32 q = 0; q < 8; ++q) v[q] = i + q * EXCP_THREADS < s0 ? cnt[i + q * EXCP_THREADS] : 0ull;
+#pragma unroll
+            for (u32 q = 0; q < 8; ++q) carry += v[q];
+        }
+    } else if (tid < part) {
+        carry = w.mask_part[(u64)t * MSCAN_PARTS + tid];
     }
+    carry = wave_sum_u64(carry);
+    if (lane == 0u) s_before[wave] = carry;
+    __syncthreads();
+    carry = (s_before[0] + s_before[1]) + (s_before[2] + s_before[3]);
     for (u32 base = s0; base < s1; base += EXCP_THREADS * 4) {
         // four consecutive sub-tiles per thread
         u64 v[4], local = 0;
@@ -466,23 +473,25 @@ __global__ __launch_bounds__(EXCP_THREADS) void k_mask_scan(Workspace w, GroupPa
             v[q] = (i < s1) ? cnt[i] : 0ull;
             local += v[q];
         }
-        s_sum[tid] = local;
+        const u64 incl = wave_incl_scan_u64(local);
+        if (lane == 63u) s_wave[wave] = incl;
         __syncthreads();
-        for (int off = 1; off < EXCP_THREADS; off <<= 1) {
-            u64 a = (tid >= (u32)off) ? s_sum[tid - off] : 0ull;
-            __syncthreads();
-            s_sum[tid] += a;
-            __syncthreads();
-        }
-        u64 run = carry + s_sum[tid] - local;
+        u64 run = carry + incl - local;
+        for (u32 q = 0; q < wave; ++q) run += s_wave[q];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             u32 i = base + tid * 4 + q;
             if (i < s1) w.mask_prefix[2ull * D.tile_begin + i] = run;
             run += v[q];
         }
-        carry += s_sum[EXCP_THREADS - 1];
+        carry += (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]);
         __syncthreads();
+    }
+    if (part == MSCAN_PARTS - 1u && tid == 0) {
+        __hip_atomic_store(&w.st[t].n_w, carry >> 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&w.st[t].n_o, carry & 0xffffffffull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // (both have arrived before the ticket is drawn)
+        s_ticket = atomicAdd(w.scan_ticket, 1u);
     }
     if (part != MSCAN_PARTS - 1u) return;
     __syncthreads();
@@ -761,16 +770,21 @@ void launch_mask_compact(const Workspace &w, const GroupParams &g, int phase, hi
         else if (w16) hipLaunchKernelGGL((k_mask_slots<false, true>), grid, block, 0, s, w, g);
         else hipLaunchKernelGGL((k_mask_slots<false, false>), grid, block, 0, s, w, g);
     } else if (phase == 1) {
-        hipLaunchKernelGGL(k_mask_scan_parts, dim3(g.ntensors * MSCAN_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
-        hipLaunchKernelGGL(k_mask_scan, dim3(g.ntensors * MSCAN_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
+        const bool direct = g.largest <= (u64)MSCAN_DIRECT * SUB;
+        if (!direct) hipLaunchKernelGGL(k_mask_scan_parts, dim3(g.ntensors * MSCAN_PARTS), dim3(EXCP_THREADS), 0, s, w, g);
+        hipLaunchKernelGGL(k_mask_scan, dim3(g.ntensors * MSCAN_PARTS), dim3(EXCP_THREADS), 0, s, w, g, direct ? 1u : 0u);
     } else {
         const u32 subs = excp_gather_subs(g.ntiles, (u32)w.cus);
         u32 grid = (nsub + subs - 1u) / subs;
         if (grid > excp_grid(w, 48)) grid = excp_grid(w, 48);
         hipLaunchKernelGGL(k_mask_gather, dim3(grid), dim3(EXCP_THREADS), 0, s, w, g, subs);
-        u32 grid_o = (g.ntiles + 3) / 4;
-        if (grid_o > excp_grid(w, 16)) grid_o = excp_grid(w, 16);
-        if (g.flags & 8u) hipLaunchKernelGGL(k_mask_bitmap_o_elems, dim3(grid_o), dim3(EXCP_THREADS), 0, s, w, g);
-        else hipLaunchKernelGGL(k_mask_bitmap_o, dim3(grid_o), dim3(EXCP_THREADS), 0, s, w, g);
     }
+}
+
+// bitmap_o, any time after the scan (phase 1).
+void launch_bitmap_o(const Workspace &w, const GroupParams &g, hipStream_t s) {
+    if (!g.ntiles) return;
+    const u32 grid = std::min((g.ntiles + 3u) / 4u, excp_grid(w, 16));
+    if (g.flags & 8u) hipLaunchKernelGGL(k_mask_bitmap_o_elems, dim3(grid), dim3(EXCP_THREADS), 0, s, w, g);
+    else hipLaunchKernelGGL(k_mask_bitmap_o, dim3(grid), dim3(EXCP_THREADS), 0, s, w, g);
 }
