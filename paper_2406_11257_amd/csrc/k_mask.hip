@@ -759,11 +759,10 @@ void launch_mask_compact(const Workspace &w, const GroupParams &g, int phase, hi
     if (!g.ntiles && phase != 1) return;                   // (the scan also makes the layout, of empty tensors too)
     const u32 nsub = 2u * g.ntiles;
     if (phase == 0) {
-        // Where there are fewer sub-tiles than waves of twenty workgroups a compute unit, eight, and a sub-tile to each wave at least:
-        // twice as many as fit at once, without a last round that is nearly empty (16.8 M elements 78 -> 63 us, 14 M 73 -> 54,
-        // 25 M 98 -> 97; 4e8 elements 1500 with twenty, 1554 with eight).
-        const u32 per_cu = nsub < excp_grid(w, 80) ? 8u : 20u;
-        const dim3 grid(std::min(excp_grid(w, per_cu), (nsub + 3u) / 4u)), block(EXCP_THREADS);
+        // A sub-tile to each wave, up to eighty workgroups a compute unit, which then take a few each: the fewer, the closer together
+        // those lie that are at work (20, 40, 80, 160 workgroups: 410M shape 1454, 1441, 1419, 1442 us, bf16 weights 1195, 1129, 1097, 1105,
+        // four layers of the 7B shape 3947, 3904, 3890, 3907; 30 M elements 116 with eight, 106 with a sub-tile to each wave).
+        const dim3 grid(std::min(excp_grid(w, 80), (nsub + 3u) / 4u)), block(EXCP_THREADS);
         const bool nw2m = (g.flags & 8u) != 0, w16 = (g.flags & 0x30u) != 0;
         if (nw2m && w16) hipLaunchKernelGGL((k_mask_slots<true, true>), grid, block, 0, s, w, g);
         else if (nw2m) hipLaunchKernelGGL((k_mask_slots<true, false>), grid, block, 0, s, w, g);
