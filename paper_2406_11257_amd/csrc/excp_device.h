@@ -359,8 +359,7 @@ struct SideStream { hipStream_t stream; hipEvent_t fork, join; };
 void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s, const SideStream &side);
 void launch_bitmap_o(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_assign_pack(const Workspace &w, const GroupParams &g, hipStream_t s);
-void launch_small_front(const Workspace &w, const GroupParams &g, const TDesc *single, hipStream_t s);
-void launch_small_codes(const Workspace &w, const GroupParams &g, hipStream_t s);
+void launch_small(const Workspace &w, const GroupParams &g, const TDesc *single, hipStream_t s);
 void launch_finalize(const Workspace &w, const GroupParams &g, bool decode, hipStream_t s);
 void launch_decode_prep(const Workspace &w, u32 ntensors, u32 ntiles, u32 largest, bool allow_raw, bool moments, bool records, const DDesc *single, hipStream_t s);
 static inline bool excp_prep_small(u32 largest) { return largest <= 32u; }      // tiles of the largest tensor of a group that takes one launch

@@ -623,8 +623,7 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             const hipStream_t to = nbig ? c->side.stream : s;
             if (nbig) (void)hipStreamWaitEvent(c->side.stream, c->side.fork, 0);
             StageTimer t(c, ST_MISC, to);
-            launch_small_front(ws, ps, single ? descs.h : nullptr, to);
-            launch_small_codes(ws, ps, to);
+            ::launch_small(ws, ps, single ? descs.h : nullptr, to);
         };
         if (!nbig) { launch_small(); continue; }
         { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, single ? descs.h : nullptr, s); }

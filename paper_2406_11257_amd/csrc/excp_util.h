@@ -29,6 +29,18 @@ template <int CTRL, int ROWS>
 __device__ __forceinline__ u32 dpp_u32(u32 neutral, u32 v) { return (u32)__builtin_amdgcn_update_dpp((int)neutral, (int)v, CTRL, ROWS, 0xf, false); }
 template <int CTRL, int ROWS>
 __device__ __forceinline__ u64 dpp_u64(u64 v) { return (u64)dpp_u32<CTRL, ROWS>(0u, (u32)(v >> 32)) << 32 | dpp_u32<CTRL, ROWS>(0u, (u32)v); }
+// the value of the lane above (the last lane: `v` itself), and of the lane below (the first: itself)
+__device__ __forceinline__ u32 lane_above_u32(u32 v) { return dpp_u32<0x130, 0xf>(v, v); }
+__device__ __forceinline__ u32 lane_below_u32(u32 v) { return dpp_u32<0x138, 0xf>(v, v); }
+__device__ __forceinline__ float lane_above_f32(float v) { return u2f(lane_above_u32(f2u(v))); }
+__device__ __forceinline__ float lane_below_f32(float v) { return u2f(lane_below_u32(f2u(v))); }
+__device__ __forceinline__ __int128 lane_above_i128(__int128 v) {
+    const unsigned __int128 x = (unsigned __int128)v;
+    unsigned __int128 r = 0;
+#pragma unroll
+    for (int q = 3; q >= 0; --q) r = r << 32 | lane_above_u32((u32)(x >> (32 * q)));
+    return (__int128)r;
+}
 #define EXCP_WAVE_SCAN(v, FOLD, MOVE)                                                                        \
     do {                                                                                                     \
         FOLD(v, MOVE(0x111, 0xf)); FOLD(v, MOVE(0x112, 0xf)); FOLD(v, MOVE(0x114, 0xf)); FOLD(v, MOVE(0x118, 0xf));   /* row_shr 1, 2, 4, 8 */ \
@@ -210,30 +222,30 @@ __device__ __forceinline__ u32 bit_pos(u32 mag) { const u32 e = mag >> 23; retur
 // the bisection goes on from what the probes have proved.  Threads 1..K-1 of the workgroup each find one;
 // entries from K up to 255 are set to 0xffffffff.  C and cut are LDS arrays of 256 entries; the caller
 // synchronises before and after.
+// The cut key between two centres ca < cb.
+__device__ __forceinline__ u32 cut_between(float ca, float cb) {
+    const double a = (double)ca, b = (double)cb;
+    auto reaches = [&](u32 key) { const double x = (double)val_of(key); return fabs(b - x) < fabs(x - a); };
+    u32 lo = key_of(ca) + 1u, hi = key_of(cb);            // invariant: hi reaches, nothing below lo does
+    if (lo > hi) lo = hi;
+    const u32 mk = min(max(key_of((float)(0.5 * (a + b))), lo), hi);
+    const u32 p_hi = hi - mk > 2u ? mk + 2u : hi, p_lo = mk - lo > 2u ? mk - 2u : lo;
+    if (reaches(p_hi)) {
+        hi = p_hi;
+        if (p_lo < hi) { if (reaches(p_lo)) hi = p_lo; else lo = p_lo + 1u; }
+    } else {
+        lo = p_hi + 1u;
+    }
+    while (lo < hi) {
+        const u32 mid = lo + ((hi - lo) >> 1);
+        if (reaches(mid)) hi = mid; else lo = mid + 1u;
+    }
+    return hi;
+}
 __device__ __forceinline__ u32 cut_key(const float *C, u32 K, u32 k) {
-    u32 res = 0xffffffffu;
     u32 j = k;
     while (j < K && !(C[j - 1u] < C[j])) ++j;
-    if (j < K) {
-        const double a = (double)C[j - 1u], b = (double)C[j];
-        auto reaches = [&](u32 key) { const double x = (double)val_of(key); return fabs(b - x) < fabs(x - a); };
-        u32 lo = key_of(C[j - 1u]) + 1u, hi = key_of(C[j]);               // invariant: hi reaches, nothing below lo does
-        if (lo > hi) lo = hi;
-        const u32 mk = min(max(key_of((float)(0.5 * (a + b))), lo), hi);
-        const u32 p_hi = hi - mk > 2u ? mk + 2u : hi, p_lo = mk - lo > 2u ? mk - 2u : lo;
-        if (reaches(p_hi)) {
-            hi = p_hi;
-            if (p_lo < hi) { if (reaches(p_lo)) hi = p_lo; else lo = p_lo + 1u; }
-        } else {
-            lo = p_hi + 1u;
-        }
-        while (lo < hi) {
-            const u32 mid = lo + ((hi - lo) >> 1);
-            if (reaches(mid)) hi = mid; else lo = mid + 1u;
-        }
-        res = hi;
-    }
-    return res;
+    return j < K ? cut_between(C[j - 1u], C[j]) : 0xffffffffu;
 }
 __device__ __forceinline__ void compute_cut_keys(const float *C, int K, u32 *cut) {
     const u32 k = threadIdx.x;

@@ -1,8 +1,8 @@
-// Tensors of at most EXCP_SMALL_ELEMS elements: Alg. 1 in two launches instead of some twenty-five, beside which a group's larger
+// Tensors of at most EXCP_SMALL_ELEMS elements: Alg. 1 in one launch or two instead of some twenty-five, beside which a group's larger
 // tensors go their way.  A call about such tensors moves a few hundred KB; what it costs is launches, and inside them chains of dependent steps
-// with a wave or two at work.  Here a workgroup holds a whole tensor in registers (k_small_front: statistics, masks,
-// compaction, header), and then one holds a whole survivor stream (k_small_codes: initial centres, Lloyd iterations,
-// codes, and for the residuals W_hat), everything they look up in LDS.  (us a call, before and now: a norm vector of 4096
+// with a wave or two at work.  Here a workgroup holds a whole tensor in registers (small_front: statistics, masks,
+// compaction, header), and then one holds a whole survivor stream (small_codes: initial centres, Lloyd iterations,
+// codes, and for the residuals W_hat), everything they look up in LDS.  Of few tensors a workgroup does both, for its stream.  (us a call, before and now: a norm vector of 4096
 // elements 169 / 61, 1000 of them 1524 / 348, 8 bits 3814 / 477; 1000 tensors of 8192 elements, all kept, 1924 / 876; 8192
 // residuals of a sign-like update, 337 / 141.)
 //
@@ -17,26 +17,51 @@ constexpr u32 BATCHES = EXCP_SMALL_ELEMS / 64;
 
 // ---------------------------------------------------------------- statistics, masks, compaction, header
 // Element (j * SM_WAVES + wave) * 64 + lane is the thread's j-th, so a ballot is a bitmap word.
-__global__ __launch_bounds__(SM) void k_small_front(Workspace w, GroupParams g, TDesc one, u32 single) {
-    __shared__ u32 hist[2048];
-    __shared__ u64 bins[EXCP_ABSM_BINS], s_L, s_H;
-    __shared__ u64 s_bw[BATCHES], s_bo[BATCHES];
-    __shared__ u32 s_at[BATCHES + 1], s_obits[EXCP_SMALL_ELEMS / 32];     // survivors before a batch (moment survivors << 16); M_o by rank
-    __shared__ u32 s_wave[SM_WAVES], s_pick[2], s_nf, s_med;
-    __shared__ float s_tw, s_ro, s_mean;
-    __shared__ double s_abs;
-    const u32 t = blockIdx.x, tid = threadIdx.x, lane = tid & 63u;
-    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-    if (single && tid == 0) w.desc[0] = one;
-    const float *pW, *pP, *pM, *pV;
+struct SmallTensor {
+    const float *W, *Wp, *m, *v;
+    float *W_out;
     unsigned char *blob;
     u64 blob_cap, elem_off;
     u32 n, rec;
-    if (single) { pW = one.W; pP = one.Wp; pM = one.m; pV = one.v; n = (u32)one.n; blob = one.blob; blob_cap = one.blob_cap; elem_off = one.elem_off; rec = one.rec; }
-    else { const TDesc &D = w.desc[t]; pW = D.W; pP = D.Wp; pM = D.m; pV = D.v; n = (u32)D.n; blob = D.blob; blob_cap = D.blob_cap; elem_off = D.elem_off; rec = D.rec; }
-    const u32 wt = excp_wtype(g.flags);
+};
+__device__ __forceinline__ SmallTensor small_tensor(const TDesc &D) {
+    return {D.W, D.Wp, D.m, D.v, D.W_out, D.blob, D.blob_cap, D.elem_off, (u32)D.n, D.rec};
+}
+struct FrontShared {
+    u32 hist[2048];
+    u64 bins[EXCP_ABSM_BINS], L, H;
+    u64 bw[BATCHES], bo[BATCHES];
+    u32 at[BATCHES + 1], obits[EXCP_SMALL_ELEMS / 32];     // survivors before a batch (moment survivors << 16); M_o by rank
+    u32 wave[SM_WAVES], pick[2], nf, med;
+    float tw, ro, mean;
+    double abs;
+};
+// What a thread knows of its elements afterwards: residuals, moments, and the two bitmaps' words of their batches.
+struct FrontValues { float d[PER], m[PER], v[PER]; u64 bw[PER], bo[PER]; };
+// Where the blob's sections are, and whether there is one.
+struct SmallLayout { u64 off_bw, off_bo, off_cw, off_cm, off_cv, bytes; u32 n_w, n_o; int status; };
+__device__ __forceinline__ SmallLayout small_layout(const FrontShared &F, const SmallTensor &D, const GroupParams &g) {
+    SmallLayout s;
+    const u64 nb = (u64)g.nbits;
+    s.n_w = F.at[BATCHES] & 0xffffu; s.n_o = F.at[BATCHES] >> 16;
+    s.off_bw = EXCP_HEADER + excp_books_bytes((u32)g.nbits);
+    s.off_bo = s.off_bw + excp_pad16(8ull * excp_words(D.n));
+    s.off_cw = s.off_bo + excp_pad16(8ull * excp_words(s.n_w));
+    s.off_cm = s.off_cw + excp_pad16(8ull * excp_words(s.n_w * nb));
+    s.off_cv = s.off_cm + excp_pad16(8ull * excp_words(s.n_o * nb));
+    s.bytes = s.off_cv + excp_pad16(8ull * excp_words(s.n_o * nb));
+    s.status = F.nf ? -3 : (s.bytes > D.blob_cap ? -2 : 0);
+    return s;
+}
 
-    float d[PER], mv[PER], vv[PER];
+__device__ __forceinline__ void small_front(const SmallTensor &D, const GroupParams &g, FrontShared &F, FrontValues &X) {
+    const u32 tid = threadIdx.x, lane = tid & 63u, n = D.n;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    u32 *hist = F.hist, *s_at = F.at, *s_wave = F.wave, *s_pick = F.pick;
+    u64 *bins = F.bins, *s_bw = F.bw, *s_bo = F.bo;
+    float (&d)[PER] = X.d, (&mv)[PER] = X.m, (&vv)[PER] = X.v;
+    u64 (&bw)[PER] = X.bw, (&bo)[PER] = X.bo;
+    const u32 wt = excp_wtype(g.flags);
     u32 key[PER];
     {
         float a[PER], p[PER];
@@ -44,8 +69,8 @@ __global__ __launch_bounds__(SM) void k_small_front(Workspace w, GroupParams g, 
         for (u32 j = 0; j < PER; ++j) {
             const u32 e = (j * SM_WAVES + wave) * 64u + lane;
             const bool ok = e < n;
-            a[j] = ok ? load_weight(pW, e, wt) : 0.f; p[j] = ok ? load_weight(pP, e, wt) : 0.f;
-            mv[j] = ok ? pM[e] : 0.f; vv[j] = ok ? pV[e] : 1.f;
+            a[j] = ok ? load_weight(D.W, e, wt) : 0.f; p[j] = ok ? load_weight(D.Wp, e, wt) : 0.f;
+            mv[j] = ok ? D.m[e] : 0.f; vv[j] = ok ? D.v[e] : 1.f;
         }
 #pragma unroll
         for (u32 j = 0; j < PER; ++j) {
@@ -63,9 +88,9 @@ __global__ __launch_bounds__(SM) void k_small_front(Workspace w, GroupParams g, 
         if (mb >= 0x7f800000u) ++nf; else mmax = max(mmax, mb);
     }
     for (u32 i = tid; i < 2048u; i += SM) hist[i] = 0;
-    if (tid < EXCP_SMALL_ELEMS / 32u) s_obits[tid] = 0;
+    if (tid < EXCP_SMALL_ELEMS / 32u) F.obits[tid] = 0;
     if (tid < EXCP_ABSM_BINS) bins[tid] = 0;
-    if (tid == 0) { s_L = 0; s_H = 0; s_nf = 0; s_pick[0] = 0; }
+    if (tid == 0) { F.L = 0; F.H = 0; F.nf = 0; s_pick[0] = 0; }
     mmax = wave_max_u32(mmax);
     if (lane == 0u) s_wave[wave] = mmax;
     __syncthreads();
@@ -89,7 +114,7 @@ __global__ __launch_bounds__(SM) void k_small_front(Workspace w, GroupParams g, 
         const u32 hi32 = (u32)(units * 2.3283064365386963e-10), lo32 = (u32)(units - (double)hi32 * 4294967296.0);
         const u64 L = wave_sum_u64(lo32), H = wave_sum_u64(hi32);
         nf = wave_sum_u32(nf);
-        if (lane == 0u) { atomicAdd(&s_L, L); atomicAdd(&s_H, H); if (nf) atomicAdd(&s_nf, nf); }
+        if (lane == 0u) { atomicAdd(&F.L, L); atomicAdd(&F.H, H); if (nf) atomicAdd(&F.nf, nf); }
         // the lower median of |d|: 11 + 10 + 10 key bits
         u32 prefix = 0, rank = n ? (n - 1u) >> 1 : 0u;
 #pragma unroll
@@ -116,23 +141,22 @@ __global__ __launch_bounds__(SM) void k_small_front(Workspace w, GroupParams g, 
             prefix = (prefix << width) | s_pick[0]; rank = s_pick[1];
         }
         if (tid == 0) {
-            const u64 lo64 = s_L + (s_H << 32), hi64 = (s_H >> 32) + (lo64 < s_L ? 1ull : 0ull);
+            const u64 lo64 = F.L + (F.H << 32), hi64 = (F.H >> 32) + (lo64 < F.L ? 1ull : 0ull);
             const u64 piece[3] = {lo64 & 0xffffffffull, lo64 >> 32, hi64};
 #pragma unroll
             for (u32 q = 0; q < 3u; ++q) { const u32 p = B + 32u * q; if (piece[q]) bins[p >> 3] += piece[q] << (p & 7u); }
             const double sum = n ? signed_bins_to_double(bins) : 0.0;
-            s_abs = sum;
-            s_mean = n ? (float)(sum / (double)n) : 0.f;
-            s_ro = __fmul_rn(g.beta, s_mean);
-            s_tw = n ? __fmul_rn(g.alpha, u2f(prefix)) : 0.f;
-            s_med = n ? prefix : 0u;
+            F.abs = sum;
+            F.mean = n ? (float)(sum / (double)n) : 0.f;
+            F.ro = __fmul_rn(g.beta, F.mean);
+            F.tw = n ? __fmul_rn(g.alpha, u2f(prefix)) : 0.f;
+            F.med = n ? prefix : 0u;
         }
     }
     __syncthreads();
-    const float t_w = s_tw, r_o = s_ro;
+    const float t_w = F.tw, r_o = F.ro;
     const float T = t_w * t_w, T_keep = T * 1.00001f, T_drop = T * 0.99999f;
     const bool T_ok = __builtin_amdgcn_classf(T, 0x100);
-    u64 bw[PER], bo[PER];
 #pragma unroll
     for (u32 j = 0; j < PER; ++j) {
         const u32 b = j * SM_WAVES + wave, left = n > b * 64u ? n - b * 64u : 0u;
@@ -167,56 +191,68 @@ __global__ __launch_bounds__(SM) void k_small_front(Workspace w, GroupParams g, 
     }
     if (tid == 0) { u32 all = 0; for (u32 q = 0; q < BATCHES / 64u; ++q) all += s_wave[q]; s_at[BATCHES] = all; }
     __syncthreads();
-    const u32 n_w = s_at[BATCHES] & 0xffffu, n_o = s_at[BATCHES] >> 16;
-    float *xw = w.xw + elem_off, *xm = w.xm + elem_off, *xv = w.xv + elem_off;
+}
+
+// The bitmaps, the header and the record.  (The record's objectives are written by the workgroups that know them.)
+__device__ __forceinline__ void small_outputs(const Workspace &w, const SmallTensor &D, const GroupParams &g, const SmallLayout &s, FrontShared &F, const FrontValues &X) {
+    const u32 tid = threadIdx.x;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
 #pragma unroll
     for (u32 j = 0; j < PER; ++j) {
-        const u32 at = s_at[j * SM_WAVES + wave];
-        if (__builtin_amdgcn_inverse_ballot_w64(bw[j])) {
-            const u32 rk = (at & 0xffffu) + lanes_below(bw[j]);
-            xw[rk] = d[j];
-            if (__builtin_amdgcn_inverse_ballot_w64(bo[j])) {
-                const u32 ro = (at >> 16) + lanes_below(bo[j]);
-                xm[ro] = mv[j]; xv[ro] = vv[j];
-                atomicOr(&s_obits[rk >> 5], 1u << (rk & 31u));
-            }
+        if (__builtin_amdgcn_inverse_ballot_w64(X.bo[j])) {
+            const u32 rk = (F.at[j * SM_WAVES + wave] & 0xffffu) + lanes_below(X.bw[j]);
+            atomicOr(&F.obits[rk >> 5], 1u << (rk & 31u));
         }
     }
-    const u64 off_bw = EXCP_HEADER + excp_books_bytes((u32)g.nbits);
     {
-        const u32 nwords = (u32)excp_words(n), padded = nwords + (nwords & 1u);
-        if (tid < padded) ((u64 *)(blob + off_bw))[tid] = tid < BATCHES ? s_bw[tid] : 0ull;      // (padded <= BATCHES: it is even)
+        const u32 nwords = (u32)excp_words(D.n), padded = nwords + (nwords & 1u);
+        if (tid < padded) ((u64 *)(D.blob + s.off_bw))[tid] = tid < BATCHES ? F.bw[tid] : 0ull;      // (padded <= BATCHES: it is even)
     }
     __syncthreads();
-    const u64 off_bo = off_bw + excp_pad16(8ull * excp_words(n));
     {
-        const u32 nwo = (u32)excp_words(n_w), padded = nwo + (nwo & 1u);
-        const u64 cap_words = blob_cap > off_bo ? (blob_cap - off_bo) >> 3 : 0ull;
-        if (tid < padded && tid < cap_words) ((u64 *)(blob + off_bo))[tid] = (u64)s_obits[2u * tid] | (u64)s_obits[2u * tid + 1u] << 32;
+        const u32 nwo = (u32)excp_words(s.n_w), padded = nwo + (nwo & 1u);
+        const u64 cap_words = D.blob_cap > s.off_bo ? (D.blob_cap - s.off_bo) >> 3 : 0ull;
+        if (tid < padded && tid < cap_words) ((u64 *)(D.blob + s.off_bo))[tid] = (u64)F.obits[2u * tid] | (u64)F.obits[2u * tid + 1u] << 32;
     }
     if (tid != 0) return;
-    TState &S = w.st[t];
-    const u64 nb = (u64)g.nbits;
-    u64 off = off_bo;
-    S.off_bo = off; off += excp_pad16(8ull * excp_words(n_w));
-    S.off_cw = off; off += excp_pad16(8ull * excp_words(n_w * nb));
-    S.off_cm = off; off += excp_pad16(8ull * excp_words(n_o * nb));
-    S.off_cv = off; off += excp_pad16(8ull * excp_words(n_o * nb));
-    S.n_w = n_w; S.n_o = n_o; S.blob_bytes = off;
-    S.status = s_nf ? -3 : (off > blob_cap ? -2 : 0);
-    u32 *h = (u32 *)blob;
-    u64 *h64 = (u64 *)blob;
-    float *hf = (float *)blob;
+    u32 *h = (u32 *)D.blob;
+    u64 *h64 = (u64 *)D.blob;
+    float *hf = (float *)D.blob;
+    const float r_o = D.n ? F.ro : 0.f;
     h[0] = EXCP_MAGIC; h[1] = EXCP_VERSION; h[2] = (u32)g.nbits; h[3] = g.flags;
-    h64[2] = n; h64[3] = n_w; h64[4] = n_o;
-    hf[10] = g.alpha; hf[11] = g.beta; hf[12] = u2f(s_med); hf[13] = s_mean;
-    hf[14] = t_w; hf[15] = n ? r_o : 0.f;
-    h64[8] = off;
+    h64[2] = D.n; h64[3] = s.n_w; h64[4] = s.n_o;
+    hf[10] = g.alpha; hf[11] = g.beta; hf[12] = u2f(F.med); hf[13] = F.mean;
+    hf[14] = F.tw; hf[15] = r_o;
+    h64[8] = s.bytes;
     h[18] = (u32)g.iters; h[19] = 0u;
-    HostRec R{};
-    R.n = n; R.n_w = n_w; R.n_o = n_o; R.blob_bytes = off; R.nonfinite = s_nf; R.abs_sum = s_abs;
-    R.med = u2f(s_med); R.mean32 = s_mean; R.t_w = t_w; R.r_o = n ? r_o : 0.f; R.status = S.status;
-    w.rec_dev[w.rec_base + rec] = R;
+    HostRec &R = w.rec_dev[w.rec_base + D.rec];
+    R.n = D.n; R.n_w = s.n_w; R.n_o = s.n_o; R.blob_bytes = s.bytes; R.nonfinite = F.nf; R.abs_sum = F.abs;
+    R.med = u2f(F.med); R.mean32 = F.mean; R.t_w = F.tw; R.r_o = r_o; R.status = s.status; R.pad = 0;
+}
+
+// A stream's survivors to their places in `to`.
+__device__ __forceinline__ void small_compact(const FrontShared &F, const u64 (&words)[PER], const float (&x)[PER], u32 shift, float *to) {
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+#pragma unroll
+    for (u32 j = 0; j < PER; ++j)
+        if (__builtin_amdgcn_inverse_ballot_w64(words[j])) to[(F.at[j * SM_WAVES + wave] >> shift & 0xffffu) + lanes_below(words[j])] = x[j];
+}
+
+__global__ __launch_bounds__(SM) void k_small_front(Workspace w, GroupParams g) {
+    __shared__ FrontShared F;
+    const u32 t = blockIdx.x;
+    const SmallTensor D = small_tensor(w.desc[t]);
+    FrontValues X;
+    small_front(D, g, F, X);
+    const SmallLayout s = small_layout(F, D, g);
+    small_compact(F, X.bw, X.d, 0u, w.xw + D.elem_off);
+    small_compact(F, X.bo, X.m, 16u, w.xm + D.elem_off);
+    small_compact(F, X.bo, X.v, 16u, w.xv + D.elem_off);
+    small_outputs(w, D, g, s, F, X);
+    if (threadIdx.x != 0) return;
+    TState &S = w.st[t];
+    S.off_bo = s.off_bo; S.off_cw = s.off_cw; S.off_cm = s.off_cm; S.off_cv = s.off_cv;
+    S.n_w = s.n_w; S.n_o = s.n_o; S.blob_bytes = s.bytes; S.status = s.status;
 }
 
 // ---------------------------------------------------------------- codebook, codes, W_hat
@@ -279,21 +315,15 @@ __device__ __forceinline__ void sort_keys(u32 *a, u32 len) {
     __syncthreads();
 }
 
+// One stream of `len` values, of which the thread holds every SM-th: centres, codes into `out`, and of the residuals (which = 0) W_hat by the
+// keep bitmap at `keep`.  `x`: the stream's place in the survivors' area, `there`: it has been written.
 template <bool ONE_WAVE>                                  // up to 63 centres: one wave's work
-__global__ __launch_bounds__(SM) void k_small_codes(Workspace w, GroupParams g) {
-    __shared__ SmallShared A;
-    const u32 t = blockIdx.x / 3u, which = blockIdx.x % 3u, tid = threadIdx.x, lane = tid & 63u;
+__device__ __forceinline__ void small_codes(const Workspace &w, const GroupParams &g, SmallShared &A, const SmallTensor &D, u32 which, bool good, u32 len,
+                                            const float (&v)[PER], float *x, bool there, u64 *out, const u64 *keep) {
+    const u32 tid = threadIdx.x, lane = tid & 63u;
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-    const TDesc &D = w.desc[t];
-    const TState &T = w.st[t];
     const u32 K = (u32)g.K, nbits = (u32)g.nbits, E = 1u << nbits;
-    const bool good = T.status == 0;
-    const u32 len = good ? (u32)(which == 0u ? T.n_w : T.n_o) : 0u;
-    const float *x = (which == 0u ? w.xw : (which == 1u ? w.xm : w.xv)) + D.elem_off;
     u32 kp2 = 1; while (kp2 < K) kp2 <<= 1;
-    float v[PER];
-#pragma unroll
-    for (u32 j = 0; j < PER; ++j) v[j] = j * SM + tid < len ? x[j * SM + tid] : 0.f;
     for (u32 i = tid; i < EXCP_SMALL_ELEMS / 4u + 2u; i += SM) A.pack[i] = 0;
     if (tid <= EXCP_MAX_K) { A.cut[tid] = 0xffffffffu; A.C[tid] = 0.f; }
     double obj = 0.0;
@@ -414,50 +444,96 @@ __global__ __launch_bounds__(SM) void k_small_codes(Workspace w, GroupParams g) 
             }
             A.C[rank] = c;
         };
-        if (!wide) {
-            if (tid == 0) { A.above[K] = 0; A.n_above[K] = 0; A.above[0] = A.before[CELLS]; A.n_above[0] = len; }
-            auto sync = [&]() { if (ONE_WAVE) wave_lds_fence(); else __syncthreads(); };
-            if (!ONE_WAVE || wave == 0u) {
+        // The sum and number of the values from a cut key up: those of the higher cells, and the cell's own one by one.
+        auto above_cut = [&](u32 cut, __int128 &sum, u32 &cnt) {
+            sum = 0; cnt = 0;
+            if (cut > kmax) return;
+            if (cut <= kmin) { sum = A.before[CELLS]; cnt = len; return; }
+            const u32 c = cell_of_key(cut), b0 = A.begin[c], b1 = A.begin[c + 1u];
+            u64 lo = 0, hi = 0;
+            sum = A.before[CELLS] - A.before[c + 1u]; cnt = len - b1;
+            for (u32 q = b0; q < b1; q += 4u) {
+                u32 key[4];
+#pragma unroll
+                for (u32 e = 0; e < 4u; ++e) key[e] = A.sorted[min(q + e, b1 - 1u)];
+#pragma unroll
+                for (u32 e = 0; e < 4u; ++e)
+                    if (q + e < b1 && key[e] >= cut) { const CellSum h = halves(f2u(val_of(key[e])), base); lo += h.lo; hi += h.hi; ++cnt; }
+            }
+            sum += joined(lo, hi);
+        };
+        if (!wide && ONE_WAVE) {
+            // A lane a centre, and what neighbours tell each other goes through registers: what bounds an iteration is its chain of
+            // dependent steps, and a trip through LDS is as long as thirty instructions.
+            if (wave == 0u) {
+                float own = A.C[min(tid, K - 1u)];
                 for (u32 i = 0;; ++i) {
+                    const float below = lane_below_f32(own);
                     u32 cut = 0;
-                    if (centre && tid) { cut = cut_key(A.C, K, tid); A.cut[tid] = cut; }
-                    if (i == (u32)g.iters) break;
-                    if (!ONE_WAVE && wave * 64u >= K) { sync(); sync(); sync(); sync(); continue; }
-                    // sum and number of the values from the cut key up: those of the higher cells, and the cell's own one by one
-                    __int128 sum = 0;
-                    u32 cnt = 0;
-                    u64 lo = 0, hi = 0;
-                    if (centre && tid && cut <= kmax) {
-                        if (cut <= kmin) {
-                            sum = A.before[CELLS]; cnt = len;
-                        } else {
-                            const u32 c = cell_of_key(cut), b0 = A.begin[c], b1 = A.begin[c + 1u];
-                            sum = A.before[CELLS] - A.before[c + 1u]; cnt = len - b1;
-                            for (u32 q = b0; q < b1; ++q) {
-                                const u32 key = A.sorted[q];
-                                if (key >= cut) { const CellSum h = halves(f2u(val_of(key)), base); lo += h.lo; hi += h.hi; ++cnt; }
-                            }
-                        }
+                    if (__all(!centre || tid == 0u || below < own)) {
+                        if (centre && tid) cut = cut_between(below, own);
+                    } else {                               // equal centres: the lowest of a run takes everything
+                        if (centre) A.C[tid] = own;
+                        wave_lds_fence();
+                        if (centre && tid) cut = cut_key(A.C, K, tid);
+                        wave_lds_fence();
                     }
-                    if (centre && tid) { A.above[tid] = sum + joined(lo, hi); A.n_above[tid] = cnt; }
-                    sync();
-                    float c = 0.f;
-                    if (centre) {
-                        const u32 m = A.n_above[tid] - A.n_above[tid + 1u];
-                        c = m ? (float)(i128_to_double(A.above[tid] - A.above[tid + 1u], base) / (double)m) : A.C[tid];
-                        A.fresh[tid] = c;
+                    if (i == (u32)g.iters) {
+                        if (centre) A.C[tid] = own;
+                        if (centre && tid) A.cut[tid] = cut;
+                        break;
                     }
-                    sync();
-                    bool unsorted = tid + 1u < K && !(c <= A.fresh[tid + 1u]);
-                    if (ONE_WAVE) unsorted = __any(unsorted);
-                    else { if (unsorted) A.disorder = 1u; sync(); unsorted = A.disorder != 0u; }
-                    put_back(c, unsorted);
-                    sync();
-                    if (!ONE_WAVE && tid == 0) A.disorder = 0u;
+                    __int128 sum = tid == 0u ? A.before[CELLS] : (__int128)0;
+                    u32 cnt = tid == 0u ? len : 0u;
+                    if (centre && tid) above_cut(cut, sum, cnt);
+                    const __int128 next = lane_above_i128(sum);            // (of lane K: nothing)
+                    const u32 m = cnt - lane_above_u32(cnt);
+                    float c = own;
+                    if (centre && m) c = (float)(i128_to_double(sum - next, base) / (double)m);
+                    const float above = lane_above_f32(c);
+                    if (__any(tid + 1u < K && !(c <= above))) {
+                        if (centre) A.fresh[tid] = c;
+                        wave_lds_fence();
+                        put_back(c, true);
+                        wave_lds_fence();
+                        c = A.C[min(tid, K - 1u)];
+                    }
+                    own = c;
                 }
+            }
+        } else if (!wide) {
+            if (tid == 0) { A.above[K] = 0; A.n_above[K] = 0; A.above[0] = A.before[CELLS]; A.n_above[0] = len; }
+            for (u32 i = 0;; ++i) {
+                u32 cut = 0;
+                if (centre && tid) { cut = cut_key(A.C, K, tid); A.cut[tid] = cut; }
+                if (i == (u32)g.iters) break;
+                if (wave * 64u >= K) { __syncthreads(); __syncthreads(); __syncthreads(); __syncthreads(); continue; }
+                if (centre && tid) {
+                    __int128 sum;
+                    u32 cnt;
+                    above_cut(cut, sum, cnt);
+                    A.above[tid] = sum; A.n_above[tid] = cnt;
+                }
+                __syncthreads();
+                float c = 0.f;
+                if (centre) {
+                    const u32 m = A.n_above[tid] - A.n_above[tid + 1u];
+                    c = m ? (float)(i128_to_double(A.above[tid] - A.above[tid + 1u], base) / (double)m) : A.C[tid];
+                    A.fresh[tid] = c;
+                }
+                __syncthreads();
+                if (tid + 1u < K && !(c <= A.fresh[tid + 1u])) A.disorder = 1u;
+                __syncthreads();
+                put_back(c, A.disorder != 0u);
+                __syncthreads();
+                if (tid == 0) A.disorder = 0u;
             }
         } else {
             // sixty binary orders and more: every value goes to its centre's bins in every iteration
+            if (!there) {
+#pragma unroll
+                for (u32 j = 0; j < PER; ++j) if (j * SM + tid < len) x[j * SM + tid] = v[j];      // (read back below by the same workgroup)
+            }
             u64 *acc = (u64 *)A.before;                   // [bin][K], and [K] numbers: runs on into `sorted`, which is done with
             static_assert(sizeof(A.before) + sizeof(A.sorted) >= (EXCP_ABSM_BINS + 1u) * EXCP_MAX_K * sizeof(u64), "bins of all centres");
             for (u32 i = 0;; ++i) {
@@ -505,22 +581,19 @@ __global__ __launch_bounds__(SM) void k_small_codes(Workspace w, GroupParams g) 
         if (lane == 0u) A.wave_obj[wave] = obj;
         __syncthreads();
         const u32 nwords = (u32)excp_words((u64)len * nbits), padded = nwords + (nwords & 1u);
-        u64 *out = (u64 *)(D.blob + (which == 0u ? T.off_cw : (which == 1u ? T.off_cm : T.off_cv)));
         for (u32 i = tid; i < padded; i += SM) out[i] = i < nwords ? (u64)A.pack[2u * i] | (u64)A.pack[2u * i + 1u] << 32 : 0ull;
-        if (tid == 0) {
-            obj = 0.0;
-            for (u32 q = 0; q < SM_WAVES; ++q) obj += A.wave_obj[q];
-            w.rec_dev[w.rec_base + D.rec].obj[which] = obj;
-        }
+        obj = 0.0;
+        if (tid == 0) for (u32 q = 0; q < SM_WAVES; ++q) obj += A.wave_obj[q];
     }
+    if (tid == 0) w.rec_dev[w.rec_base + D.rec].obj[which] = obj;
     float *books = (float *)(D.blob + EXCP_HEADER) + which * E;
     if (tid < E) books[tid] = tid && len ? A.C[tid - 1u] : 0.f;
     if (which != 0u || !good || D.W_out == nullptr) return;
     // W_hat: the previous weights, plus the centre where the residual was kept
-    const u32 n = (u32)D.n, wt = excp_wtype(g.flags);
+    const u32 n = D.n, wt = excp_wtype(g.flags);
     __syncthreads();
     if (tid < BATCHES) {
-        A.bits[tid] = tid < excp_words(n) ? ((const u64 *)(D.blob + EXCP_HEADER + excp_books_bytes(nbits)))[tid] : 0ull;
+        A.bits[tid] = tid < excp_words(n) ? keep[tid] : 0ull;
         const u32 c = (u32)__popcll(A.bits[tid]), incl = wave_incl_scan_u32(c);
         A.at[tid] = incl - c;
         if (lane == 63u) A.wave_cnt[wave] = incl;
@@ -549,12 +622,64 @@ __global__ __launch_bounds__(SM) void k_small_codes(Workspace w, GroupParams g) 
     }
 }
 
+template <bool ONE_WAVE>
+__global__ __launch_bounds__(SM) void k_small_codes(Workspace w, GroupParams g) {
+    __shared__ SmallShared A;
+    const u32 t = blockIdx.x / 3u, which = blockIdx.x % 3u, tid = threadIdx.x;
+    const SmallTensor D = small_tensor(w.desc[t]);
+    const TState &T = w.st[t];
+    const bool good = T.status == 0;
+    const u32 len = good ? (u32)(which == 0u ? T.n_w : T.n_o) : 0u;
+    float *x = (which == 0u ? w.xw : (which == 1u ? w.xm : w.xv)) + D.elem_off;
+    float v[PER];
+#pragma unroll
+    for (u32 j = 0; j < PER; ++j) v[j] = j * SM + tid < len ? x[j * SM + tid] : 0.f;
+    small_codes<ONE_WAVE>(w, g, A, D, which, good, len, v, x, true, (u64 *)(D.blob + (which == 0u ? T.off_cw : (which == 1u ? T.off_cm : T.off_cv))),
+                          (const u64 *)(D.blob + EXCP_HEADER + excp_books_bytes((u32)g.nbits)));
+}
+
+// Both in one launch, where there are no more streams than compute units: a workgroup a stream, each of which finds out about the
+// whole tensor for itself.  (A norm vector of 4096 elements: 14.7 and 28.1 us with what lies between them in two launches, 42 in one, 39
+// with the iterations' exchange through registers; the call 60.9 -> 57.0.)
+template <bool ONE_WAVE>
+__global__ __launch_bounds__(SM) void k_small_whole(Workspace w, GroupParams g, TDesc one, u32 single) {
+    __shared__ FrontShared F;
+    __shared__ SmallShared A;
+    const u32 t = blockIdx.x / 3u, which = blockIdx.x % 3u, tid = threadIdx.x;
+    const SmallTensor D = single ? small_tensor(one) : small_tensor(w.desc[t]);
+    float v[PER];
+    bool good;
+    u32 len;
+    u64 at;
+    {
+        FrontValues X;
+        small_front(D, g, F, X);
+        const SmallLayout s = small_layout(F, D, g);
+        good = s.status == 0;
+        len = good ? (which == 0u ? s.n_w : s.n_o) : 0u;
+        at = which == 0u ? s.off_cw : (which == 1u ? s.off_cm : s.off_cv);
+        float *to = (float *)A.sorted;
+        if (which == 0u) small_compact(F, X.bw, X.d, 0u, to);
+        else if (which == 1u) small_compact(F, X.bo, X.m, 16u, to);
+        else small_compact(F, X.bo, X.v, 16u, to);
+        if (which == 0u) small_outputs(w, D, g, s, F, X);
+        __syncthreads();
+#pragma unroll
+        for (u32 j = 0; j < PER; ++j) v[j] = j * SM + tid < len ? to[j * SM + tid] : 0.f;
+    }
+    small_codes<ONE_WAVE>(w, g, A, D, which, good, len, v, (which == 0u ? w.xw : (which == 1u ? w.xm : w.xv)) + D.elem_off, false, (u64 *)(D.blob + at), F.bw);
+}
+
 }  // namespace
 
-void launch_small_front(const Workspace &w, const GroupParams &g, const TDesc *single, hipStream_t s) {
-    hipLaunchKernelGGL(k_small_front, dim3(g.ntensors), dim3(SM), 0, s, w, g, single ? *single : TDesc{}, single ? 1u : 0u);
-}
-void launch_small_codes(const Workspace &w, const GroupParams &g, hipStream_t s) {
-    if (g.K <= 63) hipLaunchKernelGGL(k_small_codes<true>, dim3(3u * g.ntensors), dim3(SM), 0, s, w, g);
+void launch_small(const Workspace &w, const GroupParams &g, const TDesc *single, hipStream_t s) {
+    const bool few = g.K <= 63;
+    if (3u * g.ntensors <= (u32)w.cus) {
+        if (few) hipLaunchKernelGGL(k_small_whole<true>, dim3(3u * g.ntensors), dim3(SM), 0, s, w, g, single ? *single : TDesc{}, single ? 1u : 0u);
+        else hipLaunchKernelGGL(k_small_whole<false>, dim3(3u * g.ntensors), dim3(SM), 0, s, w, g, single ? *single : TDesc{}, single ? 1u : 0u);
+        return;
+    }
+    hipLaunchKernelGGL(k_small_front, dim3(g.ntensors), dim3(SM), 0, s, w, g);
+    if (few) hipLaunchKernelGGL(k_small_codes<true>, dim3(3u * g.ntensors), dim3(SM), 0, s, w, g);
     else hipLaunchKernelGGL(k_small_codes<false>, dim3(3u * g.ntensors), dim3(SM), 0, s, w, g);
 }
