@@ -13,7 +13,7 @@
 #define EXCP_THREADS     256
 #define EXCP_SMALL_ELEMS 8192u     // elements up to which a workgroup holds a tensor (k_small.hip)
 #define EXCP_SAMPLE_PARTS 16u      // workgroups that draw a tensor's sample of residuals
-#define EXCP_STATS_PER_CU 8u       // workgroups per compute unit of the statistics pass
+#define EXCP_STATS_PER_CU 64u      // workgroups per compute unit of the statistics pass, at most (excp_stats_grid)
 #define EXCP_ABSM_BINS   40        // u64 accumulators, 8 binary exponents apart, for the exact sum of |m|
 #define EXCP_MAX_K       255
 #define EXCP_KM_CELLS    4096u     // cells of the value -> bucket map (2048 per sign)
@@ -228,6 +228,15 @@ static inline u64 excp_cand_words(u64 group_elems, u32 group_tensors) { return g
 // every fourth list for a start, those filled and the others were found by failing there: 3 M elements 28.6 -> 18.5 us
 // for the pass, 16.8 M 41.2 -> 39.0 and 41.5 -> 37.4 for the select, whose waves share the lists out.)
 static __host__ __device__ inline u32 excp_cand_first(u32 workgroup, u32 lists) { return workgroup % lists; }
+
+// Workgroups of the statistics pass, each with a run of tiles: eight to a compute unit at least, and so many more, up to
+// EXCP_STATS_PER_CU, that a run is about six tiles.  Short runs lie close together at any time, as memory likes it (8, 16, 32, 64 to
+// a compute unit: 410M shape 854, 842, 832, 823 us, its weights in bf16 485, 477, 470, 461, four layers of the 7B shape 2314, 2300, 2310,
+// 2245), but a run that ends asks for places in its tensor's candidate lists (16.8 M elements 41, 43, 66, 125).
+static inline u32 excp_stats_grid(u32 ntiles, u32 cus) {
+    const u32 runs = ntiles / 6u, least = 8u * cus, most = EXCP_STATS_PER_CU * cus;
+    return runs < least ? least : (runs > most ? most : runs);
+}
 
 // Sub-tiles to a batch of the gather pass: as many as leave four batches to a compute unit, four at least, so that each of a
 // workgroup's waves has one, and EXCP_GATHER_SUBS at most.  (With 32 always, a 16.8 M-element tensor was 256 workgroups of eight
