@@ -871,8 +871,8 @@ __global__ __launch_bounds__(THREADS) void k_km_cells(Workspace w, GroupParams g
 // A centre: radix select inside the bucket that holds its rank, 11 bits a digit (the bits that the bucket's
 // smallest and largest key share are known and skipped), the digit's histogram scanned by the whole
 // workgroup.  Values that fit the workgroup's registers are read once.
-// (1024 threads for the residuals of 16-bit weights -- a bucket of tied values can be most of a stream -- and for
-// groups with a tensor of 2^28 elements; 256 otherwise: with 1024 for everybody the 14 000 workgroups of a 410M-shaped
+// (1024 threads for the residuals of 16-bit weights -- a bucket of tied values can be most of a stream -- for
+// groups with a tensor of 2^28 elements, whose buckets' repetitions have been counted as well (TIED), and for few large tensors; 256 otherwise: with 1024 for everybody the 14 000 workgroups of a 410M-shaped
 // checkpoint took 347 us instead of 167, and 22 instead of 33 for a 16.8 M-element tensor)
 //
 // The prefix sums turn the total of any run of buckets into one difference; the workgroup that makes them also decides
@@ -885,7 +885,7 @@ __device__ __forceinline__ u32 fine_info(const Workspace &w, const GroupParams &
 }
 constexpr u32 FINE_COST = 24;                             // a value of a cell, which sixteen lanes read, in SegState::work
 
-template <u32 INIT_THREADS>
+template <u32 INIT_THREADS, bool TIED>
 __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupParams g, u32 sel) {
     __shared__ __attribute__((aligned(16))) u32 hist[2048];
     __shared__ u32 s_wave[INIT_THREADS / 64], s_pick[2];
@@ -905,7 +905,7 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
             const u32 at = sidx * NBKT + tid, kn = w.km_min[at], kx = w.km_max[at], low = w.km_mag[at];
             const u32 b0 = w.km_begin[sidx * (NBKT + 1u) + tid], b1 = w.km_begin[sidx * (NBKT + 1u) + tid + 1u];
             // (of tied data: what is not a repetition of the bucket's first value; a bucket of one value is never cut)
-            const u32 most = b1 - b0 - (INIT_THREADS == 1024u ? w.km_dom[at] : 0u);
+            const u32 most = b1 - b0 - (TIED ? w.km_dom[at] : 0u);
             const bool any = kn <= kx;         // (an empty bucket has no extremes)
             const u32 a = f2u(val_of(kn)) & 0x7fffffffu, c = f2u(val_of(kx)) & 0x7fffffffu;
             // a border in a bucket with cells costs a cell, in another the bucket
@@ -969,7 +969,7 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
     // (k_km_cells moves values within a bucket: the first one is no longer the one that was counted where it has run.)
     const u32 info = g.fine && excp_fine_tensor(((const EXCP_CONSTANT TDesc *)(uintptr_t)(w.desc + sidx / 3u))->n)
                          ? ((const EXCP_CONSTANT u32 *)(uintptr_t)w.km_fine)[(u64)sidx * NBKT + b] : 0u;
-    if (INIT_THREADS == 1024u && !info && rank - w.km_less[(u64)sidx * NBKT + b] < w.km_dom[(u64)sidx * NBKT + b]) { if (tid == 0) *out = gptr(seg_part(w, sidx))[p0]; return; }
+    if (TIED && !info && rank - w.km_less[(u64)sidx * NBKT + b] < w.km_dom[(u64)sidx * NBKT + b]) { if (tid == 0) *out = gptr(seg_part(w, sidx))[p0]; return; }
     if (info) {                                           // the cell that holds the rank
         __shared__ u32 s_ends[2];                         // (not s_pick: a wave may still have to read the bucket from there)
         const u64 e = (u64)(sidx % 3u) * w.fine_stride + excp_fine_at(w.desc[sidx / 3u].elem_off, sidx / 3u, p0, b);
@@ -2166,11 +2166,17 @@ void launch_km_init(const Workspace &w, const GroupParams &g, hipStream_t s) {
     if (!g.ntensors) return;
     const u32 per = (u32)g.K + 1u;
     if (g.wide == 2u) {
-        hipLaunchKernelGGL(k_km_init<1024>, dim3(3 * g.ntensors * per), dim3(1024), 0, s, w, g, (u32)STREAMS_ALL);
+        hipLaunchKernelGGL((k_km_init<1024, true>), dim3(3 * g.ntensors * per), dim3(1024), 0, s, w, g, (u32)STREAMS_ALL);
     } else {
         const u32 sel = g.wide ? STREAMS_MV : STREAMS_ALL;
-        if (g.wide) hipLaunchKernelGGL(k_km_init<1024>, dim3(g.ntensors * per), dim3(1024), 0, s, w, g, (u32)STREAMS_W);
-        hipLaunchKernelGGL(k_km_init<256>, dim3(stream_count(g.ntensors, sel) * per), dim3(256), 0, s, w, g, sel);
+        if (g.wide) hipLaunchKernelGGL((k_km_init<1024, true>), dim3(g.ntensors * per), dim3(1024), 0, s, w, g, (u32)STREAMS_W);
+        // A workgroup reads a bucket, of which those of few large tensors hold a hundred thousand values: sixteen waves, if there are no
+        // more than eight workgroups to a compute unit and the tensors are of 2^24 elements on average (us with four waves / sixteen, 4 bits:
+        // one of 100 M elements 138 / 79, 40 M 61 / 33, four layers of the 7B shape 209 / 126, 8 x 16.8 M 46 / 38, 8 x 8 M 29 / 29, 20 x 3 M 22 / 40; 8 bits:
+        // 100 M 192 / 99, 40 M 80 / 65, but 8 x 16.8 M, 6144 workgroups, 120 / 269).
+        const u32 grid = stream_count(g.ntensors, sel) * per;
+        if (!g.fine && (u64)g.ntiles * EXCP_TILE >= (u64)g.ntensors << 24 && grid <= excp_grid(w, 8)) hipLaunchKernelGGL((k_km_init<1024, false>), dim3(grid), dim3(1024), 0, s, w, g, sel);
+        else hipLaunchKernelGGL((k_km_init<256, false>), dim3(grid), dim3(256), 0, s, w, g, sel);
     }
 }
 
