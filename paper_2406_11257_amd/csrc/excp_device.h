@@ -151,6 +151,7 @@ struct GroupParams {
     u32 unit_shift;             // log2 of the positions of a stream whose bucket counts share a row
     u32 fine;                   // the first `fine` tensors in order of size may have cells inside their buckets (k_km_cells)
     u32 fine_size;              // ... by the workgroups of size 0, 1 or 2
+    u32 fine_chunks;            // ... and the chunks of survivors up to which they do
     u64 largest;                // elements of the largest tensor
     u32 samples;                // values of a stream that its value -> bucket map is made from
 };
@@ -329,6 +330,24 @@ static inline bool excp_fine_group(u64 elems, u64 largest, u32 whole) {
     return elems <= EXCP_FINE_LARGEST && (whole == 0u || (whole * elems <= (u64)EXCP_FINE_CHUNKS * EXCP_CHUNK &&
                                                           largest + largest / 3u <= 256ull * excp_cells_most(excp_fine_size(largest))));
 }
+
+// And groups beyond that line, as above of tensors whose buckets fit, for which the iterations and initial centres gain more than cells cost:
+// 130 us with up to 63 centres, which 1.7 to 2.2 us a million elements are worth up to 54 M elements in tensors of 8 M, and 2.7 to 3.9
+// up to 38 M in smaller ones, 4 M at least; 150 to 1100 us with more centres.  (us a call without and with, 4 bits: 2 x 14 M 700 / 618,
+// 5 x 6 M 716 / 670, 4 x 10 M 840 / 783, 3 x 15 M 908 / 845, 2 x 25 M 957 / 929, but 10 x 4 M 864 / 873, 36 x 1 M 856 / 860, 3 x 20 M 1065 / 1084,
+// 20 x 3 M 1107 / 1202; 6 bits: 6 x 10 M 1131 / 1094, 20 x 3 M 1196 / 1258; 7 bits: 20 x 3 M 1408 / 1351, 5 x 20 M 1769 / 1736, 48 x 2.5 M 2387 / 2442;
+// 8 bits: 2 x 14 M 908 / 771, 36 x 1 M 1716 / 1130, 60 x 1 M 2581 / 1664, 5 x 20 M 2165 / 1838.)  Not where every element is kept.
+#define EXCP_CELLS_FEW  (36ull << 20)
+#define EXCP_CELLS_SOME (52ull << 20)
+#define EXCP_CELLS_MANY (100ull << 20)
+static inline bool excp_cells_group(u64 elems, u64 largest, u32 tensors, u32 K, u32 whole) {
+    if (excp_fine_group(elems, largest, whole)) return true;
+    if (whole != 0u || largest > EXCP_FINE_LARGEST) return false;
+    if (K >= 127u) return elems <= EXCP_CELLS_MANY;
+    return elems <= (elems >= (u64)tensors << 23 ? EXCP_CELLS_SOME : (elems >= (u64)tensors << 22 ? EXCP_CELLS_FEW : 0ull));
+}
+// Chunks of survivors up to which such a group keeps its cells: half the elements, and more of smaller groups.
+static inline u32 excp_cells_chunks(u64 elems) { return elems <= EXCP_CELLS_SOME ? EXCP_FINE_CHUNKS : 2u * EXCP_FINE_CHUNKS; }
 
 // Samples of a stream, from which its buckets are made: 32 to a bucket, whose sizes then differ by 18 %, or 64 and 12 % where
 // cells are made and a bucket sixty per cent above the average of the largest tensor, a third of it kept, would fill more than three

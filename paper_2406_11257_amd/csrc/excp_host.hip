@@ -599,13 +599,13 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         if (!raw) {
             p.together = lloyd_together(g, nbig) ? 1u : 0u;
             const u32 whole = (alpha == 0.f ? 1u : 0u) + (beta == 0.f && (alpha == 0.f || (flags & EXCP_FLAG_NO_W2M)) ? 2u : 0u);
-            const bool cells = p.together && !w16 && excp_fine_group(elems, largest, whole);
+            const bool cells = p.together && !w16 && excp_cells_group(elems, largest, nbig, (u32)K, whole);
             for (u32 q = 0; q < nbig; ++q) p.fine += cells && excp_fine_tensor(descs.h[g.first + q].n) ? 1u : 0u;
             p.alone_work = p.fine ? kAloneCells : (p.together ? kAloneTogether : (K < 63 ? kAloneFew : kAloneMany));
             for (u32 q = 0; q < nbig; ++q) p.slots += descs.h[g.first + q].acc_slot != EXCP_NO_SLOT ? 1u : 0u;
         }
         p.unit_shift = excp_unit_shift(elems, nbig, excp_gather_subs(g.ntiles, (u32)w.cus), (u32)w.cus, excp_count_rows(c->max_group, kMaxGroupTensors));
-        p.fine_size = excp_fine_size(largest); p.largest = largest;
+        p.fine_size = excp_fine_size(largest); p.fine_chunks = excp_cells_chunks(elems); p.largest = largest;
         p.samples = excp_samples(p.fine != 0u, largest);
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
         { StageTimer t(c, ST_LAYOUT); }                      // (made inside the mask scan and k_small_front: the span, one a group, is empty)

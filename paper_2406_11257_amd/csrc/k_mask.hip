@@ -435,7 +435,7 @@ __device__ __forceinline__ void layout(const Workspace &w, const GroupParams &g)
         run[0] += chunks;
         run[1] += (chunks + unit_chunks - 1u) / unit_chunks;
     }
-    if (tid == EXCP_THREADS - 1) { seg_chunk_begin[nseg] = total[0]; *w.chunk_total = total[0]; *w.lloyd_shared = 0u; *w.no_cells = total[0] > EXCP_FINE_CHUNKS ? 1u : 0u; }
+    if (tid == EXCP_THREADS - 1) { seg_chunk_begin[nseg] = total[0]; *w.chunk_total = total[0]; *w.lloyd_shared = 0u; *w.no_cells = total[0] > g.fine_chunks ? 1u : 0u; }
 }
 
 // (The workgroup that finds a tensor's totals draws a ticket; the last one goes on with the layout.)
