@@ -307,11 +307,10 @@ static __host__ __device__ inline u32 excp_cell_of_bits(const CellMap &M, u32 bi
 }
 // Tensors whose buckets may be worth cells (2^17 is a power of two because the host lists the tensors by powers of two), and
 // the largest ones whose buckets, a third of the values kept, nearly all fit a workgroup of k_km_cells in its three sizes.
-// A group of more elements in all goes without cells.  One tensor of more has buckets that do not fit (30 M elements, 4 bits, us a
-// call 751, 798 if it sets out for cells, 45 M 942 / 998, 60 M 1120 / 1168).  Of many tensors cells cost 2 to 4 us a million
-// elements, more than the 125 us that the iterations and initial centres gain (40 of 600 000: totals and cells 112 instead of 34 us,
-// iterations 57 instead of 151; 80 of 3 M: 1081 and 149, 64 and 253); a few tensors that fit would still gain above the
-// line (2 x 15 M 730 / 668, 3 x 15 M 914 / 865).  A group of 16-bit weights, whose few distinct residuals are shared out in any
+// A group of more elements in all goes without cells, but for what excp_cells_group adds.  One tensor of more has buckets that do not fit
+// (30 M elements, 4 bits, us a call 751, 798 if it sets out for cells, 45 M 942 / 998, 60 M 1120 / 1168).  Of many tensors cells cost 2 to 4 us
+// a million elements, more than the 125 us that the iterations and initial centres gain (40 of 600 000: totals and cells 112 instead of 34 us,
+// iterations 57 instead of 151; 80 of 3 M: 1081 and 149, 64 and 253).  A group of 16-bit weights, whose few distinct residuals are shared out in any
 // case, has none.
 static __host__ __device__ inline bool excp_fine_tensor(u64 n) { return n >= 1ull << 17; }
 #define EXCP_FINE_SMALL (1ull << 21)
