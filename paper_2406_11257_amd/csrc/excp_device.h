@@ -6,6 +6,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <algorithm>
 
 #define EXCP_TILE        4096u     // elements per tile of the full-tensor passes (256 threads x 16)
 #define EXCP_CHUNK       8192u     // survivors per chunk of the survivor passes
@@ -348,6 +349,41 @@ static inline bool excp_cells_group(u64 elems, u64 largest, u32 tensors, u32 K, 
 // Chunks of survivors up to which such a group keeps its cells: half the elements, and more of smaller groups.
 static inline u32 excp_cells_chunks(u64 elems) { return elems <= EXCP_CELLS_SOME ? EXCP_FINE_CHUNKS : 2u * EXCP_FINE_CHUNKS; }
 
+// Whether a group's small tensors (k_small.hip) take one launch, in which three workgroups a tensor, one to a stream, each read all of
+// its inputs, and that of the residuals writes W_hat.  Nothing makes that one wait for the others, which may begin much later (they need most of
+// a compute unit's LDS, and larger tensors may hold it), so W_hat must lie apart from everything that the launch reads: not over the
+// previous or the current weights of its own tensor, nor of another.  Otherwise, and where there are more streams than compute units, two
+// launches, the first of which reads all inputs before the second writes (a norm vector of 4096 elements 61 us a call, 57 in one).
+#define EXCP_SMALL_ONCE 128u
+static inline bool excp_small_once(const TDesc *d, u32 count, u32 cus, u32 weight_bytes) {
+    if (3u * count > cus || count > EXCP_SMALL_ONCE) return false;
+    struct Range { uintptr_t lo, hi; } out[EXCP_SMALL_ONCE];
+    u32 outs = 0;
+    uintptr_t lo = UINTPTR_MAX, hi = 0;                   // all outputs lie between
+    for (u32 q = 0; q < count; ++q) {
+        if (!d[q].W_out || !d[q].n) continue;
+        const Range r{(uintptr_t)d[q].W_out, (uintptr_t)d[q].W_out + (uintptr_t)d[q].n * weight_bytes};
+        lo = std::min(lo, r.lo); hi = std::max(hi, r.hi);
+        out[outs++] = r;
+    }
+    bool sorted = false;
+    for (u32 q = 0; q < count; ++q) {
+        const void *in[4] = {d[q].Wp, d[q].W, d[q].m, d[q].v};
+        for (u32 k = 0; k < 4u && d[q].n; ++k) {
+            const uintptr_t a = (uintptr_t)in[k], b = a + (uintptr_t)d[q].n * (k < 2u ? weight_bytes : 4u);
+            if (a >= hi || b <= lo) continue;
+            if (!sorted) {                                // by their beginnings; `hi`: the furthest end up to here
+                std::sort(out, out + outs, [](const Range &x, const Range &y) { return x.lo < y.lo; });
+                for (u32 i = 1; i < outs; ++i) out[i].hi = std::max(out[i].hi, out[i - 1u].hi);
+                sorted = true;
+            }
+            const Range *end = std::lower_bound(out, out + outs, b, [](const Range &x, uintptr_t y) { return x.lo < y; });
+            if (end != out && end[-1].hi > a) return false;
+        }
+    }
+    return true;
+}
+
 // Samples of a stream, from which its buckets are made: 32 to a bucket, whose sizes then differ by 18 %, or 64 and 12 % where
 // cells are made and a bucket sixty per cent above the average of the largest tensor, a third of it kept, would fill more than three
 // quarters of a workgroup (from 14.7 M elements on; of 25 M a few buckets did not fit otherwise).  More samples cost more to draw, and of
@@ -386,7 +422,7 @@ struct SideStream { hipStream_t stream; hipEvent_t fork, join; };
 void launch_km_iter(const Workspace &w, const GroupParams &g, hipStream_t s, const SideStream &side);
 void launch_bitmap_o(const Workspace &w, const GroupParams &g, hipStream_t s);
 void launch_assign_pack(const Workspace &w, const GroupParams &g, hipStream_t s);
-void launch_small(const Workspace &w, const GroupParams &g, const TDesc *single, hipStream_t s);
+void launch_small(const Workspace &w, const GroupParams &g, const TDesc *single, bool once, hipStream_t s);
 void launch_finalize(const Workspace &w, const GroupParams &g, bool decode, hipStream_t s);
 void launch_decode_prep(const Workspace &w, u32 ntensors, u32 ntiles, u32 largest, bool allow_raw, bool moments, bool records, const DDesc *single, hipStream_t s);
 static inline bool excp_prep_small(u32 largest) { return largest <= 32u; }      // tiles of the largest tensor of a group that takes one launch

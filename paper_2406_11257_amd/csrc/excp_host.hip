@@ -608,8 +608,8 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
         p.fine_size = excp_fine_size(largest); p.fine_chunks = excp_cells_chunks(elems); p.largest = largest;
         p.samples = excp_samples(p.fine != 0u, largest);
         p.wide = largest >= c->wide_elems ? 2u : ((flags & 0x30u) != 0 ? 1u : 0u);
-        { StageTimer t(c, ST_LAYOUT); }                      // (made inside the mask scan and k_small_front: the span, one a group, is empty)
-        // The small tensors: two launches, beside the larger ones on the context's own stream.  (They depend on nothing but what was
+        { StageTimer t(c, ST_LAYOUT); }                      // (made inside the mask scan and the kernels for small tensors: the span, one a group, is empty)
+        // The small tensors: one launch or two (excp_small_once), beside the larger ones on the context's own stream.  (They depend on nothing but what was
         // enqueued before this group; the 14M shape has 50 of them among 76: 535 -> 526 us; the 410M shape 194 among 292: 5337 -> 5027.
         // They are enqueued when the larger ones have something to do for a while: calls of the runtime take time too.)
         const u32 nsmall = g.count - nbig;
@@ -623,7 +623,7 @@ int excp_compress_tensors(excp_ctx *c, int count, const excp_tensor *tensors, fl
             const hipStream_t to = nbig ? c->side.stream : s;
             if (nbig) (void)hipStreamWaitEvent(c->side.stream, c->side.fork, 0);
             StageTimer t(c, ST_MISC, to);
-            ::launch_small(ws, ps, single ? descs.h : nullptr, to);
+            ::launch_small(ws, ps, single ? descs.h : nullptr, excp_small_once(descs.h + g.first + nbig, nsmall, (u32)w.cus, w16 ? 2u : 4u), to);
         };
         if (!nbig) { launch_small(); continue; }
         { StageTimer t(c, ST_SAMPLE); launch_stats(w, p, 0, single ? descs.h : nullptr, s); }

@@ -238,10 +238,12 @@ __device__ __forceinline__ void small_compact(const FrontShared &F, const u64 (&
         if (__builtin_amdgcn_inverse_ballot_w64(words[j])) to[(F.at[j * SM_WAVES + wave] >> shift & 0xffffu) + lanes_below(words[j])] = x[j];
 }
 
-__global__ __launch_bounds__(SM) void k_small_front(Workspace w, GroupParams g) {
+// `single`: the only tensor's description comes as an argument and is left where k_small_codes looks for it.
+__global__ __launch_bounds__(SM) void k_small_front(Workspace w, GroupParams g, TDesc one, u32 single) {
     __shared__ FrontShared F;
     const u32 t = blockIdx.x;
-    const SmallTensor D = small_tensor(w.desc[t]);
+    if (single && threadIdx.x == 0) w.desc[0] = one;
+    const SmallTensor D = single ? small_tensor(one) : small_tensor(w.desc[t]);
     FrontValues X;
     small_front(D, g, F, X);
     const SmallLayout s = small_layout(F, D, g);
@@ -639,7 +641,8 @@ __global__ __launch_bounds__(SM) void k_small_codes(Workspace w, GroupParams g) 
 }
 
 // Both in one launch, where there are no more streams than compute units: a workgroup a stream, each of which finds out about the
-// whole tensor for itself.  (A norm vector of 4096 elements: 14.7 and 28.1 us with what lies between them in two launches, 42 in one, 39
+// whole tensor for itself.  The three of a tensor run in any order, so nothing that one writes is read by another: sections of the blob are each
+// its own, and W_hat lies apart from all inputs (excp_small_once sees to it).  (A norm vector of 4096 elements: 14.7 and 28.1 us with what lies between them in two launches, 42 in one, 39
 // with the iterations' exchange through registers; the call 60.9 -> 57.0.)
 template <bool ONE_WAVE>
 __global__ __launch_bounds__(SM) void k_small_whole(Workspace w, GroupParams g, TDesc one, u32 single) {
@@ -672,14 +675,14 @@ __global__ __launch_bounds__(SM) void k_small_whole(Workspace w, GroupParams g, 
 
 }  // namespace
 
-void launch_small(const Workspace &w, const GroupParams &g, const TDesc *single, hipStream_t s) {
+void launch_small(const Workspace &w, const GroupParams &g, const TDesc *single, bool once, hipStream_t s) {
     const bool few = g.K <= 63;
-    if (3u * g.ntensors <= (u32)w.cus) {
+    if (once) {
         if (few) hipLaunchKernelGGL(k_small_whole<true>, dim3(3u * g.ntensors), dim3(SM), 0, s, w, g, single ? *single : TDesc{}, single ? 1u : 0u);
         else hipLaunchKernelGGL(k_small_whole<false>, dim3(3u * g.ntensors), dim3(SM), 0, s, w, g, single ? *single : TDesc{}, single ? 1u : 0u);
         return;
     }
-    hipLaunchKernelGGL(k_small_front, dim3(g.ntensors), dim3(SM), 0, s, w, g);
+    hipLaunchKernelGGL(k_small_front, dim3(g.ntensors), dim3(SM), 0, s, w, g, single ? *single : TDesc{}, single ? 1u : 0u);
     if (few) hipLaunchKernelGGL(k_small_codes<true>, dim3(3u * g.ntensors), dim3(SM), 0, s, w, g);
     else hipLaunchKernelGGL(k_small_codes<false>, dim3(3u * g.ntensors), dim3(SM), 0, s, w, g);
 }

@@ -52,6 +52,39 @@ int main() {
                     CHECK(unit >= least && units >= streams && units <= excp_lloyd_grid(at_once, slots), "%llu units, %u slots, shape %u", units, slots, shape);
                     CHECK(units <= (2 * streams <= at_once ? at_once : 2u * streams), "%llu units, %u streams, %u at once", units, streams, at_once);
                 }
+    // Small tensors in one launch: only where no W_hat lies over anything that the launch reads, by an interval test of every pair.
+    u32 both[2] = {0, 0};
+    for (u32 weight_bytes : {2u, 4u})
+        for (u32 shape = 0; shape < 4000; ++shape) {
+            static TDesc d[90];
+            const u32 count = shape % 3u == 0u ? 1u : 1u + random() % 88u, cus = random() % 8u ? 256u : 80u;
+            const u32 mode = shape / 3u % 5u;             // apart, in place, over W_t, in place for one, anywhere
+            const uintptr_t base = 1ull << 40, step = 8192 * 4;
+            for (u32 q = 0; q < count; ++q) {
+                TDesc &D = d[q];
+                D = TDesc{};
+                D.n = random() % 16u ? 1u + random() % 8192u : 0u;
+                auto place = [&](u32 i) { return (float *)(base + (5u * q + i) * step); };        // (arrays of all kinds side by side)
+                D.Wp = place(0); D.W = place(1); D.m = place(2); D.v = place(3); D.W_out = place(4);
+                if (mode == 1u || (mode == 3u && q == count / 2u)) D.W_out = (float *)D.Wp;
+                if (mode == 2u) D.W_out = (float *)D.W;
+                if (mode == 4u) D.W_out = (float *)(base + random() % (5u * count * step) / 2u * 2u);
+                if (random() % 4u == 0u) D.W_out = nullptr;
+            }
+            bool apart = true;
+            for (u32 q = 0; q < count; ++q)
+                for (u32 r = 0; r < count && d[q].W_out; ++r) {
+                    const void *in[4] = {d[r].Wp, d[r].W, d[r].m, d[r].v};
+                    for (u32 k = 0; k < 4u; ++k) {
+                        const uintptr_t a = (uintptr_t)d[q].W_out, b = (uintptr_t)in[k];
+                        if (d[q].n && d[r].n && a < b + d[r].n * (k < 2u ? weight_bytes : 4u) && b < a + d[q].n * weight_bytes) apart = false;
+                    }
+                }
+            const bool once = excp_small_once(d, count, cus, weight_bytes);
+            CHECK(once == (apart && 3u * count <= cus), "%u tensors, mode %u, %u compute units", count, mode, cus);
+            ++both[once];
+        }
+    CHECK(both[0] > 1000 && both[1] > 1000, "%u in two launches, %u in one", both[0], both[1]);
     if (fails) return 1;
     printf("ok\n");
     return 0;

@@ -110,6 +110,46 @@ def test_alone_and_over_the_previous_weights(ctx, n):
     check(ctx, [draw(n, n, "spread")], 4, 0)
 
 
+@pytest.mark.parametrize("nbits", [4, 8])           # one wave's centres, and more
+@pytest.mark.parametrize("where", ["W_prev", "W_t", "W_prev of one"])
+def test_over_their_inputs_beside_tensors_that_fill_the_gpu(where, nbits):
+    """W_hat over what a workgroup of the same tensor reads, while larger tensors hold the compute units and workgroups begin far apart: the
+    blobs and W_hat are the oracle's, and those of the larger tensors (in place too) what the call that leaves its inputs alone gives."""
+    small = [draw(4096 if i % 4 else 8192 - i, 100 * nbits + i, "spread") for i in range(40)]
+    g = torch.Generator(device="cuda").manual_seed(nbits)
+    large = []
+    for n in (18_000_001, 16_777_216, 16_777_216):
+        Wp, d, m = (torch.empty(n, device="cuda").normal_(0, s, generator=g) for s in (0.02, 1.4e-4, 5e-5))
+        large.append((Wp, Wp + d, m, torch.empty(n, device="cuda").normal_(generator=g).exp_().mul_(m).mul_(m).add_(1e-16)))
+    c = X.Context(18_000_001, 60_000_000)
+    refs = [O.compress_step(*t, 5e-5, 2.0, nbits, 4) for t in small]
+    wants = [O.decompress_step(t[0], r.blob)[0] for t, r in zip(small, refs)]
+
+    def go(over):
+        """The call with W_hat in arrays of its own, or over its inputs: blobs and W_hat of all tensors."""
+        items = []
+        for i, t in enumerate([tuple(torch.from_numpy(a).cuda() for a in t) for t in small] + [tuple(a.clone() for a in t) for t in large]):
+            out = torch.zeros_like(t[0])
+            if over and (where != "W_prev of one" or i in (20, 41)):
+                out = t[1] if where == "W_t" else t[0]
+            items.append((*t, torch.zeros(X.excp_blob_bound(t[0].numel(), nbits), dtype=torch.uint8, device="cuda"), out))
+        items = items[:13] + items[40:42] + items[13:40] + items[42:]          # (small ones between the large ones)
+        c.excp_compress_tensors(items, 5e-5, 2.0, nbits, 4)
+        rc, stats = c.excp_collect(check=False)
+        assert rc == 0
+        at = list(range(13)) + list(range(15, 42)) + [13, 14, 42]              # the order they were made in
+        return [(items[i][4][:stats[i].blob_bytes], items[i][5], stats[i]) for i in at]
+
+    apart, over = go(False), go(True)
+    for got in (apart, over):
+        for (blob, out, st), ref, want in zip(got, refs, wants):
+            assert (st.n_w, st.n_o) == (ref.n_w, ref.n_o) and blob.cpu().numpy().tobytes() == ref.blob
+            assert out.cpu().numpy().tobytes() == want.tobytes()
+    for a, b in zip(apart[40:], over[40:]):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1].view(torch.int32), b[1].view(torch.int32))
+    c.close()
+
+
 def test_small_tensors_beside_a_larger_one(ctx):
     """The larger one takes the general kernels, the others their own on the context's second stream: timed there, in one span."""
     cases = [draw(n, n, "spread") for n in (100, 8192, 8193)]
