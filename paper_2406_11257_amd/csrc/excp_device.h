@@ -234,10 +234,13 @@ static __host__ __device__ inline u32 excp_cand_first(u32 workgroup, u32 lists) 
 // Workgroups of the statistics pass, each with a run of tiles: eight to a compute unit at least, and so many more, up to
 // EXCP_STATS_PER_CU, that a run is about six tiles.  Short runs lie close together at any time, as memory likes it (8, 16, 32, 64 to
 // a compute unit: 410M shape 854, 842, 832, 823 us, its weights in bf16 485, 477, 470, 461, four layers of the 7B shape 2314, 2300, 2310,
-// 2245), but a run that ends asks for places in its tensor's candidate lists (16.8 M elements 41, 43, 66, 125).
-static inline u32 excp_stats_grid(u32 ntiles, u32 cus) {
-    const u32 runs = ntiles / 6u, least = 8u * cus, most = EXCP_STATS_PER_CU * cus;
-    return runs < least ? least : (runs > most ? most : runs);
+// 2245), but a run that ends asks for places in its tensor's candidate lists and leaves a record to add up (16.8 M elements 41, 43, 66,
+// 125), so beyond eight to a compute unit the largest tensor has runs of 24 tiles at least (with k_stats_finish, one of 100 M elements 223, 227, 227,
+// 228, 150 M 332, 336, 336, 337, 400 M 886, 871, 874, 883).
+static inline u32 excp_stats_grid(u32 ntiles, u64 largest, u32 cus) {
+    const u64 least = 8ull * cus, tiles = std::max<u64>((largest + EXCP_TILE - 1u) / EXCP_TILE, 1u);      // (of the largest)
+    const u64 most = std::min<u64>((u64)EXCP_STATS_PER_CU * cus, std::max(least, tiles / 24u) * ntiles / tiles);
+    return (u32)std::max(least, std::min<u64>(ntiles / 6u, most));
 }
 
 // Sub-tiles to a batch of the gather pass: as many as leave four batches to a compute unit, four at least, so that each of a

@@ -716,7 +716,7 @@ void launch_zero_u32(u32 *p, u64 count, hipStream_t s) {
 void launch_stats(const Workspace &w, const GroupParams &g, int phase, const TDesc *single, hipStream_t s) {
     if (!g.ntensors) return;
     const dim3 block(EXCP_THREADS);
-    const dim3 stream_grid(excp_stats_grid(g.ntiles, (u32)w.cus));
+    const dim3 stream_grid(excp_stats_grid(g.ntiles, g.largest, (u32)w.cus));
     switch (phase) {
         case 0:
             hipLaunchKernelGGL(k_median_sample, dim3(g.ntensors * EXCP_SAMPLE_PARTS), block, 0, s, w, g, single ? *single : TDesc{}, single ? 1u : 0u);

@@ -30,6 +30,16 @@ int main() {
         for (u32 j = 0; j < lists; ++j) { least = first[j] < least ? first[j] : least; most = first[j] > most ? first[j] : most; }
         CHECK(least == 64 && most == 64, "%u lists: %u to %u", lists, least, most);
     }
+    // The runs of the statistics pass: within the records that the workspace has, and of the largest tensor no more than it gains from.
+    for (u32 cus : {80u, 256u, 304u})
+        for (u64 largest : {1ull, 9000ull, 16777216ull, 100000000ull, 400000000ull, 2147479552ull})
+            for (u64 others : {0ull, 1ull, 9000ull, 16777216ull, 1000000000ull, 20000000000ull}) {
+                const u32 tiles = (u32)((largest + EXCP_TILE - 1) / EXCP_TILE), all = tiles + (u32)(others / EXCP_TILE);
+                const u64 runs = excp_stats_grid(all, largest, cus);
+                CHECK(runs >= 8u * cus && runs <= EXCP_STATS_PER_CU * cus, "%llu runs", runs);
+                CHECK(runs * tiles / all <= (tiles / 24u > 8u * cus ? tiles / 24u : 8u * cus), "%llu runs, %u of %u tiles", runs, tiles, all);
+                if (others >= 16u * largest && all / 6u >= EXCP_STATS_PER_CU * cus) CHECK(runs == EXCP_STATS_PER_CU * cus, "%llu runs", runs);
+            }
     // The units of a Lloyd iteration: never more than the launch has workgroups, and one round of them for few streams.
     u64 seed = 1;
     auto random = [&]() { seed = seed * 6364136223846793005ull + 1442695040888963407ull; return (u32)(seed >> 33); };
