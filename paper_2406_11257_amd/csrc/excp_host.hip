@@ -242,7 +242,7 @@ int run_dense(excp_ctx *c, int count, bool exporting, Fill fill) {
 
 // ---- Alg. 2 for one tensor without any allocation -------------------------------------------------
 // Everything the decoders keep between their kernels -- the descriptor and state of the tensor, its
-// two-entry tile table, the per-tile survivor counts of both bitmaps, the scan's part totals, the
+// two-entry tile table, the per-tile survivor counts of both bitmaps, the sums of their runs, the
 // result record -- lives in one file-scope device array instead of a context's workspace.  Every GPU
 // has its own copy of the array at its own address: the address is asked for once per device and kept.
 constexpr u64 kStaticMaxTiles = EXCP_STATIC_MAX_ELEMS / EXCP_TILE;

@@ -219,10 +219,9 @@ __device__ __forceinline__ u32 bit_pos(u32 mag) { const u32 e = mag >> 23; retur
 // |b - x| < |x - a| in the rule's arithmetic; smaller ones do not, larger ones do.  Where C[k-1] equals
 // C[k] the lowest index of the run takes everything, so reaching k means reaching the first index after
 // the run.  The border lies next to the midpoint: a bracket of five keys around it is probed first, and
-// the bisection goes on from what the probes have proved.  Threads 1..K-1 of the workgroup each find one;
-// entries from K up to 255 are set to 0xffffffff.  C and cut are LDS arrays of 256 entries; the caller
-// synchronises before and after.
-// The cut key between two centres ca < cb.
+// the bisection goes on from what the probes have proved.
+//
+// The cut key between two neighbours ca < cb.  (Strictly: of equal ones cut_key finds the end of the run first.)
 __device__ __forceinline__ u32 cut_between(float ca, float cb) {
     const double a = (double)ca, b = (double)cb;
     auto reaches = [&](u32 key) { const double x = (double)val_of(key); return fabs(b - x) < fabs(x - a); };
@@ -242,11 +241,14 @@ __device__ __forceinline__ u32 cut_between(float ca, float cb) {
     }
     return hi;
 }
+// cut[k] of K centres in ascending order, equal ones among them.
 __device__ __forceinline__ u32 cut_key(const float *C, u32 K, u32 k) {
     u32 j = k;
     while (j < K && !(C[j - 1u] < C[j])) ++j;
     return j < K ? cut_between(C[j - 1u], C[j]) : 0xffffffffu;
 }
+// All of them: threads 1..K-1 of the workgroup each find one; entries from K up to 255 are set to 0xffffffff.  C and cut are LDS
+// arrays of 256 entries; the caller synchronises before and after.
 __device__ __forceinline__ void compute_cut_keys(const float *C, int K, u32 *cut) {
     const u32 k = threadIdx.x;
     if (k == 0 || k > 255u) return;

@@ -102,8 +102,8 @@ __device__ __forceinline__ void decode_record(const Workspace &w, u32 t, u64 n, 
 
 // All that has to be known before the main pass, for groups of tensors of at most PREP_TILES tiles each, in one
 // launch: a workgroup per tensor parses the header, counts, and scans the counts.  Small tensors are bound by the
-// number of launches: parsing, counting and scanning are five (eight with the moments), of 2 to 4 us each and
-// as much again between them (a restore of 65 536 elements 66-75 -> 55 us).  Four tiles to a wave, so that a tensor is
+// number of launches: parsing, counting and scanning are three (five with the moments), of 2 to 4 us each and
+// as much again between them (a restore of 65 536 elements 66-75 -> 55 us when they were five and eight).  Four tiles to a wave, so that a tensor is
 // one round of loads; larger tensors would leave the one workgroup behind the general path's many.
 constexpr u32 PREP_WAVES = 8, PREP_TILES = 4 * PREP_WAVES;
 

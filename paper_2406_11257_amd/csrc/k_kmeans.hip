@@ -1123,7 +1123,7 @@ __global__ __launch_bounds__(INIT_THREADS) void k_km_init(Workspace w, GroupPara
 // iteration 8 us, a launch 14).  The host launches the iterations of the second way wherever a tensor is too large for
 // excp_lloyd_small; where no stream takes it they are empty.  (2^17 elements: one workgroup needs 0.43 ms for 130 000 residuals
 // of a sign-like update, the former work lists needed 0.81; 2^22 for three centres, of whose borders a bucket holds two at most.)
-//   Without cells (excp_fine_group), up to 85 tensors on 256 compute units go together, the line at 24 576.  (One tensor, ten
+//   Without cells (excp_cells_group), up to 85 tensors on 256 compute units go together, the line at 24 576.  (One tensor, ten
 //   iterations, us alone / shared: 4 bits, 500 000 elements 152 / 181, 1.5 M 174 / 190, 2.5 M 194 / 178, 10 M 343 / 172; 8 bits,
 //   300 000 elements 834 / 750, 1 M 1056 / 227, 10 M 4020 / 222.)
 //   More tensors fill the GPU as they are, one workgroup a stream, and the line lies at 196 608 (4 bits: 300 tensors of 600 000

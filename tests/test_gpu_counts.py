@@ -1,5 +1,5 @@
-"""Counts and scans of the restores where they are cut: a tensor of more tiles than a workgroup scans (4096) behind ragged ones,
-tensors of one tile side by side, and chains of more checkpoints than a group has tensors, with the last one's moments."""
+"""Counts and scans of the restores where they are cut: a tensor of more tiles than a workgroup scans (EXCP_SCAN_TILES, 1024) behind
+ragged ones, tensors that begin and end on a multiple of that number and one tile beside it, tensors of one tile side by side, and chains of more checkpoints than a group has tensors, with the last one's moments."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("flags", [0, X.EXCP_FLAG_NO_W2M])
-@pytest.mark.parametrize("sizes", [[70_001, 4097 * 4096 + 5, 0, 1, 33 * 4096, 4096], [40 * 4096] + [1 + 37 * i for i in range(120)] + [0, 9001]])
+@pytest.mark.parametrize("sizes", [[70_001, 4097 * 4096 + 5, 0, 1, 33 * 4096, 4096], [40 * 4096] + [1 + 37 * i for i in range(120)] + [0, 9001],
+                                   [1024 * 4096, 7, 1023 * 4096, 0, 1023 * 4096 + 5, 4096, 1025 * 4096, 1023 * 4096 - 9, 1]])
 def test_restore_of_tensors_on_both_sides_of_a_run(sizes, flags):
     cases = [case(n, 300 + i) for i, n in enumerate(sizes)]
     ctx = X.Context(max(sizes), sum(sizes))
