@@ -1245,7 +1245,8 @@ void launch_decode_small(const Workspace &w, u32 ntensors, u32 ntiles, bool mome
 // The main passes take a workgroup a tile: then those at work lie side by side.  (With 64 workgroups a compute unit, each of which
 // goes on with the tile 16 384 further, as many regions are in hand as that makes rounds: weights of the 410M shape 662 instead of 650 us,
 // 24 ragged tensors with their moments 709 instead of 682, the stored layout of 333 M elements 1112 instead of 1055; with runs of
-// neighbouring tiles to a workgroup 723 and 770.)
+// neighbouring tiles to a workgroup 723 and 770.  That every tile loads the table of tiles and the codebooks anew does not take it back:
+// 1000 tensors of 200 000 elements with one-byte codes 448 instead of 404, with their moments 819 instead of 746, of 20 000 elements 125 either way.)
 void launch_decode_main(const Workspace &w, u32 ntensors, u32 ntiles, bool moments, hipStream_t s) {
     if (!ntiles) return;
     if (moments) hipLaunchKernelGGL(k_decode_main<true>, dim3(ntiles), dim3(EXCP_THREADS), 0, s, w, ntensors, ntiles);

@@ -3,7 +3,7 @@
 // with a wave or two at work.  Here a workgroup holds a whole tensor in registers (small_front: statistics, masks,
 // compaction, header), and then one holds a whole survivor stream (small_codes: initial centres, Lloyd iterations,
 // codes, and for the residuals W_hat), everything they look up in LDS.  Of few tensors a workgroup does both, for its stream.  (us a call, before and now: a norm vector of 4096
-// elements 169 / 61, 1000 of them 1524 / 348, 8 bits 3814 / 477; 1000 tensors of 8192 elements, all kept, 1924 / 876; 8192
+// elements 169 / 57 (in two launches 61), 1000 of them 1524 / 348, 8 bits 3814 / 477; 1000 tensors of 8192 elements, all kept, 1924 / 876; 8192
 // residuals of a sign-like update, 337 / 141.)
 //
 // The definitions are those of the general kernels (k_stats, k_mask, k_kmeans) and so are the bytes: exact median, exact sums
