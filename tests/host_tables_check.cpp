@@ -37,6 +37,17 @@ int main() {
                 const bool fits = n / 256 * 4 / 3 <= excp_cells_most(excp_fine_size(n)), want = n * count <= 26214400ull && (!whole || (fits && whole * n * count <= 33554432ull));
                 CHECK(excp_fine_group(n * count, n, whole) == want, "%u tensors of %llu elements, %u whole streams", count, n, whole);
             }
+    // The groups whose blobs test_gpu_cells_many.py compares set out for cells, and do not with a tensor beside them that is too large.
+    struct Sizes { std::vector<u64> n; u32 nbits; };
+    for (const Sizes &x : {Sizes{{13500001, 14600003}, 4}, Sizes{{9000001, 8500077, 11000000, 9999999}, 3}, Sizes{std::vector<u64>(5, 6000005), 6},
+                           Sizes{std::vector<u64>(12, 3000401), 8}, Sizes{{131071, 131073, 20000001, 25ull << 20}, 7}}) {
+        u64 elems = 0, largest = 0;
+        for (u64 n : x.n) { elems += n; largest = std::max(largest, n); }
+        const u32 count = (u32)x.n.size(), K = (1u << x.nbits) - 1u;
+        CHECK(elems > EXCP_FINE_LARGEST && excp_cells_group(elems, largest, count, K, 0) && !excp_cells_group(elems, largest, count, K, 3), "%u tensors, %llu elements", count, elems);
+        CHECK(!excp_cells_group(elems + 28000003, 28000003, count + 1, K, 0), "%u tensors and a larger one", count);
+        CHECK(elems / 2 <= (u64)excp_cells_chunks(elems) * EXCP_CHUNK, "half of %llu elements", elems);
+    }
     // A third of the largest tensor kept, its buckets fit the workgroups also where they are four deviations above the average.
     for (u64 n = 131072; n <= EXCP_FINE_LARGEST; n += n / 50) {
         const u32 samples = excp_samples(true, n);
